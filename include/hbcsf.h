@@ -48,9 +48,8 @@ typedef struct hbcsf_opts {
   uint32_t fiber_threshold;   /* T_f of fbr-split (Section IV-B, VI-B): no fiber segment holds more
                                  than T_f nonzeros.  Cuts fall on multiples of T_f in a group's
                                  nonzero stream.  8, 16, 32 or 64.  Default 64 (order 3), 32 (orders 4, 5),
-                                 chosen for rank 32; a wavefront keeps 64 / (rank / 4) runs in LDS at a time, so
-                                 for ranks 16 / 8 half / a quarter of the default keeps the same number of
-                                 wavefronts resident and is markedly faster.                                 */
+                                 at every rank: several lane groups share a run where shorter pieces are
+                                 faster (low ranks, small tensors).                                          */
   uint32_t slice_threshold;   /* T_s of slc-split (Section IV-A): nonzeros one wavefront works
                                  through before it merges its partial rows; a slice of n nonzeros
                                  is shared by at most ceil(n/T_s)+1 wavefronts.  0 = sized from
@@ -192,8 +191,9 @@ int hbcsf_host_array(const hbcsf_tensor *t, int mode, int group, int level, int 
                                         keep the last n calls' event sets; 0 = off              */
 #define HBCSF_TUNE_WAVES_PER_CU     2 /* wavefront spans launched per compute unit when T_s is
                                         automatic (default 128)                                 */
-#define HBCSF_TUNE_STEPS            3 /* gathers a lane group keeps in flight: 4 or 8 (default 8 for
-                                        order 3, 4 for order 4; 4 is only available at rank 32)  */
+#define HBCSF_TUNE_STEPS            3 /* gathers a lane group keeps in flight: 4 or 8 (default: 8 for long
+                                        order-3 streams, else 4); 8 is only available with runs of 64
+                                        and rows of 128 bytes, ignored elsewhere                  */
 #define HBCSF_TUNE_KERNEL_MASK      4 /* which kernels hbcsf_mttkrp launches: bit0 define, bit1 COO,
                                         bit2 CSL, bit3 CSF (default 15).  For ablation and profiling
                                         only: with bits cleared the output is incomplete.        */

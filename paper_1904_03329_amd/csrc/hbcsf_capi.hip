@@ -61,6 +61,23 @@ bool pow2_in(uint32_t v, uint32_t lo, uint32_t hi) { return v >= lo && v <= hi &
 
 uint32_t round_up8(uint64_t v) { return (uint32_t)((v + 7) / 8 * 8); }
 
+// Nonzeros a lane group takes of a unit, as a power of two: at most a run, at least what keeps a unit (NG parts) a whole
+// number of runs.  Units of 256 nonzeros keep the most wavefronts resident (4 to 5 KB of LDS records each) and were the
+// fastest at every rank from 5 M nonzeros up (rank 8 on 42 M nonzeros 1.94 -> 1.10 ms against parts of whole runs, rank
+// 16 on 7.7 M 237 -> 204 us, rank 32 on 5 M 241 -> 217 us).  Smaller tensors take 128 below 16 units per compute unit
+// and 64 below 6: a wavefront walks its part one dependent block after the other, so with the chip not full the length
+// of that walk is the kernel's time (rank 32 on 80 000 nonzeros 67 -> 43 us, rank 8 on 10 000 60 -> 38 us, all modes).
+uint32_t part_shift(uint64_t nnz, int NG, uint32_t lshift, int numCU) {
+  uint32_t lo = 3, s = 3;
+  while (((uint32_t)NG << lo) < (1u << lshift)) ++lo;
+  while (((uint32_t)NG << s) < 256) ++s;
+  const uint64_t units = nnz / ((uint64_t)NG << s);
+  if (units < 16ull * (uint64_t)numCU) --s;
+  if (units < 3ull * (uint64_t)numCU) --s;
+  if (s < lo) s = lo;
+  return s < lshift ? s : lshift;
+}
+
 // Single representation: mode-`mode` MTTKRP from mode 0's B-CSF tree, the target at tree level T >= 1.  The
 // output is zero-filled, then every level-T segment (T = leaf: every nonzero) adds its contribution atomically.
 int mttkrp_from_mode0(const hbcsf_tensor* t, int mode, int rank, const float* const* factors, float* out,
@@ -101,6 +118,7 @@ int mttkrp_from_mode0(const hbcsf_tensor* t, int mode, int rank, const float* co
   a.nnz = (uint32_t)gf.nnz;
   a.runs = (uint32_t)gf.runs;
   a.lshift = lshift;
+  a.partShift = lshift;
   a.nUnits = (uint32_t)((gf.runs + NG - 1) / NG);
   const uint64_t target = (uint64_t)t->numCU * (t->wavesPerCU ? t->wavesPerCU : 128);
   uint64_t upw = t->sliceThreshold ? t->sliceThreshold / ((uint64_t)NG * f.L) : (a.nUnits + target - 1) / target;
@@ -157,7 +175,6 @@ int hbcsf_build_format(int order, const uint64_t* dims, uint64_t nnz, const uint
   t->nnz = nnz;
   t->opts = o;
   t->sliceThreshold = o.slice_threshold;
-  t->steps = default_steps(order);
   for (int m = 0; m < order; ++m) t->dims[m] = dims[m];
   double sq = 0.0;
   for (uint64_t z = 0; z < nnz; ++z) sq += (double)vals[z] * (double)vals[z];
@@ -268,7 +285,11 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
     return a;
   };
   bool wide = false;  // some gathered factor matrix needs 64-bit row addressing
-  for (int l = 1; l < N; ++l) wide = wide || t->dims[f.levelMode[l]] * rowBytes >= (1ull << 32);
+  // (marks address one row further on, hence the + 1); fiber levels gathered with streaming loads take the wide form too
+  for (int l = 1; l < N; ++l) {
+    const uint64_t bytes = t->dims[f.levelMode[l]] * rowBytes;
+    wide = wide || bytes + rowBytes >= (1ull << 32) || (l < N - 1 && bytes >= t->streamBytes);
+  }
 
   // 1. define every output row that no plain store will write; the COO group's rows are written
   //    in the same pass
@@ -305,69 +326,78 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
   if (es) (void)hipEventRecord(es->ev[1], s);
 
   // 2. the three group kernels (execute step of Algorithm "HB-CSF-MTTKRP")
+  const uint64_t sparseNnz = f.g[kCsl].nnz + f.g[kCsf].nnz;
+  const bool runCsl = f.g[kCsl].nnz > 0 && (t->kernelMask & 4u), runCsf = f.g[kCsf].nnz > 0 && (t->kernelMask & 8u);
+  const bool dense = t->denseMid == 1 && dense_mid_available(N, G, lshift);
+  // 8 gathers in flight with parts of whole 64-nonzero runs: four wavefronts per SIMD instead of five, but half the
+  // staging per nonzero.  Pays at order 3 with rows of 128 bytes, narrow factor matrices and a stream that fills the chip
+  // many times over (100 M nonzeros 2.32 -> 2.25 ms, 56 M 1.15 -> 1.08 ms; 40 M and fewer equal, 5 M 5 % slower).
+  const bool longParts = G == 8 && lshift == 6 && (t->steps == 8 || (t->steps == 0 && N == 3 && !wide && sparseNnz >= 40000000));
+  // CSL and B-CSF group in one launch, unless their times are asked for one by one (or the kernel with 8 gathers
+  // is used: with both bodies in it, it no longer fits four wavefronts per SIMD)
+  const bool together = runCsl && runCsf && !es && !dense && !longParts && !t->persistent;
+  auto sparse_args = [&](int g, uint32_t part) {
+    const GroupFormat& gf = f.g[g];
+    GroupArgs a = group_args(g);
+    a.val = (const float*)(base + gf.val.off);
+    a.out = out;
+    a.nnz = (uint32_t)gf.nnz;
+    a.runs = (uint32_t)gf.runs;
+    a.lshift = lshift;
+    a.trace = t->trace;
+    a.traceCapacity = (uint32_t)t->traceCapacity;
+    // B-CSF tuning variant: the fiber-level rows gathered densely through an LDS row cache (off by default:
+    // it lowered the vector-memory instruction count as intended but lengthened every block's dependent chain
+    // and measured 40-100 % slower on the benchmark tensors)
+    a.denseMid = g == kCsf && dense ? 1u : 0u;
+    a.partShift = part;
+    const uint64_t unitNnz = (uint64_t)NG << part;
+    a.nUnits = (uint32_t)((gf.nnz + unitNnz - 1) / unitNnz);
+    const uint64_t target = (uint64_t)t->numCU * (t->wavesPerCU ? t->wavesPerCU : 128);
+    uint64_t upw = t->sliceThreshold ? t->sliceThreshold / unitNnz : (a.nUnits + target - 1) / target;
+    if (upw == 0) upw = 1;
+    a.unitsPerWave = (uint32_t)upw;
+    a.nSpans = (uint32_t)((a.nUnits + upw - 1) / upw);
+    a.persistent = t->persistent ? 1u : 0u;
+    if (g == kCsf)
+      for (int l = 1; l < N - 1; ++l)
+        if (t->dims[f.levelMode[l]] * rowBytes >= t->streamBytes) a.streamLevel |= 1u << l;
+    return a;
+  };
   for (int g = 0; g < 3; ++g) {
     const GroupFormat& gf = f.g[g];
     bool launched = false;
-    if (gf.nnz > 0 && (t->kernelMask & (2u << g)) && !(g == kCoo && (fuseCoo || f.cooRowFlags))) {
-      GroupArgs a = group_args(g);
-      a.val = (const float*)(base + gf.val.off);
-      a.out = out;
-      a.nnz = (uint32_t)gf.nnz;
-      a.runs = (uint32_t)gf.runs;
-      a.lshift = lshift;
-      a.nUnits = (uint32_t)((gf.runs + NG - 1) / NG);
-      a.trace = t->trace;
-      a.traceCapacity = (uint32_t)t->traceCapacity;
-      uint32_t blocks, threads;
-      size_t lds = 0;
-      if (g == kCoo) {
-        threads = 256;
+    if (g == kCoo) {
+      if (gf.nnz > 0 && (t->kernelMask & 2u) && !fuseCoo && !f.cooRowFlags) {
+        GroupArgs a = group_args(g);
+        a.val = (const float*)(base + gf.val.off);
+        a.out = out;
+        a.nnz = (uint32_t)gf.nnz;
         const uint64_t perBlock = 64 * 4;  // 64 nonzeros per wavefront and iteration
         uint64_t b = (gf.nnz + perBlock - 1) / perBlock;
         const uint64_t cap = (uint64_t)t->numCU * 16;
         if (b > cap) b = cap;
-        blocks = round_up8(b);
-        a.unitsPerWave = 0;
-      } else {
-        int RW = N == 3 ? 4 : 8;  // LDS words per nonzero record
-        size_t ldsWave = (size_t)NG * (L + 1) * RW * 4;
-        // B-CSF tuning variant: the fiber-level rows gathered densely through an LDS row cache (off by default:
-        // it lowered the vector-memory instruction count as intended but lengthened every block's dependent chain
-        // and measured 40-100 % slower on the benchmark tensors)
-        a.denseMid = 0;
-        if (g == kCsf && t->denseMid == 1 && dense_mid_available(N, G, lshift)) {
-          a.denseMid = 1;
-          ldsWave += dense_mid_lds_bytes(G);
-        } else if (g == kCsf && N == 4) {
-          // the order-4 B-CSF kernel packs a record into 4 words and keeps the slices' rows in a list of NG * L words
-          RW = 4;
-          ldsWave = (size_t)NG * (L + 1) * RW * 4 + (size_t)NG * L * 4;
-        }
-        int wpb = 4;
-        while (wpb > 1 && ldsWave * wpb > 48 * 1024) wpb >>= 1;
-        threads = 64 * wpb;
-        lds = ldsWave * wpb;
-        uint64_t upw;
-        if (t->sliceThreshold) {
-          upw = t->sliceThreshold / ((uint64_t)NG * L);
-        } else {
-          const uint64_t target = (uint64_t)t->numCU * (t->wavesPerCU ? t->wavesPerCU : 128);
-          upw = (a.nUnits + target - 1) / target;
-        }
-        if (upw == 0) upw = 1;
-        a.unitsPerWave = (uint32_t)upw;
-        a.nSpans = (uint32_t)((a.nUnits + upw - 1) / upw);
-        a.persistent = t->persistent ? 1u : 0u;
-        a.streamLevel = 0;
-        if (g == kCsf)
-          for (int l = 1; l < N - 1; ++l)
-            if (t->dims[f.levelMode[l]] * rowBytes >= t->streamBytes) a.streamLevel |= 1u << l;
-        blocks = (uint32_t)t->numCU;  // the launcher sizes the grid
+        e = launch_group(f64, g, N, G, wide, a, nullptr, round_up8(b), 256, 0, s);
+        launched = true;
       }
-      e = launch_group(f64, g, N, G, t->steps, wide, a, blocks, threads, lds, s);
-      if (e != hipSuccess) return fail_hip(e, "launch of a group kernel");
+    } else if (g == kCsl ? runCsl && !together : runCsf) {
+      const uint32_t part = g == kCsf && dense ? lshift
+                            : longParts ? 6u
+                                        : part_shift(together ? sparseNnz : gf.nnz, NG, lshift, t->numCU);
+      const GroupArgs a = sparse_args(g, part);
+      GroupArgs csl;
+      if (together) csl = sparse_args(kCsl, part);
+      uint32_t words = g == kCsf ? csf_wave_words(N, G, (int)part, a.denseMid != 0) : 0u;
+      if (g == kCsl || together) words = words > csl_wave_words(N, G, (int)part) ? words : csl_wave_words(N, G, (int)part);
+      const size_t ldsWave = 4 * (size_t)words;
+      int wpb = 4;
+      while (wpb > 1 && ldsWave * wpb > 48 * 1024) wpb >>= 1;
+      // the launcher sizes the grid
+      e = launch_group(f64, g, N, G, wide, a, together ? &csl : nullptr, (uint32_t)t->numCU, 64 * wpb,
+                       ldsWave * wpb, s);
       launched = true;
     }
+    if (launched && e != hipSuccess) return fail_hip(e, "launch of a group kernel");
     if (es) {
       es->launched[1 + g] = launched;
       (void)hipEventRecord(es->ev[2 + g], s);

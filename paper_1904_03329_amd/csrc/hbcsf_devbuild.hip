@@ -885,7 +885,6 @@ int hbcsf_build_format_device(int order, const uint64_t* dims, uint64_t nnz, con
   t->nnz = nnz;
   t->opts = o;
   t->sliceThreshold = o.slice_threshold;
-  t->steps = default_steps(order);
   for (int m = 0; m < order; ++m) t->dims[m] = dims[m];
   int dev = 0, cu = 0;
   HIP_TRY(hipGetDevice(&dev), "hipGetDevice");

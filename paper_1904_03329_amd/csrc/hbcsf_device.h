@@ -10,12 +10,25 @@ namespace hbcsf {
 enum KernelKind { kCooKernel = 0, kCslKernel = 1, kCsfKernel = 2 };
 
 // The B-CSF kernel's dense fiber-row gather: rows its per-wavefront LDS cache holds, the instantiations that
-// exist (rank 32, orders 3 and 4, runs of 32 or 64 nonzeros), and the LDS bytes it adds per wavefront.
+// exist (rank 32, orders 3 and 4, runs of 32 or 64 nonzeros).
 constexpr int kDenseCacheRows = 32;
 inline bool dense_mid_available(int order, int G, uint32_t lshift) {
   return G == 8 && (order == 3 || order == 4) && (lshift == 5 || lshift == 6);
 }
-inline size_t dense_mid_lds_bytes(int G) { return 256 + (size_t)kDenseCacheRows * 16 * (size_t)G; }
+
+// LDS words a wavefront of the B-CSF / CSL kernel uses: one record per nonzero of a unit (64 / G parts of 2^ss nonzeros,
+// one pad record per part), one row slot per lane (the first finished slice of each part), and for the order-4 B-CSF
+// kernel the list of the unit's slices with each part's place in it.
+constexpr uint32_t csf_wave_words(int order, int G, int ss, bool dense) {
+  const uint32_t parts = 64u / (uint32_t)G, slots = parts << ss;
+  const bool pack = order == 4 && !dense;
+  return (slots + parts) * (order == 3 || pack ? 4u : 8u) + 256u + (pack ? slots + (parts < 4u ? 4u : parts) : 0u) +
+         (dense ? 64u + (uint32_t)kDenseCacheRows * 4u * (uint32_t)G : 0u);
+}
+constexpr uint32_t csl_wave_words(int order, int G, int ss) {
+  const uint32_t parts = 64u / (uint32_t)G, slots = parts << ss;
+  return (slots + parts) * (order == 3 ? 4u : 8u) + 256u;
+}
 
 // Device pointers of one slice group of one mode, by tree level (0 = root .. order-1 = leaf).
 struct GroupArgs {
@@ -28,7 +41,8 @@ struct GroupArgs {
   uint32_t nnz;                 // nonzeros in the group
   uint32_t runs;                // ceil(nnz / L)
   uint32_t lshift;              // log2 L
-  uint32_t nUnits;              // ceil(runs / lane groups per wavefront)
+  uint32_t partShift;           // log2 of the nonzeros a lane group takes of a unit (<= lshift)
+  uint32_t nUnits;              // ceil(nnz / (lane groups per wavefront << partShift))
   uint32_t unitsPerWave;        // consecutive units in one span
   uint32_t nSpans;              // ceil(nUnits / unitsPerWave)
   uint32_t streamLevel;         // bit l: the factor rows of fiber level l are gathered with streaming loads
@@ -44,13 +58,13 @@ struct GroupArgs {
 
 // kind: KernelKind; order 3, 4 or 5; G = row bytes / 16 lanes per factor row (fp32: rank / 4 = 2, 4, 8, 16 or 32;
 // fp64: rank / 2 = 8, 16 or 32, the launch functions named ...64...);
-// steps = records a lane group keeps in flight (4 or 8); wide = some gathered factor matrix
+// csl = null, or with kind = kCsfKernel the CSL group's arguments: both groups in one launch (same part size); wide = some gathered factor matrix
 // is 4 GiB or larger (64-bit row addressing).  One launch function per (G, order) pair, each
 // compiled in its own object file.  For the CSL and B-CSF kernels `blocks` is the number of compute
 // units and the launcher sizes the grid (one wavefront per span, or persistent).
 #define HBCSF_DECLARE_LAUNCH(G, N)                                                                  \
-  hipError_t launch_group_g##G##_n##N(int kind, int steps, bool wide, const GroupArgs& a,          \
-                                      uint32_t blocks, uint32_t threads, size_t ldsBytes, hipStream_t s); \
+  hipError_t launch_group_g##G##_n##N(int kind, bool wide, const GroupArgs& a,          \
+                                      const GroupArgs* csl, uint32_t blocks, uint32_t threads, size_t ldsBytes, hipStream_t s); \
   hipError_t launch_define_coo_g##G##_n##N(bool wide, const GroupArgs& a, const uint32_t* ownedBits,   \
                                            const uint32_t* cooBits, const uint32_t* cooPtr, uint64_t rows, \
                                            uint32_t blocks, hipStream_t s);
@@ -71,8 +85,8 @@ HBCSF_DECLARE_LAUNCH(16, 5)
 HBCSF_DECLARE_LAUNCH(32, 5)
 #undef HBCSF_DECLARE_LAUNCH
 #define HBCSF_DECLARE_LAUNCH64(G, N)                                                                  \
-  hipError_t launch_group64_g##G##_n##N(int kind, int steps, bool wide, const GroupArgs& a,          \
-                                        uint32_t blocks, uint32_t threads, size_t ldsBytes, hipStream_t s); \
+  hipError_t launch_group64_g##G##_n##N(int kind, bool wide, const GroupArgs& a,          \
+                                        const GroupArgs* csl, uint32_t blocks, uint32_t threads, size_t ldsBytes, hipStream_t s); \
   hipError_t launch_define_coo64_g##G##_n##N(bool wide, const GroupArgs& a, const uint32_t* ownedBits,   \
                                              const uint32_t* cooBits, const uint32_t* cooPtr, uint64_t rows, \
                                              uint32_t blocks, hipStream_t s);
@@ -88,13 +102,13 @@ HBCSF_DECLARE_LAUNCH64(32, 5)
 #undef HBCSF_DECLARE_LAUNCH64
 
 // f64: the factor matrices and the output hold doubles (GroupArgs' float pointers then address doubles).
-inline hipError_t launch_group(bool f64, int kind, int order, int G, int steps, bool wide, const GroupArgs& a,
-                               uint32_t blocks, uint32_t threads, size_t ldsBytes, hipStream_t s) {
+inline hipError_t launch_group(bool f64, int kind, int order, int G, bool wide, const GroupArgs& a,
+                               const GroupArgs* csl, uint32_t blocks, uint32_t threads, size_t ldsBytes, hipStream_t s) {
 #define HBCSF_CASE64(GV)                                                                              \
   case GV:                                                                                            \
-    return order == 3   ? launch_group64_g##GV##_n3(kind, steps, wide, a, blocks, threads, ldsBytes, s) \
-           : order == 4 ? launch_group64_g##GV##_n4(kind, steps, wide, a, blocks, threads, ldsBytes, s) \
-                        : launch_group64_g##GV##_n5(kind, steps, wide, a, blocks, threads, ldsBytes, s);
+    return order == 3   ? launch_group64_g##GV##_n3(kind, wide, a, csl, blocks, threads, ldsBytes, s) \
+           : order == 4 ? launch_group64_g##GV##_n4(kind, wide, a, csl, blocks, threads, ldsBytes, s) \
+                        : launch_group64_g##GV##_n5(kind, wide, a, csl, blocks, threads, ldsBytes, s);
   if (f64) {
     switch (G) {
       HBCSF_CASE64(8)
@@ -107,9 +121,9 @@ inline hipError_t launch_group(bool f64, int kind, int order, int G, int steps, 
 #undef HBCSF_CASE64
 #define HBCSF_CASE(GV)                                                                              \
   case GV:                                                                                          \
-    return order == 3   ? launch_group_g##GV##_n3(kind, steps, wide, a, blocks, threads, ldsBytes, s) \
-           : order == 4 ? launch_group_g##GV##_n4(kind, steps, wide, a, blocks, threads, ldsBytes, s) \
-                        : launch_group_g##GV##_n5(kind, steps, wide, a, blocks, threads, ldsBytes, s);
+    return order == 3   ? launch_group_g##GV##_n3(kind, wide, a, csl, blocks, threads, ldsBytes, s) \
+           : order == 4 ? launch_group_g##GV##_n4(kind, wide, a, csl, blocks, threads, ldsBytes, s) \
+                        : launch_group_g##GV##_n5(kind, wide, a, csl, blocks, threads, ldsBytes, s);
   switch (G) {
     HBCSF_CASE(2)
     HBCSF_CASE(4)

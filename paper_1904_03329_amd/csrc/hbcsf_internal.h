@@ -159,12 +159,9 @@ inline void fill_count_stats(ModeFormat* out, int N, uint64_t M, uint64_t S,
   st.fiber_threshold = out->L;
 }
 
-// Defaults measured on MI355X.  Order 3: runs of 64 nonzeros, 8 gathers in flight per lane group (132 / 128
-// vector registers, 8 KB of LDS records per wavefront).  Order 4 records are twice as large and the kernel holds
-// two fiber-level rows per step, so the same choice leaves 8 wavefronts per CU; runs of 32 and 4 gathers in
-// flight give 16 and were 25 % faster on a 50 M-nonzero order-4 tensor.
+// Defaults measured on MI355X: runs of 64 nonzeros at order 3, of 32 at orders 4 and 5 (whose records and fiber-level
+// rows take more LDS and registers per nonzero in flight).
 inline uint32_t default_fiber_threshold(int order) { return order >= 4 ? 32u : 64u; }
-inline int default_steps(int order) { return order >= 4 ? 4 : 8; }
 
 // Tree levels of a mode's representation: the root is the mode itself, the others follow the policy
 // (0: shortest mode first, 1: longest first, 2: natural order).

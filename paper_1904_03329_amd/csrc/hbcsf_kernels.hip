@@ -4,11 +4,11 @@
 // each, so a wavefront has NG = 64/G lane groups and a row gather is one 16-byte load per
 // lane.  (Built with HBCSF_F64 the factor matrices, the partial sums and the output are fp64: a lane
 // then holds two doubles, R = 2G, and every address computation stays the same; the tensor's
-// values are stored as fp32 either way and widened where they are multiplied.)  The nonzero stream of a group is cut into runs of L nonzeros (L = fiber threshold);
-// a lane group walks one run sequentially with its partial sums in registers, so every lane
-// group has exactly the same amount of work whatever the slice and fiber lengths are.  A
-// unit is NG consecutive runs (one per lane group); a wavefront works through a contiguous
-// span of units.
+// values are stored as fp32 either way and widened where they are multiplied.)  The nonzero stream of a group is
+// cut into runs of L nonzeros (L = fiber threshold).  A unit is NG parts of P <= L nonzeros (a whole number of
+// runs), one per lane group; a lane group walks its part sequentially with its partial sums in
+// registers, so every lane group has exactly the same amount of work whatever the slice and fiber
+// lengths are.  A wavefront works through a contiguous span of units.
 //
 // B-CSF kernel (Algorithm "CSF-MTTKRP" with fbr-split / slc-split, Sections III-B and IV):
 // per unit the wavefront loads the leaf indices and values coalesced into LDS records and
@@ -16,9 +16,10 @@
 // = fiber segment / slice, one LDS write each).  The inner loop then reads one 16-byte
 // record per nonzero: tmp += v*C(k,:); at a segment end acc += tmp*B(j,:) (Eq. 8's factored
 // form); at a slice end the row goes out with one plain 128-byte store if the slice lies in
-// one run, else with atomic adds (Section IV-A's merge of split slices).  A partial row left
-// at the end of a run stays in registers while the following units still belong to the same
-// slice, so a heavy slice costs one atomic row per wavefront span, not one per run.
+// one run, else with atomic adds (Section IV-A's merge of split slices).  The first slice that
+// ends in a part may have begun in the parts before it: it waits until the unit is closed, when a
+// segmented sum over the lane groups completes it.  What is open at the end of a unit stays in
+// registers for the next one, so a heavy slice costs one atomic row per wavefront span.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -30,6 +31,7 @@ namespace hbcsf {
 namespace {
 
 constexpr int kDenseCache = kDenseCacheRows;  // rows of the dense variant's per-wavefront row cache
+constexpr uint32_t kOwned = 0x80000000u;      // in a slice entry or mark: the slice lies inside one run
 
 
 // A lane's 16 bytes of a row: four floats, or two doubles.
@@ -83,6 +85,20 @@ __device__ __forceinline__ rowvec row_load_streaming(const float* __restrict__ b
     p = reinterpret_cast<const vec16*>(reinterpret_cast<const char*>(base) + off);
   }
   return from_vec16(__builtin_nontemporal_load(p));
+}
+
+// A fiber level's row by its mark (index + 1): `before` = row_before(the factor matrix), so that the mark scales to an
+// offset as it is.  Streaming loads exist in the WIDE form only (the caller chooses it when it asks for them): a
+// second load instruction per step costs the common form a branch each.
+template <int G>
+__device__ __forceinline__ const float* row_before(const float* fac) {
+  return fac - 4 * G;  // kept a pointer all through: a round trip over an integer would make the loads flat ones
+}
+
+template <int G, bool WIDE>
+__device__ __forceinline__ rowvec marked_row_load(const float* before, uint32_t mark, int c, bool streaming) {
+  if (WIDE && streaming) return row_load_streaming<G, WIDE>(before, mark, c);
+  return row_load<G, WIDE>(before, mark, c);
 }
 
 template <int G>
@@ -161,6 +177,20 @@ __device__ __forceinline__ void sum_lane_groups(rowvec& a) {
 }
 #endif
 
+#ifdef HBCSF_F64
+__device__ __forceinline__ void add_row(rowvec& d, const rowvec& x) { d.x += x.x; d.y += x.y; }
+__device__ __forceinline__ rowvec shfl_up_row(const rowvec& a, int o) { return rowvec{__shfl_up(a.x, o), __shfl_up(a.y, o)}; }
+__device__ __forceinline__ rowvec shfl_row(const rowvec& a, int from) { return rowvec{__shfl(a.x, from), __shfl(a.y, from)}; }
+#else
+__device__ __forceinline__ void add_row(rowvec& d, const rowvec& x) { d.x += x.x; d.y += x.y; d.z += x.z; d.w += x.w; }
+__device__ __forceinline__ rowvec shfl_up_row(const rowvec& a, int o) {
+  return make_float4(__shfl_up(a.x, o), __shfl_up(a.y, o), __shfl_up(a.z, o), __shfl_up(a.w, o));
+}
+__device__ __forceinline__ rowvec shfl_row(const rowvec& a, int from) {
+  return make_float4(__shfl(a.x, from), __shfl(a.y, from), __shfl(a.z, from), __shfl(a.w, from));
+}
+#endif
+
 // Which spans a wavefront works through.  Blocks are dealt round-robin to the 8 XCDs and the
 // grid is a multiple of 8, so XCD x = blockIdx % 8 is given the x-th eighth of the stream: one
 // slice's partial rows and its factor rows then stay within one L2 where possible.
@@ -171,10 +201,11 @@ struct SpanWalk {
   uint32_t first, end, stride;
 };
 
-__device__ __forceinline__ SpanWalk span_walk(const GroupArgs& a, int wib, int wpb) {
-  const uint32_t xcd = blockIdx.x & 7u;
-  const uint32_t local = (blockIdx.x >> 3) * (uint32_t)wpb + (uint32_t)wib;  // wavefront within its XCD
-  const uint32_t wavesPerXcd = (gridDim.x >> 3) * (uint32_t)wpb;
+// block / blocks: this block's number among the blocks that work on the group, and how many they are.
+__device__ __forceinline__ SpanWalk span_walk(const GroupArgs& a, uint32_t block, uint32_t blocks, int wib, int wpb) {
+  const uint32_t xcd = block & 7u;
+  const uint32_t local = (block >> 3) * (uint32_t)wpb + (uint32_t)wib;  // wavefront within its XCD
+  const uint32_t wavesPerXcd = (blocks >> 3) * (uint32_t)wpb;
   SpanWalk w;
   if (a.persistent) {
     const uint32_t perXcd = (a.nSpans + 7u) >> 3;
@@ -189,18 +220,85 @@ __device__ __forceinline__ SpanWalk span_walk(const GroupArgs& a, int wib, int w
   return w;
 }
 
-// Pending partial row of a lane group, merged at the end of the wavefront's span.
+// Adds the row that lane group `first / G` holds (lane first + c: its 16-byte piece c) to output row `row`, the whole
+// wavefront taking part (first and row wave-uniform): consecutive lanes add consecutive elements, so a row is one
+// atomic instruction of whole cache lines.  Atomics on one row are served one line operation after the other, and
+// row_atomic's four strided ones per row cost four times as much there (measured on one row: 12.9 ns against 50.9 ns a
+// row added, however many wavefronts ask), which bounds a slice that thousands of wavefronts share.
 template <int G>
-__device__ __forceinline__ void final_merge(float* __restrict__ out, bool pend, uint32_t pendRow,
-                                            rowvec acc, int g, int c) {
-  const uint32_t first = __builtin_amdgcn_readfirstlane(pendRow);
-  const bool uniform = __all(pend ? 1 : 0) && __all(pendRow == first ? 1 : 0);
-  if (uniform) {
-    sum_lane_groups<G>(acc);
-    if (g == 0) row_atomic<G>(out, pendRow, c, acc);
-  } else if (pend) {
-    row_atomic<G>(out, pendRow, c, acc);
+__device__ __forceinline__ void row_atomic_wave(float* __restrict__ out, uint32_t row, int first, const rowvec& a, int lane) {
+#ifdef HBCSF_F64
+  constexpr int R = 2 * G;
+#else
+  constexpr int R = 4 * G;
+#endif
+  real* p = reinterpret_cast<real*>(out + (size_t)row * (size_t)(4 * G));
+#pragma unroll
+  for (int b = 0; b < R; b += 64) {
+    const int e = b + lane;
+#ifdef HBCSF_F64
+    const int from = first + (e / 2) % G;
+    const real x = __shfl(a.x, from), y = __shfl(a.y, from);
+    const real v = (e & 1) ? y : x;
+#else
+    const int from = first + (e / 4) % G;
+    const real x = __shfl(a.x, from), y = __shfl(a.y, from), z = __shfl(a.z, from), w = __shfl(a.w, from);
+    const real v = (e & 2) ? ((e & 1) ? w : z) : ((e & 1) ? y : x);
+#endif
+    if (e < R) unsafeAtomicAdd(p + e, v);
   }
+}
+
+// A finished slice: a row that lies inside one run is written by this one store, any other is merged with atomic adds.
+template <int G>
+__device__ __forceinline__ void emit_row(float* __restrict__ out, uint32_t mark, int c, const rowvec& acc) {
+  const uint32_t row = (mark & 0x7fffffffu) - 1u;
+  if (mark & kOwned) row_store<G>(out, row, c, acc);
+  else row_atomic<G>(out, row, c, acc);
+}
+
+// Closes a unit in which some slice ends.  The lane groups' parts are consecutive, so a slice that began before a
+// lane group's part continues from the parts before it: `acc` is what a lane group holds of the slice still open at the
+// end of its part, `headMark` / `head` the first slice that ended in it (mark 0: none did).  A segmented sum over the
+// lane groups (a part with an end starts a new segment) gives every part what the open slice had collected before it;
+// the heads go out with that added, and what is still open after the last part stays in lane group 0's accumulator.
+template <int G>
+__device__ __forceinline__ void close_unit(float* __restrict__ out, const rowvec* __restrict__ head, uint32_t headMark,
+                                           rowvec& acc, int lane, int g, int c) {
+  rowvec t = acc;
+  uint32_t ended = headMark ? 1u : 0u;
+#pragma unroll
+  for (int o = G; o < 64; o <<= 1) {
+    const rowvec up = shfl_up_row(t, o);
+    const uint32_t eu = __shfl_up(ended, o);
+    if (lane >= o) {
+      if (!ended) add_row(t, up);
+      ended |= eu;
+    }
+  }
+  const rowvec before = shfl_up_row(t, G);
+  rowvec h = rv_zero();
+  if (headMark) {
+    h = head[lane];
+    if (g > 0) add_row(h, before);
+    if (headMark & kOwned) row_store<G>(out, (headMark & 0x7fffffffu) - 1u, c, h);
+  }
+  unsigned long long shared = __ballot(c == 0 && headMark != 0u && !(headMark & kOwned));
+  while (shared) {
+    const int first = __builtin_ctzll(shared);
+    shared &= shared - 1;
+    row_atomic_wave<G>(out, (uint32_t)__builtin_amdgcn_readlane((int)headMark, first) - 1u, first, h, lane);
+  }
+  const rowvec last = shfl_row(t, 64 - G + c);
+  acc = g == 0 ? last : rv_zero();
+}
+
+// The slice still open at the end of the wavefront's span: one atomic row.
+template <int G>
+__device__ __forceinline__ void close_span(float* __restrict__ out, bool open, uint32_t row, rowvec acc, int lane) {
+  if (!open) return;  // wave-uniform
+  sum_lane_groups<G>(acc);
+  row_atomic_wave<G>(out, row, 0, acc, lane);
 }
 
 // One trace record per wavefront: which compute unit it ran on and when (profiling only).
@@ -228,26 +326,39 @@ __device__ __forceinline__ uint32_t mark_of_slice(uint32_t si) {
 // ---------------------------------------------------------------------------------------
 // Unit staging shared by the B-CSF and CSL kernels.
 //
+// A unit is NG parts of 2^SS nonzeros, one per lane group, and a whole number of runs (2^a.lshift nonzeros each,
+// SS <= a.lshift <= SS + log2 NG), so neither a fiber segment nor an owned slice crosses a unit's ends.  With
+// SS = a.lshift a part is a run.  With shorter parts several lane groups share a run: the fiber segments that cross a
+// part's end get an extra end mark there (each side of the cut adds its own product with the fiber's row), and slices
+// are summed over the parts when the unit is closed.  Short parts buy latency with a few more marks: a wavefront walks
+// 2^SS nonzeros per lane group one block after the other.
+//
 // All global loads a unit needs before its inner loop (stream data, fiber-segment and slice
-// arrays, the rows at the ends of the runs) are issued back to back and awaited once, then the
+// arrays, the row of the slice at the unit's end) are issued back to back and awaited once, then the
 // LDS records are written and the end marks scattered into them.  The run-table entries of
 // the next unit are fetched one unit ahead (UnitBounds), so nothing here waits on a chain of
 // dependent loads.
 // ---------------------------------------------------------------------------------------
 struct UnitBounds {
-  uint32_t rf;      // lane t <= NG: slice holding the first nonzero of run r0 + t (clipped to runs)
+  uint32_t rf;      // lane t <= runs per unit: slice holding the first nonzero of run r0 + t (clipped to runs)
   uint32_t fHi[3];  // fiber levels 1..3: first segment of the next unit (wave-uniform)
 };
 
-template <int G, int N, bool CSF>
+// Runs in a unit.
+template <int G, int SS>
+__device__ __forceinline__ uint32_t runs_per_unit(const GroupArgs& a) {
+  return ((uint32_t)(64 / G) << SS) >> a.lshift;
+}
+
+template <int G, int N, int SS, bool CSF>
 __device__ __forceinline__ UnitBounds load_bounds(const GroupArgs& a, uint32_t u, int lane) {
-  constexpr int NG = 64 / G;
   UnitBounds b;
-  const uint32_t r0 = u * NG;
-  b.rf = a.runFirst[0][min(r0 + (uint32_t)min(lane, NG), a.runs)];
+  const uint32_t rpu = runs_per_unit<G, SS>(a);
+  const uint32_t r0 = u * rpu;
+  b.rf = a.runFirst[0][min(r0 + min((uint32_t)lane, rpu), a.runs)];
   b.fHi[0] = b.fHi[1] = b.fHi[2] = 0;
   if (CSF) {
-    const uint32_t rN = min(r0 + NG, a.runs);
+    const uint32_t rN = min(r0 + rpu, a.runs);
 #pragma unroll
     for (int l = 1; l <= N - 2; ++l) b.fHi[l - 1] = a.runFirst[l][rN];
   }
@@ -255,23 +366,27 @@ __device__ __forceinline__ UnitBounds load_bounds(const GroupArgs& a, uint32_t u
 }
 
 struct UnitEnds {
-  uint32_t headRow;  // output row of the slice holding this lane group's first nonzero
-  uint32_t tailRow;  // output row of the slice holding the first nonzero of the next run
-  uint32_t ng;       // nonzeros in this lane group's run (0 beyond the end of the stream)
-  uint32_t sideAt;   // PACK: where the slices that end in this lane group's run start in the unit's slice list
+  uint32_t row;     // END marks: output row of the slice holding the next unit's first nonzero (wave-uniform)
+                    // START marks: output row of the slice holding this lane group's first nonzero
+  bool open;        // END marks: that slice began before the next unit (wave-uniform)
+  bool ends;        // END marks: some slice ends in this unit (wave-uniform)
+  uint32_t ng;      // nonzeros in this lane group's part (0 beyond the end of the stream)
+  uint32_t sideAt;  // PACK: where the slices that end in this lane group's part start in the unit's slice list
 };
 
 // fLo: first segment of this unit per fiber level (wave-uniform; = previous unit's fHi).
 // START = false: end marks (index + 1 at the LAST nonzero of a segment / slice; slice marks carry the owned bit).
 // START = true : start marks (index + 1 at the FIRST nonzero), for the kernel that needs a level's index while
-//                its segment is still open; a slice that began before the unit has no mark in it (headRow tells).
+//                its segment is still open; a slice that began before the unit has no mark in it (the row tells).
+//                Parts are runs here (SS = a.lshift).
 // PACK (B-CSF, order 4, end marks): 16-byte records {leaf, value, level-2 mark, level-1 mark | slice-end flag in bit
-//                31} instead of 32-byte ones; the marks of slices (row | owned bit, as stored) go to `side`, one
-//                word per slice that ends in the unit, in slice order (`side` holds NG * L words).
-template <int G, int N, int LS, bool CSF, bool START = false, bool PACK = false>
+//                31} instead of 32-byte ones; the marks of slices go to `side`, one word per slice that ends in the
+//                unit, in slice order (NG << SS words), and `sideFirst` (NG words) says where each part's begin.
+template <int G, int N, int SS, bool CSF, bool START = false, bool PACK = false>
 __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __restrict__ rec, uint32_t u,
                                                const UnitBounds& b, const uint32_t (&fLo)[3], int lane,
-                                               uint32_t* __restrict__ side = nullptr) {
+                                               uint32_t* __restrict__ side = nullptr,
+                                               uint32_t* __restrict__ sideFirst = nullptr) {
   static_assert(!PACK || (CSF && N == 4 && !START), "packed records: the order-4 B-CSF kernel");
   constexpr int NG = 64 / G;
   constexpr int NF = N - 2;
@@ -280,16 +395,14 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
   constexpr int KF = 4;  // segment loads per lane and level issued together (256 segments)
   constexpr int KS = 2;  // slice loads per lane issued together (128 slices)
   constexpr int markWord = (N == 3) ? 3 : N;  // slice mark: after the N-2 segment marks (B-CSF) / the value (CSL)
-  constexpr uint32_t ls = LS, L = 1u << LS;
-  constexpr uint32_t slots = (uint32_t)NG << LS;
-  const uint32_t r0 = u * NG;
-  const uint32_t z0 = r0 << ls;
+  constexpr uint32_t ss = SS, SUB = 1u << SS;
+  constexpr uint32_t slots = (uint32_t)NG << SS;
+  const uint32_t z0 = u * slots;
   const int g = lane / G;
+  // parts shorter than runs (of at most 64 nonzeros): segments are cut at part ends too
+  const bool cutSegments = CSF && !START && SS < 6 && ss < a.lshift;
   const uint32_t* __restrict__ valb = reinterpret_cast<const uint32_t*>(a.val);
 
-  // -- issue: rows at the ends of this lane group's run
-  const uint32_t hs = __shfl(b.rf, g), ts = __shfl(b.rf, g + 1);
-  const uint32_t headRaw = a.ind[0][hs], tailRaw = a.ind[0][ts];
   // -- issue: stream data
   // B-CSF: w0 = leaf index, w1 = value.  CSL: w0..w(N-2) = the N-1 non-root indices, w(N-1) = value.
   uint32_t w0[KV], w1[KV], w2[KV], w3[KV], w4[KV];
@@ -298,7 +411,7 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
     for (int t = 0; t < KV; ++t) {
       const uint32_t p = (uint32_t)t * 64u + lane;
       w0[t] = w1[t] = w2[t] = w3[t] = w4[t] = 0;
-      if ((uint32_t)t * 64u < slots) {
+      if ((uint32_t)t * 64u < slots && (slots >= 64u || p < slots)) {
         if (CSF) {
           w0[t] = __builtin_nontemporal_load(a.ind[N - 1] + z0 + p);
           w1[t] = __builtin_nontemporal_load(valb + z0 + p);
@@ -332,7 +445,7 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
     }
   }
   // -- issue: fiber-segment ends and indices
-  uint32_t fe[3][KF], fi[3][KF];
+  uint32_t fe[3][KF], fi[3][KF], fs[3][KF];
   if (CSF) {
 #pragma unroll
     for (int l = 1; l <= NF; ++l) {
@@ -341,9 +454,11 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
         const uint32_t f = fLo[l - 1] + (uint32_t)t * 64u + lane;
         fe[l - 1][t] = 0;
         fi[l - 1][t] = 0;
+        fs[l - 1][t] = 0;
         if (f < b.fHi[l - 1]) {
           fe[l - 1][t] = __builtin_nontemporal_load(a.ptr[l] + f + (START ? 0 : 1));
           fi[l - 1][t] = __builtin_nontemporal_load(a.ind[l] + f);
+          if (cutSegments) fs[l - 1][t] = __builtin_nontemporal_load(a.ptr[l] + f);
         }
       }
     }
@@ -352,16 +467,26 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
   // END marks: the slices that end in this unit are those before the one holding the next unit's first nonzero.
   // START marks: that slice may itself begin in this unit, so it is looked at too (a position test decides).
   const uint32_t s0 = __builtin_amdgcn_readfirstlane(b.rf);
-  const uint32_t s1 = __shfl(b.rf, NG) + (START ? 1u : 0u);
-  uint32_t se[KS], si[KS];
+  const uint32_t sNext = __builtin_amdgcn_readlane(b.rf, (int)runs_per_unit<G, SS>(a));
+  const uint32_t s1 = sNext + (START ? 1u : 0u);
+  uint32_t rowRaw = 0, nextStart = 0;
+  if (START) {
+    rowRaw = a.ind[0][__shfl(b.rf, g)];
+  } else {
+    rowRaw = a.ind[0][sNext];
+    nextStart = a.ptr[0][sNext];
+  }
+  uint32_t se[KS], si[KS], sb[KS];
 #pragma unroll
   for (int t = 0; t < KS; ++t) {
     const uint32_t sl = s0 + (uint32_t)t * 64u + lane;
     se[t] = 0;
     si[t] = 0;
+    sb[t] = 0;
     if (sl < s1) {
       se[t] = a.ptr[0][sl + (START ? 0 : 1)];
       si[t] = a.ind[0][sl];
+      if (PACK) sb[t] = a.ptr[0][sl];
     }
   }
 
@@ -370,7 +495,7 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
   for (int t = 0; t < KV; ++t) {
     const uint32_t p = (uint32_t)t * 64u + lane;
     if (p < slots) {
-      uint4* dst = reinterpret_cast<uint4*>(rec + (size_t)(p + (p >> ls)) * RW);
+      uint4* dst = reinterpret_cast<uint4*>(rec + (size_t)(p + (p >> ss)) * RW);
       if (CSF) {
         dst[0] = make_uint4(w0[t], w1[t], 0u, 0u);
         if (N >= 4 && !PACK) dst[1] = make_uint4(0u, 0u, 0u, 0u);
@@ -397,7 +522,7 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
         (N == 3 ? x2 : N == 4 ? x3 : x4) = valb[z];
       }
     }
-    uint4* dst = reinterpret_cast<uint4*>(rec + (size_t)(p + (p >> ls)) * RW);
+    uint4* dst = reinterpret_cast<uint4*>(rec + (size_t)(p + (p >> ss)) * RW);
     if (CSF) {
       dst[0] = make_uint4(x0, x1, 0u, 0u);
       if (N >= 4 && !PACK) dst[1] = make_uint4(0u, 0u, 0u, 0u);
@@ -408,6 +533,7 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
       dst[1] = make_uint4(N == 5 ? x4 : 0u, 0u, 0u, 0u);
     }
   }
+  if (PACK && lane < NG) sideFirst[lane] = s1 - s0;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
 
   // -- segment end marks
@@ -415,58 +541,61 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
 #pragma unroll
     for (int l = 1; l <= NF; ++l) {
       const int word = 2 + (NF - l);
+      auto mark = [&](uint32_t p, uint32_t index) {
+        uint32_t* at = rec + (size_t)(p + (p >> ss)) * RW + word;
+        if (PACK && l == 1) atomicOr(at, index + 1u);   // the slice-end flag may land in the same word
+        else *at = index + 1u;
+      };
 #pragma unroll
       for (int t = 0; t < KF; ++t) {
         const uint32_t f = fLo[l - 1] + (uint32_t)t * 64u + lane;
         if (f < b.fHi[l - 1]) {
           const uint32_t p = fe[l - 1][t] - (START ? 0u : 1u) - z0;
-          uint32_t* at = rec + (size_t)(p + (p >> ls)) * RW + word;
-          if (PACK && l == 1) atomicOr(at, fi[l - 1][t] + 1u);   // the slice-end flag may land in the same word
-          else *at = fi[l - 1][t] + 1u;
+          mark(p, fi[l - 1][t]);
+          if (cutSegments)
+            for (uint32_t q = ((fs[l - 1][t] - z0) | (SUB - 1u)); q < p; q += SUB) mark(q, fi[l - 1][t]);
         }
       }
       for (uint32_t f = fLo[l - 1] + (uint32_t)KF * 64u + lane; f < b.fHi[l - 1]; f += 64) {
         const uint32_t p = a.ptr[l][f + (START ? 0 : 1)] - (START ? 0u : 1u) - z0;
-        uint32_t* at = rec + (size_t)(p + (p >> ls)) * RW + word;
-        if (PACK && l == 1) atomicOr(at, a.ind[l][f] + 1u);
-        else *at = a.ind[l][f] + 1u;
+        const uint32_t index = a.ind[l][f];
+        mark(p, index);
+        if (cutSegments)
+          for (uint32_t q = ((a.ptr[l][f] - z0) | (SUB - 1u)); q < p; q += SUB) mark(q, index);
       }
     }
   }
   // -- slice end marks
+  auto end_slice = [&](uint32_t sl, uint32_t begin, uint32_t at, uint32_t entry) {
+    const uint32_t p = at - (START ? 0u : 1u) - z0;
+    if (PACK) {
+      atomicOr(rec + (size_t)(p + (p >> ss)) * RW + 3, 0x80000000u);
+      side[sl - s0] = mark_of_slice(entry);
+      // the parts whose first nonzero lies in this slice start with it
+      for (uint32_t q = begin > z0 ? (begin - z0 + SUB - 1u) >> ss : 0u; (q << ss) <= p; ++q) sideFirst[q] = sl - s0;
+    } else {
+      rec[(size_t)(p + (p >> ss)) * RW + markWord] = START ? (entry & 0x7fffffffu) + 1u : mark_of_slice(entry);
+    }
+  };
 #pragma unroll
   for (int t = 0; t < KS; ++t) {
     const uint32_t sl = s0 + (uint32_t)t * 64u + lane;
-    if (sl < s1 && (!START || (se[t] >= z0 && se[t] < z0 + slots && se[t] < a.nnz))) {
-      const uint32_t p = se[t] - (START ? 0u : 1u) - z0;
-      if (PACK) {
-        atomicOr(rec + (size_t)(p + (p >> ls)) * RW + 3, 0x80000000u);
-        side[sl - s0] = si[t];
-      } else {
-        rec[(size_t)(p + (p >> ls)) * RW + markWord] = START ? (si[t] & 0x7fffffffu) + 1u : mark_of_slice(si[t]);
-      }
-    }
+    if (sl < s1 && (!START || (se[t] >= z0 && se[t] < z0 + slots && se[t] < a.nnz))) end_slice(sl, sb[t], se[t], si[t]);
   }
   for (uint32_t sl = s0 + (uint32_t)KS * 64u + lane; sl < s1; sl += 64) {
     const uint32_t at = a.ptr[0][sl + (START ? 0 : 1)];
     if (START && (at < z0 || at >= z0 + slots || at >= a.nnz)) continue;
-    const uint32_t p = at - (START ? 0u : 1u) - z0;
-    const uint32_t sv = a.ind[0][sl];
-    if (PACK) {
-      atomicOr(rec + (size_t)(p + (p >> ls)) * RW + 3, 0x80000000u);
-      side[sl - s0] = sv;
-    } else {
-      rec[(size_t)(p + (p >> ls)) * RW + markWord] = START ? (sv & 0x7fffffffu) + 1u : mark_of_slice(sv);
-    }
+    end_slice(sl, PACK ? a.ptr[0][sl] : 0u, at, a.ind[0][sl]);
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 
   UnitEnds e;
-  const uint32_t r = r0 + g;
-  e.headRow = headRaw & 0x7fffffffu;
-  e.tailRow = tailRaw & 0x7fffffffu;
-  e.ng = r < a.runs ? min(L, a.nnz - (r << ls)) : 0u;
-  e.sideAt = hs - s0;
+  const uint32_t z = z0 + ((uint32_t)g << ss);
+  e.row = rowRaw & 0x7fffffffu;
+  e.open = nextStart < min(z0 + slots, a.nnz);
+  e.ends = s1 > s0;
+  e.ng = z < a.nnz ? min(SUB, a.nnz - z) : 0u;
+  e.sideAt = PACK ? sideFirst[g] : 0u;
   return e;
 }
 
@@ -531,12 +660,12 @@ __global__ __launch_bounds__(256) void define_rows_kernel(rowvec* __restrict__ o
 // Every vector-memory instruction keeps the CU's address unit busy for the same 16 cycles however many lanes
 // are active, and that unit is what bounds this kernel when the factor matrices are cache-resident.  The cache
 // holds kDenseCache rows; marks beyond it (rare when segments average a few nonzeros) load their row directly.
-template <int G, int N, int LS, int kSteps, bool WIDE, bool DENSE>
-__device__ __forceinline__ void csf_group_body(const GroupArgs& a) {
+template <int G, int N, int SS, int kSteps, bool WIDE, bool DENSE>
+__device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t block, uint32_t blocks) {
   constexpr int NG = 64 / G;
   constexpr int NF = N - 2;
   // order 4 (the plain variant): 16-byte records, the level-1 mark and the slice-end flag in one word, the slices'
-  // rows in a per-unit list beside the records
+  // marks in a per-unit list beside the records
   constexpr bool PACK = N == 4 && !DENSE;
   constexpr int RW = (N == 3 || PACK) ? 4 : 8;
   static_assert(!DENSE || N <= 4, "the dense fiber-row gather handles orders 3 and 4");
@@ -545,62 +674,81 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a) {
   const int wib = threadIdx.x >> 6;
   const int wpb = blockDim.x >> 6;
   const int g = lane / G, c = lane % G;
-  constexpr uint32_t L = 1u << LS;
-  constexpr uint32_t recWords = NG * (L + 1) * RW;
-  constexpr uint32_t waveWords = recWords + (DENSE ? 64u + (uint32_t)kDenseCache * G * 4u : 0u) + (PACK ? NG * L : 0u);
-  uint32_t* rec = lds + (size_t)wib * waveWords;
-  uint32_t* side = rec + recWords;                                   // PACK: marks of the slices that end in the unit
-  uint32_t* list = rec + recWords;                                   // DENSE: row numbers by slot
-  rowvec* cache = reinterpret_cast<rowvec*>(rec + recWords + 64);    // DENSE: rows by slot, G rowvec each
-
+  constexpr uint32_t SUB = 1u << SS;
+  constexpr uint32_t recWords = NG * (SUB + 1) * RW;
+  uint32_t* rec = lds + (size_t)wib * csf_wave_words(N, G, SS, DENSE);
+  rowvec* head = reinterpret_cast<rowvec*>(rec + recWords);          // first finished slice of each part
+  uint32_t* side = rec + recWords + 256;                             // PACK: marks of the slices that end in the unit,
+  uint32_t* sideFirst = side + NG * SUB;                             //       and where each part's begin
+  uint32_t* list = rec + recWords + 256;                             // DENSE: row numbers by slot
+  rowvec* cache = reinterpret_cast<rowvec*>(rec + recWords + 256 + 64);  // DENSE: rows by slot, G rowvec each
 
   const float* __restrict__ facLeaf = a.fac[N - 1];
   const float* __restrict__ facDeep = a.fac[N - 2];   // deepest fiber level
   const float* __restrict__ facNext = a.fac[N >= 4 ? N - 3 : 1];  // the fiber level above it (N >= 4)
   const float* __restrict__ facTop = a.fac[1];        // level 1 (N = 5: the third fiber level from the leaf)
+  const float* markDeep = row_before<G>(facDeep);      // the same, addressed by marks (index + 1)
+  const float* markNext = row_before<G>(facNext);
+  const float* markTop = row_before<G>(facTop);
 
   const unsigned long long traceStart = a.trace ? wall_clock64() : 0ull;
-  const SpanWalk walk = span_walk(a, wib, wpb);
+  const SpanWalk walk = span_walk(a, block, blocks, wib, wpb);
   for (uint32_t span = walk.first; span < walk.end; span += walk.stride) {
   uint32_t u = span * a.unitsPerWave;
   const uint32_t uEnd = min(u + a.unitsPerWave, a.nUnits);
+  // acc: what this lane group has collected of the slice that is open at the end of its part.  Between units it is
+  // held by lane group 0 alone, unless no slice ended since (spread): then every lane group holds a share of it.
   rowvec acc = rv_zero();
-  bool pend = false;
-  uint32_t pendRow = 0;
+  bool spread = false, open = false;
+  uint32_t openRow = 0;
 
-  UnitBounds cur = load_bounds<G, N, true>(a, u, lane);
+  UnitBounds cur = load_bounds<G, N, SS, true>(a, u, lane);
   uint32_t fLo[3] = {0, 0, 0};
 #pragma unroll
-  for (int l = 1; l <= NF; ++l) fLo[l - 1] = a.runFirst[l][u * NG];
+  for (int l = 1; l <= NF; ++l) fLo[l - 1] = a.runFirst[l][u * runs_per_unit<G, SS>(a)];
 
   for (; u < uEnd; ++u) {
     // run-table entries of the next unit: in flight while this unit is staged and processed
-    const UnitBounds nxt = load_bounds<G, N, true>(a, min(u + 1, a.nUnits - 1), lane);
-    const UnitEnds ends = stage_unit<G, N, LS, true, false, PACK>(a, rec, u, cur, fLo, lane, side);
-    const uint32_t headRow = ends.headRow, tailRow = ends.tailRow, ng = ends.ng;
-    uint32_t sideAt = ends.sideAt;   // PACK: the next slice of this lane group's run in the unit's slice list
+    const UnitBounds nxt = load_bounds<G, N, SS, true>(a, min(u + 1, a.nUnits - 1), lane);
+    const UnitEnds ends = stage_unit<G, N, SS, true, false, PACK>(a, rec, u, cur, fLo, lane, side, sideFirst);
+    const uint32_t ng = ends.ng;
+    uint32_t sideAt = ends.sideAt;   // PACK: the next slice of this lane group's part in the unit's slice list
+    uint32_t headMark = 0;           // mark of the first slice that ends in this lane group's part
     fLo[0] = cur.fHi[0];
     fLo[1] = cur.fHi[1];
     fLo[2] = cur.fHi[2];
     cur = nxt;
+    open = ends.open;
+    openRow = ends.row;
+    if (ends.ends && spread) {
+      sum_lane_groups<G>(acc);
+      if (g > 0) acc = rv_zero();
+    }
+    spread = !ends.ends;
+    // a slice ends here: the first one of a part waits for the parts before it, the others are complete
+    auto slice_end = [&](uint32_t mark) {
+      if (headMark) {
+        emit_row<G>(a.out, mark, c, acc);
+      } else {
+        headMark = mark;
+        head[lane] = acc;
+      }
+      acc = rv_zero();
+    };
 
-    // A lane group whose run lies beyond the end of the stream (ng = 0, last unit only) has all-zero records.  The
+    // A lane group whose part lies beyond the end of the stream (ng = 0, last unit only) has all-zero records.  The
     // dense variant's block loop is collective (prefix sum over the lane groups, shared list and row cache), so
     // every lane group runs it, live or not; zero records hold no marks and so change nothing.
     {
-      if (ng > 0 && pend && pendRow != headRow) {
-        row_atomic<G>(a.out, pendRow, c, acc);
-        acc = rv_zero();
-      }
       // tmp: sum over the leaves of the open deepest-level segment; tmp1 / tmp2: sums over the closed segments
       // of the next levels up (N >= 4 / N = 5); acc: the slice's row.  Marks are nested: a segment of a level
       // can only end where one of every deeper level ends.
       rowvec tmp = rv_zero();
       rowvec tmp1 = rv_zero();
       rowvec tmp2 = rv_zero();
-      const uint32_t* myrec = rec + (size_t)g * (L + 1) * RW;
+      const uint32_t* myrec = rec + (size_t)g * (SUB + 1) * RW;
       if constexpr (DENSE) {
-      for (uint32_t sb = 0; sb < L; sb += kSteps) {
+      for (uint32_t sb = 0; sb < SUB; sb += kSteps) {
         uint4 rr[kSteps];
         uint32_t mi[kSteps];   // slice mark
         uint32_t sl[kSteps];   // slot (within this lane group) of the deepest level's mark, then of the next level's
@@ -681,19 +829,14 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a) {
               }
             }
             tmp = rv_zero();
-            if (mi[t]) {  // a slice can only end where a segment ends
-              const uint32_t row = (mi[t] & 0x7fffffffu) - 1u;
-              if (mi[t] & 0x80000000u) row_store<G>(a.out, row, c, acc);
-              else row_atomic<G>(a.out, row, c, acc);
-              acc = rv_zero();
-            }
+            if (mi[t]) slice_end(mi[t]);  // a slice can only end where a segment ends
           }
         }
         // the next block rewrites the list and the cache
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       }
       } else if (ng > 0) {
-      for (uint32_t sb = 0; sb < L; sb += kSteps) {
+      for (uint32_t sb = 0; sb < SUB; sb += kSteps) {
         uint4 rr[kSteps];
         uint32_t m1[kSteps];   // N = 5: mark of fiber level 1
         uint32_t mi[kSteps];   // slice mark
@@ -722,18 +865,10 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a) {
         // load issued before it has arrived too, and the leaf rows can be awaited one by one.
 #pragma unroll
         for (int t = 0; t < kSteps; ++t) {
-          if (rr[t].z) {
-            br[t] = (a.streamLevel & (1u << (N - 2))) ? row_load_streaming<G, WIDE>(facDeep, rr[t].z - 1u, c)
-                                                       : row_load<G, WIDE>(facDeep, rr[t].z - 1u, c);
-          }
-          if (N >= 4 && rr[t].w) {
-            nr[t] = (a.streamLevel & (1u << (N - 3))) ? row_load_streaming<G, WIDE>(facNext, rr[t].w - 1u, c)
-                                                       : row_load<G, WIDE>(facNext, rr[t].w - 1u, c);
-          }
-          if (N == 5 && m1[t]) {
-            ar[t] = (a.streamLevel & 2u) ? row_load_streaming<G, WIDE>(facTop, m1[t] - 1u, c)
-                                         : row_load<G, WIDE>(facTop, m1[t] - 1u, c);
-          }
+          if (rr[t].z) br[t] = marked_row_load<G, WIDE>(markDeep, rr[t].z, c, (a.streamLevel & (1u << (N - 2))) != 0u);
+          if (N >= 4 && rr[t].w)
+            nr[t] = marked_row_load<G, WIDE>(markNext, rr[t].w, c, (a.streamLevel & (1u << (N - 3))) != 0u);
+          if (N == 5 && m1[t]) ar[t] = marked_row_load<G, WIDE>(markTop, m1[t], c, (a.streamLevel & 2u) != 0u);
         }
 #pragma unroll
         for (int t = 0; t < kSteps; ++t) cr[t] = row_load<G, WIDE>(facLeaf, rr[t].x, c);
@@ -759,50 +894,38 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a) {
               }
             }
             tmp = rv_zero();
-            if (mi[t]) {  // a slice can only end where a segment ends
-              // PACK: the stored root entry (row | owned bit) of the next slice of this run; else the mark itself
-              const uint32_t sm = PACK ? side[sideAt++] : mi[t];
-              const uint32_t row = (sm & 0x7fffffffu) - (PACK ? 0u : 1u);
-              if (sm & 0x80000000u) row_store<G>(a.out, row, c, acc);
-              else row_atomic<G>(a.out, row, c, acc);
-              acc = rv_zero();
-            }
+            // a slice can only end where a segment ends (PACK: its mark is the next of this part's in the slice list)
+            if (mi[t]) slice_end(PACK ? side[sideAt++] : mi[t]);
           }
         }
       }
       }  // classic / dense
-      // the run leaves a partial row behind unless its last nonzero ends a slice
-      if (ng > 0) {
-        pend = PACK ? (myrec[(size_t)(ng - 1) * RW + 3] & 0x80000000u) == 0u
-                    : myrec[(size_t)(ng - 1) * RW + (N == 3 ? 3 : N)] == 0u;
-        pendRow = tailRow;
-      }
     }
+    if (ends.ends) close_unit<G>(a.out, head, headMark, acc, lane, g, c);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
-  final_merge<G>(a.out, pend, pendRow, acc, g, c);
+  close_span<G>(a.out, open, openRow, acc, lane);
   }  // spans
   trace_wave(a, kCsfKernel, traceStart, lane);
 }
 
-template <int G, int N, int LS, int kSteps, bool WIDE>
+template <int G, int N, int SS, int kSteps, bool WIDE>
 __global__ __launch_bounds__(256) void csf_group_kernel(const GroupArgs a) {
-  csf_group_body<G, N, LS, kSteps, WIDE, false>(a);
+  csf_group_body<G, N, SS, kSteps, WIDE, false>(a, blockIdx.x, gridDim.x);
 }
 
-template <int G, int N, int LS, int kSteps, bool WIDE>
+template <int G, int N, int SS, int kSteps, bool WIDE>
 __global__ __launch_bounds__(256) void csf_group_dense_kernel(const GroupArgs a) {
-  csf_group_body<G, N, LS, kSteps, WIDE, true>(a);
+  csf_group_body<G, N, SS, kSteps, WIDE, true>(a, blockIdx.x, gridDim.x);
 }
 
-// The order-3, R = 32, 32-bit-offset instantiation needs 132 vector registers, four more than fit four
-// wavefronts per SIMD; held to 128 it spills three registers and gains a wavefront per SIMD, which pays on
-// the cache-resident workloads (measured -4.5 % on a 100 M-nonzero tensor whose factors fit the L2).  The
-// 64-bit-offset instantiation spills more and loses; order 4 (176 registers, held to 168 for a third wavefront
-// per SIMD) measured no gain; both keep the plain kernel.
-template <int G, int N, int LS, int kSteps>
+// With 8 gathers in flight the order-3, R = 32, 32-bit-offset instantiation needs a few more vector registers than fit
+// four wavefronts per SIMD; held to 128 it spills one of them and gains a wavefront.  (With 4 in flight: 86 to 96
+// registers at order 3, five wavefronts, 118 to 126 at order 4.  Holding order 3 to 80 for a sixth spilled ten and took
+// 2.68 instead of 2.35 ms on 100 M nonzeros.)
+template <int G, int N, int SS, int kSteps>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void csf_group_kernel_occ4(const GroupArgs a) {
-  csf_group_body<G, N, LS, kSteps, false, false>(a);
+  csf_group_body<G, N, SS, kSteps, false, false>(a, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -832,17 +955,17 @@ __global__ __launch_bounds__(256) void csf_nonroot_kernel(const GroupArgs a) {
   constexpr uint32_t L = 1u << LS;
   uint32_t* rec = lds + (size_t)wib * (NG * (L + 1) * RW);
 
-  const SpanWalk walk = span_walk(a, wib, wpb);
+  const SpanWalk walk = span_walk(a, blockIdx.x, gridDim.x, wib, wpb);
   for (uint32_t span = walk.first; span < walk.end; span += walk.stride) {
     uint32_t u = span * a.unitsPerWave;
     const uint32_t uEnd = min(u + a.unitsPerWave, a.nUnits);
-    UnitBounds cur = load_bounds<G, N, true>(a, u, lane);
+    UnitBounds cur = load_bounds<G, N, LS, true>(a, u, lane);
     uint32_t fLo[3] = {0, 0, 0};
 #pragma unroll
     for (int l = 1; l <= NF; ++l) fLo[l - 1] = a.runFirst[l][u * NG];
 
     for (; u < uEnd; ++u) {
-      const UnitBounds nxt = load_bounds<G, N, true>(a, min(u + 1, a.nUnits - 1), lane);
+      const UnitBounds nxt = load_bounds<G, N, LS, true>(a, min(u + 1, a.nUnits - 1), lane);
       const UnitEnds ends = stage_unit<G, N, LS, true, true>(a, rec, u, cur, fLo, lane);
       fLo[0] = cur.fHi[0];
       fLo[1] = cur.fHi[1];
@@ -854,7 +977,7 @@ __global__ __launch_bounds__(256) void csf_nonroot_kernel(const GroupArgs a) {
         rowvec lr[LEAF];
 #pragma unroll
         for (int l = 0; l < LEAF; ++l) lr[l] = rv_ones();
-        lr[0] = row_load<G, WIDE>(a.fac[0], ends.headRow, c);   // the slice may have begun in an earlier run
+        lr[0] = row_load<G, WIDE>(a.fac[0], ends.row, c);   // the slice may have begun in an earlier run
         rowvec up = rv_ones(), dn = rv_ones();
         rowvec acc = rv_zero();
         uint32_t curT = 0;
@@ -932,8 +1055,8 @@ __global__ __launch_bounds__(256) void csf_nonroot_kernel(const GroupArgs a) {
 // LDS record: N = 3: {j, k, val, slice mark}; N = 4: {a, b, l, val, slice mark, -, -, -};
 //             N = 5: {a, b, c, l, val, slice mark, -, -}.
 // ---------------------------------------------------------------------------------------
-template <int G, int N, int LS, int kSteps, bool WIDE>
-__global__ __launch_bounds__(256) void csl_group_kernel(const GroupArgs a) {
+template <int G, int N, int SS, int kSteps, bool WIDE>
+__device__ __forceinline__ void csl_group_body(const GroupArgs& a, uint32_t block, uint32_t blocks) {
   constexpr int NG = 64 / G;
   constexpr int RW = (N == 3) ? 4 : 8;
   extern __shared__ uint32_t lds[];
@@ -941,35 +1064,39 @@ __global__ __launch_bounds__(256) void csl_group_kernel(const GroupArgs a) {
   const int wib = threadIdx.x >> 6;
   const int wpb = blockDim.x >> 6;
   const int g = lane / G, c = lane % G;
-  constexpr uint32_t L = 1u << LS;
-  uint32_t* rec = lds + (size_t)wib * (NG * (L + 1) * RW);
-
+  constexpr uint32_t SUB = 1u << SS;
+  constexpr uint32_t recWords = NG * (SUB + 1) * RW;
+  uint32_t* rec = lds + (size_t)wib * csl_wave_words(N, G, SS);
+  rowvec* head = reinterpret_cast<rowvec*>(rec + recWords);
 
   const unsigned long long traceStart = a.trace ? wall_clock64() : 0ull;
-  const SpanWalk walk = span_walk(a, wib, wpb);
+  const SpanWalk walk = span_walk(a, block, blocks, wib, wpb);
   for (uint32_t span = walk.first; span < walk.end; span += walk.stride) {
   uint32_t u = span * a.unitsPerWave;
   const uint32_t uEnd = min(u + a.unitsPerWave, a.nUnits);
-  rowvec acc = rv_zero();
-  bool pend = false;
-  uint32_t pendRow = 0;
+  rowvec acc = rv_zero();               // as in the B-CSF kernel
+  bool spread = false, open = false;
+  uint32_t openRow = 0;
 
-  UnitBounds cur = load_bounds<G, N, false>(a, u, lane);
+  UnitBounds cur = load_bounds<G, N, SS, false>(a, u, lane);
   const uint32_t fLo[3] = {0, 0, 0};
 
   for (; u < uEnd; ++u) {
-    const UnitBounds nxt = load_bounds<G, N, false>(a, min(u + 1, a.nUnits - 1), lane);
-    const UnitEnds ends = stage_unit<G, N, LS, false>(a, rec, u, cur, fLo, lane);
-    const uint32_t headRow = ends.headRow, tailRow = ends.tailRow, ng = ends.ng;
+    const UnitBounds nxt = load_bounds<G, N, SS, false>(a, min(u + 1, a.nUnits - 1), lane);
+    const UnitEnds ends = stage_unit<G, N, SS, false>(a, rec, u, cur, fLo, lane);
+    uint32_t headMark = 0;
     cur = nxt;
+    open = ends.open;
+    openRow = ends.row;
+    if (ends.ends && spread) {
+      sum_lane_groups<G>(acc);
+      if (g > 0) acc = rv_zero();
+    }
+    spread = !ends.ends;
 
-    if (ng > 0) {
-      if (pend && pendRow != headRow) {
-        row_atomic<G>(a.out, pendRow, c, acc);
-        acc = rv_zero();
-      }
-      const uint32_t* myrec = rec + (size_t)g * (L + 1) * RW;
-      for (uint32_t sb = 0; sb < L; sb += kSteps) {
+    if (ends.ng > 0) {
+      const uint32_t* myrec = rec + (size_t)g * (SUB + 1) * RW;
+      for (uint32_t sb = 0; sb < SUB; sb += kSteps) {
         uint4 rr[kSteps];
         uint32_t vv[kSteps];   // value bits
         uint32_t mi[kSteps];   // slice mark
@@ -1004,22 +1131,37 @@ __global__ __launch_bounds__(256) void csl_group_kernel(const GroupArgs a) {
           if (N >= 5) pr = mul4(pr, x4[t]);
           fma4(acc, __uint_as_float(vv[t]), pr);
           if (mi[t]) {
-            const uint32_t row = (mi[t] & 0x7fffffffu) - 1u;
-            if (mi[t] & 0x80000000u) row_store<G>(a.out, row, c, acc);
-            else row_atomic<G>(a.out, row, c, acc);
+            if (headMark) {
+              emit_row<G>(a.out, mi[t], c, acc);
+            } else {
+              headMark = mi[t];
+              head[lane] = acc;
+            }
             acc = rv_zero();
           }
         }
       }
-      // the run leaves a partial row behind unless its last nonzero ends a slice
-      pend = myrec[(size_t)(ng - 1) * RW + (N == 3 ? 3 : N)] == 0u;
-      pendRow = tailRow;
     }
+    if (ends.ends) close_unit<G>(a.out, head, headMark, acc, lane, g, c);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
-  final_merge<G>(a.out, pend, pendRow, acc, g, c);
+  close_span<G>(a.out, open, openRow, acc, lane);
   }  // spans
   trace_wave(a, kCslKernel, traceStart, lane);
+}
+
+template <int G, int N, int SS, int kSteps, bool WIDE>
+__global__ __launch_bounds__(256) void csl_group_kernel(const GroupArgs a) {
+  csl_group_body<G, N, SS, kSteps, WIDE>(a, blockIdx.x, gridDim.x);
+}
+
+// Both groups in one launch (neither reads what the other writes; rows they share are added atomically): the first
+// cslBlocks blocks walk the CSL group, the others the B-CSF group, so that the tail of one is filled with work of the
+// other.  On a 5 M-nonzero tensor the CSL kernel alone took 16 us for 80 000 nonzeros, nearly all of it latency.
+template <int G, int N, int SS, int kSteps, bool WIDE>
+__global__ __launch_bounds__(256) void csl_csf_kernel(const GroupArgs csl, const GroupArgs csf, uint32_t cslBlocks) {
+  if (blockIdx.x < cslBlocks) csl_group_body<G, N, SS, kSteps, WIDE>(csl, blockIdx.x, cslBlocks);
+  else csf_group_body<G, N, SS, kSteps, WIDE, false>(csf, blockIdx.x - cslBlocks, gridDim.x - cslBlocks);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1167,60 +1309,76 @@ using namespace f64;
 // ---------------------------------------------------------------------------------------
 namespace {
 
-// `grid` carries the number of compute units.  Default launch: one wavefront per span.  Persistent
-// launch: (resident blocks per CU) x CUs blocks, capped by the spans.  Both rounded to a multiple of 8.
-template <int G, int N, int LS, int S, bool WIDE>
-hipError_t launch_one(int kind, const GroupArgs& a, dim3 grid, dim3 block, size_t lds, hipStream_t s) {
-  auto csf = (G == 8 && N == 3 && S == 8 && !WIDE) ? csf_group_kernel_occ4<G, N, LS, S> : csf_group_kernel<G, N, LS, S, WIDE>;
-  if constexpr (G == 8 && N <= 4 && (LS == 5 || LS == 6)) {
-    if (a.denseMid) csf = csf_group_dense_kernel<G, N, LS, S, WIDE>;
-  }
-  auto csl = csl_group_kernel<G, N, LS, S, WIDE>;
-  const int which = kind == kCsfKernel ? 1 : 0;
+// Blocks of `wpb` wavefronts for a group: one wavefront per span, a multiple of 8 blocks.
+uint64_t span_blocks(const GroupArgs& a, uint32_t wpb) { return (((uint64_t)a.nSpans + wpb - 1) / wpb + 7) / 8 * 8; }
+
+// `cus`: compute units.  Default launch: one wavefront per span.  Persistent launch: (resident blocks per CU) x CUs
+// blocks, capped by the spans.  Both rounded to a multiple of 8.
+template <int G, int N, int SS, int S, bool WIDE>
+hipError_t launch_one(int kind, const GroupArgs& a, const GroupArgs* csl, uint32_t cus, dim3 block, size_t lds, hipStream_t s) {
+  constexpr bool occ4 = G == 8 && N == 3 && S == 8 && !WIDE;
   const uint32_t wpb = block.x >> 6;
-  const uint64_t need = ((uint64_t)a.nSpans + wpb - 1) / wpb;
-  uint64_t blocks = need;
+  if (csl) {
+    if constexpr (S == 4) {
+      const uint32_t cslBlocks = (uint32_t)span_blocks(*csl, wpb);
+      hipLaunchKernelGGL((csl_csf_kernel<G, N, SS, S, WIDE>), dim3(cslBlocks + (uint32_t)span_blocks(a, wpb)), block, lds,
+                         s, *csl, a, cslBlocks);
+      return hipGetLastError();
+    }
+    return hipErrorInvalidValue;  // with 8 gathers in flight the groups are launched one by one
+  }
+  void (*kernel)(GroupArgs) = csl_group_kernel<G, N, SS, S, WIDE>;
+  if (kind == kCsfKernel) {
+    if constexpr (occ4) kernel = csf_group_kernel_occ4<G, N, SS, S>;
+    else kernel = csf_group_kernel<G, N, SS, S, WIDE>;
+    if constexpr (G == 8 && N <= 4 && (SS == 5 || SS == 6)) {
+      if (a.denseMid) kernel = csf_group_dense_kernel<G, N, SS, S, WIDE>;
+    }
+  }
+  uint64_t blocks = span_blocks(a, wpb);
   if (a.persistent) {
     // resident blocks per CU of this kernel on the current device (asked per launch: the persistent launch is a
     // tuning variant, and a cached answer would be wrong for another device of the process)
     int n = 0;
-    const hipError_t e = which ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, csf, (int)block.x, lds)
-                               : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, csl, (int)block.x, lds);
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, (int)block.x, lds);
     if (e != hipSuccess) return e;
-    blocks = (uint64_t)grid.x * (uint64_t)(n > 0 ? n : 1);
-    if (blocks > need) blocks = need;
+    const uint64_t resident = ((uint64_t)cus * (uint64_t)(n > 0 ? n : 1) + 7) / 8 * 8;
+    if (blocks > resident) blocks = resident;
   }
-  blocks = (blocks + 7) / 8 * 8;
-  if (which) hipLaunchKernelGGL(csf, dim3((uint32_t)blocks), block, lds, s, a);
-  else hipLaunchKernelGGL(csl, dim3((uint32_t)blocks), block, lds, s, a);
+  hipLaunchKernelGGL(kernel, dim3((uint32_t)blocks), block, lds, s, a);
   return hipGetLastError();
 }
 
-template <int G, int N, int LS>
-hipError_t launch_ls(int kind, int steps, bool wide, const GroupArgs& a, dim3 grid, dim3 block, size_t lds,
-                     hipStream_t s) {
-  if (G == 8 && steps == 4)
-    return wide ? launch_one<G, N, LS, 4, true>(kind, a, grid, block, lds, s)
-                : launch_one<G, N, LS, 4, false>(kind, a, grid, block, lds, s);
-  return wide ? launch_one<G, N, LS, 8, true>(kind, a, grid, block, lds, s)
-              : launch_one<G, N, LS, 8, false>(kind, a, grid, block, lds, s);
+template <int G, int N, int SS>
+hipError_t launch_ss(int kind, bool wide, const GroupArgs& a, const GroupArgs* csl, uint32_t cus, dim3 block,
+                     size_t lds, hipStream_t s) {
+  constexpr int S = G == 8 && SS == 6 ? 8 : 4;
+  return wide ? launch_one<G, N, SS, S, true>(kind, a, csl, cus, block, lds, s)
+              : launch_one<G, N, SS, S, false>(kind, a, csl, cus, block, lds, s);
 }
 
+// The part sizes the caller can ask for at this G: units of at most 256 nonzeros, or at G = 8 parts of 64.
 template <int G, int N>
-hipError_t launch_g(int kind, int steps, bool wide, const GroupArgs& a, dim3 grid, dim3 block, size_t lds,
-                    hipStream_t s) {
+hipError_t launch_g(int kind, bool wide, const GroupArgs& a, const GroupArgs* csl, dim3 grid, dim3 block,
+                    size_t lds, hipStream_t s) {
   if (kind == kCooKernel) {
     if (wide) hipLaunchKernelGGL((coo_group_kernel<G, N, true>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((coo_group_kernel<G, N, false>), grid, block, 0, s, a);
     return hipGetLastError();
   }
-  switch (a.lshift) {
-    case 3: return launch_ls<G, N, 3>(kind, steps, wide, a, grid, block, lds, s);
-    case 4: return launch_ls<G, N, 4>(kind, steps, wide, a, grid, block, lds, s);
-    case 5: return launch_ls<G, N, 5>(kind, steps, wide, a, grid, block, lds, s);
-    case 6: return launch_ls<G, N, 6>(kind, steps, wide, a, grid, block, lds, s);
-    default: return hipErrorInvalidValue;
+  switch (a.partShift) {
+    case 3: return launch_ss<G, N, 3>(kind, wide, a, csl, grid.x, block, lds, s);
+    case 4:
+      if constexpr (G >= 4) return launch_ss<G, N, 4>(kind, wide, a, csl, grid.x, block, lds, s);
+      break;
+    case 5:
+      if constexpr (G >= 8) return launch_ss<G, N, 5>(kind, wide, a, csl, grid.x, block, lds, s);
+      break;
+    case 6:
+      if constexpr (G >= 8) return launch_ss<G, N, 6>(kind, wide, a, csl, grid.x, block, lds, s);
+      break;
   }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -1254,10 +1412,10 @@ hipError_t HBCSF_CAT(HBCSF_LAUNCH_DEFINE_COO, HBCSF_G, _n, HBCSF_N)(bool wide, c
   return hipGetLastError();
 }
 
-hipError_t HBCSF_CAT(HBCSF_LAUNCH_GROUP, HBCSF_G, _n, HBCSF_N)(int kind, int steps, bool wide, const GroupArgs& a,
-                                                          uint32_t blocks, uint32_t threads, size_t ldsBytes,
+hipError_t HBCSF_CAT(HBCSF_LAUNCH_GROUP, HBCSF_G, _n, HBCSF_N)(int kind, bool wide, const GroupArgs& a,
+                                                          const GroupArgs* csl, uint32_t blocks, uint32_t threads, size_t ldsBytes,
                                                           hipStream_t s) {
-  return launch_g<HBCSF_G, HBCSF_N>(kind, steps, wide, a, dim3(blocks), dim3(threads), ldsBytes, s);
+  return launch_g<HBCSF_G, HBCSF_N>(kind, wide, a, csl, dim3(blocks), dim3(threads), ldsBytes, s);
 }
 
 #if HBCSF_G == 8 && !defined(HBCSF_F64)
@@ -1277,7 +1435,7 @@ hipError_t launch_nonroot_t(bool wide, const GroupArgs& a, uint32_t threads, siz
 hipError_t HBCSF_CAT(launch_nonroot_n, HBCSF_N, , )(int level, bool wide, const GroupArgs& a, uint32_t threads,
                                                      size_t ldsBytes, hipStream_t s) {
   constexpr int LS = HBCSF_N == 3 ? 6 : 5;
-  if (a.lshift != (uint32_t)LS || a.persistent) return hipErrorInvalidValue;
+  if (a.lshift != (uint32_t)LS || a.partShift != (uint32_t)LS || a.persistent) return hipErrorInvalidValue;
   switch (level) {
     case 1: return launch_nonroot_t<HBCSF_N, LS, 1>(wide, a, threads, ldsBytes, s);
     case 2: return launch_nonroot_t<HBCSF_N, LS, 2>(wide, a, threads, ldsBytes, s);

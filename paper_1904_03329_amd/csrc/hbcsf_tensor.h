@@ -24,7 +24,7 @@ struct hbcsf_tensor {
   int numCU = 256;
   uint64_t sliceThreshold = 0;
   uint64_t wavesPerCU = 0;   // launch sizing override, 0 = default
-  int steps = 8;             // records in flight per lane group
+  int steps = 0;             // records in flight per lane group, 0 = automatic
   uint32_t kernelMask = 15;  // bit0 define, bit1 COO, bit2 CSL, bit3 CSF
   bool persistent = false;   // resident wavefronts walk the spans round-robin
   int denseMid = 0;          // B-CSF fiber-row gather through an LDS row cache (tuning variant): 0 off, 1 on
