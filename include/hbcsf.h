@@ -274,8 +274,8 @@ int hbcsf_download(hbcsf_tensor *t, void *hip_stream);
  *     A_n <- MTTKRP_n(X; other factors) * pinv( Hadamard_{m != n} A_m^T A_m ),
  * then leaves all factors with unit-2-norm columns and lambda_r = product over the modes of the
  * r-th column norms (a zero column keeps norm 1).  The MTTKRP, the Gram matrix and the product
- * with the R x R matrix run on the device in fp32 (Gram sums are accumulated in fp64); the
- * R x R algebra (Hadamard products, pseudo-inverse, norms, fit) runs on the host in fp64.
+ * with the R x R matrix run on the device in fp32 (Gram sums are accumulated in fp64); so does, in
+ * fp64, the R x R algebra (Hadamard products, pseudo-inverse, norms); the fit is formed on the host.
  * ------------------------------------------------------------------------------------------- */
 typedef struct hbcsf_als hbcsf_als;
 
@@ -316,20 +316,20 @@ int hbcsf_gram_noalloc(const float *a, uint64_t rows, int rank, double *s, void 
                                   Algorithm "CPD-ALS" may be put off: on return factors[m] can hold the
                                   unit-norm factor with column r multiplied by a norm the state remembers
                                   (lambda, the fit and the state's Gram matrices are those of the normalised
-                                  factors either way).  At rank 32 the product kernel then also forms the
+                                  factors either way).  Up to rank 32 the product kernel then also forms the
                                   new factor's Gram matrix, so the MTTKRP result is read once per mode
                                   update instead of twice.  A later call without the flag, or
                                   hbcsf_als_normalise, writes the unit-norm factors.  Use together with
                                   HBCSF_ALS_KEEP_GRAMS on the calls that follow.                        */
 
 /* Device workspace an ALS state needs for this tensor and rank: one [max dim][rank] fp32 matrix
- * for the MTTKRP result, two rank x rank matrices, one [rank] vector per mode and the Gram
+ * for the MTTKRP result, order + 5 rank x rank matrices, two [rank] vectors per mode and the Gram
  * computation's scratch (hbcsf_gram_workspace_bytes). */
 int hbcsf_als_workspace_bytes(const hbcsf_tensor *t, int rank, uint64_t *bytes);
 
 /* Creates an ALS state for an uploaded tensor.  workspace: device memory, 256-byte aligned, at
  * least hbcsf_als_workspace_bytes; the caller owns it and keeps it and the tensor alive and
- * untouched until hbcsf_als_free.  Allocates a few KB of pinned host memory.  rank as for
+ * untouched until hbcsf_als_free.  Allocates a few bytes of pinned host memory.  rank as for
  * hbcsf_mttkrp.  Errors: EINVAL, ESTATE (tensor not uploaded), ENOMEM (workspace too small),
  * EHIP. */
 int hbcsf_als_create(const hbcsf_tensor *t, int rank, void *workspace, uint64_t workspace_bytes,
@@ -341,8 +341,7 @@ int hbcsf_als_create(const hbcsf_tensor *t, int rank, void *workspace, uint64_t 
  * receives 1 - ||X - model|| / ||X|| computed from the Gram matrices and the last MTTKRP (the
  * nonzero coordinates are taken to be distinct).  flags: 0 or any of HBCSF_ALS_KEEP_GRAMS,
  * HBCSF_ALS_LAZY_NORMALISATION.
- * Blocking: the host reads an R x R matrix back for every mode, so the call returns after the
- * work on hip_stream has finished.  Two calls on one state must not overlap.  Errors: EINVAL,
+ * Blocking: the call returns after the work on hip_stream has finished.  Two calls on one state must not overlap.  Errors: EINVAL,
  * and whatever hbcsf_mttkrp reports. */
 int hbcsf_als_iteration(hbcsf_als *a, float *const *factors, float *lambda, int flags, double *fit,
                         void *hip_stream);
@@ -361,12 +360,12 @@ int hbcsf_als_normalise(hbcsf_als *a, float *const *factors, void *hip_stream);
 int hbcsf_als_run(hbcsf_als *a, float *const *factors, float *lambda, int max_iterations,
                   double tolerance, int *iterations_done, double *fit, void *hip_stream);
 
-/* Device/host time of the last iteration, summed over the modes, in milliseconds: ms[0] MTTKRP,
- * ms[1] Gram kernel with its read-back, ms[2] host R x R algebra, ms[3] product kernel with its
- * R x R upload. */
+/* Device time of the last iteration, summed over the modes, in milliseconds: ms[0] MTTKRP,
+ * ms[1] Gram kernel (0 when the product formed the Gram matrix), ms[2] R x R pseudo-inverse, ms[3]
+ * product kernel with the R x R algebra before it. */
 int hbcsf_als_phase_ms(const hbcsf_als *a, float ms[4]);
 
-/* Host only (no device call): the pseudo-inverse the mode update applies to the Hadamard product of
+/* Host only (no device call): the pseudo-inverse the mode update applies (on the device) to the Hadamard product of
  * Gram matrices (Eq. 3).  v, out: host [n][n] fp64, v symmetric, 1 <= n <= 128.  A safely positive
  * definite v is inverted by Cholesky factorisation; otherwise eigenvalues below 1e-15 of the largest
  * magnitude are treated as zero. */

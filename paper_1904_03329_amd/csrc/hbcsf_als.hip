@@ -1,16 +1,17 @@
 // CPD-ALS iteration around the MTTKRP kernels (Section II-B, Eq. 1-3, Algorithm "CPD-ALS"): the dense
-// steps of a mode update -- Gram matrix of a tall factor, product with the R x R pseudo-inverse -- as gfx950
-// kernels, the R x R algebra on the host in fp64, and the C entry points that tie them to hbcsf_mttkrp.
+// steps of a mode update -- Gram matrix of a tall factor, product with the R x R pseudo-inverse, the R x R algebra
+// between them -- as gfx950 kernels, and the C entry points that tie them to hbcsf_mttkrp.
 //
-// Per mode n the device does three passes over [I_n][R] data: the MTTKRP writes M, gram reads M, apply
-// reads M and writes the new factor.  Everything else is R x R work on the host:
-//   S = M^T M (device, fp64 accumulators)          V = Hadamard of the other factors' Gram matrices
-//   A_n = M V^+                                    hence A_n^T A_n = V^+ S V^+ without another pass.
-// The column norms of A_n are the square roots of that matrix's diagonal, so A_n can be written
-// normalised in the same pass that computes it.  The algorithm normalises after all modes are updated;
-// writing a factor normalised early scales the next MTTKRP's columns by a known diagonal, which the host
-// folds back into the R x R matrices (column scaling commutes with every step), so the result is that of
-// the algorithm's order up to rounding.
+// Every mode update runs on the device from end to end; the host only enqueues, and waits once at the end of an
+// iteration (or, where no iteration's fit decides anything, once at the end of the run):
+//   V = Hadamard of the other factors' Gram matrices, P = V^+      (small_pinv_kernel, fp64, one workgroup)
+//   M = MTTKRP
+//   ordinary call:   S = M^T M;  A_n^T A_n = V^+ S V^+ without another pass over the rows, and its diagonal gives the
+//                    column norms, so the product A_n = M P is written normalised in the pass that computes it
+//   put-off call:    A_n = M P unnormalised and G = A_n^T A_n (in the same pass for R <= 32)
+// The algorithm normalises after all modes are updated; writing a factor with another column scaling scales the next
+// MTTKRP's columns by a known diagonal, which is folded back into the R x R matrices (column scaling commutes with
+// every step), so the result is that of the algorithm's order up to rounding.
 
 #include <hip/hip_runtime.h>
 
@@ -20,6 +21,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "hbcsf.h"
@@ -38,15 +40,34 @@ constexpr int kGramFlush = 4;  // 32-row steps between two flushes of the fp32 p
 // every run: each block writes the partial sums of its rows (all R x R entries, zeros included) to its own
 // slot of a scratch buffer, and a second kernel adds the slots in block order.
 //
-// R = 32: the 32x32x2 fp32 matrix instruction.  One instruction consumes two rows of A: lane
-// (h = lane / 32, c = lane % 32) supplies A[row 2u + h][c] as both operands, since the left operand is the
-// transpose of the right one.  A wavefront walks a contiguous chunk of rows, sixteen coalesced 256-byte
-// loads in flight; partial sums leave fp32 every 128 rows.
+// R <= 32: the 32x32x2 fp32 matrix instruction over the matrix taken as rows of 32 floats (R < 32: 32 / R rows side by
+// side; their R x R Gram matrices are the diagonal blocks of the 32 x 32 product and are added when the slot is
+// written).  One instruction consumes two 32-float rows: lane (h = lane / 32, c = lane % 32) supplies element c of row
+// 2u + h as both operands, since the left operand is the transpose of the right one.  A wavefront walks a contiguous
+// chunk of rows, sixteen coalesced 256-byte loads in flight; partial sums leave fp32 every 128 of them.
 // Accumulator register v of a lane holds entry (8 (v / 4) + 4 h + v % 4, c).
 // ---------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void gram32_partial_kernel(const float* __restrict__ a, uint64_t rows,
-                                                             uint64_t rowsPerWave, double* __restrict__ partial) {
+// Writes a block's slot from its wavefronts' 32 x 32 sums: R x R entries, the diagonal blocks added up.
+template <int R>
+__device__ __forceinline__ void write_slot32(const double (*red)[1024], double* __restrict__ mine) {
+  for (int e = threadIdx.x; e < R * R; e += 256) {
+    double t = 0.0;
+#pragma unroll
+    for (int b = 0; b < 32 / R; ++b) {
+      const int at = (b * R + e / R) * 32 + b * R + e % R;
+      t += (red[0][at] + red[1][at]) + (red[2][at] + red[3][at]);
+    }
+    mine[e] = t;
+  }
+}
+
+// rows: of 32 floats, the last one perhaps cut at `total` floats.
+template <int R>
+__global__ __launch_bounds__(256) void gram32_partial_kernel(const float* __restrict__ a, uint64_t rows, uint64_t total,
+                                                             uint64_t rowsPerWave, double* __restrict__ partial,
+                                                             unsigned long long* __restrict__ stamp) {
   __shared__ double red[4][1024];
+  if (stamp && blockIdx.x == 0 && threadIdx.x == 0) *stamp = wall_clock64();
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int h = lane >> 5, c = lane & 31;
@@ -65,7 +86,7 @@ __global__ __launch_bounds__(256) void gram32_partial_kernel(const float* __rest
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         const uint64_t r = r0 + 2 * u + h;
-        x[u] = (r < r1) ? __builtin_nontemporal_load(a + r * 32 + c) : 0.f;
+        x[u] = (r < r1 && (R == 32 || r * 32 + c < total)) ? __builtin_nontemporal_load(a + r * 32 + c) : 0.f;
       }
 #pragma unroll
       for (int u = 0; u < 16; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[u], x[u], acc, 0, 0, 0);
@@ -76,84 +97,94 @@ __global__ __launch_bounds__(256) void gram32_partial_kernel(const float* __rest
 #pragma unroll
   for (int v = 0; v < 16; ++v) red[wave][(8 * (v / 4) + 4 * h + (v % 4)) * 32 + c] = acc64[v];
   __syncthreads();
-  double* mine = partial + (size_t)blockIdx.x * 1024;
-  for (int e = threadIdx.x; e < 1024; e += 256) mine[e] = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
+  write_slot32<R>(red, partial + (size_t)blockIdx.x * (R * R));
 }
 
-// s[e] = sum over the blocks' slots, in block order.  64 entries x 16 interleaved block subsets per workgroup;
-// the 16 subset sums are added in a fixed order.
-__global__ __launch_bounds__(1024) void gram_reduce_kernel(const double* __restrict__ partial, uint32_t nSlots,
-                                                           uint32_t rr, double* __restrict__ s) {
-  __shared__ double part[16][64];
-  const int el = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const uint32_t e = blockIdx.x * 64u + (uint32_t)el;
-  double t = 0.0;
-  if (e < rr)
-    for (uint32_t b = (uint32_t)q; b < nSlots; b += 16) t += partial[(size_t)b * rr + e];
-  part[q][el] = t;
-  __syncthreads();
-  if (q == 0 && e < rr) {
-    double sum = 0.0;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) sum += part[k][el];
-    s[e] = sum;
-  }
-}
+// R = 64, 128: S is symmetric, so a block's wavefronts take one pair (i <= j) of 32-column tiles each (3 or 10 of them)
+// and all walk the same rows, whose lines the first brings into the L1; a pair is accumulated as above, with tile i's
+// elements as left and tile j's as right operands, and written to both its places.
+constexpr int tile_pairs(int R) { return (R / 32) * (R / 32 + 1) / 2; }
 
-// R = 32: out = M P for blocks of 32 rows.  The contraction index is split as k = 16 h + t so that lane
-// (h, c) reads the 64 contiguous bytes M[row c of the block][16 h .. 16 h + 15] as its sixteen left
-// operands, and holds P[16 h + t][c] as the sixteen right operands for the whole kernel.
-__global__ __launch_bounds__(256) void apply32_kernel(const float* __restrict__ m, uint64_t rows,
-                                                      const float* __restrict__ p, float* __restrict__ out,
-                                                      uint64_t blocksPerWave) {
+template <int R>
+__global__ __launch_bounds__(64 * tile_pairs(R)) void gram_tiles_partial_kernel(const float* __restrict__ a, uint64_t rows,
+                                                                                uint64_t rowsPerBlock,
+                                                                                double* __restrict__ partial,
+                                                                                unsigned long long* __restrict__ stamp) {
+  if (stamp && blockIdx.x == 0 && threadIdx.x == 0) *stamp = wall_clock64();
   const int lane = threadIdx.x & 63;
   const int h = lane >> 5, c = lane & 31;
-  float pb[16];
+  int i = 0, j = threadIdx.x >> 6;            // wavefront number -> tile pair
+  while (j >= R / 32 - i) {
+    j -= R / 32 - i;
+    ++i;
+  }
+  j += i;
+  uint64_t r0 = (uint64_t)blockIdx.x * rowsPerBlock;
+  const uint64_t r1 = (r0 + rowsPerBlock < rows) ? r0 + rowsPerBlock : rows;
+  double acc64[16];
 #pragma unroll
-  for (int t = 0; t < 16; ++t) pb[t] = p[(16 * h + t) * 32 + c];
-  const uint64_t w = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const uint64_t nBlocks = (rows + 31) / 32;
-  uint64_t b = w * blocksPerWave;
-  const uint64_t bEnd = (b + blocksPerWave < nBlocks) ? b + blocksPerWave : nBlocks;
-  for (; b < bEnd; ++b) {
-    const uint64_t r = b * 32 + c;
-    float4 x[4];
-    if (r < rows) {
-      const float4* src = reinterpret_cast<const float4*>(m + r * 32 + 16 * h);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) x[q] = src[q];
-    } else {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) x[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
+  for (int v = 0; v < 16; ++v) acc64[v] = 0.0;
+  while (r0 < r1) {
     f32x16 acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    for (int it = 0; it < kGramFlush && r0 < r1; ++it, r0 += 32) {
+      float x[16], y[16];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[q].x, pb[4 * q + 0], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[q].y, pb[4 * q + 1], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[q].z, pb[4 * q + 2], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[q].w, pb[4 * q + 3], acc, 0, 0, 0);
+      for (int u = 0; u < 16; ++u) {
+        const uint64_t r = r0 + 2 * u + h;
+        x[u] = r < r1 ? a[r * R + 32 * i + c] : 0.f;
+        y[u] = r < r1 ? a[r * R + 32 * j + c] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < 16; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[u], y[u], acc, 0, 0, 0);
     }
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const uint64_t ro = b * 32 + (uint64_t)(8 * (v / 4) + 4 * h + (v % 4));
-      if (ro < rows) __builtin_nontemporal_store(acc[v], out + ro * 32 + c);
-    }
+    for (int v = 0; v < 16; ++v) acc64[v] += (double)acc[v];
+  }
+  double* mine = partial + (size_t)blockIdx.x * (R * R);
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int row = 32 * i + 8 * (v / 4) + 4 * h + (v % 4), col = 32 * j + c;
+    mine[row * R + col] = acc64[v];
+    if (i != j) mine[col * R + row] = acc64[v];
   }
 }
 
-// R = 32: out = M P as apply32_kernel, and in the same pass the Gram matrix of the rows just computed:
-// the 32 x 32 product tile leaves the matrix unit as sixteen registers whose lane (h, c) entries are
-// out[row 8 (v / 4) + 4 h + v % 4][c], i.e. for every v two different rows of the tile with lane c on
-// column c -- exactly the operand shape of gram32_partial_kernel -- so sixteen more matrix instructions
-// add the tile's out^T out without moving any data.  The partial Gram sums go to the block's scratch slot
-// (reduced by gram_reduce_kernel), so M is read once per mode update instead of twice.
-__global__ __launch_bounds__(256) void apply_gram32_kernel(const float* __restrict__ m, uint64_t rows,
-                                                           const float* __restrict__ p, float* __restrict__ out,
-                                                           uint64_t blocksPerWave, double* __restrict__ partial) {
-  __shared__ double red[4][1024];
+// s[e] = sum over the blocks' slots, in block order.  16 entries x 64 interleaved block subsets per workgroup (128
+// contiguous bytes per slot and enough workgroups to spread a few MB of slots over the chip; 64 x 16 took 11.5 us for
+// 780 slots of rank 32); the 64 subset sums are added in a fixed order.
+__global__ __launch_bounds__(1024) void gram_reduce_kernel(const double* __restrict__ partial, uint32_t nSlots,
+                                                           uint32_t rr, double* __restrict__ s) {
+  __shared__ double part[64][17];
+  const int el = threadIdx.x & 15, q = threadIdx.x >> 4;
+  const uint32_t e = blockIdx.x * 16u + (uint32_t)el;
+  double t = 0.0;
+  for (uint32_t b = (uint32_t)q; b < nSlots; b += 64) t += partial[(size_t)b * rr + e];
+  part[q][el] = t;
+  __syncthreads();
+  for (int half = 32; half > 0; half >>= 1) {
+    if (q < half) part[q][el] += part[q + half][el];
+    __syncthreads();
+  }
+  if (q == 0) s[e] = part[0][el];
+}
+
+// R <= 32: out = M P for blocks of 32 rows of 32 floats (R < 32: P is the block-diagonal matrix of 32 / R copies).  The
+// contraction index is split as k = 16 h + t so that lane (h, c) reads the 64 contiguous bytes M[row c of the
+// block][16 h .. 16 h + 15] as its sixteen left operands, and holds P[16 h + t][c] as the sixteen right operands for
+// the whole kernel.
+// GRAM: in the same pass the Gram matrix of the rows just computed: the 32 x 32 product tile leaves the matrix unit as
+// sixteen registers whose lane (h, c) entries are out[row 8 (v / 4) + 4 h + v % 4][c], i.e. for every v two different
+// rows of the tile with lane c on column c -- exactly the operand shape of gram32_partial_kernel -- so sixteen more
+// matrix instructions add the tile's out^T out without moving any data.  The partial Gram sums go to the block's
+// scratch slot (reduced by gram_reduce_kernel), so M is read once per mode update instead of twice.
+template <int R, bool GRAM>
+__global__ __launch_bounds__(256) void apply32_kernel(const float* __restrict__ m, uint64_t rows, uint64_t total,
+                                                      const float* __restrict__ p, float* __restrict__ out,
+                                                      uint64_t blocksPerWave, double* __restrict__ partial,
+                                                      unsigned long long* __restrict__ stamp) {
+  if (stamp && blockIdx.x == 0 && threadIdx.x == 0) *stamp = wall_clock64();
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int h = lane >> 5, c = lane & 31;
@@ -167,21 +198,26 @@ __global__ __launch_bounds__(256) void apply_gram32_kernel(const float* __restri
   double acc64[16];
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc64[v] = 0.0;
+  // the next block's rows are in flight while the matrix unit works on this one's
+  auto load = [&](float4 (&x)[4], uint64_t block) {
+    const uint64_t at = (block * 32 + c) * 32 + 16 * h;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      x[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (at + 4 * q < total) x[q] = *reinterpret_cast<const float4*>(m + at + 4 * q);
+    }
+  };
+  float4 next[4];
+  if (b < bEnd) load(next, b);
   while (b < bEnd) {
     f32x16 gacc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) gacc[v] = 0.f;
     for (int it = 0; it < kGramFlush && b < bEnd; ++it, ++b) {   // fp32 Gram sums over at most 128 rows
-      const uint64_t r = b * 32 + c;
       float4 x[4];
-      if (r < rows) {
-        const float4* src = reinterpret_cast<const float4*>(m + r * 32 + 16 * h);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) x[q] = src[q];
-      } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) x[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-      }
+      for (int q = 0; q < 4; ++q) x[q] = next[q];
+      if (b + 1 < bEnd) load(next, b + 1);
       f32x16 acc;
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[v] = 0.f;
@@ -194,24 +230,77 @@ __global__ __launch_bounds__(256) void apply_gram32_kernel(const float* __restri
       }
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const uint64_t ro = b * 32 + (uint64_t)(8 * (v / 4) + 4 * h + (v % 4));
-        if (ro < rows) __builtin_nontemporal_store(acc[v], out + ro * 32 + c);
+        const uint64_t to = (b * 32 + (uint64_t)(8 * (v / 4) + 4 * h + (v % 4))) * 32 + c;
+        if (to < total) __builtin_nontemporal_store(acc[v], out + to);
       }
-      // rows past the end of the matrix were computed from zeros and add nothing
+      if (GRAM) {
+        // rows past the end of the matrix were computed from zeros and add nothing
 #pragma unroll
-      for (int v = 0; v < 16; ++v) gacc = __builtin_amdgcn_mfma_f32_32x32x2f32(acc[v], acc[v], gacc, 0, 0, 0);
+        for (int v = 0; v < 16; ++v) gacc = __builtin_amdgcn_mfma_f32_32x32x2f32(acc[v], acc[v], gacc, 0, 0, 0);
+      }
     }
+    if (GRAM) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc64[v] += (double)gacc[v];
+      for (int v = 0; v < 16; ++v) acc64[v] += (double)gacc[v];
+    }
   }
+  if constexpr (GRAM) {
+    __shared__ double red[4][1024];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) red[wave][(8 * (v / 4) + 4 * h + (v % 4)) * 32 + c] = acc64[v];
-  __syncthreads();
-  double* mine = partial + (size_t)blockIdx.x * 1024;
-  for (int e = threadIdx.x; e < 1024; e += 256) mine[e] = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
+    for (int v = 0; v < 16; ++v) red[wave][(8 * (v / 4) + 4 * h + (v % 4)) * 32 + c] = acc64[v];
+    __syncthreads();
+    write_slot32<R>(red, partial + (size_t)blockIdx.x * (R * R));
+  }
 }
 
-// a[i][r] *= s[r]: the column normalisation of Algorithm "CPD-ALS" when it was put off (rank = 4 << gshift / ...).
+// R = 64, 128: out = M P; a wavefront takes 32 rows x 32 columns (tile column q = wavefront of the block), the block's
+// wavefronts share the rows.  The contraction index is split as k = (R / 2) h + t, so a lane reads 2 R contiguous bytes
+// of its row and keeps its R / 2 right operands for the whole kernel.
+template <int R>
+__global__ __launch_bounds__(2 * R) void apply_tiles_kernel(const float* __restrict__ m, uint64_t rows,
+                                                            const float* __restrict__ p, float* __restrict__ out,
+                                                            uint64_t rowBlocksPerBlock,
+                                                            unsigned long long* __restrict__ stamp) {
+  if (stamp && blockIdx.x == 0 && threadIdx.x == 0) *stamp = wall_clock64();
+  constexpr int K = R / 2;
+  const int lane = threadIdx.x & 63;
+  const int q = threadIdx.x >> 6;
+  const int h = lane >> 5, c = lane & 31;
+  float pb[K];
+#pragma unroll
+  for (int t = 0; t < K; ++t) pb[t] = p[(K * h + t) * R + 32 * q + c];
+  const uint64_t nBlocks = (rows + 31) / 32;
+  uint64_t b = (uint64_t)blockIdx.x * rowBlocksPerBlock;
+  const uint64_t bEnd = (b + rowBlocksPerBlock < nBlocks) ? b + rowBlocksPerBlock : nBlocks;
+  for (; b < bEnd; ++b) {
+    const uint64_t r = b * 32 + c;
+    float4 x[K / 4];
+#pragma unroll
+    for (int t = 0; t < K / 4; ++t) x[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (r < rows) {
+      const float4* src = reinterpret_cast<const float4*>(m + r * R + K * h);
+#pragma unroll
+      for (int t = 0; t < K / 4; ++t) x[t] = src[t];
+    }
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+    for (int t = 0; t < K / 4; ++t) {
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[t].x, pb[4 * t + 0], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[t].y, pb[4 * t + 1], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[t].z, pb[4 * t + 2], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[t].w, pb[4 * t + 3], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const uint64_t ro = b * 32 + (uint64_t)(8 * (v / 4) + 4 * h + (v % 4));
+      if (ro < rows) __builtin_nontemporal_store(acc[v], out + ro * R + 32 * q + c);
+    }
+  }
+}
+
+// a[i][r] *= s[r]: the column normalisation of Algorithm "CPD-ALS" when it was put off.
 __global__ __launch_bounds__(256) void scale_columns_kernel(float4* __restrict__ a, uint64_t nvec,
                                                             const float* __restrict__ s, int vecPerRow) {
   for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < nvec; i += (uint64_t)gridDim.x * 256) {
@@ -219,61 +308,6 @@ __global__ __launch_bounds__(256) void scale_columns_kernel(float4* __restrict__
     float4 v = a[i];
     v.x *= sc.x; v.y *= sc.y; v.z *= sc.z; v.w *= sc.w;
     a[i] = v;
-  }
-}
-
-// ---------------------------------------------------------------------------------------------------
-// Other ranks: plain vector-ALU kernels (correct for any R in the supported list, not tuned).
-// ---------------------------------------------------------------------------------------------------
-template <int R>
-__global__ __launch_bounds__(256) void gram_generic_partial_kernel(const float* __restrict__ a, uint64_t rows,
-                                                                   uint64_t rowsPerBlock, double* __restrict__ partial) {
-  constexpr int kTile = 32;                                   // rows staged per step
-  constexpr int kPer = (R * R + 255) / 256;                   // entries of S per thread
-  __shared__ float tile[kTile][R + 1];
-  double acc[kPer];
-#pragma unroll
-  for (int e = 0; e < kPer; ++e) acc[e] = 0.0;
-  uint64_t r0 = (uint64_t)blockIdx.x * rowsPerBlock;
-  const uint64_t r1 = (r0 + rowsPerBlock < rows) ? r0 + rowsPerBlock : rows;
-  for (; r0 < r1; r0 += kTile) {
-    __syncthreads();
-    for (int e = threadIdx.x; e < kTile * R; e += 256) {
-      const uint64_t r = r0 + (uint64_t)(e / R);
-      tile[e / R][e % R] = (r < r1) ? a[r * R + (uint64_t)(e % R)] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-      const int id = threadIdx.x + 256 * e;
-      if (id < R * R) {
-        const int i = id / R, j = id % R;
-        float t = 0.f;
-#pragma unroll 8
-        for (int k = 0; k < kTile; ++k) t = fmaf(tile[k][i], tile[k][j], t);
-        acc[e] += (double)t;
-      }
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < kPer; ++e) {
-    const int id = threadIdx.x + 256 * e;
-    if (id < R * R) partial[(size_t)blockIdx.x * (R * R) + id] = acc[e];
-  }
-}
-
-template <int R>
-__global__ __launch_bounds__(256) void apply_generic_kernel(const float* __restrict__ m, uint64_t rows,
-                                                            const float* __restrict__ p,
-                                                            float* __restrict__ out) {
-  const uint64_t total = rows * (uint64_t)R;
-  for (uint64_t id = (uint64_t)blockIdx.x * 256 + threadIdx.x; id < total; id += (uint64_t)gridDim.x * 256) {
-    const uint64_t r = id / R;
-    const int c = (int)(id % R);
-    float t = 0.f;
-#pragma unroll 8
-    for (int k = 0; k < R; ++k) t = fmaf(m[r * R + k], p[k * R + c], t);
-    out[id] = t;
   }
 }
 
@@ -287,53 +321,94 @@ uint32_t gram_slots_for(int rank, uint64_t scratchBytes) {
   return (uint32_t)(fit < kGramSlotsMax ? fit : kGramSlotsMax);
 }
 
+// The matrix as rows of 32 floats (R < 32: 32 / R rows in each).
+uint64_t rows_of_32(uint64_t rows, int rank) { return (rows * (uint64_t)rank + 31) / 32; }
+
+void launch_reduce(const double* scratch, uint32_t used, int rank, double* s, hipStream_t st) {
+  const uint32_t rr = (uint32_t)(rank * rank);
+  hipLaunchKernelGGL(gram_reduce_kernel, dim3(rr / 16), dim3(1024), 0, st, scratch, used, rr, s);
+}
+
 // s (device, [R][R] fp64) = a^T a; scratch holds `slots` R x R fp64 partial sums (slots >= 1).  Nothing has to be
 // cleared between calls: every launched block writes its whole slot, and only the launched blocks' slots are read.
 void launch_gram(const float* a, uint64_t rows, int rank, double* scratch, uint32_t slots, double* s, int numCU,
-                 hipStream_t st) {
-  const uint32_t rr = (uint32_t)(rank * rank);
+                 hipStream_t st, unsigned long long* stamp = nullptr) {
   uint32_t used = 0;
-  if (rows > 0 && rank == 32) {
-    // enough wavefronts to cover the memory latency, long enough chunks to amortise the final reduction
+  if (rows > 0 && rank <= 32) {
+    // a wavefront takes at least one fp32 accumulation (128 rows), so that the slots stay a small part of the traffic
+    const uint64_t n = rows_of_32(rows, rank), total = rows * (uint64_t)rank;
     uint64_t waves = (uint64_t)numCU * 16;
     if (waves > (uint64_t)slots * 4) waves = (uint64_t)slots * 4;
-    uint64_t per = (rows + waves - 1) / waves;
+    uint64_t per = (n + waves - 1) / waves;
     per = (per + 31) / 32 * 32;
-    if (per < 256) per = 256;
-    const uint64_t nWaves = (rows + per - 1) / per;
+    if (per < 32 * kGramFlush && slots > 1) per = 32 * kGramFlush;
+    const uint64_t nWaves = (n + per - 1) / per;
     used = (uint32_t)((nWaves + 3) / 4);
-    hipLaunchKernelGGL(gram32_partial_kernel, dim3(used), dim3(256), 0, st, a, rows, per, scratch);
+    switch (rank) {
+      case 8: hipLaunchKernelGGL(gram32_partial_kernel<8>, dim3(used), dim3(256), 0, st, a, n, total, per, scratch, stamp); break;
+      case 16: hipLaunchKernelGGL(gram32_partial_kernel<16>, dim3(used), dim3(256), 0, st, a, n, total, per, scratch, stamp); break;
+      default: hipLaunchKernelGGL(gram32_partial_kernel<32>, dim3(used), dim3(256), 0, st, a, n, total, per, scratch, stamp); break;
+    }
   } else if (rows > 0) {
-    uint64_t blocks = (uint64_t)numCU * 8;
+    uint64_t blocks = (uint64_t)numCU * 4;
     if (blocks > slots) blocks = slots;
     uint64_t per = (rows + blocks - 1) / blocks;
     per = (per + 31) / 32 * 32;
+    if (per < 32 * kGramFlush && slots > 1) per = 32 * kGramFlush;
     used = (uint32_t)((rows + per - 1) / per);
-    switch (rank) {
-      case 8: hipLaunchKernelGGL(gram_generic_partial_kernel<8>, dim3(used), dim3(256), 0, st, a, rows, per, scratch); break;
-      case 16: hipLaunchKernelGGL(gram_generic_partial_kernel<16>, dim3(used), dim3(256), 0, st, a, rows, per, scratch); break;
-      case 64: hipLaunchKernelGGL(gram_generic_partial_kernel<64>, dim3(used), dim3(256), 0, st, a, rows, per, scratch); break;
-      default: hipLaunchKernelGGL(gram_generic_partial_kernel<128>, dim3(used), dim3(256), 0, st, a, rows, per, scratch); break;
-    }
+    if (rank == 64)
+      hipLaunchKernelGGL(gram_tiles_partial_kernel<64>, dim3(used), dim3(64 * tile_pairs(64)), 0, st, a, rows, per, scratch, stamp);
+    else
+      hipLaunchKernelGGL(gram_tiles_partial_kernel<128>, dim3(used), dim3(64 * tile_pairs(128)), 0, st, a, rows, per, scratch, stamp);
   }
   // with no rows no slot is read and the result is all zeros
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3((rr + 63) / 64), dim3(1024), 0, st, scratch, used, rr, s);
+  launch_reduce(scratch, used, rank, s, st);
 }
 
-// R = 32 only: out = m p and g (device, [32][32] fp64) = out^T out in one pass over m.
-void launch_apply_gram32(const float* m, uint64_t rows, const float* p, float* out, double* scratch,
-                         uint32_t slots, double* g, int numCU, hipStream_t st) {
+template <int R>
+void launch_apply32(const float* m, uint64_t n, uint64_t total, const float* p, float* out, uint64_t per, uint32_t blocks,
+                    double* scratch, unsigned long long* stamp, hipStream_t st) {
+  if (scratch)
+    hipLaunchKernelGGL((apply32_kernel<R, true>), dim3(blocks), dim3(256), 0, st, m, n, total, p, out, per, scratch, stamp);
+  else
+    hipLaunchKernelGGL((apply32_kernel<R, false>), dim3(blocks), dim3(256), 0, st, m, n, total, p, out, per, scratch, stamp);
+}
+
+// out = m p, and with g: g (device, [R][R] fp64) = out^T out (in the same pass over m for R <= 32).  p: [R][R], for
+// R < 32 the [32][32] block-diagonal matrix of it.
+void launch_apply(const float* m, uint64_t rows, int rank, const float* p, float* out, double* scratch, uint32_t slots,
+                  double* g, int numCU, hipStream_t st, unsigned long long* stamp) {
+  if (rank > 32) {
+    if (rows > 0) {
+      const uint64_t nBlocks = (rows + 31) / 32;
+      uint64_t blocks = (uint64_t)numCU * 16;
+      const uint64_t per = (nBlocks + blocks - 1) / blocks;
+      blocks = (nBlocks + per - 1) / per;
+      if (rank == 64)
+        hipLaunchKernelGGL(apply_tiles_kernel<64>, dim3((uint32_t)blocks), dim3(128), 0, st, m, rows, p, out, per, stamp);
+      else
+        hipLaunchKernelGGL(apply_tiles_kernel<128>, dim3((uint32_t)blocks), dim3(256), 0, st, m, rows, p, out, per, stamp);
+    }
+    if (g) launch_gram(out, rows, rank, scratch, slots, g, numCU, st);
+    return;
+  }
   uint32_t used = 0;
   if (rows > 0) {
-    const uint64_t nBlocks = (rows + 31) / 32;
+    const uint64_t n = rows_of_32(rows, rank), total = rows * (uint64_t)rank;
+    const uint64_t nBlocks = (n + 31) / 32;
     uint64_t waves = (uint64_t)numCU * 32;
-    if (waves > (uint64_t)slots * 4) waves = (uint64_t)slots * 4;
-    const uint64_t per = (nBlocks + waves - 1) / waves;
-    const uint64_t nWaves = (nBlocks + per - 1) / per;
-    used = (uint32_t)((nWaves + 3) / 4);
-    hipLaunchKernelGGL(apply_gram32_kernel, dim3(used), dim3(256), 0, st, m, rows, p, out, per, scratch);
+    if (g && waves > (uint64_t)slots * 4) waves = (uint64_t)slots * 4;
+    uint64_t per = (nBlocks + waves - 1) / waves;
+    if (g && per < 2) per = 2;   // fewer slots to add up
+    used = (uint32_t)(((nBlocks + per - 1) / per + 3) / 4);
+    double* sc = g ? scratch : nullptr;
+    switch (rank) {
+      case 8: launch_apply32<8>(m, n, total, p, out, per, used, sc, stamp, st); break;
+      case 16: launch_apply32<16>(m, n, total, p, out, per, used, sc, stamp, st); break;
+      default: launch_apply32<32>(m, n, total, p, out, per, used, sc, stamp, st); break;
+    }
   }
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3(16), dim3(1024), 0, st, scratch, used, 1024u, g);
+  if (g) launch_reduce(scratch, used, rank, g, st);
 }
 
 void launch_scale_columns(float* a, uint64_t rows, int rank, const float* s, int numCU, hipStream_t st) {
@@ -346,32 +421,412 @@ void launch_scale_columns(float* a, uint64_t rows, int rank, const float* s, int
                      nvec, s, rank / 4);
 }
 
-void launch_apply(const float* m, uint64_t rows, int rank, const float* p, float* out, int numCU,
-                  hipStream_t st) {
-  if (rows == 0) return;
-  if (rank == 32) {
-    const uint64_t nBlocks = (rows + 31) / 32;
-    uint64_t waves = (uint64_t)numCU * 32;
-    const uint64_t per = (nBlocks + waves - 1) / waves;
-    const uint64_t nWaves = (nBlocks + per - 1) / per;
-    hipLaunchKernelGGL(apply32_kernel, dim3((unsigned)((nWaves + 3) / 4)), dim3(256), 0, st, m, rows, p, out,
-                       per);
-    return;
+// ---------------------------------------------------------------------------------------------------
+// R x R algebra on the device (fp64).  State per mode m, in the caller's workspace: gram[m] = Gram matrix of the stored
+// factor, scale[m] = c_m (the algorithm's factor is the stored one with column r divided by c_m[r]), norm[m] = column
+// norms of the last update.  These kernels are one workgroup each (the work is R^3 at most 2 M multiply-adds in a serial
+// chain of R steps); what they replace is a copy to the host, a wait, and a copy back for every mode update.
+// ---------------------------------------------------------------------------------------------------
+struct SmallState {
+  double* gram[HBCSF_MAX_ORDER];
+  double* scale[HBCSF_MAX_ORDER];
+  double* norm[HBCSF_MAX_ORDER];
+  int order;
+};
+
+// V = Hadamard product over the modes m != n of the algorithm's Gram matrices, entry (i, j)
+template <int R>
+__device__ __forceinline__ double v_entry(const SmallState& st, int n, int i, int j) {
+  double v = 1.0;
+  for (int m = 0; m < st.order; ++m)
+    if (m != n) v *= st.gram[m][i * R + j] / (st.scale[m][i] * st.scale[m][j]);
+  return v;
+}
+
+// d_r = product over the other modes of 1 / c_m[r]: M of the algorithm = M of the stored factors, columns times d
+template <int R>
+__device__ __forceinline__ double d_entry(const SmallState& st, int n, int r) {
+  double d = 1.0;
+  for (int m = 0; m < st.order; ++m)
+    if (m != n) d /= st.scale[m][r];
+  return d;
+}
+
+// p: right-hand matrix of the product kernels, P[i][j] in [R][R], or for R < 32 block-diagonal in [32][32]
+template <int R>
+__device__ __forceinline__ void put_p(float* __restrict__ p, int i, int j, float v) {
+  if (R >= 32) {
+    p[i * R + j] = v;
+  } else {
+    for (int b = 0; b < 32 / R; ++b) p[(b * R + i) * 32 + b * R + j] = v;
   }
-  const uint64_t total = rows * (uint64_t)rank;
-  uint64_t want = (total + 255) / 256;
-  const uint64_t cap = (uint64_t)numCU * 64;
-  const unsigned grid = (unsigned)(want < cap ? want : cap);
+}
+
+constexpr int small_threads(int R) { return R <= 32 ? 64 : R == 64 ? 256 : 1024; }  // (R / 4)^2, at least a wavefront
+constexpr int entry_threads(int R) { return R * R < 1024 ? R * R : 1024; }           // for kernels that walk R x R entries
+
+// Pseudo-inverse of the symmetric matrix V by cyclic Jacobi rotations, n / 2 disjoint pairs at a time (round-robin
+// pairing): only when V is not safely positive definite.  a, q: [R][R] scratch.  Eigenvalues below 1e-15 of the largest
+// magnitude count as zero (the cut-off numpy.linalg.pinv applies to singular values).
+template <int R>
+__device__ void jacobi_pinv(const SmallState& st, int n, double* __restrict__ a, double* __restrict__ q,
+                            double* __restrict__ out, double* lds /* R + 2 */, double* part /* one per thread */) {
+  constexpr int T = small_threads(R);
+  const int tid = threadIdx.x;
+  double* cs = lds;          // [R / 2] cosines, then [R / 2] sines
+  double* red = lds + R;     // two sums
+  for (int e = tid; e < R * R; e += T) {
+    a[e] = v_entry<R>(st, n, e / R, e % R);
+    q[e] = e / R == e % R ? 1.0 : 0.0;
+  }
+  __syncthreads();
+  for (int sweep = 0; sweep < 60; ++sweep) {
+    for (int diagonal = 0; diagonal < 2; ++diagonal) {
+      double sum = 0.0;
+      for (int e = tid; e < R * R; e += T)
+        if ((e / R == e % R) == (diagonal == 1)) sum += a[e] * a[e];
+      part[tid] = sum;
+      __syncthreads();
+      for (int half = T / 2; half > 0; half >>= 1) {
+        if (tid < half) part[tid] += part[tid + half];
+        __syncthreads();
+      }
+      if (tid == 0) red[diagonal] = part[0];
+      __syncthreads();
+    }
+    const bool done = red[0] <= 1e-30 * red[1] || red[0] == 0.0;
+    __syncthreads();
+    if (done) break;
+    for (int round = 0; round < R - 1; ++round) {
+      // pair k of this round: players 0 (fixed) and 1 .. R-1 (rotating)
+      auto player = [&](int slot) { return slot == 0 ? 0 : 1 + (slot - 1 + round) % (R - 1); };
+      for (int k = tid; k < R / 2; k += T) {
+        const int x = player(k), y = player(R - 1 - k);
+        const int p = x < y ? x : y, r = x < y ? y : x;
+        const double apr = a[p * R + r];
+        double c = 1.0, sn = 0.0;
+        if (apr != 0.0) {
+          const double theta = (a[r * R + r] - a[p * R + p]) / (2.0 * apr);
+          const double t = (theta >= 0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
+          c = 1.0 / sqrt(t * t + 1.0);
+          sn = t * c;
+        }
+        cs[k] = c;
+        cs[R / 2 + k] = sn;
+      }
+      __syncthreads();
+      for (int w = tid; w < R * (R / 2); w += T) {  // columns p, r of a and q
+        const int k = w % (R / 2), row = w / (R / 2);
+        const int x = player(k), y = player(R - 1 - k);
+        const int p = x < y ? x : y, r = x < y ? y : x;
+        const double c = cs[k], sn = cs[R / 2 + k];
+        const double ap = a[row * R + p], ar = a[row * R + r];
+        a[row * R + p] = c * ap - sn * ar;
+        a[row * R + r] = sn * ap + c * ar;
+        const double qp = q[row * R + p], qr = q[row * R + r];
+        q[row * R + p] = c * qp - sn * qr;
+        q[row * R + r] = sn * qp + c * qr;
+      }
+      __syncthreads();
+      for (int w = tid; w < R * (R / 2); w += T) {  // rows p, r of a
+        const int k = w / R, col = w % R;
+        const int x = player(k), y = player(R - 1 - k);
+        const int p = x < y ? x : y, r = x < y ? y : x;
+        const double c = cs[k], sn = cs[R / 2 + k];
+        const double ap = a[p * R + col], ar = a[r * R + col];
+        a[p * R + col] = c * ap - sn * ar;
+        a[r * R + col] = sn * ap + c * ar;
+      }
+      __syncthreads();
+    }
+  }
+  if (tid == 0) {
+    double wmax = 0.0;
+    for (int k = 0; k < R; ++k) wmax = fmax(wmax, fabs(a[k * R + k]));
+    red[0] = wmax;
+  }
+  __syncthreads();
+  const double wmax = red[0];
+  for (int e = tid; e < R * R; e += T) {
+    double t = 0.0;
+    for (int k = 0; k < R; ++k) {
+      const double w = a[k * R + k];
+      if (fabs(w) > 1e-15 * wmax) t += q[(e / R) * R + k] * (1.0 / w) * q[(e % R) * R + k];
+    }
+    out[e] = t;
+  }
+  __syncthreads();
+}
+
+// 1 / x for a normal positive x: the hardware's estimate and two Newton steps (relative error near 2^-53).
+__device__ __forceinline__ double reciprocal(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+
+// vp = V^+ for the update of mode n, and p = diag(d) V^+ (the right-hand matrix of a put-off update; an ordinary update
+// overwrites it).  V is inverted in place by R sweep steps without pivoting,
+//     d = a_kk;  a_kk <- -1 / d;  a_ik, a_ki <- a_ik / d;  a_ij <- a_ij - a_ik a_kj / d     (after all: -V^-1)
+// -- for a positive definite matrix as accurate as the Cholesky route, and its pivots are the squares of the Cholesky
+// factor's diagonal.  The matrix stays symmetric, so a step needs one row: each thread keeps a 4 x 4 tile in registers,
+// the threads that hold row k publish it in LDS (two buffers in turn, one barrier a step; R <= 32 is one wavefront), and
+// every thread reads the 4 + 4 entries its tile needs.  The chain of R steps is latency: the next pivot is formed from
+// the published row by every thread, so that its reciprocal is under way while the tiles are updated (rank 32: 25 us in
+// the first form, one entry per thread and a division in the chain).
+// A pivot that is not safely positive sends the whole workgroup to the eigenvalue form.
+// resetScale: after the product the stored factor is the unnormalised one, so its column scale becomes 1.
+template <int R>
+__global__ __launch_bounds__(small_threads(R)) void small_pinv_kernel(SmallState st, int n, double* __restrict__ vp,
+                                                                      float* __restrict__ p, double* __restrict__ ja,
+                                                                      double* __restrict__ jq, int resetScale,
+                                                                      unsigned long long* __restrict__ stamp) {
+  constexpr int T = small_threads(R), W = R / 4;
+  __shared__ __align__(16) double rowOf[2][R + 2];   // row k, then entry (k + 1, k + 1)
+  __shared__ double diag[R], d[R], jl[R + 2], part[T];
+  __shared__ double dmaxShared;
+  const int tid = threadIdx.x;
+  if (tid == 0 && stamp) stamp[0] = wall_clock64();
+  const bool owns = tid < W * W;
+  const int i0 = 4 * (tid / W), j0 = 4 * (tid % W);
+  double x[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[i][j] = owns ? 1.0 : 0.0;
+  if (owns) {
+    for (int m = 0; m < st.order; ++m) {
+      if (m == n) continue;
+      const double* g = st.gram[m];
+      double ci[4], cj[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        ci[i] = 1.0 / st.scale[m][i0 + i];
+        cj[i] = 1.0 / st.scale[m][j0 + i];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[i][j] *= g[(i0 + i) * R + j0 + j] * (ci[i] * cj[j]);
+    }
+    if (i0 == j0) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) diag[i0 + i] = x[i][i];
+    }
+  }
+  for (int r = tid; r < R; r += T) d[r] = d_entry<R>(st, n, r);
+  __syncthreads();
+  if (tid < 64) {
+    double m = 0.0;
+    for (int r = tid; r < R; r += 64) m = fmax(m, diag[r]);
+    for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
+    if (tid == 0) dmaxShared = m;
+  }
+  __syncthreads();
+  const double least = 1e-10 * dmaxShared;
+  double pivot = diag[0];
+  bool good = true;
+  for (int kb = 0; kb < R && good; kb += 4) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = kb + q;
+      double* row = rowOf[k & 1];
+      if (owns && i0 == kb) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) row[j0 + j] = x[q][j];
+        if (q < 3 && j0 == kb) row[R] = x[q < 3 ? q + 1 : 0][q < 3 ? q + 1 : 0];
+      }
+      if (q == 3 && owns && i0 == kb + 4 && j0 == kb + 4) row[R] = x[0][0];
+      if (!(pivot > least)) good = false;   // the same for every thread
+      const double inv = reciprocal(pivot);
+      __syncthreads();
+      double ri[4], rj[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        ri[i] = row[i0 + i];
+        rj[i] = row[j0 + i];
+      }
+      const double nextRow = k + 1 < R ? row[k + 1] : 0.0;
+      pivot = fma(-nextRow * inv, nextRow, row[R]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const double f = ri[i] * inv;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const bool inRow = i == q && i0 == kb, inCol = j == q && j0 == kb;
+          const double swept = fma(-f, rj[j], x[i][j]);
+          if (i == q || j == q) x[i][j] = inRow ? (inCol ? -inv : rj[j] * inv) : inCol ? f : swept;
+          else x[i][j] = swept;
+        }
+      }
+    }
+  }
+  if (good) {
+    if (owns) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          x[i][j] = -x[i][j];
+          vp[(i0 + i) * R + j0 + j] = x[i][j];
+        }
+    }
+  } else {
+    __syncthreads();
+    jacobi_pinv<R>(st, n, ja, jq, vp, jl, part);
+    if (owns) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[i][j] = vp[(i0 + i) * R + j0 + j];
+    }
+  }
+  if (owns) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) put_p<R>(p, i0 + i, j0 + j, (float)(d[i0 + i] * x[i][j]));
+  }
+  if (resetScale)
+    for (int r = tid; r < R; r += T) st.scale[n][r] = 1.0;
+  if (tid == 0 && stamp) stamp[1] = wall_clock64();
+}
+
+// c = a b (fp64, [R][R]); one entry per thread.  da: null, or b's rows and columns are scaled by d first (S of the
+// algorithm from S of the stored factors).
+template <int R>
+__global__ __launch_bounds__(256) void small_matmul_kernel(const double* __restrict__ a, const double* __restrict__ b,
+                                                           double* __restrict__ c, SmallState st, int n, int scaled,
+                                                            unsigned long long* __restrict__ stamp) {
+  const int id = blockIdx.x * 256 + threadIdx.x;
+  if (id == 0 && stamp) *stamp = wall_clock64();
+  if (id >= R * R) return;
+  const int i = id / R, j = id % R;
+  double t = 0.0;
+  for (int k = 0; k < R; ++k) {
+    double bk = b[k * R + j];
+    if (scaled) bk *= d_entry<R>(st, n, k);
+    t = fma(a[i * R + k], bk, t);
+  }
+  if (scaled) t *= d_entry<R>(st, n, j);
+  c[id] = t;
+}
+
+// Ordinary update of mode n: t = A_n^T A_n = V^+ S V^+.  The column norms, the matrix that writes the factor with
+// unit-norm columns, the stored factor's Gram matrix and scale, and (last mode) <X, model> = trace(S V^+).
+template <int R>
+__global__ __launch_bounds__(entry_threads(R)) void small_update_kernel(SmallState st, int n, const double* __restrict__ t,
+                                                                        const double* __restrict__ vp,
+                                                                        const double* __restrict__ s, float* __restrict__ p,
+                                                                        double* __restrict__ inner) {
+  constexpr int T = entry_threads(R);
+  __shared__ double norm[R], d[R], part[T];
+  const int tid = threadIdx.x;
+  for (int r = tid; r < R; r += T) {
+    const double g = t[r * R + r];
+    norm[r] = g > 0.0 ? sqrt(g) : 1.0;
+    d[r] = d_entry<R>(st, n, r);
+  }
+  __syncthreads();
+  double sum = 0.0;
+  for (int e = tid; e < R * R; e += T) {
+    const int i = e / R, j = e % R;
+    put_p<R>(p, i, j, (float)(d[i] * vp[e] / norm[j]));
+    st.gram[n][e] = t[e] / (norm[i] * norm[j]);
+    sum += s[e] * d[i] * d[j] * vp[j * R + i];
+  }
+  part[tid] = sum;
+  __syncthreads();
+  for (int half = T / 2; half > 0; half >>= 1) {
+    if (tid < half) part[tid] += part[tid + half];
+    __syncthreads();
+  }
+  if (tid == 0) *inner = part[0];
+  for (int r = tid; r < R; r += T) {
+    st.norm[n][r] = norm[r];
+    st.scale[n][r] = 1.0 / norm[r];
+  }
+}
+
+// End of an iteration: lambda_r = product over the modes of the column norms, the model's squared norm from the Gram
+// matrices of the unnormalised factors, <X, model>; then the algorithm's closing normalisation c_m <- c_m norms_m (which
+// makes c_m = 1 where the factor was written normalised).  report (host memory): {<X, model>, ||model||^2}.
+template <int R>
+__global__ __launch_bounds__(entry_threads(R)) void small_finish_kernel(SmallState st, int lazy, const double* __restrict__ inner,
+                                                                        float* __restrict__ lambda,
+                                                                        double* __restrict__ report,
+                                                                        unsigned long long* __restrict__ stamp) {
+  constexpr int T = entry_threads(R);
+  __shared__ double part[T];
+  const int tid = threadIdx.x;
+  if (tid == 0) *stamp = wall_clock64();
+  double model = 0.0;
+  for (int e = tid; e < R * R; e += T) {
+    const int i = e / R, j = e % R;
+    double g = 1.0;
+    for (int m = 0; m < st.order; ++m) g *= st.gram[m][e] / (st.scale[m][i] * st.scale[m][j]);
+    model += g;
+  }
+  part[tid] = model;
+  __syncthreads();
+  for (int half = T / 2; half > 0; half >>= 1) {
+    if (tid < half) part[tid] += part[tid + half];
+    __syncthreads();
+  }
+  if (tid == 0) {
+    // put-off updates: V^+ V V^+ = V^+, so <X, model> = trace(V A_n^T A_n), which is the same sum
+    report[0] = lazy ? part[0] : *inner;
+    report[1] = part[0];
+  }
+  for (int r = tid; r < R; r += T) {
+    double lam = 1.0;
+    for (int m = 0; m < st.order; ++m) {
+      double norm;
+      if (lazy) {
+        const double g = st.gram[m][r * R + r];
+        norm = g > 0.0 ? sqrt(g) : 1.0;
+        st.scale[m][r] = norm;
+      } else {
+        norm = st.norm[m][r];
+        st.scale[m][r] = 1.0;
+      }
+      lam *= norm;
+    }
+    if (lambda) lambda[r] = (float)lam;
+  }
+}
+
+// Column factors of the put-off normalisation of mode m, with the Gram matrix and scale that go with the scaled factor.
+template <int R>
+__global__ __launch_bounds__(entry_threads(R)) void small_normalise_kernel(SmallState st, int m, float* __restrict__ factor) {
+  constexpr int T = entry_threads(R);
+  const int tid = threadIdx.x;
+  for (int e = tid; e < R * R; e += T) st.gram[m][e] /= st.scale[m][e / R] * st.scale[m][e % R];
+  for (int r = tid; r < R; r += T) factor[r] = (float)(1.0 / st.scale[m][r]);
+  __syncthreads();
+  for (int r = tid; r < R; r += T) st.scale[m][r] = 1.0;
+}
+
+// The factors are taken as they are: every column scale 1, and p cleared (R < 32 writes only its diagonal blocks).
+__global__ __launch_bounds__(256) void small_reset_kernel(SmallState st, int rank, float* __restrict__ p, int pCount) {
+  for (int e = threadIdx.x; e < st.order * rank; e += 256) st.scale[e / rank][e % rank] = 1.0;
+  for (int e = threadIdx.x; e < pCount; e += 256) p[e] = 0.f;
+}
+
+// calls `f` with the rank as a compile-time constant
+template <typename F>
+void with_rank(int rank, F&& f) {
   switch (rank) {
-    case 8: hipLaunchKernelGGL(apply_generic_kernel<8>, dim3(grid), dim3(256), 0, st, m, rows, p, out); break;
-    case 16: hipLaunchKernelGGL(apply_generic_kernel<16>, dim3(grid), dim3(256), 0, st, m, rows, p, out); break;
-    case 64: hipLaunchKernelGGL(apply_generic_kernel<64>, dim3(grid), dim3(256), 0, st, m, rows, p, out); break;
-    default: hipLaunchKernelGGL(apply_generic_kernel<128>, dim3(grid), dim3(256), 0, st, m, rows, p, out); break;
+    case 8: f(std::integral_constant<int, 8>()); break;
+    case 16: f(std::integral_constant<int, 16>()); break;
+    case 32: f(std::integral_constant<int, 32>()); break;
+    case 64: f(std::integral_constant<int, 64>()); break;
+    default: f(std::integral_constant<int, 128>()); break;
   }
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Host R x R algebra (fp64)
+// Host R x R pseudo-inverse (fp64): hbcsf_sym_pinv
 // ---------------------------------------------------------------------------------------------------
 using Mat = std::vector<double>;
 
@@ -480,16 +935,6 @@ Mat pinv_of_gram_product(const Mat& v, int n) {
   return sym_pinv(v, n);
 }
 
-Mat matmul(const Mat& a, const Mat& b, int n) {
-  Mat c((size_t)n * n, 0.0);
-  for (int i = 0; i < n; ++i)
-    for (int k = 0; k < n; ++k) {
-      const double aik = a[(size_t)i * n + k];
-      for (int j = 0; j < n; ++j) c[(size_t)i * n + j] += aik * b[(size_t)k * n + j];
-    }
-  return c;
-}
-
 uint64_t round256(uint64_t v) { return (v + 255) / 256 * 256; }
 
 bool rank_ok(int rank) { return rank == 8 || rank == 16 || rank == 32 || rank == 64 || rank == 128; }
@@ -499,31 +944,37 @@ bool rank_ok(int rank) { return rank == 8 || rank == 16 || rank == 32 || rank ==
 struct hbcsf_als {
   const hbcsf_tensor* t = nullptr;
   int rank = 0;
-  float* m = nullptr;    // workspace: MTTKRP output of the mode being updated [max dim][R]
-  double* s = nullptr;   // workspace: Gram matrix [R][R]
-  double* gramScratch = nullptr;  // workspace: per-block partial sums of the Gram kernel
+  // workspace (device)
+  float* m = nullptr;             // MTTKRP output of the mode being updated [max dim][R]
+  double* s = nullptr;            // Gram matrix of it [R][R]
+  double* gramScratch = nullptr;  // per-block partial sums of the Gram kernels
   uint32_t gramSlots = 0;
-  float* p = nullptr;    // workspace: right-hand R x R matrix of the update [R][R], then one [R] column-scale
-                         // vector per mode
-  double* hostS = nullptr;  // pinned staging
-  float* hostP = nullptr;   // pinned staging
-  float* hostLambda = nullptr;
-  float* hostScale = nullptr;   // pinned staging: [order][R] column factors for the put-off normalisation
-  Mat gram[HBCSF_MAX_ORDER];  // Gram matrices of the factors as stored in device memory after the last iteration
-  // The algorithm's factor A_m is the stored matrix with column r divided by colScale[m][r].  All ones when
-  // the factors were left normalised; the column norms when the normalisation was put off (lazy flag).
-  std::vector<double> colScale[HBCSF_MAX_ORDER];
+  float* p = nullptr;             // right-hand matrix of the product [max(R, 32)][max(R, 32)]
+  float* factor = nullptr;        // [R] column factors of the put-off normalisation
+  double* vp = nullptr;           // V^+ [R][R]
+  double* tmp[2] = {nullptr, nullptr};  // [R][R] each
+  double* inner = nullptr;        // <X, model> of an ordinary iteration
+  SmallState small{};
+  bool pending[HBCSF_MAX_ORDER] = {};  // the stored factor's columns still carry norms (small.scale)
   bool gramsValid = false;
-  hipEvent_t ev[HBCSF_MAX_ORDER][5];
-  int eventsCreated = 0;  // events are created in order; this many exist
-  float phaseMs[4] = {0, 0, 0, 0};  // MTTKRP, Gram (with its read-back), host algebra, apply: last iteration
+  // Pinned host memory the kernels of an iteration write: {<X, model>, ||model||^2}, and wall-clock stamps (taken by a
+  // thread of each kernel as it begins: an event record between two kernels costs 5.6 us on the stream, as much as
+  // many of the kernels).  Per mode: inverse begins, inverse ends, Gram or product begins, R x R part after the Gram
+  // begins; one more at the iteration's end.
+  struct Report {
+    double value[2];
+    unsigned long long stamp[HBCSF_MAX_ORDER][4], end;
+  };
+  Report* report = nullptr;
+  double msPerTick = 1e-5;
+  bool timed = false;      // an iteration has been enqueued
+  bool timedGram = false;  // ... an ordinary one: stamp[.][3] is set too
 
   hbcsf_als() = default;
   hbcsf_als(const hbcsf_als&) = delete;
   hbcsf_als& operator=(const hbcsf_als&) = delete;
   ~hbcsf_als() {
-    if (hostS) (void)hipHostFree(hostS);
-    for (int k = 0; k < eventsCreated; ++k) (void)hipEventDestroy(ev[k / 5][k % 5]);
+    if (report) (void)hipHostFree(report);
   }
 };
 
@@ -573,24 +1024,125 @@ namespace {
 // algorithm's unit-norm factors again; the Gram matrices the state keeps are scaled with them.
 int apply_pending_normalisation(hbcsf_als* a, float* const* factors, hipStream_t st) {
   const hbcsf_tensor* t = a->t;
-  const int order = t->order, R = a->rank;
-  for (int m = 0; m < order; ++m) {
-    bool pending = false;
-    for (int r = 0; r < R; ++r) pending = pending || a->colScale[m][r] != 1.0;
-    if (!pending) continue;
-    float* hs = a->hostScale + (size_t)m * R;
-    float* ds = a->p + (size_t)R * R + (size_t)m * R;
-    for (int r = 0; r < R; ++r) hs[r] = (float)(1.0 / a->colScale[m][r]);
-    hipError_t e = hipMemcpyAsync(ds, hs, (size_t)R * 4, hipMemcpyHostToDevice, st);
-    if (e != hipSuccess) return fail_hip(e, "hipMemcpyAsync");
-    launch_scale_columns(factors[m], t->dims[m], R, ds, t->numCU, st);
-    e = hipGetLastError();
+  for (int m = 0; m < t->order; ++m) {
+    if (!a->pending[m]) continue;
+    with_rank(a->rank, [&](auto r) {
+      constexpr int R = decltype(r)::value;
+      hipLaunchKernelGGL(small_normalise_kernel<R>, dim3(1), dim3(entry_threads(R)), 0, st, a->small, m, a->factor);
+    });
+    launch_scale_columns(factors[m], t->dims[m], a->rank, a->factor, t->numCU, st);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail_hip(e, "column scaling kernel launch");
-    if (a->gramsValid)
-      for (int i = 0; i < R; ++i)
-        for (int j = 0; j < R; ++j) a->gram[m][(size_t)i * R + j] /= a->colScale[m][i] * a->colScale[m][j];
-    a->colScale[m].assign((size_t)R, 1.0);
+    a->pending[m] = false;
   }
+  return HBCSF_OK;
+}
+
+// Where the parts of an ALS state's workspace lie (bytes from its start).
+struct AlsLayout {
+  uint64_t m, s, p, factor, vp, tmp[2], inner, gram, scale, norm, scratch, total;
+};
+
+AlsLayout als_layout(const hbcsf_tensor* t, int rank) {
+  uint64_t maxDim = 0;
+  for (int m = 0; m < t->order; ++m) maxDim = t->dims[m] > maxDim ? t->dims[m] : maxDim;
+  uint64_t gramBytes = 0;
+  (void)hbcsf_gram_workspace_bytes(rank, &gramBytes);
+  const uint64_t rr = (uint64_t)rank * rank, pr = rank < 32 ? 32 : rank;
+  AlsLayout l{};
+  uint64_t off = 0;
+  auto take = [&off](uint64_t bytes) {
+    const uint64_t at = off;
+    off += round256(bytes);
+    return at;
+  };
+  l.m = take(maxDim * (uint64_t)rank * 4);
+  l.s = take(rr * 8);
+  l.p = take(pr * pr * 4);
+  l.factor = take((uint64_t)rank * 4);
+  l.vp = take(rr * 8);
+  for (int k = 0; k < 2; ++k) l.tmp[k] = take(rr * 8);
+  l.inner = take(8);
+  l.gram = take((uint64_t)t->order * rr * 8);
+  l.scale = take((uint64_t)t->order * rank * 8);
+  l.norm = take((uint64_t)t->order * rank * 8);
+  l.scratch = take(gramBytes);
+  l.total = off;
+  return l;
+}
+
+// Enqueues one iteration on st (no wait).  After it small.scale holds the norms a put-off normalisation still owes.
+int enqueue_iteration(hbcsf_als* a, float* const* factors, float* lambda, int flags, hipStream_t st) {
+  const hbcsf_tensor* t = a->t;
+  const int order = t->order, R = a->rank;
+  const bool lazy = (flags & HBCSF_ALS_LAZY_NORMALISATION) != 0;
+  hipError_t e;
+  // Gram matrices of the factors that are read before they are updated (all but the first mode's).  Without
+  // the keep flag the caller may have replaced the factors: they are then taken as they are (scale 1).
+  if (!(flags & HBCSF_ALS_KEEP_GRAMS) || !a->gramsValid) {
+    const int pr = R < 32 ? 32 : R;
+    hipLaunchKernelGGL(small_reset_kernel, dim3(1), dim3(256), 0, st, a->small, R, a->p, pr * pr);
+    for (int m = 0; m < order; ++m) a->pending[m] = false;
+    for (int m = 1; m < order; ++m)
+      launch_gram(factors[m], t->dims[m], R, a->gramScratch, a->gramSlots, a->small.gram[m], t->numCU, st);
+  }
+  a->gramsValid = false;
+  a->timed = false;
+  for (int n = 0; n < order; ++n) {
+    const float* facs[HBCSF_MAX_ORDER];
+    for (int m = 0; m < order; ++m) facs[m] = factors[m];
+    with_rank(R, [&](auto r) {
+      constexpr int RR = decltype(r)::value;
+      hipLaunchKernelGGL(small_pinv_kernel<RR>, dim3(1), dim3(small_threads(RR)), 0, st, a->small, n, a->vp, a->p,
+                         a->tmp[0], a->tmp[1], lazy ? 1 : 0, a->report->stamp[n]);
+    });
+    const int rc = hbcsf_mttkrp(t, n, R, facs, a->m, st);
+    if (rc != HBCSF_OK) return rc;
+    if (lazy) {
+      // A_n = M V^+ written unnormalised, with its Gram matrix
+      launch_apply(a->m, t->dims[n], R, a->p, factors[n], a->gramScratch, a->gramSlots, a->small.gram[n], t->numCU, st,
+                   &a->report->stamp[n][2]);
+    } else {
+      launch_gram(a->m, t->dims[n], R, a->gramScratch, a->gramSlots, a->s, t->numCU, st, &a->report->stamp[n][2]);
+      with_rank(R, [&](auto r) {
+        constexpr int RR = decltype(r)::value;
+        const dim3 grid((RR * RR + 255) / 256);
+        hipLaunchKernelGGL(small_matmul_kernel<RR>, grid, dim3(256), 0, st, a->vp, a->s, a->tmp[0], a->small, n, 1,
+                           &a->report->stamp[n][3]);
+        hipLaunchKernelGGL(small_matmul_kernel<RR>, grid, dim3(256), 0, st, a->tmp[0], a->vp, a->tmp[1], a->small, n, 0,
+                           nullptr);
+        hipLaunchKernelGGL(small_update_kernel<RR>, dim3(1), dim3(entry_threads(RR)), 0, st, a->small, n, a->tmp[1],
+                           a->vp, a->s, a->p, a->inner);
+      });
+      launch_apply(a->m, t->dims[n], R, a->p, factors[n], nullptr, 0, nullptr, t->numCU, st, nullptr);
+    }
+    e = hipGetLastError();
+    if (e != hipSuccess) return fail_hip(e, "mode update kernel launch");
+  }
+  with_rank(R, [&](auto r) {
+    constexpr int RR = decltype(r)::value;
+    hipLaunchKernelGGL(small_finish_kernel<RR>, dim3(1), dim3(entry_threads(RR)), 0, st, a->small, lazy ? 1 : 0, a->inner,
+                       lambda, a->report->value, &a->report->end);
+  });
+  e = hipGetLastError();
+  if (e != hipSuccess) return fail_hip(e, "iteration end kernel launch");
+  for (int m = 0; m < order; ++m) a->pending[m] = lazy;
+  a->gramsValid = true;
+  a->timed = true;
+  a->timedGram = !lazy;
+  return HBCSF_OK;
+}
+
+// The fit of the last finished iteration.
+double als_fit(const hbcsf_als* a) {
+  const double x = a->t->normSq, res = x - 2.0 * a->report->value[0] + a->report->value[1];
+  return x > 0.0 ? 1.0 - std::sqrt(res > 0.0 ? res : 0.0) / std::sqrt(x) : 0.0;
+}
+
+int als_check(const hbcsf_als* a, float* const* factors) {
+  if (!a || !factors) return fail(HBCSF_EINVAL, "null argument");
+  for (int m = 0; m < a->t->order; ++m)
+    if (!factors[m]) return fail(HBCSF_EINVAL, "a factor pointer is null");
   return HBCSF_OK;
 }
 
@@ -656,12 +1208,7 @@ int hbcsf_gram_noalloc(const float* a, uint64_t rows, int rank, double* s, void*
 int hbcsf_als_workspace_bytes(const hbcsf_tensor* t, int rank, uint64_t* bytes) try {
   if (!t || !bytes) return fail(HBCSF_EINVAL, "null argument");
   if (!rank_ok(rank)) return fail(HBCSF_EINVAL, "rank must be 8, 16, 32, 64 or 128");
-  uint64_t maxDim = 0;
-  for (int m = 0; m < t->order; ++m) maxDim = t->dims[m] > maxDim ? t->dims[m] : maxDim;
-  uint64_t gramBytes = 0;
-  (void)hbcsf_gram_workspace_bytes(rank, &gramBytes);
-  *bytes = round256(maxDim * (uint64_t)rank * 4) + round256((uint64_t)rank * rank * 8) +
-           round256(((uint64_t)rank * rank + (uint64_t)HBCSF_MAX_ORDER * rank) * 4) + round256(gramBytes);
+  *bytes = als_layout(t, rank).total;
   return HBCSF_OK;
 } HBCSF_CATCH_ALL
 
@@ -680,217 +1227,55 @@ int hbcsf_als_create(const hbcsf_tensor* t, int rank, void* workspace, uint64_t 
   if (!a) return fail(HBCSF_ENOMEM, "out of host memory");
   a->t = t;
   a->rank = rank;
-  uint64_t maxDim = 0;
-  for (int m = 0; m < t->order; ++m) maxDim = t->dims[m] > maxDim ? t->dims[m] : maxDim;
+  const AlsLayout l = als_layout(t, rank);
   uint8_t* w = (uint8_t*)workspace;
-  a->m = (float*)w;
-  w += round256(maxDim * (uint64_t)rank * 4);
-  a->s = (double*)w;
-  w += round256((uint64_t)rank * rank * 8);
-  a->p = (float*)w;
-  w += round256(((uint64_t)rank * rank + (uint64_t)HBCSF_MAX_ORDER * rank) * 4);
-  a->gramScratch = (double*)w;
+  a->m = (float*)(w + l.m);
+  a->s = (double*)(w + l.s);
+  a->p = (float*)(w + l.p);
+  a->factor = (float*)(w + l.factor);
+  a->vp = (double*)(w + l.vp);
+  for (int k = 0; k < 2; ++k) a->tmp[k] = (double*)(w + l.tmp[k]);
+  a->inner = (double*)(w + l.inner);
+  a->small.order = t->order;
+  for (int m = 0; m < t->order; ++m) {
+    a->small.gram[m] = (double*)(w + l.gram) + (size_t)m * rank * rank;
+    a->small.scale[m] = (double*)(w + l.scale) + (size_t)m * rank;
+    a->small.norm[m] = (double*)(w + l.norm) + (size_t)m * rank;
+  }
+  a->gramScratch = (double*)(w + l.scratch);
   uint64_t gramBytes = 0;
   (void)hbcsf_gram_workspace_bytes(rank, &gramBytes);
   a->gramSlots = gram_slots_for(rank, gramBytes);
-  const size_t rr = (size_t)rank * rank;
-  hipError_t e = hipHostMalloc((void**)&a->hostS,
-                               rr * 8 + HBCSF_MAX_ORDER * rr * 4 + (size_t)rank * 4 + (size_t)HBCSF_MAX_ORDER * rank * 4,
-                               hipHostMallocDefault);
+  hipError_t e = hipHostMalloc((void**)&a->report, sizeof(hbcsf_als::Report), hipHostMallocDefault);
   if (e != hipSuccess) return fail_hip(e, "hipHostMalloc");
-  a->hostP = (float*)(a->hostS + rr);
-  a->hostLambda = a->hostP + HBCSF_MAX_ORDER * rr;
-  a->hostScale = a->hostLambda + rank;
-  for (int m = 0; m < t->order; ++m) a->colScale[m].assign((size_t)rank, 1.0);
-  for (int k = 0; k < HBCSF_MAX_ORDER * 5; ++k) {
-    e = hipEventCreate(&a->ev[k / 5][k % 5]);
-    if (e != hipSuccess) return fail_hip(e, "hipEventCreate");  // the destructor releases what exists
-    a->eventsCreated = k + 1;
-  }
+  int dev = 0, kHz = 0;
+  e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&kHz, hipDeviceAttributeWallClockRate, dev);
+  if (e != hipSuccess) return fail_hip(e, "hipDeviceGetAttribute");
+  if (kHz > 0) a->msPerTick = 1.0 / kHz;
   *out = a.release();
   return HBCSF_OK;
 } HBCSF_CATCH_ALL
 
 int hbcsf_als_iteration(hbcsf_als* a, float* const* factors, float* lambda, int flags, double* fit,
                         void* hip_stream) try {
-  if (!a || !factors) return fail(HBCSF_EINVAL, "null argument");
-  const hbcsf_tensor* t = a->t;
-  const int order = t->order, R = a->rank;
-  const size_t rr = (size_t)R * R;
-  for (int m = 0; m < order; ++m)
-    if (!factors[m]) return fail(HBCSF_EINVAL, "a factor pointer is null");
+  const int rc = als_check(a, factors);
+  if (rc != HBCSF_OK) return rc;
   if (flags & ~(HBCSF_ALS_KEEP_GRAMS | HBCSF_ALS_LAZY_NORMALISATION)) return fail(HBCSF_EINVAL, "unknown flag");
-  const bool lazy = (flags & HBCSF_ALS_LAZY_NORMALISATION) != 0;
-  // the product kernel that also forms the new factor's Gram matrix exists for R = 32
-  const bool fused = lazy && R == 32;
   hipStream_t st = (hipStream_t)hip_stream;
-  hipError_t e;
-
-  auto gram_to_host = [&](const float* src, uint64_t rows, Mat& dst) -> int {
-    launch_gram(src, rows, R, a->gramScratch, a->gramSlots, a->s, t->numCU, st);
-    e = hipGetLastError();
-    if (e != hipSuccess) return fail_hip(e, "Gram kernel launch");
-    e = hipMemcpyAsync(a->hostS, a->s, rr * 8, hipMemcpyDeviceToHost, st);
-    if (e != hipSuccess) return fail_hip(e, "hipMemcpyAsync");
-    e = hipStreamSynchronize(st);
-    if (e != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
-    dst.assign(a->hostS, a->hostS + rr);
-    return HBCSF_OK;
-  };
-
-  // Gram matrices of the factors that are read before they are updated (all but the first mode's).  Without
-  // the keep flag the caller may have replaced the factors: they are then taken as they are (scale 1).
-  if (!(flags & HBCSF_ALS_KEEP_GRAMS) || !a->gramsValid) {
-    for (int m = 0; m < order; ++m) a->colScale[m].assign((size_t)R, 1.0);
-    for (int m = 1; m < order; ++m) {
-      const int rc = gram_to_host(factors[m], t->dims[m], a->gram[m]);
-      if (rc != HBCSF_OK) return rc;
-    }
-  }
-  a->gramsValid = false;
-
-  // Book-keeping: the algorithm's current factor A_m is stored_m diag(1 / c_m) with c_m = colScale[m]; algGram[m]
-  // is its Gram matrix.  Column scaling commutes with every step of the update, so the device works on the
-  // stored matrices and the host folds the diagonals into the R x R matrices.
-  Mat norms[HBCSF_MAX_ORDER];
-  Mat algGram[HBCSF_MAX_ORDER];
-  for (int m = 1; m < order; ++m) {
-    algGram[m] = a->gram[m];
-    for (int i = 0; i < R; ++i)
-      for (int j = 0; j < R; ++j) algGram[m][(size_t)i * R + j] /= a->colScale[m][i] * a->colScale[m][j];
-  }
-  double inner = 0.0;
-
-  for (int n = 0; n < order; ++n) {
-    const float* facs[HBCSF_MAX_ORDER];
-    for (int m = 0; m < order; ++m) facs[m] = factors[m];
-    (void)hipEventRecord(a->ev[n][0], st);
-    const int rc = hbcsf_mttkrp(t, n, R, facs, a->m, st);
-    if (rc != HBCSF_OK) return rc;
-    (void)hipEventRecord(a->ev[n][1], st);
-    // M of the algorithm = M of the device diag(d), d_r = product over the other modes of 1 / c_m[r]
-    std::vector<double> d((size_t)R, 1.0);
-    for (int m = 0; m < order; ++m)
-      if (m != n)
-        for (int r = 0; r < R; ++r) d[r] /= a->colScale[m][r];
-    Mat V(rr, 1.0);
-    for (int m = 0; m < order; ++m)
-      if (m != n)
-        for (size_t k = 0; k < rr; ++k) V[k] *= algGram[m][k];
-    float* hostP = a->hostP + (size_t)n * rr;  // one staging copy per mode: no wait before it is reused
-    norms[n].assign(R, 1.0);
-    if (fused) {
-      // A_n = M V^+ written unnormalised, its Gram matrix G formed in the same pass; <X, model> = trace(M^T A_n)
-      // = trace(V G) because V^+ V V^+ = V^+.
-      (void)hipEventRecord(a->ev[n][2], st);
-      const Mat Vp = pinv_of_gram_product(V, R);
-      for (int i = 0; i < R; ++i)
-        for (int j = 0; j < R; ++j) hostP[(size_t)i * R + j] = (float)(d[i] * Vp[(size_t)i * R + j]);
-      (void)hipEventRecord(a->ev[n][3], st);
-      e = hipMemcpyAsync(a->p, hostP, rr * 4, hipMemcpyHostToDevice, st);
-      if (e != hipSuccess) return fail_hip(e, "hipMemcpyAsync");
-      launch_apply_gram32(a->m, t->dims[n], a->p, factors[n], a->gramScratch, a->gramSlots, a->s, t->numCU, st);
-      e = hipGetLastError();
-      if (e != hipSuccess) return fail_hip(e, "product kernel launch");
-      e = hipMemcpyAsync(a->hostS, a->s, rr * 8, hipMemcpyDeviceToHost, st);
-      if (e != hipSuccess) return fail_hip(e, "hipMemcpyAsync");
-      e = hipStreamSynchronize(st);
-      if (e != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
-      (void)hipEventRecord(a->ev[n][4], st);
-      algGram[n].assign(a->hostS, a->hostS + rr);
-      a->gram[n] = algGram[n];                 // stored = the algorithm's unnormalised factor
-      a->colScale[n].assign((size_t)R, 1.0);
-      for (int r = 0; r < R; ++r) {
-        const double g = algGram[n][(size_t)r * R + r];
-        norms[n][r] = g > 0.0 ? std::sqrt(g) : 1.0;
-      }
-      if (n == order - 1) {
-        inner = 0.0;
-        for (size_t k = 0; k < rr; ++k) inner += V[k] * algGram[n][k];   // both symmetric: trace(V G)
-      }
-    } else {
-      Mat S;
-      const int rg = gram_to_host(a->m, t->dims[n], S);
-      if (rg != HBCSF_OK) return rg;
-      (void)hipEventRecord(a->ev[n][2], st);
-      for (int i = 0; i < R; ++i)
-        for (int j = 0; j < R; ++j) S[(size_t)i * R + j] *= d[i] * d[j];
-      const Mat Vp = pinv_of_gram_product(V, R);
-      algGram[n] = matmul(matmul(Vp, S, R), Vp, R);   // A_n^T A_n = V^+ S V^+ without another pass
-      for (int r = 0; r < R; ++r) {
-        const double g = algGram[n][(size_t)r * R + r];
-        norms[n][r] = g > 0.0 ? std::sqrt(g) : 1.0;
-      }
-      // the factor is written with unit-norm columns at once: stored = A_n diag(1 / norms), so c_n = 1 / norms
-      // until the algorithm's closing normalisation makes it 1
-      for (int i = 0; i < R; ++i)
-        for (int j = 0; j < R; ++j) hostP[(size_t)i * R + j] = (float)(d[i] * Vp[(size_t)i * R + j] / norms[n][j]);
-      if (n == order - 1) {
-        inner = 0.0;  // <X, model> = trace(M^T A_n) = trace(S V^+)
-        for (int i = 0; i < R; ++i)
-          for (int j = 0; j < R; ++j) inner += S[(size_t)i * R + j] * Vp[(size_t)j * R + i];
-      }
-      (void)hipEventRecord(a->ev[n][3], st);
-      e = hipMemcpyAsync(a->p, hostP, rr * 4, hipMemcpyHostToDevice, st);
-      if (e != hipSuccess) return fail_hip(e, "hipMemcpyAsync");
-      launch_apply(a->m, t->dims[n], R, a->p, factors[n], t->numCU, st);
-      e = hipGetLastError();
-      if (e != hipSuccess) return fail_hip(e, "apply kernel launch");
-      (void)hipEventRecord(a->ev[n][4], st);
-      a->gram[n] = algGram[n];
-      for (int i = 0; i < R; ++i)
-        for (int j = 0; j < R; ++j) a->gram[n][(size_t)i * R + j] /= norms[n][i] * norms[n][j];
-      for (int r = 0; r < R; ++r) a->colScale[n][r] = 1.0 / norms[n][r];
-    }
-  }
-
-  // lambda: product over the modes of the column norms; the model's squared norm from the Gram matrices of the
-  // unnormalised factors
-  double modelSq = 0.0;
-  for (size_t k = 0; k < rr; ++k) {
-    double prod = 1.0;
-    for (int m = 0; m < order; ++m) prod *= algGram[m][k];
-    modelSq += prod;
-  }
-  // the algorithm's closing normalisation: A_m <- A_m diag(1 / norms_m), i.e. c_m <- c_m norms_m
-  std::vector<double> lam((size_t)R, 1.0);
-  for (int m = 0; m < order; ++m)
-    for (int r = 0; r < R; ++r) {
-      a->colScale[m][r] *= norms[m][r];
-      if (std::fabs(a->colScale[m][r] - 1.0) < 1e-12) a->colScale[m][r] = 1.0;   // written normalised already
-      lam[r] *= norms[m][r];
-    }
-  a->gramsValid = true;
-  if (!lazy) {
-    const int rn = apply_pending_normalisation(a, factors, st);
-    if (rn != HBCSF_OK) return rn;
-  }
-  if (lambda) {
-    for (int r = 0; r < R; ++r) a->hostLambda[r] = (float)lam[r];
-    e = hipMemcpyAsync(lambda, a->hostLambda, (size_t)R * 4, hipMemcpyHostToDevice, st);
-    if (e != hipSuccess) return fail_hip(e, "hipMemcpyAsync");
-  }
-  e = hipStreamSynchronize(st);
+  const int ri = enqueue_iteration(a, factors, lambda, flags, st);
+  if (ri != HBCSF_OK) return ri;
+  const hipError_t e = hipStreamSynchronize(st);
   if (e != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
-  if (fit) {
-    const double res = t->normSq - 2.0 * inner + modelSq;
-    *fit = t->normSq > 0.0 ? 1.0 - std::sqrt(res > 0.0 ? res : 0.0) / std::sqrt(t->normSq) : 0.0;
-  }
-  for (int k = 0; k < 4; ++k) a->phaseMs[k] = 0.f;
-  for (int n = 0; n < order; ++n)
-    for (int k = 0; k < 4; ++k) {
-      float ms = 0.f;
-      if (hipEventElapsedTime(&ms, a->ev[n][k], a->ev[n][k + 1]) == hipSuccess) a->phaseMs[k] += ms;
-    }
+  if (fit) *fit = als_fit(a);
   return HBCSF_OK;
 } HBCSF_CATCH_ALL
 
 int hbcsf_als_normalise(hbcsf_als* a, float* const* factors, void* hip_stream) try {
-  if (!a || !factors) return fail(HBCSF_EINVAL, "null argument");
-  for (int m = 0; m < a->t->order; ++m)
-    if (!factors[m]) return fail(HBCSF_EINVAL, "a factor pointer is null");
-  const int rc = apply_pending_normalisation(a, factors, (hipStream_t)hip_stream);
+  const int rc = als_check(a, factors);
   if (rc != HBCSF_OK) return rc;
+  const int rn = apply_pending_normalisation(a, factors, (hipStream_t)hip_stream);
+  if (rn != HBCSF_OK) return rn;
   const hipError_t e = hipStreamSynchronize((hipStream_t)hip_stream);
   if (e != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
   return HBCSF_OK;
@@ -898,15 +1283,19 @@ int hbcsf_als_normalise(hbcsf_als* a, float* const* factors, void* hip_stream) t
 
 int hbcsf_als_run(hbcsf_als* a, float* const* factors, float* lambda, int max_iterations, double tolerance,
                   int* iterations_done, double* fit, void* hip_stream) try {
-  if (!a || !factors) return fail(HBCSF_EINVAL, "null argument");
+  const int rc = als_check(a, factors);
+  if (rc != HBCSF_OK) return rc;
   if (max_iterations < 1) return fail(HBCSF_EINVAL, "max_iterations must be at least 1");
+  hipStream_t st = (hipStream_t)hip_stream;
   double prev = 0.0, cur = 0.0;
   int it = 0;
   for (; it < max_iterations; ++it) {
-    const int rc = hbcsf_als_iteration(a, factors, lambda,
-                                       (it > 0 ? HBCSF_ALS_KEEP_GRAMS : 0) | HBCSF_ALS_LAZY_NORMALISATION, &cur,
-                                       hip_stream);
-    if (rc != HBCSF_OK) return rc;
+    const int ri = enqueue_iteration(a, factors, lambda, (it > 0 ? HBCSF_ALS_KEEP_GRAMS : 0) | HBCSF_ALS_LAZY_NORMALISATION, st);
+    if (ri != HBCSF_OK) return ri;
+    if (!(tolerance > 0.0)) continue;   // no fit can end the loop: the iterations follow each other without a wait
+    const hipError_t e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
+    cur = als_fit(a);
     if (it > 0 && std::fabs(cur - prev) < tolerance) {
       ++it;
       break;
@@ -916,7 +1305,7 @@ int hbcsf_als_run(hbcsf_als* a, float* const* factors, float* lambda, int max_it
   const int rn = hbcsf_als_normalise(a, factors, hip_stream);
   if (rn != HBCSF_OK) return rn;
   if (iterations_done) *iterations_done = it;
-  if (fit) *fit = cur;
+  if (fit) *fit = als_fit(a);
   return HBCSF_OK;
 } HBCSF_CATCH_ALL
 
@@ -931,7 +1320,20 @@ int hbcsf_sym_pinv(const double* v, int n, double* out) try {
 
 int hbcsf_als_phase_ms(const hbcsf_als* a, float ms[4]) try {
   if (!a || !ms) return fail(HBCSF_EINVAL, "null argument");
-  for (int k = 0; k < 4; ++k) ms[k] = a->phaseMs[k];
+  for (int k = 0; k < 4; ++k) ms[k] = 0.f;
+  if (!a->timed) return HBCSF_OK;
+  const int order = a->t->order;
+  auto add = [&](float& to, unsigned long long from, unsigned long long until) {
+    to += (float)((double)(until - from) * a->msPerTick);
+  };
+  for (int n = 0; n < order; ++n) {
+    const unsigned long long* at = a->report->stamp[n];
+    const unsigned long long end = n + 1 < order ? a->report->stamp[n + 1][0] : a->report->end;
+    add(ms[2], at[0], at[1]);
+    add(ms[0], at[1], at[2]);
+    if (a->timedGram) add(ms[1], at[2], at[3]);
+    add(ms[3], at[a->timedGram ? 3 : 2], end);
+  }
   return HBCSF_OK;
 } HBCSF_CATCH_ALL
 

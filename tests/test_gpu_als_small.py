@@ -1,0 +1,59 @@
+"""The mode update's R x R algebra and tile kernels at their edges: rank-deficient products of Gram matrices (the eigenvalue
+form) and matrices that end inside a tile or inside one row of 32 floats, against the numpy fp64 oracle."""
+import numpy as np
+import pytest
+
+from oracle import cpd_als
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("lazy", [False, True])
+@pytest.mark.parametrize("rank", [8, 16, 32, 64, 128])
+def test_rank_deficient_update(rank, lazy):
+    """Two identical components: V has two equal rows, so the update takes the pseudo-inverse."""
+    import torch
+    from paper_1904_03329_amd import CpdAls, HbcsfTensor
+
+    rng = np.random.default_rng(rank)
+    dims = (300, 301, 157)
+    flat = rng.choice(int(np.prod(dims)), size=30000, replace=False)
+    inds = [(flat // (dims[1] * dims[2])).astype(np.uint32), (flat // dims[2] % dims[1]).astype(np.uint32),
+            (flat % dims[2]).astype(np.uint32)]
+    vals = rng.uniform(0.1, 1.0, size=flat.size).astype(np.float32)
+    facs = [rng.uniform(-1, 1, size=(d, rank)).astype(np.float32) for d in dims]
+    for f in facs:
+        f[:, 1] = f[:, 0]
+    t = HbcsfTensor(dims, inds, vals).to_device()
+    als = CpdAls(t, rank)
+    dfacs = [torch.from_numpy(f.copy()).cuda() for f in facs]
+    print("als deficient", rank, lazy, flush=True)
+    fit = als.iteration(dfacs, lazy=lazy)
+    als.normalise(dfacs)
+    want, lam = cpd_als.als_iteration(dims, inds, vals, facs)
+    # the two components stay equal up to rounding, so what the later updates invert has one singular value at rounding
+    # level: the model is compared, not the factors
+    got = [f.cpu().numpy() for f in dfacs]
+    model = cpd_als.model_values(inds, got, als.lam.cpu().numpy())
+    ref = cpd_als.model_values(inds, want, lam)
+    assert np.max(np.abs(model - ref)) <= 2e-3 * np.max(np.abs(ref))
+    assert abs(fit - cpd_als.fit(dims, inds, vals, want, lam)) <= 1e-3
+    als.close()
+    t.close()
+
+
+@pytest.mark.parametrize("rank", [8, 16, 64, 128])
+@pytest.mark.parametrize("rows", [1, 3, 33, 129, 4099])
+def test_gram_of_ragged_matrices(rank, rows):
+    import torch
+    from paper_1904_03329_amd import binding as B
+
+    a = np.random.default_rng(rows).uniform(-1, 1, size=(rows, rank)).astype(np.float32)
+    # the matrix ends where its allocation does not: what follows must not be taken in
+    buf = torch.full((rows * rank + 64,), 1e30, device="cuda")
+    buf[:rows * rank] = torch.from_numpy(a.reshape(-1)).cuda()
+    ws = torch.empty(B.gram_workspace_bytes(rank), dtype=torch.uint8, device="cuda")
+    s = torch.full((rank, rank), float("nan"), dtype=torch.float64, device="cuda")
+    B.gram(buf.data_ptr(), rows, rank, ws.data_ptr(), ws.numel(), s.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    want = cpd_als.gram(a)
+    assert np.max(np.abs(s.cpu().numpy() - want)) <= 1e-5 * np.max(np.abs(want))
