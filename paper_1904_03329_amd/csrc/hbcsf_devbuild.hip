@@ -4,11 +4,20 @@
 // put each slice into the COO / CSL / CSF group, cut fibers on the run grid (fbr-split), record which
 // slices span several runs (slc-split), and write the run tables and row bitmaps.
 //
-// Sorting, scans and reductions are rocPRIM device primitives; everything specific to the format is in
-// the kernels below.  Every per-nonzero quantity is a function of the nonzero's place p in the sorted
-// order: its slice (scan of "root index changes here"), the slice's group and start inside the group's
-// stream (scan over slices), hence its position in that stream, hence whether a fiber segment starts
-// there (fiber index changes, or the position lies on the run grid).
+// Sorting.  Every mode's levels below the root keep the order of one list of all modes, so the nonzeros are sorted once
+// by that list and a mode's order is one stable sort of the result by the mode's own index alone: two or three radix
+// passes instead of a whole key's eight.
+//
+// Numbering.  No array is kept per nonzero.  A wavefront takes 1024 sorted nonzeros, 64 at a time; "a slice / a fiber
+// begins here" are ballots, so what it needs to number them is the count before its tile (one scan over the tiles).
+// Slices get their group, their place in it and the fibers before them by a scan over slices; fbr-split adds a segment
+// start only where a run begins inside a fiber, which is looked up once per run (a search over the slices, a scan over
+// the runs), so a segment's number is the fibers before it plus the cuts before it.  The sorted keys are read three times
+// and each output is written once.
+//
+// Radix sort and the scans over tiles, slices and runs are rocPRIM device primitives; everything specific to the format
+// is in the kernels below.  With the per-fiber group choice a slice's nonzeros part between two groups, and the
+// numbering goes through per-nonzero scans instead (number_mode_per_fiber).
 
 #include <hip/hip_runtime.h>
 
@@ -35,6 +44,7 @@ struct Spec {
   int shift[HBCSF_MAX_ORDER];
   uint64_t mask[HBCSF_MAX_ORDER];
   uint32_t L, cooOn, cslOn, cooRowFlags;
+  uint32_t byteLevels;  // bit l: level l's row map holds bytes, otherwise bits
   uint32_t perFiber;  // hybrid_granularity = 1: heavy slices are split into a CSL piece and a CSF piece
   int blockBits, blockShift, blockDrop;  // level-1 blocking: (index of level 1 >> blockDrop) << blockShift tops the key
 };
@@ -192,22 +202,27 @@ struct Carried {  // what rides along while one 64-bit half of a wide key is bei
   uint32_t v, pad;
 };
 
+// Where each mode's index lies in the key of the common order.
+struct BaseKey {
+  int shift[HBCSF_MAX_ORDER];       // by mode
+  uint64_t mask[HBCSF_MAX_ORDER], dims[HBCSF_MAX_ORDER];
+};
+
 // Key = uint64_t: K / V receive the packed key and the value bits.  Key = u128: the key is sorted in two
 // stable 64-bit passes, so the low half goes to K (as uint64_t) and the high half rides in C.
 template <typename Key>
-__global__ void pack_kernel(IndPtrs inds, const float* vals, size_t M, Spec sp, uint64_t dim0, uint64_t dim1,
-                            uint64_t dim2, uint64_t dim3, uint64_t dim4, uint64_t* K, uint32_t* V, Carried* C,
-                            unsigned long long* cnt) {
+__global__ void pack_kernel(IndPtrs inds, const float* vals, size_t M, int N, BaseKey bk, uint64_t* K, uint32_t* V, Carried* C,
+                            unsigned long long* bad) {
   const size_t z = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (z >= M) return;
-  const uint64_t dims[HBCSF_MAX_ORDER] = {dim0, dim1, dim2, dim3, dim4};
   Key key = 0;
-  bool bad = false;
-  for (int l = 0; l < sp.N; ++l) {
-    const uint32_t i = inds.p[l][z];
-    bad = bad || (uint64_t)i >= dims[l];
-    key |= (Key)i << sp.shift[l];
-    if (l == 1 && sp.blockBits) key |= (Key)(i >> sp.blockDrop) << sp.blockShift;
+  bool off = false;
+#pragma unroll
+  for (int m = 0; m < HBCSF_MAX_ORDER; ++m) {
+    if (m >= N) break;
+    const uint32_t i = inds.p[m][z];
+    off = off || (uint64_t)i >= bk.dims[m];
+    key |= (Key)i << bk.shift[m];
   }
   if (sizeof(Key) == 8) {
     K[z] = (uint64_t)key;
@@ -216,7 +231,49 @@ __global__ void pack_kernel(IndPtrs inds, const float* vals, size_t M, Spec sp, 
     K[z] = (uint64_t)key;
     C[z] = Carried{(uint64_t)((u128)key >> 64), __float_as_uint(vals[z]), 0u};
   }
-  if (bad) atomicOr(cnt, 1ull);
+  if (off) atomicOr(bad, 1ull);
+}
+
+// The key of one mode's representation from the key of the common order.
+struct ModeKey {
+  int from[HBCSF_MAX_ORDER];  // by level: shift in the common key
+};
+template <typename Key>
+__device__ __forceinline__ Key mode_key(Key base, const ModeKey& mk, const Spec& sp) {
+  Key key = 0;
+#pragma unroll
+  for (int l = 0; l < HBCSF_MAX_ORDER; ++l) {
+    if (l >= sp.N) break;
+    const uint64_t i = (uint64_t)(base >> mk.from[l]) & sp.mask[l];
+    key |= (Key)i << sp.shift[l];
+    if (l == 1 && sp.blockBits) key |= (Key)(i >> sp.blockDrop) << sp.blockShift;
+  }
+  return key;
+}
+
+__global__ void mode_key_kernel(const uint64_t* __restrict__ base, const uint32_t* __restrict__ baseV, size_t M, Spec sp,
+                                ModeKey mk, uint64_t* __restrict__ K, uint32_t* __restrict__ V) {
+  const size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= M) return;
+  K[p] = mode_key<uint64_t>(base[p], mk, sp);
+  V[p] = baseV[p];
+}
+
+// Wide keys: what is sorted is (block, root) with the place in the common order, then the rest is fetched.
+__global__ void root_key_kernel(const u128* __restrict__ base, size_t M, Spec sp, ModeKey mk, uint64_t* __restrict__ K,
+                                uint32_t* __restrict__ V) {
+  const size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= M) return;
+  K[p] = (uint64_t)(mode_key<u128>(base[p], mk, sp) >> sp.shift[0]);
+  V[p] = (uint32_t)p;
+}
+__global__ void fetch_kernel(const u128* __restrict__ base, const uint32_t* __restrict__ baseV, const uint32_t* __restrict__ at,
+                             size_t M, Spec sp, ModeKey mk, u128* __restrict__ K, uint32_t* __restrict__ V) {
+  const size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= M) return;
+  const uint32_t z = at[p];
+  K[p] = mode_key<u128>(base[z], mk, sp);
+  V[p] = baseV[z];
 }
 
 // between the two passes of a wide sort: the high half becomes the key, the low half rides along
@@ -325,12 +382,21 @@ struct OutArrays {
   uint32_t* csfVal;
   uint32_t* owned;
   uint32_t* cooBits;
-  uint32_t* seen[3][HBCSF_MAX_ORDER];  // statistics: bitmap of the factor rows each group gathers, per level
+  uint32_t* seen[3][HBCSF_MAX_ORDER];  // statistics: map of the factor rows each group gathers, per level (mark_row)
 };
 
-__device__ __forceinline__ void mark_row(uint32_t* bitmap, uint32_t r) {
-  const uint32_t bit = 1u << (r & 31);
-  if (!(bitmap[r >> 5] & bit)) atomicOr(&bitmap[r >> 5], bit);
+// Marks a factor row as gathered (statistics).  Up to kByteRows rows one byte each: a plain store of the same byte whoever
+// writes it, nothing read first and nothing atomic (as a bitmap, tested before an atomic or, the marks took 30 % of a
+// 5 M-nonzero build: copies of a word in eight L2s stay stale, and every nonzero that meets one adds an atomic).  Longer
+// modes keep the bitmap, which is what still fits an L2 (40 M rows: 7 ms of a 150 M-nonzero build against 10 ms).
+constexpr uint64_t kByteRows = 4ull << 20;
+__device__ __forceinline__ void mark_row(const Spec& sp, int level, uint32_t* map, uint32_t r) {
+  if ((sp.byteLevels >> level) & 1u) {
+    reinterpret_cast<uint8_t*>(map)[r] = 1;
+  } else {
+    const uint32_t bit = 1u << (r & 31);
+    if (!(map[r >> 5] & bit)) atomicOr(&map[r >> 5], bit);
+  }
 }
 
 // every nonzero writes itself into its group's stream; segment starts write the fiber-level entries
@@ -348,7 +414,7 @@ __global__ void fill_nonzeros_kernel(const Key* K, const uint32_t* V, size_t M, 
   const uint32_t v = V[p];
   if (g == kCoo) {
     for (int l = sp.cooRowFlags ? 1 : 0; l < sp.N; ++l) o.cooInd[l][pos] = idx[l];
-    for (int l = 1; l < sp.N; ++l) mark_row(o.seen[kCoo][l], idx[l]);
+    for (int l = 1; l < sp.N; ++l) mark_row(sp, l, o.seen[kCoo][l], idx[l]);
     o.cooVal[pos] = v;
     atomicOr(&o.cooBits[idx[0] >> 5], 1u << (idx[0] & 31));
     atomicOr(&o.owned[idx[0] >> 5], 1u << (idx[0] & 31));
@@ -358,13 +424,13 @@ __global__ void fill_nonzeros_kernel(const Key* K, const uint32_t* V, size_t M, 
   const uint32_t ord = t.c6[s].s[g];
   if (g == kCsl) {
     for (int l = 1; l < sp.N; ++l) o.cslInd[l][pos] = idx[l];
-    for (int l = 1; l < sp.N; ++l) mark_row(o.seen[kCsl][l], idx[l]);
+    for (int l = 1; l < sp.N; ++l) mark_row(sp, l, o.seen[kCsl][l], idx[l]);
     o.cslVal[pos] = v;
     if (cut) o.cslRun[pos / sp.L] = ord;
     return;
   }
   o.csfInd[sp.N - 1][pos] = idx[sp.N - 1];
-  mark_row(o.seen[kCsf][sp.N - 1], idx[sp.N - 1]);
+  mark_row(sp, sp.N - 1, o.seen[kCsf][sp.N - 1], idx[sp.N - 1]);
   o.csfVal[pos] = v;
   if (cut) o.csfRun[0][pos / sp.L] = ord;
   for (int l = 1; l <= sp.NF; ++l) {
@@ -373,7 +439,7 @@ __global__ void fill_nonzeros_kernel(const Key* K, const uint32_t* V, size_t M, 
       const uint32_t id = (l == 1 ? seg0 : l == 2 ? seg1 : seg2)[p];
       o.csfInd[l][id] = idx[l];
       o.csfPtr[l][id] = pos;
-      mark_row(o.seen[kCsf][l], idx[l]);
+      mark_row(sp, l, o.seen[kCsf][l], idx[l]);
       if (cut) o.csfRun[l][pos / sp.L] = id;
     }
   }
@@ -412,6 +478,371 @@ __global__ void fill_slices_kernel(const Key* K, size_t S, Spec sp, Tables t, Ou
   wave_add(cnt + 1, shared);
 }
 
+// ---- numbering without per-nonzero arrays ----
+constexpr uint32_t kTile = 1024;       // sorted nonzeros a wavefront numbers
+constexpr uint32_t kSliceBlock = 1024; // slices a block numbers
+
+struct Count4 {  // v[0]: slices, v[1..3]: fibers of levels 1..3
+  uint32_t v[4];
+};
+struct Count4Plus {
+  __host__ __device__ Count4 operator()(const Count4& a, const Count4& b) const {
+    Count4 r;
+    for (int l = 0; l < 4; ++l) r.v[l] = a.v[l] + b.v[l];
+    return r;
+  }
+};
+struct GroupCounts {  // slices and nonzeros per group, fibers of the CSF group per level
+  uint32_t s[3], m[3], f[3];
+};
+struct GroupCountsPlus {
+  __host__ __device__ GroupCounts operator()(const GroupCounts& a, const GroupCounts& b) const {
+    GroupCounts r;
+    for (int g = 0; g < 3; ++g) {
+      r.s[g] = a.s[g] + b.s[g];
+      r.m[g] = a.m[g] + b.m[g];
+      r.f[g] = a.f[g] + b.f[g];
+    }
+    return r;
+  }
+};
+struct SliceInfo {
+  uint32_t off, ord;  // first place in the group's stream, number in the group
+  uint32_t grp;
+  uint32_t fib0;      // CSF: level-1 fibers before the slice
+};
+struct Totals {
+  uint32_t bad, S, fibNat[3];
+  GroupCounts g;
+  uint32_t extra[3];  // cuts that do not fall on the begin of a fiber, per level
+};
+
+// The tables one mode's numbering fills (device memory).
+struct Numbers {
+  Count4* tile;          // [tiles + 1] counts per tile, then before each
+  uint32_t* sStart;      // [S + 1] first nonzero of every slice
+  uint32_t* fStart[3];   // [S + 1] fibers of each level before the slice
+  GroupCounts* block;    // [slice blocks + 1] counts per block of slices, then before each
+  SliceInfo* info;       // [S]
+  uint32_t* fib[2];      // [S] CSF: fibers of levels 2, 3 before the slice
+  uint32_t* csfOff;      // by CSF slice: its first place in the stream,
+  uint32_t* csfStart;    //               its first sorted nonzero
+  Count4* cut;           // [runs + 1] cuts inside a fiber, per run, then before each
+  uint32_t* count;       // {S}
+};
+
+// bit l: a slice (l = 0) or a fiber of level l begins at sorted nonzero p
+template <typename Key>
+__device__ __forceinline__ uint32_t begins(const Key* __restrict__ K, size_t p, const Spec& sp) {
+  if (p == 0) return 15u;
+  const Key x = K[p] ^ K[p - 1];
+  uint32_t b = 0;
+  for (int l = 0; l <= sp.NF; ++l) b |= ((x >> sp.shift[l]) != 0 ? 1u : 0u) << l;
+  return b;
+}
+
+template <typename Key>
+__global__ __launch_bounds__(256) void count_tiles_kernel(const Key* __restrict__ K, size_t M, Spec sp, uint32_t tiles,
+                                                          Count4* __restrict__ tile) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t t = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (t > tiles) return;
+  Count4 c{{0, 0, 0, 0}};
+  if (t < tiles) {
+    for (uint32_t j = 0; j < kTile; j += 64) {
+      const size_t p = (size_t)t * kTile + j + lane;
+      const uint32_t b = p < M ? begins(K, p, sp) : 0u;
+#pragma unroll
+      for (int l = 0; l < 4; ++l)
+        if (l <= sp.NF) c.v[l] += (uint32_t)__popcll(__ballot((b >> l) & 1u));
+    }
+  }
+  if (lane == 0) tile[t] = c;
+}
+
+template <typename Key>
+__global__ __launch_bounds__(256) void slice_tables_kernel(const Key* __restrict__ K, size_t M, Spec sp, uint32_t tiles,
+                                                           Numbers n) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t t = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (t >= tiles) return;
+  Count4 c = n.tile[t];
+  const unsigned long long below = (1ull << lane) - 1ull;
+  for (uint32_t j = 0; j < kTile; j += 64) {
+    const size_t p = (size_t)t * kTile + j + lane;
+    const uint32_t b = p < M ? begins(K, p, sp) : 0u;
+    uint32_t before[4];
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+      before[l] = 0;
+      if (l <= sp.NF) {
+        const unsigned long long w = __ballot((b >> l) & 1u);
+        before[l] = c.v[l] + (uint32_t)__popcll(w & below);
+        c.v[l] += (uint32_t)__popcll(w);
+      }
+    }
+    if (b & 1u) {
+      n.sStart[before[0]] = (uint32_t)p;
+      for (int l = 1; l <= sp.NF; ++l) n.fStart[l - 1][before[0]] = before[l];
+    }
+    if (p == M - 1) {  // one past the last slice
+      const uint32_t S = before[0] + (b & 1u);
+      n.sStart[S] = (uint32_t)M;
+      for (int l = 1; l <= sp.NF; ++l) n.fStart[l - 1][S] = before[l] + ((b >> l) & 1u);
+      n.count[0] = S;
+    }
+  }
+}
+
+// Section V / VI-D: one nonzero -> COO; every fiber a single nonzero -> CSL; otherwise CSF
+__device__ __forceinline__ GroupCounts slice_counts(const Numbers& n, const Spec& sp, uint32_t s, int& g) {
+  const uint32_t m = n.sStart[s + 1] - n.sStart[s];
+  uint32_t f[3] = {0, 0, 0};
+  for (int l = 0; l < sp.NF; ++l) f[l] = n.fStart[l][s + 1] - n.fStart[l][s];
+  if (m == 1 && sp.cooOn) g = kCoo;
+  else if (f[sp.NF - 1] == m && sp.cslOn) g = kCsl;
+  else g = kCsf;
+  GroupCounts c{{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    c.s[k] = g == k ? 1u : 0u;
+    c.m[k] = g == k ? m : 0u;
+    c.f[k] = g == kCsf ? f[k] : 0u;
+  }
+  return c;
+}
+
+// inclusive sum over the block's threads, with the block's total in `total`
+__device__ __forceinline__ GroupCounts block_sum(GroupCounts c, GroupCounts& total) {
+  __shared__ GroupCounts wave[4];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  auto each = [](GroupCounts& x, auto&& f) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      f(x.s[k]);
+      f(x.m[k]);
+      f(x.f[k]);
+    }
+  };
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1)
+    each(c, [&](uint32_t& v) {
+      const uint32_t up = __shfl_up(v, o);
+      if (lane >= o) v += up;
+    });
+  if (lane == 63) wave[w] = c;
+  __syncthreads();
+  GroupCountsPlus plus;
+  for (int k = 0; k < w; ++k) c = plus(c, wave[k]);
+  total = plus(plus(wave[0], wave[1]), plus(wave[2], wave[3]));
+  __syncthreads();
+  return c;
+}
+
+__global__ __launch_bounds__(256) void count_slices_kernel(Numbers n, Spec sp, uint32_t blocks) {
+  GroupCountsPlus plus;
+  GroupCounts c{{0, 0, 0}, {0, 0, 0}, {0, 0, 0}}, total;
+  const uint32_t S = n.count[0];
+  const uint64_t first = (uint64_t)blockIdx.x * kSliceBlock;
+  if (blockIdx.x < blocks)
+    for (uint32_t k = 0; k < kSliceBlock; k += 256) {
+      const uint64_t s = first + k + threadIdx.x;
+      int g;
+      if (s < S) c = plus(c, slice_counts(n, sp, (uint32_t)s, g));
+    }
+  block_sum(c, total);
+  if (threadIdx.x == 0) n.block[blockIdx.x] = total;
+}
+
+__global__ __launch_bounds__(256) void number_slices_kernel(Numbers n, Spec sp) {
+  GroupCountsPlus plus;
+  const uint32_t S = n.count[0];
+  GroupCounts before = n.block[blockIdx.x];
+  for (uint32_t k = 0; k < kSliceBlock; k += 256) {
+    const uint64_t s = (uint64_t)blockIdx.x * kSliceBlock + k + threadIdx.x;
+    if ((uint64_t)blockIdx.x * kSliceBlock + k >= S) return;  // the same for the whole block
+    int g = kCoo;
+    GroupCounts own{{0, 0, 0}, {0, 0, 0}, {0, 0, 0}}, total;
+    if (s < S) own = slice_counts(n, sp, (uint32_t)s, g);
+    const GroupCounts upTo = block_sum(own, total);
+    if (s < S) {
+      SliceInfo i;
+      i.off = before.m[g] + upTo.m[g] - own.m[g];
+      i.ord = before.s[g] + upTo.s[g] - own.s[g];
+      i.grp = (uint32_t)g;
+      i.fib0 = before.f[0] + upTo.f[0] - own.f[0];
+      n.info[s] = i;
+      for (int l = 1; l < sp.NF; ++l) n.fib[l - 1][s] = before.f[l] + upTo.f[l] - own.f[l];
+      if (g == kCsf) {
+        n.csfOff[i.ord] = i.off;
+        n.csfStart[i.ord] = n.sStart[s];
+      }
+    }
+    before = plus(before, total);
+  }
+}
+
+// Per run of the CSF stream and level: does it begin inside a fiber?
+template <typename Key>
+__global__ __launch_bounds__(256) void find_cuts_kernel(const Key* __restrict__ K, Spec sp, Numbers n, uint32_t blocks,
+                                                        uint32_t maxRuns) {
+  const uint32_t r = blockIdx.x * 256 + threadIdx.x;
+  if (r > maxRuns) return;
+  const GroupCounts& all = n.block[blocks];
+  const uint64_t at = (uint64_t)r * sp.L;
+  Count4 c{{0, 0, 0, 0}};
+  if (at < all.m[kCsf]) {
+    uint32_t lo = 0, hi = all.s[kCsf];  // the last slice that begins at or before `at`
+    while (hi - lo > 1) {
+      const uint32_t mid = lo + (hi - lo) / 2;
+      if (n.csfOff[mid] <= at) lo = mid;
+      else hi = mid;
+    }
+    const uint32_t b = begins(K, (size_t)n.csfStart[lo] + (size_t)(at - n.csfOff[lo]), sp);
+    for (int l = 1; l <= sp.NF; ++l) c.v[l] = (b >> l) & 1u ? 0u : 1u;
+  }
+  n.cut[r] = c;
+}
+
+__global__ void totals_kernel(Numbers n, Spec sp, uint32_t tiles, uint32_t blocks, uint32_t maxRuns,
+                              const unsigned long long* bad, Totals* out) {
+  Totals t{};
+  t.bad = (uint32_t)*bad;
+  t.S = n.count[0];
+  for (int l = 0; l < sp.NF; ++l) {
+    t.fibNat[l] = n.tile[tiles].v[1 + l];
+    t.extra[l] = n.cut[maxRuns].v[1 + l];
+  }
+  t.g = n.block[blocks];
+  *out = t;
+}
+
+// Every nonzero writes itself into its group's stream; segment starts write the fiber-level entries.  A wavefront takes
+// kFill chunks of 64 nonzeros at a time and issues the loads of all of them first (keys, values; then slice tables), since each nonzero's chain key -> slice -> place is three loads long and the stores between them
+// may not be passed by a load.
+constexpr int kFill = 4;
+template <typename Key, int N>
+__global__ __launch_bounds__(256) void fill_tiles_kernel(const Key* __restrict__ K, const uint32_t* __restrict__ V, size_t M,
+                                                         Spec sp, uint32_t tiles, Numbers n, OutArrays o) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t t = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (t >= tiles) return;
+  Count4 c = n.tile[t];
+  const unsigned long long below = (1ull << lane) - 1ull;
+  constexpr int leaf = N - 1, NF = N - 2;
+  for (uint32_t j0 = 0; j0 < kTile; j0 += 64 * kFill) {
+    Key key[kFill];
+    uint32_t b[kFill], v[kFill], s[kFill], begun[kFill][3], start[kFill], leafIdx[kFill];
+    SliceInfo in[kFill];
+#pragma unroll
+    for (int q = 0; q < kFill; ++q) {
+      const size_t p = (size_t)t * kTile + j0 + q * 64 + lane;
+      b[q] = 0;
+      key[q] = 0;
+      v[q] = 0;
+      if (p < M) {
+        b[q] = begins(K, p, sp);
+        key[q] = K[p];
+        v[q] = V[p];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kFill; ++q) {
+      const size_t p = (size_t)t * kTile + j0 + q * 64 + lane;
+      s[q] = 0;
+#pragma unroll
+      for (int l = 0; l <= NF; ++l) {  // begun before p
+        const unsigned long long w = __ballot((b[q] >> l) & 1u);
+        const uint32_t before = c.v[l] + (uint32_t)__popcll(w & below);
+        c.v[l] += (uint32_t)__popcll(w);
+        if (l == 0) s[q] = before + (b[q] & 1u) - 1u;
+        else begun[q][l > 0 ? l - 1 : 0] = before;
+      }
+      if (p < M) {
+        in[q] = n.info[s[q]];
+        start[q] = n.sStart[s[q]];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kFill; ++q) {
+      leafIdx[q] = (uint32_t)((uint64_t)key[q] & sp.mask[leaf]);
+    }
+#pragma unroll
+    for (int q = 0; q < kFill; ++q) {
+      const size_t p = (size_t)t * kTile + j0 + q * 64 + lane;
+      if (p >= M) continue;
+      const uint32_t pos = in[q].off + ((uint32_t)p - start[q]);
+      auto index = [&](int l) { return (uint32_t)((uint64_t)(key[q] >> sp.shift[l]) & sp.mask[l]); };
+      const bool cut = (pos & (sp.L - 1u)) == 0;
+      if (in[q].grp == kCsf) {
+        o.csfVal[pos] = v[q];
+        o.csfInd[leaf][pos] = leafIdx[q];
+        mark_row(sp, leaf, o.seen[kCsf][leaf], leafIdx[q]);
+        if (cut) o.csfRun[0][pos / sp.L] = in[q].ord;
+#pragma unroll
+        for (int l = 1; l <= NF; ++l) {
+          if (cut || ((b[q] >> l) & 1u)) {
+            // fibers before the slice and in it, cuts before this place
+            const uint32_t fibers = l == 1 ? in[q].fib0 : n.fib[l == 3 ? 1 : 0][s[q]];
+            const uint32_t id = fibers + begun[q][l - 1] - n.fStart[l - 1][s[q]] + n.cut[(pos + sp.L - 1u) / sp.L].v[l];
+            const uint32_t i = index(l);
+            o.csfInd[l][id] = i;
+            o.csfPtr[l][id] = pos;
+            mark_row(sp, l, o.seen[kCsf][l], i);
+            if (cut) o.csfRun[l][pos / sp.L] = id;
+          }
+        }
+      } else if (in[q].grp == kCsl) {
+        o.cslVal[pos] = v[q];
+        if (cut) o.cslRun[pos / sp.L] = in[q].ord;
+        o.cslInd[leaf][pos] = leafIdx[q];
+        mark_row(sp, leaf, o.seen[kCsl][leaf], leafIdx[q]);
+#pragma unroll
+        for (int l = 1; l < leaf; ++l) {
+            const uint32_t i = index(l);
+            o.cslInd[l][pos] = i;
+            mark_row(sp, l, o.seen[kCsl][l], i);
+          }
+      } else {
+        o.cooVal[pos] = v[q];
+        o.cooInd[leaf][pos] = leafIdx[q];
+        mark_row(sp, leaf, o.seen[kCoo][leaf], leafIdx[q]);
+#pragma unroll
+        for (int l = 1; l < leaf; ++l) {
+            const uint32_t i = index(l);
+            o.cooInd[l][pos] = i;
+            mark_row(sp, l, o.seen[kCoo][l], i);
+          }
+        const uint32_t root = index(0);
+        if (!sp.cooRowFlags) o.cooInd[0][pos] = root;
+        atomicOr(&o.cooBits[root >> 5], 1u << (root & 31));
+        atomicOr(&o.owned[root >> 5], 1u << (root & 31));
+      }
+    }
+  }
+}
+
+// Per-slice entries of the CSL and CSF groups; a slice inside one run owns its output row.
+template <typename Key>
+__global__ __launch_bounds__(256) void fill_slice_entries_kernel(const Key* __restrict__ K, uint32_t S, Spec sp, Numbers n,
+                                                                 OutArrays o, unsigned long long* cnt) {
+  unsigned long long shared = 0;
+  for (uint64_t s = (uint64_t)blockIdx.x * 256 + threadIdx.x; s < S; s += (uint64_t)gridDim.x * 256) {
+    const SliceInfo in = n.info[s];
+    if (in.grp == kCoo) continue;
+    const uint32_t b = n.sStart[s], m = n.sStart[s + 1] - b;
+    const uint32_t root = (uint32_t)((uint64_t)(K[b] >> sp.shift[0]) & sp.mask[0]);
+    const bool own = sp.blockBits == 0 && (in.off / sp.L) == ((in.off + m - 1) / sp.L);
+    uint32_t* ind = in.grp == kCsl ? o.cslInd[0] : o.csfInd[0];
+    uint32_t* ptr = in.grp == kCsl ? o.cslPtr : o.csfPtr[0];
+    ind[in.ord] = root | (own ? kOwnedBit : 0u);
+    ptr[in.ord] = in.off;
+    if (own) atomicOr(&o.owned[root >> 5], 1u << (root & 31));
+    else ++shared;
+  }
+  wave_add(cnt + 1, shared);
+}
+
 struct Sentinels {
   uint64_t cslN0, cslNnz, cslRuns, csfN[HBCSF_MAX_ORDER], csfNnz, csfRuns;
 };
@@ -428,16 +859,24 @@ __global__ void sentinel_kernel(Spec sp, OutArrays o, Sentinels z) {
   }
 }
 
-__global__ void zero_words_kernel(uint32_t* p, size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
+__global__ void zero_words_kernel(uint32_t* a, size_t na, uint32_t* b, size_t nb, uint32_t* c, size_t nc) {
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < na + nb + nc; i += (size_t)gridDim.x * blockDim.x)
+    *(i < na ? a + i : i < na + nb ? b + (i - na) : c + (i - na - nb)) = 0;
 }
 
-__global__ void count_bits_kernel(const uint32_t* bitmap, size_t words, unsigned long long* dst) {
+// Bits set in several maps (bitmaps, or bytes of 0 and 1): blockIdx.y says which.
+struct BitCounts {
+  const uint32_t* map[1 + 3 * (HBCSF_MAX_ORDER - 1)];
+  size_t words[1 + 3 * (HBCSF_MAX_ORDER - 1)];
+  int to[1 + 3 * (HBCSF_MAX_ORDER - 1)];  // place in cnt
+};
+__global__ void count_bits_kernel(BitCounts b, unsigned long long* cnt) {
+  const uint32_t* map = b.map[blockIdx.y];
+  const size_t words = b.words[blockIdx.y];
   unsigned long long c = 0;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += (size_t)gridDim.x * blockDim.x)
-    c += (unsigned long long)__popc(bitmap[i]);
-  wave_add(dst, c);
+    c += (unsigned long long)__popc(map[i]);
+  wave_add(cnt + b.to[blockIdx.y], c);
 }
 
 // for kernels that loop over their items and end in a few same-address atomics per wavefront
@@ -447,21 +886,22 @@ inline uint64_t up256(uint64_t v) { return (v + 255) / 256 * 256; }
 
 // Workspace carve-up for M nonzeros; `temp` is the rocPRIM scratch, sized by temp_bytes().
 struct Workspace {
-  uint64_t* K[2];        // 64-bit sort keys (the packed key, or one half of a wide key), double buffered
-  uint32_t* V[2];        // values riding along a 64-bit key sort, double buffered
+  uint64_t* K[3];        // 64-bit sort keys: the common order and a double buffer (wide keys: two are used)
+  uint32_t* V[3];        // values (or places) riding along
   Carried* C[2];         // wide keys only: the other half + value, double buffered
-  u128* K128;            // wide keys only: the sorted keys put together again
-  uint32_t* seg2;        // order 5 only: the third fiber level's scan
+  u128* K128[2];         // wide keys only: the common order, one mode's order
+  Numbers n;             // numbering tables
+  uint32_t* seg2;        // order 5 with the per-fiber choice: the third fiber level's scan
   uint32_t* sgScan;      // per-fiber choice only: scan of the singleton-fiber flags
   uint32_t* nat[2];      // per-fiber choice, orders 4 / 5: natural fiber numbers of the upper fiber levels
   uint32_t* firstKept[2];  // ... and the first nonzero of each such fiber that stays in the CSF group
-  uint32_t* sStart;
-  uint8_t* grp;
-  C6* c6;
-  unsigned long long* cnt;  // 32 counters
+  uint8_t* grp;          // per-fiber choice only
+  C6* c6;                // per-fiber choice only
+  unsigned long long* bad;  // an index is not below its dimension
+  unsigned long long* cnt;  // kCounters per mode
+  Totals* totals;
   double* normSq;
-  uint32_t* bitmap;      // 3 groups x (order - 1) levels of row bitmaps (statistics)
-  size_t bitmapWords;    // words of one of them
+  uint8_t* seen;         // row maps of the 3 groups and the levels below the root (statistics)
   void* temp;
   size_t tempBytes;
   uint64_t total;
@@ -469,7 +909,21 @@ struct Workspace {
 
 constexpr int kCounters = 32;
 
-hipError_t temp_bytes(size_t M, size_t maxWords, int totalBits, size_t* out) {
+// Is the group chosen per fiber?  (needs the CSL group)
+bool per_fiber(const hbcsf_opts& o) { return o.hybrid_granularity == 1 && (o.group_mask == 0 || (o.group_mask & 2u)); }
+
+// Bytes of a mode's row map, and of one group's row maps of all modes.
+uint64_t row_map_bytes(uint64_t rows) { return up256(rows <= kByteRows ? rows : (rows + 7) / 8); }
+uint64_t row_maps_bytes(int order, const uint64_t* dims) {
+  uint64_t sum = 0;
+  for (int m = 0; m < order; ++m) sum += row_map_bytes(dims[m]);
+  return sum;
+}
+
+// Entries the slice tables need: slices are at most nonzeros, and without blocking at most rows.
+uint64_t slice_bound(size_t M, uint64_t maxDim, bool blocked) { return blocked || (uint64_t)M < maxDim ? (uint64_t)M : maxDim; }
+
+hipError_t temp_bytes(size_t M, size_t maxWords, uint64_t slices, uint32_t L, int totalBits, size_t* out) {
   const bool wide = totalBits > 64;
   // the largest scratch any rocPRIM call below asks for
   size_t need = 0, b = 0;
@@ -485,6 +939,14 @@ hipError_t temp_bytes(size_t M, size_t maxWords, int totalBits, size_t* out) {
     if (e != hipSuccess) return e;
     need = b > need ? b : need;
   }
+  const size_t runs = M / L + 2, tiles = M / kTile + 2;
+  e = rocprim::exclusive_scan(nullptr, b, (Count4*)nullptr, (Count4*)nullptr, Count4{}, runs > tiles ? runs : tiles, Count4Plus());
+  if (e != hipSuccess) return e;
+  need = b > need ? b : need;
+  e = rocprim::exclusive_scan(nullptr, b, (GroupCounts*)nullptr, (GroupCounts*)nullptr, GroupCounts{},
+                              (size_t)(slices / kSliceBlock + 2), GroupCountsPlus());
+  if (e != hipSuccess) return e;
+  need = b > need ? b : need;
   auto cnt = rocprim::counting_iterator<size_t>(0);
   e = rocprim::inclusive_scan(nullptr, b, rocprim::make_transform_iterator(cnt, FreshFlag<u128>{nullptr, 0}),
                               (uint32_t*)nullptr, M + 1, rocprim::plus<uint32_t>());
@@ -514,32 +976,43 @@ hipError_t temp_bytes(size_t M, size_t maxWords, int totalBits, size_t* out) {
   return hipSuccess;
 }
 
-void carve(Workspace& w, uint8_t* base, int order, size_t M, uint64_t maxDim, size_t tempBytes, bool wide,
-           bool perFiber) {
+void carve(Workspace& w, uint8_t* base, int order, size_t M, uint64_t mapBytes, uint64_t slices, uint32_t L, size_t tempBytes,
+           bool wide, bool perFiber) {
   uint64_t off = 0;
   auto take = [&](uint64_t bytes) {
     uint8_t* p = base ? base + off : nullptr;
     off += up256(bytes);
     return p;
   };
-  for (int i = 0; i < 2; ++i) w.K[i] = (uint64_t*)take((M + 1) * 8);
-  for (int i = 0; i < 2; ++i) w.V[i] = (uint32_t*)take((M + 1) * 4);
+  for (int i = 0; i < 3; ++i) w.K[i] = wide && i == 2 ? nullptr : (uint64_t*)take((M + 1) * 8);
+  for (int i = 0; i < 3; ++i) w.V[i] = (uint32_t*)take((M + 1) * 4);
   for (int i = 0; i < 2; ++i) w.C[i] = wide ? (Carried*)take((M + 1) * sizeof(Carried)) : nullptr;
-  w.K128 = wide ? (u128*)take((M + 1) * 16) : nullptr;
-  w.seg2 = order >= 5 ? (uint32_t*)take((M + 2) * 4) : nullptr;
+  for (int i = 0; i < 2; ++i) w.K128[i] = wide ? (u128*)take((M + 1) * 16) : nullptr;
+  const uint64_t tables = perFiber ? (uint64_t)M : slices;
+  w.n.tile = (Count4*)take((M / kTile + 2) * sizeof(Count4));
+  w.n.sStart = (uint32_t*)take((tables + 2) * 4);
+  for (int l = 0; l < 3; ++l) w.n.fStart[l] = l < order - 2 && !perFiber ? (uint32_t*)take((tables + 2) * 4) : nullptr;
+  w.n.block = (GroupCounts*)take((tables / kSliceBlock + 2) * sizeof(GroupCounts));
+  w.n.info = perFiber ? nullptr : (SliceInfo*)take((tables + 1) * sizeof(SliceInfo));
+  for (int l = 0; l < 2; ++l) w.n.fib[l] = l + 1 < order - 2 && !perFiber ? (uint32_t*)take((tables + 1) * 4) : nullptr;
+  w.n.csfOff = perFiber ? nullptr : (uint32_t*)take((tables + 1) * 4);
+  w.n.csfStart = perFiber ? nullptr : (uint32_t*)take((tables + 1) * 4);
+  w.n.cut = (Count4*)take((M / L + 2) * sizeof(Count4));
+  w.n.count = (uint32_t*)take(4);
+  w.seg2 = perFiber && order >= 5 ? (uint32_t*)take((M + 2) * 4) : nullptr;
   w.sgScan = perFiber ? (uint32_t*)take((M + 2) * 4) : nullptr;
   for (int f = 0; f < 2; ++f) {
     const bool upper = perFiber && f < order - 3;   // fiber level f + 1 lies above the deepest one
     w.nat[f] = upper ? (uint32_t*)take((M + 2) * 4) : nullptr;
     w.firstKept[f] = upper ? (uint32_t*)take((M + 2) * 4) : nullptr;
   }
-  w.sStart = (uint32_t*)take((M + 2) * 4);
-  w.grp = (uint8_t*)take(M + 1);
-  w.c6 = (C6*)take((M + 2) * sizeof(C6));
-  w.cnt = (unsigned long long*)take(kCounters * 8);
+  w.grp = perFiber ? (uint8_t*)take(M + 1) : nullptr;
+  w.c6 = perFiber ? (C6*)take((M + 2) * sizeof(C6)) : nullptr;
+  w.bad = (unsigned long long*)take(8);
+  w.cnt = (unsigned long long*)take(HBCSF_MAX_ORDER * kCounters * 8);
+  w.totals = (Totals*)take(sizeof(Totals));
   w.normSq = (double*)take(8);
-  w.bitmap = (uint32_t*)take(3 * (HBCSF_MAX_ORDER - 1) * ((maxDim + 31) / 32 + 1) * 4);
-  w.bitmapWords = (maxDim + 31) / 32 + 1;
+  w.seen = (uint8_t*)take(3 * mapBytes);
   w.temp = take(tempBytes);
   w.tempBytes = tempBytes;
   w.total = off;
@@ -600,170 +1073,245 @@ int check_args(int order, const uint64_t* dims, uint64_t nnz, const hbcsf_opts* 
     if (e_ != hipSuccess) return fail_hip(e_, what); \
   } while (0)
 
-template <typename Key>
-int build_mode_device(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds, const float* vals,
-                      const hbcsf_opts& opts, int mode, int totalBits, Workspace& w, uint8_t* arena,
-                      uint64_t arenaBytes, uint64_t* arenaUsed, ModeFormat* out, hipStream_t st) {
-  const auto t_begin = std::chrono::steady_clock::now();
+// What one mode's build needs to know, and what it leaves for the end.
+struct ModeBuild {
   Spec sp{};
-  sp.N = N;
-  sp.NF = N - 2;
-  sp.L = opts.fiber_threshold;
-  const uint32_t gmask = opts.group_mask == 0 ? 3u : (opts.group_mask & 3u);
-  sp.blockBits = mid_block_bits(N, dims, opts, mode);
-  sp.cooOn = (gmask & 1u) && sp.blockBits == 0 ? 1u : 0u;   // with blocking no piece owns its row
-  sp.cslOn = (gmask & 2u) ? 1u : 0u;
-  sp.cooRowFlags = opts.coo_row_flags == 1 ? 1u : 0u;
-  sp.perFiber = opts.hybrid_granularity == 1 && sp.cslOn ? 1u : 0u;
-  int lv[HBCSF_MAX_ORDER];
-  level_order(N, dims, mode, opts.mode_order_policy, lv);
-  int total = 0;
-  for (int l = N - 1; l >= 0; --l) {
-    const int b = bits_for(dims[lv[l]]);
-    sp.shift[l] = total;
-    sp.mask[l] = (1ull << b) - 1;
-    total += b;
-  }
-  out->order = N;
-  out->mode = mode;
-  sp.blockShift = total;
-  sp.blockDrop = sp.blockBits ? bits_for(dims[lv[1]]) - sp.blockBits : 0;
-  out->L = sp.L;
-  out->blockBits = sp.blockBits;
-  out->cooRowFlags = sp.cooRowFlags != 0;
-  out->rows = dims[mode];
-  for (int l = 0; l < N; ++l) out->levelMode[l] = lv[l];
+  ModeKey mk{};
+  int keyBits = 0;   // of this mode's key, block bits included
+  uint64_t S = 0, gS[3] = {0, 0, 0}, gM[3] = {0, 0, 0};
+  uint64_t nSeg[HBCSF_MAX_FIBER_LEVELS] = {0, 0, 0}, fibNat[HBCSF_MAX_FIBER_LEVELS] = {0, 0, 0};
+  uint64_t fibCsf[HBCSF_MAX_FIBER_LEVELS] = {0, 0, 0};
+  unsigned long long* cnt = nullptr;  // device counters: [1] shared slices, [2], [3], [5] CSF fibers (per-fiber choice),
+                                      // [4] owned rows, [8 ..] distinct rows
+};
 
-  uint64_t S = 0, gS[3] = {0, 0, 0}, gM[3] = {0, 0, 0}, nSeg[HBCSF_MAX_FIBER_LEVELS] = {0, 0, 0}, fibNat[HBCSF_MAX_FIBER_LEVELS] = {0, 0, 0};
-  unsigned long long hostCnt[kCounters];
-  std::memset(hostCnt, 0, sizeof(hostCnt));
-  HIP_TRY(hipMemsetAsync(w.cnt, 0, kCounters * 8, st), "hipMemsetAsync");
+// The sorted nonzeros of one mode, and two buffers of 8 (M + 1) and 4 (M + 1) bytes free until the next mode.
+template <typename Key>
+struct Sorted {
   const Key* K = nullptr;
-  const uint32_t* V = w.V[0];
-  uint32_t* sidp = nullptr;
-  uint32_t* seg[3] = {nullptr, nullptr, w.seg2};
-  Tables tb{};
+  const uint32_t* V = nullptr;
+  void* freeKeys = nullptr;
+  void* freeVals = nullptr;
+};
+
+// The common order of all modes: base.K / base.V (they must survive until the last mode is built).
+template <typename Key>
+int sort_base(int N, size_t M, const uint32_t* const* inds, const float* vals, const BaseKey& bk, int totalBits, Workspace& w,
+              Sorted<Key>* base, hipStream_t st) {
+  constexpr bool kWide = sizeof(Key) == 16;
+  IndPtrs ip{};
+  for (int m = 0; m < N; ++m) ip.p[m] = inds[m];
+  hipLaunchKernelGGL(pack_kernel<Key>, dim3(grid_for(M)), dim3(256), 0, st, ip, vals, M, N, bk, w.K[0], w.V[0], w.C[0], w.bad);
+  rocprim::double_buffer<uint64_t> kb(w.K[0], w.K[1]);
+  size_t tb = w.tempBytes;
+  if constexpr (!kWide) {
+    rocprim::double_buffer<uint32_t> vb(w.V[0], w.V[1]);
+    HIP_TRY(rocprim::radix_sort_pairs(w.temp, tb, kb, vb, M, 0u, (unsigned)totalBits, st), "radix sort");
+    base->K = kb.current();
+    base->V = vb.current();
+    // from here on the sorted keys are buffer 2, the two others the double buffer of the modes' sorts
+    uint64_t* k = kb.current() == w.K[0] ? w.K[0] : w.K[1];
+    uint32_t* v = vb.current() == w.V[0] ? w.V[0] : w.V[1];
+    uint64_t* k2 = w.K[2];
+    uint32_t* v2 = w.V[2];
+    w.K[2] = k;
+    w.V[2] = v;
+    (k == w.K[0] ? w.K[0] : w.K[1]) = k2;
+    (v == w.V[0] ? w.V[0] : w.V[1]) = v2;
+  } else {
+    // two stable passes: by the low 64 bits with the high half riding along, then by the high bits
+    rocprim::double_buffer<Carried> cb(w.C[0], w.C[1]);
+    HIP_TRY(rocprim::radix_sort_pairs(w.temp, tb, kb, cb, M, 0u, 64u, st), "radix sort");
+    hipLaunchKernelGGL(swap_halves_kernel, dim3(grid_for(M)), dim3(256), 0, st, kb.current(), cb.current(), M,
+                       kb.alternate(), cb.alternate());
+    rocprim::double_buffer<uint64_t> kb2(kb.alternate(), kb.current());
+    rocprim::double_buffer<Carried> cb2(cb.alternate(), cb.current());
+    tb = w.tempBytes;
+    // (a key may be wide by its block bits alone, which are not in this order)
+    HIP_TRY(rocprim::radix_sort_pairs(w.temp, tb, kb2, cb2, M, 0u, (unsigned)(totalBits > 64 ? totalBits - 64 : 1), st),
+            "radix sort");
+    hipLaunchKernelGGL(join_halves_kernel, dim3(grid_for(M)), dim3(256), 0, st, kb2.current(), cb2.current(), M,
+                       w.K128[0], w.V[2]);
+    base->K = w.K128[0];
+    base->V = w.V[2];
+  }
+  return HBCSF_OK;
+}
+
+// One mode's order: a stable sort of the common order by (block,) root.  isBase: the common order is this mode's own.
+template <typename Key>
+int sort_mode(size_t M, const Sorted<Key>& base, const ModeBuild& mb, bool isBase, Workspace& w, Sorted<Key>* out, hipStream_t st) {
+  constexpr bool kWide = sizeof(Key) == 16;
+  if (isBase) {
+    *out = base;
+    out->freeKeys = w.K[0];
+    out->freeVals = w.V[0];
+    return HBCSF_OK;
+  }
+  rocprim::double_buffer<uint64_t> kb(w.K[0], w.K[1]);
+  rocprim::double_buffer<uint32_t> vb(w.V[0], w.V[1]);
+  size_t tb = w.tempBytes;
+  if constexpr (!kWide) {
+    hipLaunchKernelGGL(mode_key_kernel, dim3(grid_for(M)), dim3(256), 0, st, base.K, base.V, M, mb.sp, mb.mk, w.K[0], w.V[0]);
+    HIP_TRY(rocprim::radix_sort_pairs(w.temp, tb, kb, vb, M, (unsigned)mb.sp.shift[0], (unsigned)mb.keyBits, st), "radix sort");
+    out->K = kb.current();
+    out->V = vb.current();
+    out->freeKeys = kb.alternate();
+    out->freeVals = vb.alternate();
+  } else {
+    hipLaunchKernelGGL(root_key_kernel, dim3(grid_for(M)), dim3(256), 0, st, base.K, M, mb.sp, mb.mk, w.K[0], w.V[0]);
+    HIP_TRY(rocprim::radix_sort_pairs(w.temp, tb, kb, vb, M, 0u, (unsigned)(mb.keyBits - mb.sp.shift[0]), st), "radix sort");
+    hipLaunchKernelGGL(fetch_kernel, dim3(grid_for(M)), dim3(256), 0, st, base.K, base.V, vb.current(), M, mb.sp, mb.mk,
+                       w.K128[1], vb.alternate());
+    out->K = w.K128[1];
+    out->V = vb.alternate();
+    out->freeKeys = kb.current();
+    out->freeVals = vb.current();
+  }
+  return HBCSF_OK;
+}
+
+// Numbers slices, fibers and cuts of one mode and brings the group sizes to the host (one wait).
+template <typename Key>
+int number_mode(size_t M, uint64_t slices, const Sorted<Key>& so, ModeBuild& mb, Workspace& w, hipStream_t st) {
+  const Spec& sp = mb.sp;
+  const uint32_t tiles = (uint32_t)((M + kTile - 1) / kTile);
+  const uint32_t blocks = (uint32_t)((slices + kSliceBlock - 1) / kSliceBlock);
+  const uint32_t maxRuns = (uint32_t)((M + sp.L - 1) / sp.L);
+  const dim3 tileGrid(tiles / 4 + 1);
+  size_t tb = w.tempBytes;
+  hipLaunchKernelGGL(count_tiles_kernel<Key>, tileGrid, dim3(256), 0, st, so.K, M, sp, tiles, w.n.tile);
+  HIP_TRY(rocprim::exclusive_scan(w.temp, tb, w.n.tile, w.n.tile, Count4{}, (size_t)tiles + 1, Count4Plus(), st), "scan");
+  hipLaunchKernelGGL(slice_tables_kernel<Key>, tileGrid, dim3(256), 0, st, so.K, M, sp, tiles, w.n);
+  hipLaunchKernelGGL(count_slices_kernel, dim3(blocks + 1), dim3(256), 0, st, w.n, sp, blocks);
+  tb = w.tempBytes;
+  HIP_TRY(rocprim::exclusive_scan(w.temp, tb, w.n.block, w.n.block, GroupCounts{}, (size_t)blocks + 1, GroupCountsPlus(), st),
+          "scan");
+  hipLaunchKernelGGL(number_slices_kernel, dim3(blocks), dim3(256), 0, st, w.n, sp);
+  hipLaunchKernelGGL(find_cuts_kernel<Key>, dim3(maxRuns / 256 + 1), dim3(256), 0, st, so.K, sp, w.n, blocks, maxRuns);
+  tb = w.tempBytes;
+  HIP_TRY(rocprim::exclusive_scan(w.temp, tb, w.n.cut, w.n.cut, Count4{}, (size_t)maxRuns + 1, Count4Plus(), st), "scan");
+  hipLaunchKernelGGL(totals_kernel, dim3(1), dim3(1), 0, st, w.n, sp, tiles, blocks, maxRuns, w.bad, w.totals);
+  Totals t{};
+  HIP_TRY(hipMemcpyAsync(&t, w.totals, sizeof(Totals), hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
+  HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
+  if (t.bad) return fail(HBCSF_ERANGE, "an index is not below its dimension");
+  mb.S = t.S;
+  for (int g = 0; g < 3; ++g) {
+    mb.gS[g] = t.g.s[g];
+    mb.gM[g] = t.g.m[g];
+  }
+  for (int f = 0; f < sp.NF; ++f) {
+    mb.fibNat[f] = t.fibNat[f];
+    mb.fibCsf[f] = t.g.f[f];
+    mb.nSeg[f] = (uint64_t)t.g.f[f] + t.extra[f];
+  }
+  return HBCSF_OK;
+}
+
+// The per-fiber group choice: numbering through scans over the nonzeros (two waits).  sidp and seg[] lie in the sort's
+// free buffers.
+template <typename Key>
+int number_mode_per_fiber(size_t M, const Sorted<Key>& so, ModeBuild& mb, Workspace& w, Tables* tables, uint32_t* (&seg)[3],
+                          hipStream_t st) {
+  const Spec& sp = mb.sp;
+  const Key* K = so.K;
+  uint32_t* sidp = (uint32_t*)so.freeKeys;
+  seg[0] = sidp + (M + 1);
+  seg[1] = (uint32_t*)so.freeVals;
+  seg[2] = w.seg2;
+  Tables& tb = *tables;
   auto cit = rocprim::counting_iterator<size_t>(0);
-
-  if (M > 0) {
-    // ---- packed keys, sorted; the value rides along ----
-    IndPtrs ip{};
-    uint64_t dl[HBCSF_MAX_ORDER] = {1, 1, 1, 1, 1};
-    for (int l = 0; l < N; ++l) {
-      ip.p[l] = inds[lv[l]];
-      dl[l] = dims[lv[l]];
-    }
-    constexpr bool kWide = sizeof(Key) == 16;
-    hipLaunchKernelGGL(pack_kernel<Key>, dim3(grid_for(M)), dim3(256), 0, st, ip, vals, M, sp, dl[0], dl[1], dl[2],
-                       dl[3], dl[4], w.K[0], w.V[0], w.C[0], w.cnt);
-    rocprim::double_buffer<uint64_t> kb(w.K[0], w.K[1]);
-    size_t tb_ = w.tempBytes;
-    if (!kWide) {
-      rocprim::double_buffer<uint32_t> vb(w.V[0], w.V[1]);
-      HIP_TRY(rocprim::radix_sort_pairs(w.temp, tb_, kb, vb, M, 0u, (unsigned)totalBits, st), "radix sort");
-      K = (const Key*)kb.current();
-      V = vb.current();
-      // the buffers the sort no longer needs hold the per-nonzero scans from here on
-      sidp = (uint32_t*)kb.alternate();
-      seg[0] = sidp + (M + 1);
-      seg[1] = vb.alternate();
-    } else {
-      // two stable passes: by the low 64 bits with the high half riding along, then by the high bits
-      rocprim::double_buffer<Carried> cb(w.C[0], w.C[1]);
-      HIP_TRY(rocprim::radix_sort_pairs(w.temp, tb_, kb, cb, M, 0u, 64u, st), "radix sort");
-      hipLaunchKernelGGL(swap_halves_kernel, dim3(grid_for(M)), dim3(256), 0, st, kb.current(), cb.current(), M,
-                         kb.alternate(), cb.alternate());
-      rocprim::double_buffer<uint64_t> kb2(kb.alternate(), kb.current());
-      rocprim::double_buffer<Carried> cb2(cb.alternate(), cb.current());
-      tb_ = w.tempBytes;
-      HIP_TRY(rocprim::radix_sort_pairs(w.temp, tb_, kb2, cb2, M, 0u, (unsigned)(totalBits - 64), st), "radix sort");
-      hipLaunchKernelGGL(join_halves_kernel, dim3(grid_for(M)), dim3(256), 0, st, kb2.current(), cb2.current(), M,
-                         w.K128, w.V[1]);
-      K = (const Key*)w.K128;
-      V = w.V[1];
-      sidp = (uint32_t*)w.K[0];      // 8 (M + 1) bytes: slice numbers and the first fiber level's scan
-      seg[0] = sidp + (M + 1);
-      seg[1] = w.V[0];
-    }
-
-    // ---- slices: scan of "root index changes" ----
+  // ---- slices: scan of "root index changes" ----
+  size_t tb_ = w.tempBytes;
+  HIP_TRY(rocprim::inclusive_scan(w.temp, tb_, rocprim::make_transform_iterator(cit, FreshFlag<Key>{K, sp.shift[0]}),
+                                  sidp, M, rocprim::plus<uint32_t>(), st), "scan");
+  hipLaunchKernelGGL(slice_start_kernel<Key>, dim3(grid_for(M)), dim3(256), 0, st, K, sidp, M, sp.shift[0], w.n.sStart);
+  // natural fibers per level (the deepest level decides CSL membership)
+  for (int f = 0; f < sp.NF; ++f) {
     tb_ = w.tempBytes;
-    HIP_TRY(rocprim::inclusive_scan(w.temp, tb_, rocprim::make_transform_iterator(cit, FreshFlag<Key>{K, sp.shift[0]}),
-                                    sidp, M, rocprim::plus<uint32_t>(), st), "scan");
-    hipLaunchKernelGGL(slice_start_kernel<Key>, dim3(grid_for(M)), dim3(256), 0, st, K, sidp, M, sp.shift[0], w.sStart);
-    // natural fibers per level (the deepest level decides CSL membership)
-    for (int f = 0; f < sp.NF; ++f) {
-      tb_ = w.tempBytes;
-      HIP_TRY(rocprim::inclusive_scan(w.temp, tb_, rocprim::make_transform_iterator(cit, FreshFlag<Key>{K, sp.shift[1 + f]}),
-                                      seg[f], M, rocprim::plus<uint32_t>(), st), "scan");
-    }
-    uint32_t tail[4] = {0, 0, 0, 0};
-    HIP_TRY(hipMemcpyAsync(&tail[0], sidp + (M - 1), 4, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-    for (int f = 0; f < sp.NF; ++f)
-      HIP_TRY(hipMemcpyAsync(&tail[1 + f], seg[f] + (M - 1), 4, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-    HIP_TRY(hipMemcpyAsync(hostCnt, w.cnt, 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-    HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
-    if (hostCnt[0]) return fail(HBCSF_ERANGE, "an index is not below its dimension");
-    S = tail[0];
-    fibNat[0] = tail[1];
-    fibNat[1] = tail[2];
-    fibNat[2] = tail[3];
+    HIP_TRY(rocprim::inclusive_scan(w.temp, tb_, rocprim::make_transform_iterator(cit, FreshFlag<Key>{K, sp.shift[1 + f]}),
+                                    seg[f], M, rocprim::plus<uint32_t>(), st), "scan");
+  }
+  uint32_t tail[4] = {0, 0, 0, 0};
+  HIP_TRY(hipMemcpyAsync(&tail[0], sidp + (M - 1), 4, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
+  for (int f = 0; f < sp.NF; ++f)
+    HIP_TRY(hipMemcpyAsync(&tail[1 + f], seg[f] + (M - 1), 4, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
+  unsigned long long bad = 0;
+  HIP_TRY(hipMemcpyAsync(&bad, w.bad, 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
+  HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
+  if (bad) return fail(HBCSF_ERANGE, "an index is not below its dimension");
+  const size_t S = tail[0];
+  mb.S = S;
+  for (int f = 0; f < 3; ++f) mb.fibNat[f] = tail[1 + f];
 
-    // ---- per-fiber group choice: which nonzeros are whole fibers of their own; the natural fiber numbers of the
-    //      upper fiber levels are kept (the segment scans below overwrite seg[]) ----
-    if (sp.perFiber) {
-      tb_ = w.tempBytes;
-      HIP_TRY(rocprim::inclusive_scan(w.temp, tb_,
-                                      rocprim::make_transform_iterator(cit, SingleFlag<Key>{K, sp.shift[sp.NF], M}),
-                                      w.sgScan, M, rocprim::plus<uint32_t>(), st), "scan");
-      for (int f = 0; f + 1 < sp.NF; ++f)
-        HIP_TRY(hipMemcpyAsync(w.nat[f], seg[f], M * 4, hipMemcpyDeviceToDevice, st), "hipMemcpyAsync");
-    }
-    // ---- groups, and where every slice starts inside its group ----
-    hipLaunchKernelGGL(classify_kernel, dim3(grid_capped(S)), dim3(256), 0, st, w.sStart, seg[0], seg[1], seg[2], S, sp,
-                       sp.perFiber ? w.sgScan : nullptr, w.grp, w.cnt);
+  // ---- per-fiber group choice: which nonzeros are whole fibers of their own; the natural fiber numbers of the
+  //      upper fiber levels are kept (the segment scans below overwrite seg[]) ----
+  tb_ = w.tempBytes;
+  HIP_TRY(rocprim::inclusive_scan(w.temp, tb_,
+                                  rocprim::make_transform_iterator(cit, SingleFlag<Key>{K, sp.shift[sp.NF], M}),
+                                  w.sgScan, M, rocprim::plus<uint32_t>(), st), "scan");
+  for (int f = 0; f + 1 < sp.NF; ++f)
+    HIP_TRY(hipMemcpyAsync(w.nat[f], seg[f], M * 4, hipMemcpyDeviceToDevice, st), "hipMemcpyAsync");
+  // ---- groups, and where every slice starts inside its group ----
+  hipLaunchKernelGGL(classify_kernel, dim3(grid_capped(S)), dim3(256), 0, st, w.n.sStart, seg[0], seg[1], seg[2], S, sp,
+                     w.sgScan, w.grp, mb.cnt);
+  tb_ = w.tempBytes;
+  HIP_TRY(rocprim::exclusive_scan(w.temp, tb_,
+                                  rocprim::make_transform_iterator(cit, SliceIn{w.grp, w.n.sStart, S, w.sgScan}),
+                                  w.c6, C6{{0, 0, 0}, {0, 0, 0}}, S + 1, C6Plus(), st), "scan");
+  tb = Tables{sidp, w.n.sStart, w.grp, w.c6, w.sgScan, {nullptr, nullptr}, {nullptr, nullptr}};
+  // the first nonzero of every upper-level fiber that stays in the CSF group, then the fibers that stay
+  for (int f = 0; f + 1 < sp.NF; ++f) {
+    tb.nat[f] = w.nat[f];
+    hipLaunchKernelGGL(fill_words_kernel, dim3(grid_for(M + 1)), dim3(256), 0, st, w.firstKept[f], M + 1, 0xffffffffu);
+  }
+  if (sp.NF >= 2)
+    hipLaunchKernelGGL(first_kept_kernel, dim3(grid_for(M)), dim3(256), 0, st, M, tb, w.firstKept[0],
+                       sp.NF >= 3 ? w.firstKept[1] : nullptr);
+  for (int f = 0; f + 1 < sp.NF; ++f) tb.firstKept[f] = w.firstKept[f];
+  hipLaunchKernelGGL(count_kept_fibers_kernel<Key>, dim3(grid_capped(M)), dim3(256), 0, st, K, M, sp, tb, mb.cnt);
+  // ---- fiber segments of the CSF group: numbered by a scan over the sorted order ----
+  for (int f = 0; f < sp.NF; ++f) {
     tb_ = w.tempBytes;
     HIP_TRY(rocprim::exclusive_scan(w.temp, tb_,
-                                    rocprim::make_transform_iterator(cit, SliceIn{w.grp, w.sStart, S, w.sgScan}),
-                                    w.c6, C6{{0, 0, 0}, {0, 0, 0}}, S + 1, C6Plus(), st), "scan");
-    tb = Tables{sidp, w.sStart, w.grp, w.c6, sp.perFiber ? w.sgScan : nullptr, {nullptr, nullptr}, {nullptr, nullptr}};
-    if (sp.perFiber) {
-      // the first nonzero of every upper-level fiber that stays in the CSF group, then the fibers that stay
-      for (int f = 0; f + 1 < sp.NF; ++f) {
-        tb.nat[f] = w.nat[f];
-        hipLaunchKernelGGL(fill_words_kernel, dim3(grid_for(M + 1)), dim3(256), 0, st, w.firstKept[f], M + 1, 0xffffffffu);
-      }
-      if (sp.NF >= 2)
-        hipLaunchKernelGGL(first_kept_kernel, dim3(grid_for(M)), dim3(256), 0, st, M, tb, w.firstKept[0],
-                           sp.NF >= 3 ? w.firstKept[1] : nullptr);
-      for (int f = 0; f + 1 < sp.NF; ++f) tb.firstKept[f] = w.firstKept[f];
-      hipLaunchKernelGGL(count_kept_fibers_kernel<Key>, dim3(grid_capped(M)), dim3(256), 0, st, K, M, sp, tb, w.cnt);
-    }
-    // ---- fiber segments of the CSF group: numbered by a scan over the sorted order ----
-    for (int f = 0; f < sp.NF; ++f) {
-      tb_ = w.tempBytes;
-      HIP_TRY(rocprim::exclusive_scan(w.temp, tb_,
-                                      rocprim::make_transform_iterator(
-                                          cit, SegFlag<Key>{K, sp.shift[1 + f], tb, sp.L, M, f + 1 < sp.NF ? f : -1}),
-                                      seg[f], 0u, M + 1, rocprim::plus<uint32_t>(), st), "scan");
-    }
-    C6 totals{};
-    uint32_t segTotal[3] = {0, 0, 0};
-    HIP_TRY(hipMemcpyAsync(&totals, w.c6 + S, sizeof(C6), hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-    for (int f = 0; f < sp.NF; ++f)
-      HIP_TRY(hipMemcpyAsync(&segTotal[f], seg[f] + M, 4, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-    HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
-    for (int g = 0; g < 3; ++g) {
-      gS[g] = totals.s[g];
-      gM[g] = totals.m[g];
-    }
-    nSeg[0] = segTotal[0];
-    nSeg[1] = segTotal[1];
-    nSeg[2] = segTotal[2];
+                                    rocprim::make_transform_iterator(
+                                        cit, SegFlag<Key>{K, sp.shift[1 + f], tb, sp.L, M, f + 1 < sp.NF ? f : -1}),
+                                    seg[f], 0u, M + 1, rocprim::plus<uint32_t>(), st), "scan");
   }
+  C6 totals{};
+  uint32_t segTotal[3] = {0, 0, 0};
+  unsigned long long kept[kCounters];
+  HIP_TRY(hipMemcpyAsync(&totals, w.c6 + S, sizeof(C6), hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
+  for (int f = 0; f < sp.NF; ++f)
+    HIP_TRY(hipMemcpyAsync(&segTotal[f], seg[f] + M, 4, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
+  HIP_TRY(hipMemcpyAsync(kept, mb.cnt, sizeof(kept), hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
+  HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
+  for (int g = 0; g < 3; ++g) {
+    mb.gS[g] = totals.s[g];
+    mb.gM[g] = totals.m[g];
+  }
+  const int place[3] = {2, 3, 5};
+  for (int f = 0; f < 3; ++f) {
+    mb.nSeg[f] = segTotal[f];
+    mb.fibCsf[f] = kept[place[f]];
+  }
+  return HBCSF_OK;
+}
 
+// Builds one mode from its sorted nonzeros: sizes, layout, fill.  The statistics that need counters are left in mb.cnt.
+template <typename Key>
+int build_mode_device(int N, const uint64_t* dims, size_t M, uint64_t slices, const Sorted<Key>& so, ModeBuild& mb, Workspace& w,
+                      uint8_t* arena, uint64_t arenaBytes, uint64_t* arenaUsed, ModeFormat* out, hipStream_t st) {
+  const Spec& sp = mb.sp;
+  Tables tb{};
+  uint32_t* seg[3] = {nullptr, nullptr, nullptr};
+  if (M > 0) {
+    const int rn = sp.perFiber ? number_mode_per_fiber(M, so, mb, w, &tb, seg, st) : number_mode(M, slices, so, mb, w, st);
+    if (rn != HBCSF_OK) return rn;
+  }
   // ---- layout, then fill ----
-  layout_mode(out, N, gS, gM, nSeg);
+  layout_mode(out, N, mb.gS, mb.gM, mb.nSeg);
   if (*arenaUsed + out->blobBytes > arenaBytes) return fail(HBCSF_ENOMEM, "device arena is too small for the format");
   out->devOffset = *arenaUsed;
   uint8_t* base = arena + out->devOffset;
@@ -785,18 +1333,30 @@ int build_mode_device(int N, const uint64_t* dims, size_t M, const uint32_t* con
   o.owned = U32(out->ownedBits);
   o.cooBits = U32(out->cooBits);
   const size_t ownedWords = (out->rows + 31) / 32;
-  hipLaunchKernelGGL(zero_words_kernel, dim3(grid_for(ownedWords)), dim3(256), 0, st, o.owned, ownedWords);
-  hipLaunchKernelGGL(zero_words_kernel, dim3(grid_for(ownedWords)), dim3(256), 0, st, o.cooBits, ownedWords);
+  // row maps: the groups that exist, their levels one after the other
+  uint64_t mapBytes = 0;
   for (int g = 0; g < 3; ++g)
-    for (int l = 1; l < N; ++l) o.seen[g][l] = w.bitmap + (size_t)(g * (HBCSF_MAX_ORDER - 1) + (l - 1)) * w.bitmapWords;
+    for (int l = 1; l < N; ++l) {
+      o.seen[g][l] = (uint32_t*)(w.seen + mapBytes);
+      if (out->g[g].nnz > 0) mapBytes += row_map_bytes(dims[out->levelMode[l]]);
+    }
   {
-    const size_t all = (size_t)3 * (HBCSF_MAX_ORDER - 1) * w.bitmapWords;
-    hipLaunchKernelGGL(zero_words_kernel, dim3(grid_for(all)), dim3(256), 0, st, w.bitmap, all);
+    const size_t mapWords = (size_t)(mapBytes / 4);
+    hipLaunchKernelGGL(zero_words_kernel, dim3(grid_capped(mapWords + 2 * ownedWords)), dim3(256), 0, st, (uint32_t*)w.seen,
+                       mapWords, o.owned, ownedWords, o.cooBits, ownedWords);
   }
-  if (M > 0) {
-    hipLaunchKernelGGL(fill_nonzeros_kernel<Key>, dim3(grid_for(M)), dim3(256), 0, st, K, V, M, sp, tb, seg[0], seg[1],
+  if (M > 0 && sp.perFiber) {
+    hipLaunchKernelGGL(fill_nonzeros_kernel<Key>, dim3(grid_for(M)), dim3(256), 0, st, so.K, so.V, M, sp, tb, seg[0], seg[1],
                        seg[2], o);
-    hipLaunchKernelGGL(fill_slices_kernel<Key>, dim3(grid_capped(S)), dim3(256), 0, st, K, S, sp, tb, o, w.cnt);
+    hipLaunchKernelGGL(fill_slices_kernel<Key>, dim3(grid_capped(mb.S)), dim3(256), 0, st, so.K, mb.S, sp, tb, o, mb.cnt);
+  } else if (M > 0) {
+    const uint32_t tiles = (uint32_t)((M + kTile - 1) / kTile);
+    const dim3 grid(tiles / 4 + 1);
+    if (N == 3) hipLaunchKernelGGL((fill_tiles_kernel<Key, 3>), grid, dim3(256), 0, st, so.K, so.V, M, sp, tiles, w.n, o);
+    else if (N == 4) hipLaunchKernelGGL((fill_tiles_kernel<Key, 4>), grid, dim3(256), 0, st, so.K, so.V, M, sp, tiles, w.n, o);
+    else hipLaunchKernelGGL((fill_tiles_kernel<Key, 5>), grid, dim3(256), 0, st, so.K, so.V, M, sp, tiles, w.n, o);
+    hipLaunchKernelGGL(fill_slice_entries_kernel<Key>, dim3(grid_capped(mb.S)), dim3(256), 0, st, so.K, (uint32_t)mb.S, sp,
+                       w.n, o, mb.cnt);
   }
   Sentinels z{};
   z.cslN0 = out->g[kCsl].n[0];
@@ -808,28 +1368,127 @@ int build_mode_device(int N, const uint64_t* dims, size_t M, const uint32_t* con
   hipLaunchKernelGGL(sentinel_kernel, dim3(1), dim3(64), 0, st, sp, o, z);
   {
     size_t tb_ = w.tempBytes;
+    auto cit = rocprim::counting_iterator<size_t>(0);
     HIP_TRY(rocprim::exclusive_scan(w.temp, tb_, rocprim::make_transform_iterator(cit, PopcIn{o.cooBits, ownedWords}),
                                     U32(out->cooPtr), 0u, ownedWords + 1, rocprim::plus<uint32_t>(), st), "scan");
   }
 
   // ---- statistics that need a pass: rows owned by a plain store, distinct factor rows per group and level ----
-  hipLaunchKernelGGL(count_bits_kernel, dim3(grid_capped(ownedWords)), dim3(256), 0, st, o.owned, ownedWords, w.cnt + 4);
+  BitCounts bc{};
+  int which = 0;
+  auto count = [&](const uint32_t* map, size_t words, int to) {
+    bc.map[which] = map;
+    bc.words[which] = words;
+    bc.to[which++] = to;
+  };
+  count(o.owned, ownedWords, 4);
   for (int g = 0; g < 3; ++g)
-    for (int l = 1; l < N; ++l) {
-      if (out->g[g].nnz == 0) continue;
-      const size_t words = (dims[lv[l]] + 31) / 32;
-      hipLaunchKernelGGL(count_bits_kernel, dim3(grid_capped(words)), dim3(256), 0, st, o.seen[g][l], words,
-                         w.cnt + 8 + g * HBCSF_MAX_ORDER + l);
-    }
+    for (int l = 1; l < N; ++l)
+      if (out->g[g].nnz > 0) count(o.seen[g][l], (size_t)(row_map_bytes(dims[out->levelMode[l]]) / 4), 8 + g * HBCSF_MAX_ORDER + l);
+  size_t most = 0;
+  for (int k = 0; k < which; ++k) most = bc.words[k] > most ? bc.words[k] : most;
+  const unsigned bx = grid_capped((most + 15) / 16);
+  hipLaunchKernelGGL(count_bits_kernel, dim3(bx, (unsigned)which), dim3(256), 0, st, bc, mb.cnt);
   HIP_TRY(hipGetLastError(), "format kernels");
-  HIP_TRY(hipMemcpyAsync(hostCnt, w.cnt, kCounters * 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
+  return HBCSF_OK;
+}
+
+// All modes of one key type.
+template <typename Key>
+int build_all(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds, const float* vals, const hbcsf_opts& opts,
+              int totalBits, Workspace& w, uint8_t* arena, uint64_t arenaBytes, uint64_t* arenaUsed,
+              hbcsf_tensor* t, hipStream_t st) {
+  const auto t_begin = std::chrono::steady_clock::now();
+  const int nModes = t->single ? 1 : N;  // single representation: only mode 0's tree is stored
+  // the common order: the list every mode's levels below the root follow (with one mode to build, that mode's own order)
+  int order[HBCSF_MAX_ORDER];
+  level_order(N, dims, 0, opts.mode_order_policy, order);
+  if (!t->single) {
+    // mode 0 goes where the policy puts it among the others
+    int at = 0;
+    while (at + 1 < N) {
+      const uint64_t next = dims[order[at + 1]];
+      const bool before = opts.mode_order_policy == 0 ? next < dims[0] : opts.mode_order_policy == 1 && next > dims[0];
+      if (!before) break;
+      order[at] = order[at + 1];
+      order[++at] = 0;
+    }
+  }
+  BaseKey bk{};
+  for (int l = N - 1, at = 0; l >= 0; --l) {
+    const int m = order[l], b = bits_for(dims[m]);
+    bk.shift[m] = at;
+    bk.mask[m] = (1ull << b) - 1;
+    bk.dims[m] = dims[m];
+    at += b;
+  }
+  const int counters = HBCSF_MAX_ORDER * kCounters;
+  hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(256), 0, st, (uint32_t*)w.cnt, (size_t)counters * 2, (uint32_t*)w.bad,
+                     (size_t)2, (uint32_t*)nullptr, (size_t)0);
+  Sorted<Key> base;
+  if (M > 0) {
+    const int rs = sort_base<Key>(N, M, inds, vals, bk, totalBits, w, &base, st);
+    if (rs != HBCSF_OK) return rs;
+  }
+  ModeBuild mbs[HBCSF_MAX_ORDER];
+  for (int mode = 0; mode < nModes; ++mode) {
+    ModeBuild& mb = mbs[mode];
+    ModeFormat* out = t->modes[mode].get();
+    Spec& sp = mb.sp;
+    sp.N = N;
+    sp.NF = N - 2;
+    sp.L = opts.fiber_threshold;
+    const uint32_t gmask = opts.group_mask == 0 ? 3u : (opts.group_mask & 3u);
+    sp.blockBits = mid_block_bits(N, dims, opts, mode);
+    sp.cooOn = (gmask & 1u) && sp.blockBits == 0 ? 1u : 0u;   // with blocking no piece owns its row
+    sp.cslOn = (gmask & 2u) ? 1u : 0u;
+    sp.cooRowFlags = opts.coo_row_flags == 1 ? 1u : 0u;
+    sp.perFiber = per_fiber(opts) ? 1u : 0u;
+    int lv[HBCSF_MAX_ORDER];
+    level_order(N, dims, mode, opts.mode_order_policy, lv);
+    int at = 0;
+    for (int l = N - 1; l >= 0; --l) {
+      const int b = bits_for(dims[lv[l]]);
+      sp.shift[l] = at;
+      sp.mask[l] = (1ull << b) - 1;
+      if (dims[lv[l]] <= kByteRows) sp.byteLevels |= 1u << l;
+      at += b;
+      mb.mk.from[l] = bk.shift[lv[l]];
+    }
+    sp.blockShift = at;
+    sp.blockDrop = sp.blockBits ? bits_for(dims[lv[1]]) - sp.blockBits : 0;
+    mb.keyBits = at + sp.blockBits;
+    mb.cnt = w.cnt + (size_t)mode * kCounters;
+    out->order = N;
+    out->mode = mode;
+    out->L = sp.L;
+    out->blockBits = sp.blockBits;
+    out->cooRowFlags = sp.cooRowFlags != 0;
+    out->rows = dims[mode];
+    for (int l = 0; l < N; ++l) out->levelMode[l] = lv[l];
+    Sorted<Key> so;
+    if (M > 0) {
+      const int rs = sort_mode<Key>(M, base, mb, mode == order[0] && sp.blockBits == 0, w, &so, st);
+      if (rs != HBCSF_OK) return rs;
+    }
+    const int rb = build_mode_device<Key>(N, dims, M, slice_bound(M, dims[mode], sp.blockBits != 0), so, mb, w, arena, arenaBytes,
+                                          arenaUsed, out, st);
+    if (rb != HBCSF_OK) return rb;
+  }
+  unsigned long long host[HBCSF_MAX_ORDER * kCounters];
+  HIP_TRY(hipMemcpyAsync(host, w.cnt, sizeof(host), hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
   HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
-  const uint64_t fibNatCsf[HBCSF_MAX_FIBER_LEVELS] = {hostCnt[2], hostCnt[3], hostCnt[5]};
-  fill_count_stats(out, N, M, S, fibNat, fibNatCsf, nSeg, gS, gM, hostCnt[1]);
-  out->stats.owned_rows = hostCnt[4];
-  for (int g = 0; g < 3; ++g)
-    for (int l = 1; l < N; ++l) out->stats.distinct_rows[g][l] = hostCnt[8 + g * HBCSF_MAX_ORDER + l];
-  out->stats.build_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_begin).count();
+  const double seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_begin).count();
+  for (int mode = 0; mode < nModes; ++mode) {
+    const ModeBuild& mb = mbs[mode];
+    const unsigned long long* c = host + (size_t)mode * kCounters;
+    ModeFormat* out = t->modes[mode].get();
+    fill_count_stats(out, N, M, mb.S, mb.fibNat, mb.fibCsf, mb.nSeg, mb.gS, mb.gM, c[1]);
+    out->stats.owned_rows = c[4];
+    for (int g = 0; g < 3; ++g)
+      for (int l = 1; l < N; ++l) out->stats.distinct_rows[g][l] = c[8 + g * HBCSF_MAX_ORDER + l];
+    out->stats.build_seconds = seconds / nModes;
+  }
   return HBCSF_OK;
 }
 
@@ -847,9 +1506,11 @@ int hbcsf_device_build_bytes(int order, const uint64_t* dims, uint64_t nnz, cons
   uint64_t maxDim = 0;
   for (int m = 0; m < order; ++m) maxDim = dims[m] > maxDim ? dims[m] : maxDim;
   size_t tbytes = 0;
-  HIP_TRY(temp_bytes((size_t)nnz, (size_t)((maxDim + 31) / 32), maxBits, &tbytes), "rocPRIM scratch query");
+  const uint64_t slices = slice_bound((size_t)nnz, maxDim, o.mid_blocking > 1);
+  HIP_TRY(temp_bytes((size_t)nnz, (size_t)((maxDim + 31) / 32), slices, o.fiber_threshold, maxBits, &tbytes),
+          "rocPRIM scratch query");
   Workspace w{};
-  carve(w, nullptr, order, (size_t)nnz, maxDim, tbytes, maxBits > 64, o.hybrid_granularity == 1);
+  carve(w, nullptr, order, (size_t)nnz, row_maps_bytes(order, dims), slices, o.fiber_threshold, tbytes, maxBits > 64, per_fiber(o));
   *workspace_bytes = w.total;
   *arena_bytes = arena_bound(order, dims, nnz, o.fiber_threshold);
   return HBCSF_OK;
@@ -874,9 +1535,12 @@ int hbcsf_build_format_device(int order, const uint64_t* dims, uint64_t nnz, con
   uint64_t maxDim = 0;
   for (int m = 0; m < order; ++m) maxDim = dims[m] > maxDim ? dims[m] : maxDim;
   size_t tbytes = 0;
-  HIP_TRY(temp_bytes((size_t)nnz, (size_t)((maxDim + 31) / 32), maxBits, &tbytes), "rocPRIM scratch query");
+  const uint64_t slices = slice_bound((size_t)nnz, maxDim, o.mid_blocking > 1);
+  HIP_TRY(temp_bytes((size_t)nnz, (size_t)((maxDim + 31) / 32), slices, o.fiber_threshold, maxBits, &tbytes),
+          "rocPRIM scratch query");
   Workspace w{};
-  carve(w, (uint8_t*)workspace, order, (size_t)nnz, maxDim, tbytes, maxBits > 64, o.hybrid_granularity == 1);
+  carve(w, (uint8_t*)workspace, order, (size_t)nnz, row_maps_bytes(order, dims), slices, o.fiber_threshold, tbytes, maxBits > 64,
+        per_fiber(o));
   if (workspace_bytes < w.total) return fail(HBCSF_ENOMEM, "workspace is smaller than hbcsf_device_build_bytes");
 
   std::unique_ptr<hbcsf_tensor> t(new (std::nothrow) hbcsf_tensor);
@@ -892,17 +1556,15 @@ int hbcsf_build_format_device(int order, const uint64_t* dims, uint64_t nnz, con
   t->numCU = cu > 0 ? cu : 256;
   uint64_t used = 0;
   t->single = o.single_representation == 1;
-  for (int m = 0; m < (t->single ? 1 : order); ++m) {  // single representation: only mode 0's tree is stored
+  for (int m = 0; m < (t->single ? 1 : order); ++m) {
     t->modes[m].reset(new (std::nothrow) ModeFormat);
     if (!t->modes[m]) return fail(HBCSF_ENOMEM, "out of host memory");
-    const int modeBits = totalBits + mid_block_bits(order, dims, o, m);   // this mode's key width
-    const int rb = modeBits > 64
-                       ? build_mode_device<u128>(order, dims, (size_t)nnz, inds, vals, o, m, modeBits, w,
-                                                 (uint8_t*)device_arena, arena_bytes, &used, t->modes[m].get(), st)
-                       : build_mode_device<uint64_t>(order, dims, (size_t)nnz, inds, vals, o, m, modeBits, w,
-                                                     (uint8_t*)device_arena, arena_bytes, &used, t->modes[m].get(), st);
-    if (rb != HBCSF_OK) return rb;
   }
+  const int rb = maxBits > 64 ? build_all<u128>(order, dims, (size_t)nnz, inds, vals, o, totalBits, w,
+                                                (uint8_t*)device_arena, arena_bytes, &used, t.get(), st)
+                              : build_all<uint64_t>(order, dims, (size_t)nnz, inds, vals, o, totalBits, w,
+                                                    (uint8_t*)device_arena, arena_bytes, &used, t.get(), st);
+  if (rb != HBCSF_OK) return rb;
   double sq = 0.0;
   if (nnz > 0) {
     size_t tb_ = w.tempBytes;
