@@ -176,17 +176,20 @@ int hbcsf_build_format(int order, const uint64_t* dims, uint64_t nnz, const uint
   t->opts = o;
   t->sliceThreshold = o.slice_threshold;
   for (int m = 0; m < order; ++m) t->dims[m] = dims[m];
-  double sq = 0.0;
-  for (uint64_t z = 0; z < nnz; ++z) sq += (double)vals[z] * (double)vals[z];
-  t->normSq = sq;
+  t->normSq = sum_of_squares(vals, nnz);
   t->single = o.single_representation == 1;
-  uint64_t off = 0;
-  for (int m = 0; m < (t->single ? 1 : order); ++m) {
+  const int nModes = t->single ? 1 : order;
+  ModeFormat* formats[HBCSF_MAX_ORDER];
+  for (int m = 0; m < nModes; ++m) {
     t->modes[m].reset(new (std::nothrow) ModeFormat);
     if (!t->modes[m]) return fail(HBCSF_ENOMEM, "out of host memory");
-    std::string err;
-    const int rc = build_mode(order, dims, nnz, inds, vals, o, m, t->modes[m].get(), &err);
-    if (rc != HBCSF_OK) return fail(rc, err);
+    formats[m] = t->modes[m].get();
+  }
+  std::string err;
+  const int rc = build_modes(order, dims, nnz, inds, vals, o, nModes, formats, &err);
+  if (rc != HBCSF_OK) return fail(rc, err);
+  uint64_t off = 0;
+  for (int m = 0; m < nModes; ++m) {
     t->modes[m]->devOffset = off;
     off += t->modes[m]->blobBytes;
   }

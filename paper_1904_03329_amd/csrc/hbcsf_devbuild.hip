@@ -1402,18 +1402,7 @@ int build_all(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds
   const int nModes = t->single ? 1 : N;  // single representation: only mode 0's tree is stored
   // the common order: the list every mode's levels below the root follow (with one mode to build, that mode's own order)
   int order[HBCSF_MAX_ORDER];
-  level_order(N, dims, 0, opts.mode_order_policy, order);
-  if (!t->single) {
-    // mode 0 goes where the policy puts it among the others
-    int at = 0;
-    while (at + 1 < N) {
-      const uint64_t next = dims[order[at + 1]];
-      const bool before = opts.mode_order_policy == 0 ? next < dims[0] : opts.mode_order_policy == 1 && next > dims[0];
-      if (!before) break;
-      order[at] = order[at + 1];
-      order[++at] = 0;
-    }
-  }
+  common_order(N, dims, opts.mode_order_policy, t->single, order);
   BaseKey bk{};
   for (int l = N - 1, at = 0; l >= 0; --l) {
     const int m = order[l], b = bits_for(dims[m]);

@@ -1,7 +1,9 @@
 // Host-side format builder: COO -> per-mode HB-CSF (Sections III-B, IV, V).
 //
 // For the root mode n the nonzeros are sorted by (root, middle level(s), leaf) index, which
-// gives the compressed-sparse-fiber tree (Section III-B).  Each slice is then put into one of
+// gives the compressed-sparse-fiber tree (Section III-B).  The levels below the root follow one list of modes
+// whatever the root is, so the nonzeros are sorted by that list once and every mode's order is one stable sort
+// of the result by the mode's own index.  Each slice is then put into one of
 // three groups (Section V and Section VI-D: one nonzero -> COO; every fiber a single nonzero
 // -> CSL; otherwise CSF).  Inside the CSL and CSF groups the group's nonzero stream is cut
 // into runs of T_f nonzeros: a fiber is cut wherever it crosses a run boundary (fbr-split,
@@ -22,18 +24,25 @@
 namespace hbcsf {
 namespace {
 
-// Stable parallel LSD radix sort of (key, payload) pairs on the low `totalBits` bits.
+// Chunks to cut n items into for the threads: not so small that a parallel region costs more than it saves.
+int chunks_for(size_t n) {
+  const size_t most = n / 8192 + 1;
+  const int nt = omp_get_max_threads();
+  return (size_t)nt < most ? nt : (int)most;
+}
+
+// Stable parallel LSD radix sort of (key, payload) pairs on key bits fromBit .. fromBit + totalBits - 1.
 // On return k / v point at the sorted data (either the first or the second buffer pair).
 template <typename Key>
-void radix_sort_pairs(Key*& k, uint32_t*& v, Key*& k2, uint32_t*& v2, size_t n, int totalBits) {
+void radix_sort_pairs(Key*& k, uint32_t*& v, Key*& k2, uint32_t*& v2, size_t n, int fromBit, int totalBits) {
   if (n < 2 || totalBits <= 0) return;
   const int passes = (totalBits + 11) / 12;
   const int digit = (totalBits + passes - 1) / passes;
   const size_t buckets = (size_t)1 << digit;
-  const int nt = omp_get_max_threads();
+  const int nt = chunks_for(n);
   std::vector<size_t> hist((size_t)nt * buckets);
   for (int pass = 0; pass < passes; ++pass) {
-    const int shift = pass * digit;
+    const int shift = fromBit + pass * digit;
     std::fill(hist.begin(), hist.end(), 0);
     const Key* src = k;
     const uint32_t* srcv = v;
@@ -41,7 +50,7 @@ void radix_sort_pairs(Key*& k, uint32_t*& v, Key*& k2, uint32_t*& v2, size_t n, 
     uint32_t* dstv = v2;
     // The data is cut into nt chunks and the loops run over chunk numbers, so the result does not depend on how
     // many threads the runtime really grants.
-#pragma omp parallel
+#pragma omp parallel num_threads(nt)
     {
 #pragma omp for schedule(static, 1)
       for (int c = 0; c < nt; ++c) {
@@ -75,10 +84,91 @@ void radix_sort_pairs(Key*& k, uint32_t*& v, Key*& k2, uint32_t*& v2, size_t n, 
   }
 }
 
+// Where the bits of each tree level lie in a packed (root, ..., leaf) key.
+struct KeyLayout {
+  int lv[HBCSF_MAX_ORDER];     // mode of each level
+  int shift[HBCSF_MAX_ORDER];  // by level
+  uint64_t mask[HBCSF_MAX_ORDER];
+  int total;
+};
+
+KeyLayout key_layout(int N, const uint64_t* dims, const int* lv) {
+  KeyLayout k{};
+  for (int l = N - 1; l >= 0; --l) {
+    const int b = bits_for(dims[lv[l]]);
+    k.lv[l] = lv[l];
+    k.shift[l] = k.total;
+    k.mask[l] = (1ull << b) - 1;
+    k.total += b;
+  }
+  return k;
+}
+
+// The nonzeros in the common order, and two buffer pairs in which one mode after the other is sorted.
 template <typename Key>
-int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* const* inds,
-                 const float* vals, const hbcsf_opts& opts, int mode, ModeFormat* out,
-                 std::string* err) {
+struct Sorted {
+  std::unique_ptr<Key[]> key[3];
+  std::unique_ptr<uint32_t[]> val[3];
+  Key* K = nullptr;  // the common order: one of the three buffers
+  uint32_t* V = nullptr;
+  KeyLayout at;
+  int spare[2];      // the other two buffers
+
+  bool alloc(int i, size_t M) {
+    if (!key[i]) key[i].reset(new (std::nothrow) Key[M + 1]);
+    if (!val[i]) val[i].reset(new (std::nothrow) uint32_t[M + 1]);
+    return key[i] && val[i];
+  }
+};
+
+template <typename Key>
+int sort_common(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds, const float* vals,
+                const KeyLayout& at, Sorted<Key>* so, std::string* err) {
+  so->at = at;
+  if (!so->alloc(0, M) || !so->alloc(1, M)) {
+    *err = "out of host memory while sorting";
+    return HBCSF_ENOMEM;
+  }
+  Key* K = so->key[0].get();
+  Key* K2 = so->key[1].get();
+  uint32_t* V = so->val[0].get();
+  uint32_t* V2 = so->val[1].get();
+  const int nt = chunks_for(M);
+  int bad = 0;
+  int unsorted = 0;
+#pragma omp parallel for schedule(static) reduction(| : bad) num_threads(nt)
+  for (int64_t z = 0; z < (int64_t)M; ++z) {
+    Key key = 0;
+    for (int l = 0; l < N; ++l) {
+      const uint32_t i = inds[at.lv[l]][z];
+      if ((uint64_t)i >= dims[at.lv[l]]) bad |= 1;
+      key |= (Key)i << at.shift[l];
+    }
+    K[z] = key;
+    uint32_t vb;
+    std::memcpy(&vb, &vals[z], 4);
+    V[z] = vb;
+  }
+  if (bad) {
+    *err = "an index is not below its dimension";
+    return HBCSF_ERANGE;
+  }
+#pragma omp parallel for schedule(static) reduction(| : unsorted) num_threads(nt)
+  for (int64_t z = 1; z < (int64_t)M; ++z)
+    if (K[z] < K[z - 1]) unsorted |= 1;
+  if (unsorted) radix_sort_pairs<Key>(K, V, K2, V2, M, 0, at.total);
+  so->K = K;
+  so->V = V;
+  const int common = K == so->key[0].get() ? 0 : 1;
+  so->spare[0] = 1 - common;
+  so->spare[1] = 2;
+  return HBCSF_OK;
+}
+
+// One mode's representation from the common order.
+template <typename Key>
+int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, Sorted<Key>& so, const hbcsf_opts& opts, int mode,
+                 ModeFormat* out, std::string* err) {
   const auto t_begin = std::chrono::steady_clock::now();
   const int N = order;
   const uint32_t L = opts.fiber_threshold ? opts.fiber_threshold : 64;
@@ -89,15 +179,9 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* 
   // Tree levels: root = the target mode; the other modes ordered by the policy.
   int lv[HBCSF_MAX_ORDER];
   level_order(N, dims, mode, opts.mode_order_policy, lv);
-  int bits[HBCSF_MAX_ORDER], shift[HBCSF_MAX_ORDER];
-  uint64_t mask[HBCSF_MAX_ORDER];
-  int total = 0;
-  for (int l = N - 1; l >= 0; --l) {
-    bits[l] = bits_for(dims[lv[l]]);
-    shift[l] = total;
-    mask[l] = (1ull << bits[l]) - 1;
-    total += bits[l];
-  }
+  const KeyLayout kl = key_layout(N, dims, lv);
+  const int* shift = kl.shift;
+  const uint64_t* mask = kl.mask;
 
   out->order = N;
   out->mode = mode;
@@ -107,68 +191,79 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* 
   out->rows = dims[mode];
   for (int l = 0; l < N; ++l) out->levelMode[l] = lv[l];
 
-  // ---- sort by packed (root, ..., leaf) key; the value rides along as payload ----
+  // ---- this mode's order: a stable sort of the common one by (block,) root; the value rides along as payload ----
   const size_t M = (size_t)nnz;
-  std::unique_ptr<Key[]> kbuf1(new (std::nothrow) Key[M + 1]), kbuf2(new (std::nothrow) Key[M + 1]);
-  std::unique_ptr<uint32_t[]> vbuf1(new (std::nothrow) uint32_t[M + 1]), vbuf2(new (std::nothrow) uint32_t[M + 1]);
-  if (!kbuf1 || !kbuf2 || !vbuf1 || !vbuf2) {
-    *err = "out of host memory while sorting";
-    return HBCSF_ENOMEM;
-  }
-  Key* K = kbuf1.get();
-  Key* K2 = kbuf2.get();
-  uint32_t* V = vbuf1.get();
-  uint32_t* V2 = vbuf2.get();
-  int bad = 0;
-  int unsorted = 0;
-#pragma omp parallel for schedule(static) reduction(| : bad)
-  for (int64_t z = 0; z < (int64_t)M; ++z) {
-    Key key = 0;
-    for (int l = 0; l < N; ++l) {
-      const uint32_t i = inds[lv[l]][z];
-      if ((uint64_t)i >= dims[lv[l]]) bad |= 1;
-      key |= (Key)i << shift[l];
+  const int nt = chunks_for(M);
+  Key* K = so.K;
+  uint32_t* V = so.V;
+  if (mode != so.at.lv[0] || bb != 0) {
+    if (!so.alloc(so.spare[0], M) || !so.alloc(so.spare[1], M)) {
+      *err = "out of host memory while sorting";
+      return HBCSF_ENOMEM;
     }
-    if (bb) key |= (Key)(inds[lv[1]][z] >> (bits[1] - bb)) << total;
-    K[z] = key;
-    uint32_t vb;
-    std::memcpy(&vb, &vals[z], 4);
-    V[z] = vb;
+    K = so.key[so.spare[0]].get();
+    V = so.val[so.spare[0]].get();
+    Key* K2 = so.key[so.spare[1]].get();
+    uint32_t* V2 = so.val[so.spare[1]].get();
+    int from[HBCSF_MAX_ORDER];
+    for (int l = 0; l < N; ++l)
+      for (int c = 0; c < N; ++c)
+        if (so.at.lv[c] == lv[l]) from[l] = so.at.shift[c];
+    const int drop = bb ? bits_for(dims[lv[1]]) - bb : 0;
+#pragma omp parallel for schedule(static) num_threads(nt)
+    for (int64_t z = 0; z < (int64_t)M; ++z) {
+      const Key c = so.K[z];
+      Key key = 0;
+      for (int l = 0; l < N; ++l) {
+        const uint64_t i = (uint64_t)(c >> from[l]) & mask[l];
+        key |= (Key)i << shift[l];
+        if (l == 1 && bb) key |= (Key)(i >> drop) << kl.total;
+      }
+      K[z] = key;
+      V[z] = so.V[z];
+    }
+    radix_sort_pairs<Key>(K, V, K2, V2, M, shift[0], kl.total - shift[0] + bb);
   }
-  if (bad) {
-    *err = "an index is not below its dimension";
-    return HBCSF_ERANGE;
-  }
-#pragma omp parallel for schedule(static) reduction(| : unsorted)
-  for (int64_t z = 1; z < (int64_t)M; ++z)
-    if (K[z] < K[z - 1]) unsorted |= 1;
-  if (unsorted) radix_sort_pairs<Key>(K, V, K2, V2, M, total + bb);
-  if (K == kbuf1.get()) { kbuf2.reset(); vbuf2.reset(); } else { kbuf1.reset(); vbuf1.reset(); }
 
   auto idx = [&](int l, size_t p) -> uint32_t { return (uint32_t)((uint64_t)(K[p] >> shift[l]) & mask[l]); };
   auto fresh = [&](int l, size_t p) -> bool { return p == 0 || (K[p] >> shift[l]) != (K[p - 1] >> shift[l]); };
 
   // ---- slices ----
-  const int nt = omp_get_max_threads();
-  std::vector<uint64_t> tcount(nt + 1, 0);
-#pragma omp parallel for schedule(static, 1)
+  const int NF = N - 2;  // fiber levels 1..NF
+  std::vector<uint64_t> tcount[HBCSF_MAX_ORDER - 1];  // by level: slices, then fibers, before each chunk
+  for (int l = 0; l <= NF; ++l) tcount[l].assign(nt + 1, 0);
+#pragma omp parallel for schedule(static, 1) num_threads(nt)
   for (int t = 0; t < nt; ++t) {  // chunk numbers, not thread numbers: any team size gives the same result
     const size_t lo = M * (size_t)t / nt, hi = M * (size_t)(t + 1) / nt;
-    uint64_t c = 0;
-    for (size_t p = lo; p < hi; ++p) c += fresh(0, p);
-    tcount[t + 1] = c;
+    uint64_t c[HBCSF_MAX_ORDER - 1] = {};
+    for (size_t p = lo; p < hi; ++p) {
+      const Key x = p == 0 ? ~(Key)0 : K[p] ^ K[p - 1];  // fresh() of all levels from one difference
+      for (int l = 0; l <= NF; ++l) c[l] += (x >> shift[l]) != 0;
+    }
+    for (int l = 0; l <= NF; ++l) tcount[l][t + 1] = c[l];
   }
-  for (int t = 0; t < nt; ++t) tcount[t + 1] += tcount[t];
-  const uint64_t S = tcount[nt];
+  for (int l = 0; l <= NF; ++l)
+    for (int t = 0; t < nt; ++t) tcount[l][t + 1] += tcount[l][t];
+  const uint64_t S = tcount[0][nt];
   std::vector<uint32_t> sStart(S + 1);
-#pragma omp parallel for schedule(static, 1)
+  std::vector<uint32_t> fStart[HBCSF_MAX_FIBER_LEVELS];  // fibers of each level before every slice
+  for (int f = 0; f < NF; ++f) fStart[f].resize(S + 1);
+#pragma omp parallel for schedule(static, 1) num_threads(nt)
   for (int t = 0; t < nt; ++t) {
     const size_t lo = M * (size_t)t / nt, hi = M * (size_t)(t + 1) / nt;
-    uint64_t at = tcount[t];
-    for (size_t p = lo; p < hi; ++p)
-      if (fresh(0, p)) sStart[at++] = (uint32_t)p;
+    uint64_t c[HBCSF_MAX_ORDER - 1] = {};
+    for (int l = 0; l <= NF; ++l) c[l] = tcount[l][t];
+    for (size_t p = lo; p < hi; ++p) {
+      const Key x = p == 0 ? ~(Key)0 : K[p] ^ K[p - 1];
+      if ((x >> shift[0]) != 0) {
+        for (int f = 0; f < NF; ++f) fStart[f][c[0]] = (uint32_t)c[1 + f];
+        sStart[c[0]] = (uint32_t)p;
+      }
+      for (int l = 0; l <= NF; ++l) c[l] += (x >> shift[l]) != 0;
+    }
   }
   sStart[S] = (uint32_t)M;
+  for (int f = 0; f < NF; ++f) fStart[f][S] = (uint32_t)tcount[1 + f][nt];
 
   // ---- classify slices (Section V; Section VI-D) ----
   // Per slice (the paper's rule): one nonzero -> COO; every deepest-level fiber a singleton -> CSL; else CSF.
@@ -176,7 +271,6 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* 
   // nonzeros (it spans several runs, so its row is merged with atomic adds anyway) of which at least an eighth
   // sit in singleton deepest-level fibers is split: those nonzeros form a CSL-group slice of the same root index,
   // the others a CSF-group slice; both pieces are marked shared.
-  const int NF = N - 2;  // fiber levels 1..NF
   const bool perFiber = opts.hybrid_granularity == 1 && cslOn;
   // a nonzero whose deepest-level fiber holds only itself
   auto single = [&](size_t p, size_t e) -> bool { return fresh(NF, p) && (p + 1 == e || fresh(NF, p + 1)); };
@@ -188,12 +282,11 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* 
   uint64_t fibNatCsf[kFL] = {0, 0, 0};
   {
     uint64_t f0 = 0, f1 = 0, f2 = 0, c0 = 0, c1 = 0, c2 = 0;
-#pragma omp parallel for schedule(dynamic, 512) reduction(+ : f0, f1, f2, c0, c1, c2)
+#pragma omp parallel for schedule(dynamic, 64) reduction(+ : f0, f1, f2, c0, c1, c2) num_threads(nt)
     for (int64_t s = 0; s < (int64_t)S; ++s) {
       const size_t b = sStart[s], e = sStart[s + 1];
       uint64_t nf[kFL] = {0, 0, 0};
-      for (size_t p = b; p < e; ++p)
-        for (int f = 0; f < NF; ++f) nf[f] += fresh(f + 1, p);
+      for (int f = 0; f < NF; ++f) nf[f] = fStart[f][s + 1] - fStart[f][s];
       const uint64_t n = e - b, deep = nf[NF - 1];
       uint8_t g;
       if (n == 1 && cooOn) g = kCoo;
@@ -253,18 +346,53 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* 
     gM[g] += n;
   }
 
+  // ---- pieces: at most kPiece nonzeros of one slice each ----
+  // (a slice of a power-law tensor holds up to a fifth of all nonzeros; as one item it was the whole loop's time.)
+  // A split slice is one piece: what it has kept so far decides the places.  A thread takes the pieces that begin in one
+  // of `parts` equal ranges of the nonzeros.
+  constexpr size_t kPiece = 4096;
+  std::vector<uint64_t> pieceAt(S + 1);  // first piece of every slice
+  pieceAt[0] = 0;
+  for (uint64_t s = 0; s < S; ++s) {
+    const size_t n = sStart[s + 1] - sStart[s];
+    pieceAt[s + 1] = pieceAt[s] + (grp[s] == kSplit ? 1 : (n + kPiece - 1) / kPiece);
+  }
+  const uint64_t P = pieceAt[S];
+  struct Piece {
+    uint32_t s, b, e;
+  };
+  std::vector<Piece> piece(P);
+#pragma omp parallel for schedule(static) num_threads(nt)
+  for (int64_t s = 0; s < (int64_t)S; ++s) {
+    const size_t e = sStart[s + 1];
+    size_t b = sStart[s];
+    for (uint64_t q = pieceAt[s]; q < pieceAt[s + 1]; ++q) {
+      const size_t pe = q + 1 == pieceAt[s + 1] ? e : b + kPiece;
+      piece[q] = Piece{(uint32_t)s, (uint32_t)b, (uint32_t)pe};
+      b = pe;
+    }
+  }
+
+  const int parts = nt > 1 ? nt * 8 : 1;
+  auto piece_at = [&](int part) -> int64_t {  // first piece that begins at or behind the part's first nonzero
+    const size_t z = part == parts ? M : M * (size_t)part / parts;
+    return std::lower_bound(piece.begin(), piece.end(), z, [](const Piece& x, size_t at) { return x.b < at; }) - piece.begin();
+  };
+
   // ---- count fiber segments of the CSF group (fbr-split on the run grid) ----
   // A segment starts at a kept nonzero that lies on the run grid or is the first kept one of its fiber.
-  std::vector<uint32_t> segOff[kFL];
+  std::vector<uint32_t> segOff[kFL];  // by piece
   uint64_t nSeg[kFL] = {0, 0, 0};
-  for (int f = 0; f < NF; ++f) segOff[f].assign(S + 1, 0);
-#pragma omp parallel for schedule(dynamic, 512)
-  for (int64_t s = 0; s < (int64_t)S; ++s) {
+  for (int f = 0; f < NF; ++f) segOff[f].assign(P + 1, 0);
+#pragma omp parallel for schedule(dynamic, 1) num_threads(nt)
+  for (int part = 0; part < parts; ++part)
+  for (int64_t q = piece_at(part), qEnd = piece_at(part + 1); q < qEnd; ++q) {
+    const uint32_t s = piece[q].s;
     if (grp[s] != kCsf && grp[s] != kSplit) continue;
-    const size_t b = sStart[s], e = sStart[s + 1];
+    const size_t b = piece[q].b, e = piece[q].e;
     const bool split = grp[s] == kSplit;
     uint32_t c[kFL] = {0, 0, 0};
-    uint32_t pos = off[s];
+    uint32_t pos = off[s] + (uint32_t)(b - sStart[s]);
     bool pend[kFL] = {false, false, false};
     for (size_t p = b; p < e; ++p) {
       for (int f = 0; f < NF; ++f) pend[f] = pend[f] || fresh(f + 1, p);
@@ -276,16 +404,16 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* 
       }
       ++pos;
     }
-    for (int f = 0; f < NF; ++f) segOff[f][s + 1] = c[f];
+    for (int f = 0; f < NF; ++f) segOff[f][q + 1] = c[f];
   }
   for (int f = 0; f < NF; ++f) {
     uint64_t run = 0;
-    for (uint64_t s = 0; s < S; ++s) {
-      const uint32_t c = segOff[f][s + 1];
-      segOff[f][s] = (uint32_t)run;
+    for (uint64_t q = 0; q < P; ++q) {
+      const uint32_t c = segOff[f][q + 1];
+      segOff[f][q] = (uint32_t)run;
       run += c;
     }
-    segOff[f][S] = (uint32_t)run;
+    segOff[f][P] = (uint32_t)run;
     nSeg[f] = run;
   }
 
@@ -326,9 +454,13 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* 
   uint32_t* cslRun = U32(Gl.runFirst[0]);
 
   uint64_t sharedSlices = 0;
-#pragma omp parallel for schedule(dynamic, 512) reduction(+ : sharedSlices)
-  for (int64_t s = 0; s < (int64_t)S; ++s) {
-    const size_t b = sStart[s], e = sStart[s + 1];
+#pragma omp parallel for schedule(dynamic, 1) reduction(+ : sharedSlices) num_threads(nt)
+  for (int part = 0; part < parts; ++part)
+  for (int64_t q = piece_at(part), qEnd = piece_at(part + 1); q < qEnd; ++q) {
+    const uint32_t s = piece[q].s;
+    const size_t b = piece[q].b, e = piece[q].e;
+    const size_t sb = sStart[s], se = sStart[s + 1];
+    const bool first = b == sb;  // the slice's own entries go with its first piece
     const uint32_t root = idx(0, b);
     const int g = grp[s];
     bool own = true;
@@ -342,12 +474,14 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* 
       // the CSL piece (a whole CSL slice, or the singleton-fiber nonzeros of a split slice)
       if (g == kCsl || split) {
         const uint32_t a = split ? offL[s] : off[s], o = split ? ordL[s] : ord[s];
-        const uint32_t n = split ? nSingle[s] : (uint32_t)(e - b);
+        const uint32_t n = split ? nSingle[s] : (uint32_t)(se - sb);
         own = !split && bb == 0 && (a / L) == ((a + n - 1) / L);
-        for (uint32_t r = (a + L - 1) / L; r <= (a + n - 1) / L; ++r) cslRun[r] = o;
-        cslInd[0][o] = root | (own ? kOwnedBit : 0u);
-        cslPtr[o] = a;
-        uint32_t pos = a;
+        if (first) {
+          for (uint32_t r = (a + L - 1) / L; r <= (a + n - 1) / L; ++r) cslRun[r] = o;
+          cslInd[0][o] = root | (own ? kOwnedBit : 0u);
+          cslPtr[o] = a;
+        }
+        uint32_t pos = a + (uint32_t)(b - sb);
         for (size_t p = b; p < e; ++p) {
           if (split && !single(p, e)) continue;
           for (int l = 1; l < N; ++l) cslInd[l][pos] = idx(l, p);
@@ -358,17 +492,19 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* 
       // the CSF piece
       if (g == kCsf || split) {
         const uint32_t a = off[s], o = ord[s];
-        const uint32_t n = split ? (uint32_t)(e - b) - nSingle[s] : (uint32_t)(e - b);
+        const uint32_t n = split ? (uint32_t)(se - sb) - nSingle[s] : (uint32_t)(se - sb);
         own = !split && bb == 0 && (a / L) == ((a + n - 1) / L);
-        for (uint32_t r = (a + L - 1) / L; r <= (a + n - 1) / L; ++r) csfRun[0][r] = o;
-        csfInd[0][o] = root | (own ? kOwnedBit : 0u);
-        csfPtr[0][o] = a;
+        if (first) {
+          for (uint32_t r = (a + L - 1) / L; r <= (a + n - 1) / L; ++r) csfRun[0][r] = o;
+          csfInd[0][o] = root | (own ? kOwnedBit : 0u);
+          csfPtr[0][o] = a;
+        }
         uint32_t f[kFL] = {0, 0, 0};
-        for (int q = 0; q < NF; ++q) f[q] = segOff[q][s];
-        uint32_t pos = a;
+        for (int k = 0; k < NF; ++k) f[k] = segOff[k][q];
+        uint32_t pos = a + (uint32_t)(b - sb);
         bool pend[kFL] = {false, false, false};
         for (size_t p = b; p < e; ++p) {
-          for (int q = 0; q < NF; ++q) pend[q] = pend[q] || fresh(q + 1, p);
+          for (int k = 0; k < NF; ++k) pend[k] = pend[k] || fresh(k + 1, p);
           if (split && single(p, e)) continue;
           const bool cut = (pos % L) == 0;
           for (int l = 1; l <= NF; ++l) {
@@ -385,9 +521,9 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* 
           ++pos;
         }
       }
-      if (!own) ++sharedSlices;
+      if (!own && first) ++sharedSlices;
     }
-    if (own) __atomic_fetch_or(&owned[root >> 5], 1u << (root & 31), __ATOMIC_RELAXED);
+    if (own && first) __atomic_fetch_or(&owned[root >> 5], 1u << (root & 31), __ATOMIC_RELAXED);
   }
   {
     // COO-group nonzeros are stored in row order, so a running count over the bitmap locates them
@@ -414,7 +550,7 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* 
   hbcsf_stats& st = out->stats;
   {
     uint64_t cnt = 0;
-#pragma omp parallel for schedule(static) reduction(+ : cnt)
+#pragma omp parallel for schedule(static) reduction(+ : cnt) num_threads(nt)
     for (int64_t w = 0; w < (int64_t)ownedWords; ++w) cnt += (uint64_t)__builtin_popcount(owned[w]);
     st.owned_rows = cnt;
   }
@@ -436,9 +572,12 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* 
         } else {
           seen.assign(dims[lv[l]], 0);
           uint8_t* sp = seen.data();
-#pragma omp parallel for schedule(static)
-          for (int64_t t = 0; t < (int64_t)cnt; ++t) __atomic_store_n(&sp[a[t]], (uint8_t)1, __ATOMIC_RELAXED);
-#pragma omp parallel for schedule(static) reduction(+ : d)
+          // looked at before it is written: a row that many nonzeros share would otherwise take its cache line from
+          // one thread to the next with every one of them
+#pragma omp parallel for schedule(static) num_threads(nt)
+          for (int64_t t = 0; t < (int64_t)cnt; ++t)
+            if (!__atomic_load_n(&sp[a[t]], __ATOMIC_RELAXED)) __atomic_store_n(&sp[a[t]], (uint8_t)1, __ATOMIC_RELAXED);
+#pragma omp parallel for schedule(static) reduction(+ : d) num_threads(nt)
           for (int64_t t = 0; t < (int64_t)seen.size(); ++t) d += sp[t];
         }
         st.distinct_rows[g][l] = d;
@@ -451,15 +590,54 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* 
 
 }  // namespace
 
-int build_mode(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* const* inds,
-               const float* vals, const hbcsf_opts& opts, int mode, ModeFormat* out,
-               std::string* err) {
-  int total = mid_block_bits(order, dims, opts, mode);
+namespace {
+
+template <typename Key>
+int build_modes_t(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* const* inds, const float* vals,
+                  const hbcsf_opts& opts, int modes, ModeFormat* const* out, std::string* err) {
+  int lv[HBCSF_MAX_ORDER];
+  common_order(order, dims, opts.mode_order_policy, modes == 1, lv);
+  Sorted<Key> so;
+  int rc = sort_common<Key>(order, dims, (size_t)nnz, inds, vals, key_layout(order, dims, lv), &so, err);
+  for (int m = 0; rc == HBCSF_OK && m < modes; ++m)
+    rc = build_mode_t<Key>(order, dims, nnz, so, opts, m, out[m], err);
+  return rc;
+}
+
+}  // namespace
+
+double sum_of_squares(const float* v, uint64_t n) {
+  constexpr uint64_t kBlock = 16384;
+  const int64_t blocks = (int64_t)((n + kBlock - 1) / kBlock);
+  std::vector<double> part((size_t)blocks);
+#pragma omp parallel for schedule(static) num_threads(chunks_for(n))
+  for (int64_t b = 0; b < blocks; ++b) {
+    const uint64_t lo = (uint64_t)b * kBlock, hi = lo + kBlock < n ? lo + kBlock : n;
+    double s[8] = {};  // one running sum alone would wait for its own last addition at every value
+    uint64_t z = lo;
+    for (; z + 8 <= hi; z += 8)
+      for (int k = 0; k < 8; ++k) s[k] += (double)v[z + k] * (double)v[z + k];
+    for (; z < hi; ++z) s[0] += (double)v[z] * (double)v[z];
+    part[(size_t)b] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+  }
+  double sum = 0.0;
+  for (int64_t b = 0; b < blocks; ++b) sum += part[(size_t)b];
+  return sum;
+}
+
+int build_modes(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* const* inds,
+                const float* vals, const hbcsf_opts& opts, int modes, ModeFormat* const* out,
+                std::string* err) {
+  int total = 0, blocks = 0;
   for (int m = 0; m < order; ++m) total += bits_for(dims[m]);
+  for (int m = 0; m < modes; ++m) {
+    const int b = mid_block_bits(order, dims, opts, m);
+    blocks = b > blocks ? b : blocks;
+  }
   try {
-    if (total <= 64)
-      return build_mode_t<uint64_t>(order, dims, nnz, inds, vals, opts, mode, out, err);
-    return build_mode_t<unsigned __int128>(order, dims, nnz, inds, vals, opts, mode, out, err);
+    if (total + blocks <= 64)
+      return build_modes_t<uint64_t>(order, dims, nnz, inds, vals, opts, modes, out, err);
+    return build_modes_t<unsigned __int128>(order, dims, nnz, inds, vals, opts, modes, out, err);
   } catch (const std::bad_alloc&) {
     *err = "out of host memory while building the format";
     return HBCSF_ENOMEM;

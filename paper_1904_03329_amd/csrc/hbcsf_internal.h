@@ -181,6 +181,20 @@ inline void level_order(int N, const uint64_t* dims, int mode, uint32_t policy, 
   for (int l = 1; l < N; ++l) lv[l] = rest[l - 1];
 }
 
+// The list of all modes that every mode's levels below the root follow (`onlyMode0`: mode 0's own levels): mode 0's
+// levels with mode 0 itself where the policy puts it among the others.
+inline void common_order(int N, const uint64_t* dims, uint32_t policy, bool onlyMode0, int order[HBCSF_MAX_ORDER]) {
+  level_order(N, dims, 0, policy, order);
+  if (onlyMode0) return;
+  for (int at = 0; at + 1 < N; ++at) {
+    const uint64_t next = dims[order[at + 1]];
+    const bool before = policy == 0 ? next < dims[0] : policy == 1 && next > dims[0];
+    if (!before) break;
+    order[at] = order[at + 1];
+    order[at + 1] = 0;
+  }
+}
+
 inline int bits_for(uint64_t dim) {
   int b = 1;
   while (b < 63 && (1ull << b) < dim) ++b;
@@ -204,10 +218,14 @@ inline int mid_block_bits(int N, const uint64_t* dims, const hbcsf_opts& opts, i
   return 0;
 }
 
-// Builds one mode's representation.  Returns HBCSF_OK or an error code and fills `err`.
-int build_mode(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* const* inds,
-               const float* vals, const hbcsf_opts& opts, int mode, ModeFormat* out,
-               std::string* err);
+// Sum of the squares of n values in fp64, in an order that depends on n alone.
+double sum_of_squares(const float* v, uint64_t n);
+
+// Builds the representations of modes 0 .. modes - 1 (all, or mode 0 alone).  Returns HBCSF_OK or an error code and
+// fills `err`.
+int build_modes(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* const* inds,
+                const float* vals, const hbcsf_opts& opts, int modes, ModeFormat* const* out,
+                std::string* err);
 
 }  // namespace hbcsf
 
