@@ -668,6 +668,16 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
   // marks in a per-unit list beside the records
   constexpr bool PACK = N == 4 && !DENSE;
   constexpr int RW = (N == 3 || PACK) ? 4 : 8;
+  // Order 3: a lane group moves the fiber marks of every kQueue steps together, without gaps, so that its k-th fiber end
+  // of them is loaded by the k-th instruction: as many load instructions as the most ends any lane group has there,
+  // instead of one per step in which some lane group has an end (at one end in five nonzeros and eight lane groups 1.9
+  // instead of 3.2 per four steps; the address unit takes as long for a load of one row as for one of eight).  The rows
+  // are used in that order: the first is always next, and an end moves the others up.  100 M nonzeros, all modes:
+  // 2302 -> 2212 us; with a third of the nonzeros ending a fiber (150 M) 9230 -> 9195 us, smaller tensors equal.  At
+  // order 4 nearly every step ends a deepest fiber, and the level above it gains nothing (2504 / 2517 us on 50 M).
+  constexpr bool QUEUE = N == 3 && !DENSE;
+  constexpr int kQueue = 4;
+  static_assert(kSteps % kQueue == 0, "whole queues");
   static_assert(!DENSE || N <= 4, "the dense fiber-row gather handles orders 3 and 4");
   extern __shared__ uint32_t lds[];
   const int lane = threadIdx.x & 63;
@@ -863,9 +873,26 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
         }
         // Conditional loads first: loads return in order, so once a leaf row has arrived every
         // load issued before it has arrived too, and the leaf rows can be awaited one by one.
+        if constexpr (QUEUE) {
+#pragma unroll
+          for (int b = 0; b < kSteps; b += kQueue) {
+            uint32_t q[kQueue] = {};
+#pragma unroll
+            for (int t = kQueue - 1; t >= 0; --t) {
+              const bool marked = rr[b + t].z != 0u;
+#pragma unroll
+              for (int k = kQueue - 1 - t; k > 0; --k) q[k] = marked ? q[k - 1] : q[k];
+              q[0] = marked ? rr[b + t].z : q[0];
+            }
+#pragma unroll
+            for (int k = 0; k < kQueue; ++k)
+              if (q[k]) br[b + k] = marked_row_load<G, WIDE>(markDeep, q[k], c, (a.streamLevel & (1u << (N - 2))) != 0u);
+          }
+        }
 #pragma unroll
         for (int t = 0; t < kSteps; ++t) {
-          if (rr[t].z) br[t] = marked_row_load<G, WIDE>(markDeep, rr[t].z, c, (a.streamLevel & (1u << (N - 2))) != 0u);
+          if (!QUEUE && rr[t].z)
+            br[t] = marked_row_load<G, WIDE>(markDeep, rr[t].z, c, (a.streamLevel & (1u << (N - 2))) != 0u);
           if (N >= 4 && rr[t].w)
             nr[t] = marked_row_load<G, WIDE>(markNext, rr[t].w, c, (a.streamLevel & (1u << (N - 3))) != 0u);
           if (N == 5 && m1[t]) ar[t] = marked_row_load<G, WIDE>(markTop, m1[t], c, (a.streamLevel & 2u) != 0u);
@@ -876,8 +903,11 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
         for (int t = 0; t < kSteps; ++t) {
           fma4(tmp, __uint_as_float(rr[t].y), cr[t]);
           if (rr[t].z) {
-            if (N == 3) {
-              fma4(acc, tmp, br[t]);
+            if (QUEUE) {
+              const int head = t / kQueue * kQueue;
+              fma4(acc, tmp, br[head]);
+#pragma unroll
+              for (int k = 0; k < kQueue - 1 - t % kQueue; ++k) br[head + k] = br[head + k + 1];
             } else {
               fma4(tmp1, tmp, br[t]);
               if (rr[t].w) {
