@@ -6,7 +6,9 @@
 //
 // Sorting.  Every mode's levels below the root keep the order of one list of all modes, so the nonzeros are sorted once
 // by that list and a mode's order is one stable sort of the result by the mode's own index alone: two or three radix
-// passes instead of a whole key's eight.
+// passes instead of a whole key's eight.  The keys keep the layout of the common order in every mode: the sort looks at
+// the root's bits where they lie, and "the index of some level or one above it changes" is a difference of two keys
+// under that level's mask (a pass that rewrote the keys as (root, ..., leaf) first took 0.23 ms of 50 M nonzeros).
 //
 // Numbering.  No array is kept per nonzero.  A wavefront takes 1024 sorted nonzeros, 64 at a time; "a slice / a fiber
 // begins here" are ballots, so what it needs to number them is the count before its tile (one scan over the tiles).
@@ -41,12 +43,13 @@ typedef unsigned __int128 u128;
 
 struct Spec {
   int N, NF;
-  int shift[HBCSF_MAX_ORDER];
+  int shift[HBCSF_MAX_ORDER];       // by level: where its index lies in the common key
   uint64_t mask[HBCSF_MAX_ORDER];
+  u128 upTo[HBCSF_MAX_ORDER];       // by level: the bits of it and of every level above, the block's among them
   uint32_t L, cooOn, cslOn, cooRowFlags;
   uint32_t byteLevels;  // bit l: level l's row map holds bytes, otherwise bits
   uint32_t perFiber;  // hybrid_granularity = 1: heavy slices are split into a CSL piece and a CSF piece
-  int blockBits, blockShift, blockDrop;  // level-1 blocking: (index of level 1 >> blockDrop) << blockShift tops the key
+  int blockBits, blockDrop;  // level-1 blocking: (index of level 1 >> blockDrop) stands above the root
 };
 
 struct C6 {  // running slice and nonzero counts of the three groups
@@ -77,12 +80,16 @@ struct Tables {
   const uint32_t* firstKept[2];  // by natural fiber of that level: its first nonzero that stays in the CSF group
 };
 
-// Is nonzero p the only one of its deepest-level fiber?  (shiftDeep: key shift of that level)
+// Does some index of the levels in `upTo` change at sorted nonzero p?
 template <typename Key>
-__device__ __forceinline__ bool single_at(const Key* K, size_t p, size_t M, int shiftDeep) {
-  const bool freshHere = p == 0 || (K[p] >> shiftDeep) != (K[p - 1] >> shiftDeep);
-  const bool freshNext = p + 1 == M || (K[p + 1] >> shiftDeep) != (K[p] >> shiftDeep);
-  return freshHere && freshNext;
+__device__ __forceinline__ bool fresh_at(const Key* K, size_t p, Key upTo) {
+  return p == 0 || ((K[p] ^ K[p - 1]) & upTo) != 0;
+}
+
+// Is nonzero p the only one of its deepest-level fiber?  (deep: the bits down to that level)
+template <typename Key>
+__device__ __forceinline__ bool single_at(const Key* K, size_t p, size_t M, Key deep) {
+  return fresh_at(K, p, deep) && (p + 1 == M || fresh_at(K, p + 1, deep));
 }
 
 // Group and position of sorted nonzero p.  In a split slice the singleton-fiber nonzeros go, in order, to the
@@ -110,26 +117,24 @@ __device__ __forceinline__ void locate(const Tables& t, size_t p, uint32_t& s, i
 template <typename Key>
 struct FreshFlag {  // 1 where the index at some tree level (and everything above it) changes
   const Key* K;
-  int shift;
-  __device__ uint32_t operator()(size_t p) const {
-    return (p == 0 || (K[p] >> shift) != (K[p - 1] >> shift)) ? 1u : 0u;
-  }
+  Key upTo;
+  __device__ uint32_t operator()(size_t p) const { return fresh_at(K, p, upTo) ? 1u : 0u; }
 };
 
-// Does a fiber of the CSF group start at nonzero p (of that group) at the level whose key shift is `shift`?  Without
+// Does a fiber of the CSF group start at nonzero p (of that group) at the level whose bits end `upTo`?  Without
 // the per-fiber choice: where the index at that level or above changes.  With it, nonzeros may have left the slice
 // for the CSL piece, so: where p is the first nonzero of its natural fiber that stayed (`upper` = 0 / 1 selects the
 // tables of fiber level 1 / 2; the deepest level needs none: a nonzero that left was a fiber of its own).
 template <typename Key>
-__device__ __forceinline__ bool fiber_starts(const Key* K, size_t p, int shift, const Tables& t, int upper) {
+__device__ __forceinline__ bool fiber_starts(const Key* K, size_t p, Key upTo, const Tables& t, int upper) {
   if (upper >= 0 && t.firstKept[upper]) return t.firstKept[upper][t.nat[upper][p] - 1u] == (uint32_t)p;
-  return p == 0 || (K[p] >> shift) != (K[p - 1] >> shift);
+  return fresh_at(K, p, upTo);
 }
 
 template <typename Key>
 struct SegFlag {  // 1 where a fiber segment of the CSF group starts
   const Key* K;
-  int shift;
+  Key upTo;
   Tables t;
   uint32_t L;
   size_t M;
@@ -140,16 +145,16 @@ struct SegFlag {  // 1 where a fiber segment of the CSF group starts
     int g;
     locate(t, p, s, g, pos);
     if (g != kCsf) return 0u;
-    return ((pos % L) == 0 || fiber_starts(K, p, shift, t, upper)) ? 1u : 0u;
+    return ((pos % L) == 0 || fiber_starts(K, p, upTo, t, upper)) ? 1u : 0u;
   }
 };
 
 template <typename Key>
 struct SingleFlag {  // 1 where a nonzero is the only one of its deepest-level fiber
   const Key* K;
-  int shiftDeep;
+  Key deep;
   size_t M;
-  __device__ uint32_t operator()(size_t p) const { return p < M && single_at(K, p, M, shiftDeep) ? 1u : 0u; }
+  __device__ uint32_t operator()(size_t p) const { return p < M && single_at(K, p, M, deep) ? 1u : 0u; }
 };
 
 struct SliceIn {  // what a slice adds to the running group counts
@@ -234,45 +239,22 @@ __global__ void pack_kernel(IndPtrs inds, const float* vals, size_t M, int N, Ba
   if (off) atomicOr(bad, 1ull);
 }
 
-// The key of one mode's representation from the key of the common order.
-struct ModeKey {
-  int from[HBCSF_MAX_ORDER];  // by level: shift in the common key
-};
-template <typename Key>
-__device__ __forceinline__ Key mode_key(Key base, const ModeKey& mk, const Spec& sp) {
-  Key key = 0;
-#pragma unroll
-  for (int l = 0; l < HBCSF_MAX_ORDER; ++l) {
-    if (l >= sp.N) break;
-    const uint64_t i = (uint64_t)(base >> mk.from[l]) & sp.mask[l];
-    key |= (Key)i << sp.shift[l];
-    if (l == 1 && sp.blockBits) key |= (Key)(i >> sp.blockDrop) << sp.blockShift;
-  }
-  return key;
-}
-
-__global__ void mode_key_kernel(const uint64_t* __restrict__ base, const uint32_t* __restrict__ baseV, size_t M, Spec sp,
-                                ModeKey mk, uint64_t* __restrict__ K, uint32_t* __restrict__ V) {
-  const size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= M) return;
-  K[p] = mode_key<uint64_t>(base[p], mk, sp);
-  V[p] = baseV[p];
-}
-
 // Wide keys: what is sorted is (block, root) with the place in the common order, then the rest is fetched.
-__global__ void root_key_kernel(const u128* __restrict__ base, size_t M, Spec sp, ModeKey mk, uint64_t* __restrict__ K,
+__global__ void root_key_kernel(const u128* __restrict__ base, size_t M, Spec sp, int rootBits, uint64_t* __restrict__ K,
                                 uint32_t* __restrict__ V) {
   const size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= M) return;
-  K[p] = (uint64_t)(mode_key<u128>(base[p], mk, sp) >> sp.shift[0]);
+  uint64_t key = (uint64_t)(base[p] >> sp.shift[0]) & sp.mask[0];
+  if (sp.blockBits) key |= (((uint64_t)(base[p] >> sp.shift[1]) & sp.mask[1]) >> sp.blockDrop) << rootBits;
+  K[p] = key;
   V[p] = (uint32_t)p;
 }
 __global__ void fetch_kernel(const u128* __restrict__ base, const uint32_t* __restrict__ baseV, const uint32_t* __restrict__ at,
-                             size_t M, Spec sp, ModeKey mk, u128* __restrict__ K, uint32_t* __restrict__ V) {
+                             size_t M, u128* __restrict__ K, uint32_t* __restrict__ V) {
   const size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= M) return;
   const uint32_t z = at[p];
-  K[p] = mode_key<u128>(base[z], mk, sp);
+  K[p] = base[z];
   V[p] = baseV[z];
 }
 
@@ -296,10 +278,10 @@ __global__ void join_halves_kernel(const uint64_t* hi, const Carried* car, size_
 
 // first nonzero of every slice, from the scanned slice numbers
 template <typename Key>
-__global__ void slice_start_kernel(const Key* K, const uint32_t* sidp, size_t M, int shift0, uint32_t* sStart) {
+__global__ void slice_start_kernel(const Key* K, const uint32_t* sidp, size_t M, Key upTo0, uint32_t* sStart) {
   const size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= M) return;
-  if (p == 0 || (K[p] >> shift0) != (K[p - 1] >> shift0)) sStart[sidp[p] - 1] = (uint32_t)p;
+  if (fresh_at(K, p, upTo0)) sStart[sidp[p] - 1] = (uint32_t)p;
   if (p == M - 1) sStart[sidp[p]] = (uint32_t)M;
 }
 
@@ -362,7 +344,7 @@ __global__ void count_kept_fibers_kernel(const Key* K, size_t M, Spec sp, Tables
     int g;
     locate(t, p, s, g, pos);
     if (g != kCsf) continue;
-    for (int l = 1; l <= sp.NF; ++l) c[l - 1] += fiber_starts(K, p, sp.shift[l], t, l < sp.NF ? l - 1 : -1) ? 1u : 0u;
+    for (int l = 1; l <= sp.NF; ++l) c[l - 1] += fiber_starts(K, p, (Key)sp.upTo[l], t, l < sp.NF ? l - 1 : -1) ? 1u : 0u;
   }
   wave_add(cnt + 2, c[0]);
   wave_add(cnt + 3, c[1]);
@@ -434,7 +416,7 @@ __global__ void fill_nonzeros_kernel(const Key* K, const uint32_t* V, size_t M, 
   o.csfVal[pos] = v;
   if (cut) o.csfRun[0][pos / sp.L] = ord;
   for (int l = 1; l <= sp.NF; ++l) {
-    const bool fresh = fiber_starts(K, p, sp.shift[l], t, l < sp.NF ? l - 1 : -1);
+    const bool fresh = fiber_starts(K, p, (Key)sp.upTo[l], t, l < sp.NF ? l - 1 : -1);
     if (cut || fresh) {
       const uint32_t id = (l == 1 ? seg0 : l == 2 ? seg1 : seg2)[p];
       o.csfInd[l][id] = idx[l];
@@ -537,7 +519,7 @@ __device__ __forceinline__ uint32_t begins(const Key* __restrict__ K, size_t p, 
   if (p == 0) return 15u;
   const Key x = K[p] ^ K[p - 1];
   uint32_t b = 0;
-  for (int l = 0; l <= sp.NF; ++l) b |= ((x >> sp.shift[l]) != 0 ? 1u : 0u) << l;
+  for (int l = 0; l <= sp.NF; ++l) b |= ((x & (Key)sp.upTo[l]) != 0 ? 1u : 0u) << l;
   return b;
 }
 
@@ -765,7 +747,7 @@ __global__ __launch_bounds__(256) void fill_tiles_kernel(const Key* __restrict__
     }
 #pragma unroll
     for (int q = 0; q < kFill; ++q) {
-      leafIdx[q] = (uint32_t)((uint64_t)key[q] & sp.mask[leaf]);
+      leafIdx[q] = (uint32_t)((uint64_t)(key[q] >> sp.shift[leaf]) & sp.mask[leaf]);
     }
 #pragma unroll
     for (int q = 0; q < kFill; ++q) {
@@ -886,8 +868,9 @@ inline uint64_t up256(uint64_t v) { return (v + 255) / 256 * 256; }
 
 // Workspace carve-up for M nonzeros; `temp` is the rocPRIM scratch, sized by temp_bytes().
 struct Workspace {
-  uint64_t* K[3];        // 64-bit sort keys: the common order and a double buffer (wide keys: two are used)
-  uint32_t* V[3];        // values (or places) riding along
+  uint64_t* K[3];        // 64-bit sort keys.  Up to 64 bits: [2] the common order, [0] one mode's order, [1] where a
+  uint32_t* V[3];        // blocked order or the per-fiber choice needs it; wide keys: [0], [1] a double buffer.  V: the
+                         // values (or places) riding along
   Carried* C[2];         // wide keys only: the other half + value, double buffered
   u128* K128[2];         // wide keys only: the common order, one mode's order
   Numbers n;             // numbering tables
@@ -928,17 +911,21 @@ hipError_t temp_bytes(size_t M, size_t maxWords, uint64_t slices, uint32_t L, in
   // the largest scratch any rocPRIM call below asks for
   size_t need = 0, b = 0;
   hipError_t e;
-  rocprim::double_buffer<uint64_t> kb((uint64_t*)nullptr, (uint64_t*)nullptr);
-  rocprim::double_buffer<uint32_t> vb((uint32_t*)nullptr, (uint32_t*)nullptr);
-  e = rocprim::radix_sort_pairs(nullptr, b, kb, vb, M, 0u, (unsigned)(wide ? 64 : totalBits));
-  if (e != hipSuccess) return e;
-  need = b > need ? b : need;
   if (wide) {
-    rocprim::double_buffer<Carried> cb((Carried*)nullptr, (Carried*)nullptr);
-    e = rocprim::radix_sort_pairs(nullptr, b, kb, cb, M, 0u, 64u);
+    rocprim::double_buffer<uint64_t> kb((uint64_t*)nullptr, (uint64_t*)nullptr);
+    rocprim::double_buffer<uint32_t> vb((uint32_t*)nullptr, (uint32_t*)nullptr);
+    e = rocprim::radix_sort_pairs(nullptr, b, kb, vb, M, 0u, 64u);
     if (e != hipSuccess) return e;
     need = b > need ? b : need;
+    rocprim::double_buffer<Carried> cb((Carried*)nullptr, (Carried*)nullptr);
+    e = rocprim::radix_sort_pairs(nullptr, b, kb, cb, M, 0u, 64u);
+  } else {
+    // (the most any range of bits takes: with more than one pass the scratch holds a second copy of the pairs)
+    e = rocprim::radix_sort_pairs(nullptr, b, (const uint64_t*)nullptr, (uint64_t*)nullptr, (const uint32_t*)nullptr,
+                                  (uint32_t*)nullptr, M, 0u, 64u);
   }
+  if (e != hipSuccess) return e;
+  need = b > need ? b : need;
   const size_t runs = M / L + 2, tiles = M / kTile + 2;
   e = rocprim::exclusive_scan(nullptr, b, (Count4*)nullptr, (Count4*)nullptr, Count4{}, runs > tiles ? runs : tiles, Count4Plus());
   if (e != hipSuccess) return e;
@@ -977,15 +964,16 @@ hipError_t temp_bytes(size_t M, size_t maxWords, uint64_t slices, uint32_t L, in
 }
 
 void carve(Workspace& w, uint8_t* base, int order, size_t M, uint64_t mapBytes, uint64_t slices, uint32_t L, size_t tempBytes,
-           bool wide, bool perFiber) {
+           bool wide, bool perFiber, bool blocked) {
   uint64_t off = 0;
   auto take = [&](uint64_t bytes) {
     uint8_t* p = base ? base + off : nullptr;
     off += up256(bytes);
     return p;
   };
-  for (int i = 0; i < 3; ++i) w.K[i] = wide && i == 2 ? nullptr : (uint64_t*)take((M + 1) * 8);
-  for (int i = 0; i < 3; ++i) w.V[i] = (uint32_t*)take((M + 1) * 4);
+  for (int i = 0; i < 3; ++i)
+    w.K[i] = (wide ? i < 2 : i != 1 || perFiber || blocked) ? (uint64_t*)take((M + 1) * 8) : nullptr;
+  for (int i = 0; i < 3; ++i) w.V[i] = wide || i != 1 || perFiber || blocked ? (uint32_t*)take((M + 1) * 4) : nullptr;
   for (int i = 0; i < 2; ++i) w.C[i] = wide ? (Carried*)take((M + 1) * sizeof(Carried)) : nullptr;
   for (int i = 0; i < 2; ++i) w.K128[i] = wide ? (u128*)take((M + 1) * 16) : nullptr;
   const uint64_t tables = perFiber ? (uint64_t)M : slices;
@@ -1076,8 +1064,7 @@ int check_args(int order, const uint64_t* dims, uint64_t nnz, const hbcsf_opts* 
 // What one mode's build needs to know, and what it leaves for the end.
 struct ModeBuild {
   Spec sp{};
-  ModeKey mk{};
-  int keyBits = 0;   // of this mode's key, block bits included
+  int rootBits = 0;
   uint64_t S = 0, gS[3] = {0, 0, 0}, gM[3] = {0, 0, 0};
   uint64_t nSeg[HBCSF_MAX_FIBER_LEVELS] = {0, 0, 0}, fibNat[HBCSF_MAX_FIBER_LEVELS] = {0, 0, 0};
   uint64_t fibCsf[HBCSF_MAX_FIBER_LEVELS] = {0, 0, 0};
@@ -1102,24 +1089,15 @@ int sort_base(int N, size_t M, const uint32_t* const* inds, const float* vals, c
   IndPtrs ip{};
   for (int m = 0; m < N; ++m) ip.p[m] = inds[m];
   hipLaunchKernelGGL(pack_kernel<Key>, dim3(grid_for(M)), dim3(256), 0, st, ip, vals, M, N, bk, w.K[0], w.V[0], w.C[0], w.bad);
-  rocprim::double_buffer<uint64_t> kb(w.K[0], w.K[1]);
   size_t tb = w.tempBytes;
   if constexpr (!kWide) {
-    rocprim::double_buffer<uint32_t> vb(w.V[0], w.V[1]);
-    HIP_TRY(rocprim::radix_sort_pairs(w.temp, tb, kb, vb, M, 0u, (unsigned)totalBits, st), "radix sort");
-    base->K = kb.current();
-    base->V = vb.current();
-    // from here on the sorted keys are buffer 2, the two others the double buffer of the modes' sorts
-    uint64_t* k = kb.current() == w.K[0] ? w.K[0] : w.K[1];
-    uint32_t* v = vb.current() == w.V[0] ? w.V[0] : w.V[1];
-    uint64_t* k2 = w.K[2];
-    uint32_t* v2 = w.V[2];
-    w.K[2] = k;
-    w.V[2] = v;
-    (k == w.K[0] ? w.K[0] : w.K[1]) = k2;
-    (v == w.V[0] ? w.V[0] : w.V[1]) = v2;
+    HIP_TRY(rocprim::radix_sort_pairs(w.temp, tb, (const uint64_t*)w.K[0], w.K[2], (const uint32_t*)w.V[0], w.V[2], M, 0u,
+                                      (unsigned)totalBits, st), "radix sort");
+    base->K = w.K[2];
+    base->V = w.V[2];
   } else {
     // two stable passes: by the low 64 bits with the high half riding along, then by the high bits
+    rocprim::double_buffer<uint64_t> kb(w.K[0], w.K[1]);
     rocprim::double_buffer<Carried> cb(w.C[0], w.C[1]);
     HIP_TRY(rocprim::radix_sort_pairs(w.temp, tb, kb, cb, M, 0u, 64u, st), "radix sort");
     hipLaunchKernelGGL(swap_halves_kernel, dim3(grid_for(M)), dim3(256), 0, st, kb.current(), cb.current(), M,
@@ -1142,27 +1120,40 @@ int sort_base(int N, size_t M, const uint32_t* const* inds, const float* vals, c
 template <typename Key>
 int sort_mode(size_t M, const Sorted<Key>& base, const ModeBuild& mb, bool isBase, Workspace& w, Sorted<Key>* out, hipStream_t st) {
   constexpr bool kWide = sizeof(Key) == 16;
-  if (isBase) {
-    *out = base;
-    out->freeKeys = w.K[0];
-    out->freeVals = w.V[0];
-    return HBCSF_OK;
-  }
-  rocprim::double_buffer<uint64_t> kb(w.K[0], w.K[1]);
-  rocprim::double_buffer<uint32_t> vb(w.V[0], w.V[1]);
   size_t tb = w.tempBytes;
   if constexpr (!kWide) {
-    hipLaunchKernelGGL(mode_key_kernel, dim3(grid_for(M)), dim3(256), 0, st, base.K, base.V, M, mb.sp, mb.mk, w.K[0], w.V[0]);
-    HIP_TRY(rocprim::radix_sort_pairs(w.temp, tb, kb, vb, M, (unsigned)mb.sp.shift[0], (unsigned)mb.keyBits, st), "radix sort");
-    out->K = kb.current();
-    out->V = vb.current();
-    out->freeKeys = kb.alternate();
-    out->freeVals = vb.alternate();
+    out->freeKeys = w.K[1];
+    out->freeVals = w.V[1];
+    out->K = base.K;
+    out->V = base.V;
+    if (isBase) return HBCSF_OK;
+    const Spec& sp = mb.sp;
+    // by root, then (blocked modes) by block: the top bits of the level-1 index
+    uint64_t* k = w.K[sp.blockBits ? 1 : 0];
+    uint32_t* v = w.V[sp.blockBits ? 1 : 0];
+    HIP_TRY(rocprim::radix_sort_pairs(w.temp, tb, base.K, k, base.V, v, M, (unsigned)sp.shift[0],
+                                      (unsigned)(sp.shift[0] + mb.rootBits), st), "radix sort");
+    if (sp.blockBits) {
+      const unsigned from = (unsigned)(sp.shift[1] + sp.blockDrop);
+      tb = w.tempBytes;
+      HIP_TRY(rocprim::radix_sort_pairs(w.temp, tb, (const uint64_t*)k, w.K[0], (const uint32_t*)v, w.V[0], M, from,
+                                        from + (unsigned)sp.blockBits, st), "radix sort");
+    }
+    out->K = w.K[0];
+    out->V = w.V[0];
   } else {
-    hipLaunchKernelGGL(root_key_kernel, dim3(grid_for(M)), dim3(256), 0, st, base.K, M, mb.sp, mb.mk, w.K[0], w.V[0]);
-    HIP_TRY(rocprim::radix_sort_pairs(w.temp, tb, kb, vb, M, 0u, (unsigned)(mb.keyBits - mb.sp.shift[0]), st), "radix sort");
-    hipLaunchKernelGGL(fetch_kernel, dim3(grid_for(M)), dim3(256), 0, st, base.K, base.V, vb.current(), M, mb.sp, mb.mk,
-                       w.K128[1], vb.alternate());
+    if (isBase) {
+      *out = base;
+      out->freeKeys = w.K[0];
+      out->freeVals = w.V[0];
+      return HBCSF_OK;
+    }
+    rocprim::double_buffer<uint64_t> kb(w.K[0], w.K[1]);
+    rocprim::double_buffer<uint32_t> vb(w.V[0], w.V[1]);
+    hipLaunchKernelGGL(root_key_kernel, dim3(grid_for(M)), dim3(256), 0, st, base.K, M, mb.sp, mb.rootBits, w.K[0], w.V[0]);
+    HIP_TRY(rocprim::radix_sort_pairs(w.temp, tb, kb, vb, M, 0u, (unsigned)(mb.rootBits + mb.sp.blockBits), st), "radix sort");
+    hipLaunchKernelGGL(fetch_kernel, dim3(grid_for(M)), dim3(256), 0, st, base.K, base.V, vb.current(), M, w.K128[1],
+                       vb.alternate());
     out->K = w.K128[1];
     out->V = vb.alternate();
     out->freeKeys = kb.current();
@@ -1224,13 +1215,13 @@ int number_mode_per_fiber(size_t M, const Sorted<Key>& so, ModeBuild& mb, Worksp
   auto cit = rocprim::counting_iterator<size_t>(0);
   // ---- slices: scan of "root index changes" ----
   size_t tb_ = w.tempBytes;
-  HIP_TRY(rocprim::inclusive_scan(w.temp, tb_, rocprim::make_transform_iterator(cit, FreshFlag<Key>{K, sp.shift[0]}),
+  HIP_TRY(rocprim::inclusive_scan(w.temp, tb_, rocprim::make_transform_iterator(cit, FreshFlag<Key>{K, (Key)sp.upTo[0]}),
                                   sidp, M, rocprim::plus<uint32_t>(), st), "scan");
-  hipLaunchKernelGGL(slice_start_kernel<Key>, dim3(grid_for(M)), dim3(256), 0, st, K, sidp, M, sp.shift[0], w.n.sStart);
+  hipLaunchKernelGGL(slice_start_kernel<Key>, dim3(grid_for(M)), dim3(256), 0, st, K, sidp, M, (Key)sp.upTo[0], w.n.sStart);
   // natural fibers per level (the deepest level decides CSL membership)
   for (int f = 0; f < sp.NF; ++f) {
     tb_ = w.tempBytes;
-    HIP_TRY(rocprim::inclusive_scan(w.temp, tb_, rocprim::make_transform_iterator(cit, FreshFlag<Key>{K, sp.shift[1 + f]}),
+    HIP_TRY(rocprim::inclusive_scan(w.temp, tb_, rocprim::make_transform_iterator(cit, FreshFlag<Key>{K, (Key)sp.upTo[1 + f]}),
                                     seg[f], M, rocprim::plus<uint32_t>(), st), "scan");
   }
   uint32_t tail[4] = {0, 0, 0, 0};
@@ -1249,7 +1240,7 @@ int number_mode_per_fiber(size_t M, const Sorted<Key>& so, ModeBuild& mb, Worksp
   //      upper fiber levels are kept (the segment scans below overwrite seg[]) ----
   tb_ = w.tempBytes;
   HIP_TRY(rocprim::inclusive_scan(w.temp, tb_,
-                                  rocprim::make_transform_iterator(cit, SingleFlag<Key>{K, sp.shift[sp.NF], M}),
+                                  rocprim::make_transform_iterator(cit, SingleFlag<Key>{K, (Key)sp.upTo[sp.NF], M}),
                                   w.sgScan, M, rocprim::plus<uint32_t>(), st), "scan");
   for (int f = 0; f + 1 < sp.NF; ++f)
     HIP_TRY(hipMemcpyAsync(w.nat[f], seg[f], M * 4, hipMemcpyDeviceToDevice, st), "hipMemcpyAsync");
@@ -1276,7 +1267,7 @@ int number_mode_per_fiber(size_t M, const Sorted<Key>& so, ModeBuild& mb, Worksp
     tb_ = w.tempBytes;
     HIP_TRY(rocprim::exclusive_scan(w.temp, tb_,
                                     rocprim::make_transform_iterator(
-                                        cit, SegFlag<Key>{K, sp.shift[1 + f], tb, sp.L, M, f + 1 < sp.NF ? f : -1}),
+                                        cit, SegFlag<Key>{K, (Key)sp.upTo[1 + f], tb, sp.L, M, f + 1 < sp.NF ? f : -1}),
                                     seg[f], 0u, M + 1, rocprim::plus<uint32_t>(), st), "scan");
   }
   C6 totals{};
@@ -1435,18 +1426,17 @@ int build_all(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds
     sp.perFiber = per_fiber(opts) ? 1u : 0u;
     int lv[HBCSF_MAX_ORDER];
     level_order(N, dims, mode, opts.mode_order_policy, lv);
-    int at = 0;
-    for (int l = N - 1; l >= 0; --l) {
-      const int b = bits_for(dims[lv[l]]);
-      sp.shift[l] = at;
-      sp.mask[l] = (1ull << b) - 1;
-      if (dims[lv[l]] <= kByteRows) sp.byteLevels |= 1u << l;
-      at += b;
-      mb.mk.from[l] = bk.shift[lv[l]];
-    }
-    sp.blockShift = at;
     sp.blockDrop = sp.blockBits ? bits_for(dims[lv[1]]) - sp.blockBits : 0;
-    mb.keyBits = at + sp.blockBits;
+    u128 upTo = 0;
+    for (int l = 0; l < N; ++l) {
+      sp.shift[l] = bk.shift[lv[l]];
+      sp.mask[l] = bk.mask[lv[l]];
+      upTo |= (u128)sp.mask[l] << sp.shift[l];
+      sp.upTo[l] = upTo;
+      if (dims[lv[l]] <= kByteRows) sp.byteLevels |= 1u << l;
+    }
+    if (sp.blockBits) sp.upTo[0] |= ((u128)((1ull << sp.blockBits) - 1)) << (bk.shift[lv[1]] + sp.blockDrop);
+    mb.rootBits = bits_for(dims[mode]);
     mb.cnt = w.cnt + (size_t)mode * kCounters;
     out->order = N;
     out->mode = mode;
@@ -1499,7 +1489,8 @@ int hbcsf_device_build_bytes(int order, const uint64_t* dims, uint64_t nnz, cons
   HIP_TRY(temp_bytes((size_t)nnz, (size_t)((maxDim + 31) / 32), slices, o.fiber_threshold, maxBits, &tbytes),
           "rocPRIM scratch query");
   Workspace w{};
-  carve(w, nullptr, order, (size_t)nnz, row_maps_bytes(order, dims), slices, o.fiber_threshold, tbytes, maxBits > 64, per_fiber(o));
+  carve(w, nullptr, order, (size_t)nnz, row_maps_bytes(order, dims), slices, o.fiber_threshold, tbytes, maxBits > 64, per_fiber(o),
+        o.mid_blocking > 1);
   *workspace_bytes = w.total;
   *arena_bytes = arena_bound(order, dims, nnz, o.fiber_threshold);
   return HBCSF_OK;
@@ -1529,7 +1520,7 @@ int hbcsf_build_format_device(int order, const uint64_t* dims, uint64_t nnz, con
           "rocPRIM scratch query");
   Workspace w{};
   carve(w, (uint8_t*)workspace, order, (size_t)nnz, row_maps_bytes(order, dims), slices, o.fiber_threshold, tbytes, maxBits > 64,
-        per_fiber(o));
+        per_fiber(o), o.mid_blocking > 1);
   if (workspace_bytes < w.total) return fail(HBCSF_ENOMEM, "workspace is smaller than hbcsf_device_build_bytes");
 
   std::unique_ptr<hbcsf_tensor> t(new (std::nothrow) hbcsf_tensor);
