@@ -258,7 +258,7 @@ def time_device_build(torch, np, B, HbcsfTensor, t, host_tensor, args, log):
 def time_als(torch, ht, dfacs, rank, iterations, build_s, dev_build, log):
     """CPD-ALS iterations (Algorithm "CPD-ALS") from copies of the benchmark's factor matrices: wall time per
     iteration with the factors' Gram matrices carried over (the steady state of a decomposition), and the
-    library's own split into MTTKRP / Gram / host / product time."""
+    library's own split into MTTKRP / Gram / R x R pseudo-inverse ("host", the field's name) / product time."""
     from paper_1904_03329_amd import CpdAls
 
     facs = [f.clone() for f in dfacs]
