@@ -225,8 +225,13 @@ __global__ void pack_kernel(IndPtrs inds, const float* vals, size_t M, int N, Ba
 #pragma unroll
   for (int m = 0; m < HBCSF_MAX_ORDER; ++m) {
     if (m >= N) break;
-    const uint32_t i = inds.p[m][z];
-    off = off || (uint64_t)i >= bk.dims[m];
+    uint32_t i = inds.p[m][z];
+    if ((uint64_t)i >= bk.dims[m]) {
+      // the call will be refused, but the numbering is enqueued before the host knows: it has room for as many
+      // slices as the mode has rows, so an index past them must not become one (nor spill into the next field)
+      off = true;
+      i = 0;
+    }
     key |= (Key)i << bk.shift[m];
   }
   if (sizeof(Key) == 8) {
