@@ -465,6 +465,18 @@ __device__ __forceinline__ void put_p(float* __restrict__ p, int i, int j, float
 constexpr int small_threads(int R) { return R <= 32 ? 64 : R == 64 ? 256 : 1024; }  // (R / 4)^2, at least a wavefront
 constexpr int entry_threads(int R) { return R * R < 1024 ? R * R : 1024; }           // for kernels that walk R x R entries
 
+// First row and column of the 4 x 4 tile of an R x R matrix that thread `tid` keeps.  Below rank 32 a wavefront has more
+// threads than there are tiles: those without one are given the first (they read what it reads and store nothing).
+constexpr int tile_row(int R, int tid) { return tid < (R / 4) * (R / 4) ? 4 * (tid / (R / 4)) : 0; }
+constexpr int tile_column(int R, int tid) { return tid < (R / 4) * (R / 4) ? 4 * (tid % (R / 4)) : 0; }
+constexpr bool tiles_inside(int R) {
+  for (int tid = 0; tid < small_threads(R); ++tid)
+    if (tile_row(R, tid) + 4 > R || tile_column(R, tid) + 4 > R) return false;
+  return true;
+}
+static_assert(tiles_inside(8) && tiles_inside(16) && tiles_inside(32) && tiles_inside(64) && tiles_inside(128),
+              "every thread's tile lies in the matrix");
+
 // Pseudo-inverse of the symmetric matrix V by cyclic Jacobi rotations, n / 2 disjoint pairs at a time (round-robin
 // pairing): only when V is not safely positive definite.  a, q: [R][R] scratch.  Eigenvalues below 1e-15 of the largest
 // magnitude count as zero (the cut-off numpy.linalg.pinv applies to singular values).
@@ -588,7 +600,7 @@ __global__ __launch_bounds__(small_threads(R)) void small_pinv_kernel(SmallState
   const int tid = threadIdx.x;
   if (tid == 0 && stamp) stamp[0] = wall_clock64();
   const bool owns = tid < W * W;
-  const int i0 = 4 * (tid / W), j0 = 4 * (tid % W);
+  const int i0 = tile_row(R, tid), j0 = tile_column(R, tid);
   double x[4][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
