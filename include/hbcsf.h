@@ -293,8 +293,9 @@ typedef struct hbcsf_als hbcsf_als;
  *              lowers the number of workgroups.  Contents on entry are irrelevant; two calls that
  *              overlap in time must not share a workspace.
  *   s          device [rank][rank] fp64, 8-byte aligned, overwritten.
- * Products are formed in fp32 (matrix instructions at rank 32) and summed in fp64; the partial sums
- * are added in a fixed order, so equal inputs give equal bits.  Errors: EINVAL, ENOMEM (workspace
+ * Products are formed and summed in fp32 over at most 128 rows at rank 32 and 32 rows at the other
+ * ranks (matrix instructions), these partial sums in fp64; they are added in a fixed order, so equal
+ * inputs give equal bits.  Errors: EINVAL, ENOMEM (workspace
  * smaller than one slot), EHIP. */
 int hbcsf_gram_workspace_bytes(int rank, uint64_t *bytes);
 int hbcsf_gram(const float *a, uint64_t rows, int rank, void *workspace, uint64_t workspace_bytes,

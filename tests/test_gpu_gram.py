@@ -1,8 +1,8 @@
 """GPU parity of hbcsf_gram (the Gram matrices A^T A of Eq. 3) against the fp64 oracle.
 
-Bar: the device multiplies in fp32 and keeps fp32 partial sums for at most 128 rows before they go to fp64, so an
-entry's error is bounded by 128 * 2^-24 * sum_i |A[i][r] A[i][s]| <= 7.7e-6 * max(diag S) (Cauchy-Schwarz); the test
-asks for max |S_gpu - S_oracle| <= 1e-5 * max |S_oracle|.
+Bar: the device multiplies in fp32 and keeps fp32 partial sums for at most 128 rows (rank 32; 32 at the other ranks)
+before they go to fp64, so an entry's error is bounded by 128 * 2^-24 * sum_i |A[i][r] A[i][s]| <= 7.7e-6 * max(diag S)
+(Cauchy-Schwarz); the test asks for max |S_gpu - S_oracle| <= 1e-5 * max |S_oracle|.
 """
 import numpy as np
 import pytest
@@ -54,6 +54,18 @@ def test_gram_large_positive_matrix_and_small_workspace():
     for nbytes in (None, 32 * 32 * 8, 5 * 32 * 32 * 8 + 100):
         got = _gram(a, workspace_bytes=nbytes)
         assert np.max(np.abs(got - want)) <= TOL * np.max(np.abs(want)), nbytes
+
+
+@pytest.mark.parametrize("rank", [8, 16, 64, 128])
+def test_fp32_sums_end_after_32_rows(rank):
+    """At these ranks no fp32 sum goes over more than 32 rows (of a residue class modulo 32 / rank below rank 32).  The
+    first such stretch sums to 2^26, the next three to 32 each: in fp32 2^26 + 2 is 2^26 again, so a sum over two of the
+    stretches would lose every one of the small products; taken apart all sums are exact."""
+    rows = 32 * max(1, 32 // rank)
+    a = np.ones((4 * rows, rank), np.float32)
+    a[:rows] = 0
+    a[:max(1, 32 // rank)] = 8192
+    assert np.array_equal(_gram(a), cpd_als.gram(a))
 
 
 def test_gram_of_no_rows_is_zero_and_errors():
