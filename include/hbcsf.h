@@ -122,7 +122,8 @@ typedef struct hbcsf_stats {
  *   vals   host [nnz].     opts   host, may be NULL.
  *   out    receives the handle.  The inputs are not referenced after the call returns.
  * Duplicate coordinates are legal and act as separate nonzeros.
- * Limits: dims[m] <= 2^31 - 2, nnz < 2^32 - 2^16. */
+ * Limits: dims[m] <= 2^31 - 2, nnz < 2^32 - 2^16; the index bits of all modes together (rounded up per mode; with
+ * mid_blocking those of the block number too) at most 128, which only order-5 tensors can exceed (HBCSF_ERANGE). */
 int hbcsf_build_format(int order, const uint64_t *dims, uint64_t nnz,
                        const uint32_t *const *inds, const float *vals,
                        const hbcsf_opts *opts, hbcsf_tensor **out);
@@ -237,8 +238,8 @@ int hbcsf_kernel_ms(hbcsf_tensor *t, uint32_t calls_back, float ms[4]);
  * byte, built from COO arrays that already are in device memory and written straight into the
  * caller's device arena.  Packed coordinates (sum over the modes of ceil(log2(dim)) bits) above
  * 64 bits are sorted in two stable 64-bit passes; above 128 bits (possible at order 5 only) the
- * build is refused with HBCSF_ERANGE and hbcsf_build_format has to be used.  Orders 3 to 5 and
- * every option of hbcsf_opts.
+ * build is refused with HBCSF_ERANGE (a blocked mode's block number needs no bits of its own here).
+ * Orders 3 to 5 and every option of hbcsf_opts.
  * ------------------------------------------------------------------------------------------- */
 
 /* Sizes to allocate before hbcsf_build_format_device: arena_bytes is an upper bound over every

@@ -1049,7 +1049,7 @@ int check_args(int order, const uint64_t* dims, uint64_t nnz, const hbcsf_opts* 
     o->group_mask = 4;  // plain B-CSF: the kernel for the other modes walks one group
   }
   if (total > 128)
-    return fail(HBCSF_ERANGE, "the packed coordinates exceed 128 bits: build this tensor with hbcsf_build_format");
+    return fail(HBCSF_ERANGE, "the packed coordinates exceed 128 bits");
   *totalBits = total;
   int bbMax = 0;
   for (int m = 0; m < order; ++m) {

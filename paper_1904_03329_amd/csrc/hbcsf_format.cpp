@@ -634,6 +634,10 @@ int build_modes(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* c
     const int b = mid_block_bits(order, dims, opts, m);
     blocks = b > blocks ? b : blocks;
   }
+  if (nnz > 0 && total + blocks > 128) {
+    *err = "the packed coordinates, with a blocked mode's block number, exceed 128 bits";
+    return HBCSF_ERANGE;
+  }
   try {
     if (total + blocks <= 64)
       return build_modes_t<uint64_t>(order, dims, nnz, inds, vals, opts, modes, out, err);
