@@ -112,7 +112,8 @@ typedef struct hbcsf_stats {
   uint64_t flops_real;        /* multiply-adds actually done x2 (Section III-B's count)       */
   uint32_t level_mode[HBCSF_MAX_ORDER]; /* tensor mode at tree level 0 (root) .. N-1 (leaf)   */
   uint32_t fiber_threshold;   /* T_f in use                                                   */
-  double   build_seconds;     /* host time to build this mode's representation                */
+  double   build_seconds;     /* host time to build this mode's representation, with an equal share of
+                                 what is done once for all modes                              */
 } hbcsf_stats;
 
 /* Builds the per-mode HB-CSF representations on the host (sort by mode, CSF, fbr-split,

@@ -1,4 +1,6 @@
 """What the host builder refuses, what it reports and what it holds (no GPU)."""
+import time
+
 import numpy as np
 import pytest
 
@@ -38,3 +40,21 @@ def test_keys_above_128_bits_are_refused(bits, opts, built):
             assert np.array_equal(got[:, np.lexsort(got[::-1])], want[:, np.lexsort(want[::-1])])
     finally:
         B.free(h)
+
+
+def test_build_seconds_account_for_the_whole_call():
+    """The modes' times add up to the call's: what is done once for all modes (packing and sorting the coordinates, about
+    a third of this build) has its share in each.  The part outside them is one sum over the values."""
+    rng = np.random.default_rng(3)
+    dims, nnz = (300, 300, 30_000), 1_500_000
+    inds = [np.minimum(d * rng.random(nnz) ** 2, d - 1).astype(np.uint32) for d in dims]
+    vals = rng.uniform(-1, 1, nnz).astype(np.float32)
+    share = 0.0
+    for _ in range(5):
+        begin = time.perf_counter()
+        h = B.build_format(dims, inds, vals)
+        call = time.perf_counter() - begin
+        share = max(share, sum(B.get_stats(h, m)["build_seconds"] for m in range(3)) / call)
+        assert share <= 1.0
+        B.free(h)
+    assert share >= 0.9
