@@ -18,6 +18,7 @@
 #include <chrono>
 #include <cstring>
 #include <memory>
+#include <utility>
 
 #include <omp.h>
 
@@ -104,7 +105,10 @@ KeyLayout key_layout(int N, const uint64_t* dims, const int* lv) {
   return k;
 }
 
-// The nonzeros in the common order, and two buffer pairs in which one mode after the other is sorted.
+// The nonzeros in the common order, and two buffer pairs in which one mode after the other is sorted: 12 bytes (20 with
+// wide keys) a nonzero and pair.  The last mode sorts in the common order's own buffers and gives back what its sort did
+// not end in before its arrays are made; so does every mode of a large tensor.  20 M nonzeros, order 3: a peak of 42
+// bytes a nonzero with the format's 36, against 64 with all pairs kept to the end.
 template <typename Key>
 struct Sorted {
   std::unique_ptr<Key[]> key[3];
@@ -118,6 +122,10 @@ struct Sorted {
     if (!key[i]) key[i].reset(new (std::nothrow) Key[M + 1]);
     if (!val[i]) val[i].reset(new (std::nothrow) uint32_t[M + 1]);
     return key[i] && val[i];
+  }
+  void release(int i) {
+    key[i].reset();
+    val[i].reset();
   }
 };
 
@@ -165,10 +173,10 @@ int sort_common(int N, const uint64_t* dims, size_t M, const uint32_t* const* in
   return HBCSF_OK;
 }
 
-// One mode's representation from the common order.
+// One mode's representation from the common order, which the last mode may overwrite.
 template <typename Key>
 int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, Sorted<Key>& so, const hbcsf_opts& opts, int mode,
-                 ModeFormat* out, std::string* err) {
+                 bool last, ModeFormat* out, std::string* err) {
   const auto t_begin = std::chrono::steady_clock::now();
   const int N = order;
   const uint32_t L = opts.fiber_threshold ? opts.fiber_threshold : 64;
@@ -196,15 +204,18 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, Sorted<Key>& so,
   const int nt = chunks_for(M);
   Key* K = so.K;
   uint32_t* V = so.V;
-  if (mode != so.at.lv[0] || bb != 0) {
-    if (!so.alloc(so.spare[0], M) || !so.alloc(so.spare[1], M)) {
+  const bool sorted = mode == so.at.lv[0] && bb == 0;  // the common order is this mode's own
+  if (!sorted) {
+    if (!so.key[so.spare[0]]) std::swap(so.spare[0], so.spare[1]);
+    const int other = last ? 3 - so.spare[0] - so.spare[1] : so.spare[1];
+    if (!so.alloc(so.spare[0], M) || !so.alloc(other, M)) {
       *err = "out of host memory while sorting";
       return HBCSF_ENOMEM;
     }
     K = so.key[so.spare[0]].get();
     V = so.val[so.spare[0]].get();
-    Key* K2 = so.key[so.spare[1]].get();
-    uint32_t* V2 = so.val[so.spare[1]].get();
+    Key* K2 = so.key[other].get();
+    uint32_t* V2 = so.val[other].get();
     int from[HBCSF_MAX_ORDER];
     for (int l = 0; l < N; ++l)
       for (int c = 0; c < N; ++c)
@@ -224,6 +235,11 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, Sorted<Key>& so,
     }
     radix_sort_pairs<Key>(K, V, K2, V2, M, shift[0], kl.total - shift[0] + bb);
   }
+  // (a pair the next mode needs again is given back only where the allocator maps it by itself, from 32 MB on: a smaller
+  // one stays with the process either way)
+  if (last || (!sorted && M * sizeof(Key) >= ((size_t)32 << 20)))
+    for (int i = 0; i < 3; ++i)
+      if (so.key[i].get() != K && (last || so.key[i].get() != so.K)) so.release(i);
 
   auto idx = [&](int l, size_t p) -> uint32_t { return (uint32_t)((uint64_t)(K[p] >> shift[l]) & mask[l]); };
   auto fresh = [&](int l, size_t p) -> bool { return p == 0 || (K[p] >> shift[l]) != (K[p - 1] >> shift[l]); };
@@ -603,7 +619,7 @@ int build_modes_t(int order, const uint64_t* dims, uint64_t nnz, const uint32_t*
   // the sort every mode's order is taken from is part of each mode's time
   const double share = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_begin).count() / modes;
   for (int m = 0; rc == HBCSF_OK && m < modes; ++m) {
-    rc = build_mode_t<Key>(order, dims, nnz, so, opts, m, out[m], err);
+    rc = build_mode_t<Key>(order, dims, nnz, so, opts, m, m + 1 == modes, out[m], err);
     out[m]->stats.build_seconds += share;
   }
   return rc;

@@ -1,4 +1,7 @@
 """What the host builder refuses, what it reports and what it holds (no GPU)."""
+import os
+import subprocess
+import sys
 import time
 
 import numpy as np
@@ -58,3 +61,31 @@ def test_build_seconds_account_for_the_whole_call():
         assert share <= 1.0
         B.free(h)
     assert share >= 0.9
+
+
+_PEAK = """
+import numpy as np
+from paper_1904_03329_amd import binding as B
+def kib(field):
+    with open("/proc/self/status") as f:
+        return [int(l.split()[1]) for l in f if l.startswith(field)][0]
+rng, dims, nnz = np.random.default_rng(2), {dims}, {nnz}
+inds = [rng.integers(0, d, size=nnz, dtype=np.uint32) for d in dims]
+vals = rng.random(nnz, dtype=np.float32)
+B.free(B.build_format(dims, [i[:100] for i in inds], vals[:100]))
+before = kib("VmRSS:")
+h = B.build_format(dims, inds, vals)
+print((kib("VmHWM:") - before) * 1024 / nnz, B.device_bytes(h) / nnz)
+"""
+
+
+@pytest.mark.parametrize("dims", [(300, 300, 30_000), (30_000, 300, 300), (300, 30_000, 300)])
+def test_peak_memory_of_a_build(dims):
+    """Beside the format itself the build holds one sorted pair of key and value (12 bytes a nonzero) in its last fill;
+    the pairs other modes were sorted in are gone.  20 bytes a nonzero leave room for tables and what the allocator keeps;
+    the two pairs more that a builder without releases holds are 24."""
+    out = subprocess.run([sys.executable, "-c", _PEAK.format(dims=dims, nnz=9_000_000)], capture_output=True, text=True,
+                         check=True, cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    peak, formats = map(float, out.stdout.split()[-2:])
+    print(f"{dims}: peak {peak:.1f}, format {formats:.1f} bytes a nonzero")
+    assert peak <= formats + 20
