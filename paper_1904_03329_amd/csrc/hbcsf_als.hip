@@ -566,7 +566,7 @@ __device__ void jacobi_pinv(const SmallState& st, int n, double* __restrict__ a,
     double t = 0.0;
     for (int k = 0; k < R; ++k) {
       const double w = a[k * R + k];
-      if (fabs(w) > 1e-15 * wmax) t += q[(e / R) * R + k] * (1.0 / w) * q[(e % R) * R + k];
+      if (!(fabs(w) <= 1e-15 * wmax)) t += q[(e / R) * R + k] * (1.0 / w) * q[(e % R) * R + k];  // (a NaN is not small)
     }
     out[e] = t;
   }

@@ -42,6 +42,36 @@ def test_rank_deficient_update(rank, lazy):
     t.close()
 
 
+def _one_infinite_value(rank):
+    rng = np.random.default_rng(rank)
+    dims = (100, 61, 37)
+    flat = rng.choice(int(np.prod(dims)), size=2000, replace=False)
+    inds = [x.astype(np.uint32) for x in np.unravel_index(flat, dims)]
+    vals = rng.uniform(0.1, 1.0, size=flat.size).astype(np.float32)
+    vals[np.flatnonzero(inds[0] == 41)[0]] = np.inf
+    return dims, inds, vals, [rng.uniform(-1, 1, size=(d, rank)).astype(np.float32) for d in dims]
+
+
+@pytest.mark.parametrize("lazy", [False, True])
+@pytest.mark.parametrize("rank", [8, 16, 32, 64, 128])
+def test_pseudo_inverse_of_a_matrix_that_is_not_finite(rank, lazy):
+    """An infinite value makes one row of the first factor infinite or NaN, hence its Gram matrix and the V of both later
+    updates: no row of theirs can come out finite."""
+    import torch
+    from paper_1904_03329_amd import CpdAls, HbcsfTensor
+
+    dims, inds, vals, facs = _one_infinite_value(rank)
+    t = HbcsfTensor(dims, inds, vals).to_device()
+    als = CpdAls(t, rank)
+    dfacs = [torch.from_numpy(f.copy()).cuda() for f in facs]
+    print("als not finite", rank, lazy, flush=True)
+    als.iteration(dfacs, lazy=lazy)
+    for m in (1, 2):
+        assert bool((~torch.isfinite(dfacs[m])).any(dim=1).all()), f"factor {m}"
+    als.close()
+    t.close()
+
+
 @pytest.mark.parametrize("rank", [8, 16, 64, 128])
 @pytest.mark.parametrize("rows", [1, 3, 33, 129, 4099])
 def test_gram_of_ragged_matrices(rank, rows):
