@@ -341,8 +341,9 @@ int hbcsf_als_create(const hbcsf_tensor *t, int rank, void *workspace, uint64_t 
 /* One iteration.  factors: host array of `order` device pointers, factors[m] = [dims[m]][rank]
  * fp32 row-major, read and overwritten in place (factors[0]'s content on entry is not used, as in
  * the algorithm).  lambda: device [rank] fp32, written; may be null.  fit: host, may be null;
- * receives 1 - ||X - model|| / ||X|| computed from the Gram matrices and the last MTTKRP (the
- * nonzero coordinates are taken to be distinct).  flags: 0 or any of HBCSF_ALS_KEEP_GRAMS,
+ * receives 1 - ||X - model|| / ||X|| computed from the Gram matrices and the last MTTKRP: of the factors as they
+ * are written with HBCSF_ALS_LAZY_NORMALISATION, else of the update's exact solution (the nonzero coordinates are taken
+ * to be distinct).  flags: 0 or any of HBCSF_ALS_KEEP_GRAMS,
  * HBCSF_ALS_LAZY_NORMALISATION.
  * Blocking: the call returns after the work on hip_stream has finished.  Two calls on one state must not overlap.  Errors: EINVAL,
  * and whatever hbcsf_mttkrp reports. */

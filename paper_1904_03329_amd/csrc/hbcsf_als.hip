@@ -173,6 +173,21 @@ __global__ __launch_bounds__(1024) void gram_reduce_kernel(const double* __restr
   if (q == 0) s[e] = part[0][el];
 }
 
+// dots[block] = sum of v over the block's W wavefronts, in a fixed order.
+template <int W>
+__device__ __forceinline__ void block_dot(double v, double* __restrict__ dots) {
+  __shared__ double part[W];
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = part[0];
+#pragma unroll
+    for (int w = 1; w < W; ++w) t += part[w];
+    dots[blockIdx.x] = t;
+  }
+}
+
 // R <= 32: out = M P for blocks of 32 rows of 32 floats (R < 32: P is the block-diagonal matrix of 32 / R copies).  The
 // contraction index is split as k = 16 h + t so that lane (h, c) reads the 64 contiguous bytes M[row c of the
 // block][16 h .. 16 h + 15] as its sixteen left operands, and holds P[16 h + t][c] as the sixteen right operands for
@@ -182,15 +197,19 @@ __global__ __launch_bounds__(1024) void gram_reduce_kernel(const double* __restr
 // rows of the tile with lane c on column c -- exactly the operand shape of gram32_partial_kernel -- so sixteen more
 // matrix instructions add the tile's out^T out without moving any data.  The partial Gram sums go to the block's
 // scratch slot (reduced by gram_reduce_kernel), so M is read once per mode update instead of twice.
+// dots (may be null): per block the sum of M[i][r] out[i][r] over its entries, i.e. <X, model> of these factors once the
+// blocks' sums are added.  M's entries come a second time, in the product tile's layout, from lines just read.
 template <int R, bool GRAM>
 __global__ __launch_bounds__(256) void apply32_kernel(const float* __restrict__ m, uint64_t rows, uint64_t total,
                                                       const float* __restrict__ p, float* __restrict__ out,
                                                       uint64_t blocksPerWave, double* __restrict__ partial,
+                                                      double* __restrict__ dots,
                                                       unsigned long long* __restrict__ stamp) {
   if (stamp && blockIdx.x == 0 && threadIdx.x == 0) *stamp = wall_clock64();
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int h = lane >> 5, c = lane & 31;
+  double dot = 0.0;
   float pb[16];
 #pragma unroll
   for (int t = 0; t < 16; ++t) pb[t] = p[(16 * h + t) * 32 + c];
@@ -236,6 +255,13 @@ __global__ __launch_bounds__(256) void apply32_kernel(const float* __restrict__ 
         const uint64_t to = (b * 32 + (uint64_t)(8 * (v / 4) + 4 * h + (v % 4))) * 32 + c;
         if (to < total) __builtin_nontemporal_store(acc[v], out + to);
       }
+      if (GRAM && dots) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const uint64_t at = (b * 32 + (uint64_t)(8 * (v / 4) + 4 * h + (v % 4))) * 32 + c;
+          if (at < total) dot = fma((double)m[at], (double)acc[v], dot);
+        }
+      }
       if (GRAM) {
         // rows past the end of the matrix were computed from zeros and add nothing
 #pragma unroll
@@ -253,22 +279,24 @@ __global__ __launch_bounds__(256) void apply32_kernel(const float* __restrict__ 
     for (int v = 0; v < 16; ++v) red[wave][(8 * (v / 4) + 4 * h + (v % 4)) * 32 + c] = acc64[v];
     __syncthreads();
     write_slot32<R>(red, partial + (size_t)blockIdx.x * (R * R));
+    if (dots) block_dot<4>(dot, dots);
   }
 }
 
 // R = 64, 128: out = M P; a wavefront takes 32 rows x 32 columns (tile column q = wavefront of the block), the block's
 // wavefronts share the rows.  The contraction index is split as k = (R / 2) h + t, so a lane reads 2 R contiguous bytes
-// of its row and keeps its R / 2 right operands for the whole kernel.
+// of its row and keeps its R / 2 right operands for the whole kernel.  dots: as in apply32_kernel.
 template <int R>
 __global__ __launch_bounds__(2 * R) void apply_tiles_kernel(const float* __restrict__ m, uint64_t rows,
                                                             const float* __restrict__ p, float* __restrict__ out,
-                                                            uint64_t rowBlocksPerBlock,
+                                                            uint64_t rowBlocksPerBlock, double* __restrict__ dots,
                                                             unsigned long long* __restrict__ stamp) {
   if (stamp && blockIdx.x == 0 && threadIdx.x == 0) *stamp = wall_clock64();
   constexpr int K = R / 2;
   const int lane = threadIdx.x & 63;
   const int q = threadIdx.x >> 6;
   const int h = lane >> 5, c = lane & 31;
+  double dot = 0.0;
   float pb[K];
 #pragma unroll
   for (int t = 0; t < K; ++t) pb[t] = p[(K * h + t) * R + 32 * q + c];
@@ -300,7 +328,15 @@ __global__ __launch_bounds__(2 * R) void apply_tiles_kernel(const float* __restr
       const uint64_t ro = b * 32 + (uint64_t)(8 * (v / 4) + 4 * h + (v % 4));
       if (ro < rows) __builtin_nontemporal_store(acc[v], out + ro * R + 32 * q + c);
     }
+    if (dots) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const uint64_t ro = b * 32 + (uint64_t)(8 * (v / 4) + 4 * h + (v % 4));
+        if (ro < rows) dot = fma((double)m[ro * R + 32 * q + c], (double)acc[v], dot);
+      }
+    }
   }
+  if (dots) block_dot<R / 32>(dot, dots);
 }
 
 // a[i][r] *= s[r]: the column normalisation of Algorithm "CPD-ALS" when it was put off.
@@ -317,6 +353,7 @@ __global__ __launch_bounds__(256) void scale_columns_kernel(float4* __restrict__
 // Scratch of the Gram computation: one R x R fp64 slot per block.  At most kGramSlotsMax blocks, fewer when the
 // scratch buffer is smaller; any number of blocks >= 1 gives the same sum up to fp64 rounding.
 constexpr uint32_t kGramSlotsMax = 1024;
+constexpr uint32_t kDotsMax = 4096;   // blocks of a product kernel that leaves <M, out> (at most kGramSlotsMax for R <= 32)
 constexpr uint64_t kGramWorkspaceCap = 32ull << 20;   // hbcsf_gram_workspace_bytes never asks for more
 
 uint32_t gram_slots_for(int rank, uint64_t scratchBytes) {
@@ -370,32 +407,34 @@ void launch_gram(const float* a, uint64_t rows, int rank, double* scratch, uint3
 
 template <int R>
 void launch_apply32(const float* m, uint64_t n, uint64_t total, const float* p, float* out, uint64_t per, uint32_t blocks,
-                    double* scratch, unsigned long long* stamp, hipStream_t st) {
+                    double* scratch, double* dots, unsigned long long* stamp, hipStream_t st) {
   if (scratch)
-    hipLaunchKernelGGL((apply32_kernel<R, true>), dim3(blocks), dim3(256), 0, st, m, n, total, p, out, per, scratch, stamp);
+    hipLaunchKernelGGL((apply32_kernel<R, true>), dim3(blocks), dim3(256), 0, st, m, n, total, p, out, per, scratch, dots, stamp);
   else
-    hipLaunchKernelGGL((apply32_kernel<R, false>), dim3(blocks), dim3(256), 0, st, m, n, total, p, out, per, scratch, stamp);
+    hipLaunchKernelGGL((apply32_kernel<R, false>), dim3(blocks), dim3(256), 0, st, m, n, total, p, out, per, scratch, dots, stamp);
 }
 
 // out = m p, and with g: g (device, [R][R] fp64) = out^T out (in the same pass over m for R <= 32).  p: [R][R], for
-// R < 32 the [32][32] block-diagonal matrix of it.
-void launch_apply(const float* m, uint64_t rows, int rank, const float* p, float* out, double* scratch, uint32_t slots,
-                  double* g, int numCU, hipStream_t st, unsigned long long* stamp) {
+// R < 32 the [32][32] block-diagonal matrix of it.  dots (with g only, [kDotsMax]): <m, out> as one sum per block; returns
+// how many there are.
+uint32_t launch_apply(const float* m, uint64_t rows, int rank, const float* p, float* out, double* scratch, uint32_t slots,
+                      double* g, double* dots, int numCU, hipStream_t st, unsigned long long* stamp) {
+  uint32_t used = 0;
   if (rank > 32) {
     if (rows > 0) {
       const uint64_t nBlocks = (rows + 31) / 32;
       uint64_t blocks = (uint64_t)numCU * 16;
+      if (blocks > kDotsMax) blocks = kDotsMax;
       const uint64_t per = (nBlocks + blocks - 1) / blocks;
-      blocks = (nBlocks + per - 1) / per;
+      used = (uint32_t)((nBlocks + per - 1) / per);
       if (rank == 64)
-        hipLaunchKernelGGL(apply_tiles_kernel<64>, dim3((uint32_t)blocks), dim3(128), 0, st, m, rows, p, out, per, stamp);
+        hipLaunchKernelGGL(apply_tiles_kernel<64>, dim3(used), dim3(128), 0, st, m, rows, p, out, per, dots, stamp);
       else
-        hipLaunchKernelGGL(apply_tiles_kernel<128>, dim3((uint32_t)blocks), dim3(256), 0, st, m, rows, p, out, per, stamp);
+        hipLaunchKernelGGL(apply_tiles_kernel<128>, dim3(used), dim3(256), 0, st, m, rows, p, out, per, dots, stamp);
     }
     if (g) launch_gram(out, rows, rank, scratch, slots, g, numCU, st);
-    return;
+    return used;
   }
-  uint32_t used = 0;
   if (rows > 0) {
     const uint64_t n = rows_of_32(rows, rank), total = rows * (uint64_t)rank;
     const uint64_t nBlocks = (n + 31) / 32;
@@ -406,12 +445,13 @@ void launch_apply(const float* m, uint64_t rows, int rank, const float* p, float
     used = (uint32_t)(((nBlocks + per - 1) / per + 3) / 4);
     double* sc = g ? scratch : nullptr;
     switch (rank) {
-      case 8: launch_apply32<8>(m, n, total, p, out, per, used, sc, stamp, st); break;
-      case 16: launch_apply32<16>(m, n, total, p, out, per, used, sc, stamp, st); break;
-      default: launch_apply32<32>(m, n, total, p, out, per, used, sc, stamp, st); break;
+      case 8: launch_apply32<8>(m, n, total, p, out, per, used, sc, dots, stamp, st); break;
+      case 16: launch_apply32<16>(m, n, total, p, out, per, used, sc, dots, stamp, st); break;
+      default: launch_apply32<32>(m, n, total, p, out, per, used, sc, dots, stamp, st); break;
     }
   }
   if (g) launch_reduce(scratch, used, rank, g, st);
+  return used;
 }
 
 void launch_scale_columns(float* a, uint64_t rows, int rank, const float* s, int numCU, hipStream_t st) {
@@ -766,16 +806,23 @@ __global__ __launch_bounds__(entry_threads(R)) void small_update_kernel(SmallSta
 // End of an iteration: lambda_r = product over the modes of the column norms, the model's squared norm from the Gram
 // matrices of the unnormalised factors, <X, model>; then the algorithm's closing normalisation c_m <- c_m norms_m (which
 // makes c_m = 1 where the factor was written normalised).  report (host memory): {<X, model>, ||model||^2}.
+// <X, model> of put-off updates is <M, A_n> of the last mode n (the other factors' scales are 1 by then), from the sums the
+// product's blocks left in `dots`.  For the exact solution trace(V A_n^T A_n), the same sum as ||model||^2, would do, but
+// A_n carries the rounding of P and of the product, and what that adds to the trace is of first order, amplified by the
+// condition of V: at rank 16 with two nearly equal columns (condition 3e6) the fit is off by 1.1e-3, with <M, A_n> by 7e-6.
 template <int R>
 __global__ __launch_bounds__(entry_threads(R)) void small_finish_kernel(SmallState st, int lazy, const double* __restrict__ inner,
+                                                                        const double* __restrict__ dots, uint32_t nDots,
                                                                         float* __restrict__ lambda,
                                                                         double* __restrict__ report,
                                                                         unsigned long long* __restrict__ stamp) {
   constexpr int T = entry_threads(R);
-  __shared__ double part[T];
+  __shared__ double part[T], partInner[T];
   const int tid = threadIdx.x;
   if (tid == 0) *stamp = wall_clock64();
-  double model = 0.0;
+  double model = 0.0, sum = 0.0;
+  if (lazy)
+    for (uint32_t k = (uint32_t)tid; k < nDots; k += T) sum += dots[k];
   for (int e = tid; e < R * R; e += T) {
     const int i = e / R, j = e % R;
     double g = 1.0;
@@ -783,14 +830,17 @@ __global__ __launch_bounds__(entry_threads(R)) void small_finish_kernel(SmallSta
     model += g;
   }
   part[tid] = model;
+  partInner[tid] = sum;
   __syncthreads();
   for (int half = T / 2; half > 0; half >>= 1) {
-    if (tid < half) part[tid] += part[tid + half];
+    if (tid < half) {
+      part[tid] += part[tid + half];
+      partInner[tid] += partInner[tid + half];
+    }
     __syncthreads();
   }
   if (tid == 0) {
-    // put-off updates: V^+ V V^+ = V^+, so <X, model> = trace(V A_n^T A_n), which is the same sum
-    report[0] = lazy ? part[0] : *inner;
+    report[0] = lazy ? partInner[0] : *inner;
     report[1] = part[0];
   }
   for (int r = tid; r < R; r += T) {
@@ -969,6 +1019,7 @@ struct hbcsf_als {
   double* vp = nullptr;           // V^+ [R][R]
   double* tmp[2] = {nullptr, nullptr};  // [R][R] each
   double* inner = nullptr;        // <X, model> of an ordinary iteration
+  double* dots = nullptr;         // of a put-off one, as the blocks' sums [kDotsMax]
   SmallState small{};
   bool pending[HBCSF_MAX_ORDER] = {};  // the stored factor's columns still carry norms (small.scale)
   bool gramsValid = false;
@@ -1055,7 +1106,7 @@ int apply_pending_normalisation(hbcsf_als* a, float* const* factors, hipStream_t
 
 // Where the parts of an ALS state's workspace lie (bytes from its start).
 struct AlsLayout {
-  uint64_t m, s, p, factor, vp, tmp[2], inner, gram, scale, norm, scratch, total;
+  uint64_t m, s, p, factor, vp, tmp[2], inner, dots, gram, scale, norm, scratch, total;
 };
 
 AlsLayout als_layout(const hbcsf_tensor* t, int rank) {
@@ -1078,6 +1129,7 @@ AlsLayout als_layout(const hbcsf_tensor* t, int rank) {
   l.vp = take(rr * 8);
   for (int k = 0; k < 2; ++k) l.tmp[k] = take(rr * 8);
   l.inner = take(8);
+  l.dots = take((uint64_t)kDotsMax * 8);
   l.gram = take((uint64_t)t->order * rr * 8);
   l.scale = take((uint64_t)t->order * rank * 8);
   l.norm = take((uint64_t)t->order * rank * 8);
@@ -1103,6 +1155,7 @@ int enqueue_iteration(hbcsf_als* a, float* const* factors, float* lambda, int fl
   }
   a->gramsValid = false;
   a->timed = false;
+  uint32_t nDots = 0;
   for (int n = 0; n < order; ++n) {
     const float* facs[HBCSF_MAX_ORDER];
     for (int m = 0; m < order; ++m) facs[m] = factors[m];
@@ -1115,8 +1168,8 @@ int enqueue_iteration(hbcsf_als* a, float* const* factors, float* lambda, int fl
     if (rc != HBCSF_OK) return rc;
     if (lazy) {
       // A_n = M V^+ written unnormalised, with its Gram matrix
-      launch_apply(a->m, t->dims[n], R, a->p, factors[n], a->gramScratch, a->gramSlots, a->small.gram[n], t->numCU, st,
-                   &a->report->stamp[n][2]);
+      nDots = launch_apply(a->m, t->dims[n], R, a->p, factors[n], a->gramScratch, a->gramSlots, a->small.gram[n],
+                           n + 1 == order ? a->dots : nullptr, t->numCU, st, &a->report->stamp[n][2]);
     } else {
       launch_gram(a->m, t->dims[n], R, a->gramScratch, a->gramSlots, a->s, t->numCU, st, &a->report->stamp[n][2]);
       with_rank(R, [&](auto r) {
@@ -1129,7 +1182,7 @@ int enqueue_iteration(hbcsf_als* a, float* const* factors, float* lambda, int fl
         hipLaunchKernelGGL(small_update_kernel<RR>, dim3(1), dim3(entry_threads(RR)), 0, st, a->small, n, a->tmp[1],
                            a->vp, a->s, a->p, a->inner);
       });
-      launch_apply(a->m, t->dims[n], R, a->p, factors[n], nullptr, 0, nullptr, t->numCU, st, nullptr);
+      launch_apply(a->m, t->dims[n], R, a->p, factors[n], nullptr, 0, nullptr, nullptr, t->numCU, st, nullptr);
     }
     e = hipGetLastError();
     if (e != hipSuccess) return fail_hip(e, "mode update kernel launch");
@@ -1137,7 +1190,7 @@ int enqueue_iteration(hbcsf_als* a, float* const* factors, float* lambda, int fl
   with_rank(R, [&](auto r) {
     constexpr int RR = decltype(r)::value;
     hipLaunchKernelGGL(small_finish_kernel<RR>, dim3(1), dim3(entry_threads(RR)), 0, st, a->small, lazy ? 1 : 0, a->inner,
-                       lambda, a->report->value, &a->report->end);
+                       a->dots, nDots, lambda, a->report->value, &a->report->end);
   });
   e = hipGetLastError();
   if (e != hipSuccess) return fail_hip(e, "iteration end kernel launch");
@@ -1251,6 +1304,7 @@ int hbcsf_als_create(const hbcsf_tensor* t, int rank, void* workspace, uint64_t 
   a->vp = (double*)(w + l.vp);
   for (int k = 0; k < 2; ++k) a->tmp[k] = (double*)(w + l.tmp[k]);
   a->inner = (double*)(w + l.inner);
+  a->dots = (double*)(w + l.dots);
   a->small.order = t->order;
   for (int m = 0; m < t->order; ++m) {
     a->small.gram[m] = (double*)(w + l.gram) + (size_t)m * rank * rank;

@@ -42,6 +42,44 @@ def test_rank_deficient_update(rank, lazy):
     t.close()
 
 
+def _nearly_equal_columns(rank, eps):
+    """A third of a rank-4 tensor's entries, and starting factors whose first two columns differ by eps."""
+    rng = np.random.default_rng(rank)
+    dims = (16, 12, 6007)
+    flat = rng.choice(int(np.prod(dims)), size=380_000, replace=False)
+    inds = [x.astype(np.uint32) for x in np.unravel_index(flat, dims)]
+    vals = cpd_als.model_values(inds, [rng.uniform(0, 1, size=(d, 4)) for d in dims], np.ones(4)).astype(np.float32)
+    facs = [rng.uniform(0, 1, size=(d, rank)).astype(np.float32) for d in dims]
+    for f in facs:
+        f[:, 1] = f[:, 0] + eps * rng.uniform(-1, 1, f.shape[0]).astype(np.float32)
+    return dims, inds, vals, facs
+
+
+@pytest.mark.parametrize("eps", [1.0, 1e-3])
+@pytest.mark.parametrize("rank", [8, 16, 32, 64, 128])
+def test_fit_of_a_put_off_update_is_that_of_the_factors_written(rank, eps):
+    """||model||^2 is the sum of V's entries times those of the last factor's Gram matrix.  Its entries are fp32 sums of 128
+    rows at most (each added with one rounding of up to 2^-24, as a random walk sqrt(128) / 3 of them): 2^-22 of the
+    terms' magnitudes bounds the error, and the residual's with it.  An inner product taken from the same sum, as if the
+    factor solved the normal equations exactly, is off by several times that."""
+    import torch
+    from paper_1904_03329_amd import CpdAls, HbcsfTensor
+
+    dims, inds, vals, facs = _nearly_equal_columns(rank, eps)
+    t = HbcsfTensor(dims, inds, vals).to_device()
+    als = CpdAls(t, rank)
+    dfacs = [torch.from_numpy(f.copy()).cuda() for f in facs]
+    print("als fit", rank, eps, flush=True)
+    fit = als.iteration(dfacs, lazy=True)
+    got = [f.cpu().numpy() for f in dfacs]   # not normalised yet: the model without weights
+    want = cpd_als.fit(dims, inds, vals, got, np.ones(rank))
+    terms = np.abs(np.prod([cpd_als.gram(f) for f in got], axis=0)).sum() / np.sum(vals.astype(np.float64) ** 2)
+    print(f"fit {fit:.8f}, off by {fit - want:+.1e}, terms {terms:.1f}", flush=True)
+    assert abs(fit - want) <= 2.0 ** -22 * (1 + terms) / (2 * (1 - want))
+    als.close()
+    t.close()
+
+
 def _one_infinite_value(rank):
     rng = np.random.default_rng(rank)
     dims = (100, 61, 37)
