@@ -193,9 +193,10 @@ int hbcsf_host_array(const hbcsf_tensor *t, int mode, int group, int level, int 
                                         keep the last n calls' event sets; 0 = off              */
 #define HBCSF_TUNE_WAVES_PER_CU     2 /* wavefront spans launched per compute unit when T_s is
                                         automatic (default 128)                                 */
-#define HBCSF_TUNE_STEPS            3 /* gathers a lane group keeps in flight: 4 or 8 (default: 8 for long
-                                        order-3 streams, else 4); 8 is only available with runs of 64
-                                        and rows of 128 bytes, ignored elsewhere                  */
+#define HBCSF_TUNE_STEPS            3 /* gathers a lane group keeps in flight: 4, 8 or 0 = automatic, the
+                                        default (8 for order-3 streams of 40 M nonzeros and more in runs
+                                        of 64, else 4).  A choice of two at rows of 128 bytes; the other
+                                        ranks have 4.                                              */
 #define HBCSF_TUNE_KERNEL_MASK      4 /* which kernels hbcsf_mttkrp launches: bit0 define, bit1 COO,
                                         bit2 CSL, bit3 CSF (default 15).  For ablation and profiling
                                         only: with bits cleared the output is incomplete.        */

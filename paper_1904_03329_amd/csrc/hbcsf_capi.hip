@@ -332,10 +332,12 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
   const uint64_t sparseNnz = f.g[kCsl].nnz + f.g[kCsf].nnz;
   const bool runCsl = f.g[kCsl].nnz > 0 && (t->kernelMask & 4u), runCsf = f.g[kCsf].nnz > 0 && (t->kernelMask & 8u);
   const bool dense = t->denseMid == 1 && dense_mid_available(N, G, lshift);
-  // 8 gathers in flight with parts of whole 64-nonzero runs: four wavefronts per SIMD instead of five, but half the
-  // staging per nonzero.  Pays at order 3 with rows of 128 bytes, narrow factor matrices and a stream that fills the chip
-  // many times over (100 M nonzeros 2.32 -> 2.25 ms, 56 M 1.15 -> 1.08 ms; 40 M and fewer equal, 5 M 5 % slower).
-  const bool longParts = G == 8 && lshift == 6 && (t->steps == 8 || (t->steps == 0 && N == 3 && !wide && sparseNnz >= 40000000));
+  // 8 gathers in flight with parts of whole runs: at order 3 and runs of 64 four wavefronts per SIMD instead of five, but
+  // half the staging per nonzero.  Pays there with rows of 128 bytes, narrow factor matrices and a stream that fills the
+  // chip many times over (100 M nonzeros 2.32 -> 2.25 ms, 56 M 1.15 -> 1.08 ms; 40 M and fewer equal, 5 M 5 % slower);
+  // at other run lengths and orders only where the tuning key asks for it.
+  const bool longParts = G == 8 && (t->steps == 8 || (t->steps == 0 && N == 3 && lshift == 6 && !wide && sparseNnz >= 40000000));
+  const int denseSteps = t->steps ? t->steps : N == 3 ? 8 : 4;
   // CSL and B-CSF group in one launch, unless their times are asked for one by one (or the kernel with 8 gathers
   // is used: with both bodies in it, it no longer fits four wavefronts per SIMD)
   const bool together = runCsl && runCsf && !es && !dense && !longParts && !t->persistent;
@@ -380,12 +382,12 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
         uint64_t b = (gf.nnz + perBlock - 1) / perBlock;
         const uint64_t cap = (uint64_t)t->numCU * 16;
         if (b > cap) b = cap;
-        e = launch_group(f64, g, N, G, wide, a, nullptr, round_up8(b), 256, 0, s);
+        e = launch_group(f64, g, N, G, 4, wide, a, nullptr, round_up8(b), 256, 0, s);
         launched = true;
       }
     } else if (g == kCsl ? runCsl && !together : runCsf) {
       const uint32_t part = g == kCsf && dense ? lshift
-                            : longParts ? 6u
+                            : longParts ? lshift
                                         : part_shift(together ? sparseNnz : gf.nnz, NG, lshift, t->numCU);
       const GroupArgs a = sparse_args(g, part);
       GroupArgs csl;
@@ -396,7 +398,7 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
       int wpb = 4;
       while (wpb > 1 && ldsWave * wpb > 48 * 1024) wpb >>= 1;
       // the launcher sizes the grid
-      e = launch_group(f64, g, N, G, wide, a, together ? &csl : nullptr, (uint32_t)t->numCU, 64 * wpb,
+      e = launch_group(f64, g, N, G, a.denseMid ? denseSteps : longParts ? 8 : 4, wide, a, together ? &csl : nullptr, (uint32_t)t->numCU, 64 * wpb,
                        ldsWave * wpb, s);
       launched = true;
     }
@@ -529,7 +531,7 @@ int hbcsf_tune(hbcsf_tensor* t, int key, uint64_t value) try {
     return HBCSF_OK;
   }
   if (key == HBCSF_TUNE_STEPS) {
-    if (value != 4 && value != 8) return fail(HBCSF_EINVAL, "steps must be 4 or 8");
+    if (value != 0 && value != 4 && value != 8) return fail(HBCSF_EINVAL, "steps must be 4 or 8, or 0 for the automatic choice");
     t->steps = (int)value;
     return HBCSF_OK;
   }

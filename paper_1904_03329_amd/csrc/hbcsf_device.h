@@ -58,12 +58,13 @@ struct GroupArgs {
 
 // kind: KernelKind; order 3, 4 or 5; G = row bytes / 16 lanes per factor row (fp32: rank / 4 = 2, 4, 8, 16 or 32;
 // fp64: rank / 2 = 8, 16 or 32, the launch functions named ...64...);
-// csl = null, or with kind = kCsfKernel the CSL group's arguments: both groups in one launch (same part size); wide = some gathered factor matrix
-// is 4 GiB or larger (64-bit row addressing).  One launch function per (G, order) pair, each
+// steps = records a lane group keeps in flight (4, or at G = 8 also 8; not used for the COO group); csl = null, or with
+// kind = kCsfKernel and 4 steps the CSL group's arguments: both groups in one launch (same part size); wide = some
+// gathered factor matrix is 4 GiB or larger (64-bit row addressing).  One launch function per (G, order) pair, each
 // compiled in its own object file.  For the CSL and B-CSF kernels `blocks` is the number of compute
 // units and the launcher sizes the grid (one wavefront per span, or persistent).
 #define HBCSF_DECLARE_LAUNCH(G, N)                                                                  \
-  hipError_t launch_group_g##G##_n##N(int kind, bool wide, const GroupArgs& a,          \
+  hipError_t launch_group_g##G##_n##N(int kind, int steps, bool wide, const GroupArgs& a,          \
                                       const GroupArgs* csl, uint32_t blocks, uint32_t threads, size_t ldsBytes, hipStream_t s); \
   hipError_t launch_define_coo_g##G##_n##N(bool wide, const GroupArgs& a, const uint32_t* ownedBits,   \
                                            const uint32_t* cooBits, const uint32_t* cooPtr, uint64_t rows, \
@@ -85,7 +86,7 @@ HBCSF_DECLARE_LAUNCH(16, 5)
 HBCSF_DECLARE_LAUNCH(32, 5)
 #undef HBCSF_DECLARE_LAUNCH
 #define HBCSF_DECLARE_LAUNCH64(G, N)                                                                  \
-  hipError_t launch_group64_g##G##_n##N(int kind, bool wide, const GroupArgs& a,          \
+  hipError_t launch_group64_g##G##_n##N(int kind, int steps, bool wide, const GroupArgs& a,          \
                                         const GroupArgs* csl, uint32_t blocks, uint32_t threads, size_t ldsBytes, hipStream_t s); \
   hipError_t launch_define_coo64_g##G##_n##N(bool wide, const GroupArgs& a, const uint32_t* ownedBits,   \
                                              const uint32_t* cooBits, const uint32_t* cooPtr, uint64_t rows, \
@@ -102,13 +103,13 @@ HBCSF_DECLARE_LAUNCH64(32, 5)
 #undef HBCSF_DECLARE_LAUNCH64
 
 // f64: the factor matrices and the output hold doubles (GroupArgs' float pointers then address doubles).
-inline hipError_t launch_group(bool f64, int kind, int order, int G, bool wide, const GroupArgs& a,
+inline hipError_t launch_group(bool f64, int kind, int order, int G, int steps, bool wide, const GroupArgs& a,
                                const GroupArgs* csl, uint32_t blocks, uint32_t threads, size_t ldsBytes, hipStream_t s) {
 #define HBCSF_CASE64(GV)                                                                              \
   case GV:                                                                                            \
-    return order == 3   ? launch_group64_g##GV##_n3(kind, wide, a, csl, blocks, threads, ldsBytes, s) \
-           : order == 4 ? launch_group64_g##GV##_n4(kind, wide, a, csl, blocks, threads, ldsBytes, s) \
-                        : launch_group64_g##GV##_n5(kind, wide, a, csl, blocks, threads, ldsBytes, s);
+    return order == 3   ? launch_group64_g##GV##_n3(kind, steps, wide, a, csl, blocks, threads, ldsBytes, s) \
+           : order == 4 ? launch_group64_g##GV##_n4(kind, steps, wide, a, csl, blocks, threads, ldsBytes, s) \
+                        : launch_group64_g##GV##_n5(kind, steps, wide, a, csl, blocks, threads, ldsBytes, s);
   if (f64) {
     switch (G) {
       HBCSF_CASE64(8)
@@ -121,9 +122,9 @@ inline hipError_t launch_group(bool f64, int kind, int order, int G, bool wide, 
 #undef HBCSF_CASE64
 #define HBCSF_CASE(GV)                                                                              \
   case GV:                                                                                          \
-    return order == 3   ? launch_group_g##GV##_n3(kind, wide, a, csl, blocks, threads, ldsBytes, s) \
-           : order == 4 ? launch_group_g##GV##_n4(kind, wide, a, csl, blocks, threads, ldsBytes, s) \
-                        : launch_group_g##GV##_n5(kind, wide, a, csl, blocks, threads, ldsBytes, s);
+    return order == 3   ? launch_group_g##GV##_n3(kind, steps, wide, a, csl, blocks, threads, ldsBytes, s) \
+           : order == 4 ? launch_group_g##GV##_n4(kind, steps, wide, a, csl, blocks, threads, ldsBytes, s) \
+                        : launch_group_g##GV##_n5(kind, steps, wide, a, csl, blocks, threads, ldsBytes, s);
   switch (G) {
     HBCSF_CASE(2)
     HBCSF_CASE(4)

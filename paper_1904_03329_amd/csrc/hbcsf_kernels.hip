@@ -1357,14 +1357,18 @@ hipError_t launch_one(int kind, const GroupArgs& a, const GroupArgs* csl, uint32
     }
     return hipErrorInvalidValue;  // with 8 gathers in flight the groups are launched one by one
   }
-  void (*kernel)(GroupArgs) = csl_group_kernel<G, N, SS, S, WIDE>;
-  if (kind == kCsfKernel) {
-    if constexpr (occ4) kernel = csf_group_kernel_occ4<G, N, SS, S>;
-    else kernel = csf_group_kernel<G, N, SS, S, WIDE>;
-    if constexpr (G == 8 && N <= 4 && (SS == 5 || SS == 6)) {
-      if (a.denseMid) kernel = csf_group_dense_kernel<G, N, SS, S, WIDE>;
+  void (*kernel)(GroupArgs) = nullptr;
+  if constexpr (G != 8 || SS < 6 || S == 8) {  // (G = 8, 4 gathers: parts of at most 32 except in the dense variant)
+    kernel = csl_group_kernel<G, N, SS, S, WIDE>;
+    if (kind == kCsfKernel) {
+      if constexpr (occ4) kernel = csf_group_kernel_occ4<G, N, SS, S>;
+      else kernel = csf_group_kernel<G, N, SS, S, WIDE>;
     }
   }
+  if constexpr (G == 8 && N <= 4 && (SS == 5 || SS == 6)) {
+    if (kind == kCsfKernel && a.denseMid) kernel = csf_group_dense_kernel<G, N, SS, S, WIDE>;
+  }
+  if (!kernel) return hipErrorInvalidValue;
   uint64_t blocks = span_blocks(a, wpb);
   if (a.persistent) {
     // resident blocks per CU of this kernel on the current device (asked per launch: the persistent launch is a
@@ -1380,16 +1384,21 @@ hipError_t launch_one(int kind, const GroupArgs& a, const GroupArgs* csl, uint32
 }
 
 template <int G, int N, int SS>
-hipError_t launch_ss(int kind, bool wide, const GroupArgs& a, const GroupArgs* csl, uint32_t cus, dim3 block,
+hipError_t launch_ss(int kind, int steps, bool wide, const GroupArgs& a, const GroupArgs* csl, uint32_t cus, dim3 block,
                      size_t lds, hipStream_t s) {
-  constexpr int S = G == 8 && SS == 6 ? 8 : 4;
-  return wide ? launch_one<G, N, SS, S, true>(kind, a, csl, cus, block, lds, s)
-              : launch_one<G, N, SS, S, false>(kind, a, csl, cus, block, lds, s);
+  if constexpr (G == 8) {
+    if (steps == 8)
+      return wide ? launch_one<G, N, SS, 8, true>(kind, a, csl, cus, block, lds, s)
+                  : launch_one<G, N, SS, 8, false>(kind, a, csl, cus, block, lds, s);
+  }
+  if (steps != 4) return hipErrorInvalidValue;
+  return wide ? launch_one<G, N, SS, 4, true>(kind, a, csl, cus, block, lds, s)
+              : launch_one<G, N, SS, 4, false>(kind, a, csl, cus, block, lds, s);
 }
 
 // The part sizes the caller can ask for at this G: units of at most 256 nonzeros, or at G = 8 parts of 64.
 template <int G, int N>
-hipError_t launch_g(int kind, bool wide, const GroupArgs& a, const GroupArgs* csl, dim3 grid, dim3 block,
+hipError_t launch_g(int kind, int steps, bool wide, const GroupArgs& a, const GroupArgs* csl, dim3 grid, dim3 block,
                     size_t lds, hipStream_t s) {
   if (kind == kCooKernel) {
     if (wide) hipLaunchKernelGGL((coo_group_kernel<G, N, true>), grid, block, 0, s, a);
@@ -1397,15 +1406,15 @@ hipError_t launch_g(int kind, bool wide, const GroupArgs& a, const GroupArgs* cs
     return hipGetLastError();
   }
   switch (a.partShift) {
-    case 3: return launch_ss<G, N, 3>(kind, wide, a, csl, grid.x, block, lds, s);
+    case 3: return launch_ss<G, N, 3>(kind, steps, wide, a, csl, grid.x, block, lds, s);
     case 4:
-      if constexpr (G >= 4) return launch_ss<G, N, 4>(kind, wide, a, csl, grid.x, block, lds, s);
+      if constexpr (G >= 4) return launch_ss<G, N, 4>(kind, steps, wide, a, csl, grid.x, block, lds, s);
       break;
     case 5:
-      if constexpr (G >= 8) return launch_ss<G, N, 5>(kind, wide, a, csl, grid.x, block, lds, s);
+      if constexpr (G >= 8) return launch_ss<G, N, 5>(kind, steps, wide, a, csl, grid.x, block, lds, s);
       break;
     case 6:
-      if constexpr (G >= 8) return launch_ss<G, N, 6>(kind, wide, a, csl, grid.x, block, lds, s);
+      if constexpr (G >= 8) return launch_ss<G, N, 6>(kind, steps, wide, a, csl, grid.x, block, lds, s);
       break;
   }
   return hipErrorInvalidValue;
@@ -1442,10 +1451,10 @@ hipError_t HBCSF_CAT(HBCSF_LAUNCH_DEFINE_COO, HBCSF_G, _n, HBCSF_N)(bool wide, c
   return hipGetLastError();
 }
 
-hipError_t HBCSF_CAT(HBCSF_LAUNCH_GROUP, HBCSF_G, _n, HBCSF_N)(int kind, bool wide, const GroupArgs& a,
+hipError_t HBCSF_CAT(HBCSF_LAUNCH_GROUP, HBCSF_G, _n, HBCSF_N)(int kind, int steps, bool wide, const GroupArgs& a,
                                                           const GroupArgs* csl, uint32_t blocks, uint32_t threads, size_t ldsBytes,
                                                           hipStream_t s) {
-  return launch_g<HBCSF_G, HBCSF_N>(kind, wide, a, csl, dim3(blocks), dim3(threads), ldsBytes, s);
+  return launch_g<HBCSF_G, HBCSF_N>(kind, steps, wide, a, csl, dim3(blocks), dim3(threads), ldsBytes, s);
 }
 
 #if HBCSF_G == 8 && !defined(HBCSF_F64)

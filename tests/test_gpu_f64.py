@@ -63,13 +63,15 @@ def test_build_options_do_not_change_the_result(oracle, dims, nnz, opts):
 
 
 def test_rank_16_kernel_variants(oracle):
-    """Rank 16 in fp64 is the 8-lanes-per-row mapping: its held-to-128-registers B-CSF variant and the dense
-    fiber-row gather (a tuning variant) are instantiated for doubles too."""
+    """Rank 16 in fp64 is the 8-lanes-per-row mapping: the kernels with 8 gathers in flight (the B-CSF one held to 128
+    registers, chosen by itself from 40 M nonzeros up, and the CSL one) and the dense fiber-row gather (a tuning variant)
+    are instantiated for doubles too."""
     rng = np.random.default_rng(5)
     dims = (4000, 500, 80)
     inds, vals = _skewed(rng, dims, 150_000)
     facs = _factors64(rng, dims, 16)
-    for kw in (dict(), dict(tune_dense=1), dict(tune_dense=1, group_mask=4)):
+    for kw in (dict(), dict(tune_steps=8), dict(tune_steps=8, group_mask=4), dict(tune_dense=1),
+               dict(tune_dense=1, group_mask=4)):
         print("f64 rank 16", kw, flush=True)
         _check_all_modes(oracle, dims, inds, vals, facs, f"f64 R=16 {kw}", **kw)
 
