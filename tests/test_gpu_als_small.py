@@ -80,6 +80,56 @@ def test_fit_of_a_put_off_update_is_that_of_the_factors_written(rank, eps):
     t.close()
 
 
+def _one_small_pivot(rank, ratio):
+    """Factors with nearly orthogonal columns, one of them scaled so that its pivot in V is about `ratio` of the largest
+    diagonal entry: V = D (I + E) D with a well conditioned I + E, so that the update is well determined all the same."""
+    rng = np.random.default_rng(rank)
+    dims = (333, 4 * rank + 5, 4 * rank + 9)
+    flat = rng.choice(int(np.prod(dims)), size=20_000, replace=False)
+    inds = [x.astype(np.uint32) for x in np.unravel_index(flat, dims)]
+    vals = rng.uniform(0.1, 1.0, size=flat.size).astype(np.float32)
+    facs = []
+    for d in dims:
+        f = rng.normal(size=(d, rank))
+        f /= np.linalg.norm(f, axis=0)
+        f[:, rank // 2 + 1] *= ratio ** 0.25
+        facs.append(f.astype(np.float32))
+    return dims, inds, vals, facs
+
+
+@pytest.mark.parametrize("ratio", [5e-11, 2e-10])
+@pytest.mark.parametrize("rank", [8, 16, 32, 64, 128])
+def test_pivots_on_both_sides_of_the_line(oracle, rank, ratio):
+    """A pivot below 1e-10 of the largest diagonal entry sends the update from the sweep to the eigenvalue form.  Both give
+    A = M V^-1, whose entries are sums of n rows' terms and R products in fp32: gamma (|M| |P|) bounds their error, with |M|
+    the MTTKRP of the absolute values and gamma = 2^-24 times the operations in one entry's chain."""
+    import torch
+    from paper_1904_03329_amd import CpdAls, HbcsfTensor
+
+    dims, inds, vals, facs = _one_small_pivot(rank, ratio)
+    v = cpd_als.gram(facs[1]) * cpd_als.gram(facs[2])
+    pivots = np.diag(np.linalg.cholesky(v)) ** 2
+    assert (pivots.min() < 1e-10 * v.max()) == (ratio < 1e-10)
+    p = np.linalg.inv(v)
+    want = oracle.mttkrp(dims, inds, vals, facs, 0) @ p
+    most = np.abs(oracle.mttkrp(dims, inds, np.abs(vals), [np.abs(f) for f in facs], 0)) @ np.abs(p)
+    bound = 2.0 ** -24 * (np.bincount(inds[0]).max() + rank + 8) * most
+    norm = np.linalg.norm(want, axis=0)
+    t = HbcsfTensor(dims, inds, vals).to_device()
+    als = CpdAls(t, rank)
+    dfacs = [torch.from_numpy(f.copy()).cuda() for f in facs]
+    print("als pivot", rank, ratio, flush=True)
+    als.iteration(dfacs)
+    got = dfacs[0].cpu().numpy().astype(np.float64)
+    got /= np.linalg.norm(got, axis=0)
+    want /= norm
+    bound = bound / norm + np.abs(want) * (np.linalg.norm(bound, axis=0) / norm)
+    print(f"largest error / bound {np.max(np.abs(got - want) / bound):.3f}", flush=True)
+    assert np.all(np.abs(got - want) <= bound)
+    als.close()
+    t.close()
+
+
 def _one_infinite_value(rank):
     rng = np.random.default_rng(rank)
     dims = (100, 61, 37)
