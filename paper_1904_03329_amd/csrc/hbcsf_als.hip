@@ -508,6 +508,7 @@ __device__ __forceinline__ void put_p(float* __restrict__ p, int i, int j, float
 }
 
 constexpr int small_threads(int R) { return R <= 32 ? 64 : R == 64 ? 256 : 1024; }  // (R / 4)^2, at least a wavefront
+constexpr int pinv_threads(int R) { return R == 32 ? 256 : small_threads(R); }       // the eigenvalue form uses them all
 constexpr int entry_threads(int R) { return R * R < 1024 ? R * R : 1024; }           // for kernels that walk R x R entries
 
 // First row and column of the 4 x 4 tile of an R x R matrix that thread `tid` keeps.  Below rank 32 a wavefront has more
@@ -515,111 +516,202 @@ constexpr int entry_threads(int R) { return R * R < 1024 ? R * R : 1024; }      
 constexpr int tile_row(int R, int tid) { return tid < (R / 4) * (R / 4) ? 4 * (tid / (R / 4)) : 0; }
 constexpr int tile_column(int R, int tid) { return tid < (R / 4) * (R / 4) ? 4 * (tid % (R / 4)) : 0; }
 constexpr bool tiles_inside(int R) {
-  for (int tid = 0; tid < small_threads(R); ++tid)
+  for (int tid = 0; tid < pinv_threads(R); ++tid)
     if (tile_row(R, tid) + 4 > R || tile_column(R, tid) + 4 > R) return false;
   return true;
 }
 static_assert(tiles_inside(8) && tiles_inside(16) && tiles_inside(32) && tiles_inside(64) && tiles_inside(128),
               "every thread's tile lies in the matrix");
 
+// 1 / x for a normal positive x: the hardware's estimate and two Newton steps (relative error near 2^-53).
+__device__ __forceinline__ double reciprocal(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+
+// 1 / sqrt(x) for a normal positive x, in the same way.
+__device__ __forceinline__ double reciprocal_root(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  r = fma(0.5 * r, fma(-x * r, r, 1.0), r);
+  return fma(0.5 * r, fma(-x * r, r, 1.0), r);
+}
+
 // Pseudo-inverse of the symmetric matrix V by cyclic Jacobi rotations, n / 2 disjoint pairs at a time (round-robin
-// pairing): only when V is not safely positive definite.  a, q: [R][R] scratch.  Eigenvalues below 1e-15 of the largest
-// magnitude count as zero (the cut-off numpy.linalg.pinv applies to singular values).
+// pairing): only when V is not safely positive definite.  Eigenvalues below 1e-15 of the largest magnitude count as zero
+// (the cut-off numpy.linalg.pinv applies to singular values).
+// A round is a chain of its angles, the rotations and two barriers, some hundred rounds a matrix, so the matrix stays in
+// LDS: a 2 x 2 block of row pair k and column pair l takes both its rotations from one thread, which loads all its blocks
+// before it stores any.  So do the eigenvectors up to rank 64; at 128, where both do not fit, a wavefront keeps to its own
+// rows of them in `qGlobal` ([R][R] scratch).  At rank 32 four wavefronts work on it, which wait while one sweeps: 1.6 ->
+// 0.7 us a round.  One matrix with half the components equal takes 52 / 147 / 820 / 6200 us at ranks 16 / 32 / 64 / 128
+// (150 / 1170 / 6000 / 52700 with both matrices in global memory; the host routine 23 / 180 / 1640 / 22600 and two copies).
+// Two diagonal entries that would both count as zero are rotated only once the entry between them is no smaller than the
+// others: rounding noise would turn them by any angle and stir what the sweep has just cleared back into their columns
+// (half the components equal, rank 32: 7 sweeps instead of 12 to 17).
 template <int R>
-__device__ void jacobi_pinv(const SmallState& st, int n, double* __restrict__ a, double* __restrict__ q,
-                            double* __restrict__ out, double* lds /* R + 2 */, double* part /* one per thread */) {
-  constexpr int T = small_threads(R);
+struct JacobiLds {
+  static constexpr bool kVectors = R <= 64;
+  double a[R * R];
+  double q[kVectors ? R * R : 1];
+  double c[R / 2], s[R / 2], inv[R];
+  double sums[3][pinv_threads(R) / 64];
+  int2 pair[R / 2];
+};
+
+template <int R>
+__device__ void jacobi_pinv(const SmallState& st, int n, JacobiLds<R>& lds, double* __restrict__ qGlobal, double* __restrict__ out) {
+  constexpr int T = pinv_threads(R), H = R / 2, S = T / H;   // S row pairs of a, or rows of q, at a time
+  constexpr bool kVectors = JacobiLds<R>::kVectors;
+  // blocks of a and rows of q a thread takes, and rows of q it holds at a time (with all eight at rank 128 it would spill)
+  constexpr int KA = (H + S - 1) / S, KQ = (R + S - 1) / S, KB = kVectors ? KQ : 4;
   const int tid = threadIdx.x;
-  double* cs = lds;          // [R / 2] cosines, then [R / 2] sines
-  double* red = lds + R;     // two sums
+  const int l = tid % H, first = tid / H;
+  double* a = lds.a;
+  double* q = kVectors ? lds.q : qGlobal;
   for (int e = tid; e < R * R; e += T) {
     a[e] = v_entry<R>(st, n, e / R, e % R);
     q[e] = e / R == e % R ? 1.0 : 0.0;
   }
   __syncthreads();
   for (int sweep = 0; sweep < 60; ++sweep) {
-    for (int diagonal = 0; diagonal < 2; ++diagonal) {
-      double sum = 0.0;
-      for (int e = tid; e < R * R; e += T)
-        if ((e / R == e % R) == (diagonal == 1)) sum += a[e] * a[e];
-      part[tid] = sum;
-      __syncthreads();
-      for (int half = T / 2; half > 0; half >>= 1) {
-        if (tid < half) part[tid] += part[tid + half];
-        __syncthreads();
+    double off = 0.0, diagonal = 0.0, most = 0.0;
+    for (int e = tid; e < R * R; e += T) {
+      const double x = a[e] * a[e];
+      if (e / R == e % R) {
+        diagonal += x;
+        most = fmax(most, fabs(a[e]));
+      } else {
+        off += x;
       }
-      if (tid == 0) red[diagonal] = part[0];
-      __syncthreads();
     }
-    const bool done = red[0] <= 1e-30 * red[1] || red[0] == 0.0;
+    for (int o = 32; o > 0; o >>= 1) {
+      off += __shfl_xor(off, o);
+      diagonal += __shfl_xor(diagonal, o);
+      most = fmax(most, __shfl_xor(most, o));
+    }
+    if ((tid & 63) == 0) {
+      lds.sums[0][tid >> 6] = off;
+      lds.sums[1][tid >> 6] = diagonal;
+      lds.sums[2][tid >> 6] = most;
+    }
     __syncthreads();
-    if (done) break;
+    off = diagonal = most = 0.0;
+    for (int w = 0; w < T / 64; ++w) {
+      off += lds.sums[0][w];
+      diagonal += lds.sums[1][w];
+      most = fmax(most, lds.sums[2][w]);
+    }
+    if (off <= 1e-30 * diagonal || off == 0.0) break;   // the same for every thread
+    const double small = 1e-15 * most, least = off / (R * R);
     for (int round = 0; round < R - 1; ++round) {
       // pair k of this round: players 0 (fixed) and 1 .. R-1 (rotating)
-      auto player = [&](int slot) { return slot == 0 ? 0 : 1 + (slot - 1 + round) % (R - 1); };
-      for (int k = tid; k < R / 2; k += T) {
-        const int x = player(k), y = player(R - 1 - k);
+      auto player = [&](int slot) {
+        const int x = slot - 1 + round;
+        return slot == 0 ? 0 : 1 + (x >= R - 1 ? x - (R - 1) : x);
+      };
+      if (tid < H) {
+        const int x = player(tid), y = player(R - 1 - tid);
         const int p = x < y ? x : y, r = x < y ? y : x;
-        const double apr = a[p * R + r];
+        const double app = a[p * R + p], arr = a[r * R + r], apr = a[p * R + r];
+        // t = tan of the angle, the smaller root: tan(2 angle) = 2 apr / (arr - app)
+        const double d = arr - app, h = 2.0 * apr, dh = fma(d, d, h * h);
         double c = 1.0, sn = 0.0;
-        if (apr != 0.0) {
-          const double theta = (a[r * R + r] - a[p * R + p]) / (2.0 * apr);
-          const double t = (theta >= 0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-          c = 1.0 / sqrt(t * t + 1.0);
+        const bool skip = fabs(app) <= small && fabs(arr) <= small && apr * apr < least;
+        if (apr != 0.0 && !skip && !(dh <= 1e-280)) {
+          const double t = (d >= 0 ? h : -h) * reciprocal(fabs(d) + dh * reciprocal_root(dh));
+          c = reciprocal_root(fma(t, t, 1.0));
           sn = t * c;
         }
-        cs[k] = c;
-        cs[R / 2 + k] = sn;
+        lds.c[tid] = c;
+        lds.s[tid] = sn;
+        lds.pair[tid] = make_int2(p, r);
       }
       __syncthreads();
-      for (int w = tid; w < R * (R / 2); w += T) {  // columns p, r of a and q
-        const int k = w % (R / 2), row = w / (R / 2);
-        const int x = player(k), y = player(R - 1 - k);
-        const int p = x < y ? x : y, r = x < y ? y : x;
-        const double c = cs[k], sn = cs[R / 2 + k];
-        const double ap = a[row * R + p], ar = a[row * R + r];
-        a[row * R + p] = c * ap - sn * ar;
-        a[row * R + r] = sn * ap + c * ar;
-        const double qp = q[row * R + p], qr = q[row * R + r];
-        q[row * R + p] = c * qp - sn * qr;
-        q[row * R + r] = sn * qp + c * qr;
+      const int2 cols = lds.pair[l];
+      const double cl = lds.c[l], sl = lds.s[l];
+      double x[KA][4], y[KB][2];
+      auto load_vectors = [&](int from) {
+#pragma unroll
+        for (int m = 0; m < KB; ++m) {
+          const int row = first + (from + m) * S;
+          if (row < R) {
+            y[m][0] = q[row * R + cols.x];
+            y[m][1] = q[row * R + cols.y];
+          }
+        }
+      };
+      auto turn_vectors = [&](int from) {
+#pragma unroll
+        for (int m = 0; m < KB; ++m) {
+          const int row = first + (from + m) * S;
+          if (row < R) {
+            q[row * R + cols.x] = cl * y[m][0] - sl * y[m][1];
+            q[row * R + cols.y] = sl * y[m][0] + cl * y[m][1];
+          }
+        }
+      };
+#pragma unroll
+      for (int m = 0; m < KA; ++m) {
+        const int k = first + m * S;
+        if (k < H) {
+          const int2 rows = lds.pair[k];
+          x[m][0] = a[rows.x * R + cols.x];
+          x[m][1] = a[rows.x * R + cols.y];
+          x[m][2] = a[rows.y * R + cols.x];
+          x[m][3] = a[rows.y * R + cols.y];
+        }
       }
-      __syncthreads();
-      for (int w = tid; w < R * (R / 2); w += T) {  // rows p, r of a
-        const int k = w / R, col = w % R;
-        const int x = player(k), y = player(R - 1 - k);
-        const int p = x < y ? x : y, r = x < y ? y : x;
-        const double c = cs[k], sn = cs[R / 2 + k];
-        const double ap = a[p * R + col], ar = a[r * R + col];
-        a[p * R + col] = c * ap - sn * ar;
-        a[r * R + col] = sn * ap + c * ar;
+      if (kVectors) load_vectors(0);
+#pragma unroll
+      for (int m = 0; m < KA; ++m) {
+        const int k = first + m * S;
+        if (k < H) {
+          const int2 rows = lds.pair[k];
+          const double ck = lds.c[k], sk = lds.s[k];
+          const double p0 = cl * x[m][0] - sl * x[m][1], p1 = sl * x[m][0] + cl * x[m][1];
+          const double r0 = cl * x[m][2] - sl * x[m][3], r1 = sl * x[m][2] + cl * x[m][3];
+          a[rows.x * R + cols.x] = ck * p0 - sk * r0;
+          a[rows.y * R + cols.x] = sk * p0 + ck * r0;
+          a[rows.x * R + cols.y] = ck * p1 - sk * r1;
+          a[rows.y * R + cols.y] = sk * p1 + ck * r1;
+        }
+      }
+      if (kVectors) {
+        turn_vectors(0);
+      } else {
+        for (int from = 0; from < KQ; from += KB) {
+          load_vectors(from);
+          turn_vectors(from);
+        }
       }
       __syncthreads();
     }
   }
-  if (tid == 0) {
-    double wmax = 0.0;
-    for (int k = 0; k < R; ++k) wmax = fmax(wmax, fabs(a[k * R + k]));
-    red[0] = wmax;
+  double wmax = 0.0;
+  for (int k = 0; k < R; ++k) wmax = fmax(wmax, fabs(a[k * R + k]));
+  for (int k = tid; k < R; k += T) {
+    const double w = a[k * R + k];
+    lds.inv[k] = fabs(w) <= 1e-15 * wmax ? 0.0 : 1.0 / w;   // (a NaN is not small)
   }
   __syncthreads();
-  const double wmax = red[0];
+  if constexpr (!kVectors) {
+    for (int e = tid; e < R * R; e += T) a[e] = q[e];
+    __syncthreads();
+    q = a;
+  }
+  // the terms of entry (i, j) from number i + j on: neighbouring threads then read different LDS banks, and (j, i) adds
+  // the same terms in the same order
   for (int e = tid; e < R * R; e += T) {
+    const int i = e / R, j = e % R;
     double t = 0.0;
-    for (int k = 0; k < R; ++k) {
-      const double w = a[k * R + k];
-      if (!(fabs(w) <= 1e-15 * wmax)) t += q[(e / R) * R + k] * (1.0 / w) * q[(e % R) * R + k];  // (a NaN is not small)
+    for (int m = 0; m < R; ++m) {
+      const int k = (i + j + m) & (R - 1);
+      if (lds.inv[k] != 0.0) t += q[i * R + k] * lds.inv[k] * q[j * R + k];
     }
     out[e] = t;
   }
   __syncthreads();
-}
-
-// 1 / x for a normal positive x: the hardware's estimate and two Newton steps (relative error near 2^-53).
-__device__ __forceinline__ double reciprocal(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(fma(-x, r, 1.0), r, r);
-  return fma(fma(-x, r, 1.0), r, r);
 }
 
 // vp = V^+ for the update of mode n, and p = diag(d) V^+ (the right-hand matrix of a put-off update; an ordinary update
@@ -634,14 +726,16 @@ __device__ __forceinline__ double reciprocal(double x) {
 // A pivot that is not safely positive sends the whole workgroup to the eigenvalue form.
 // resetScale: after the product the stored factor is the unnormalised one, so its column scale becomes 1.
 template <int R>
-__global__ __launch_bounds__(small_threads(R)) void small_pinv_kernel(SmallState st, int n, double* __restrict__ vp,
-                                                                      float* __restrict__ p, double* __restrict__ ja,
-                                                                      double* __restrict__ jq, int resetScale,
+__global__ __launch_bounds__(pinv_threads(R)) void small_pinv_kernel(SmallState st, int n, double* __restrict__ vp,
+                                                                      float* __restrict__ p, double* __restrict__ jq,
+                                                                      int resetScale,
                                                                       unsigned long long* __restrict__ stamp) {
-  constexpr int T = small_threads(R), W = R / 4;
+  constexpr int T = small_threads(R), U = pinv_threads(R), W = R / 4;
   __shared__ __align__(16) double rowOf[2][R + 2];   // row k, then entry (k + 1, k + 1)
-  __shared__ double diag[R], d[R], jl[R + 2], part[T];
+  __shared__ double diag[R], d[R];
   __shared__ double dmaxShared;
+  __shared__ int goodShared;
+  __shared__ JacobiLds<R> jl;
   const int tid = threadIdx.x;
   if (tid == 0 && stamp) stamp[0] = wall_clock64();
   const bool owns = tid < W * W;
@@ -671,7 +765,7 @@ __global__ __launch_bounds__(small_threads(R)) void small_pinv_kernel(SmallState
       for (int i = 0; i < 4; ++i) diag[i0 + i] = x[i][i];
     }
   }
-  for (int r = tid; r < R; r += T) d[r] = d_entry<R>(st, n, r);
+  for (int r = tid; r < R; r += U) d[r] = d_entry<R>(st, n, r);
   __syncthreads();
   if (tid < 64) {
     double m = 0.0;
@@ -683,7 +777,7 @@ __global__ __launch_bounds__(small_threads(R)) void small_pinv_kernel(SmallState
   const double least = 1e-10 * dmaxShared;
   double pivot = diag[0];
   bool good = true;
-  for (int kb = 0; kb < R && good; kb += 4) {
+  for (int kb = 0; kb < R && good && tid < T; kb += 4) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int k = kb + q;
@@ -696,7 +790,8 @@ __global__ __launch_bounds__(small_threads(R)) void small_pinv_kernel(SmallState
       if (q == 3 && owns && i0 == kb + 4 && j0 == kb + 4) row[R] = x[0][0];
       if (!(pivot > least)) good = false;   // the same for every thread
       const double inv = reciprocal(pivot);
-      __syncthreads();
+      if constexpr (T == 64) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // one wavefront sweeps
+      else __syncthreads();
       double ri[4], rj[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -718,6 +813,11 @@ __global__ __launch_bounds__(small_threads(R)) void small_pinv_kernel(SmallState
       }
     }
   }
+  if constexpr (U > T) {  // the other wavefronts have waited here
+    if (tid == 0) goodShared = good;
+    __syncthreads();
+    good = goodShared;
+  }
   if (good) {
     if (owns) {
 #pragma unroll
@@ -730,7 +830,7 @@ __global__ __launch_bounds__(small_threads(R)) void small_pinv_kernel(SmallState
     }
   } else {
     __syncthreads();
-    jacobi_pinv<R>(st, n, ja, jq, vp, jl, part);
+    jacobi_pinv<R>(st, n, jl, jq, vp);
     if (owns) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
@@ -745,7 +845,7 @@ __global__ __launch_bounds__(small_threads(R)) void small_pinv_kernel(SmallState
       for (int j = 0; j < 4; ++j) put_p<R>(p, i0 + i, j0 + j, (float)(d[i0 + i] * x[i][j]));
   }
   if (resetScale)
-    for (int r = tid; r < R; r += T) st.scale[n][r] = 1.0;
+    for (int r = tid; r < R; r += U) st.scale[n][r] = 1.0;
   if (tid == 0 && stamp) stamp[1] = wall_clock64();
 }
 
@@ -1163,8 +1263,8 @@ int enqueue_iteration(hbcsf_als* a, float* const* factors, float* lambda, int fl
     for (int m = 0; m < order; ++m) facs[m] = factors[m];
     with_rank(R, [&](auto r) {
       constexpr int RR = decltype(r)::value;
-      hipLaunchKernelGGL(small_pinv_kernel<RR>, dim3(1), dim3(small_threads(RR)), 0, st, a->small, n, a->vp, a->p,
-                         a->tmp[0], a->tmp[1], lazy ? 1 : 0, a->report->stamp[n]);
+      hipLaunchKernelGGL(small_pinv_kernel<RR>, dim3(1), dim3(pinv_threads(RR)), 0, st, a->small, n, a->vp, a->p,
+                         a->tmp[0], lazy ? 1 : 0, a->report->stamp[n]);
     });
     const int rc = hbcsf_mttkrp(t, n, R, facs, a->m, st);
     if (rc != HBCSF_OK) return rc;
