@@ -64,9 +64,10 @@ uint32_t round_up8(uint64_t v) { return (uint32_t)((v + 7) / 8 * 8); }
 // Nonzeros a lane group takes of a unit, as a power of two: at most a run, at least what keeps a unit (NG parts) a whole
 // number of runs.  Units of 256 nonzeros keep the most wavefronts resident (4 to 5 KB of LDS records each) and were the
 // fastest at every rank from 5 M nonzeros up (rank 8 on 42 M nonzeros 1.94 -> 1.10 ms against parts of whole runs, rank
-// 16 on 7.7 M 237 -> 204 us, rank 32 on 5 M 241 -> 217 us).  Smaller tensors take 128 below 16 units per compute unit
-// and 64 below 6: a wavefront walks its part one dependent block after the other, so with the chip not full the length
-// of that walk is the kernel's time (rank 32 on 80 000 nonzeros 67 -> 43 us, rank 8 on 10 000 60 -> 38 us, all modes).
+// 16 on 7.7 M 237 -> 204 us, rank 32 on 5 M 241 -> 217 us).  Smaller tensors take 128 where there would be fewer than 16
+// units of 256 per compute unit, and 64 below 3: a wavefront walks its part one dependent block after the other, so with
+// the chip not full the length of that walk is the kernel's time (rank 32 on 80 000 nonzeros 67 -> 43 us, rank 8 on
+// 10 000 60 -> 38 us, all modes).
 uint32_t part_shift(uint64_t nnz, int NG, uint32_t lshift, int numCU) {
   uint32_t lo = 3, s = 3;
   while (((uint32_t)NG << lo) < (1u << lshift)) ++lo;

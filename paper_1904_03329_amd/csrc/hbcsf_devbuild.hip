@@ -705,8 +705,8 @@ __global__ void totals_kernel(Numbers n, Spec sp, uint32_t tiles, uint32_t block
 }
 
 // Every nonzero writes itself into its group's stream; segment starts write the fiber-level entries.  A wavefront takes
-// kFill chunks of 64 nonzeros at a time and issues the loads of all of them first (keys, values; then slice tables), since each nonzero's chain key -> slice -> place is three loads long and the stores between them
-// may not be passed by a load.
+// kFill chunks of 64 nonzeros at a time and issues the loads of all of them first (keys, values; then slice tables), since
+// each nonzero's chain key -> slice -> place is three loads long and the stores between them may not be passed by a load.
 constexpr int kFill = 4;
 template <typename Key, int N>
 __global__ __launch_bounds__(256) void fill_tiles_kernel(const Key* __restrict__ K, const uint32_t* __restrict__ V, size_t M,
@@ -786,20 +786,20 @@ __global__ __launch_bounds__(256) void fill_tiles_kernel(const Key* __restrict__
         mark_row(sp, leaf, o.seen[kCsl][leaf], leafIdx[q]);
 #pragma unroll
         for (int l = 1; l < leaf; ++l) {
-            const uint32_t i = index(l);
-            o.cslInd[l][pos] = i;
-            mark_row(sp, l, o.seen[kCsl][l], i);
-          }
+          const uint32_t i = index(l);
+          o.cslInd[l][pos] = i;
+          mark_row(sp, l, o.seen[kCsl][l], i);
+        }
       } else {
         o.cooVal[pos] = v[q];
         o.cooInd[leaf][pos] = leafIdx[q];
         mark_row(sp, leaf, o.seen[kCoo][leaf], leafIdx[q]);
 #pragma unroll
         for (int l = 1; l < leaf; ++l) {
-            const uint32_t i = index(l);
-            o.cooInd[l][pos] = i;
-            mark_row(sp, l, o.seen[kCoo][l], i);
-          }
+          const uint32_t i = index(l);
+          o.cooInd[l][pos] = i;
+          mark_row(sp, l, o.seen[kCoo][l], i);
+        }
         const uint32_t root = index(0);
         if (!sp.cooRowFlags) o.cooInd[0][pos] = root;
         atomicOr(&o.cooBits[root >> 5], 1u << (root & 31));

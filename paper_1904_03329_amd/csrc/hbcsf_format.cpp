@@ -402,26 +402,26 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, Sorted<Key>& so,
   for (int f = 0; f < NF; ++f) segOff[f].assign(P + 1, 0);
 #pragma omp parallel for schedule(dynamic, 1) num_threads(nt)
   for (int part = 0; part < parts; ++part)
-  for (int64_t q = piece_at(part), qEnd = piece_at(part + 1); q < qEnd; ++q) {
-    const uint32_t s = piece[q].s;
-    if (grp[s] != kCsf && grp[s] != kSplit) continue;
-    const size_t b = piece[q].b, e = piece[q].e;
-    const bool split = grp[s] == kSplit;
-    uint32_t c[kFL] = {0, 0, 0};
-    uint32_t pos = off[s] + (uint32_t)(b - sStart[s]);
-    bool pend[kFL] = {false, false, false};
-    for (size_t p = b; p < e; ++p) {
-      for (int f = 0; f < NF; ++f) pend[f] = pend[f] || fresh(f + 1, p);
-      if (split && single(p, e)) continue;
-      const bool cut = (pos % L) == 0;
-      for (int f = 0; f < NF; ++f) {
-        c[f] += cut || pend[f];
-        pend[f] = false;
+    for (int64_t q = piece_at(part), qEnd = piece_at(part + 1); q < qEnd; ++q) {
+      const uint32_t s = piece[q].s;
+      if (grp[s] != kCsf && grp[s] != kSplit) continue;
+      const size_t b = piece[q].b, e = piece[q].e;
+      const bool split = grp[s] == kSplit;
+      uint32_t c[kFL] = {0, 0, 0};
+      uint32_t pos = off[s] + (uint32_t)(b - sStart[s]);
+      bool pend[kFL] = {false, false, false};
+      for (size_t p = b; p < e; ++p) {
+        for (int f = 0; f < NF; ++f) pend[f] = pend[f] || fresh(f + 1, p);
+        if (split && single(p, e)) continue;
+        const bool cut = (pos % L) == 0;
+        for (int f = 0; f < NF; ++f) {
+          c[f] += cut || pend[f];
+          pend[f] = false;
+        }
+        ++pos;
       }
-      ++pos;
+      for (int f = 0; f < NF; ++f) segOff[f][q + 1] = c[f];
     }
-    for (int f = 0; f < NF; ++f) segOff[f][q + 1] = c[f];
-  }
   for (int f = 0; f < NF; ++f) {
     uint64_t run = 0;
     for (uint64_t q = 0; q < P; ++q) {
@@ -472,75 +472,75 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, Sorted<Key>& so,
   uint64_t sharedSlices = 0;
 #pragma omp parallel for schedule(dynamic, 1) reduction(+ : sharedSlices) num_threads(nt)
   for (int part = 0; part < parts; ++part)
-  for (int64_t q = piece_at(part), qEnd = piece_at(part + 1); q < qEnd; ++q) {
-    const uint32_t s = piece[q].s;
-    const size_t b = piece[q].b, e = piece[q].e;
-    const size_t sb = sStart[s], se = sStart[s + 1];
-    const bool first = b == sb;  // the slice's own entries go with its first piece
-    const uint32_t root = idx(0, b);
-    const int g = grp[s];
-    bool own = true;
-    if (g == kCoo) {
-      const uint32_t a = off[s];
-      for (int l = out->cooRowFlags ? 1 : 0; l < N; ++l) cooInd[l][a] = idx(l, b);
-      cooVal[a] = V[b];
-      __atomic_fetch_or(&cooBits[root >> 5], 1u << (root & 31), __ATOMIC_RELAXED);
-    } else {
-      const bool split = g == kSplit;
-      // the CSL piece (a whole CSL slice, or the singleton-fiber nonzeros of a split slice)
-      if (g == kCsl || split) {
-        const uint32_t a = split ? offL[s] : off[s], o = split ? ordL[s] : ord[s];
-        const uint32_t n = split ? nSingle[s] : (uint32_t)(se - sb);
-        own = !split && bb == 0 && (a / L) == ((a + n - 1) / L);
-        if (first) {
-          for (uint32_t r = (a + L - 1) / L; r <= (a + n - 1) / L; ++r) cslRun[r] = o;
-          cslInd[0][o] = root | (own ? kOwnedBit : 0u);
-          cslPtr[o] = a;
-        }
-        uint32_t pos = a + (uint32_t)(b - sb);
-        for (size_t p = b; p < e; ++p) {
-          if (split && !single(p, e)) continue;
-          for (int l = 1; l < N; ++l) cslInd[l][pos] = idx(l, p);
-          cslVal[pos] = V[p];
-          ++pos;
-        }
-      }
-      // the CSF piece
-      if (g == kCsf || split) {
-        const uint32_t a = off[s], o = ord[s];
-        const uint32_t n = split ? (uint32_t)(se - sb) - nSingle[s] : (uint32_t)(se - sb);
-        own = !split && bb == 0 && (a / L) == ((a + n - 1) / L);
-        if (first) {
-          for (uint32_t r = (a + L - 1) / L; r <= (a + n - 1) / L; ++r) csfRun[0][r] = o;
-          csfInd[0][o] = root | (own ? kOwnedBit : 0u);
-          csfPtr[0][o] = a;
-        }
-        uint32_t f[kFL] = {0, 0, 0};
-        for (int k = 0; k < NF; ++k) f[k] = segOff[k][q];
-        uint32_t pos = a + (uint32_t)(b - sb);
-        bool pend[kFL] = {false, false, false};
-        for (size_t p = b; p < e; ++p) {
-          for (int k = 0; k < NF; ++k) pend[k] = pend[k] || fresh(k + 1, p);
-          if (split && single(p, e)) continue;
-          const bool cut = (pos % L) == 0;
-          for (int l = 1; l <= NF; ++l) {
-            if (cut || pend[l - 1]) {
-              csfInd[l][f[l - 1]] = idx(l, p);
-              csfPtr[l][f[l - 1]] = pos;
-              if (cut) csfRun[l][pos / L] = f[l - 1];
-              ++f[l - 1];
-            }
+    for (int64_t q = piece_at(part), qEnd = piece_at(part + 1); q < qEnd; ++q) {
+      const uint32_t s = piece[q].s;
+      const size_t b = piece[q].b, e = piece[q].e;
+      const size_t sb = sStart[s], se = sStart[s + 1];
+      const bool first = b == sb;  // the slice's own entries go with its first piece
+      const uint32_t root = idx(0, b);
+      const int g = grp[s];
+      bool own = true;
+      if (g == kCoo) {
+        const uint32_t a = off[s];
+        for (int l = out->cooRowFlags ? 1 : 0; l < N; ++l) cooInd[l][a] = idx(l, b);
+        cooVal[a] = V[b];
+        __atomic_fetch_or(&cooBits[root >> 5], 1u << (root & 31), __ATOMIC_RELAXED);
+      } else {
+        const bool split = g == kSplit;
+        // the CSL piece (a whole CSL slice, or the singleton-fiber nonzeros of a split slice)
+        if (g == kCsl || split) {
+          const uint32_t a = split ? offL[s] : off[s], o = split ? ordL[s] : ord[s];
+          const uint32_t n = split ? nSingle[s] : (uint32_t)(se - sb);
+          own = !split && bb == 0 && (a / L) == ((a + n - 1) / L);
+          if (first) {
+            for (uint32_t r = (a + L - 1) / L; r <= (a + n - 1) / L; ++r) cslRun[r] = o;
+            cslInd[0][o] = root | (own ? kOwnedBit : 0u);
+            cslPtr[o] = a;
           }
-          pend[0] = pend[1] = pend[2] = false;
-          csfInd[N - 1][pos] = idx(N - 1, p);
-          csfVal[pos] = V[p];
-          ++pos;
+          uint32_t pos = a + (uint32_t)(b - sb);
+          for (size_t p = b; p < e; ++p) {
+            if (split && !single(p, e)) continue;
+            for (int l = 1; l < N; ++l) cslInd[l][pos] = idx(l, p);
+            cslVal[pos] = V[p];
+            ++pos;
+          }
         }
+        // the CSF piece
+        if (g == kCsf || split) {
+          const uint32_t a = off[s], o = ord[s];
+          const uint32_t n = split ? (uint32_t)(se - sb) - nSingle[s] : (uint32_t)(se - sb);
+          own = !split && bb == 0 && (a / L) == ((a + n - 1) / L);
+          if (first) {
+            for (uint32_t r = (a + L - 1) / L; r <= (a + n - 1) / L; ++r) csfRun[0][r] = o;
+            csfInd[0][o] = root | (own ? kOwnedBit : 0u);
+            csfPtr[0][o] = a;
+          }
+          uint32_t f[kFL] = {0, 0, 0};
+          for (int k = 0; k < NF; ++k) f[k] = segOff[k][q];
+          uint32_t pos = a + (uint32_t)(b - sb);
+          bool pend[kFL] = {false, false, false};
+          for (size_t p = b; p < e; ++p) {
+            for (int k = 0; k < NF; ++k) pend[k] = pend[k] || fresh(k + 1, p);
+            if (split && single(p, e)) continue;
+            const bool cut = (pos % L) == 0;
+            for (int l = 1; l <= NF; ++l) {
+              if (cut || pend[l - 1]) {
+                csfInd[l][f[l - 1]] = idx(l, p);
+                csfPtr[l][f[l - 1]] = pos;
+                if (cut) csfRun[l][pos / L] = f[l - 1];
+                ++f[l - 1];
+              }
+            }
+            pend[0] = pend[1] = pend[2] = false;
+            csfInd[N - 1][pos] = idx(N - 1, p);
+            csfVal[pos] = V[p];
+            ++pos;
+          }
+        }
+        if (!own && first) ++sharedSlices;
       }
-      if (!own && first) ++sharedSlices;
+      if (own && first) __atomic_fetch_or(&owned[root >> 5], 1u << (root & 31), __ATOMIC_RELAXED);
     }
-    if (own && first) __atomic_fetch_or(&owned[root >> 5], 1u << (root & 31), __ATOMIC_RELAXED);
-  }
   {
     // COO-group nonzeros are stored in row order, so a running count over the bitmap locates them
     uint32_t* cooPtr = U32(out->cooPtr);
