@@ -106,9 +106,10 @@ KeyLayout key_layout(int N, const uint64_t* dims, const int* lv) {
 }
 
 // The nonzeros in the common order, and two buffer pairs in which one mode after the other is sorted: 12 bytes (20 with
-// wide keys) a nonzero and pair.  The last mode sorts in the common order's own buffers and gives back what its sort did
-// not end in before its arrays are made; so does every mode of a large tensor.  20 M nonzeros, order 3: a peak of 42
-// bytes a nonzero with the format's 36, against 64 with all pairs kept to the end.
+// wide keys) a nonzero and pair.  The mode that is sorted already comes first; the last one sorts in the common order's own
+// buffers, so that of a large tensor the last mode but one and the last can give back what their sort did not end in before
+// their arrays are made, and none gives back pages that a later mode asks for again.  Peak of a build, 20 M nonzeros of order
+// 3 / 10 M of order 4: 51 / 73 bytes a nonzero (75 / 97 with all pairs kept to the end, in the same time).
 template <typename Key>
 struct Sorted {
   std::unique_ptr<Key[]> key[3];
@@ -173,10 +174,11 @@ int sort_common(int N, const uint64_t* dims, size_t M, const uint32_t* const* in
   return HBCSF_OK;
 }
 
-// One mode's representation from the common order, which the last mode may overwrite.
+// One mode's representation from the common order, which the last mode may overwrite.  left: modes still to come.
 template <typename Key>
 int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, Sorted<Key>& so, const hbcsf_opts& opts, int mode,
-                 bool last, ModeFormat* out, std::string* err) {
+                 int left, ModeFormat* out, std::string* err) {
+  const bool last = left == 0;
   const auto t_begin = std::chrono::steady_clock::now();
   const int N = order;
   const uint32_t L = opts.fiber_threshold ? opts.fiber_threshold : 64;
@@ -235,9 +237,9 @@ int build_mode_t(int order, const uint64_t* dims, uint64_t nnz, Sorted<Key>& so,
     }
     radix_sort_pairs<Key>(K, V, K2, V2, M, shift[0], kl.total - shift[0] + bb);
   }
-  // (a pair the next mode needs again is given back only where the allocator maps it by itself, from 32 MB on: a smaller
-  // one stays with the process either way)
-  if (last || (!sorted && M * sizeof(Key) >= ((size_t)32 << 20)))
+  // Buffers are given back only where the allocator maps each by itself, from 32 MB on: smaller ones stay with the process
+  // either way, and freed before the arrays are made they leave the top of its heap, which is then cut and faulted in again.
+  if ((last || (left == 1 && !sorted)) && M * sizeof(Key) >= ((size_t)32 << 20))
     for (int i = 0; i < 3; ++i)
       if (so.key[i].get() != K && (last || so.key[i].get() != so.K)) so.release(i);
 
@@ -618,8 +620,9 @@ int build_modes_t(int order, const uint64_t* dims, uint64_t nnz, const uint32_t*
   int rc = sort_common<Key>(order, dims, (size_t)nnz, inds, vals, key_layout(order, dims, lv), &so, err);
   // the sort every mode's order is taken from is part of each mode's time
   const double share = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_begin).count() / modes;
-  for (int m = 0; rc == HBCSF_OK && m < modes; ++m) {
-    rc = build_mode_t<Key>(order, dims, nnz, so, opts, m, m + 1 == modes, out[m], err);
+  for (int k = 0; rc == HBCSF_OK && k < modes; ++k) {
+    const int m = modes == 1 || k > lv[0] ? k : k == 0 ? lv[0] : k - 1;  // the common order's own mode, then the others
+    rc = build_mode_t<Key>(order, dims, nnz, so, opts, m, modes - 1 - k, out[m], err);
     out[m]->stats.build_seconds += share;
   }
   return rc;
