@@ -188,6 +188,23 @@ __device__ __forceinline__ void block_dot(double v, double* __restrict__ dots) {
   }
 }
 
+// 32 rows of 32 floats that a wavefront turns from the row layout of its loads into the layout of a product tile: row stride
+// 36, so that whole float4s are written.  The `count` float4s x[first ..] of row c from column `from` on; then the sum of the
+// products with acc.
+constexpr int kTurnStride = 36;
+template <int first, int count, int n>
+__device__ __forceinline__ void put_rows(float* turned, int c, int from, const float4 (&x)[n]) {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+  for (int q = 0; q < count; ++q) *reinterpret_cast<float4*>(turned + c * kTurnStride + from + 4 * q) = x[first + q];
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+__device__ __forceinline__ void add_dot(const float* turned, int h, int c, const f32x16& acc, double& dot) {
+#pragma unroll
+  for (int v = 0; v < 16; ++v)
+    dot = fma((double)turned[(8 * (v / 4) + 4 * h + (v % 4)) * kTurnStride + c], (double)acc[v], dot);
+}
+
 // R <= 32: out = M P for blocks of 32 rows of 32 floats (R < 32: P is the block-diagonal matrix of 32 / R copies).  The
 // contraction index is split as k = 16 h + t so that lane (h, c) reads the 64 contiguous bytes M[row c of the
 // block][16 h .. 16 h + 15] as its sixteen left operands, and holds P[16 h + t][c] as the sixteen right operands for
@@ -197,10 +214,12 @@ __device__ __forceinline__ void block_dot(double v, double* __restrict__ dots) {
 // rows of the tile with lane c on column c -- exactly the operand shape of gram32_partial_kernel -- so sixteen more
 // matrix instructions add the tile's out^T out without moving any data.  The partial Gram sums go to the block's
 // scratch slot (reduced by gram_reduce_kernel), so M is read once per mode update instead of twice.
-// dots (may be null): per block the sum of M[i][r] out[i][r] over its entries, i.e. <X, model> of these factors once the
-// blocks' sums are added.  M's entries come a second time, in the product tile's layout, from lines just read.
-template <int R, bool GRAM>
-__global__ __launch_bounds__(256) void apply32_kernel(const float* __restrict__ m, uint64_t rows, uint64_t total,
+// DOTS (with GRAM): dots receives per block the sum of M[i][r] out[i][r] over its entries, i.e. <X, model> of these factors
+// once the blocks' sums are added.  M's entries reach the product tile's layout through LDS, in what the end of the kernel
+// sums in (five iterations whose last mode has 5 M rows of 32: 4.81 ms with M loaded a second time, 3.30 this way, 3.40
+// without the sum in the code before it); an instantiation of its own, since only an iteration's last mode asks for it.
+template <int R, bool GRAM, bool DOTS>
+__global__ __launch_bounds__(256, DOTS ? 3 : 1) void apply32_kernel(const float* __restrict__ m, uint64_t rows, uint64_t total,
                                                       const float* __restrict__ p, float* __restrict__ out,
                                                       uint64_t blocksPerWave, double* __restrict__ partial,
                                                       double* __restrict__ dots,
@@ -210,6 +229,8 @@ __global__ __launch_bounds__(256) void apply32_kernel(const float* __restrict__ 
   const int wave = threadIdx.x >> 6;
   const int h = lane >> 5, c = lane & 31;
   double dot = 0.0;
+  __shared__ double red[GRAM ? 4 : 1][1024];
+  float* turned = reinterpret_cast<float*>(red[GRAM ? wave : 0]);   // DOTS: a wavefront's 32 rows of M
   float pb[16];
 #pragma unroll
   for (int t = 0; t < 16; ++t) pb[t] = p[(16 * h + t) * 32 + c];
@@ -240,6 +261,7 @@ __global__ __launch_bounds__(256) void apply32_kernel(const float* __restrict__ 
 #pragma unroll
       for (int q = 0; q < 4; ++q) x[q] = next[q];
       if (b + 1 < bEnd) load(next, b + 1);
+      if constexpr (DOTS) put_rows<0, 4>(turned, c, 16 * h, x);
       f32x16 acc;
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[v] = 0.f;
@@ -255,13 +277,7 @@ __global__ __launch_bounds__(256) void apply32_kernel(const float* __restrict__ 
         const uint64_t to = (b * 32 + (uint64_t)(8 * (v / 4) + 4 * h + (v % 4))) * 32 + c;
         if (to < total) __builtin_nontemporal_store(acc[v], out + to);
       }
-      if (GRAM && dots) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const uint64_t at = (b * 32 + (uint64_t)(8 * (v / 4) + 4 * h + (v % 4))) * 32 + c;
-          if (at < total) dot = fma((double)m[at], (double)acc[v], dot);
-        }
-      }
+      if constexpr (DOTS) add_dot(turned, h, c, acc, dot);  // (a row past the end is zero)
       if (GRAM) {
         // rows past the end of the matrix were computed from zeros and add nothing
 #pragma unroll
@@ -274,19 +290,20 @@ __global__ __launch_bounds__(256) void apply32_kernel(const float* __restrict__ 
     }
   }
   if constexpr (GRAM) {
-    __shared__ double red[4][1024];
+    if constexpr (DOTS) __syncthreads();
 #pragma unroll
     for (int v = 0; v < 16; ++v) red[wave][(8 * (v / 4) + 4 * h + (v % 4)) * 32 + c] = acc64[v];
     __syncthreads();
     write_slot32<R>(red, partial + (size_t)blockIdx.x * (R * R));
-    if (dots) block_dot<4>(dot, dots);
+    if constexpr (DOTS) block_dot<4>(dot, dots);
   }
 }
 
 // R = 64, 128: out = M P; a wavefront takes 32 rows x 32 columns (tile column q = wavefront of the block), the block's
 // wavefronts share the rows.  The contraction index is split as k = (R / 2) h + t, so a lane reads 2 R contiguous bytes
-// of its row and keeps its R / 2 right operands for the whole kernel.  dots: as in apply32_kernel.
-template <int R>
+// of its row and keeps its R / 2 right operands for the whole kernel.  DOTS: as in apply32_kernel; the 32 columns of a
+// wavefront's tile are in the registers of one half of its lanes.
+template <int R, bool DOTS>
 __global__ __launch_bounds__(2 * R) void apply_tiles_kernel(const float* __restrict__ m, uint64_t rows,
                                                             const float* __restrict__ p, float* __restrict__ out,
                                                             uint64_t rowBlocksPerBlock, double* __restrict__ dots,
@@ -297,6 +314,7 @@ __global__ __launch_bounds__(2 * R) void apply_tiles_kernel(const float* __restr
   const int q = threadIdx.x >> 6;
   const int h = lane >> 5, c = lane & 31;
   double dot = 0.0;
+  __shared__ __align__(16) float turned[DOTS ? R / 32 : 1][32 * kTurnStride];
   float pb[K];
 #pragma unroll
   for (int t = 0; t < K; ++t) pb[t] = p[(K * h + t) * R + 32 * q + c];
@@ -328,15 +346,16 @@ __global__ __launch_bounds__(2 * R) void apply_tiles_kernel(const float* __restr
       const uint64_t ro = b * 32 + (uint64_t)(8 * (v / 4) + 4 * h + (v % 4));
       if (ro < rows) __builtin_nontemporal_store(acc[v], out + ro * R + 32 * q + c);
     }
-    if (dots) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const uint64_t ro = b * 32 + (uint64_t)(8 * (v / 4) + 4 * h + (v % 4));
-        if (ro < rows) dot = fma((double)m[ro * R + 32 * q + c], (double)acc[v], dot);
+    if constexpr (DOTS) {
+      if (h == 32 * q / K) {
+        if (K == 64 && (q & 1)) put_rows<K == 64 ? 8 : 0, 8>(turned[q], c, 0, x);
+        else put_rows<0, 8>(turned[q], c, 0, x);
       }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      add_dot(turned[q], h, c, acc, dot);
     }
   }
-  if (dots) block_dot<R / 32>(dot, dots);
+  if constexpr (DOTS) block_dot<R / 32>(dot, dots);
 }
 
 // a[i][r] *= s[r]: the column normalisation of Algorithm "CPD-ALS" when it was put off.
@@ -410,10 +429,8 @@ void launch_gram(const float* a, uint64_t rows, int rank, double* scratch, uint3
 template <int R>
 void launch_apply32(const float* m, uint64_t n, uint64_t total, const float* p, float* out, uint64_t per, uint32_t blocks,
                     double* scratch, double* dots, unsigned long long* stamp, hipStream_t st) {
-  if (scratch)
-    hipLaunchKernelGGL((apply32_kernel<R, true>), dim3(blocks), dim3(256), 0, st, m, n, total, p, out, per, scratch, dots, stamp);
-  else
-    hipLaunchKernelGGL((apply32_kernel<R, false>), dim3(blocks), dim3(256), 0, st, m, n, total, p, out, per, scratch, dots, stamp);
+  auto kernel = !scratch ? apply32_kernel<R, false, false> : dots ? apply32_kernel<R, true, true> : apply32_kernel<R, true, false>;
+  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, st, m, n, total, p, out, per, scratch, dots, stamp);
 }
 
 // out = m p, and with g: g (device, [R][R] fp64) = out^T out (in the same pass over m for R <= 32).  p: [R][R], for
@@ -430,9 +447,11 @@ uint32_t launch_apply(const float* m, uint64_t rows, int rank, const float* p, f
       const uint64_t per = (nBlocks + blocks - 1) / blocks;
       used = (uint32_t)((nBlocks + per - 1) / per);
       if (rank == 64)
-        hipLaunchKernelGGL(apply_tiles_kernel<64>, dim3(used), dim3(128), 0, st, m, rows, p, out, per, dots, stamp);
+        hipLaunchKernelGGL((dots ? apply_tiles_kernel<64, true> : apply_tiles_kernel<64, false>), dim3(used), dim3(128), 0, st,
+                           m, rows, p, out, per, dots, stamp);
       else
-        hipLaunchKernelGGL(apply_tiles_kernel<128>, dim3(used), dim3(256), 0, st, m, rows, p, out, per, dots, stamp);
+        hipLaunchKernelGGL((dots ? apply_tiles_kernel<128, true> : apply_tiles_kernel<128, false>), dim3(used), dim3(256), 0, st,
+                           m, rows, p, out, per, dots, stamp);
     }
     if (g) launch_gram(out, rows, rank, scratch, slots, g, numCU, st);
     return used;
