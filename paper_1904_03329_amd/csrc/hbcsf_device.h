@@ -17,13 +17,13 @@ inline bool dense_mid_available(int order, int G, uint32_t lshift) {
 }
 
 // LDS words a wavefront of the B-CSF / CSL kernel uses: one record per nonzero of a unit (64 / G parts of 2^ss nonzeros,
-// one pad record per part), one row slot per lane (the first finished slice of each part), and for the order-4 B-CSF
-// kernel the list of the unit's slices with each part's place in it.
+// one pad record per part), one row slot per lane (the first finished slice of each part; not in the dense variant), and
+// for the order-4 B-CSF kernel the list of the unit's slices with each part's place in it.
 constexpr uint32_t csf_wave_words(int order, int G, int ss, bool dense) {
   const uint32_t parts = 64u / (uint32_t)G, slots = parts << ss;
   const bool pack = order == 4 && !dense;
-  return (slots + parts) * (order == 3 || pack ? 4u : 8u) + 256u + (pack ? slots + (parts < 4u ? 4u : parts) : 0u) +
-         (dense ? 64u + (uint32_t)kDenseCacheRows * 4u * (uint32_t)G : 0u);
+  return (slots + parts) * (order == 3 || pack ? 4u : 8u) + (pack ? slots + (parts < 4u ? 4u : parts) : 0u) +
+         (dense ? 64u + (uint32_t)kDenseCacheRows * 4u * (uint32_t)G : 256u);
 }
 constexpr uint32_t csl_wave_words(int order, int G, int ss) {
   const uint32_t parts = 64u / (uint32_t)G, slots = parts << ss;

@@ -259,12 +259,12 @@ __device__ __forceinline__ void emit_row(float* __restrict__ out, uint32_t mark,
 
 // Closes a unit in which some slice ends.  The lane groups' parts are consecutive, so a slice that began before a
 // lane group's part continues from the parts before it: `acc` is what a lane group holds of the slice still open at the
-// end of its part, `headMark` / `head` the first slice that ended in it (mark 0: none did).  A segmented sum over the
+// end of its part, `headMark` / `head` the first slice that ended in it (mark 0: none did, zeros).  A segmented sum over the
 // lane groups (a part with an end starts a new segment) gives every part what the open slice had collected before it;
 // the heads go out with that added, and what is still open after the last part stays in lane group 0's accumulator.
 template <int G>
-__device__ __forceinline__ void close_unit(float* __restrict__ out, const rowvec* __restrict__ head, uint32_t headMark,
-                                           rowvec& acc, int lane, int g, int c) {
+__device__ __forceinline__ void close_unit(float* __restrict__ out, const rowvec& head, uint32_t headMark, rowvec& acc,
+                                           int lane, int g, int c) {
   rowvec t = acc;
   uint32_t ended = headMark ? 1u : 0u;
 #pragma unroll
@@ -277,9 +277,8 @@ __device__ __forceinline__ void close_unit(float* __restrict__ out, const rowvec
     }
   }
   const rowvec before = shfl_up_row(t, G);
-  rowvec h = rv_zero();
+  rowvec h = head;
   if (headMark) {
-    h = head[lane];
     if (g > 0) add_row(h, before);
     if (headMark & kOwned) row_store<G>(out, (headMark & 0x7fffffffu) - 1u, c, h);
   }
@@ -687,11 +686,12 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
   constexpr uint32_t SUB = 1u << SS;
   constexpr uint32_t recWords = NG * (SUB + 1) * RW;
   uint32_t* rec = lds + (size_t)wib * csf_wave_words(N, G, SS, DENSE);
-  rowvec* head = reinterpret_cast<rowvec*>(rec + recWords);          // first finished slice of each part
+  // first finished slice of each part (the dense variant holds it in registers: its row cache already fills the LDS)
+  rowvec* head = reinterpret_cast<rowvec*>(rec + recWords);
   uint32_t* side = rec + recWords + 256;                             // PACK: marks of the slices that end in the unit,
   uint32_t* sideFirst = side + NG * SUB;                             //       and where each part's begin
-  uint32_t* list = rec + recWords + 256;                             // DENSE: row numbers by slot
-  rowvec* cache = reinterpret_cast<rowvec*>(rec + recWords + 256 + 64);  // DENSE: rows by slot, G rowvec each
+  uint32_t* list = rec + recWords;                                   // DENSE: row numbers by slot
+  rowvec* cache = reinterpret_cast<rowvec*>(rec + recWords + 64);    // DENSE: rows by slot, G rowvec each
 
   const float* __restrict__ facLeaf = a.fac[N - 1];
   const float* __restrict__ facDeep = a.fac[N - 2];   // deepest fiber level
@@ -735,13 +735,15 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
       if (g > 0) acc = rv_zero();
     }
     spread = !ends.ends;
+    rowvec held = rv_zero();         // DENSE: that slice
     // a slice ends here: the first one of a part waits for the parts before it, the others are complete
     auto slice_end = [&](uint32_t mark) {
       if (headMark) {
         emit_row<G>(a.out, mark, c, acc);
       } else {
         headMark = mark;
-        head[lane] = acc;
+        if constexpr (DENSE) held = acc;
+        else head[lane] = acc;
       }
       acc = rv_zero();
     };
@@ -931,7 +933,11 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
       }
       }  // classic / dense
     }
-    if (ends.ends) close_unit<G>(a.out, head, headMark, acc, lane, g, c);
+    if (ends.ends) {
+      if constexpr (!DENSE)
+        if (headMark) held = head[lane];
+      close_unit<G>(a.out, held, headMark, acc, lane, g, c);
+    }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
   close_span<G>(a.out, open, openRow, acc, lane);
@@ -1172,7 +1178,7 @@ __device__ __forceinline__ void csl_group_body(const GroupArgs& a, uint32_t bloc
         }
       }
     }
-    if (ends.ends) close_unit<G>(a.out, head, headMark, acc, lane, g, c);
+    if (ends.ends) close_unit<G>(a.out, headMark ? head[lane] : rv_zero(), headMark, acc, lane, g, c);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
   close_span<G>(a.out, open, openRow, acc, lane);
