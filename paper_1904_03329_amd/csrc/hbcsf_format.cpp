@@ -41,7 +41,10 @@ void radix_sort_pairs(Key*& k, uint32_t*& v, Key*& k2, uint32_t*& v2, size_t n, 
   const int digit = (totalBits + passes - 1) / passes;
   const size_t buckets = (size_t)1 << digit;
   const int nt = chunks_for(n);
-  std::vector<size_t> hist((size_t)nt * buckets);
+  // (a chunk's counts begin two lines past a whole power of two: the pass over one bucket of all chunks would otherwise
+  // go through a single cache set, and each of its loads wait for the store before it, whose address ends in the same bits)
+  const size_t row = buckets + 16;
+  std::vector<size_t> hist((size_t)nt * row);
   for (int pass = 0; pass < passes; ++pass) {
     const int shift = fromBit + pass * digit;
     std::fill(hist.begin(), hist.end(), 0);
@@ -56,7 +59,7 @@ void radix_sort_pairs(Key*& k, uint32_t*& v, Key*& k2, uint32_t*& v2, size_t n, 
 #pragma omp for schedule(static, 1)
       for (int c = 0; c < nt; ++c) {
         const size_t lo = n * (size_t)c / nt, hi = n * (size_t)(c + 1) / nt;
-        size_t* h = &hist[(size_t)c * buckets];
+        size_t* h = &hist[(size_t)c * row];
         for (size_t i = lo; i < hi; ++i) ++h[(size_t)(src[i] >> shift) & (buckets - 1)];
       }
 #pragma omp single
@@ -64,15 +67,15 @@ void radix_sort_pairs(Key*& k, uint32_t*& v, Key*& k2, uint32_t*& v2, size_t n, 
         size_t run = 0;
         for (size_t d = 0; d < buckets; ++d)
           for (int tt = 0; tt < nt; ++tt) {
-            const size_t c = hist[(size_t)tt * buckets + d];
-            hist[(size_t)tt * buckets + d] = run;
+            const size_t c = hist[(size_t)tt * row + d];
+            hist[(size_t)tt * row + d] = run;
             run += c;
           }
       }
 #pragma omp for schedule(static, 1)
       for (int c = 0; c < nt; ++c) {
         const size_t lo = n * (size_t)c / nt, hi = n * (size_t)(c + 1) / nt;
-        size_t* h = &hist[(size_t)c * buckets];
+        size_t* h = &hist[(size_t)c * row];
         for (size_t i = lo; i < hi; ++i) {
           const size_t at = h[(size_t)(src[i] >> shift) & (buckets - 1)]++;
           dst[at] = src[i];
