@@ -16,18 +16,17 @@ inline bool dense_mid_available(int order, int G, uint32_t lshift) {
   return G == 8 && (order == 3 || order == 4) && (lshift == 5 || lshift == 6);
 }
 
-// LDS words a wavefront of the B-CSF / CSL kernel uses: one record per nonzero of a unit (64 / G parts of 2^ss nonzeros,
-// one pad record per part), one row slot per lane (the first finished slice of each part; not in the dense variant), and
-// for the order-4 B-CSF kernel the list of the unit's slices with each part's place in it.
+// LDS words a wavefront of the B-CSF / CSL kernel uses: an array of one word per nonzero of a unit (64 / G parts of 2^ss
+// nonzeros) for each of the things it stages, one row slot per lane (the first finished slice of each part), and for the
+// B-CSF kernel the list of the unit's slices with each part's place in it.  The dense variant: one record per nonzero,
+// one pad record per part, its row numbers and row cache.
 constexpr uint32_t csf_wave_words(int order, int G, int ss, bool dense) {
   const uint32_t parts = 64u / (uint32_t)G, slots = parts << ss;
-  const bool pack = order == 4 && !dense;
-  return (slots + parts) * (order == 3 || pack ? 4u : 8u) + (pack ? slots + (parts < 4u ? 4u : parts) : 0u) +
-         (dense ? 64u + (uint32_t)kDenseCacheRows * 4u * (uint32_t)G : 256u);
+  if (dense) return (slots + parts) * (order == 3 ? 4u : 8u) + 64u + (uint32_t)kDenseCacheRows * 4u * (uint32_t)G;
+  return slots * (uint32_t)(order + 1) + (parts < 4u ? 4u : parts) + 256u;
 }
 constexpr uint32_t csl_wave_words(int order, int G, int ss) {
-  const uint32_t parts = 64u / (uint32_t)G, slots = parts << ss;
-  return (slots + parts) * (order == 3 ? 4u : 8u) + 256u;
+  return ((64u / (uint32_t)G) << ss) * (uint32_t)(order + 1) + 256u;
 }
 
 // Device pointers of one slice group of one mode, by tree level (0 = root .. order-1 = leaf).

@@ -87,8 +87,8 @@ __device__ __forceinline__ rowvec row_load_streaming(const float* __restrict__ b
   return from_vec16(__builtin_nontemporal_load(p));
 }
 
-// A fiber level's row by its mark (index + 1): `before` = row_before(the factor matrix), so that the mark scales to an
-// offset as it is.  Streaming loads exist in the WIDE form only (the caller chooses it when it asks for them): a
+// A fiber level's row by its mark (index + 1, perhaps with bit 31 set, which the 32-bit offset drops by itself): `before`
+// = row_before(the factor matrix), so that the mark scales to an offset as it is.  Streaming loads exist in the WIDE form only (the caller chooses it when it asks for them): a
 // second load instruction per step costs the common form a branch each.
 template <int G>
 __device__ __forceinline__ const float* row_before(const float* fac) {
@@ -97,6 +97,7 @@ __device__ __forceinline__ const float* row_before(const float* fac) {
 
 template <int G, bool WIDE>
 __device__ __forceinline__ rowvec marked_row_load(const float* before, uint32_t mark, int c, bool streaming) {
+  if (WIDE) mark &= 0x7fffffffu;
   if (WIDE && streaming) return row_load_streaming<G, WIDE>(before, mark, c);
   return row_load<G, WIDE>(before, mark, c);
 }
@@ -370,7 +371,7 @@ struct UnitEnds {
   bool open;        // END marks: that slice began before the next unit (wave-uniform)
   bool ends;        // END marks: some slice ends in this unit (wave-uniform)
   uint32_t ng;      // nonzeros in this lane group's part (0 beyond the end of the stream)
-  uint32_t sideAt;  // PACK: where the slices that end in this lane group's part start in the unit's slice list
+  uint32_t sideAt;  // B-CSF: where the slices that end in this lane group's part start in the unit's slice list
 };
 
 // fLo: first segment of this unit per fiber level (wave-uniform; = previous unit's fHi).
@@ -378,49 +379,34 @@ struct UnitEnds {
 // START = true : start marks (index + 1 at the FIRST nonzero), for the kernel that needs a level's index while
 //                its segment is still open; a slice that began before the unit has no mark in it (the row tells).
 //                Parts are runs here (SS = a.lshift).
-// PACK (B-CSF, order 4, end marks): 16-byte records {leaf, value, level-2 mark, level-1 mark | slice-end flag in bit
-//                31} instead of 32-byte ones; the marks of slices go to `side`, one word per slice that ends in the
-//                unit, in slice order (NG << SS words), and `sideFirst` (NG words) says where each part's begin.
-template <int G, int N, int SS, bool CSF, bool START = false, bool PACK = false>
+template <int G, int N, int SS, bool START = false>
 __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __restrict__ rec, uint32_t u,
-                                               const UnitBounds& b, const uint32_t (&fLo)[3], int lane,
-                                               uint32_t* __restrict__ side = nullptr,
-                                               uint32_t* __restrict__ sideFirst = nullptr) {
-  static_assert(!PACK || (CSF && N == 4 && !START), "packed records: the order-4 B-CSF kernel");
+                                               const UnitBounds& b, const uint32_t (&fLo)[3], int lane) {
   constexpr int NG = 64 / G;
   constexpr int NF = N - 2;
-  constexpr int RW = (N == 3 || PACK) ? 4 : 8;
+  constexpr int RW = N == 3 ? 4 : 8;
   constexpr int KV = 8;  // stream loads per lane issued together (covers 512 nonzeros)
   constexpr int KF = 4;  // segment loads per lane and level issued together (256 segments)
   constexpr int KS = 2;  // slice loads per lane issued together (128 slices)
-  constexpr int markWord = (N == 3) ? 3 : N;  // slice mark: after the N-2 segment marks (B-CSF) / the value (CSL)
+  constexpr int markWord = (N == 3) ? 3 : N;  // slice mark: after the N-2 segment marks
   constexpr uint32_t ss = SS, SUB = 1u << SS;
   constexpr uint32_t slots = (uint32_t)NG << SS;
   const uint32_t z0 = u * slots;
   const int g = lane / G;
   // parts shorter than runs (of at most 64 nonzeros): segments are cut at part ends too
-  const bool cutSegments = CSF && !START && SS < 6 && ss < a.lshift;
+  const bool cutSegments = !START && SS < 6 && ss < a.lshift;
   const uint32_t* __restrict__ valb = reinterpret_cast<const uint32_t*>(a.val);
 
   // -- issue: stream data
-  // B-CSF: w0 = leaf index, w1 = value.  CSL: w0..w(N-2) = the N-1 non-root indices, w(N-1) = value.
-  uint32_t w0[KV], w1[KV], w2[KV], w3[KV], w4[KV];
+  uint32_t w0[KV], w1[KV];   // leaf index, value
   if (z0 + slots <= a.nnz) {  // wave-uniform: every slot of the unit holds a nonzero
 #pragma unroll
     for (int t = 0; t < KV; ++t) {
       const uint32_t p = (uint32_t)t * 64u + lane;
-      w0[t] = w1[t] = w2[t] = w3[t] = w4[t] = 0;
+      w0[t] = w1[t] = 0;
       if ((uint32_t)t * 64u < slots && (slots >= 64u || p < slots)) {
-        if (CSF) {
-          w0[t] = __builtin_nontemporal_load(a.ind[N - 1] + z0 + p);
-          w1[t] = __builtin_nontemporal_load(valb + z0 + p);
-        } else {
-          w0[t] = __builtin_nontemporal_load(a.ind[1] + z0 + p);
-          w1[t] = __builtin_nontemporal_load(a.ind[2] + z0 + p);
-          if (N >= 4) w2[t] = __builtin_nontemporal_load(a.ind[3] + z0 + p);
-          if (N >= 5) w3[t] = __builtin_nontemporal_load(a.ind[4] + z0 + p);
-          (N == 3 ? w2[t] : N == 4 ? w3[t] : w4[t]) = __builtin_nontemporal_load(valb + z0 + p);
-        }
+        w0[t] = __builtin_nontemporal_load(a.ind[N - 1] + z0 + p);
+        w1[t] = __builtin_nontemporal_load(valb + z0 + p);
       }
     }
   } else {
@@ -428,37 +414,27 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
     for (int t = 0; t < KV; ++t) {
       const uint32_t p = (uint32_t)t * 64u + lane;
       const uint32_t z = z0 + p;
-      w0[t] = w1[t] = w2[t] = w3[t] = w4[t] = 0;
+      w0[t] = w1[t] = 0;
       if (p < slots && z < a.nnz) {
-        if (CSF) {
-          w0[t] = __builtin_nontemporal_load(a.ind[N - 1] + z);
-          w1[t] = __builtin_nontemporal_load(valb + z);
-        } else {
-          w0[t] = __builtin_nontemporal_load(a.ind[1] + z);
-          w1[t] = __builtin_nontemporal_load(a.ind[2] + z);
-          if (N >= 4) w2[t] = __builtin_nontemporal_load(a.ind[3] + z);
-          if (N >= 5) w3[t] = __builtin_nontemporal_load(a.ind[4] + z);
-          (N == 3 ? w2[t] : N == 4 ? w3[t] : w4[t]) = __builtin_nontemporal_load(valb + z);
-        }
+        w0[t] = __builtin_nontemporal_load(a.ind[N - 1] + z);
+        w1[t] = __builtin_nontemporal_load(valb + z);
       }
     }
   }
   // -- issue: fiber-segment ends and indices
   uint32_t fe[3][KF], fi[3][KF], fs[3][KF];
-  if (CSF) {
 #pragma unroll
-    for (int l = 1; l <= NF; ++l) {
+  for (int l = 1; l <= NF; ++l) {
 #pragma unroll
-      for (int t = 0; t < KF; ++t) {
-        const uint32_t f = fLo[l - 1] + (uint32_t)t * 64u + lane;
-        fe[l - 1][t] = 0;
-        fi[l - 1][t] = 0;
-        fs[l - 1][t] = 0;
-        if (f < b.fHi[l - 1]) {
-          fe[l - 1][t] = __builtin_nontemporal_load(a.ptr[l] + f + (START ? 0 : 1));
-          fi[l - 1][t] = __builtin_nontemporal_load(a.ind[l] + f);
-          if (cutSegments) fs[l - 1][t] = __builtin_nontemporal_load(a.ptr[l] + f);
-        }
+    for (int t = 0; t < KF; ++t) {
+      const uint32_t f = fLo[l - 1] + (uint32_t)t * 64u + lane;
+      fe[l - 1][t] = 0;
+      fi[l - 1][t] = 0;
+      fs[l - 1][t] = 0;
+      if (f < b.fHi[l - 1]) {
+        fe[l - 1][t] = __builtin_nontemporal_load(a.ptr[l] + f + (START ? 0 : 1));
+        fi[l - 1][t] = __builtin_nontemporal_load(a.ind[l] + f);
+        if (cutSegments) fs[l - 1][t] = __builtin_nontemporal_load(a.ptr[l] + f);
       }
     }
   }
@@ -475,17 +451,15 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
     rowRaw = a.ind[0][sNext];
     nextStart = a.ptr[0][sNext];
   }
-  uint32_t se[KS], si[KS], sb[KS];
+  uint32_t se[KS], si[KS];
 #pragma unroll
   for (int t = 0; t < KS; ++t) {
     const uint32_t sl = s0 + (uint32_t)t * 64u + lane;
     se[t] = 0;
     si[t] = 0;
-    sb[t] = 0;
     if (sl < s1) {
       se[t] = a.ptr[0][sl + (START ? 0 : 1)];
       si[t] = a.ind[0][sl];
-      if (PACK) sb[t] = a.ptr[0][sl];
     }
   }
 
@@ -495,96 +469,49 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
     const uint32_t p = (uint32_t)t * 64u + lane;
     if (p < slots) {
       uint4* dst = reinterpret_cast<uint4*>(rec + (size_t)(p + (p >> ss)) * RW);
-      if (CSF) {
-        dst[0] = make_uint4(w0[t], w1[t], 0u, 0u);
-        if (N >= 4 && !PACK) dst[1] = make_uint4(0u, 0u, 0u, 0u);
-      } else if (N == 3) {
-        dst[0] = make_uint4(w0[t], w1[t], w2[t], 0u);
-      } else {
-        dst[0] = make_uint4(w0[t], w1[t], w2[t], w3[t]);
-        dst[1] = make_uint4(N == 5 ? w4[t] : 0u, 0u, 0u, 0u);
-      }
+      dst[0] = make_uint4(w0[t], w1[t], 0u, 0u);
+      if (N >= 4) dst[1] = make_uint4(0u, 0u, 0u, 0u);
     }
   }
-  for (uint32_t p = (uint32_t)KV * 64u + lane; p < slots; p += 64) {  // units above 512 nonzeros
-    const uint32_t z = z0 + p;
-    uint32_t x0 = 0, x1 = 0, x2 = 0, x3 = 0, x4 = 0;
-    if (z < a.nnz) {
-      if (CSF) {
-        x0 = a.ind[N - 1][z];
-        x1 = valb[z];
-      } else {
-        x0 = a.ind[1][z];
-        x1 = a.ind[2][z];
-        if (N >= 4) x2 = a.ind[3][z];
-        if (N >= 5) x3 = a.ind[4][z];
-        (N == 3 ? x2 : N == 4 ? x3 : x4) = valb[z];
-      }
-    }
-    uint4* dst = reinterpret_cast<uint4*>(rec + (size_t)(p + (p >> ss)) * RW);
-    if (CSF) {
-      dst[0] = make_uint4(x0, x1, 0u, 0u);
-      if (N >= 4 && !PACK) dst[1] = make_uint4(0u, 0u, 0u, 0u);
-    } else if (N == 3) {
-      dst[0] = make_uint4(x0, x1, x2, 0u);
-    } else {
-      dst[0] = make_uint4(x0, x1, x2, x3);
-      dst[1] = make_uint4(N == 5 ? x4 : 0u, 0u, 0u, 0u);
-    }
-  }
-  if (PACK && lane < NG) sideFirst[lane] = s1 - s0;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
 
   // -- segment end marks
-  if (CSF) {
 #pragma unroll
-    for (int l = 1; l <= NF; ++l) {
-      const int word = 2 + (NF - l);
-      auto mark = [&](uint32_t p, uint32_t index) {
-        uint32_t* at = rec + (size_t)(p + (p >> ss)) * RW + word;
-        if (PACK && l == 1) atomicOr(at, index + 1u);   // the slice-end flag may land in the same word
-        else *at = index + 1u;
-      };
+  for (int l = 1; l <= NF; ++l) {
+    const int word = 2 + (NF - l);
+    auto mark = [&](uint32_t p, uint32_t index) { rec[(size_t)(p + (p >> ss)) * RW + word] = index + 1u; };
 #pragma unroll
-      for (int t = 0; t < KF; ++t) {
-        const uint32_t f = fLo[l - 1] + (uint32_t)t * 64u + lane;
-        if (f < b.fHi[l - 1]) {
-          const uint32_t p = fe[l - 1][t] - (START ? 0u : 1u) - z0;
-          mark(p, fi[l - 1][t]);
-          if (cutSegments)
-            for (uint32_t q = ((fs[l - 1][t] - z0) | (SUB - 1u)); q < p; q += SUB) mark(q, fi[l - 1][t]);
-        }
-      }
-      for (uint32_t f = fLo[l - 1] + (uint32_t)KF * 64u + lane; f < b.fHi[l - 1]; f += 64) {
-        const uint32_t p = a.ptr[l][f + (START ? 0 : 1)] - (START ? 0u : 1u) - z0;
-        const uint32_t index = a.ind[l][f];
-        mark(p, index);
+    for (int t = 0; t < KF; ++t) {
+      const uint32_t f = fLo[l - 1] + (uint32_t)t * 64u + lane;
+      if (f < b.fHi[l - 1]) {
+        const uint32_t p = fe[l - 1][t] - (START ? 0u : 1u) - z0;
+        mark(p, fi[l - 1][t]);
         if (cutSegments)
-          for (uint32_t q = ((a.ptr[l][f] - z0) | (SUB - 1u)); q < p; q += SUB) mark(q, index);
+          for (uint32_t q = ((fs[l - 1][t] - z0) | (SUB - 1u)); q < p; q += SUB) mark(q, fi[l - 1][t]);
       }
+    }
+    for (uint32_t f = fLo[l - 1] + (uint32_t)KF * 64u + lane; f < b.fHi[l - 1]; f += 64) {
+      const uint32_t p = a.ptr[l][f + (START ? 0 : 1)] - (START ? 0u : 1u) - z0;
+      const uint32_t index = a.ind[l][f];
+      mark(p, index);
+      if (cutSegments)
+        for (uint32_t q = ((a.ptr[l][f] - z0) | (SUB - 1u)); q < p; q += SUB) mark(q, index);
     }
   }
   // -- slice end marks
-  auto end_slice = [&](uint32_t sl, uint32_t begin, uint32_t at, uint32_t entry) {
+  auto mark_slice = [&](uint32_t at, uint32_t entry) {
     const uint32_t p = at - (START ? 0u : 1u) - z0;
-    if (PACK) {
-      atomicOr(rec + (size_t)(p + (p >> ss)) * RW + 3, 0x80000000u);
-      side[sl - s0] = mark_of_slice(entry);
-      // the parts whose first nonzero lies in this slice start with it
-      for (uint32_t q = begin > z0 ? (begin - z0 + SUB - 1u) >> ss : 0u; (q << ss) <= p; ++q) sideFirst[q] = sl - s0;
-    } else {
-      rec[(size_t)(p + (p >> ss)) * RW + markWord] = START ? (entry & 0x7fffffffu) + 1u : mark_of_slice(entry);
-    }
+    rec[(size_t)(p + (p >> ss)) * RW + markWord] = START ? (entry & 0x7fffffffu) + 1u : mark_of_slice(entry);
   };
 #pragma unroll
   for (int t = 0; t < KS; ++t) {
     const uint32_t sl = s0 + (uint32_t)t * 64u + lane;
-    if (sl < s1 && (!START || (se[t] >= z0 && se[t] < z0 + slots && se[t] < a.nnz))) end_slice(sl, sb[t], se[t], si[t]);
+    if (sl < s1 && (!START || (se[t] >= z0 && se[t] < z0 + slots && se[t] < a.nnz))) mark_slice(se[t], si[t]);
   }
   for (uint32_t sl = s0 + (uint32_t)KS * 64u + lane; sl < s1; sl += 64) {
     const uint32_t at = a.ptr[0][sl + (START ? 0 : 1)];
     if (START && (at < z0 || at >= z0 + slots || at >= a.nnz)) continue;
-    end_slice(sl, PACK ? a.ptr[0][sl] : 0u, at, a.ind[0][sl]);
+    mark_slice(at, a.ind[0][sl]);
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 
@@ -594,7 +521,209 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
   e.open = nextStart < min(z0 + slots, a.nnz);
   e.ends = s1 > s0;
   e.ng = z < a.nnz ? min(SUB, a.nnz - z) : 0u;
-  e.sideAt = PACK ? sideFirst[g] : 0u;
+  e.sideAt = 0;
+  return e;
+}
+
+// ---------------------------------------------------------------------------------------
+// Staging of the B-CSF and CSL kernels: arrays of one word per nonzero in LDS instead of records.
+//
+// A vector-memory instruction of a full wavefront occupies the compute unit's address unit for 16 cycles whatever its
+// width, and that unit is what these kernels wait for, so a unit is staged with the widest loads there are: the stream
+// data (leaf index and value, or the N - 1 indices and the value) goes from memory straight to LDS, 16 bytes a lane and
+// without passing through registers, and a lane takes four consecutive fiber segments with one load of their ends and
+// one of their indices (with dword loads through registers into records: 50 M nonzeros of order 4 2514 -> 2427 us over
+// all modes, 150 M hypersparse 9290 -> 9200, rank 16 on 7.7 M 204 -> 196, fp64 on 5 M 314 -> 307, 100 M of order 3 with
+// long fibers 2185 -> 2188, 5 M 190 -> 190).  A part's words are read four nonzeros at a time, so within each array the quads of a part are
+// exchanged by quad_swizzle: the lane groups then read from different banks, which the padded records did by a pad
+// that a direct load to LDS (lane l writes place l) cannot leave.
+// ---------------------------------------------------------------------------------------
+
+// Place of quad j (of 2^(SS - 2)) of part g is j ^ quad_swizzle(g): 128 bytes of LDS, eight quads, hold one quad of each
+// of eight consecutive reads.
+template <int SS>
+__device__ __forceinline__ uint32_t quad_swizzle(uint32_t g) {
+  return SS >= 5 ? (g & 7u) : SS == 4 ? ((g >> 1) & 3u) : ((g >> 2) & 1u);
+}
+
+// Word that holds nonzero p of the unit.
+template <int SS>
+__device__ __forceinline__ uint32_t word_of(uint32_t p) {
+  return p ^ (quad_swizzle<SS>(p >> SS) << 2);
+}
+
+typedef uint32_t quad __attribute__((ext_vector_type(4)));
+typedef uint32_t quad_unaligned __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ quad load_quad_unaligned(const uint32_t* p) {
+  return __builtin_nontemporal_load(reinterpret_cast<const quad_unaligned*>(p));
+}
+
+// Words z0 .. z0 + SLOTS - 1 of the K arrays from(0 .. K - 1) to `to` (K x SLOTS words, wave-uniform), 16 bytes a lane,
+// not awaited.  Quads that begin past `nnz` are left out; one that straddles it reads on inside the array's padding to
+// 256 bytes.
+template <uint32_t K, int SS, uint32_t SLOTS, typename From>
+__device__ __forceinline__ void stream_to_lds(From from, uint32_t* to, uint32_t z0, uint32_t nnz, int lane) {
+  constexpr uint32_t Q = SLOTS / 4, total = K * Q;
+  constexpr int kNonTemporal = 2;
+#pragma unroll
+  for (uint32_t t = 0; t < (total + 63) / 64; ++t) {
+    const uint32_t q = t * 64u + (uint32_t)lane;
+    const uint32_t* src = from(Q % 64 == 0 ? t * 64u / Q : 0u);
+    if (Q % 64 != 0) {
+#pragma unroll
+      for (uint32_t k = 1; k < K; ++k)
+        if (q >= k * Q) src = from(k);
+    }
+    const uint32_t p = word_of<SS>((q % Q) * 4u);
+    if (q < total && p < nnz - z0)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + z0 + p),
+                                       (__attribute__((address_space(3))) void*)(to + t * 256u), 16, 0, kNonTemporal);
+  }
+}
+
+// LDS of a unit, in arrays of SLOTS words.  B-CSF: leaf index, value, then the marks of the fiber levels from the deepest
+// up; where a slice ends, bit 31 of the level-1 mark is set, and the marks of the unit's slices stand in `side`, one word
+// per slice in slice order; `sideFirst` (NG words) says where each part's begin.  CSL: the N - 1 indices, the value, the
+// slice marks.  Marks are end marks: index + 1 at the LAST nonzero of a segment / slice, else 0; a slice mark carries the
+// owned bit.
+// fLo: first segment of this unit per fiber level (wave-uniform; = previous unit's fHi).
+template <int G, int N, int SS, bool CSF>
+__device__ __forceinline__ UnitEnds stage_arrays(const GroupArgs& a, uint32_t* __restrict__ words, uint32_t u,
+                                                 const UnitBounds& b, const uint32_t (&fLo)[3], int lane,
+                                                 uint32_t* __restrict__ side = nullptr,
+                                                 uint32_t* __restrict__ sideFirst = nullptr) {
+  constexpr int NG = 64 / G;
+  constexpr int NF = N - 2;
+  constexpr uint32_t SUB = 1u << SS;
+  constexpr uint32_t slots = (uint32_t)NG << SS;
+  constexpr int KF = (slots + 255) / 256;   // a segment holds at least one nonzero
+  constexpr int KS = 2;                     // slice loads per lane issued together (128 slices)
+  constexpr uint32_t kData = CSF ? 2 : N;   // arrays of stream data
+  constexpr uint32_t kMarks = CSF ? NF : 1;
+  const uint32_t z0 = u * slots;
+  const uint32_t zEnd = min(z0 + slots, a.nnz);
+  const int g = lane / G;
+  // parts shorter than runs (of at most 64 nonzeros): segments are cut at part ends too
+  const bool cutSegments = CSF && SS < 6 && SS < a.lshift;
+
+  // -- issue: ends and indices of the slices that end in this unit, those before the one holding the next unit's first
+  // nonzero (first: the run table's entries are awaited here, and with them whatever was issued before)
+  const uint32_t s0 = __builtin_amdgcn_readfirstlane(b.rf);
+  const uint32_t s1 = __builtin_amdgcn_readlane(b.rf, (int)runs_per_unit<G, SS>(a));
+  const uint32_t rowRaw = a.ind[0][s1];
+  const uint32_t nextStart = a.ptr[0][s1];
+  uint32_t se[KS], si[KS], sb[KS];
+#pragma unroll
+  for (int t = 0; t < KS; ++t) {
+    const uint32_t sl = s0 + (uint32_t)t * 64u + lane;
+    se[t] = 0;
+    si[t] = 0;
+    sb[t] = 0;
+    if (sl < s1) {
+      se[t] = a.ptr[0][sl + 1];
+      si[t] = a.ind[0][sl];
+      if (CSF) sb[t] = a.ptr[0][sl];
+    }
+  }
+  // -- issue: stream data
+  stream_to_lds<kData, SS, slots>(
+      [&](uint32_t k) { return k == kData - 1 ? reinterpret_cast<const uint32_t*>(a.val) : a.ind[CSF ? N - 1 : k + 1]; },
+      words, z0, a.nnz, lane);
+  // -- issue: fiber-segment ends and indices, four segments a lane (the last lane's may reach three words past the array,
+  // which the arrays that follow it in the arena cover)
+  quad fe[3][KF], fi[3][KF];
+  if constexpr (CSF) {
+#pragma unroll
+    for (int l = 1; l <= NF; ++l) {
+#pragma unroll
+      for (int t = 0; t < KF; ++t) {
+        const uint32_t f = fLo[l - 1] + ((uint32_t)t * 64u + lane) * 4u;
+        fe[l - 1][t] = fi[l - 1][t] = quad{0u, 0u, 0u, 0u};
+        if (f < b.fHi[l - 1]) {
+          fe[l - 1][t] = load_quad_unaligned(a.ptr[l] + f + 1);
+          fi[l - 1][t] = load_quad_unaligned(a.ind[l] + f);
+        }
+      }
+    }
+  }
+  // -- marks cleared
+  uint32_t* __restrict__ marks = words + kData * slots;
+#pragma unroll
+  for (uint32_t t = 0; t < (kMarks * slots + 255) / 256; ++t) {
+    const uint32_t q = t * 64u + (uint32_t)lane;
+    if ((kMarks * slots) % 256 == 0 || q < kMarks * slots / 4) reinterpret_cast<quad*>(marks)[q] = quad{0u, 0u, 0u, 0u};
+  }
+  if (CSF && lane < NG) sideFirst[lane] = s1 - s0;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+
+  // -- segment end marks
+  if constexpr (CSF) {
+#pragma unroll
+    for (int l = 1; l <= NF; ++l) {
+      uint32_t* __restrict__ at = marks + (uint32_t)(NF - l) * slots;
+      auto mark = [&](uint32_t p, uint32_t index) { at[word_of<SS>(p)] = index + 1u; };
+      uint32_t before = z0;   // lane 0's first segment begins with the unit
+#pragma unroll
+      for (int t = 0; t < KF; ++t) {
+        const uint32_t f = fLo[l - 1] + ((uint32_t)t * 64u + lane) * 4u;
+        uint32_t begin = 0;
+        if (cutSegments) {
+          begin = __shfl_up(fe[l - 1][t].w, 1);
+          if (lane == 0) begin = before;
+          before = __builtin_amdgcn_readlane(fe[l - 1][t].w, 63);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if (f + (uint32_t)k < b.fHi[l - 1]) {
+            const uint32_t p = fe[l - 1][t][k] - 1u - z0, index = fi[l - 1][t][k];
+            mark(p, index);
+            if (cutSegments)
+              for (uint32_t q = (begin - z0) | (SUB - 1u); q < p; q += SUB) mark(q, index);
+          }
+          begin = fe[l - 1][t][k];
+        }
+      }
+    }
+  }
+  // -- slice end marks
+  auto end_slice = [&](uint32_t sl, uint32_t begin, uint32_t end, uint32_t entry) {
+    const uint32_t p = end - 1u - z0;
+    if constexpr (CSF) {
+      atomicOr(marks + (NF - 1) * slots + word_of<SS>(p), 0x80000000u);
+      side[sl - s0] = mark_of_slice(entry);
+      // the parts whose first nonzero lies in this slice start with it
+      for (uint32_t q = begin > z0 ? (begin - z0 + SUB - 1u) >> SS : 0u; (q << SS) <= p; ++q) sideFirst[q] = sl - s0;
+    } else {
+      marks[word_of<SS>(p)] = mark_of_slice(entry);
+    }
+  };
+#pragma unroll
+  for (int t = 0; t < KS; ++t) {
+    const uint32_t sl = s0 + (uint32_t)t * 64u + lane;
+    if (sl < s1) end_slice(sl, sb[t], se[t], si[t]);
+  }
+  for (uint32_t sl = s0 + (uint32_t)KS * 64u + lane; sl < s1; sl += 64)
+    end_slice(sl, CSF ? a.ptr[0][sl] : 0u, a.ptr[0][sl + 1], a.ind[0][sl]);
+
+  // -- the stream data has arrived; past the end of the stream (last unit only) zeros, which add nothing
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  if (zEnd < z0 + slots) {
+    for (uint32_t p = zEnd - z0 + lane; p < slots; p += 64) {
+#pragma unroll
+      for (uint32_t k = 0; k < kData; ++k) words[k * slots + word_of<SS>(p)] = 0u;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
+
+  UnitEnds e;
+  const uint32_t z = z0 + ((uint32_t)g << SS);
+  e.row = rowRaw & 0x7fffffffu;
+  e.open = nextStart < zEnd;
+  e.ends = s1 > s0;
+  e.ng = z < a.nnz ? min(SUB, a.nnz - z) : 0u;
+  e.sideAt = CSF ? sideFirst[g] : 0u;
   return e;
 }
 
@@ -641,12 +770,10 @@ __global__ __launch_bounds__(256) void define_rows_kernel(rowvec* __restrict__ o
 
 // ---------------------------------------------------------------------------------------
 // B-CSF group.  N = tensor order (3, 4 or 5); G = lanes per factor row.
-// LDS record per nonzero: N = 3: {leaf, val, seg1 mark, slice mark};
-//                         N = 4: {leaf, val, seg2 mark, seg1 mark | slice-end flag} (16 bytes; the marks of the
-//                                slices that end in the unit sit in a list beside the records, in slice order,
-//                                and a lane group takes them one after the other as it meets the flags);
-//                                the dense-gather variant keeps {leaf, val, seg2, seg1, slice mark, -, -, -};
-//                         N = 5: {leaf, val, seg3 mark, seg2 mark, seg1 mark, slice mark, -, -}.
+// LDS words per nonzero: leaf, val, the segment marks from the deepest level up, the last with the slice-end flag (the
+// marks of the slices that end in the unit sit in a list beside them, in slice order, and a lane group takes them one
+// after the other as it meets the flags).  The dense-gather variant's record is {leaf, val, seg1, slice mark} or
+// {leaf, val, seg2, seg1, slice mark, -, -, -}.
 // A segment mark is index+1 at the segment's last nonzero, else 0.  A slice mark is
 // (row+1) | owned bit at the slice's last nonzero, else 0.
 // ---------------------------------------------------------------------------------------
@@ -663,10 +790,7 @@ template <int G, int N, int SS, int kSteps, bool WIDE, bool DENSE>
 __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t block, uint32_t blocks) {
   constexpr int NG = 64 / G;
   constexpr int NF = N - 2;
-  // order 4 (the plain variant): 16-byte records, the level-1 mark and the slice-end flag in one word, the slices'
-  // marks in a per-unit list beside the records
-  constexpr bool PACK = N == 4 && !DENSE;
-  constexpr int RW = (N == 3 || PACK) ? 4 : 8;
+  constexpr int RW = N == 3 ? 4 : 8;   // DENSE: words of a record
   // Order 3: a lane group moves the fiber marks of every kQueue steps together, without gaps, so that its k-th fiber end
   // of them is loaded by the k-th instruction: as many load instructions as the most ends any lane group has there,
   // instead of one per step in which some lane group has an end (at one end in five nonzeros and eight lane groups 1.9
@@ -680,15 +804,16 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
   static_assert(!DENSE || N <= 4, "the dense fiber-row gather handles orders 3 and 4");
   extern __shared__ uint32_t lds[];
   const int lane = threadIdx.x & 63;
-  const int wib = threadIdx.x >> 6;
+  const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wpb = blockDim.x >> 6;
   const int g = lane / G, c = lane % G;
   constexpr uint32_t SUB = 1u << SS;
-  constexpr uint32_t recWords = NG * (SUB + 1) * RW;
-  uint32_t* rec = lds + (size_t)wib * csf_wave_words(N, G, SS, DENSE);
+  constexpr uint32_t slots = NG << SS;
+  constexpr uint32_t recWords = DENSE ? NG * (SUB + 1) * RW : (2 + NF) * slots;
+  uint32_t* rec = lds + (uint32_t)wib * csf_wave_words(N, G, SS, DENSE);
   // first finished slice of each part (the dense variant holds it in registers: its row cache already fills the LDS)
   rowvec* head = reinterpret_cast<rowvec*>(rec + recWords);
-  uint32_t* side = rec + recWords + 256;                             // PACK: marks of the slices that end in the unit,
+  uint32_t* side = rec + recWords + 256;                             // marks of the slices that end in the unit,
   uint32_t* sideFirst = side + NG * SUB;                             //       and where each part's begin
   uint32_t* list = rec + recWords;                                   // DENSE: row numbers by slot
   rowvec* cache = reinterpret_cast<rowvec*>(rec + recWords + 64);    // DENSE: rows by slot, G rowvec each
@@ -720,9 +845,11 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
   for (; u < uEnd; ++u) {
     // run-table entries of the next unit: in flight while this unit is staged and processed
     const UnitBounds nxt = load_bounds<G, N, SS, true>(a, min(u + 1, a.nUnits - 1), lane);
-    const UnitEnds ends = stage_unit<G, N, SS, true, false, PACK>(a, rec, u, cur, fLo, lane, side, sideFirst);
+    UnitEnds ends;
+    if constexpr (DENSE) ends = stage_unit<G, N, SS>(a, rec, u, cur, fLo, lane);
+    else ends = stage_arrays<G, N, SS, true>(a, rec, u, cur, fLo, lane, side, sideFirst);
     const uint32_t ng = ends.ng;
-    uint32_t sideAt = ends.sideAt;   // PACK: the next slice of this lane group's part in the unit's slice list
+    uint32_t sideAt = ends.sideAt;   // the next slice of this lane group's part in the unit's slice list
     uint32_t headMark = 0;           // mark of the first slice that ends in this lane group's part
     fLo[0] = cur.fHi[0];
     fLo[1] = cur.fHi[1];
@@ -758,8 +885,8 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
       rowvec tmp = rv_zero();
       rowvec tmp1 = rv_zero();
       rowvec tmp2 = rv_zero();
-      const uint32_t* myrec = rec + (size_t)g * (SUB + 1) * RW;
       if constexpr (DENSE) {
+      const uint32_t* myrec = rec + (size_t)g * (SUB + 1) * RW;
       for (uint32_t sb = 0; sb < SUB; sb += kSteps) {
         uint4 rr[kSteps];
         uint32_t mi[kSteps];   // slice mark
@@ -848,29 +975,29 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       }
       } else if (ng > 0) {
+      const uint32_t swizzle = quad_swizzle<SS>((uint32_t)g);
+#pragma unroll 1
       for (uint32_t sb = 0; sb < SUB; sb += kSteps) {
-        uint4 rr[kSteps];
-        uint32_t m1[kSteps];   // N = 5: mark of fiber level 1
-        uint32_t mi[kSteps];   // slice mark
+        uint32_t leaf[kSteps], val[kSteps];
+        // marks of the deepest fiber level, (N >= 4) the one above it, (N = 5) fiber level 1; bit 31 of a level-1 mark:
+        // the slice ends too, and its mark is the next of this part's in the slice list
+        uint32_t m3[kSteps], m2[kSteps], m1[kSteps];
+        uint32_t (&top)[kSteps] = N == 3 ? m3 : N == 4 ? m2 : m1;
         rowvec cr[kSteps], br[kSteps], nr[kSteps], ar[kSteps];
 #pragma unroll
-        for (int t = 0; t < kSteps; ++t) {
-          const uint4* src = reinterpret_cast<const uint4*>(myrec + (size_t)(sb + t) * RW);
-          rr[t] = src[0];
-          if (N == 3) {
-            mi[t] = rr[t].w;
-            m1[t] = 0;
-          } else if (PACK) {
-            mi[t] = rr[t].w & 0x80000000u;   // slice-end flag; the slice's mark is next in the unit's slice list
-            rr[t].w &= 0x7fffffffu;
-            m1[t] = 0;
-          } else if (N == 4) {
-            mi[t] = reinterpret_cast<const uint32_t*>(src)[4];
-            m1[t] = 0;
-          } else {
-            const uint2 hi = reinterpret_cast<const uint2*>(src)[2];
-            m1[t] = hi.x;
-            mi[t] = hi.y;
+        for (int b = 0; b < kSteps; b += 4) {
+          const quad* src = reinterpret_cast<const quad*>(rec) + (((uint32_t)g << (SS - 2)) + ((sb / 4 + b / 4) ^ swizzle));
+          const quad q0 = src[0], q1 = src[slots / 4], q2 = src[2 * slots / 4];
+          quad q3 = quad{0u, 0u, 0u, 0u}, q4 = q3;
+          if constexpr (N >= 4) q3 = src[3 * slots / 4];
+          if constexpr (N == 5) q4 = src[4 * slots / 4];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            leaf[b + t] = q0[t];
+            val[b + t] = q1[t];
+            m3[b + t] = q2[t];
+            m2[b + t] = q3[t];
+            m1[b + t] = q4[t];
           }
         }
         // Conditional loads first: loads return in order, so once a leaf row has arrived every
@@ -881,10 +1008,10 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
             uint32_t q[kQueue] = {};
 #pragma unroll
             for (int t = kQueue - 1; t >= 0; --t) {
-              const bool marked = rr[b + t].z != 0u;
+              const bool marked = m3[b + t] != 0u;
 #pragma unroll
               for (int k = kQueue - 1 - t; k > 0; --k) q[k] = marked ? q[k - 1] : q[k];
-              q[0] = marked ? rr[b + t].z : q[0];
+              q[0] = marked ? m3[b + t] : q[0];
             }
 #pragma unroll
             for (int k = 0; k < kQueue; ++k)
@@ -893,18 +1020,18 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
         }
 #pragma unroll
         for (int t = 0; t < kSteps; ++t) {
-          if (!QUEUE && rr[t].z)
-            br[t] = marked_row_load<G, WIDE>(markDeep, rr[t].z, c, (a.streamLevel & (1u << (N - 2))) != 0u);
-          if (N >= 4 && rr[t].w)
-            nr[t] = marked_row_load<G, WIDE>(markNext, rr[t].w, c, (a.streamLevel & (1u << (N - 3))) != 0u);
+          if (!QUEUE && m3[t])
+            br[t] = marked_row_load<G, WIDE>(markDeep, m3[t], c, (a.streamLevel & (1u << (N - 2))) != 0u);
+          if (N >= 4 && m2[t])
+            nr[t] = marked_row_load<G, WIDE>(markNext, m2[t], c, (a.streamLevel & (1u << (N - 3))) != 0u);
           if (N == 5 && m1[t]) ar[t] = marked_row_load<G, WIDE>(markTop, m1[t], c, (a.streamLevel & 2u) != 0u);
         }
 #pragma unroll
-        for (int t = 0; t < kSteps; ++t) cr[t] = row_load<G, WIDE>(facLeaf, rr[t].x, c);
+        for (int t = 0; t < kSteps; ++t) cr[t] = row_load<G, WIDE>(facLeaf, leaf[t], c);
 #pragma unroll
         for (int t = 0; t < kSteps; ++t) {
-          fma4(tmp, __uint_as_float(rr[t].y), cr[t]);
-          if (rr[t].z) {
+          fma4(tmp, __uint_as_float(val[t]), cr[t]);
+          if (m3[t]) {
             if (QUEUE) {
               const int head = t / kQueue * kQueue;
               fma4(acc, tmp, br[head]);
@@ -912,7 +1039,7 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
               for (int k = 0; k < kQueue - 1 - t % kQueue; ++k) br[head + k] = br[head + k + 1];
             } else {
               fma4(tmp1, tmp, br[t]);
-              if (rr[t].w) {
+              if (m2[t]) {
                 if (N == 4) {
                   fma4(acc, tmp1, nr[t]);
                 } else {
@@ -926,8 +1053,7 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
               }
             }
             tmp = rv_zero();
-            // a slice can only end where a segment ends (PACK: its mark is the next of this part's in the slice list)
-            if (mi[t]) slice_end(PACK ? side[sideAt++] : mi[t]);
+            if ((int)top[t] < 0) slice_end(side[sideAt++]);   // a slice can only end where a segment ends
           }
         }
       }
@@ -1002,7 +1128,7 @@ __global__ __launch_bounds__(256) void csf_nonroot_kernel(const GroupArgs a) {
 
     for (; u < uEnd; ++u) {
       const UnitBounds nxt = load_bounds<G, N, LS, true>(a, min(u + 1, a.nUnits - 1), lane);
-      const UnitEnds ends = stage_unit<G, N, LS, true, true>(a, rec, u, cur, fLo, lane);
+      const UnitEnds ends = stage_unit<G, N, LS, true>(a, rec, u, cur, fLo, lane);
       fLo[0] = cur.fHi[0];
       fLo[1] = cur.fHi[1];
       fLo[2] = cur.fHi[2];
@@ -1088,22 +1214,20 @@ __global__ __launch_bounds__(256) void csf_nonroot_kernel(const GroupArgs a) {
 // ---------------------------------------------------------------------------------------
 // CSL group (Algorithm "CSL-MTTKRP"): every nonzero carries all its non-root indices; the
 // slice pointer goes straight to the nonzeros.
-// LDS record: N = 3: {j, k, val, slice mark}; N = 4: {a, b, l, val, slice mark, -, -, -};
-//             N = 5: {a, b, c, l, val, slice mark, -, -}.
+// LDS of a unit: an array each for the N - 1 indices, the value and the slice mark.
 // ---------------------------------------------------------------------------------------
 template <int G, int N, int SS, int kSteps, bool WIDE>
 __device__ __forceinline__ void csl_group_body(const GroupArgs& a, uint32_t block, uint32_t blocks) {
   constexpr int NG = 64 / G;
-  constexpr int RW = (N == 3) ? 4 : 8;
   extern __shared__ uint32_t lds[];
   const int lane = threadIdx.x & 63;
-  const int wib = threadIdx.x >> 6;
+  const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wpb = blockDim.x >> 6;
   const int g = lane / G, c = lane % G;
   constexpr uint32_t SUB = 1u << SS;
-  constexpr uint32_t recWords = NG * (SUB + 1) * RW;
-  uint32_t* rec = lds + (size_t)wib * csl_wave_words(N, G, SS);
-  rowvec* head = reinterpret_cast<rowvec*>(rec + recWords);
+  constexpr uint32_t slots = NG << SS;
+  uint32_t* words = lds + (uint32_t)wib * csl_wave_words(N, G, SS);
+  rowvec* head = reinterpret_cast<rowvec*>(words + (N + 1) * slots);
 
   const unsigned long long traceStart = a.trace ? wall_clock64() : 0ull;
   const SpanWalk walk = span_walk(a, block, blocks, wib, wpb);
@@ -1119,7 +1243,7 @@ __device__ __forceinline__ void csl_group_body(const GroupArgs& a, uint32_t bloc
 
   for (; u < uEnd; ++u) {
     const UnitBounds nxt = load_bounds<G, N, SS, false>(a, min(u + 1, a.nUnits - 1), lane);
-    const UnitEnds ends = stage_unit<G, N, SS, false>(a, rec, u, cur, fLo, lane);
+    const UnitEnds ends = stage_arrays<G, N, SS, false>(a, words, u, cur, fLo, lane);
     uint32_t headMark = 0;
     cur = nxt;
     open = ends.open;
@@ -1131,34 +1255,33 @@ __device__ __forceinline__ void csl_group_body(const GroupArgs& a, uint32_t bloc
     spread = !ends.ends;
 
     if (ends.ng > 0) {
-      const uint32_t* myrec = rec + (size_t)g * (SUB + 1) * RW;
+      const uint32_t swizzle = quad_swizzle<SS>((uint32_t)g);
+#pragma unroll 1
       for (uint32_t sb = 0; sb < SUB; sb += kSteps) {
-        uint4 rr[kSteps];
+        uint32_t ix[N - 1][kSteps];
         uint32_t vv[kSteps];   // value bits
         uint32_t mi[kSteps];   // slice mark
         rowvec x1[kSteps], x2[kSteps], x3[kSteps], x4[kSteps];
 #pragma unroll
-        for (int t = 0; t < kSteps; ++t) {
-          const uint4* src = reinterpret_cast<const uint4*>(myrec + (size_t)(sb + t) * RW);
-          rr[t] = src[0];
-          if (N == 3) {
-            vv[t] = rr[t].z;
-            mi[t] = rr[t].w;
-          } else if (N == 4) {
-            vv[t] = rr[t].w;
-            mi[t] = reinterpret_cast<const uint32_t*>(src)[4];
-          } else {
-            const uint2 hi = reinterpret_cast<const uint2*>(src)[2];
-            vv[t] = hi.x;
-            mi[t] = hi.y;
+        for (int b = 0; b < kSteps; b += 4) {
+          const quad* src = reinterpret_cast<const quad*>(words) + (((uint32_t)g << (SS - 2)) + ((sb / 4 + b / 4) ^ swizzle));
+          quad q[N + 1];
+#pragma unroll
+          for (int k = 0; k <= N; ++k) q[k] = src[(uint32_t)k * slots / 4];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+#pragma unroll
+            for (int k = 0; k < N - 1; ++k) ix[k][b + t] = q[k][t];
+            vv[b + t] = q[N - 1][t];
+            mi[b + t] = q[N][t];
           }
         }
 #pragma unroll
         for (int t = 0; t < kSteps; ++t) {
-          x1[t] = row_load<G, WIDE>(a.fac[1], rr[t].x, c);
-          x2[t] = row_load<G, WIDE>(a.fac[2], rr[t].y, c);
-          if (N >= 4) x3[t] = row_load<G, WIDE>(a.fac[3], rr[t].z, c);
-          if (N >= 5) x4[t] = row_load<G, WIDE>(a.fac[4], rr[t].w, c);
+          x1[t] = row_load<G, WIDE>(a.fac[1], ix[0][t], c);
+          x2[t] = row_load<G, WIDE>(a.fac[2], ix[1][t], c);
+          if constexpr (N >= 4) x3[t] = row_load<G, WIDE>(a.fac[3], ix[2][t], c);
+          if constexpr (N >= 5) x4[t] = row_load<G, WIDE>(a.fac[4], ix[3][t], c);
         }
 #pragma unroll
         for (int t = 0; t < kSteps; ++t) {
