@@ -192,7 +192,7 @@ int hbcsf_host_array(const hbcsf_tensor *t, int mode, int group, int level, int 
 #define HBCSF_TUNE_PROFILE         1 /* n > 0: bracket the kernels of each call with HIP events and
                                         keep the last n calls' event sets; 0 = off              */
 #define HBCSF_TUNE_WAVES_PER_CU     2 /* wavefront spans launched per compute unit when T_s is
-                                        automatic (default 128)                                 */
+                                        automatic (0, the default: 512 at most, in whole units)  */
 #define HBCSF_TUNE_STEPS            3 /* gathers a lane group keeps in flight: 4, 8 or 0 = automatic, the
                                         default (8 for order-3 streams of 40 M nonzeros and more in runs
                                         of 64, else 4).  A choice of two at rows of 128 bytes; the other

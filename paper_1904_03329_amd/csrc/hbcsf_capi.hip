@@ -359,8 +359,14 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
     a.partShift = part;
     const uint64_t unitNnz = (uint64_t)NG << part;
     a.nUnits = (uint32_t)((gf.nnz + unitNnz - 1) / unitNnz);
-    const uint64_t target = (uint64_t)t->numCU * (t->wavesPerCU ? t->wavesPerCU : 128);
+    // Spans: one unit while that gives at most 256 wavefronts per compute unit (6 M to 16 M nonzeros: with two 372 instead
+    // of 369 us on 12 M), then two, since the run-table entries of a second unit are there when the first is done (20 M:
+    // 577 instead of 584 us, 50 M of order 4 2400 instead of 2513), and more only beyond 512 wavefronts per compute unit
+    // (150 M: 9050 us at 128 of them, 8959 at 256, 8822 at 512, 8791 at 1024; 100 M with parts of whole runs 2101, 2041,
+    // 2032, 2079).
+    const uint64_t cus = (uint64_t)t->numCU, target = cus * (t->wavesPerCU ? t->wavesPerCU : 512);
     uint64_t upw = t->sliceThreshold ? t->sliceThreshold / unitNnz : (a.nUnits + target - 1) / target;
+    if (!t->sliceThreshold && !t->wavesPerCU && a.nUnits > 256 * cus && upw < 2) upw = 2;
     if (upw == 0) upw = 1;
     a.unitsPerWave = (uint32_t)upw;
     a.nSpans = (uint32_t)((a.nUnits + upw - 1) / upw);

@@ -301,6 +301,31 @@ __device__ __forceinline__ void close_span(float* __restrict__ out, bool open, u
   row_atomic_wave<G>(out, row, 0, acc, lane);
 }
 
+// The slices still open at the ends of a block's spans (one span a wavefront, all wavefronts take part; they are
+// consecutive): one atomic row for each sequence of wavefronts with the same row.  `words`: the wavefront's LDS, `stride`
+// words from one wavefront's to the next.  With an atomic row per wavefront a slice of 472 000 nonzeros of a 5 M-nonzero
+// tensor was added up by 1844 of them on its row, 12.9 ns after each other, while a mode takes 60 us; that is also what kept
+// the spans long (all modes, with one span of 256 nonzeros and up a wavefront, per-wavefront atomics -> this: 5 M
+// 189.7 -> 181 us, fp64 307 -> 290, 100 M 2188 -> 2032, 150 M hypersparse 9200 -> 8820, 50 M of order 4 2427 -> 2400).
+template <int G>
+__device__ __forceinline__ void close_block(float* __restrict__ out, uint32_t* words, uint32_t stride, bool open,
+                                            uint32_t row, rowvec acc, int lane, int wib, int wpb) {
+  constexpr uint32_t kNone = 0xffffffffu;
+  sum_lane_groups<G>(acc);
+  rowvec* mine = reinterpret_cast<rowvec*>(words);
+  if (lane < G) mine[lane] = acc;
+  if (lane == 0) words[4 * G] = open ? row : kNone;
+  __syncthreads();
+  if (!open) return;
+  if (wib > 0 && (words - stride)[4 * G] == row) return;   // the wavefront before it adds this row up
+  for (int w = wib + 1; w < wpb; ++w) {
+    words += stride;
+    if (words[4 * G] != row) break;
+    add_row(acc, reinterpret_cast<const rowvec*>(words)[lane % G]);
+  }
+  row_atomic_wave<G>(out, row, 0, acc, lane);
+}
+
 // One trace record per wavefront: which compute unit it ran on and when (profiling only).
 __device__ __forceinline__ void trace_wave(const GroupArgs& a, int kind, unsigned long long t0, int lane) {
   if (a.trace == nullptr || lane != 0) return;
@@ -828,14 +853,16 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
 
   const unsigned long long traceStart = a.trace ? wall_clock64() : 0ull;
   const SpanWalk walk = span_walk(a, block, blocks, wib, wpb);
-  for (uint32_t span = walk.first; span < walk.end; span += walk.stride) {
-  uint32_t u = span * a.unitsPerWave;
-  const uint32_t uEnd = min(u + a.unitsPerWave, a.nUnits);
   // acc: what this lane group has collected of the slice that is open at the end of its part.  Between units it is
   // held by lane group 0 alone, unless no slice ended since (spread): then every lane group holds a share of it.
   rowvec acc = rv_zero();
-  bool spread = false, open = false;
+  bool open = false;
   uint32_t openRow = 0;
+  for (uint32_t span = walk.first; span < walk.end; span += walk.stride) {
+  uint32_t u = span * a.unitsPerWave;
+  const uint32_t uEnd = min(u + a.unitsPerWave, a.nUnits);
+  acc = rv_zero();
+  bool spread = false;
 
   UnitBounds cur = load_bounds<G, N, SS, true>(a, u, lane);
   uint32_t fLo[3] = {0, 0, 0};
@@ -1066,8 +1093,10 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
-  close_span<G>(a.out, open, openRow, acc, lane);
+  if (a.persistent) close_span<G>(a.out, open, openRow, acc, lane);
   }  // spans
+  if (!a.persistent)
+    close_block<G>(a.out, rec, csf_wave_words(N, G, SS, DENSE), open, openRow, acc, lane, wib, wpb);
   trace_wave(a, kCsfKernel, traceStart, lane);
 }
 
@@ -1082,9 +1111,9 @@ __global__ __launch_bounds__(256) void csf_group_dense_kernel(const GroupArgs a)
 }
 
 // With 8 gathers in flight the order-3, R = 32, 32-bit-offset instantiation needs a few more vector registers than fit
-// four wavefronts per SIMD; held to 128 it spills one of them and gains a wavefront.  (With 4 in flight: 86 to 96
-// registers at order 3, five wavefronts, 118 to 126 at order 4.  Holding order 3 to 80 for a sixth spilled ten and took
-// 2.68 instead of 2.35 ms on 100 M nonzeros.)
+// four wavefronts per SIMD; held to 128 it gains a wavefront.  (With 4 in flight: 82 to 96 registers at order 3, five
+// wavefronts, 108 to 122 at order 4.  Holding order 3 to 80 for a sixth spills and takes 206 instead of 181 us on 5 M
+// nonzeros, order 4 to 96 for a fifth 2702 instead of 2420 us on 50 M.)
 template <int G, int N, int SS, int kSteps>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void csf_group_kernel_occ4(const GroupArgs a) {
   csf_group_body<G, N, SS, kSteps, false, false>(a, blockIdx.x, gridDim.x);
@@ -1231,12 +1260,14 @@ __device__ __forceinline__ void csl_group_body(const GroupArgs& a, uint32_t bloc
 
   const unsigned long long traceStart = a.trace ? wall_clock64() : 0ull;
   const SpanWalk walk = span_walk(a, block, blocks, wib, wpb);
+  rowvec acc = rv_zero();               // as in the B-CSF kernel
+  bool open = false;
+  uint32_t openRow = 0;
   for (uint32_t span = walk.first; span < walk.end; span += walk.stride) {
   uint32_t u = span * a.unitsPerWave;
   const uint32_t uEnd = min(u + a.unitsPerWave, a.nUnits);
-  rowvec acc = rv_zero();               // as in the B-CSF kernel
-  bool spread = false, open = false;
-  uint32_t openRow = 0;
+  acc = rv_zero();
+  bool spread = false;
 
   UnitBounds cur = load_bounds<G, N, SS, false>(a, u, lane);
   const uint32_t fLo[3] = {0, 0, 0};
@@ -1304,8 +1335,9 @@ __device__ __forceinline__ void csl_group_body(const GroupArgs& a, uint32_t bloc
     if (ends.ends) close_unit<G>(a.out, headMark ? head[lane] : rv_zero(), headMark, acc, lane, g, c);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
-  close_span<G>(a.out, open, openRow, acc, lane);
+  if (a.persistent) close_span<G>(a.out, open, openRow, acc, lane);
   }  // spans
+  if (!a.persistent) close_block<G>(a.out, words, csl_wave_words(N, G, SS), open, openRow, acc, lane, wib, wpb);
   trace_wave(a, kCslKernel, traceStart, lane);
 }
 
