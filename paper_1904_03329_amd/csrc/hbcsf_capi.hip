@@ -335,9 +335,9 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
   const bool dense = t->denseMid == 1 && dense_mid_available(N, G, lshift);
   // 8 gathers in flight with parts of whole runs: at order 3 and runs of 64 four wavefronts per SIMD instead of five, but
   // half the staging per nonzero.  Pays there with rows of 128 bytes, narrow factor matrices and a stream that fills the
-  // chip many times over (100 M nonzeros 2.32 -> 2.25 ms, 56 M 1.15 -> 1.08 ms; 40 M and fewer equal, 5 M 5 % slower);
-  // at other run lengths and orders only where the tuning key asks for it.
-  const bool longParts = G == 8 && (t->steps == 8 || (t->steps == 0 && N == 3 && lshift == 6 && !wide && sparseNnz >= 40000000));
+  // chip many times over (100 M nonzeros 2.15 -> 2.03 ms, 30 M 867 -> 841 us, 25 M 735 -> 727 and 926 -> 926, 20 M 578 ->
+  // 579 and 496 -> 480, 12 M 370 -> 381, 5 M 181 -> 221); at other run lengths and orders only where the tuning key asks.
+  const bool longParts = G == 8 && (t->steps == 8 || (t->steps == 0 && N == 3 && lshift == 6 && !wide && sparseNnz >= 25000000));
   const int denseSteps = t->steps ? t->steps : N == 3 ? 8 : 4;
   // CSL and B-CSF group in one launch, unless their times are asked for one by one (or the kernel with 8 gathers
   // is used: with both bodies in it, it no longer fits four wavefronts per SIMD)

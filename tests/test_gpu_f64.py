@@ -64,7 +64,7 @@ def test_build_options_do_not_change_the_result(oracle, dims, nnz, opts):
 
 def test_rank_16_kernel_variants(oracle):
     """Rank 16 in fp64 is the 8-lanes-per-row mapping: the kernels with 8 gathers in flight (the B-CSF one held to 128
-    registers, chosen by itself from 40 M nonzeros up, and the CSL one) and the dense fiber-row gather (a tuning variant)
+    registers, chosen by itself from 25 M nonzeros up, and the CSL one) and the dense fiber-row gather (a tuning variant)
     are instantiated for doubles too."""
     rng = np.random.default_rng(5)
     dims = (4000, 500, 80)
