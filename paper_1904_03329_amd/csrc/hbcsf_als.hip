@@ -4,7 +4,8 @@
 //
 // Every mode update runs on the device from end to end; the host only enqueues, and waits once at the end of an
 // iteration (or, where no iteration's fit decides anything, once at the end of the run):
-//   V = Hadamard of the other factors' Gram matrices, P = V^+      (small_pinv_kernel, fp64, one workgroup)
+//   V = Hadamard of the other factors' Gram matrices, P = V^+      (fp64, one workgroup: small_pinv_kernel, or up to rank
+//                                                                   64 a block of the MTTKRP launch)
 //   M = MTTKRP
 //   ordinary call:   S = M^T M;  A_n^T A_n = V^+ S V^+ without another pass over the rows, and its diagonal gives the
 //                    column norms, so the product A_n = M P is written normalised in the pass that computes it
@@ -25,6 +26,7 @@
 #include <vector>
 
 #include "hbcsf.h"
+#include "hbcsf_small.h"
 #include "hbcsf_tensor.h"
 
 using namespace hbcsf;
@@ -491,70 +493,8 @@ void launch_scale_columns(float* a, uint64_t rows, int rank, const float* s, int
 // norms of the last update.  These kernels are one workgroup each (the work is R^3 at most 2 M multiply-adds in a serial
 // chain of R steps); what they replace is a copy to the host, a wait, and a copy back for every mode update.
 // ---------------------------------------------------------------------------------------------------
-struct SmallState {
-  double* gram[HBCSF_MAX_ORDER];
-  double* scale[HBCSF_MAX_ORDER];
-  double* norm[HBCSF_MAX_ORDER];
-  int order;
-};
-
-// V = Hadamard product over the modes m != n of the algorithm's Gram matrices, entry (i, j)
-template <int R>
-__device__ __forceinline__ double v_entry(const SmallState& st, int n, int i, int j) {
-  double v = 1.0;
-  for (int m = 0; m < st.order; ++m)
-    if (m != n) v *= st.gram[m][i * R + j] / (st.scale[m][i] * st.scale[m][j]);
-  return v;
-}
-
-// d_r = product over the other modes of 1 / c_m[r]: M of the algorithm = M of the stored factors, columns times d
-template <int R>
-__device__ __forceinline__ double d_entry(const SmallState& st, int n, int r) {
-  double d = 1.0;
-  for (int m = 0; m < st.order; ++m)
-    if (m != n) d /= st.scale[m][r];
-  return d;
-}
-
-// p: right-hand matrix of the product kernels, P[i][j] in [R][R], or for R < 32 block-diagonal in [32][32]
-template <int R>
-__device__ __forceinline__ void put_p(float* __restrict__ p, int i, int j, float v) {
-  if (R >= 32) {
-    p[i * R + j] = v;
-  } else {
-    for (int b = 0; b < 32 / R; ++b) p[(b * R + i) * 32 + b * R + j] = v;
-  }
-}
-
-constexpr int small_threads(int R) { return R <= 32 ? 64 : R == 64 ? 256 : 1024; }  // (R / 4)^2, at least a wavefront
 constexpr int pinv_threads(int R) { return R == 32 ? 256 : small_threads(R); }       // the eigenvalue form uses them all
 constexpr int entry_threads(int R) { return R * R < 1024 ? R * R : 1024; }           // for kernels that walk R x R entries
-
-// First row and column of the 4 x 4 tile of an R x R matrix that thread `tid` keeps.  Below rank 32 a wavefront has more
-// threads than there are tiles: those without one are given the first (they read what it reads and store nothing).
-constexpr int tile_row(int R, int tid) { return tid < (R / 4) * (R / 4) ? 4 * (tid / (R / 4)) : 0; }
-constexpr int tile_column(int R, int tid) { return tid < (R / 4) * (R / 4) ? 4 * (tid % (R / 4)) : 0; }
-constexpr bool tiles_inside(int R) {
-  for (int tid = 0; tid < pinv_threads(R); ++tid)
-    if (tile_row(R, tid) + 4 > R || tile_column(R, tid) + 4 > R) return false;
-  return true;
-}
-static_assert(tiles_inside(8) && tiles_inside(16) && tiles_inside(32) && tiles_inside(64) && tiles_inside(128),
-              "every thread's tile lies in the matrix");
-
-// 1 / x for a normal positive x: the hardware's estimate and two Newton steps (relative error near 2^-53).
-__device__ __forceinline__ double reciprocal(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(fma(-x, r, 1.0), r, r);
-  return fma(fma(-x, r, 1.0), r, r);
-}
-
-// 1 / sqrt(x) for a normal positive x, in the same way.
-__device__ __forceinline__ double reciprocal_root(double x) {
-  double r = __builtin_amdgcn_rsq(x);
-  r = fma(0.5 * r, fma(-x * r, r, 1.0), r);
-  return fma(0.5 * r, fma(-x * r, r, 1.0), r);
-}
 
 // Pseudo-inverse of the symmetric matrix V by cyclic Jacobi rotations, n / 2 disjoint pairs at a time (round-robin
 // pairing): only when V is not safely positive definite.  Eigenvalues below 1e-15 of the largest magnitude count as zero
@@ -734,109 +674,27 @@ __device__ void jacobi_pinv(const SmallState& st, int n, JacobiLds<R>& lds, doub
 }
 
 // vp = V^+ for the update of mode n, and p = diag(d) V^+ (the right-hand matrix of a put-off update; an ordinary update
-// overwrites it).  V is inverted in place by R sweep steps without pivoting,
-//     d = a_kk;  a_kk <- -1 / d;  a_ik, a_ki <- a_ik / d;  a_ij <- a_ij - a_ik a_kj / d     (after all: -V^-1)
-// -- for a positive definite matrix as accurate as the Cholesky route, and its pivots are the squares of the Cholesky
-// factor's diagonal.  The matrix stays symmetric, so a step needs one row: each thread keeps a 4 x 4 tile in registers,
-// the threads that hold row k publish it in LDS (two buffers in turn, one barrier a step; R <= 32 is one wavefront), and
-// every thread reads the 4 + 4 entries its tile needs.  The chain of R steps is latency: the next pivot is formed from
-// the published row by every thread, so that its reciprocal is under way while the tiles are updated (rank 32: 25 us in
-// the first form, one entry per thread and a division in the chain).
-// A pivot that is not safely positive sends the whole workgroup to the eigenvalue form.
+// overwrites it).  A pivot of the sweep that is not safely positive sends the whole workgroup to the eigenvalue form.
 // resetScale: after the product the stored factor is the unnormalised one, so its column scale becomes 1.
+// hosted: null, or the outcome of the sweep that ran beside the MTTKRP: where that was good, all is done, and where it was
+// not only the eigenvalue form is left.
 template <int R>
 __global__ __launch_bounds__(pinv_threads(R)) void small_pinv_kernel(SmallState st, int n, double* __restrict__ vp,
                                                                       float* __restrict__ p, double* __restrict__ jq,
-                                                                      int resetScale,
+                                                                      int resetScale, const int* __restrict__ hosted,
                                                                       unsigned long long* __restrict__ stamp) {
-  constexpr int T = small_threads(R), U = pinv_threads(R), W = R / 4;
-  __shared__ __align__(16) double rowOf[2][R + 2];   // row k, then entry (k + 1, k + 1)
-  __shared__ double diag[R], d[R];
-  __shared__ double dmaxShared;
-  __shared__ int goodShared;
+  constexpr int U = pinv_threads(R), W = R / 4;
+  __shared__ SweepLds<R> sweep;
+  __shared__ double d[R];
   __shared__ JacobiLds<R> jl;
   const int tid = threadIdx.x;
+  if (hosted && *hosted) return;
   if (tid == 0 && stamp) stamp[0] = wall_clock64();
   const bool owns = tid < W * W;
   const int i0 = tile_row(R, tid), j0 = tile_column(R, tid);
-  double x[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) x[i][j] = owns ? 1.0 : 0.0;
-  if (owns) {
-    for (int m = 0; m < st.order; ++m) {
-      if (m == n) continue;
-      const double* g = st.gram[m];
-      double ci[4], cj[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        ci[i] = 1.0 / st.scale[m][i0 + i];
-        cj[i] = 1.0 / st.scale[m][j0 + i];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) x[i][j] *= g[(i0 + i) * R + j0 + j] * (ci[i] * cj[j]);
-    }
-    if (i0 == j0) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) diag[i0 + i] = x[i][i];
-    }
-  }
   for (int r = tid; r < R; r += U) d[r] = d_entry<R>(st, n, r);
-  __syncthreads();
-  if (tid < 64) {
-    double m = 0.0;
-    for (int r = tid; r < R; r += 64) m = fmax(m, diag[r]);
-    for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
-    if (tid == 0) dmaxShared = m;
-  }
-  __syncthreads();
-  const double least = 1e-10 * dmaxShared;
-  double pivot = diag[0];
-  bool good = true;
-  for (int kb = 0; kb < R && good && tid < T; kb += 4) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int k = kb + q;
-      double* row = rowOf[k & 1];
-      if (owns && i0 == kb) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) row[j0 + j] = x[q][j];
-        if (q < 3 && j0 == kb) row[R] = x[q < 3 ? q + 1 : 0][q < 3 ? q + 1 : 0];
-      }
-      if (q == 3 && owns && i0 == kb + 4 && j0 == kb + 4) row[R] = x[0][0];
-      if (!(pivot > least)) good = false;   // the same for every thread
-      const double inv = reciprocal(pivot);
-      if constexpr (T == 64) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // one wavefront sweeps
-      else __syncthreads();
-      double ri[4], rj[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        ri[i] = row[i0 + i];
-        rj[i] = row[j0 + i];
-      }
-      const double nextRow = k + 1 < R ? row[k + 1] : 0.0;
-      pivot = fma(-nextRow * inv, nextRow, row[R]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const double f = ri[i] * inv;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const bool inRow = i == q && i0 == kb, inCol = j == q && j0 == kb;
-          const double swept = fma(-f, rj[j], x[i][j]);
-          if (i == q || j == q) x[i][j] = inRow ? (inCol ? -inv : rj[j] * inv) : inCol ? f : swept;
-          else x[i][j] = swept;
-        }
-      }
-    }
-  }
-  if constexpr (U > T) {  // the other wavefronts have waited here
-    if (tid == 0) goodShared = good;
-    __syncthreads();
-    good = goodShared;
-  }
+  double x[4][4];
+  const bool good = !hosted && pinv_sweep<R, U>(st, n, sweep, x);
   if (good) {
     if (owns) {
 #pragma unroll
@@ -1142,6 +1000,7 @@ struct hbcsf_als {
   double* inner = nullptr;        // <X, model> of an ordinary iteration
   double* dots = nullptr;         // of a put-off one, as the blocks' sums [kDotsMax]
   SmallState small{};
+  int* good = nullptr;            // outcome of the sweep a guest made
   bool pending[HBCSF_MAX_ORDER] = {};  // the stored factor's columns still carry norms (small.scale)
   bool gramsValid = false;
   // Pinned host memory the kernels of an iteration write: {<X, model>, ||model||^2}, and wall-clock stamps (taken by a
@@ -1227,7 +1086,7 @@ int apply_pending_normalisation(hbcsf_als* a, float* const* factors, hipStream_t
 
 // Where the parts of an ALS state's workspace lie (bytes from its start).
 struct AlsLayout {
-  uint64_t m, s, p, factor, vp, tmp[2], inner, dots, gram, scale, norm, scratch, total;
+  uint64_t m, s, p, factor, vp, tmp[2], inner, dots, good, gram, scale, norm, scratch, total;
 };
 
 AlsLayout als_layout(const hbcsf_tensor* t, int rank) {
@@ -1251,6 +1110,7 @@ AlsLayout als_layout(const hbcsf_tensor* t, int rank) {
   for (int k = 0; k < 2; ++k) l.tmp[k] = take(rr * 8);
   l.inner = take(8);
   l.dots = take((uint64_t)kDotsMax * 8);
+  l.good = take(4);
   l.gram = take((uint64_t)t->order * rr * 8);
   l.scale = take((uint64_t)t->order * rank * 8);
   l.norm = take((uint64_t)t->order * rank * 8);
@@ -1280,13 +1140,30 @@ int enqueue_iteration(hbcsf_als* a, float* const* factors, float* lambda, int fl
   for (int n = 0; n < order; ++n) {
     const float* facs[HBCSF_MAX_ORDER];
     for (int m = 0; m < order; ++m) facs[m] = factors[m];
-    with_rank(R, [&](auto r) {
-      constexpr int RR = decltype(r)::value;
-      hipLaunchKernelGGL(small_pinv_kernel<RR>, dim3(1), dim3(pinv_threads(RR)), 0, st, a->small, n, a->vp, a->p,
-                         a->tmp[0], lazy ? 1 : 0, a->report->stamp[n]);
-    });
-    const int rc = hbcsf_mttkrp(t, n, R, facs, a->m, st);
+    // a put-off update's inverse goes with the MTTKRP where it takes guests
+    const bool hosted = lazy && mttkrp_takes_guest(t, n, R);
+    auto invert = [&] {
+      with_rank(R, [&](auto r) {
+        constexpr int RR = decltype(r)::value;
+        hipLaunchKernelGGL(small_pinv_kernel<RR>, dim3(1), dim3(pinv_threads(RR)), 0, st, a->small, n, a->vp, a->p,
+                           a->tmp[0], lazy ? 1 : 0, hosted ? a->good : nullptr, hosted ? nullptr : a->report->stamp[n]);
+      });
+    };
+    int rc;
+    if (hosted) {
+      GuestArgs guest{};
+      guest.small = a->small;
+      guest.n = n;
+      guest.p = a->p;
+      guest.good = a->good;
+      guest.stamp = a->report->stamp[n];
+      rc = mttkrp_with_guest(t, n, R, facs, a->m, guest, st);
+    } else {
+      invert();
+      rc = hbcsf_mttkrp(t, n, R, facs, a->m, st);
+    }
     if (rc != HBCSF_OK) return rc;
+    if (hosted) invert();   // what is left of it
     if (lazy) {
       // A_n = M V^+ written unnormalised, with its Gram matrix
       nDots = launch_apply(a->m, t->dims[n], R, a->p, factors[n], a->gramScratch, a->gramSlots, a->small.gram[n],
@@ -1426,6 +1303,7 @@ int hbcsf_als_create(const hbcsf_tensor* t, int rank, void* workspace, uint64_t 
   for (int k = 0; k < 2; ++k) a->tmp[k] = (double*)(w + l.tmp[k]);
   a->inner = (double*)(w + l.inner);
   a->dots = (double*)(w + l.dots);
+  a->good = (int*)(w + l.good);
   a->small.order = t->order;
   for (int m = 0; m < t->order; ++m) {
     a->small.gram[m] = (double*)(w + l.gram) + (size_t)m * rank * rank;

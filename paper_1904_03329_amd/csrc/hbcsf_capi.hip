@@ -236,11 +236,30 @@ int hbcsf_upload(hbcsf_tensor* t, void* device_arena, uint64_t bytes, void* hip_
 
 namespace {
 
+// Some gathered factor matrix needs 64-bit row addressing (marks address one row further on, hence the + rowBytes); fiber
+// levels gathered with streaming loads take the wide form too.
+bool needs_wide(const hbcsf_tensor* t, const ModeFormat& f, uint64_t rowBytes) {
+  for (int l = 1; l < t->order; ++l) {
+    const uint64_t bytes = t->dims[f.levelMode[l]] * rowBytes;
+    if (bytes + rowBytes >= (1ull << 32) || (l < t->order - 1 && bytes >= t->streamBytes)) return true;
+  }
+  return false;
+}
+
+// 8 gathers in flight with parts of whole runs: at order 3 and runs of 64 four wavefronts per SIMD instead of five, but
+// half the staging per nonzero.  Pays there with rows of 128 bytes, narrow factor matrices and a stream that fills the
+// chip many times over (100 M nonzeros 2.15 -> 2.03 ms, 30 M 867 -> 841 us, 25 M 735 -> 727 and 926 -> 926, 20 M 578 ->
+// 579 and 496 -> 480, 12 M 370 -> 381, 5 M 181 -> 221); at other run lengths and orders only where the tuning key asks.
+bool long_parts(const hbcsf_tensor* t, const ModeFormat& f, int G, uint32_t lshift, bool wide) {
+  if (G != 8 || t->steps == 8) return G == 8;
+  return t->steps == 0 && t->order == 3 && lshift == 6 && !wide && f.g[kCsl].nnz + f.g[kCsf].nnz >= 25000000;
+}
+
 // The MTTKRP of both element types: `elem` = bytes per element of the factor matrices and the output (4: fp32,
 // 8: fp64; the tensor's values are fp32 either way).  The kernels see a row as G = rank * elem / 16 lanes of 16 bytes
 // and GroupArgs' float pointers as row addresses, so everything below the launch dispatch is shared.
 int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float* const* factors, float* out,
-               void* hip_stream) {
+               void* hip_stream, const GuestArgs* guest = nullptr) {
   if (!t || !factors || !out) return fail(HBCSF_EINVAL, "null argument");
   if (mode < 0 || mode >= t->order) return fail(HBCSF_EINVAL, "mode out of range");
   const bool f64 = elem == 8;
@@ -288,12 +307,7 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
     }
     return a;
   };
-  bool wide = false;  // some gathered factor matrix needs 64-bit row addressing
-  // (marks address one row further on, hence the + 1); fiber levels gathered with streaming loads take the wide form too
-  for (int l = 1; l < N; ++l) {
-    const uint64_t bytes = t->dims[f.levelMode[l]] * rowBytes;
-    wide = wide || bytes + rowBytes >= (1ull << 32) || (l < N - 1 && bytes >= t->streamBytes);
-  }
+  const bool wide = needs_wide(t, f, rowBytes);
 
   // 1. define every output row that no plain store will write; the COO group's rows are written
   //    in the same pass
@@ -333,15 +347,11 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
   const uint64_t sparseNnz = f.g[kCsl].nnz + f.g[kCsf].nnz;
   const bool runCsl = f.g[kCsl].nnz > 0 && (t->kernelMask & 4u), runCsf = f.g[kCsf].nnz > 0 && (t->kernelMask & 8u);
   const bool dense = t->denseMid == 1 && dense_mid_available(N, G, lshift);
-  // 8 gathers in flight with parts of whole runs: at order 3 and runs of 64 four wavefronts per SIMD instead of five, but
-  // half the staging per nonzero.  Pays there with rows of 128 bytes, narrow factor matrices and a stream that fills the
-  // chip many times over (100 M nonzeros 2.15 -> 2.03 ms, 30 M 867 -> 841 us, 25 M 735 -> 727 and 926 -> 926, 20 M 578 ->
-  // 579 and 496 -> 480, 12 M 370 -> 381, 5 M 181 -> 221); at other run lengths and orders only where the tuning key asks.
-  const bool longParts = G == 8 && (t->steps == 8 || (t->steps == 0 && N == 3 && lshift == 6 && !wide && sparseNnz >= 25000000));
+  const bool longParts = long_parts(t, f, G, lshift, wide);
   const int denseSteps = t->steps ? t->steps : N == 3 ? 8 : 4;
   // CSL and B-CSF group in one launch, unless their times are asked for one by one (or the kernel with 8 gathers
   // is used: with both bodies in it, it no longer fits four wavefronts per SIMD)
-  const bool together = runCsl && runCsf && !es && !dense && !longParts && !t->persistent;
+  const bool together = guest || (runCsl && runCsf && !es && !dense && !longParts && !t->persistent);
   auto sparse_args = [&](int g, uint32_t part) {
     const GroupFormat& gf = f.g[g];
     GroupArgs a = group_args(g);
@@ -389,10 +399,10 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
         uint64_t b = (gf.nnz + perBlock - 1) / perBlock;
         const uint64_t cap = (uint64_t)t->numCU * 16;
         if (b > cap) b = cap;
-        e = launch_group(f64, g, N, G, 4, wide, a, nullptr, round_up8(b), 256, 0, s);
+        e = launch_group(f64, g, N, G, 4, wide, a, nullptr, nullptr, round_up8(b), 256, 0, s);
         launched = true;
       }
-    } else if (g == kCsl ? runCsl && !together : runCsf) {
+    } else if (g == kCsl ? runCsl && !together : runCsf || guest) {
       const uint32_t part = g == kCsf && dense ? lshift
                             : longParts ? lshift
                                         : part_shift(together ? sparseNnz : gf.nnz, NG, lshift, t->numCU);
@@ -405,8 +415,8 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
       int wpb = 4;
       while (wpb > 1 && ldsWave * wpb > 48 * 1024) wpb >>= 1;
       // the launcher sizes the grid
-      e = launch_group(f64, g, N, G, a.denseMid ? denseSteps : longParts ? 8 : 4, wide, a, together ? &csl : nullptr, (uint32_t)t->numCU, 64 * wpb,
-                       ldsWave * wpb, s);
+      e = launch_group(f64, g, N, G, a.denseMid ? denseSteps : longParts ? 8 : 4, wide, a, together ? &csl : nullptr,
+                       guest, (uint32_t)t->numCU, 64 * wpb, ldsWave * wpb, s);
       launched = true;
     }
     if (launched && e != hipSuccess) return fail_hip(e, "launch of a group kernel");
@@ -423,6 +433,26 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
 }
 
 }  // namespace
+
+namespace hbcsf {
+
+// The launch of the plain fp32 kernels with 4 gathers in flight takes a guest up to rank 64 (above, the inverse wants more
+// threads than a block of theirs has); a tensor long enough for the other kernels hides nothing worth having.
+bool mttkrp_takes_guest(const hbcsf_tensor* t, int mode, int rank) {
+  if (rank > 64 || t->single || !t->ring.empty() || t->persistent || t->denseMid == 1 || t->kernelMask != 15u) return false;
+  const ModeFormat& f = *t->modes[mode];
+  uint32_t lshift = 0;
+  while ((1u << lshift) < f.L) ++lshift;
+  const bool wide = needs_wide(t, f, (uint64_t)rank * 4);
+  return f.g[kCsl].nnz + f.g[kCsf].nnz > 0 && !wide && !long_parts(t, f, rank / 4, lshift, wide);
+}
+
+int mttkrp_with_guest(const hbcsf_tensor* t, int mode, int rank, const float* const* factors, float* out, const GuestArgs& guest,
+                      hipStream_t s) {
+  return mttkrp_any(t, mode, rank, 4, factors, out, (void*)s, &guest);
+}
+
+}  // namespace hbcsf
 
 extern "C" {
 

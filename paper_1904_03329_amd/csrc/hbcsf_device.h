@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "hbcsf.h"
+
 namespace hbcsf {
 
 enum KernelKind { kCooKernel = 0, kCslKernel = 1, kCsfKernel = 2 };
@@ -28,6 +30,24 @@ constexpr uint32_t csf_wave_words(int order, int G, int ss, bool dense) {
 constexpr uint32_t csl_wave_words(int order, int G, int ss) {
   return ((64u / (uint32_t)G) << ss) * (uint32_t)(order + 1) + 256u;
 }
+
+// What a CPD-ALS state keeps per mode m in the caller's workspace: the Gram matrix of the stored factor, c_m (the
+// algorithm's factor is the stored one with column r divided by c_m[r]) and the column norms of the last update.
+struct SmallState {
+  double* gram[HBCSF_MAX_ORDER];
+  double* scale[HBCSF_MAX_ORDER];
+  double* norm[HBCSF_MAX_ORDER];
+  int order;
+};
+
+// The part of a put-off ALS update that an MTTKRP launch carries in its first block (hbcsf_small.h).
+struct GuestArgs {
+  SmallState small;
+  int n;                     // the mode being updated
+  float* p;                  // right-hand matrix of the product that follows
+  int* good;                 // receives 1 where the inverse succeeded, else 0
+  unsigned long long* stamp; // [2]
+};
 
 // Device pointers of one slice group of one mode, by tree level (0 = root .. order-1 = leaf).
 struct GroupArgs {
@@ -58,13 +78,16 @@ struct GroupArgs {
 // kind: KernelKind; order 3, 4 or 5; G = row bytes / 16 lanes per factor row (fp32: rank / 4 = 2, 4, 8, 16 or 32;
 // fp64: rank / 2 = 8, 16 or 32, the launch functions named ...64...);
 // steps = records a lane group keeps in flight (4, or at G = 8 also 8; not used for the COO group); csl = null, or with
-// kind = kCsfKernel and 4 steps the CSL group's arguments: both groups in one launch (same part size); wide = some
+// kind = kCsfKernel and 4 steps the CSL group's arguments: both groups in one launch (same part size); guest = null, or
+// (fp32, G <= 16, 4 steps, not wide, blocks of 256 threads, kind = kCsfKernel, either group perhaps without a nonzero) ALS
+// work for the first block of that launch; wide = some
 // gathered factor matrix is 4 GiB or larger (64-bit row addressing).  One launch function per (G, order) pair, each
 // compiled in its own object file.  For the CSL and B-CSF kernels `blocks` is the number of compute
 // units and the launcher sizes the grid (one wavefront per span, or persistent).
 #define HBCSF_DECLARE_LAUNCH(G, N)                                                                  \
   hipError_t launch_group_g##G##_n##N(int kind, int steps, bool wide, const GroupArgs& a,          \
-                                      const GroupArgs* csl, uint32_t blocks, uint32_t threads, size_t ldsBytes, hipStream_t s); \
+                                      const GroupArgs* csl, const GuestArgs* guest, uint32_t blocks, uint32_t threads, size_t ldsBytes, \
+                                      hipStream_t s);                                                \
   hipError_t launch_define_coo_g##G##_n##N(bool wide, const GroupArgs& a, const uint32_t* ownedBits,   \
                                            const uint32_t* cooBits, const uint32_t* cooPtr, uint64_t rows, \
                                            uint32_t blocks, hipStream_t s);
@@ -86,7 +109,8 @@ HBCSF_DECLARE_LAUNCH(32, 5)
 #undef HBCSF_DECLARE_LAUNCH
 #define HBCSF_DECLARE_LAUNCH64(G, N)                                                                  \
   hipError_t launch_group64_g##G##_n##N(int kind, int steps, bool wide, const GroupArgs& a,          \
-                                        const GroupArgs* csl, uint32_t blocks, uint32_t threads, size_t ldsBytes, hipStream_t s); \
+                                        const GroupArgs* csl, const GuestArgs* guest, uint32_t blocks, uint32_t threads, size_t ldsBytes, \
+                                        hipStream_t s);                                                \
   hipError_t launch_define_coo64_g##G##_n##N(bool wide, const GroupArgs& a, const uint32_t* ownedBits,   \
                                              const uint32_t* cooBits, const uint32_t* cooPtr, uint64_t rows, \
                                              uint32_t blocks, hipStream_t s);
@@ -103,12 +127,13 @@ HBCSF_DECLARE_LAUNCH64(32, 5)
 
 // f64: the factor matrices and the output hold doubles (GroupArgs' float pointers then address doubles).
 inline hipError_t launch_group(bool f64, int kind, int order, int G, int steps, bool wide, const GroupArgs& a,
-                               const GroupArgs* csl, uint32_t blocks, uint32_t threads, size_t ldsBytes, hipStream_t s) {
+                               const GroupArgs* csl, const GuestArgs* guest, uint32_t blocks, uint32_t threads, size_t ldsBytes,
+                               hipStream_t s) {
 #define HBCSF_CASE64(GV)                                                                              \
   case GV:                                                                                            \
-    return order == 3   ? launch_group64_g##GV##_n3(kind, steps, wide, a, csl, blocks, threads, ldsBytes, s) \
-           : order == 4 ? launch_group64_g##GV##_n4(kind, steps, wide, a, csl, blocks, threads, ldsBytes, s) \
-                        : launch_group64_g##GV##_n5(kind, steps, wide, a, csl, blocks, threads, ldsBytes, s);
+    return order == 3   ? launch_group64_g##GV##_n3(kind, steps, wide, a, csl, guest, blocks, threads, ldsBytes, s) \
+           : order == 4 ? launch_group64_g##GV##_n4(kind, steps, wide, a, csl, guest, blocks, threads, ldsBytes, s) \
+                        : launch_group64_g##GV##_n5(kind, steps, wide, a, csl, guest, blocks, threads, ldsBytes, s);
   if (f64) {
     switch (G) {
       HBCSF_CASE64(8)
@@ -121,9 +146,9 @@ inline hipError_t launch_group(bool f64, int kind, int order, int G, int steps, 
 #undef HBCSF_CASE64
 #define HBCSF_CASE(GV)                                                                              \
   case GV:                                                                                          \
-    return order == 3   ? launch_group_g##GV##_n3(kind, steps, wide, a, csl, blocks, threads, ldsBytes, s) \
-           : order == 4 ? launch_group_g##GV##_n4(kind, steps, wide, a, csl, blocks, threads, ldsBytes, s) \
-                        : launch_group_g##GV##_n5(kind, steps, wide, a, csl, blocks, threads, ldsBytes, s);
+    return order == 3   ? launch_group_g##GV##_n3(kind, steps, wide, a, csl, guest, blocks, threads, ldsBytes, s) \
+           : order == 4 ? launch_group_g##GV##_n4(kind, steps, wide, a, csl, guest, blocks, threads, ldsBytes, s) \
+                        : launch_group_g##GV##_n5(kind, steps, wide, a, csl, guest, blocks, threads, ldsBytes, s);
   switch (G) {
     HBCSF_CASE(2)
     HBCSF_CASE(4)

@@ -25,6 +25,9 @@
 #include <stdint.h>
 
 #include "hbcsf_device.h"
+#ifndef HBCSF_F64
+#include "hbcsf_small.h"
+#endif
 
 namespace hbcsf {
 
@@ -1355,6 +1358,25 @@ __global__ __launch_bounds__(256) void csl_csf_kernel(const GroupArgs csl, const
   else csf_group_body<G, N, SS, kSteps, WIDE, false>(csf, blockIdx.x - cslBlocks, gridDim.x - cslBlocks);
 }
 
+#ifndef HBCSF_F64
+// The same with ALS work in the launch's first block (of 8, so that the others keep their XCDs).  The inverse takes 110
+// registers: where units of 256 nonzeros fill the chip, the order-3 kernels are held to the 96 that leave five wavefronts
+// per SIMD.
+constexpr uint32_t kGuestBlocks = 8;
+template <int G, int N, int SS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(N == 3 && ((64 / G) << SS) == 256 ? 5 : 4)))
+void guest_csl_csf_kernel(const GroupArgs csl, const GroupArgs csf, uint32_t cslBlocks, const GuestArgs guest) {
+  extern __shared__ uint32_t lds[];
+  if (blockIdx.x < kGuestBlocks) {
+    if (blockIdx.x == 0) guest_block<4 * G>(guest, lds);
+    return;
+  }
+  const uint32_t block = blockIdx.x - kGuestBlocks, blocks = gridDim.x - kGuestBlocks;
+  if (block < cslBlocks) csl_group_body<G, N, SS, 4, false>(csl, block, cslBlocks);
+  else csf_group_body<G, N, SS, 4, false, false>(csf, block - cslBlocks, blocks - cslBlocks);
+}
+#endif
+
 // ---------------------------------------------------------------------------------------
 // COO group (Algorithm "COO-MTTKRP" restricted to slices with one nonzero): each nonzero owns
 // its output row, so the row is written with a plain store and no atomic is needed.
@@ -1506,9 +1528,24 @@ uint64_t span_blocks(const GroupArgs& a, uint32_t wpb) { return (((uint64_t)a.nS
 // `cus`: compute units.  Default launch: one wavefront per span.  Persistent launch: (resident blocks per CU) x CUs
 // blocks, capped by the spans.  Both rounded to a multiple of 8.
 template <int G, int N, int SS, int S, bool WIDE>
-hipError_t launch_one(int kind, const GroupArgs& a, const GroupArgs* csl, uint32_t cus, dim3 block, size_t lds, hipStream_t s) {
+hipError_t launch_one(int kind, const GroupArgs& a, const GroupArgs* csl, const GuestArgs* guest, uint32_t cus, dim3 block,
+                      size_t lds, hipStream_t s) {
   constexpr bool occ4 = G == 8 && N == 3 && S == 8 && !WIDE;
   const uint32_t wpb = block.x >> 6;
+  if (guest) {
+#ifndef HBCSF_F64
+    if constexpr (G <= 16 && S == 4 && !WIDE && (G != 8 || SS < 6)) {
+      constexpr int R = 4 * G;
+      if (!csl || block.x != 256) return hipErrorInvalidValue;
+      if (lds < guest_lds_bytes<R>()) lds = guest_lds_bytes<R>();
+      const uint32_t cslBlocks = (uint32_t)span_blocks(*csl, wpb);
+      hipLaunchKernelGGL((guest_csl_csf_kernel<G, N, SS>), dim3(kGuestBlocks + cslBlocks + (uint32_t)span_blocks(a, wpb)),
+                         block, lds, s, *csl, a, cslBlocks, *guest);
+      return hipGetLastError();
+    }
+#endif
+    return hipErrorInvalidValue;
+  }
   if (csl) {
     if constexpr (S == 4) {
       const uint32_t cslBlocks = (uint32_t)span_blocks(*csl, wpb);
@@ -1545,37 +1582,37 @@ hipError_t launch_one(int kind, const GroupArgs& a, const GroupArgs* csl, uint32
 }
 
 template <int G, int N, int SS>
-hipError_t launch_ss(int kind, int steps, bool wide, const GroupArgs& a, const GroupArgs* csl, uint32_t cus, dim3 block,
-                     size_t lds, hipStream_t s) {
+hipError_t launch_ss(int kind, int steps, bool wide, const GroupArgs& a, const GroupArgs* csl, const GuestArgs* guest, uint32_t cus,
+                     dim3 block, size_t lds, hipStream_t s) {
   if constexpr (G == 8) {
     if (steps == 8)
-      return wide ? launch_one<G, N, SS, 8, true>(kind, a, csl, cus, block, lds, s)
-                  : launch_one<G, N, SS, 8, false>(kind, a, csl, cus, block, lds, s);
+      return wide ? launch_one<G, N, SS, 8, true>(kind, a, csl, guest, cus, block, lds, s)
+                  : launch_one<G, N, SS, 8, false>(kind, a, csl, guest, cus, block, lds, s);
   }
   if (steps != 4) return hipErrorInvalidValue;
-  return wide ? launch_one<G, N, SS, 4, true>(kind, a, csl, cus, block, lds, s)
-              : launch_one<G, N, SS, 4, false>(kind, a, csl, cus, block, lds, s);
+  return wide ? launch_one<G, N, SS, 4, true>(kind, a, csl, guest, cus, block, lds, s)
+              : launch_one<G, N, SS, 4, false>(kind, a, csl, guest, cus, block, lds, s);
 }
 
 // The part sizes the caller can ask for at this G: units of at most 256 nonzeros, or at G = 8 parts of 64.
 template <int G, int N>
-hipError_t launch_g(int kind, int steps, bool wide, const GroupArgs& a, const GroupArgs* csl, dim3 grid, dim3 block,
-                    size_t lds, hipStream_t s) {
+hipError_t launch_g(int kind, int steps, bool wide, const GroupArgs& a, const GroupArgs* csl, const GuestArgs* guest,
+                    dim3 grid, dim3 block, size_t lds, hipStream_t s) {
   if (kind == kCooKernel) {
     if (wide) hipLaunchKernelGGL((coo_group_kernel<G, N, true>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((coo_group_kernel<G, N, false>), grid, block, 0, s, a);
     return hipGetLastError();
   }
   switch (a.partShift) {
-    case 3: return launch_ss<G, N, 3>(kind, steps, wide, a, csl, grid.x, block, lds, s);
+    case 3: return launch_ss<G, N, 3>(kind, steps, wide, a, csl, guest, grid.x, block, lds, s);
     case 4:
-      if constexpr (G >= 4) return launch_ss<G, N, 4>(kind, steps, wide, a, csl, grid.x, block, lds, s);
+      if constexpr (G >= 4) return launch_ss<G, N, 4>(kind, steps, wide, a, csl, guest, grid.x, block, lds, s);
       break;
     case 5:
-      if constexpr (G >= 8) return launch_ss<G, N, 5>(kind, steps, wide, a, csl, grid.x, block, lds, s);
+      if constexpr (G >= 8) return launch_ss<G, N, 5>(kind, steps, wide, a, csl, guest, grid.x, block, lds, s);
       break;
     case 6:
-      if constexpr (G >= 8) return launch_ss<G, N, 6>(kind, steps, wide, a, csl, grid.x, block, lds, s);
+      if constexpr (G >= 8) return launch_ss<G, N, 6>(kind, steps, wide, a, csl, guest, grid.x, block, lds, s);
       break;
   }
   return hipErrorInvalidValue;
@@ -1613,9 +1650,9 @@ hipError_t HBCSF_CAT(HBCSF_LAUNCH_DEFINE_COO, HBCSF_G, _n, HBCSF_N)(bool wide, c
 }
 
 hipError_t HBCSF_CAT(HBCSF_LAUNCH_GROUP, HBCSF_G, _n, HBCSF_N)(int kind, int steps, bool wide, const GroupArgs& a,
-                                                          const GroupArgs* csl, uint32_t blocks, uint32_t threads, size_t ldsBytes,
-                                                          hipStream_t s) {
-  return launch_g<HBCSF_G, HBCSF_N>(kind, steps, wide, a, csl, dim3(blocks), dim3(threads), ldsBytes, s);
+                                                          const GroupArgs* csl, const GuestArgs* guest, uint32_t blocks,
+                                                          uint32_t threads, size_t ldsBytes, hipStream_t s) {
+  return launch_g<HBCSF_G, HBCSF_N>(kind, steps, wide, a, csl, guest, dim3(blocks), dim3(threads), ldsBytes, s);
 }
 
 #if HBCSF_G == 8 && !defined(HBCSF_F64)

@@ -52,6 +52,12 @@ int fail_hip(hipError_t e, const char* what);
 // (std::bad_alloc -> HBCSF_ENOMEM, anything else -> HBCSF_EINVAL with its text) and never throws itself.
 int fail_exception() noexcept;
 
+// hbcsf_mttkrp with ALS work in the same launch, for calls that take it (fp32).
+struct GuestArgs;
+bool mttkrp_takes_guest(const hbcsf_tensor* t, int mode, int rank);
+int mttkrp_with_guest(const hbcsf_tensor* t, int mode, int rank, const float* const* factors, float* out, const GuestArgs& guest,
+                      hipStream_t s);
+
 }  // namespace hbcsf
 
 // Every entry point that returns an error code is a function-try-block closed by this handler, so that no C++
