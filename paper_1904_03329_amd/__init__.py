@@ -10,6 +10,20 @@ from . import binding
 
 __all__ = ["binding", "HbcsfTensor", "CpdAls"]
 
+_native_mttkrp = None
+
+
+def _load_native():
+    """The native form of HbcsfTensor.mttkrp (built with the library; its absence is an error like the library's)."""
+    global _native_mttkrp
+    import torch  # noqa: F401  (its libraries have to be there first)
+
+    binding.lib()
+    from . import _hbcsf_torch
+
+    _native_mttkrp = _hbcsf_torch.mttkrp
+    return _native_mttkrp
+
 
 class HbcsfTensor:
     """A sparse tensor built into per-mode HB-CSF, optionally resident on the current GPU."""
@@ -70,6 +84,13 @@ class HbcsfTensor:
     def mttkrp(self, mode: int, factors, out=None):
         """factors: one CUDA [dims[m], R] tensor per mode (entry `mode` may be None), all float32 or all float64
         (float64: fp64 partial sums and output, hbcsf_mttkrp_f64)."""
+        if self.handle is not None:
+            done = (_native_mttkrp or _load_native())(self.handle.value, self.dims, mode, factors, out)
+            if done is not None:
+                if type(done) is int:
+                    binding._check(done)
+                return done
+        # not such a call as is served there: the checks that say why, and whatever else is accepted
         import torch
 
         rank = None

@@ -1,4 +1,4 @@
-"""Builds libhbcsf.so (host format builder + gfx950 kernels + C ABI) in-tree."""
+"""Builds libhbcsf.so (host format builder + gfx950 kernels + C ABI) and the torch call on top of it in-tree."""
 from __future__ import annotations
 
 import os
@@ -9,6 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 SO = os.path.join(HERE, "libhbcsf.so")
+TORCH_SO = os.path.join(HERE, "_hbcsf_torch.so")
 
 HIP_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-munsafe-fp-atomics",
@@ -53,7 +54,23 @@ def build(verbose: bool = False) -> str:
     with ThreadPoolExecutor(workers) as pool:
         list(pool.map(run, jobs))
     run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", SO] + objs + ["-lgomp"])
+    build_torch_call(run)
     return SO
+
+
+def build_torch_call(run) -> None:
+    """The native MTTKRP call on torch tensors: host code only, against the headers and libraries of the torch in use."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    inc = [INCLUDE, CSRC, sysconfig.get_paths()["include"]] + cpp_extension.include_paths("cuda")
+    libs = cpp_extension.library_paths("cuda")
+    run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+         f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-o", TORCH_SO,
+         os.path.join(CSRC, "hbcsf_torch.cpp")] + [f"-I{d}" for d in inc] + [f"-L{d}" for d in libs + [HERE]]
+        + ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-l:libhbcsf.so", "-Wl,-rpath,$ORIGIN"])
 
 
 if __name__ == "__main__":

@@ -1,0 +1,85 @@
+"""HbcsfTensor.mttkrp: calls served natively and calls that go through the checks in Python give one result and one error."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+DIMS = (40, 30, 20)
+
+
+@pytest.fixture(scope="module")
+def problem(synth):
+    import torch  # noqa: F401
+
+    from paper_1904_03329_amd import HbcsfTensor
+
+    t = synth.tensor(DIMS, 3000, (0.0, 0.0, 0.0), seed=4)
+    ht = HbcsfTensor(DIMS, t.inds, t.vals).to_device()
+    yield t, ht
+    ht.close()
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("rank", [16, 32])
+def test_forms_of_a_call(oracle, synth, problem, rank, dtype):
+    import torch
+
+    import gpu_util as GU
+
+    t, ht = problem
+    facs = [f.astype(dtype) for f in synth.factors(DIMS, rank, seed=5)]
+    ref, tol = (oracle.mttkrp_f64, GU.REL_TOL_F64) if dtype == np.float64 else (oracle.mttkrp, GU.REL_TOL)
+    dev = [torch.from_numpy(f).cuda() for f in facs]
+    for mode in range(3):
+        want = ref(DIMS, t.inds, t.vals, facs, mode)
+        others = [None if m == mode else f for m, f in enumerate(dev)]
+        out = torch.empty((DIMS[mode], rank), dtype=dev[0].dtype, device="cuda")
+        forms = [lambda: ht.mttkrp(mode, dev), lambda: ht.mttkrp(mode, others), lambda: ht.mttkrp(mode, tuple(others)),
+                 lambda: ht.mttkrp(mode, dict(enumerate(others))), lambda: ht.mttkrp(np.int64(mode), others),
+                 lambda: ht.mttkrp(mode, [torch.nn.Parameter(f) for f in dev]), lambda: ht.mttkrp(mode, dev, out)]
+        for k, form in enumerate(forms):
+            got = form()
+            assert got.shape == (DIMS[mode], rank) and got.dtype == dev[0].dtype and got.device == dev[0].device
+            GU.assert_close(got.cpu().numpy(), want, f"form {k} mode {mode}", tol)
+        assert ht.mttkrp(mode, dev, out) is out
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            got = ht.mttkrp(mode, others)
+        side.synchronize()
+        GU.assert_close(got.cpu().numpy(), want, f"other stream, mode {mode}", tol)
+
+
+def test_refused_calls(problem):
+    import torch
+
+    from paper_1904_03329_amd import HbcsfTensor, binding as B
+
+    _, ht = problem
+    f = [torch.rand((d, 16), device="cuda") for d in DIMS]
+
+    def but(m, x):
+        return [x if k == m else v for k, v in enumerate(f)]
+
+    for factors in (but(1, f[1].cpu()), but(1, f[1].double()), but(1, f[1].half()), but(1, f[1][:-1]), but(2, f[2][:, :8].contiguous()),
+                    but(1, torch.rand((16, DIMS[1]), device="cuda").t()), [x.half() for x in f]):
+        with pytest.raises(ValueError):
+            ht.mttkrp(0, factors)
+    for out in (torch.empty((DIMS[0], 8), device="cuda"), torch.empty((DIMS[0], 16)), torch.empty((DIMS[1], 16), device="cuda"),
+                torch.empty((DIMS[0], 16), dtype=torch.float64, device="cuda"), torch.empty((16, DIMS[0]), device="cuda").t()):
+        with pytest.raises(ValueError):
+            ht.mttkrp(0, f, out)
+    with pytest.raises(B.HbcsfError, match="a factor pointer is null"):
+        ht.mttkrp(0, but(1, None))
+    with pytest.raises(B.HbcsfError, match="rank must be"):
+        ht.mttkrp(0, [x[:, :4].contiguous() for x in f])
+    with pytest.raises(B.HbcsfError, match="16-byte aligned"):
+        ht.mttkrp(0, but(1, torch.rand(DIMS[1] * 16 + 1, device="cuda")[1:].view(DIMS[1], 16)))
+    with pytest.raises(IndexError):
+        ht.mttkrp(3, f)
+    closed = HbcsfTensor(DIMS, [np.zeros(1, dtype=np.uint32)] * 3, np.ones(1, dtype=np.float32))
+    with pytest.raises(B.HbcsfError, match="hbcsf_upload has not been called"):
+        closed.mttkrp(0, f)
+    closed.close()
+    with pytest.raises(B.HbcsfError, match="null argument"):
+        closed.mttkrp(0, f)
