@@ -493,10 +493,10 @@ struct GroupCountsPlus {
     return r;
   }
 };
-struct SliceInfo {
-  uint32_t off, ord;  // first place in the group's stream, number in the group
+struct alignas(16) SliceInfo {  // one load of 16 bytes; its differences are modulo 2^32
+  uint32_t shift, ord;  // place in the group's stream minus sorted place, number in the group
   uint32_t grp;
-  uint32_t fib0;      // CSF: level-1 fibers before the slice
+  uint32_t fib0;        // CSF: level-1 fibers before the slice in its group minus those before it at all
 };
 struct Totals {
   uint32_t bad, S, fibNat[3];
@@ -511,7 +511,7 @@ struct Numbers {
   uint32_t* fStart[3];   // [S + 1] fibers of each level before the slice
   GroupCounts* block;    // [slice blocks + 1] counts per block of slices, then before each
   SliceInfo* info;       // [S]
-  uint32_t* fib[2];      // [S] CSF: fibers of levels 2, 3 before the slice
+  uint32_t* fib[2];      // [S] as fib0, levels 2, 3
   uint32_t* csfOff;      // by CSF slice: its first place in the stream,
   uint32_t* csfStart;    //               its first sorted nonzero
   Count4* cut;           // [runs + 1] cuts inside a fiber, per run, then before each
@@ -528,6 +528,51 @@ __device__ __forceinline__ uint32_t begins(const Key* __restrict__ K, size_t p, 
   return b;
 }
 
+// x of the lane before; lane 0: `first`
+template <typename Key>
+__device__ __forceinline__ Key lane_before(Key x, Key first, int lane) {
+  uint32_t w[sizeof(Key) / 4];
+  __builtin_memcpy(w, &x, sizeof(Key));
+#pragma unroll
+  for (uint32_t& k : w) k = __shfl_up(k, 1);
+  __builtin_memcpy(&x, w, sizeof(Key));
+  return lane == 0 ? first : x;
+}
+
+template <typename Key>
+__device__ __forceinline__ Key last_lane(Key x) {
+  uint32_t w[sizeof(Key) / 4];
+  __builtin_memcpy(w, &x, sizeof(Key));
+#pragma unroll
+  for (uint32_t& k : w) k = __builtin_amdgcn_readlane(k, 63);
+  __builtin_memcpy(&x, w, sizeof(Key));
+  return x;
+}
+
+// (The two kernels below, 50 M nonzeros: 106 -> 92 and 107 -> 88 us, 4.4 TB/s, with one load a nonzero and four in flight.)
+// Keys and begins of the kFill chunks of 64 sorted nonzeros from p0 on (a whole wavefront), zeros past M.  last: the key
+// before p0, then the last one here.
+constexpr int kFill = 4;
+template <typename Key>
+__device__ __forceinline__ void load_chunks(const Key* __restrict__ K, size_t p0, size_t M, const Spec& sp, int lane, Key& last,
+                                            Key (&key)[kFill], uint32_t (&b)[kFill]) {
+#pragma unroll
+  for (int q = 0; q < kFill; ++q) {
+    const size_t p = p0 + q * 64 + lane;
+    key[q] = 0;
+    if (p < M) key[q] = K[p];
+  }
+#pragma unroll
+  for (int q = 0; q < kFill; ++q) {
+    const size_t p = p0 + q * 64 + lane;
+    const Key x = key[q] ^ lane_before(key[q], last, lane);
+    last = last_lane(key[q]);
+    b[q] = 0;
+    for (int l = 0; l <= sp.NF; ++l) b[q] |= (p == 0 || (x & (Key)sp.upTo[l]) != 0 ? 1u : 0u) << l;
+    if (p >= M) b[q] = 0;
+  }
+}
+
 template <typename Key>
 __global__ __launch_bounds__(256) void count_tiles_kernel(const Key* __restrict__ K, size_t M, Spec sp, uint32_t tiles,
                                                           Count4* __restrict__ tile) {
@@ -536,12 +581,17 @@ __global__ __launch_bounds__(256) void count_tiles_kernel(const Key* __restrict_
   if (t > tiles) return;
   Count4 c{{0, 0, 0, 0}};
   if (t < tiles) {
-    for (uint32_t j = 0; j < kTile; j += 64) {
-      const size_t p = (size_t)t * kTile + j + lane;
-      const uint32_t b = p < M ? begins(K, p, sp) : 0u;
+    const size_t p0 = (size_t)t * kTile;
+    Key last = p0 ? K[p0 - 1] : Key(0);
+    for (uint32_t j = 0; j < kTile; j += 64 * kFill) {
+      Key key[kFill];
+      uint32_t b[kFill];
+      load_chunks(K, p0 + j, M, sp, lane, last, key, b);
 #pragma unroll
-      for (int l = 0; l < 4; ++l)
-        if (l <= sp.NF) c.v[l] += (uint32_t)__popcll(__ballot((b >> l) & 1u));
+      for (int q = 0; q < kFill; ++q)
+#pragma unroll
+        for (int l = 0; l < 4; ++l)
+          if (l <= sp.NF) c.v[l] += (uint32_t)__popcll(__ballot((b[q] >> l) & 1u));
     }
   }
   if (lane == 0) tile[t] = c;
@@ -555,28 +605,40 @@ __global__ __launch_bounds__(256) void slice_tables_kernel(const Key* __restrict
   if (t >= tiles) return;
   Count4 c = n.tile[t];
   const unsigned long long below = (1ull << lane) - 1ull;
-  for (uint32_t j = 0; j < kTile; j += 64) {
-    const size_t p = (size_t)t * kTile + j + lane;
-    const uint32_t b = p < M ? begins(K, p, sp) : 0u;
-    uint32_t before[4];
+  const size_t p0 = (size_t)t * kTile;
+  Key last = p0 ? K[p0 - 1] : Key(0);
+  for (uint32_t j = 0; j < kTile; j += 64 * kFill) {
+    Key key[kFill];
+    uint32_t begun[kFill];
+    load_chunks(K, p0 + j, M, sp, lane, last, key, begun);
 #pragma unroll
-    for (int l = 0; l < 4; ++l) {
-      before[l] = 0;
-      if (l <= sp.NF) {
-        const unsigned long long w = __ballot((b >> l) & 1u);
-        before[l] = c.v[l] + (uint32_t)__popcll(w & below);
-        c.v[l] += (uint32_t)__popcll(w);
+    for (int q = 0; q < kFill; ++q) {
+      const size_t p = p0 + j + q * 64 + lane;
+      const uint32_t b = begun[q];
+      uint32_t before[4];
+#pragma unroll
+      for (int l = 0; l < 4; ++l) {
+        before[l] = 0;
+        if (l <= sp.NF) {
+          const unsigned long long w = __ballot((b >> l) & 1u);
+          before[l] = c.v[l] + (uint32_t)__popcll(w & below);
+          c.v[l] += (uint32_t)__popcll(w);
+        }
       }
-    }
-    if (b & 1u) {
-      n.sStart[before[0]] = (uint32_t)p;
-      for (int l = 1; l <= sp.NF; ++l) n.fStart[l - 1][before[0]] = before[l];
-    }
-    if (p == M - 1) {  // one past the last slice
-      const uint32_t S = before[0] + (b & 1u);
-      n.sStart[S] = (uint32_t)M;
-      for (int l = 1; l <= sp.NF; ++l) n.fStart[l - 1][S] = before[l] + ((b >> l) & 1u);
-      n.count[0] = S;
+      if (b & 1u) {
+        n.sStart[before[0]] = (uint32_t)p;
+#pragma unroll
+        for (int l = 1; l < 4; ++l)
+          if (l <= sp.NF) n.fStart[l - 1][before[0]] = before[l];
+      }
+      if (p == M - 1) {  // one past the last slice
+        const uint32_t S = before[0] + (b & 1u);
+        n.sStart[S] = (uint32_t)M;
+#pragma unroll
+        for (int l = 1; l < 4; ++l)
+          if (l <= sp.NF) n.fStart[l - 1][S] = before[l] + ((b >> l) & 1u);
+        n.count[0] = S;
+      }
     }
   }
 }
@@ -653,16 +715,17 @@ __global__ __launch_bounds__(256) void number_slices_kernel(Numbers n, Spec sp) 
     if (s < S) own = slice_counts(n, sp, (uint32_t)s, g);
     const GroupCounts upTo = block_sum(own, total);
     if (s < S) {
+      const uint32_t off = before.m[g] + upTo.m[g] - own.m[g], start = n.sStart[s];
       SliceInfo i;
-      i.off = before.m[g] + upTo.m[g] - own.m[g];
+      i.shift = off - start;
       i.ord = before.s[g] + upTo.s[g] - own.s[g];
       i.grp = (uint32_t)g;
-      i.fib0 = before.f[0] + upTo.f[0] - own.f[0];
+      i.fib0 = before.f[0] + upTo.f[0] - own.f[0] - n.fStart[0][s];
       n.info[s] = i;
-      for (int l = 1; l < sp.NF; ++l) n.fib[l - 1][s] = before.f[l] + upTo.f[l] - own.f[l];
+      for (int l = 1; l < sp.NF; ++l) n.fib[l - 1][s] = before.f[l] + upTo.f[l] - own.f[l] - n.fStart[l][s];
       if (g == kCsf) {
-        n.csfOff[i.ord] = i.off;
-        n.csfStart[i.ord] = n.sStart[s];
+        n.csfOff[i.ord] = off;
+        n.csfStart[i.ord] = start;
       }
     }
     before = plus(before, total);
@@ -705,9 +768,11 @@ __global__ void totals_kernel(Numbers n, Spec sp, uint32_t tiles, uint32_t block
 }
 
 // Every nonzero writes itself into its group's stream; segment starts write the fiber-level entries.  A wavefront takes
-// kFill chunks of 64 nonzeros at a time and issues the loads of all of them first (keys, values; then slice tables), since
-// each nonzero's chain key -> slice -> place is three loads long and the stores between them may not be passed by a load.
-constexpr int kFill = 4;
+// kFill chunks of 64 nonzeros at a time and issues the loads of all of them first (keys, values; then slice tables; then
+// cuts), since each nonzero's chain key -> slice -> place -> cuts is four loads long and the stores between them may not be
+// passed by a load.  What bounds it is the number of vector-memory instructions, hence tables of differences (one entry
+// instead of two) and the key before from the lane before: order 4, 50 M nonzeros, 768 -> 634 us a mode against separate
+// tables with the fiber and cut entries loaded between the stores (of that, the stores of the row marks are 130 us).
 template <typename Key, int N>
 __global__ __launch_bounds__(256) void fill_tiles_kernel(const Key* __restrict__ K, const uint32_t* __restrict__ V, size_t M,
                                                          Spec sp, uint32_t tiles, Numbers n, OutArrays o) {
@@ -717,91 +782,98 @@ __global__ __launch_bounds__(256) void fill_tiles_kernel(const Key* __restrict__
   Count4 c = n.tile[t];
   const unsigned long long below = (1ull << lane) - 1ull;
   constexpr int leaf = N - 1, NF = N - 2;
+  const uint32_t ls = __builtin_ctz(sp.L);  // runs are of 8, 16, 32 or 64 nonzeros
+  const size_t p0 = (size_t)t * kTile;
+  Key last = p0 ? K[p0 - 1] : Key(0);
   for (uint32_t j0 = 0; j0 < kTile; j0 += 64 * kFill) {
     Key key[kFill];
-    uint32_t b[kFill], v[kFill], s[kFill], begun[kFill][3], start[kFill], leafIdx[kFill];
+    uint32_t b[kFill], v[kFill], begun[kFill][NF], fib[kFill][NF], pos[kFill], cuts[kFill][NF], leafIdx[kFill];
     SliceInfo in[kFill];
 #pragma unroll
     for (int q = 0; q < kFill; ++q) {
-      const size_t p = (size_t)t * kTile + j0 + q * 64 + lane;
-      b[q] = 0;
-      key[q] = 0;
+      const size_t p = p0 + j0 + q * 64 + lane;
       v[q] = 0;
-      if (p < M) {
-        b[q] = begins(K, p, sp);
-        key[q] = K[p];
-        v[q] = V[p];
-      }
+      if (p < M) v[q] = V[p];
     }
+    load_chunks(K, p0 + j0, M, sp, lane, last, key, b);
 #pragma unroll
     for (int q = 0; q < kFill; ++q) {
-      const size_t p = (size_t)t * kTile + j0 + q * 64 + lane;
-      s[q] = 0;
+      const size_t p = p0 + j0 + q * 64 + lane;
+      uint32_t s = 0;
 #pragma unroll
       for (int l = 0; l <= NF; ++l) {  // begun before p
         const unsigned long long w = __ballot((b[q] >> l) & 1u);
         const uint32_t before = c.v[l] + (uint32_t)__popcll(w & below);
         c.v[l] += (uint32_t)__popcll(w);
-        if (l == 0) s[q] = before + (b[q] & 1u) - 1u;
+        if (l == 0) s = before + (b[q] & 1u) - 1u;
         else begun[q][l > 0 ? l - 1 : 0] = before;
       }
       if (p < M) {
-        in[q] = n.info[s[q]];
-        start[q] = n.sStart[s[q]];
+        in[q] = n.info[s];
+#pragma unroll
+        for (int l = 2; l <= NF; ++l) fib[q][l - 1] = n.fib[l - 2][s];
       }
     }
 #pragma unroll
     for (int q = 0; q < kFill; ++q) {
+      const size_t p = p0 + j0 + q * 64 + lane;
       leafIdx[q] = (uint32_t)((uint64_t)(key[q] >> sp.shift[leaf]) & sp.mask[leaf]);
+      if (p < M) {
+        pos[q] = (uint32_t)p + in[q].shift;
+        fib[q][0] = in[q].fib0;
+        if (in[q].grp == kCsf) {  // cuts before this place
+          const Count4& at = n.cut[(pos[q] + sp.L - 1u) >> ls];
+#pragma unroll
+          for (int l = 1; l <= NF; ++l) cuts[q][l - 1] = at.v[l];
+        }
+      }
     }
 #pragma unroll
     for (int q = 0; q < kFill; ++q) {
-      const size_t p = (size_t)t * kTile + j0 + q * 64 + lane;
-      if (p >= M) continue;
-      const uint32_t pos = in[q].off + ((uint32_t)p - start[q]);
+      if (p0 + j0 + q * 64 + lane >= M) continue;
+      const uint32_t at = pos[q];
       auto index = [&](int l) { return (uint32_t)((uint64_t)(key[q] >> sp.shift[l]) & sp.mask[l]); };
-      const bool cut = (pos & (sp.L - 1u)) == 0;
+      const bool cut = (at & (sp.L - 1u)) == 0;
       if (in[q].grp == kCsf) {
-        o.csfVal[pos] = v[q];
-        o.csfInd[leaf][pos] = leafIdx[q];
+        o.csfVal[at] = v[q];
+        o.csfInd[leaf][at] = leafIdx[q];
         mark_row(sp, leaf, o.seen[kCsf][leaf], leafIdx[q]);
-        if (cut) o.csfRun[0][pos / sp.L] = in[q].ord;
+        if (cut) o.csfRun[0][at >> ls] = in[q].ord;
 #pragma unroll
         for (int l = 1; l <= NF; ++l) {
           if (cut || ((b[q] >> l) & 1u)) {
             // fibers before the slice and in it, cuts before this place
-            const uint32_t fibers = l == 1 ? in[q].fib0 : n.fib[l == 3 ? 1 : 0][s[q]];
-            const uint32_t id = fibers + begun[q][l - 1] - n.fStart[l - 1][s[q]] + n.cut[(pos + sp.L - 1u) / sp.L].v[l];
+            const uint32_t id = fib[q][l - 1] + begun[q][l - 1] + cuts[q][l - 1];
             const uint32_t i = index(l);
             o.csfInd[l][id] = i;
-            o.csfPtr[l][id] = pos;
+            o.csfPtr[l][id] = at;
             mark_row(sp, l, o.seen[kCsf][l], i);
-            if (cut) o.csfRun[l][pos / sp.L] = id;
+            if (cut) o.csfRun[l][at >> ls] = id;
           }
         }
       } else if (in[q].grp == kCsl) {
-        o.cslVal[pos] = v[q];
-        if (cut) o.cslRun[pos / sp.L] = in[q].ord;
-        o.cslInd[leaf][pos] = leafIdx[q];
+        o.cslVal[at] = v[q];
+        if (cut) o.cslRun[at >> ls] = in[q].ord;
+        o.cslInd[leaf][at] = leafIdx[q];
         mark_row(sp, leaf, o.seen[kCsl][leaf], leafIdx[q]);
 #pragma unroll
         for (int l = 1; l < leaf; ++l) {
           const uint32_t i = index(l);
-          o.cslInd[l][pos] = i;
+          o.cslInd[l][at] = i;
           mark_row(sp, l, o.seen[kCsl][l], i);
         }
       } else {
-        o.cooVal[pos] = v[q];
-        o.cooInd[leaf][pos] = leafIdx[q];
+        o.cooVal[at] = v[q];
+        o.cooInd[leaf][at] = leafIdx[q];
         mark_row(sp, leaf, o.seen[kCoo][leaf], leafIdx[q]);
 #pragma unroll
         for (int l = 1; l < leaf; ++l) {
           const uint32_t i = index(l);
-          o.cooInd[l][pos] = i;
+          o.cooInd[l][at] = i;
           mark_row(sp, l, o.seen[kCoo][l], i);
         }
         const uint32_t root = index(0);
-        if (!sp.cooRowFlags) o.cooInd[0][pos] = root;
+        if (!sp.cooRowFlags) o.cooInd[0][at] = root;
         atomicOr(&o.cooBits[root >> 5], 1u << (root & 31));
         atomicOr(&o.owned[root >> 5], 1u << (root & 31));
       }
@@ -819,11 +891,12 @@ __global__ __launch_bounds__(256) void fill_slice_entries_kernel(const Key* __re
     if (in.grp == kCoo) continue;
     const uint32_t b = n.sStart[s], m = n.sStart[s + 1] - b;
     const uint32_t root = (uint32_t)((uint64_t)(K[b] >> sp.shift[0]) & sp.mask[0]);
-    const bool own = sp.blockBits == 0 && (in.off / sp.L) == ((in.off + m - 1) / sp.L);
+    const uint32_t off = in.shift + b;
+    const bool own = sp.blockBits == 0 && (off / sp.L) == ((off + m - 1) / sp.L);
     uint32_t* ind = in.grp == kCsl ? o.cslInd[0] : o.csfInd[0];
     uint32_t* ptr = in.grp == kCsl ? o.cslPtr : o.csfPtr[0];
     ind[in.ord] = root | (own ? kOwnedBit : 0u);
-    ptr[in.ord] = in.off;
+    ptr[in.ord] = off;
     if (own) atomicOr(&o.owned[root >> 5], 1u << (root & 31));
     else ++shared;
   }
