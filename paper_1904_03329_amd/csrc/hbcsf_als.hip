@@ -677,7 +677,7 @@ __device__ void jacobi_pinv(const SmallState& st, int n, JacobiLds<R>& lds, doub
 // overwrites it).  A pivot of the sweep that is not safely positive sends the whole workgroup to the eigenvalue form.
 // resetScale: after the product the stored factor is the unnormalised one, so its column scale becomes 1.
 // hosted: null, or the outcome of the sweep that ran beside the MTTKRP: where that was good, all is done, and where it was
-// not only the eigenvalue form is left.
+// not only the eigenvalue form is left.  stamp: when it begins and ends (nothing where all is done).
 template <int R>
 __global__ __launch_bounds__(pinv_threads(R)) void small_pinv_kernel(SmallState st, int n, double* __restrict__ vp,
                                                                       float* __restrict__ p, double* __restrict__ jq,
@@ -1006,13 +1006,15 @@ struct hbcsf_als {
   // Pinned host memory the kernels of an iteration write: {<X, model>, ||model||^2}, and wall-clock stamps (taken by a
   // thread of each kernel as it begins: an event record between two kernels costs 5.6 us on the stream, as much as
   // many of the kernels).  Per mode: inverse begins, inverse ends, Gram or product begins, R x R part after the Gram
-  // begins; one more at the iteration's end.
+  // begins; one more at the iteration's end.  Where the inverse goes with the MTTKRP the first two are: MTTKRP begins,
+  // eigenvalue form begins (0: it was not needed).
   struct Report {
     double value[2];
     unsigned long long stamp[HBCSF_MAX_ORDER][4], end;
   };
   Report* report = nullptr;
   double msPerTick = 1e-5;
+  bool hosted[HBCSF_MAX_ORDER] = {};  // the last iteration's inverse of the mode went with the MTTKRP
   bool timed = false;      // an iteration has been enqueued
   bool timedGram = false;  // ... an ordinary one: stamp[.][3] is set too
 
@@ -1141,12 +1143,13 @@ int enqueue_iteration(hbcsf_als* a, float* const* factors, float* lambda, int fl
     const float* facs[HBCSF_MAX_ORDER];
     for (int m = 0; m < order; ++m) facs[m] = factors[m];
     // a put-off update's inverse goes with the MTTKRP where it takes guests
-    const bool hosted = lazy && mttkrp_takes_guest(t, n, R);
+    // (what is left of it then begins at stamp 1, and its end, at stamp 2, is overwritten by the product that follows)
+    const bool hosted = a->hosted[n] = lazy && mttkrp_takes_guest(t, n, R);
     auto invert = [&] {
       with_rank(R, [&](auto r) {
         constexpr int RR = decltype(r)::value;
         hipLaunchKernelGGL(small_pinv_kernel<RR>, dim3(1), dim3(pinv_threads(RR)), 0, st, a->small, n, a->vp, a->p,
-                           a->tmp[0], lazy ? 1 : 0, hosted ? a->good : nullptr, hosted ? nullptr : a->report->stamp[n]);
+                           a->tmp[0], lazy ? 1 : 0, hosted ? a->good : nullptr, a->report->stamp[n] + (hosted ? 1 : 0));
       });
     };
     int rc;
@@ -1397,8 +1400,14 @@ int hbcsf_als_phase_ms(const hbcsf_als* a, float ms[4]) try {
   for (int n = 0; n < order; ++n) {
     const unsigned long long* at = a->report->stamp[n];
     const unsigned long long end = n + 1 < order ? a->report->stamp[n + 1][0] : a->report->end;
-    add(ms[2], at[0], at[1]);
-    add(ms[0], at[1], at[2]);
+    if (a->hosted[n]) {
+      const unsigned long long mttkrpEnd = at[1] ? at[1] : at[2];
+      add(ms[0], at[0], mttkrpEnd);
+      add(ms[2], mttkrpEnd, at[2]);
+    } else {
+      add(ms[2], at[0], at[1]);
+      add(ms[0], at[1], at[2]);
+    }
     if (a->timedGram) add(ms[1], at[2], at[3]);
     add(ms[3], at[a->timedGram ? 3 : 2], end);
   }

@@ -315,6 +315,7 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
   // (without stored root indices only the fused pass can place the COO group's rows)
   const bool wantFuse = f.cooRowFlags || t->fuseCoo == 1 ||
                         (t->fuseCoo == 2 && f.rows * rowBytes <= (64ull << 20));
+  unsigned long long* const stamp = guest ? guest->stamp : nullptr;
   const bool fuseCoo = wantFuse && (t->kernelMask & 3u) == 3u && f.g[kCoo].nnz > 0;
   if (t->kernelMask & 1u) {
     // one wavefront per 8 x 32 rows, capped at 64 wavefronts per compute unit
@@ -332,9 +333,9 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
       a.nnz = (uint32_t)f.g[kCoo].nnz;
       e = launch_define_coo(f64, N, G, wide, a, (const uint32_t*)(base + f.ownedBits.off),
                             (const uint32_t*)(base + f.cooBits.off), (const uint32_t*)(base + f.cooPtr.off),
-                            f.rows, (uint32_t)blocks, s);
+                            f.rows, (uint32_t)blocks, stamp, s);
     } else {
-      e = launch_define(out, (const uint32_t*)(base + f.ownedBits.off), f.rows, G, (uint32_t)blocks, s);
+      e = launch_define(out, (const uint32_t*)(base + f.ownedBits.off), f.rows, G, (uint32_t)blocks, stamp, s);
     }
     if (e != hipSuccess) return fail_hip(e, "launch of the output-definition kernel");
     if (es) es->launched[0] = true;

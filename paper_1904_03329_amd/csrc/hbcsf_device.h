@@ -46,7 +46,7 @@ struct GuestArgs {
   int n;                     // the mode being updated
   float* p;                  // right-hand matrix of the product that follows
   int* good;                 // receives 1 where the inverse succeeded, else 0
-  unsigned long long* stamp; // [2]
+  unsigned long long* stamp; // [2]: receives the time at which the MTTKRP's first kernel begins, and 0
 };
 
 // Device pointers of one slice group of one mode, by tree level (0 = root .. order-1 = leaf).
@@ -90,7 +90,7 @@ struct GroupArgs {
                                       hipStream_t s);                                                \
   hipError_t launch_define_coo_g##G##_n##N(bool wide, const GroupArgs& a, const uint32_t* ownedBits,   \
                                            const uint32_t* cooBits, const uint32_t* cooPtr, uint64_t rows, \
-                                           uint32_t blocks, hipStream_t s);
+                                           uint32_t blocks, unsigned long long* stamp, hipStream_t s);
 HBCSF_DECLARE_LAUNCH(2, 3)
 HBCSF_DECLARE_LAUNCH(4, 3)
 HBCSF_DECLARE_LAUNCH(8, 3)
@@ -113,7 +113,7 @@ HBCSF_DECLARE_LAUNCH(32, 5)
                                         hipStream_t s);                                                \
   hipError_t launch_define_coo64_g##G##_n##N(bool wide, const GroupArgs& a, const uint32_t* ownedBits,   \
                                              const uint32_t* cooBits, const uint32_t* cooPtr, uint64_t rows, \
-                                             uint32_t blocks, hipStream_t s);
+                                             uint32_t blocks, unsigned long long* stamp, hipStream_t s);
 HBCSF_DECLARE_LAUNCH64(8, 3)
 HBCSF_DECLARE_LAUNCH64(16, 3)
 HBCSF_DECLARE_LAUNCH64(32, 3)
@@ -161,15 +161,15 @@ inline hipError_t launch_group(bool f64, int kind, int order, int G, int steps, 
 #undef HBCSF_CASE
 }
 
-// Output definition fused with the COO group (a: the COO group's arguments).
+// Output definition fused with the COO group (a: the COO group's arguments).  stamp: null, or GuestArgs' stamps.
 inline hipError_t launch_define_coo(bool f64, int order, int G, bool wide, const GroupArgs& a,
                                     const uint32_t* ownedBits, const uint32_t* cooBits, const uint32_t* cooPtr,
-                                    uint64_t rows, uint32_t blocks, hipStream_t s) {
+                                    uint64_t rows, uint32_t blocks, unsigned long long* stamp, hipStream_t s) {
 #define HBCSF_CASE64(GV)                                                                                     \
   case GV:                                                                                                   \
-    return order == 3   ? launch_define_coo64_g##GV##_n3(wide, a, ownedBits, cooBits, cooPtr, rows, blocks, s) \
-           : order == 4 ? launch_define_coo64_g##GV##_n4(wide, a, ownedBits, cooBits, cooPtr, rows, blocks, s) \
-                        : launch_define_coo64_g##GV##_n5(wide, a, ownedBits, cooBits, cooPtr, rows, blocks, s);
+    return order == 3   ? launch_define_coo64_g##GV##_n3(wide, a, ownedBits, cooBits, cooPtr, rows, blocks, stamp, s) \
+           : order == 4 ? launch_define_coo64_g##GV##_n4(wide, a, ownedBits, cooBits, cooPtr, rows, blocks, stamp, s) \
+                        : launch_define_coo64_g##GV##_n5(wide, a, ownedBits, cooBits, cooPtr, rows, blocks, stamp, s);
   if (f64) {
     switch (G) {
       HBCSF_CASE64(8)
@@ -182,9 +182,9 @@ inline hipError_t launch_define_coo(bool f64, int order, int G, bool wide, const
 #undef HBCSF_CASE64
 #define HBCSF_CASE(GV)                                                                                     \
   case GV:                                                                                                 \
-    return order == 3   ? launch_define_coo_g##GV##_n3(wide, a, ownedBits, cooBits, cooPtr, rows, blocks, s) \
-           : order == 4 ? launch_define_coo_g##GV##_n4(wide, a, ownedBits, cooBits, cooPtr, rows, blocks, s) \
-                        : launch_define_coo_g##GV##_n5(wide, a, ownedBits, cooBits, cooPtr, rows, blocks, s);
+    return order == 3   ? launch_define_coo_g##GV##_n3(wide, a, ownedBits, cooBits, cooPtr, rows, blocks, stamp, s) \
+           : order == 4 ? launch_define_coo_g##GV##_n4(wide, a, ownedBits, cooBits, cooPtr, rows, blocks, stamp, s) \
+                        : launch_define_coo_g##GV##_n5(wide, a, ownedBits, cooBits, cooPtr, rows, blocks, stamp, s);
   switch (G) {
     HBCSF_CASE(2)
     HBCSF_CASE(4)
@@ -197,9 +197,9 @@ inline hipError_t launch_define_coo(bool f64, int order, int G, bool wide, const
 #undef HBCSF_CASE
 }
 
-// Zero fill of the rows whose bit in ownedBits is clear; a row is G 16-byte pieces (fp32 or fp64 alike).
+// Zero fill of the rows whose bit in ownedBits is clear; a row is G 16-byte pieces (fp32 or fp64 alike).  stamp as above.
 hipError_t launch_define(float* out, const uint32_t* ownedBits, uint64_t rows, int G,
-                         uint32_t blocks, hipStream_t s);
+                         uint32_t blocks, unsigned long long* stamp, hipStream_t s);
 
 // Zero fill of nvec float4s (an output that is then only reached by atomic adds).
 hipError_t launch_zero_rows(float* out, uint64_t nvec, uint32_t blocks, hipStream_t s);

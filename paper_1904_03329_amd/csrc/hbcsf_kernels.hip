@@ -346,6 +346,13 @@ __device__ __forceinline__ void trace_wave(const GroupArgs& a, int kind, unsigne
   }
 }
 
+// GuestArgs' stamps: an MTTKRP that carries ALS work begins with this kernel.
+__device__ __forceinline__ void stamp_begin(unsigned long long* __restrict__ stamp) {
+  if (stamp == nullptr || blockIdx.x != 0 || threadIdx.x != 0) return;
+  stamp[0] = wall_clock64();
+  stamp[1] = 0;
+}
+
 __device__ __forceinline__ uint32_t mark_of_slice(uint32_t si) {
   return ((si & 0x7fffffffu) + 1u) | (si & 0x80000000u);
 }
@@ -772,7 +779,9 @@ namespace f64 {
 // scalar path and each lane then stores its share of the 32 rows' float4s.
 __global__ __launch_bounds__(256) void define_rows_kernel(rowvec* __restrict__ out,
                                                           const uint32_t* __restrict__ ownedBits,
-                                                          uint64_t nvec, int gshift) {
+                                                          uint64_t nvec, int gshift,
+                                                          unsigned long long* __restrict__ stamp) {
+  stamp_begin(stamp);
   const int lane = threadIdx.x & 63;
   const uint32_t waves = (gridDim.x * blockDim.x) >> 6;
   const uint32_t wave = __builtin_amdgcn_readfirstlane((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
@@ -1451,7 +1460,9 @@ __global__ __launch_bounds__(256) void coo_group_kernel(const GroupArgs a) {
 template <int G, int N, bool WIDE>
 __global__ __launch_bounds__(256) void define_coo_kernel(const GroupArgs a, const uint32_t* __restrict__ ownedBits,
                                                          const uint32_t* __restrict__ cooBits,
-                                                         const uint32_t* __restrict__ cooPtr, uint64_t rows) {
+                                                         const uint32_t* __restrict__ cooPtr, uint64_t rows,
+                                                         unsigned long long* __restrict__ stamp) {
+  stamp_begin(stamp);
   constexpr int NG = 64 / G;
   constexpr int RPG = 32 / NG;              // rows of a word per lane group (NG <= 32)
   constexpr int CH = RPG < 4 ? RPG : 4;     // rows per lane group handled together
@@ -1639,13 +1650,13 @@ hipError_t launch_g(int kind, int steps, bool wide, const GroupArgs& a, const Gr
 hipError_t HBCSF_CAT(HBCSF_LAUNCH_DEFINE_COO, HBCSF_G, _n, HBCSF_N)(bool wide, const GroupArgs& a,
                                                                const uint32_t* ownedBits, const uint32_t* cooBits,
                                                                const uint32_t* cooPtr, uint64_t rows, uint32_t blocks,
-                                                               hipStream_t s) {
+                                                               unsigned long long* stamp, hipStream_t s) {
   if (wide)
     hipLaunchKernelGGL((define_coo_kernel<HBCSF_G, HBCSF_N, true>), dim3(blocks), dim3(256), 0, s, a, ownedBits,
-                       cooBits, cooPtr, rows);
+                       cooBits, cooPtr, rows, stamp);
   else
     hipLaunchKernelGGL((define_coo_kernel<HBCSF_G, HBCSF_N, false>), dim3(blocks), dim3(256), 0, s, a, ownedBits,
-                       cooBits, cooPtr, rows);
+                       cooBits, cooPtr, rows, stamp);
   return hipGetLastError();
 }
 
@@ -1700,11 +1711,11 @@ hipError_t launch_zero_rows(float* out, uint64_t nvec, uint32_t blocks, hipStrea
 }
 
 hipError_t launch_define(float* out, const uint32_t* ownedBits, uint64_t rows, int G, uint32_t blocks,
-                         hipStream_t s) {
+                         unsigned long long* stamp, hipStream_t s) {
   int gshift = 0;
   while ((1 << gshift) < G) ++gshift;
   hipLaunchKernelGGL(define_rows_kernel, dim3(blocks), dim3(256), 0, s, reinterpret_cast<rowvec*>(out),
-                     ownedBits, rows * (uint64_t)G, gshift);
+                     ownedBits, rows * (uint64_t)G, gshift, stamp);
   return hipGetLastError();
 }
 

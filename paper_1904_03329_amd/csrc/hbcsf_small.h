@@ -187,7 +187,6 @@ template <int R>
 __device__ __forceinline__ void guest_block(const GuestArgs& a, uint32_t* lds) {
   static_assert(R <= 64, "one block of 256 threads inverts V");
   const int tid = threadIdx.x;
-  if (tid == 0) a.stamp[0] = a.stamp[1] = wall_clock64();
   double x[4][4];
   const bool good = pinv_sweep<R, 256>(a.small, a.n, *reinterpret_cast<SweepLds<R>*>(lds), x);
   if (tid == 0) *a.good = good;
