@@ -6,6 +6,8 @@ computation happens in libhbcsf.so.
 """
 from __future__ import annotations
 
+import warnings
+
 from . import binding
 
 __all__ = ["binding", "HbcsfTensor", "CpdAls"]
@@ -13,15 +15,24 @@ __all__ = ["binding", "HbcsfTensor", "CpdAls"]
 _native_mttkrp = None
 
 
+def _not_native(*args):
+    return None
+
+
 def _load_native():
-    """The native form of HbcsfTensor.mttkrp (built with the library; its absence is an error like the library's)."""
+    """The native form of HbcsfTensor.mttkrp.  It is built for one torch and one Python; under another, calls go to the same
+    library through the checks in Python, after a warning."""
     global _native_mttkrp
     import torch  # noqa: F401  (its libraries have to be there first)
 
     binding.lib()
-    from . import _hbcsf_torch
+    try:
+        from . import _hbcsf_torch
 
-    _native_mttkrp = _hbcsf_torch.mttkrp
+        _native_mttkrp = _hbcsf_torch.mttkrp
+    except ImportError as e:
+        _native_mttkrp = _not_native
+        warnings.warn(f"HbcsfTensor.mttkrp: calls are checked in Python until the package is built again ({e})", RuntimeWarning)
     return _native_mttkrp
 
 

@@ -3,13 +3,14 @@ from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 SO = os.path.join(HERE, "libhbcsf.so")
-TORCH_SO = os.path.join(HERE, "_hbcsf_torch.so")
+TORCH_SO = os.path.join(HERE, "_hbcsf_torch" + sysconfig.get_config_var("EXT_SUFFIX"))   # found by this Python only
 
 HIP_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-munsafe-fp-atomics",
@@ -59,16 +60,15 @@ def build(verbose: bool = False) -> str:
 
 
 def build_torch_call(run) -> None:
-    """The native MTTKRP call on torch tensors: host code only, against the headers and libraries of the torch in use."""
-    import sysconfig
-
+    """The native MTTKRP call on torch tensors: host code only, against the headers and libraries of the torch in use, whose
+    version it is given (it loads under no other)."""
     import torch
     from torch.utils import cpp_extension
 
     inc = [INCLUDE, CSRC, sysconfig.get_paths()["include"]] + cpp_extension.include_paths("cuda")
     libs = cpp_extension.library_paths("cuda")
     run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-         f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-o", TORCH_SO,
+         f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DHBCSF_TORCH="{torch.__version__}"', "-o", TORCH_SO,
          os.path.join(CSRC, "hbcsf_torch.cpp")] + [f"-I{d}" for d in inc] + [f"-L{d}" for d in libs + [HERE]]
         + ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-l:libhbcsf.so", "-Wl,-rpath,$ORIGIN"])
 

@@ -13,6 +13,8 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <cstring>
+
 #include "hbcsf.h"
 
 namespace {
@@ -92,4 +94,14 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_hbcsf_torch", nullptr, -1, method
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__hbcsf_torch() { return PyModule_Create(&module); }
+// The tensors' layout is that of the torch this was compiled against: under any other the module does not load.
+PyMODINIT_FUNC PyInit__hbcsf_torch() {
+  PyObject* torch = PyImport_ImportModule("torch");
+  PyObject* version = torch ? PyObject_GetAttrString(torch, "__version__") : nullptr;
+  const char* text = version ? PyUnicode_AsUTF8(version) : nullptr;
+  const bool same = text && std::strcmp(text, HBCSF_TORCH) == 0;
+  if (text && !same) PyErr_Format(PyExc_ImportError, "built for torch " HBCSF_TORCH ", this is torch %s", text);
+  Py_XDECREF(version);
+  Py_XDECREF(torch);
+  return same ? PyModule_Create(&module) : nullptr;
+}
