@@ -359,20 +359,15 @@ __device__ __forceinline__ uint32_t mark_of_slice(uint32_t si) {
 
 
 // ---------------------------------------------------------------------------------------
-// Unit staging shared by the B-CSF and CSL kernels.
+// Unit staging.
 //
 // A unit is NG parts of 2^SS nonzeros, one per lane group, and a whole number of runs (2^a.lshift nonzeros each,
-// SS <= a.lshift <= SS + log2 NG), so neither a fiber segment nor an owned slice crosses a unit's ends.  With
-// SS = a.lshift a part is a run.  With shorter parts several lane groups share a run: the fiber segments that cross a
-// part's end get an extra end mark there (each side of the cut adds its own product with the fiber's row), and slices
-// are summed over the parts when the unit is closed.  Short parts buy latency with a few more marks: a wavefront walks
-// 2^SS nonzeros per lane group one block after the other.
+// SS <= a.lshift <= SS + log2 NG), so neither a fiber segment nor an owned slice crosses a unit's ends.
 //
 // All global loads a unit needs before its inner loop (stream data, fiber-segment and slice
-// arrays, the row of the slice at the unit's end) are issued back to back and awaited once, then the
-// LDS records are written and the end marks scattered into them.  The run-table entries of
-// the next unit are fetched one unit ahead (UnitBounds), so nothing here waits on a chain of
-// dependent loads.
+// arrays, the row of the slice at the unit's end) are issued back to back and awaited once, and the end marks scattered
+// into LDS.  The run-table entries of the next unit are fetched one unit ahead (UnitBounds), so nothing here waits on a
+// chain of dependent loads.
 // ---------------------------------------------------------------------------------------
 struct UnitBounds {
   uint32_t rf;      // lane t <= runs per unit: slice holding the first nonzero of run r0 + t (clipped to runs)
@@ -409,11 +404,12 @@ struct UnitEnds {
   uint32_t sideAt;  // B-CSF: where the slices that end in this lane group's part start in the unit's slice list
 };
 
+// Staging as one LDS record per nonzero, through registers: for the dense-gather variant of the B-CSF kernel and the
+// single-representation kernel, whose parts are runs (SS = a.lshift).
 // fLo: first segment of this unit per fiber level (wave-uniform; = previous unit's fHi).
 // START = false: end marks (index + 1 at the LAST nonzero of a segment / slice; slice marks carry the owned bit).
 // START = true : start marks (index + 1 at the FIRST nonzero), for the kernel that needs a level's index while
 //                its segment is still open; a slice that began before the unit has no mark in it (the row tells).
-//                Parts are runs here (SS = a.lshift).
 template <int G, int N, int SS, bool START = false>
 __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __restrict__ rec, uint32_t u,
                                                const UnitBounds& b, const uint32_t (&fLo)[3], int lane) {
@@ -428,8 +424,6 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
   constexpr uint32_t slots = (uint32_t)NG << SS;
   const uint32_t z0 = u * slots;
   const int g = lane / G;
-  // parts shorter than runs (of at most 64 nonzeros): segments are cut at part ends too
-  const bool cutSegments = !START && SS < 6 && ss < a.lshift;
   const uint32_t* __restrict__ valb = reinterpret_cast<const uint32_t*>(a.val);
 
   // -- issue: stream data
@@ -457,7 +451,7 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
     }
   }
   // -- issue: fiber-segment ends and indices
-  uint32_t fe[3][KF], fi[3][KF], fs[3][KF];
+  uint32_t fe[3][KF], fi[3][KF];
 #pragma unroll
   for (int l = 1; l <= NF; ++l) {
 #pragma unroll
@@ -465,11 +459,9 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
       const uint32_t f = fLo[l - 1] + (uint32_t)t * 64u + lane;
       fe[l - 1][t] = 0;
       fi[l - 1][t] = 0;
-      fs[l - 1][t] = 0;
       if (f < b.fHi[l - 1]) {
         fe[l - 1][t] = __builtin_nontemporal_load(a.ptr[l] + f + (START ? 0 : 1));
         fi[l - 1][t] = __builtin_nontemporal_load(a.ind[l] + f);
-        if (cutSegments) fs[l - 1][t] = __builtin_nontemporal_load(a.ptr[l] + f);
       }
     }
   }
@@ -518,20 +510,10 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
 #pragma unroll
     for (int t = 0; t < KF; ++t) {
       const uint32_t f = fLo[l - 1] + (uint32_t)t * 64u + lane;
-      if (f < b.fHi[l - 1]) {
-        const uint32_t p = fe[l - 1][t] - (START ? 0u : 1u) - z0;
-        mark(p, fi[l - 1][t]);
-        if (cutSegments)
-          for (uint32_t q = ((fs[l - 1][t] - z0) | (SUB - 1u)); q < p; q += SUB) mark(q, fi[l - 1][t]);
-      }
+      if (f < b.fHi[l - 1]) mark(fe[l - 1][t] - (START ? 0u : 1u) - z0, fi[l - 1][t]);
     }
-    for (uint32_t f = fLo[l - 1] + (uint32_t)KF * 64u + lane; f < b.fHi[l - 1]; f += 64) {
-      const uint32_t p = a.ptr[l][f + (START ? 0 : 1)] - (START ? 0u : 1u) - z0;
-      const uint32_t index = a.ind[l][f];
-      mark(p, index);
-      if (cutSegments)
-        for (uint32_t q = ((a.ptr[l][f] - z0) | (SUB - 1u)); q < p; q += SUB) mark(q, index);
-    }
+    for (uint32_t f = fLo[l - 1] + (uint32_t)KF * 64u + lane; f < b.fHi[l - 1]; f += 64)
+      mark(a.ptr[l][f + (START ? 0 : 1)] - (START ? 0u : 1u) - z0, a.ind[l][f]);
   }
   // -- slice end marks
   auto mark_slice = [&](uint32_t at, uint32_t entry) {
@@ -569,9 +551,14 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
 // without passing through registers, and a lane takes four consecutive fiber segments with one load of their ends and
 // one of their indices (with dword loads through registers into records: 50 M nonzeros of order 4 2514 -> 2427 us over
 // all modes, 150 M hypersparse 9290 -> 9200, rank 16 on 7.7 M 204 -> 196, fp64 on 5 M 314 -> 307, 100 M of order 3 with
-// long fibers 2185 -> 2188, 5 M 190 -> 190).  A part's words are read four nonzeros at a time, so within each array the quads of a part are
-// exchanged by quad_swizzle: the lane groups then read from different banks, which the padded records did by a pad
-// that a direct load to LDS (lane l writes place l) cannot leave.
+// long fibers 2185 -> 2188, 5 M 190 -> 190).  A part's words are read four nonzeros at a time, so within each array the
+// quads of a part are exchanged by quad_swizzle: the lane groups then read from different banks, which the padded records
+// did by a pad that a direct load to LDS (lane l writes place l) cannot leave.
+//
+// With SS = a.lshift a part is a run.  With shorter parts several lane groups share a run: the fiber segments that cross a
+// part's end get an extra end mark there (each side of the cut adds its own product with the fiber's row), and slices
+// are summed over the parts when the unit is closed.  Short parts buy latency with a few more marks: a wavefront walks
+// 2^SS nonzeros per lane group one block after the other.
 // ---------------------------------------------------------------------------------------
 
 // Place of quad j (of 2^(SS - 2)) of part g is j ^ quad_swizzle(g): 128 bytes of LDS, eight quads, hold one quad of each
