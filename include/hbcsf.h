@@ -194,9 +194,9 @@ int hbcsf_host_array(const hbcsf_tensor *t, int mode, int group, int level, int 
 #define HBCSF_TUNE_WAVES_PER_CU     2 /* wavefront spans launched per compute unit when T_s is
                                         automatic (0, the default: 512 at most, in whole units)  */
 #define HBCSF_TUNE_STEPS            3 /* gathers a lane group keeps in flight: 4, 8 or 0 = automatic, the
-                                        default (8 for order-3 streams of 25 M nonzeros and more in runs
-                                        of 64, else 4).  A choice of two at rows of 128 bytes; the other
-                                        ranks have 4.                                              */
+                                        default (8 for order-3 streams in runs of 64 of 97 656 nonzeros
+                                        per compute unit and more, 25 M on 256, else 4).  A choice of two
+                                        at rows of 128 bytes; the other ranks have 4.              */
 #define HBCSF_TUNE_KERNEL_MASK      4 /* which kernels hbcsf_mttkrp launches: bit0 define, bit1 COO,
                                         bit2 CSL, bit3 CSF (default 15).  For ablation and profiling
                                         only: with bits cleared the output is incomplete.        */

@@ -248,11 +248,14 @@ bool needs_wide(const hbcsf_tensor* t, const ModeFormat& f, uint64_t rowBytes) {
 
 // 8 gathers in flight with parts of whole runs: at order 3 and runs of 64 four wavefronts per SIMD instead of five, but
 // half the staging per nonzero.  Pays there with rows of 128 bytes, narrow factor matrices and a stream that fills the
-// chip many times over (100 M nonzeros 2.15 -> 2.03 ms, 30 M 867 -> 841 us, 25 M 735 -> 727 and 926 -> 926, 20 M 578 ->
-// 579 and 496 -> 480, 12 M 370 -> 381, 5 M 181 -> 221); at other run lengths and orders only where the tuning key asks.
+// chip many times over, 25 M nonzeros on 256 compute units (100 M nonzeros 2.15 -> 2.03 ms, 30 M 867 -> 841 us, 25 M 735 ->
+// 727 and 926 -> 926, 20 M 578 -> 579 and 496 -> 480, 12 M 370 -> 381, 5 M 181 -> 221; rank 16 in fp64, medians over three
+// index laws whose runs differ by 2 to 4 %: 60 M 1514 -> 1490, 1506 -> 1475 and 1407 -> 1361, 30 M 819 -> 829, 814 -> 796 and
+// 768 -> 766, 25 M 709 -> 717, 693 -> 677 and 665 -> 660, 20 M 587 -> 601, 572 -> 562 and 543 -> 546); at other run lengths
+// and orders only where the tuning key asks.
 bool long_parts(const hbcsf_tensor* t, const ModeFormat& f, int G, uint32_t lshift, bool wide) {
   if (G != 8 || t->steps == 8) return G == 8;
-  return t->steps == 0 && t->order == 3 && lshift == 6 && !wide && f.g[kCsl].nnz + f.g[kCsf].nnz >= 25000000;
+  return t->steps == 0 && t->order == 3 && lshift == 6 && !wide && f.g[kCsl].nnz + f.g[kCsf].nnz >= 97656ull * (uint64_t)t->numCU;
 }
 
 // The MTTKRP of both element types: `elem` = bytes per element of the factor matrices and the output (4: fp32,
