@@ -97,9 +97,10 @@ def _one_small_pivot(rank, ratio):
     return dims, inds, vals, facs
 
 
+@pytest.mark.parametrize("lazy", [False, True])
 @pytest.mark.parametrize("ratio", [5e-11, 2e-10])
 @pytest.mark.parametrize("rank", [8, 16, 32, 64, 128])
-def test_pivots_on_both_sides_of_the_line(oracle, rank, ratio):
+def test_pivots_on_both_sides_of_the_line(oracle, rank, ratio, lazy):
     """A pivot below 1e-10 of the largest diagonal entry sends the update from the sweep to the eigenvalue form.  Both give
     A = M V^-1, whose entries are sums of n rows' terms and R products in fp32: gamma (|M| |P|) bounds their error, with |M|
     the MTTKRP of the absolute values and gamma = 2^-24 times the operations in one entry's chain."""
@@ -118,8 +119,9 @@ def test_pivots_on_both_sides_of_the_line(oracle, rank, ratio):
     t = HbcsfTensor(dims, inds, vals).to_device()
     als = CpdAls(t, rank)
     dfacs = [torch.from_numpy(f.copy()).cuda() for f in facs]
-    print("als pivot", rank, ratio, flush=True)
-    als.iteration(dfacs)
+    print("als pivot", rank, ratio, lazy, flush=True)
+    als.iteration(dfacs, lazy=lazy)
+    assert ratio > 1e-10 or als.phase_ms()[2] > 0   # the eigenvalue form was taken, also after a sweep beside the MTTKRP
     got = dfacs[0].cpu().numpy().astype(np.float64)
     got /= np.linalg.norm(got, axis=0)
     want /= norm

@@ -50,6 +50,27 @@ def test_forms_of_a_call(oracle, synth, problem, rank, dtype):
         GU.assert_close(got.cpu().numpy(), want, f"other stream, mode {mode}", tol)
 
 
+def test_which_calls_are_served_natively(problem):
+    import torch
+    from paper_1904_03329_amd import HbcsfTensor, _hbcsf_torch
+
+    _, ht = problem
+    assert isinstance(ht, HbcsfTensor)
+    f = [torch.rand((d, 16), device="cuda") for d in DIMS]
+    out = torch.empty((DIMS[0], 16), device="cuda")
+
+    def native(mode, factors, out=None):
+        return _hbcsf_torch.mttkrp(ht.handle.value, ht.dims, mode, factors, out)
+
+    for factors in (f, tuple(f), [None] + f[1:], [torch.nn.Parameter(x) for x in f], [x.double() for x in f]):
+        got = native(0, factors)
+        assert isinstance(got, torch.Tensor) and got.shape == (DIMS[0], 16)
+    assert native(0, f, out) is out
+    for mode, factors in ((0, dict(enumerate(f))), (np.int64(0), f), (3, f), (-1, f), (0, [x.half() for x in f]), (0, f[:2])):
+        assert native(mode, factors) is None
+    assert native(0, f, out.cpu()) is None and native(0, f, out[:, :8]) is None
+
+
 def test_refused_calls(problem):
     import torch
 
