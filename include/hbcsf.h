@@ -192,7 +192,9 @@ int hbcsf_host_array(const hbcsf_tensor *t, int mode, int group, int level, int 
 #define HBCSF_TUNE_PROFILE         1 /* n > 0: bracket the kernels of each call with HIP events and
                                         keep the last n calls' event sets; 0 = off              */
 #define HBCSF_TUNE_WAVES_PER_CU     2 /* wavefront spans launched per compute unit when T_s is
-                                        automatic (0, the default: 512 at most, in whole units)  */
+                                        automatic (0, the default: 512 at most, in whole units;
+                                        128 for the modes a single representation computes from
+                                        mode 0's tree)                                            */
 #define HBCSF_TUNE_STEPS            3 /* gathers a lane group keeps in flight: 4, 8 or 0 = automatic, the
                                         default (8 for order-3 streams in runs of 64 of 97 656 nonzeros
                                         per compute unit and more, 25 M on 256, else 4).  A choice of two

@@ -62,7 +62,7 @@ bool pow2_in(uint32_t v, uint32_t lo, uint32_t hi) { return v >= lo && v <= hi &
 uint32_t round_up8(uint64_t v) { return (uint32_t)((v + 7) / 8 * 8); }
 
 // Nonzeros a lane group takes of a unit, as a power of two: at most a run, at least what keeps a unit (NG parts) a whole
-// number of runs.  Units of 256 nonzeros keep the most wavefronts resident (5 to 6 KB of LDS each) and were the
+// number of runs.  Units of 256 nonzeros keep the most wavefronts resident (5 to 7 KB of LDS each) and were the
 // fastest at every rank from 5 M nonzeros up (rank 8 on 42 M nonzeros 1.94 -> 1.10 ms against parts of whole runs, rank
 // 16 on 7.7 M 237 -> 204 us, rank 32 on 5 M 241 -> 217 us).  Smaller tensors take 128 where there would be fewer than 16
 // units of 256 per compute unit, and 64 below 3: a wavefront walks its part one dependent block after the other, so with

@@ -11,15 +11,16 @@
 // lengths are.  A wavefront works through a contiguous span of units.
 //
 // B-CSF kernel (Algorithm "CSF-MTTKRP" with fbr-split / slc-split, Sections III-B and IV):
-// per unit the wavefront loads the leaf indices and values coalesced into LDS records and
-// turns the compressed pointer arrays into per-nonzero end marks in the same records (lane
-// = fiber segment / slice, one LDS write each).  The inner loop then reads one 16-byte
-// record per nonzero: tmp += v*C(k,:); at a segment end acc += tmp*B(j,:) (Eq. 8's factored
-// form); at a slice end the row goes out with one plain 128-byte store if the slice lies in
-// one run, else with atomic adds (Section IV-A's merge of split slices).  The first slice that
+// per unit the wavefront brings the leaf indices and values straight from memory to LDS, an
+// array each, and turns the compressed pointer arrays into per-nonzero end marks in further
+// arrays (a lane takes four fiber segments, or one slice).  The inner loop then reads four
+// nonzeros' words with one LDS load per array: tmp += v*C(k,:); at a segment end acc += tmp*B(j,:)
+// (Eq. 8's factored form); at a slice end the row goes out with one plain 128-byte store if the
+// slice lies in one run, else with atomic adds (Section IV-A's merge of split slices).  The first slice that
 // ends in a part may have begun in the parts before it: it waits until the unit is closed, when a
 // segmented sum over the lane groups completes it.  What is open at the end of a unit stays in
-// registers for the next one, so a heavy slice costs one atomic row per wavefront span.
+// registers for the next one, and what is open at the ends of a block's spans is summed over its
+// wavefronts, so a heavy slice costs one atomic row per block.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -309,7 +310,7 @@ __device__ __forceinline__ void close_span(float* __restrict__ out, bool open, u
 // words from one wavefront's to the next.  With an atomic row per wavefront a slice of 472 000 nonzeros of a 5 M-nonzero
 // tensor was added up by 1844 of them on its row, 12.9 ns after each other, while a mode takes 60 us; that is also what kept
 // the spans long (all modes, with one span of 256 nonzeros and up a wavefront, per-wavefront atomics -> this: 5 M
-// 189.7 -> 181 us, fp64 307 -> 290, 100 M 2188 -> 2032, 150 M hypersparse 9200 -> 8820, 50 M of order 4 2427 -> 2400).
+// 189.7 -> 181 us, fp64 307 -> 288, 100 M 2188 -> 2057, 150 M hypersparse 9200 -> 9008, 50 M of order 4 no gain).
 template <int G>
 __device__ __forceinline__ void close_block(float* __restrict__ out, uint32_t* words, uint32_t stride, bool open,
                                             uint32_t row, rowvec acc, int lane, int wib, int wpb) {

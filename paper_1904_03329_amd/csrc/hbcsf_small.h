@@ -173,10 +173,10 @@ __device__ __forceinline__ bool pinv_sweep(const SmallState& st, int n, SweepLds
 // ---------------------------------------------------------------------------------------------------
 // Guest of an MTTKRP launch (its first block of 256 threads, rank <= 64): inverts V for the update that the MTTKRP belongs to.
 // Nothing the MTTKRP reads or writes is touched, and nothing here is needed before the product that follows it, so the
-// chain of R dependent steps runs beside the MTTKRP instead of before it (5 iterations, 5 M
-// nonzeros at rank 32 1381 -> 1290 us, 0.8 M at rank 64 1190 -> 916).  *good = 0 leaves the update to the eigenvalue form.  (The sum of the slots would fit in beside it, but not for nothing: the blocks that
-// sum have to hand over to the one that inverts, and with agent-scope fences for that, which write an L2 back, the MTTKRP
-// of a small tensor took 70 instead of 28 us.)
+// chain of R dependent steps runs beside the MTTKRP instead of before it (5 iterations, 5 M nonzeros at rank 32 1381 ->
+// 1290 us, 0.8 M at rank 64 1204 -> 916).  *good = 0 leaves the update to the eigenvalue form.  (The sum of the slots would
+// fit in beside it, but not for nothing: the blocks that sum have to hand over to the one that inverts, and with agent-scope
+// fences for that, which write an L2 back, the MTTKRP of a small tensor took 70 instead of 28 us.)
 // ---------------------------------------------------------------------------------------------------
 template <int R>
 constexpr uint32_t guest_lds_bytes() {
