@@ -129,7 +129,8 @@ int hbcsf_build_format(int order, const uint64_t *dims, uint64_t nnz,
                        const uint32_t *const *inds, const float *vals,
                        const hbcsf_opts *opts, hbcsf_tensor **out);
 
-/* Size in bytes of the device arena that holds all modes' arrays. */
+/* Size in bytes of the device arena that holds all modes' arrays and, behind them, the words of state of calls that define
+ * a small output in one launch (hbcsf_mttkrp on the NULL stream). */
 int hbcsf_device_bytes(const hbcsf_tensor *t, uint64_t *bytes);
 
 /* Copies all modes' arrays into the caller's device arena (device, 256-byte aligned, at least
@@ -145,10 +146,11 @@ int hbcsf_upload(hbcsf_tensor *t, void *device_arena, uint64_t bytes, void *hip_
  *            (rows of empty slices are zero), as Algorithm "COO-MTTKRP" returns Y from zero.
  * Launches the output-definition kernel, then the COO-group, CSL-group and B-CSF-group kernels
  * (Algorithm "HB-CSF-MTTKRP", execute step); for small outputs the COO group's rows are written
- * by the output-definition pass instead (HBCSF_TUNE_FUSE_COO).  Slices that span several work units
+ * by the output-definition pass instead (HBCSF_TUNE_FUSE_COO), and on the NULL stream of the arena's
+ * device small outputs are defined by the launch of the group kernels.  Slices that span several work units
  * are merged with fp32 atomic adds (Section IV-A), so results can differ between runs in
- * the last bits.  NaN / Inf inputs propagate.  The handle is const because the representation is
- * only read; with profiling on (HBCSF_TUNE_PROFILE) the call also records HIP events into the
+ * the last bits.  NaN / Inf inputs propagate.  Calls on one handle may overlap, on several streams
+ * and from several threads.  The handle is const because the representation is only read; with profiling on (HBCSF_TUNE_PROFILE) the call also records HIP events into the
  * handle's event ring, which is bookkeeping outside the const promise, so calls on one handle
  * must not overlap in time while profiling or tracing is on.
  * With profiling off the call only launches kernels on hip_stream (no memset, no allocation, no

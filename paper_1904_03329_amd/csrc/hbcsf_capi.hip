@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstring>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -51,6 +52,27 @@ int fail_exception() noexcept {
     g_err.clear();  // even the message could not be stored
   }
   return code;
+}
+
+uint64_t define_state_bytes(uint64_t rows) {
+  return rows <= kDefineStateRows ? ((rows + 31) / 32 * 4 + kAlign - 1) / kAlign * kAlign : 0;
+}
+
+void place_states(hbcsf_tensor* t, uint64_t formatBytes) {
+  t->formatBytes = t->arenaBytes = formatBytes;
+  for (int m = 0; m < t->order; ++m) {
+    if (!t->modes[m]) continue;
+    ModeFormat& f = *t->modes[m];
+    f.stateOffset = t->arenaBytes;
+    f.stateBytes = define_state_bytes(f.rows);
+    t->arenaBytes += f.stateBytes;
+  }
+}
+
+hipError_t clear_states(const hbcsf_tensor* t, uint8_t* arena, hipStream_t s) {
+  const uint64_t vecs = (t->arenaBytes - t->formatBytes) / 16;
+  if (vecs == 0) return hipSuccess;
+  return launch_zero_rows((float*)(arena + t->formatBytes), vecs, (uint32_t)(vecs < 256 * 1024 ? (vecs + 255) / 256 : 1024), s);
 }
 
 }  // namespace hbcsf
@@ -194,7 +216,7 @@ int hbcsf_build_format(int order, const uint64_t* dims, uint64_t nnz, const uint
     t->modes[m]->devOffset = off;
     off += t->modes[m]->blobBytes;
   }
-  t->arenaBytes = off;
+  place_states(t.get(), off);
   *out = t.release();
   return HBCSF_OK;
 } HBCSF_CATCH_ALL
@@ -220,11 +242,14 @@ int hbcsf_upload(hbcsf_tensor* t, void* device_arena, uint64_t bytes, void* hip_
   e = hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return fail_hip(e, "hipDeviceGetAttribute");
   t->numCU = cu > 0 ? cu : 256;
+  t->device = dev;
   for (int m = 0; m < nModes; ++m) {
     const ModeFormat& f = *t->modes[m];
     e = hipMemcpyAsync((uint8_t*)device_arena + f.devOffset, f.blob, f.blobBytes, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return fail_hip(e, "hipMemcpyAsync");
   }
+  e = clear_states(t, (uint8_t*)device_arena, s);
+  if (e != hipSuccess) return fail_hip(e, "launch of the zero-fill kernel");
   e = hipStreamSynchronize(s);
   if (e != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
   t->arena = (uint8_t*)device_arena;
@@ -256,6 +281,33 @@ bool needs_wide(const hbcsf_tensor* t, const ModeFormat& f, uint64_t rowBytes) {
 bool long_parts(const hbcsf_tensor* t, const ModeFormat& f, int G, uint32_t lshift, bool wide) {
   if (G != 8 || t->steps == 8) return G == 8;
   return t->steps == 0 && t->order == 3 && lshift == 6 && !wide && f.g[kCsl].nnz + f.g[kCsf].nnz >= 97656ull * (uint64_t)t->numCU;
+}
+
+// Is the output defined in the launch of the group kernels?  That saves a launch, 1.4 to 5 us, and costs the group kernels the
+// code that asks for rows, 1 to 4 % of a launch.  So: at most 8192 nonzeros per compute unit (2 M on 256 of them), at order 3
+// rows of up to 1 GiB together (8 M at rank 32); all modes, launch of its own -> here, rank 32: order 3 on 0.3 M 43 -> 37 us,
+// 4 M 155 -> 147, 8 M 260 -> 255 (fp64 4 M 254 -> 249, 8 M 441 -> 445); order 4 on 0.3 M 57 -> 45, 1.5 M 130 -> 120, 8 M 422 ->
+// 423 (rank 8 273 -> 278), 50 M 2435 -> 2485; order 5 on 1.5 M 182 -> 172, 8 M 766 -> 775.  And no more words of 32 rows than
+// the first blocks have wavefronts, 16 MiB at most: the zeros go through the L2 8 bytes a lane, and who comes early waits for
+// them (modes of 300 000 and 100 000 rows, rank 32 on 0.3 M 73 -> 77, rank 128 on 30 000 102 -> 114).
+constexpr uint64_t kDefineBlocksPerCU = 4;   // (with one the words are late: 5 M 180 -> 190 us)
+bool defines_here(const hbcsf_tensor* t, const ModeFormat& f, uint64_t nnz, uint64_t rowBytes) {
+  const uint64_t cus = (uint64_t)t->numCU;
+  return f.stateBytes > 0 && f.rows <= 32 * 4 * kDefineBlocksPerCU * cus && f.rows * rowBytes <= (16ull << 20) && nnz > 0 &&
+         (nnz <= 8192 * cus || (t->order == 3 && nnz * rowBytes <= (4ull << 20) * cus));
+}
+
+// Takes the turn of the mode's words of state for a call on stream s, where that is the stream they serve
+// (hbcsf_tensor::DefineTurn): the lock is then held, and `claimed` is what the call marks words with.
+bool take_turn(const hbcsf_tensor* t, int mode, hipStream_t s, std::unique_lock<std::mutex>* held, uint32_t* claimed) {
+  int device = -1;
+  if (s != nullptr || hipGetDevice(&device) != hipSuccess || device != t->device) return false;
+  hbcsf_tensor::DefineTurn& turn = t->turns[mode];
+  std::unique_lock<std::mutex> lock(turn.lock);
+  if (turn.call >= 0x7ffffff0u) return false;   // the marks would start again at 0
+  *claimed = 2 * ++turn.call + 1;
+  *held = std::move(lock);
+  return true;
 }
 
 // The MTTKRP of both element types: `elem` = bytes per element of the factor matrices and the output (4: fp32,
@@ -312,6 +364,29 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
   };
   const bool wide = needs_wide(t, f, rowBytes);
 
+  const uint64_t sparseNnz = f.g[kCsl].nnz + f.g[kCsf].nnz;
+  const bool dense = t->denseMid == 1 && dense_mid_available(N, G, lshift);
+  const bool longParts = long_parts(t, f, G, lshift, wide);
+  // 0. small outputs are defined in the launch of the group kernels, unless a kernel without that is asked for or needed,
+  //    slices are stored in pieces (which add to rows in the middle of a part), or the stream is not the one that the
+  //    mode's words of state serve
+  std::unique_lock<std::mutex> turn;
+  DefineArgs here{};
+  const bool oneLaunch = defines_here(t, f, sparseNnz, rowBytes) && t->fuseCoo == 2 && t->opts.hybrid_granularity == 0 &&
+                         f.blockBits == 0 && t->kernelMask == 15u && !es && !dense && !longParts && !wide && !t->persistent &&
+                         take_turn(t, mode, s, &turn, &here.claimed);
+  if (oneLaunch) {
+    const GroupArgs coo = group_args(kCoo);
+    for (int l = 0; l < N; ++l) here.ind[l] = coo.ind[l];
+    here.val = (const float*)(base + f.g[kCoo].val.off);
+    here.ownedBits = (const uint32_t*)(base + f.ownedBits.off);
+    here.cooBits = (const uint32_t*)(base + f.cooBits.off);
+    here.cooPtr = (const uint32_t*)(base + f.cooPtr.off);
+    here.rows = (uint32_t)f.rows;
+    here.state = (uint32_t*)(t->arena + f.stateOffset);
+    here.blocks = round_up8((f.rows + 127) / 128);   // a word a wavefront
+  }
+
   // 1. define every output row that no plain store will write; the COO group's rows are written
   //    in the same pass
   // (measured: the fused pass saves a launch on small outputs but hides latency worse on large ones)
@@ -319,8 +394,8 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
   const bool wantFuse = f.cooRowFlags || t->fuseCoo == 1 ||
                         (t->fuseCoo == 2 && f.rows * rowBytes <= (64ull << 20));
   unsigned long long* const stamp = guest ? guest->stamp : nullptr;
-  const bool fuseCoo = wantFuse && (t->kernelMask & 3u) == 3u && f.g[kCoo].nnz > 0;
-  if (t->kernelMask & 1u) {
+  const bool fuseCoo = oneLaunch || (wantFuse && (t->kernelMask & 3u) == 3u && f.g[kCoo].nnz > 0);
+  if ((t->kernelMask & 1u) && !oneLaunch) {
     // one wavefront per 8 x 32 rows, capped at 64 wavefronts per compute unit
     uint64_t blocks = ((f.rows + 255) / 256 + 3) / 4;
     const uint64_t cap = (uint64_t)t->numCU * 16;
@@ -348,14 +423,11 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
   if (es) (void)hipEventRecord(es->ev[1], s);
 
   // 2. the three group kernels (execute step of Algorithm "HB-CSF-MTTKRP")
-  const uint64_t sparseNnz = f.g[kCsl].nnz + f.g[kCsf].nnz;
   const bool runCsl = f.g[kCsl].nnz > 0 && (t->kernelMask & 4u), runCsf = f.g[kCsf].nnz > 0 && (t->kernelMask & 8u);
-  const bool dense = t->denseMid == 1 && dense_mid_available(N, G, lshift);
-  const bool longParts = long_parts(t, f, G, lshift, wide);
   const int denseSteps = t->steps ? t->steps : N == 3 ? 8 : 4;
   // CSL and B-CSF group in one launch, unless their times are asked for one by one (or the kernel with 8 gathers
   // is used: with both bodies in it, it no longer fits four wavefronts per SIMD)
-  const bool together = guest || (runCsl && runCsf && !es && !dense && !longParts && !t->persistent);
+  const bool together = guest || oneLaunch || (runCsl && runCsf && !es && !dense && !longParts && !t->persistent);
   auto sparse_args = [&](int g, uint32_t part) {
     const GroupFormat& gf = f.g[g];
     GroupArgs a = group_args(g);
@@ -403,10 +475,10 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
         uint64_t b = (gf.nnz + perBlock - 1) / perBlock;
         const uint64_t cap = (uint64_t)t->numCU * 16;
         if (b > cap) b = cap;
-        e = launch_group(f64, g, N, G, 4, wide, a, nullptr, nullptr, round_up8(b), 256, 0, s);
+        e = launch_group(f64, g, N, G, 4, wide, a, nullptr, nullptr, nullptr, round_up8(b), 256, 0, s);
         launched = true;
       }
-    } else if (g == kCsl ? runCsl && !together : runCsf || guest) {
+    } else if (g == kCsl ? runCsl && !together : runCsf || guest || oneLaunch) {
       const uint32_t part = g == kCsf && dense ? lshift
                             : longParts ? lshift
                                         : part_shift(together ? sparseNnz : gf.nnz, NG, lshift, t->numCU);
@@ -420,7 +492,7 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
       while (wpb > 1 && ldsWave * wpb > 48 * 1024) wpb >>= 1;
       // the launcher sizes the grid
       e = launch_group(f64, g, N, G, a.denseMid ? denseSteps : longParts ? 8 : 4, wide, a, together ? &csl : nullptr,
-                       guest, (uint32_t)t->numCU, 64 * wpb, ldsWave * wpb, s);
+                       oneLaunch ? &here : nullptr, guest, (uint32_t)t->numCU, 64 * wpb, ldsWave * wpb, s);
       launched = true;
     }
     if (launched && e != hipSuccess) return fail_hip(e, "launch of a group kernel");

@@ -1088,7 +1088,7 @@ uint64_t arena_bound(int N, const uint64_t* dims, uint64_t M, uint32_t L) {
   uint64_t bytes = 0;
   for (int m = 0; m < N; ++m) {
     const uint64_t words = (uint64_t)(2 * N + 1) * M + (uint64_t)3 * N * (M / L + 2) + 3 * (dims[m] / 32 + 2) + 64;
-    bytes += words * 4 + 40 * kAlign;
+    bytes += words * 4 + 40 * kAlign + define_state_bytes(dims[m]);
   }
   return bytes;
 }
@@ -1612,6 +1612,7 @@ int hbcsf_build_format_device(int order, const uint64_t* dims, uint64_t nnz, con
   HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
   HIP_TRY(hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev), "hipDeviceGetAttribute");
   t->numCU = cu > 0 ? cu : 256;
+  t->device = dev;
   uint64_t used = 0;
   t->single = o.single_representation == 1;
   for (int m = 0; m < (t->single ? 1 : order); ++m) {
@@ -1623,6 +1624,9 @@ int hbcsf_build_format_device(int order, const uint64_t* dims, uint64_t nnz, con
                               : build_all<uint64_t>(order, dims, (size_t)nnz, inds, vals, o, totalBits, w,
                                                     (uint8_t*)device_arena, arena_bytes, &used, t.get(), st);
   if (rb != HBCSF_OK) return rb;
+  place_states(t.get(), used);
+  if (t->arenaBytes > arena_bytes) return fail(HBCSF_ENOMEM, "device arena is too small for the format");
+  HIP_TRY(clear_states(t.get(), (uint8_t*)device_arena, st), "launch of the zero-fill kernel");
   double sq = 0.0;
   if (nnz > 0) {
     size_t tb_ = w.tempBytes;
@@ -1633,7 +1637,6 @@ int hbcsf_build_format_device(int order, const uint64_t* dims, uint64_t nnz, con
     HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
   }
   t->normSq = sq;
-  t->arenaBytes = used;
   t->arena = (uint8_t*)device_arena;
   t->uploaded = true;
   *out = t.release();

@@ -75,18 +75,36 @@ struct GroupArgs {
   uint32_t traceCapacity;       // records the buffer can hold
 };
 
+// Output definition inside an MTTKRP launch: the rows that no CSL / B-CSF slice stores by itself are written by the launch's
+// first blocks, one 32-row word of the bitmaps at a time.  state[word] grows from call to call: `claimed` (2 call + 1) while a
+// wavefront of this call writes the word's rows, claimed + 1 once they are written.
+struct DefineArgs {
+  const uint32_t* ownedBits;
+  const uint32_t* cooBits;
+  const uint32_t* cooPtr;
+  const uint32_t* ind[5];        // the COO group, by tree level
+  const float* val;
+  uint32_t rows;
+  uint32_t blocks;               // the launch's first blocks (a multiple of 8); 0: the rows were defined before the launch
+  uint32_t* state;
+  uint32_t claimed;
+};
+
+// Longest mode whose format has room for DefineArgs' state.
+constexpr uint64_t kDefineStateRows = 1ull << 18;
+
 // kind: KernelKind; order 3, 4 or 5; G = row bytes / 16 lanes per factor row (fp32: rank / 4 = 2, 4, 8, 16 or 32;
 // fp64: rank / 2 = 8, 16 or 32, the launch functions named ...64...);
 // steps = records a lane group keeps in flight (4, or at G = 8 also 8; not used for the COO group); csl = null, or with
-// kind = kCsfKernel and 4 steps the CSL group's arguments: both groups in one launch (same part size); guest = null, or
-// (fp32, G <= 16, 4 steps, not wide, blocks of 256 threads, kind = kCsfKernel, either group perhaps without a nonzero) ALS
-// work for the first block of that launch; wide = some
+// kind = kCsfKernel and 4 steps the CSL group's arguments: both groups in one launch (same part size), one of them perhaps
+// without a nonzero; define = null, or (not wide, with csl) the output definition for the first blocks of that launch; guest
+// = null, or (fp32, G <= 16, 4 steps, not wide, with csl, blocks of 256 threads) ALS work for the first block; wide = some
 // gathered factor matrix is 4 GiB or larger (64-bit row addressing).  One launch function per (G, order) pair, each
 // compiled in its own object file.  For the CSL and B-CSF kernels `blocks` is the number of compute
 // units and the launcher sizes the grid (one wavefront per span, or persistent).
 #define HBCSF_DECLARE_LAUNCH(G, N)                                                                  \
   hipError_t launch_group_g##G##_n##N(int kind, int steps, bool wide, const GroupArgs& a,          \
-                                      const GroupArgs* csl, const GuestArgs* guest, uint32_t blocks, uint32_t threads, size_t ldsBytes, \
+                                      const GroupArgs* csl, const DefineArgs* define, const GuestArgs* guest, uint32_t blocks, uint32_t threads, size_t ldsBytes, \
                                       hipStream_t s);                                                \
   hipError_t launch_define_coo_g##G##_n##N(bool wide, const GroupArgs& a, const uint32_t* ownedBits,   \
                                            const uint32_t* cooBits, const uint32_t* cooPtr, uint64_t rows, \
@@ -109,7 +127,7 @@ HBCSF_DECLARE_LAUNCH(32, 5)
 #undef HBCSF_DECLARE_LAUNCH
 #define HBCSF_DECLARE_LAUNCH64(G, N)                                                                  \
   hipError_t launch_group64_g##G##_n##N(int kind, int steps, bool wide, const GroupArgs& a,          \
-                                        const GroupArgs* csl, const GuestArgs* guest, uint32_t blocks, uint32_t threads, size_t ldsBytes, \
+                                        const GroupArgs* csl, const DefineArgs* define, const GuestArgs* guest, uint32_t blocks, uint32_t threads, size_t ldsBytes, \
                                         hipStream_t s);                                                \
   hipError_t launch_define_coo64_g##G##_n##N(bool wide, const GroupArgs& a, const uint32_t* ownedBits,   \
                                              const uint32_t* cooBits, const uint32_t* cooPtr, uint64_t rows, \
@@ -127,13 +145,13 @@ HBCSF_DECLARE_LAUNCH64(32, 5)
 
 // f64: the factor matrices and the output hold doubles (GroupArgs' float pointers then address doubles).
 inline hipError_t launch_group(bool f64, int kind, int order, int G, int steps, bool wide, const GroupArgs& a,
-                               const GroupArgs* csl, const GuestArgs* guest, uint32_t blocks, uint32_t threads, size_t ldsBytes,
+                               const GroupArgs* csl, const DefineArgs* define, const GuestArgs* guest, uint32_t blocks, uint32_t threads, size_t ldsBytes,
                                hipStream_t s) {
 #define HBCSF_CASE64(GV)                                                                              \
   case GV:                                                                                            \
-    return order == 3   ? launch_group64_g##GV##_n3(kind, steps, wide, a, csl, guest, blocks, threads, ldsBytes, s) \
-           : order == 4 ? launch_group64_g##GV##_n4(kind, steps, wide, a, csl, guest, blocks, threads, ldsBytes, s) \
-                        : launch_group64_g##GV##_n5(kind, steps, wide, a, csl, guest, blocks, threads, ldsBytes, s);
+    return order == 3   ? launch_group64_g##GV##_n3(kind, steps, wide, a, csl, define, guest, blocks, threads, ldsBytes, s) \
+           : order == 4 ? launch_group64_g##GV##_n4(kind, steps, wide, a, csl, define, guest, blocks, threads, ldsBytes, s) \
+                        : launch_group64_g##GV##_n5(kind, steps, wide, a, csl, define, guest, blocks, threads, ldsBytes, s);
   if (f64) {
     switch (G) {
       HBCSF_CASE64(8)
@@ -146,9 +164,9 @@ inline hipError_t launch_group(bool f64, int kind, int order, int G, int steps, 
 #undef HBCSF_CASE64
 #define HBCSF_CASE(GV)                                                                              \
   case GV:                                                                                          \
-    return order == 3   ? launch_group_g##GV##_n3(kind, steps, wide, a, csl, guest, blocks, threads, ldsBytes, s) \
-           : order == 4 ? launch_group_g##GV##_n4(kind, steps, wide, a, csl, guest, blocks, threads, ldsBytes, s) \
-                        : launch_group_g##GV##_n5(kind, steps, wide, a, csl, guest, blocks, threads, ldsBytes, s);
+    return order == 3   ? launch_group_g##GV##_n3(kind, steps, wide, a, csl, define, guest, blocks, threads, ldsBytes, s) \
+           : order == 4 ? launch_group_g##GV##_n4(kind, steps, wide, a, csl, define, guest, blocks, threads, ldsBytes, s) \
+                        : launch_group_g##GV##_n5(kind, steps, wide, a, csl, define, guest, blocks, threads, ldsBytes, s);
   switch (G) {
     HBCSF_CASE(2)
     HBCSF_CASE(4)

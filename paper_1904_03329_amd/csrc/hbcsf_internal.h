@@ -53,6 +53,8 @@ struct ModeFormat {
   uint8_t* blob = nullptr;         // host copy of all arrays, kAlign-aligned
   uint64_t blobBytes = 0;
   uint64_t devOffset = 0;          // where the blob sits in the device arena
+  uint64_t stateOffset = 0;        // ... and the launches' words of state (DefineArgs), one per 32 rows
+  uint64_t stateBytes = 0;         // 0: the mode is too long for them
   hbcsf_stats stats{};
 
   ModeFormat() = default;

@@ -254,7 +254,9 @@ __device__ __forceinline__ void row_atomic_wave(float* __restrict__ out, uint32_
   }
 }
 
-// A finished slice: a row that lies inside one run is written by this one store, any other is merged with atomic adds.
+// A finished slice: a row that lies inside one run is written by this one store, any other is merged with atomic adds.  (A
+// part lies in one run, so that a slice which begins and ends in it is merged only where it is a piece of one: never in a
+// launch that defines the output itself.)
 template <int G>
 __device__ __forceinline__ void emit_row(float* __restrict__ out, uint32_t mark, int c, const rowvec& acc) {
   const uint32_t row = (mark & 0x7fffffffu) - 1u;
@@ -360,6 +362,85 @@ __device__ __forceinline__ uint32_t mark_of_slice(uint32_t si) {
 
 
 // ---------------------------------------------------------------------------------------
+// Output definition in the launch that adds to the rows.  A launch of its own takes 1.4 us for 100 rows and 5 us for 100 000,
+// all of it before the first wavefront of the group kernels starts; here its words are the work of the first blocks of
+// their launch.  What a group kernel adds to must have been zeroed: every word is claimed by the wavefront that writes its
+// zeros and marked when they are written, and whoever wants to add to a row of a word that nobody has claimed yet
+// claims and zeroes it itself.  So nothing waits for a wavefront that has not started (blocks of one launch may start in any
+// order, and another launch may occupy the chip): a wait is for one that is between its claim and its mark, where it waits
+// for nothing but memory.  The zeros are written through the L2, which the atomic adds pass by.
+// A row's state is asked for before the row is added to, behind the last gathers of a part, so that the answer costs little
+// time (asked for where it is used it took 1.3 us a mode of 80 000 nonzeros, asked for while the unit is staged, before the
+// rows are defined, 1.2).
+// ---------------------------------------------------------------------------------------
+__device__ __forceinline__ void store_zero_through(rowvec* p) {
+  unsigned long long* q = reinterpret_cast<unsigned long long*>(p);
+  __hip_atomic_store(q, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(q + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+struct DefinedBefore {  // by an earlier launch
+  static constexpr bool kAsks = false;
+  __device__ __forceinline__ uint32_t ask(uint32_t) const { return 0; }
+};
+
+template <int G>
+struct DefinedHere {
+  static constexpr bool kAsks = true;
+  const DefineArgs& d;
+  float* out;
+
+  // State of the row's word; where the rows were defined before the launch, one past all.
+  __device__ __forceinline__ uint32_t ask(uint32_t row) const {
+    if (d.state == nullptr) return ~0u;
+    return __hip_atomic_load(d.state + (row >> 5), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+
+  // Zeroes the rows of word `wd` (uniform) that nothing stores, unless another wavefront has claimed it.  A whole wavefront.
+  __device__ __forceinline__ bool claim(uint32_t wd, int lane) const {
+    uint32_t old = 0;
+    const uint32_t stored = d.ownedBits[wd];
+    if (lane == 0) old = atomicMax(d.state + wd, d.claimed);
+    if ((uint32_t)__builtin_amdgcn_readfirstlane((int)old) >= d.claimed) return false;
+    constexpr uint32_t NG = 64 / G;
+#pragma unroll 1
+    for (uint32_t bit = (uint32_t)lane / G; bit < 32; bit += NG) {
+      const uint32_t row = (wd << 5) + bit;
+      if (row < d.rows && ((stored >> bit) & 1u) == 0u)
+        store_zero_through(reinterpret_cast<rowvec*>(out + ((size_t)row * (size_t)(4 * G) + (size_t)(4 * (lane % G)))));
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the zeros have arrived, then the mark
+    if (lane == 0) __hip_atomic_store(d.state + wd, d.claimed + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+  }
+
+  // Returns when `row` (uniform) is defined.
+  __device__ __forceinline__ void wait(uint32_t row, int lane) const {
+    for (;;) {
+      const uint32_t now = (uint32_t)__builtin_amdgcn_readfirstlane((int)ask(row));
+      if (now > d.claimed || (now < d.claimed && claim(row >> 5, lane))) return;
+      __builtin_amdgcn_s_sleep(4);
+    }
+  }
+};
+
+// Before a unit is closed: waits for the rows that are added to there, those of the heads that are shared (headMark: a lane
+// group's) and of the slice left open (openRow).  headState, openState: what ask() said of them.
+template <typename Defined>
+__device__ __forceinline__ void wait_defined(const Defined& defined, uint32_t headMark, uint32_t headState, bool open,
+                                             uint32_t openRow, uint32_t openState, int lane, int c) {
+  constexpr unsigned long long kOpen = 1ull << 63;   // (lane 63 is no lane group's first)
+  unsigned long long late = __ballot(c == 0 && headMark != 0u && !(headMark & kOwned) && headState <= defined.d.claimed);
+  if (open && (uint32_t)__builtin_amdgcn_readfirstlane((int)openState) <= defined.d.claimed) late |= kOpen;
+#pragma unroll 1
+  while (late) {
+    const int from = __builtin_ctzll(late);
+    late &= late - 1;
+    defined.wait(from == 63 ? openRow : (uint32_t)__builtin_amdgcn_readlane((int)headMark, from) - 1u, lane);
+  }
+}
+
+// ---------------------------------------------------------------------------------------
 // Unit staging.
 //
 // A unit is NG parts of 2^SS nonzeros, one per lane group, and a whole number of runs (2^a.lshift nonzeros each,
@@ -403,6 +484,7 @@ struct UnitEnds {
   bool ends;        // END marks: some slice ends in this unit (wave-uniform)
   uint32_t ng;      // nonzeros in this lane group's part (0 beyond the end of the stream)
   uint32_t sideAt;  // B-CSF: where the slices that end in this lane group's part start in the unit's slice list
+  uint32_t slices;  // entries of that list (wave-uniform)
 };
 
 // Staging as one LDS record per nonzero, through registers: for the dense-gather variant of the B-CSF kernel and the
@@ -540,6 +622,7 @@ __device__ __forceinline__ UnitEnds stage_unit(const GroupArgs& a, uint32_t* __r
   e.ends = s1 > s0;
   e.ng = z < a.nnz ? min(SUB, a.nnz - z) : 0u;
   e.sideAt = 0;
+  e.slices = 0;
   return e;
 }
 
@@ -747,6 +830,7 @@ __device__ __forceinline__ UnitEnds stage_arrays(const GroupArgs& a, uint32_t* _
   e.ends = s1 > s0;
   e.ng = z < a.nnz ? min(SUB, a.nnz - z) : 0u;
   e.sideAt = CSF ? sideFirst[g] : 0u;
+  e.slices = s1 - s0;
   return e;
 }
 
@@ -794,6 +878,89 @@ __global__ __launch_bounds__(256) void define_rows_kernel(rowvec* __restrict__ o
 #endif  // HBCSF_WITH_DEFINE
 
 // ---------------------------------------------------------------------------------------
+// Output definition fused with the COO group, 32 rows (one word of the bitmaps) a wavefront: rows of the COO group get v *
+// hadamard(factor rows), rows that nothing else stores get zeros, rows owned by a CSL / CSF slice are left alone.  The rows
+// of single-nonzero slices are scattered thinly over the output (about one row in five on the hypersparse workloads), and
+// writing them in a pass of their own costs far more DRAM time per byte than writing them together with the zero fill of
+// their neighbours.  COO nonzeros are stored in row order, so the nonzero of a row is cooPtr[word] + (number of COO rows
+// before it in the word).
+// ZEROS = false: the COO group's rows alone.
+// ---------------------------------------------------------------------------------------
+struct CooGroup {
+  const uint32_t* ind[5];
+  const float* val;
+};
+
+template <int G, int N, bool WIDE, bool ZEROS>
+__device__ __forceinline__ void define_word(const float* const (&fac)[5], float* __restrict__ out, const CooGroup& coo, uint32_t wo,
+                                            uint32_t wc, uint32_t zBase, uint64_t wd, uint64_t rows, int lane) {
+  constexpr int NG = 64 / G;
+  constexpr int RPG = 32 / NG;              // rows of a word per lane group (NG <= 32)
+  constexpr int CH = RPG < 4 ? RPG : 4;     // rows per lane group handled together
+  const int g = lane / G, c = lane % G;
+  const uint32_t* __restrict__ valb = reinterpret_cast<const uint32_t*>(coo.val);
+#pragma unroll (ZEROS ? 4 : 1)
+  for (int qb = 0; qb < RPG; qb += CH) {
+    uint32_t i1[CH], i2[CH], i3[CH], i4[CH], v[CH];
+    bool isCoo[CH], fill[CH];
+#pragma unroll
+    for (int q = 0; q < CH; ++q) {
+      const uint32_t bit = (uint32_t)(g * RPG + qb + q);
+      const uint64_t row = (wd << 5) + bit;
+      isCoo[q] = ((wc >> bit) & 1u) != 0u;
+      fill[q] = ZEROS && row < rows && !isCoo[q] && ((wo >> bit) & 1u) == 0u;
+      i1[q] = i2[q] = i3[q] = i4[q] = v[q] = 0;
+      if (isCoo[q]) {
+        const uint32_t z = zBase + (uint32_t)__builtin_popcount(wc & ((1u << bit) - 1u));
+        i1[q] = coo.ind[1][z];
+        i2[q] = coo.ind[2][z];
+        if (N >= 4) i3[q] = coo.ind[3][z];
+        if (N >= 5) i4[q] = coo.ind[4][z];
+        v[q] = valb[z];
+      }
+    }
+    rowvec x1[CH], x2[CH], x3[CH], x4[CH];
+#pragma unroll
+    for (int q = 0; q < CH; ++q) {
+      if (isCoo[q]) {
+        x1[q] = row_load<G, WIDE>(fac[1], i1[q], c);
+        x2[q] = row_load<G, WIDE>(fac[2], i2[q], c);
+        if (N >= 4) x3[q] = row_load<G, WIDE>(fac[3], i3[q], c);
+        if (N >= 5) x4[q] = row_load<G, WIDE>(fac[4], i4[q], c);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < CH; ++q) {
+      const uint32_t bit = (uint32_t)(g * RPG + qb + q);
+      rowvec* dst = reinterpret_cast<rowvec*>(out + (((wd << 5) + bit) * (uint64_t)(4 * G) + (uint64_t)(4 * c)));
+      if (isCoo[q]) {
+        rowvec pr = mul4(x1[q], x2[q]);
+        if (N >= 4) pr = mul4(pr, x3[q]);
+        if (N >= 5) pr = mul4(pr, x4[q]);
+        store_streaming(dst, scale4(__uint_as_float(v[q]), pr));
+      } else if (fill[q]) {
+        store_streaming(dst, rv_zero());
+      }
+    }
+  }
+}
+
+template <int G, int N, bool WIDE>
+__global__ __launch_bounds__(256) void define_coo_kernel(const GroupArgs a, const uint32_t* __restrict__ ownedBits,
+                                                         const uint32_t* __restrict__ cooBits,
+                                                         const uint32_t* __restrict__ cooPtr, uint64_t rows,
+                                                         unsigned long long* __restrict__ stamp) {
+  stamp_begin(stamp);
+  const int lane = threadIdx.x & 63;
+  const uint32_t waves = (gridDim.x * blockDim.x) >> 6;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+  const uint64_t words = (rows + 31) >> 5;
+  const CooGroup coo{{a.ind[0], a.ind[1], a.ind[2], a.ind[3], a.ind[4]}, a.val};
+  for (uint64_t wd = wave; wd < words; wd += waves)
+    define_word<G, N, WIDE, true>(a.fac, a.out, coo, ownedBits[wd], cooBits[wd], cooPtr[wd], wd, rows, lane);
+}
+
+// ---------------------------------------------------------------------------------------
 // B-CSF group.  N = tensor order (3, 4 or 5); G = lanes per factor row.
 // LDS words per nonzero: leaf, val, the segment marks from the deepest level up, the last with the slice-end flag (the
 // marks of the slices that end in the unit sit in a list beside them, in slice order, and a lane group takes them one
@@ -811,8 +978,9 @@ __global__ __launch_bounds__(256) void define_rows_kernel(rowvec* __restrict__ o
 // Every vector-memory instruction keeps the CU's address unit busy for the same 16 cycles however many lanes
 // are active, and that unit is what bounds this kernel when the factor matrices are cache-resident.  The cache
 // holds kDenseCache rows; marks beyond it (rare when segments average a few nonzeros) load their row directly.
-template <int G, int N, int SS, int kSteps, bool WIDE, bool DENSE>
-__device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t block, uint32_t blocks) {
+template <int G, int N, int SS, int kSteps, bool WIDE, bool DENSE, typename Defined = DefinedBefore>
+__device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t block, uint32_t blocks,
+                                               const Defined& defined = Defined()) {
   constexpr int NG = 64 / G;
   constexpr int NF = N - 2;
   constexpr int RW = N == 3 ? 4 : 8;   // DENSE: words of a record
@@ -878,6 +1046,8 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
     const uint32_t ng = ends.ng;
     uint32_t sideAt = ends.sideAt;   // the next slice of this lane group's part in the unit's slice list
     uint32_t headMark = 0;           // mark of the first slice that ends in this lane group's part
+    uint32_t headState = 0;          // DefinedHere: the state of its row,
+    uint32_t openState = 0;          //              and of the row of the slice open at the end of the unit
     fLo[0] = cur.fHi[0];
     fLo[1] = cur.fHi[1];
     fLo[2] = cur.fHi[2];
@@ -1055,6 +1225,13 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
         }
 #pragma unroll
         for (int t = 0; t < kSteps; ++t) cr[t] = row_load<G, WIDE>(facLeaf, leaf[t], c);
+        if constexpr (Defined::kAsks) {
+          if (sb == SUB - kSteps) {
+            // the first slice that ends here or after this part (if that is not here, nothing comes of the answer)
+            if (ends.sideAt < ends.slices) headState = defined.ask((side[ends.sideAt] & 0x7fffffffu) - 1u);
+            openState = defined.ask(ends.row);
+          }
+        }
 #pragma unroll
         for (int t = 0; t < kSteps; ++t) {
           fma4(tmp, __uint_as_float(val[t]), cr[t]);
@@ -1086,6 +1263,7 @@ __device__ __forceinline__ void csf_group_body(const GroupArgs& a, uint32_t bloc
       }
       }  // classic / dense
     }
+    if constexpr (Defined::kAsks) wait_defined(defined, headMark, headState, open, openRow, openState, lane, c);
     if (ends.ends) {
       if constexpr (!DENSE)
         if (headMark) held = head[lane];
@@ -1245,8 +1423,9 @@ __global__ __launch_bounds__(256) void csf_nonroot_kernel(const GroupArgs a) {
 // slice pointer goes straight to the nonzeros.
 // LDS of a unit: an array each for the N - 1 indices, the value and the slice mark.
 // ---------------------------------------------------------------------------------------
-template <int G, int N, int SS, int kSteps, bool WIDE>
-__device__ __forceinline__ void csl_group_body(const GroupArgs& a, uint32_t block, uint32_t blocks) {
+template <int G, int N, int SS, int kSteps, bool WIDE, typename Defined = DefinedBefore>
+__device__ __forceinline__ void csl_group_body(const GroupArgs& a, uint32_t block, uint32_t blocks,
+                                               const Defined& defined = Defined()) {
   constexpr int NG = 64 / G;
   extern __shared__ uint32_t lds[];
   const int lane = threadIdx.x & 63;
@@ -1332,6 +1511,10 @@ __device__ __forceinline__ void csl_group_body(const GroupArgs& a, uint32_t bloc
         }
       }
     }
+    if constexpr (Defined::kAsks) {
+      const uint32_t headState = headMark ? defined.ask((headMark & 0x7fffffffu) - 1u) : 0u;
+      wait_defined(defined, headMark, headState, open, openRow, defined.ask(openRow), lane, c);
+    }
     if (ends.ends) close_unit<G>(a.out, headMark ? head[lane] : rv_zero(), headMark, acc, lane, g, c);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
@@ -1346,6 +1529,20 @@ __global__ __launch_bounds__(256) void csl_group_kernel(const GroupArgs a) {
   csl_group_body<G, N, SS, kSteps, WIDE>(a, blockIdx.x, gridDim.x);
 }
 
+// The output definition's share of one of the first blocks of a launch.
+template <int G, int N>
+__device__ __forceinline__ void define_block(const GroupArgs& a, const DefineArgs& d, uint32_t block) {
+  const DefinedHere<G> defined{d, a.out};
+  const int lane = threadIdx.x & 63;
+  const uint32_t words = (d.rows + 31u) >> 5, waves = d.blocks * (blockDim.x >> 6);
+  const CooGroup coo{{d.ind[0], d.ind[1], d.ind[2], d.ind[3], d.ind[4]}, d.val};
+  for (uint32_t wd = __builtin_amdgcn_readfirstlane(block * (blockDim.x >> 6) + (threadIdx.x >> 6)); wd < words; wd += waves) {
+    const uint32_t wc = d.cooBits[wd], zBase = d.cooPtr[wd];
+    (void)defined.claim(wd, lane);
+    if (wc) define_word<G, N, false, false>(a.fac, a.out, coo, 0u, wc, zBase, wd, d.rows, lane);
+  }
+}
+
 // Both groups in one launch (neither reads what the other writes; rows they share are added atomically): the first
 // cslBlocks blocks walk the CSL group, the others the B-CSF group, so that the tail of one is filled with work of the
 // other.  On a 5 M-nonzero tensor the CSL kernel alone took 16 us for 80 000 nonzeros, nearly all of it latency.
@@ -1355,6 +1552,20 @@ __global__ __launch_bounds__(256) void csl_csf_kernel(const GroupArgs csl, const
   else csf_group_body<G, N, SS, kSteps, WIDE, false>(csf, blockIdx.x - cslBlocks, gridDim.x - cslBlocks);
 }
 
+// The same with the output definition in its first blocks.
+template <int G, int N, int SS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(N == 3 ? 5 : N == 4 ? 4 : 3))) void define_csl_csf_kernel(const GroupArgs csl, const GroupArgs csf, uint32_t cslBlocks,
+                                                             const DefineArgs define) {
+  if (blockIdx.x < define.blocks) {
+    define_block<G, N>(csf, define, blockIdx.x);
+    return;
+  }
+  const DefinedHere<G> defined{define, csf.out};
+  const uint32_t block = blockIdx.x - define.blocks, blocks = gridDim.x - define.blocks;
+  if (block < cslBlocks) csl_group_body<G, N, SS, 4, false>(csl, block, cslBlocks, defined);
+  else csf_group_body<G, N, SS, 4, false, false>(csf, block - cslBlocks, blocks - cslBlocks, defined);
+}
+
 #ifndef HBCSF_F64
 // The same with ALS work in the launch's first block (of 8, so that the others keep their XCDs).  The inverse takes 110
 // registers: where units of 256 nonzeros fill the chip, the order-3 kernels are held to the 96 that leave five wavefronts
@@ -1362,15 +1573,23 @@ __global__ __launch_bounds__(256) void csl_csf_kernel(const GroupArgs csl, const
 constexpr uint32_t kGuestBlocks = 8;
 template <int G, int N, int SS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(N == 3 && ((64 / G) << SS) == 256 ? 5 : 4)))
-void guest_csl_csf_kernel(const GroupArgs csl, const GroupArgs csf, uint32_t cslBlocks, const GuestArgs guest) {
+void guest_csl_csf_kernel(const GroupArgs csl, const GroupArgs csf, uint32_t cslBlocks, const DefineArgs define,
+                          const GuestArgs guest) {
   extern __shared__ uint32_t lds[];
   if (blockIdx.x < kGuestBlocks) {
+    if (define.state) stamp_begin(guest.stamp);
     if (blockIdx.x == 0) guest_block<4 * G>(guest, lds);
     return;
   }
-  const uint32_t block = blockIdx.x - kGuestBlocks, blocks = gridDim.x - kGuestBlocks;
-  if (block < cslBlocks) csl_group_body<G, N, SS, 4, false>(csl, block, cslBlocks);
-  else csf_group_body<G, N, SS, 4, false, false>(csf, block - cslBlocks, blocks - cslBlocks);
+  if (blockIdx.x < kGuestBlocks + define.blocks) {
+    define_block<G, N>(csf, define, blockIdx.x - kGuestBlocks);
+    return;
+  }
+  const DefinedHere<G> defined{define, csf.out};
+  const uint32_t first = kGuestBlocks + define.blocks;
+  const uint32_t block = blockIdx.x - first, blocks = gridDim.x - first;
+  if (block < cslBlocks) csl_group_body<G, N, SS, 4, false>(csl, block, cslBlocks, defined);
+  else csf_group_body<G, N, SS, 4, false, false>(csf, block - cslBlocks, blocks - cslBlocks, defined);
 }
 #endif
 
@@ -1436,81 +1655,6 @@ __global__ __launch_bounds__(256) void coo_group_kernel(const GroupArgs a) {
   }
 }
 
-// ---------------------------------------------------------------------------------------
-// Output definition fused with the COO group.  The rows of single-nonzero slices are scattered
-// thinly over the output (about one row in five on the hypersparse workloads), and writing them
-// in a pass of their own costs far more DRAM time per byte than writing them together with the
-// zero fill of their neighbours.  One wavefront takes one 32-row word at a time: rows of the
-// COO group get v * hadamard(factor rows), rows that nothing else stores get zeros, rows owned
-// by a CSL / CSF slice are left alone.  COO nonzeros are stored in row order, so the nonzero of
-// a row is cooPtr[word] + (number of COO rows before it in the word).
-// ---------------------------------------------------------------------------------------
-template <int G, int N, bool WIDE>
-__global__ __launch_bounds__(256) void define_coo_kernel(const GroupArgs a, const uint32_t* __restrict__ ownedBits,
-                                                         const uint32_t* __restrict__ cooBits,
-                                                         const uint32_t* __restrict__ cooPtr, uint64_t rows,
-                                                         unsigned long long* __restrict__ stamp) {
-  stamp_begin(stamp);
-  constexpr int NG = 64 / G;
-  constexpr int RPG = 32 / NG;              // rows of a word per lane group (NG <= 32)
-  constexpr int CH = RPG < 4 ? RPG : 4;     // rows per lane group handled together
-  const int lane = threadIdx.x & 63;
-  const int g = lane / G, c = lane % G;
-  const uint32_t waves = (gridDim.x * blockDim.x) >> 6;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-  const uint64_t words = (rows + 31) >> 5;
-  const uint32_t* __restrict__ valb = reinterpret_cast<const uint32_t*>(a.val);
-  for (uint64_t wd = wave; wd < words; wd += waves) {
-    const uint32_t wo = ownedBits[wd];
-    const uint32_t wc = cooBits[wd];
-    const uint32_t zBase = cooPtr[wd];
-#pragma unroll
-    for (int qb = 0; qb < RPG; qb += CH) {
-      uint32_t i1[CH], i2[CH], i3[CH], i4[CH], v[CH];
-      bool isCoo[CH], fill[CH];
-#pragma unroll
-      for (int q = 0; q < CH; ++q) {
-        const uint32_t bit = (uint32_t)(g * RPG + qb + q);
-        const uint64_t row = (wd << 5) + bit;
-        isCoo[q] = ((wc >> bit) & 1u) != 0u;
-        fill[q] = row < rows && !isCoo[q] && ((wo >> bit) & 1u) == 0u;
-        i1[q] = i2[q] = i3[q] = i4[q] = v[q] = 0;
-        if (isCoo[q]) {
-          const uint32_t z = zBase + (uint32_t)__builtin_popcount(wc & ((1u << bit) - 1u));
-          i1[q] = a.ind[1][z];
-          i2[q] = a.ind[2][z];
-          if (N >= 4) i3[q] = a.ind[3][z];
-          if (N >= 5) i4[q] = a.ind[4][z];
-          v[q] = valb[z];
-        }
-      }
-      rowvec x1[CH], x2[CH], x3[CH], x4[CH];
-#pragma unroll
-      for (int q = 0; q < CH; ++q) {
-        if (isCoo[q]) {
-          x1[q] = row_load<G, WIDE>(a.fac[1], i1[q], c);
-          x2[q] = row_load<G, WIDE>(a.fac[2], i2[q], c);
-          if (N >= 4) x3[q] = row_load<G, WIDE>(a.fac[3], i3[q], c);
-          if (N >= 5) x4[q] = row_load<G, WIDE>(a.fac[4], i4[q], c);
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < CH; ++q) {
-        const uint32_t bit = (uint32_t)(g * RPG + qb + q);
-        rowvec* dst = reinterpret_cast<rowvec*>(a.out + (((wd << 5) + bit) * (uint64_t)(4 * G) + (uint64_t)(4 * c)));
-        if (isCoo[q]) {
-          rowvec pr = mul4(x1[q], x2[q]);
-          if (N >= 4) pr = mul4(pr, x3[q]);
-          if (N >= 5) pr = mul4(pr, x4[q]);
-          store_streaming(dst, scale4(__uint_as_float(v[q]), pr));
-        } else if (fill[q]) {
-          store_streaming(dst, rv_zero());
-        }
-      }
-    }
-  }
-}
-
 #ifdef HBCSF_F64
 }  // namespace f64
 using namespace f64;
@@ -1527,8 +1671,8 @@ uint64_t span_blocks(const GroupArgs& a, uint32_t wpb) { return (((uint64_t)a.nS
 // `cus`: compute units.  Default launch: one wavefront per span.  Persistent launch: (resident blocks per CU) x CUs
 // blocks, capped by the spans.  Both rounded to a multiple of 8.
 template <int G, int N, int SS, int S, bool WIDE>
-hipError_t launch_one(int kind, const GroupArgs& a, const GroupArgs* csl, const GuestArgs* guest, uint32_t cus, dim3 block,
-                      size_t lds, hipStream_t s) {
+hipError_t launch_one(int kind, const GroupArgs& a, const GroupArgs* csl, const DefineArgs* define, const GuestArgs* guest,
+                      uint32_t cus, dim3 block, size_t lds, hipStream_t s) {
   constexpr bool occ4 = G == 8 && N == 3 && S == 8 && !WIDE;
   const uint32_t wpb = block.x >> 6;
   if (guest) {
@@ -1538,11 +1682,23 @@ hipError_t launch_one(int kind, const GroupArgs& a, const GroupArgs* csl, const 
       if (!csl || block.x != 256) return hipErrorInvalidValue;
       if (lds < guest_lds_bytes<R>()) lds = guest_lds_bytes<R>();
       const uint32_t cslBlocks = (uint32_t)span_blocks(*csl, wpb);
-      hipLaunchKernelGGL((guest_csl_csf_kernel<G, N, SS>), dim3(kGuestBlocks + cslBlocks + (uint32_t)span_blocks(a, wpb)),
-                         block, lds, s, *csl, a, cslBlocks, *guest);
+      const DefineArgs here = define ? *define : DefineArgs{};
+      hipLaunchKernelGGL((guest_csl_csf_kernel<G, N, SS>),
+                         dim3(kGuestBlocks + here.blocks + cslBlocks + (uint32_t)span_blocks(a, wpb)), block, lds, s, *csl, a,
+                         cslBlocks, here, *guest);
       return hipGetLastError();
     }
 #endif
+    return hipErrorInvalidValue;
+  }
+  if (define) {
+    if constexpr (S == 4 && !WIDE && (G != 8 || SS < 6)) {
+      if (!csl) return hipErrorInvalidValue;
+      const uint32_t cslBlocks = (uint32_t)span_blocks(*csl, wpb);
+      hipLaunchKernelGGL((define_csl_csf_kernel<G, N, SS>), dim3(define->blocks + cslBlocks + (uint32_t)span_blocks(a, wpb)), block,
+                         lds, s, *csl, a, cslBlocks, *define);
+      return hipGetLastError();
+    }
     return hipErrorInvalidValue;
   }
   if (csl) {
@@ -1581,37 +1737,37 @@ hipError_t launch_one(int kind, const GroupArgs& a, const GroupArgs* csl, const 
 }
 
 template <int G, int N, int SS>
-hipError_t launch_ss(int kind, int steps, bool wide, const GroupArgs& a, const GroupArgs* csl, const GuestArgs* guest, uint32_t cus,
-                     dim3 block, size_t lds, hipStream_t s) {
+hipError_t launch_ss(int kind, int steps, bool wide, const GroupArgs& a, const GroupArgs* csl, const DefineArgs* define,
+                     const GuestArgs* guest, uint32_t cus, dim3 block, size_t lds, hipStream_t s) {
   if constexpr (G == 8) {
     if (steps == 8)
-      return wide ? launch_one<G, N, SS, 8, true>(kind, a, csl, guest, cus, block, lds, s)
-                  : launch_one<G, N, SS, 8, false>(kind, a, csl, guest, cus, block, lds, s);
+      return wide ? launch_one<G, N, SS, 8, true>(kind, a, csl, define, guest, cus, block, lds, s)
+                  : launch_one<G, N, SS, 8, false>(kind, a, csl, define, guest, cus, block, lds, s);
   }
   if (steps != 4) return hipErrorInvalidValue;
-  return wide ? launch_one<G, N, SS, 4, true>(kind, a, csl, guest, cus, block, lds, s)
-              : launch_one<G, N, SS, 4, false>(kind, a, csl, guest, cus, block, lds, s);
+  return wide ? launch_one<G, N, SS, 4, true>(kind, a, csl, define, guest, cus, block, lds, s)
+              : launch_one<G, N, SS, 4, false>(kind, a, csl, define, guest, cus, block, lds, s);
 }
 
 // The part sizes the caller can ask for at this G: units of at most 256 nonzeros, or at G = 8 parts of 64.
 template <int G, int N>
-hipError_t launch_g(int kind, int steps, bool wide, const GroupArgs& a, const GroupArgs* csl, const GuestArgs* guest,
-                    dim3 grid, dim3 block, size_t lds, hipStream_t s) {
+hipError_t launch_g(int kind, int steps, bool wide, const GroupArgs& a, const GroupArgs* csl, const DefineArgs* define,
+                    const GuestArgs* guest, dim3 grid, dim3 block, size_t lds, hipStream_t s) {
   if (kind == kCooKernel) {
     if (wide) hipLaunchKernelGGL((coo_group_kernel<G, N, true>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((coo_group_kernel<G, N, false>), grid, block, 0, s, a);
     return hipGetLastError();
   }
   switch (a.partShift) {
-    case 3: return launch_ss<G, N, 3>(kind, steps, wide, a, csl, guest, grid.x, block, lds, s);
+    case 3: return launch_ss<G, N, 3>(kind, steps, wide, a, csl, define, guest, grid.x, block, lds, s);
     case 4:
-      if constexpr (G >= 4) return launch_ss<G, N, 4>(kind, steps, wide, a, csl, guest, grid.x, block, lds, s);
+      if constexpr (G >= 4) return launch_ss<G, N, 4>(kind, steps, wide, a, csl, define, guest, grid.x, block, lds, s);
       break;
     case 5:
-      if constexpr (G >= 8) return launch_ss<G, N, 5>(kind, steps, wide, a, csl, guest, grid.x, block, lds, s);
+      if constexpr (G >= 8) return launch_ss<G, N, 5>(kind, steps, wide, a, csl, define, guest, grid.x, block, lds, s);
       break;
     case 6:
-      if constexpr (G >= 8) return launch_ss<G, N, 6>(kind, steps, wide, a, csl, guest, grid.x, block, lds, s);
+      if constexpr (G >= 8) return launch_ss<G, N, 6>(kind, steps, wide, a, csl, define, guest, grid.x, block, lds, s);
       break;
   }
   return hipErrorInvalidValue;
@@ -1649,9 +1805,9 @@ hipError_t HBCSF_CAT(HBCSF_LAUNCH_DEFINE_COO, HBCSF_G, _n, HBCSF_N)(bool wide, c
 }
 
 hipError_t HBCSF_CAT(HBCSF_LAUNCH_GROUP, HBCSF_G, _n, HBCSF_N)(int kind, int steps, bool wide, const GroupArgs& a,
-                                                          const GroupArgs* csl, const GuestArgs* guest, uint32_t blocks,
-                                                          uint32_t threads, size_t ldsBytes, hipStream_t s) {
-  return launch_g<HBCSF_G, HBCSF_N>(kind, steps, wide, a, csl, guest, dim3(blocks), dim3(threads), ldsBytes, s);
+                                                          const GroupArgs* csl, const DefineArgs* define,
+                                                          const GuestArgs* guest, uint32_t blocks, uint32_t threads, size_t ldsBytes, hipStream_t s) {
+  return launch_g<HBCSF_G, HBCSF_N>(kind, steps, wide, a, csl, define, guest, dim3(blocks), dim3(threads), ldsBytes, s);
 }
 
 #if HBCSF_G == 8 && !defined(HBCSF_F64)

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -18,10 +19,12 @@ struct hbcsf_tensor {
   hbcsf_opts opts{};
   std::unique_ptr<hbcsf::ModeFormat> modes[HBCSF_MAX_ORDER];
   uint64_t arenaBytes = 0;
-  uint8_t* arena = nullptr;  // caller's device memory
+  uint8_t* arena = nullptr;  // caller's device memory: the formats, then the launches' words of state
+  uint64_t formatBytes = 0;  // of the arena's bytes, the formats'
   bool uploaded = false;
   bool single = false;       // only modes[0] exists; the other modes are computed from it (single representation)
   int numCU = 256;
+  int device = -1;           // the arena's
   uint64_t sliceThreshold = 0;
   uint64_t wavesPerCU = 0;   // launch sizing override, 0 = default
   int steps = 0;             // records in flight per lane group, 0 = automatic
@@ -32,6 +35,15 @@ struct hbcsf_tensor {
   uint64_t streamBytes = 1ull << 30;  // fiber-level factors at least this large are gathered with streaming loads
   unsigned long long* trace = nullptr;  // caller's device buffer for wavefront traces
   uint64_t traceCapacity = 0;
+  // Calls that define the output in the launch that adds to it, per mode.  The words of state in the arena serve one call at a
+  // time, so such calls are those on the null stream of the arena's device: there they follow each other, whichever threads
+  // make them, and the stream is never destroyed nor captured.  A call on another stream defines the output in a launch of
+  // its own, without state.  `lock`: a call's number and its launch go together.
+  struct DefineTurn {
+    std::mutex lock;
+    uint32_t call = 0;
+  };
+  mutable DefineTurn turns[HBCSF_MAX_ORDER];
   // profiling: a ring of event sets, one per hbcsf_mttkrp call
   struct EventSet {
     hipEvent_t ev[5];
@@ -51,6 +63,13 @@ int fail_hip(hipError_t e, const char* what);
 // For the handler of an entry point's function-try-block: turns the exception in flight into an error code
 // (std::bad_alloc -> HBCSF_ENOMEM, anything else -> HBCSF_EINVAL with its text) and never throws itself.
 int fail_exception() noexcept;
+
+// Bytes of the words of state (DefineArgs) of a mode with that many rows.
+uint64_t define_state_bytes(uint64_t rows);
+// Places the words of state behind the formats, which take the arena's first `formatBytes` bytes: sets arenaBytes.
+void place_states(hbcsf_tensor* t, uint64_t formatBytes);
+// Clears them, in an arena of the caller's.
+hipError_t clear_states(const hbcsf_tensor* t, uint8_t* arena, hipStream_t s);
 
 // hbcsf_mttkrp with ALS work in the same launch, for calls that take it (fp32).
 struct GuestArgs;
