@@ -265,6 +265,15 @@ int hbcsf_build_format_device(int order, const uint64_t *dims, uint64_t nnz,
                               void *device_arena, uint64_t arena_bytes, void *workspace,
                               uint64_t workspace_bytes, void *hip_stream, hbcsf_tensor **out);
 
+/* The same, with memory that is asked for as the sizes become known, so that nothing has to be sized for every pattern nor
+ * moved afterwards: `allocate` is called once per mode and once for the words of state (hbcsf_device_bytes in all), on the
+ * calling thread, and returns device memory of that many bytes, 256-byte aligned, which the caller keeps for the handle's
+ * lifetime (also what was given before an error), or NULL: ENOMEM. */
+typedef void *(*hbcsf_allocate)(void *context, uint64_t bytes);
+int hbcsf_build_format_device_pieces(int order, const uint64_t *dims, uint64_t nnz, const uint32_t *const *inds,
+                                     const float *vals, const hbcsf_opts *opts, hbcsf_allocate allocate, void *context,
+                                     void *workspace, uint64_t workspace_bytes, void *hip_stream, hbcsf_tensor **out);
+
 /* Moves a resident handle's arrays into another device arena of at least hbcsf_device_bytes
  * (256-byte aligned, not overlapping the old one) and makes the handle use it, e.g. to release the
  * upper-bound arena a device build was given.  Blocking.  The old arena is the caller's again. */

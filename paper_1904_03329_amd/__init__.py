@@ -48,8 +48,8 @@ class HbcsfTensor:
     @classmethod
     def from_device_coo(cls, dims, inds, vals, compact: bool = True, **opts):
         """Builds the format on the GPU from CUDA tensors (int32 / uint32-valued index tensors of dtype
-        torch.int32, float32 values); the result is resident.  With `compact` the arrays are moved from the
-        upper-bound arena the build needs into one of exactly their size."""
+        torch.int32, float32 values); the result is resident.  With `compact` the arrays get memory of exactly their
+        size, a piece per mode, as it becomes known; otherwise one arena sized for any sparsity pattern."""
         import torch
 
         self = cls.__new__(cls)
@@ -65,17 +65,22 @@ class HbcsfTensor:
             raise ValueError("indices must be torch.int32 and values torch.float32")
         stream = torch.cuda.current_stream().cuda_stream
         arena_bytes, ws_bytes = binding.device_build_bytes(self.dims, nnz, **opts)
-        arena = torch.empty(arena_bytes, dtype=torch.uint8, device="cuda")
         ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
-        self.handle = binding.build_format_device(self.dims, nnz, [x.data_ptr() for x in inds], vals.data_ptr(),
-                                                  arena.data_ptr(), arena_bytes, ws.data_ptr(), ws_bytes, stream, **opts)
-        del ws
         if compact:
-            used = max(binding.device_bytes(self.handle), 256)
-            small = torch.empty(used, dtype=torch.uint8, device="cuda")
-            binding.relocate(self.handle, small.data_ptr(), used, stream)
-            arena = small
-        self._arena = arena
+            pieces = []
+
+            def allocate(nbytes):
+                pieces.append(torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+                return pieces[-1].data_ptr()
+
+            self.handle = binding.build_format_device_pieces(self.dims, nnz, [x.data_ptr() for x in inds], vals.data_ptr(),
+                                                             allocate, ws.data_ptr(), ws_bytes, stream, **opts)
+            self._arena = pieces
+        else:
+            arena = torch.empty(arena_bytes, dtype=torch.uint8, device="cuda")
+            self.handle = binding.build_format_device(self.dims, nnz, [x.data_ptr() for x in inds], vals.data_ptr(),
+                                                      arena.data_ptr(), arena_bytes, ws.data_ptr(), ws_bytes, stream, **opts)
+            self._arena = arena
         return self
 
     def stats(self, mode: int) -> dict:

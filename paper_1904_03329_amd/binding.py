@@ -61,7 +61,7 @@ class HbcsfError(RuntimeError):
 
 
 _lib = None
-
+_ALLOCATE = ctypes.CFUNCTYPE(ctypes.c_void_p, ctypes.c_void_p, ctypes.c_uint64)
 
 def lib():
     """Loads libhbcsf.so (built by paper_1904_03329_amd.build.build()); raises if it is absent."""
@@ -113,6 +113,8 @@ def lib():
         L.hbcsf_device_build_bytes.argtypes = [i32, vp, u64, vp, ctypes.POINTER(u64), ctypes.POINTER(u64)]
         L.hbcsf_build_format_device.restype = i32
         L.hbcsf_build_format_device.argtypes = [i32, vp, u64, vp, vp, vp, vp, u64, vp, u64, vp, ctypes.POINTER(vp)]
+        L.hbcsf_build_format_device_pieces.restype = i32
+        L.hbcsf_build_format_device_pieces.argtypes = [i32, vp, u64, vp, vp, vp, _ALLOCATE, vp, vp, u64, vp, ctypes.POINTER(vp)]
         L.hbcsf_relocate.restype = i32
         L.hbcsf_relocate.argtypes = [vp, vp, u64, vp]
         L.hbcsf_download.restype = i32
@@ -185,6 +187,34 @@ def build_format_device(dims, nnz: int, ind_ptrs, val_ptr: int, arena_ptr: int, 
                                            ctypes.cast(ctypes.pointer(opts), ctypes.c_void_p),
                                            ctypes.c_void_p(arena_ptr), arena_bytes, ctypes.c_void_p(workspace_ptr),
                                            workspace_bytes, ctypes.c_void_p(stream), ctypes.byref(h)))
+    return h
+
+
+def build_format_device_pieces(dims, nnz: int, ind_ptrs, val_ptr: int, allocate, workspace_ptr: int, workspace_bytes: int,
+                               stream: int = 0, fiber_threshold=0, slice_threshold=0, mode_order_policy=0, group_mask=0,
+                               hybrid_granularity=0, coo_row_flags=0, mid_blocking=0, single_representation=0):
+    """hbcsf_build_format_device_pieces: allocate(bytes) returns a device address."""
+    d = np.asarray(dims, dtype=np.uint64)
+    opts = _opts(fiber_threshold, slice_threshold, mode_order_policy, group_mask, hybrid_granularity, coo_row_flags, mid_blocking, single_representation)
+    ptrs = (ctypes.c_void_p * len(dims))(*[(p if p else None) for p in ind_ptrs])
+    h = ctypes.c_void_p()
+    raised = []
+
+    def call(_, nbytes):
+        try:
+            return allocate(nbytes)
+        except BaseException as e:  # must not pass through the library
+            raised.append(e)
+            return None
+
+    rc = lib().hbcsf_build_format_device_pieces(len(dims), d.ctypes.data, nnz, ctypes.cast(ptrs, ctypes.c_void_p),
+                                                ctypes.c_void_p(val_ptr or None),
+                                                ctypes.cast(ctypes.pointer(opts), ctypes.c_void_p), _ALLOCATE(call), None,
+                                                ctypes.c_void_p(workspace_ptr), workspace_bytes, ctypes.c_void_p(stream),
+                                                ctypes.byref(h))
+    if raised:
+        raise raised[0]
+    _check(rc)
     return h
 
 

@@ -58,21 +58,28 @@ uint64_t define_state_bytes(uint64_t rows) {
   return rows <= kDefineStateRows ? ((rows + 31) / 32 * 4 + kAlign - 1) / kAlign * kAlign : 0;
 }
 
-void place_states(hbcsf_tensor* t, uint64_t formatBytes) {
-  t->formatBytes = t->arenaBytes = formatBytes;
+void size_arena(hbcsf_tensor* t) {
+  uint64_t states = 0;
+  t->formatBytes = 0;
   for (int m = 0; m < t->order; ++m) {
     if (!t->modes[m]) continue;
     ModeFormat& f = *t->modes[m];
-    f.stateOffset = t->arenaBytes;
-    f.stateBytes = define_state_bytes(f.rows);
-    t->arenaBytes += f.stateBytes;
+    t->formatBytes += f.blobBytes;
+    states += f.stateBytes = define_state_bytes(f.rows);
   }
+  t->arenaBytes = t->formatBytes + states;
 }
 
-hipError_t clear_states(const hbcsf_tensor* t, uint8_t* arena, hipStream_t s) {
-  const uint64_t vecs = (t->arenaBytes - t->formatBytes) / 16;
+hipError_t place_states(hbcsf_tensor* t, uint8_t* at, hipStream_t s) {
+  uint8_t* next = at;
+  for (int m = 0; m < t->order; ++m) {
+    if (!t->modes[m]) continue;
+    t->modes[m]->state = next;
+    next += t->modes[m]->stateBytes;
+  }
+  const uint64_t vecs = (uint64_t)(next - at) / 16;
   if (vecs == 0) return hipSuccess;
-  return launch_zero_rows((float*)(arena + t->formatBytes), vecs, (uint32_t)(vecs < 256 * 1024 ? (vecs + 255) / 256 : 1024), s);
+  return launch_zero_rows((float*)at, vecs, (uint32_t)(vecs < 256 * 1024 ? (vecs + 255) / 256 : 1024), s);
 }
 
 }  // namespace hbcsf
@@ -114,7 +121,7 @@ int mttkrp_from_mode0(const hbcsf_tensor* t, int mode, int rank, const float* co
   for (int l = 1; l < N; ++l)
     if (f.levelMode[l] == mode) level = l;
   if (level == 0) return fail(HBCSF_EINVAL, "mode out of range");
-  const uint8_t* base = t->arena + f.devOffset;
+  const uint8_t* base = f.dev;
   const GroupFormat& gf = f.g[kCsf];
   const uint64_t nvec = t->dims[mode] * (uint64_t)G;
   uint64_t zb = (nvec + 255) / 256;
@@ -211,12 +218,7 @@ int hbcsf_build_format(int order, const uint64_t* dims, uint64_t nnz, const uint
   std::string err;
   const int rc = build_modes(order, dims, nnz, inds, vals, o, nModes, formats, &err);
   if (rc != HBCSF_OK) return fail(rc, err);
-  uint64_t off = 0;
-  for (int m = 0; m < nModes; ++m) {
-    t->modes[m]->devOffset = off;
-    off += t->modes[m]->blobBytes;
-  }
-  place_states(t.get(), off);
+  size_arena(t.get());
   *out = t.release();
   return HBCSF_OK;
 } HBCSF_CATCH_ALL
@@ -243,16 +245,18 @@ int hbcsf_upload(hbcsf_tensor* t, void* device_arena, uint64_t bytes, void* hip_
   if (e != hipSuccess) return fail_hip(e, "hipDeviceGetAttribute");
   t->numCU = cu > 0 ? cu : 256;
   t->device = dev;
+  uint8_t* at = (uint8_t*)device_arena;
   for (int m = 0; m < nModes; ++m) {
-    const ModeFormat& f = *t->modes[m];
-    e = hipMemcpyAsync((uint8_t*)device_arena + f.devOffset, f.blob, f.blobBytes, hipMemcpyHostToDevice, s);
+    ModeFormat& f = *t->modes[m];
+    e = hipMemcpyAsync(at, f.blob, f.blobBytes, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return fail_hip(e, "hipMemcpyAsync");
+    f.dev = at;
+    at += f.blobBytes;
   }
-  e = clear_states(t, (uint8_t*)device_arena, s);
+  e = place_states(t, at, s);
   if (e != hipSuccess) return fail_hip(e, "launch of the zero-fill kernel");
   e = hipStreamSynchronize(s);
   if (e != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
-  t->arena = (uint8_t*)device_arena;
   t->uploaded = true;
   return HBCSF_OK;
 } HBCSF_CATCH_ALL
@@ -338,7 +342,7 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
   uint32_t lshift = 0;
   while ((1u << lshift) < L) ++lshift;
   hipStream_t s = (hipStream_t)hip_stream;
-  const uint8_t* base = t->arena + f.devOffset;
+  const uint8_t* base = f.dev;
   const uint64_t rowBytes = (uint64_t)rank * (uint64_t)elem;
   hipError_t e;
 
@@ -383,7 +387,7 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
     here.cooBits = (const uint32_t*)(base + f.cooBits.off);
     here.cooPtr = (const uint32_t*)(base + f.cooPtr.off);
     here.rows = (uint32_t)f.rows;
-    here.state = (uint32_t*)(t->arena + f.stateOffset);
+    here.state = (uint32_t*)f.state;
     here.blocks = round_up8((f.rows + 127) / 128);   // a word a wavefront
   }
 

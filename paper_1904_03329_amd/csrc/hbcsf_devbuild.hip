@@ -28,6 +28,7 @@
 #include <rocprim/rocprim.hpp>
 
 #include <chrono>
+#include <functional>
 #include <memory>
 #include <new>
 #include <string>
@@ -1139,6 +1140,9 @@ int check_args(int order, const uint64_t* dims, uint64_t nnz, const hbcsf_opts* 
     if (e_ != hipSuccess) return fail_hip(e_, what); \
   } while (0)
 
+// Where a mode's arrays go: memory of that many bytes, 256-byte aligned, or an error code.
+using Place = std::function<int(uint64_t, uint8_t**)>;
+
 // What one mode's build needs to know, and what it leaves for the end.
 struct ModeBuild {
   Spec sp{};
@@ -1371,7 +1375,7 @@ int number_mode_per_fiber(size_t M, const Sorted<Key>& so, ModeBuild& mb, Worksp
 // Builds one mode from its sorted nonzeros: sizes, layout, fill.  The statistics that need counters are left in mb.cnt.
 template <typename Key>
 int build_mode_device(int N, const uint64_t* dims, size_t M, uint64_t slices, const Sorted<Key>& so, ModeBuild& mb, Workspace& w,
-                      uint8_t* arena, uint64_t arenaBytes, uint64_t* arenaUsed, ModeFormat* out, hipStream_t st) {
+                      const Place& place, ModeFormat* out, hipStream_t st) {
   const Spec& sp = mb.sp;
   Tables tb{};
   uint32_t* seg[3] = {nullptr, nullptr, nullptr};
@@ -1381,10 +1385,10 @@ int build_mode_device(int N, const uint64_t* dims, size_t M, uint64_t slices, co
   }
   // ---- layout, then fill ----
   layout_mode(out, N, mb.gS, mb.gM, mb.nSeg);
-  if (*arenaUsed + out->blobBytes > arenaBytes) return fail(HBCSF_ENOMEM, "device arena is too small for the format");
-  out->devOffset = *arenaUsed;
-  uint8_t* base = arena + out->devOffset;
-  *arenaUsed += out->blobBytes;
+  uint8_t* base = nullptr;
+  const int rp = place(out->blobBytes, &base);
+  if (rp != HBCSF_OK) return rp;
+  out->dev = base;
   auto U32 = [&](const ArrayRef& r) { return (uint32_t*)(base + r.off); };
   OutArrays o{};
   for (int l = 0; l < N; ++l) {
@@ -1465,8 +1469,7 @@ int build_mode_device(int N, const uint64_t* dims, size_t M, uint64_t slices, co
 // All modes of one key type.
 template <typename Key>
 int build_all(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds, const float* vals, const hbcsf_opts& opts,
-              int totalBits, Workspace& w, uint8_t* arena, uint64_t arenaBytes, uint64_t* arenaUsed,
-              hbcsf_tensor* t, hipStream_t st) {
+              int totalBits, Workspace& w, const Place& place, hbcsf_tensor* t, hipStream_t st) {
   const auto t_begin = std::chrono::steady_clock::now();
   const int nModes = t->single ? 1 : N;  // single representation: only mode 0's tree is stored
   // the common order: the list every mode's levels below the root follow (with one mode to build, that mode's own order)
@@ -1528,8 +1531,7 @@ int build_all(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds
       const int rs = sort_mode<Key>(M, base, mb, mode == order[0] && sp.blockBits == 0, w, &so, st);
       if (rs != HBCSF_OK) return rs;
     }
-    const int rb = build_mode_device<Key>(N, dims, M, slice_bound(M, dims[mode], sp.blockBits != 0), so, mb, w, arena, arenaBytes,
-                                          arenaUsed, out, st);
+    const int rb = build_mode_device<Key>(N, dims, M, slice_bound(M, dims[mode], sp.blockBits != 0), so, mb, w, place, out, st);
     if (rb != HBCSF_OK) return rb;
   }
   unsigned long long host[HBCSF_MAX_ORDER * kCounters];
@@ -1549,34 +1551,10 @@ int build_all(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds
   return HBCSF_OK;
 }
 
-}  // namespace
-
-extern "C" {
-
-int hbcsf_device_build_bytes(int order, const uint64_t* dims, uint64_t nnz, const hbcsf_opts* opts,
-                             uint64_t* arena_bytes, uint64_t* workspace_bytes) try {
-  hbcsf_opts o;
-  int totalBits = 0, maxBits = 0;
-  const int rc = check_args(order, dims, nnz, opts, &o, &totalBits, &maxBits);
-  if (rc != HBCSF_OK) return rc;
-  if (!arena_bytes || !workspace_bytes) return fail(HBCSF_EINVAL, "null argument");
-  uint64_t maxDim = 0;
-  for (int m = 0; m < order; ++m) maxDim = dims[m] > maxDim ? dims[m] : maxDim;
-  size_t tbytes = 0;
-  const uint64_t slices = slice_bound((size_t)nnz, maxDim, o.mid_blocking > 1);
-  HIP_TRY(temp_bytes((size_t)nnz, (size_t)((maxDim + 31) / 32), slices, o.fiber_threshold, maxBits, &tbytes),
-          "rocPRIM scratch query");
-  Workspace w{};
-  carve(w, nullptr, order, (size_t)nnz, row_maps_bytes(order, dims), slices, o.fiber_threshold, tbytes, maxBits > 64, per_fiber(o),
-        o.mid_blocking > 1);
-  *workspace_bytes = w.total;
-  *arena_bytes = arena_bound(order, dims, nnz, o.fiber_threshold);
-  return HBCSF_OK;
-} HBCSF_CATCH_ALL
-
-int hbcsf_build_format_device(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* const* inds,
-                              const float* vals, const hbcsf_opts* opts, void* device_arena, uint64_t arena_bytes,
-                              void* workspace, uint64_t workspace_bytes, void* hip_stream, hbcsf_tensor** out) try {
+// hbcsf_build_format_device; place: where the modes' arrays and the words of state go.
+int build_device(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* const* inds, const float* vals,
+                 const hbcsf_opts* opts, void* device_arena, const Place& place, void* workspace, uint64_t workspace_bytes,
+                 void* hip_stream, hbcsf_tensor** out) {
   if (!out) return fail(HBCSF_EINVAL, "out is null");
   *out = nullptr;
   hbcsf_opts o;
@@ -1613,20 +1591,21 @@ int hbcsf_build_format_device(int order, const uint64_t* dims, uint64_t nnz, con
   HIP_TRY(hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev), "hipDeviceGetAttribute");
   t->numCU = cu > 0 ? cu : 256;
   t->device = dev;
-  uint64_t used = 0;
   t->single = o.single_representation == 1;
   for (int m = 0; m < (t->single ? 1 : order); ++m) {
     t->modes[m].reset(new (std::nothrow) ModeFormat);
     if (!t->modes[m]) return fail(HBCSF_ENOMEM, "out of host memory");
   }
-  const int rb = maxBits > 64 ? build_all<u128>(order, dims, (size_t)nnz, inds, vals, o, totalBits, w,
-                                                (uint8_t*)device_arena, arena_bytes, &used, t.get(), st)
-                              : build_all<uint64_t>(order, dims, (size_t)nnz, inds, vals, o, totalBits, w,
-                                                    (uint8_t*)device_arena, arena_bytes, &used, t.get(), st);
+  const int rb = maxBits > 64 ? build_all<u128>(order, dims, (size_t)nnz, inds, vals, o, totalBits, w, place, t.get(), st)
+                              : build_all<uint64_t>(order, dims, (size_t)nnz, inds, vals, o, totalBits, w, place, t.get(), st);
   if (rb != HBCSF_OK) return rb;
-  place_states(t.get(), used);
-  if (t->arenaBytes > arena_bytes) return fail(HBCSF_ENOMEM, "device arena is too small for the format");
-  HIP_TRY(clear_states(t.get(), (uint8_t*)device_arena, st), "launch of the zero-fill kernel");
+  size_arena(t.get());
+  if (t->arenaBytes > t->formatBytes) {
+    uint8_t* states = nullptr;
+    const int rp = place(t->arenaBytes - t->formatBytes, &states);
+    if (rp != HBCSF_OK) return rp;
+    HIP_TRY(place_states(t.get(), states, st), "launch of the zero-fill kernel");
+  }
   double sq = 0.0;
   if (nnz > 0) {
     size_t tb_ = w.tempBytes;
@@ -1637,27 +1616,90 @@ int hbcsf_build_format_device(int order, const uint64_t* dims, uint64_t nnz, con
     HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
   }
   t->normSq = sq;
-  t->arena = (uint8_t*)device_arena;
   t->uploaded = true;
   *out = t.release();
   return HBCSF_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+int hbcsf_device_build_bytes(int order, const uint64_t* dims, uint64_t nnz, const hbcsf_opts* opts,
+                             uint64_t* arena_bytes, uint64_t* workspace_bytes) try {
+  hbcsf_opts o;
+  int totalBits = 0, maxBits = 0;
+  const int rc = check_args(order, dims, nnz, opts, &o, &totalBits, &maxBits);
+  if (rc != HBCSF_OK) return rc;
+  if (!arena_bytes || !workspace_bytes) return fail(HBCSF_EINVAL, "null argument");
+  uint64_t maxDim = 0;
+  for (int m = 0; m < order; ++m) maxDim = dims[m] > maxDim ? dims[m] : maxDim;
+  size_t tbytes = 0;
+  const uint64_t slices = slice_bound((size_t)nnz, maxDim, o.mid_blocking > 1);
+  HIP_TRY(temp_bytes((size_t)nnz, (size_t)((maxDim + 31) / 32), slices, o.fiber_threshold, maxBits, &tbytes),
+          "rocPRIM scratch query");
+  Workspace w{};
+  carve(w, nullptr, order, (size_t)nnz, row_maps_bytes(order, dims), slices, o.fiber_threshold, tbytes, maxBits > 64, per_fiber(o),
+        o.mid_blocking > 1);
+  *workspace_bytes = w.total;
+  *arena_bytes = arena_bound(order, dims, nnz, o.fiber_threshold);
+  return HBCSF_OK;
+} HBCSF_CATCH_ALL
+
+int hbcsf_build_format_device(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* const* inds,
+                              const float* vals, const hbcsf_opts* opts, void* device_arena, uint64_t arena_bytes,
+                              void* workspace, uint64_t workspace_bytes, void* hip_stream, hbcsf_tensor** out) try {
+  uint64_t used = 0;
+  return build_device(order, dims, nnz, inds, vals, opts, device_arena, [&](uint64_t bytes, uint8_t** at) {
+    if (used + bytes > arena_bytes) return fail(HBCSF_ENOMEM, "device arena is too small for the format");
+    *at = (uint8_t*)device_arena + used;
+    used += bytes;
+    return (int)HBCSF_OK;
+  }, workspace, workspace_bytes, hip_stream, out);
+} HBCSF_CATCH_ALL
+
+int hbcsf_build_format_device_pieces(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* const* inds, const float* vals,
+                                     const hbcsf_opts* opts, hbcsf_allocate allocate, void* context, void* workspace,
+                                     uint64_t workspace_bytes, void* hip_stream, hbcsf_tensor** out) try {
+  if (!allocate) {
+    if (out) *out = nullptr;
+    return fail(HBCSF_EINVAL, "null argument");
+  }
+  return build_device(order, dims, nnz, inds, vals, opts, workspace, [&](uint64_t bytes, uint8_t** at) {
+    *at = (uint8_t*)allocate(context, bytes);
+    if (!*at) return fail(HBCSF_ENOMEM, "no device memory was given for a part of the format");
+    if (((uintptr_t)*at & (kAlign - 1)) != 0) return fail(HBCSF_EINVAL, "device memory must be 256-byte aligned");
+    return (int)HBCSF_OK;
+  }, workspace, workspace_bytes, hip_stream, out);
 } HBCSF_CATCH_ALL
 
 int hbcsf_relocate(hbcsf_tensor* t, void* new_arena, uint64_t bytes, void* hip_stream) try {
   if (!t || !new_arena) return fail(HBCSF_EINVAL, "null argument");
-  if (!t->uploaded || !t->arena) return fail(HBCSF_ESTATE, "the tensor has no device copy");
+  if (!t->uploaded) return fail(HBCSF_ESTATE, "the tensor has no device copy");
   if (bytes < t->arenaBytes) return fail(HBCSF_ENOMEM, "the new arena is smaller than hbcsf_device_bytes");
   if (((uintptr_t)new_arena & (kAlign - 1)) != 0) return fail(HBCSF_EINVAL, "device arena must be 256-byte aligned");
   hipStream_t st = (hipStream_t)hip_stream;
-  HIP_TRY(hipMemcpyAsync(new_arena, t->arena, t->arenaBytes, hipMemcpyDeviceToDevice, st), "hipMemcpyAsync");
+  uint8_t* at = (uint8_t*)new_arena;
+  for (int m = 0; m < t->order; ++m) {
+    if (!t->modes[m]) continue;
+    HIP_TRY(hipMemcpyAsync(at, t->modes[m]->dev, t->modes[m]->blobBytes, hipMemcpyDeviceToDevice, st), "hipMemcpyAsync");
+    at += t->modes[m]->blobBytes;
+  }
   HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
-  t->arena = (uint8_t*)new_arena;
+  HIP_TRY(place_states(t, at, st), "launch of the zero-fill kernel");
+  HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
+  at = (uint8_t*)new_arena;
+  for (int m = 0; m < t->order; ++m) {
+    if (!t->modes[m]) continue;
+    t->modes[m]->dev = at;
+    at += t->modes[m]->blobBytes;
+  }
   return HBCSF_OK;
 } HBCSF_CATCH_ALL
 
 int hbcsf_download(hbcsf_tensor* t, void* hip_stream) try {
   if (!t) return fail(HBCSF_EINVAL, "null argument");
-  if (!t->uploaded || !t->arena) return fail(HBCSF_ESTATE, "the tensor has no device copy");
+  if (!t->uploaded) return fail(HBCSF_ESTATE, "the tensor has no device copy");
   hipStream_t st = (hipStream_t)hip_stream;
   for (int m = 0; m < t->order; ++m) {
     if (!t->modes[m]) continue;   // single representation: only mode 0 exists
@@ -1666,7 +1708,7 @@ int hbcsf_download(hbcsf_tensor* t, void* hip_stream) try {
     void* mem = nullptr;
     if (posix_memalign(&mem, kAlign, (size_t)f.blobBytes) != 0 || !mem) return fail(HBCSF_ENOMEM, "out of host memory");
     f.blob = (uint8_t*)mem;
-    HIP_TRY(hipMemcpyAsync(f.blob, t->arena + f.devOffset, f.blobBytes, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
+    HIP_TRY(hipMemcpyAsync(f.blob, f.dev, f.blobBytes, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
   }
   HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
   return HBCSF_OK;

@@ -52,8 +52,8 @@ struct ModeFormat {
   ArrayRef cooPtr;                 // COO-group nonzeros before each 32-row word (words + 1 entries)
   uint8_t* blob = nullptr;         // host copy of all arrays, kAlign-aligned
   uint64_t blobBytes = 0;
-  uint64_t devOffset = 0;          // where the blob sits in the device arena
-  uint64_t stateOffset = 0;        // ... and the launches' words of state (DefineArgs), one per 32 rows
+  uint8_t* dev = nullptr;          // the blob in device memory (the caller's)
+  uint8_t* state = nullptr;        // ... and the launches' words of state (DefineArgs), one per 32 rows
   uint64_t stateBytes = 0;         // 0: the mode is too long for them
   hbcsf_stats stats{};
 

@@ -18,13 +18,12 @@ struct hbcsf_tensor {
   double normSq = 0.0;  // sum of the squared values (for the CPD fit)
   hbcsf_opts opts{};
   std::unique_ptr<hbcsf::ModeFormat> modes[HBCSF_MAX_ORDER];
-  uint64_t arenaBytes = 0;
-  uint8_t* arena = nullptr;  // caller's device memory: the formats, then the launches' words of state
-  uint64_t formatBytes = 0;  // of the arena's bytes, the formats'
+  uint64_t arenaBytes = 0;   // device memory of it all: the formats, then the launches' words of state
+  uint64_t formatBytes = 0;  // of these, the formats'
   bool uploaded = false;
   bool single = false;       // only modes[0] exists; the other modes are computed from it (single representation)
   int numCU = 256;
-  int device = -1;           // the arena's
+  int device = -1;           // the device memory's
   uint64_t sliceThreshold = 0;
   uint64_t wavesPerCU = 0;   // launch sizing override, 0 = default
   int steps = 0;             // records in flight per lane group, 0 = automatic
@@ -66,10 +65,10 @@ int fail_exception() noexcept;
 
 // Bytes of the words of state (DefineArgs) of a mode with that many rows.
 uint64_t define_state_bytes(uint64_t rows);
-// Places the words of state behind the formats, which take the arena's first `formatBytes` bytes: sets arenaBytes.
-void place_states(hbcsf_tensor* t, uint64_t formatBytes);
-// Clears them, in an arena of the caller's.
-hipError_t clear_states(const hbcsf_tensor* t, uint8_t* arena, hipStream_t s);
+// Sets the sizes of the words of state and of the whole, once the formats' are known.
+void size_arena(hbcsf_tensor* t);
+// Says where the words of state lie (one mode's behind the other's) and clears them.
+hipError_t place_states(hbcsf_tensor* t, uint8_t* at, hipStream_t s);
 
 // hbcsf_mttkrp with ALS work in the same launch, for calls that take it (fp32).
 struct GuestArgs;
