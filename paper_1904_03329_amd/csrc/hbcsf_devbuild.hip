@@ -49,6 +49,7 @@ struct Spec {
   u128 upTo[HBCSF_MAX_ORDER];       // by level: the bits of it and of every level above, the block's among them
   uint32_t L, cooOn, cslOn, cooRowFlags;
   uint32_t byteLevels;  // bit l: level l's row map holds bytes, otherwise bits
+  uint32_t marked;      // bit g: group g has row maps
   uint32_t perFiber;  // hybrid_granularity = 1: heavy slices are split into a CSL piece and a CSF piece
   int blockBits, blockDrop;  // level-1 blocking: (index of level 1 >> blockDrop) stands above the root
 };
@@ -378,7 +379,8 @@ struct OutArrays {
 // 5 M-nonzero build: copies of a word in eight L2s stay stale, and every nonzero that meets one adds an atomic).  Longer
 // modes keep the bitmap, which is what still fits an L2 (40 M rows: 7 ms of a 150 M-nonzero build against 10 ms).
 constexpr uint64_t kByteRows = 4ull << 20;
-__device__ __forceinline__ void mark_row(const Spec& sp, int level, uint32_t* map, uint32_t r) {
+__device__ __forceinline__ void mark_row(const Spec& sp, int group, int level, uint32_t* map, uint32_t r) {
+  if (!((sp.marked >> group) & 1u)) return;
   if ((sp.byteLevels >> level) & 1u) {
     reinterpret_cast<uint8_t*>(map)[r] = 1;
   } else {
@@ -402,7 +404,7 @@ __global__ void fill_nonzeros_kernel(const Key* K, const uint32_t* V, size_t M, 
   const uint32_t v = V[p];
   if (g == kCoo) {
     for (int l = sp.cooRowFlags ? 1 : 0; l < sp.N; ++l) o.cooInd[l][pos] = idx[l];
-    for (int l = 1; l < sp.N; ++l) mark_row(sp, l, o.seen[kCoo][l], idx[l]);
+    for (int l = 1; l < sp.N; ++l) mark_row(sp, kCoo, l, o.seen[kCoo][l], idx[l]);
     o.cooVal[pos] = v;
     atomicOr(&o.cooBits[idx[0] >> 5], 1u << (idx[0] & 31));
     atomicOr(&o.owned[idx[0] >> 5], 1u << (idx[0] & 31));
@@ -412,13 +414,13 @@ __global__ void fill_nonzeros_kernel(const Key* K, const uint32_t* V, size_t M, 
   const uint32_t ord = t.c6[s].s[g];
   if (g == kCsl) {
     for (int l = 1; l < sp.N; ++l) o.cslInd[l][pos] = idx[l];
-    for (int l = 1; l < sp.N; ++l) mark_row(sp, l, o.seen[kCsl][l], idx[l]);
+    for (int l = 1; l < sp.N; ++l) mark_row(sp, kCsl, l, o.seen[kCsl][l], idx[l]);
     o.cslVal[pos] = v;
     if (cut) o.cslRun[pos / sp.L] = ord;
     return;
   }
   o.csfInd[sp.N - 1][pos] = idx[sp.N - 1];
-  mark_row(sp, sp.N - 1, o.seen[kCsf][sp.N - 1], idx[sp.N - 1]);
+  mark_row(sp, kCsf, sp.N - 1, o.seen[kCsf][sp.N - 1], idx[sp.N - 1]);
   o.csfVal[pos] = v;
   if (cut) o.csfRun[0][pos / sp.L] = ord;
   for (int l = 1; l <= sp.NF; ++l) {
@@ -427,7 +429,7 @@ __global__ void fill_nonzeros_kernel(const Key* K, const uint32_t* V, size_t M, 
       const uint32_t id = (l == 1 ? seg0 : l == 2 ? seg1 : seg2)[p];
       o.csfInd[l][id] = idx[l];
       o.csfPtr[l][id] = pos;
-      mark_row(sp, l, o.seen[kCsf][l], idx[l]);
+      mark_row(sp, kCsf, l, o.seen[kCsf][l], idx[l]);
       if (cut) o.csfRun[l][pos / sp.L] = id;
     }
   }
@@ -838,7 +840,7 @@ __global__ __launch_bounds__(256) void fill_tiles_kernel(const Key* __restrict__
       if (in[q].grp == kCsf) {
         o.csfVal[at] = v[q];
         o.csfInd[leaf][at] = leafIdx[q];
-        mark_row(sp, leaf, o.seen[kCsf][leaf], leafIdx[q]);
+        mark_row(sp, kCsf, leaf, o.seen[kCsf][leaf], leafIdx[q]);
         if (cut) o.csfRun[0][at >> ls] = in[q].ord;
 #pragma unroll
         for (int l = 1; l <= NF; ++l) {
@@ -848,7 +850,7 @@ __global__ __launch_bounds__(256) void fill_tiles_kernel(const Key* __restrict__
             const uint32_t i = index(l);
             o.csfInd[l][id] = i;
             o.csfPtr[l][id] = at;
-            mark_row(sp, l, o.seen[kCsf][l], i);
+            mark_row(sp, kCsf, l, o.seen[kCsf][l], i);
             if (cut) o.csfRun[l][at >> ls] = id;
           }
         }
@@ -856,22 +858,22 @@ __global__ __launch_bounds__(256) void fill_tiles_kernel(const Key* __restrict__
         o.cslVal[at] = v[q];
         if (cut) o.cslRun[at >> ls] = in[q].ord;
         o.cslInd[leaf][at] = leafIdx[q];
-        mark_row(sp, leaf, o.seen[kCsl][leaf], leafIdx[q]);
+        mark_row(sp, kCsl, leaf, o.seen[kCsl][leaf], leafIdx[q]);
 #pragma unroll
         for (int l = 1; l < leaf; ++l) {
           const uint32_t i = index(l);
           o.cslInd[l][at] = i;
-          mark_row(sp, l, o.seen[kCsl][l], i);
+          mark_row(sp, kCsl, l, o.seen[kCsl][l], i);
         }
       } else {
         o.cooVal[at] = v[q];
         o.cooInd[leaf][at] = leafIdx[q];
-        mark_row(sp, leaf, o.seen[kCoo][leaf], leafIdx[q]);
+        mark_row(sp, kCoo, leaf, o.seen[kCoo][leaf], leafIdx[q]);
 #pragma unroll
         for (int l = 1; l < leaf; ++l) {
           const uint32_t i = index(l);
           o.cooInd[l][at] = i;
-          mark_row(sp, l, o.seen[kCoo][l], i);
+          mark_row(sp, kCoo, l, o.seen[kCoo][l], i);
         }
         const uint32_t root = index(0);
         if (!sp.cooRowFlags) o.cooInd[0][at] = root;
@@ -1150,6 +1152,7 @@ struct ModeBuild {
   uint64_t S = 0, gS[3] = {0, 0, 0}, gM[3] = {0, 0, 0};
   uint64_t nSeg[HBCSF_MAX_FIBER_LEVELS] = {0, 0, 0}, fibNat[HBCSF_MAX_FIBER_LEVELS] = {0, 0, 0};
   uint64_t fibCsf[HBCSF_MAX_FIBER_LEVELS] = {0, 0, 0};
+  bool whole[3] = {false, false, false};  // the group holds all nonzeros: its distinct rows are the other modes' slices
   unsigned long long* cnt = nullptr;  // device counters: [1] shared slices, [2], [3], [5] CSF fibers (per-fiber choice),
                                       // [4] owned rows, [8 ..] distinct rows
 };
@@ -1375,7 +1378,7 @@ int number_mode_per_fiber(size_t M, const Sorted<Key>& so, ModeBuild& mb, Worksp
 // Builds one mode from its sorted nonzeros: sizes, layout, fill.  The statistics that need counters are left in mb.cnt.
 template <typename Key>
 int build_mode_device(int N, const uint64_t* dims, size_t M, uint64_t slices, const Sorted<Key>& so, ModeBuild& mb, Workspace& w,
-                      const Place& place, ModeFormat* out, hipStream_t st) {
+                      const Place& place, ModeFormat* out, bool othersCounted, hipStream_t st) {
   const Spec& sp = mb.sp;
   Tables tb{};
   uint32_t* seg[3] = {nullptr, nullptr, nullptr};
@@ -1406,12 +1409,17 @@ int build_mode_device(int N, const uint64_t* dims, size_t M, uint64_t slices, co
   o.owned = U32(out->ownedBits);
   o.cooBits = U32(out->cooBits);
   const size_t ownedWords = (out->rows + 31) / 32;
-  // row maps: the groups that exist, their levels one after the other
+  // row maps: the groups that exist, their levels one after the other.  A group that holds all nonzeros gathers every row of a
+  // mode that has a nonzero, as many as that mode has slices, and needs no map (50 M nonzeros 130 us a mode).
+  for (int g = 0; g < 3; ++g) {
+    mb.whole[g] = othersCounted && !sp.perFiber && M > 0 && out->g[g].nnz == M;
+    if (out->g[g].nnz > 0 && !mb.whole[g]) mb.sp.marked |= 1u << g;
+  }
   uint64_t mapBytes = 0;
   for (int g = 0; g < 3; ++g)
     for (int l = 1; l < N; ++l) {
       o.seen[g][l] = (uint32_t*)(w.seen + mapBytes);
-      if (out->g[g].nnz > 0) mapBytes += row_map_bytes(dims[out->levelMode[l]]);
+      if ((sp.marked >> g) & 1u) mapBytes += row_map_bytes(dims[out->levelMode[l]]);
     }
   {
     const size_t mapWords = (size_t)(mapBytes / 4);
@@ -1457,7 +1465,7 @@ int build_mode_device(int N, const uint64_t* dims, size_t M, uint64_t slices, co
   count(o.owned, ownedWords, 4);
   for (int g = 0; g < 3; ++g)
     for (int l = 1; l < N; ++l)
-      if (out->g[g].nnz > 0) count(o.seen[g][l], (size_t)(row_map_bytes(dims[out->levelMode[l]]) / 4), 8 + g * HBCSF_MAX_ORDER + l);
+      if ((sp.marked >> g) & 1u) count(o.seen[g][l], (size_t)(row_map_bytes(dims[out->levelMode[l]]) / 4), 8 + g * HBCSF_MAX_ORDER + l);
   size_t most = 0;
   for (int k = 0; k < which; ++k) most = bc.words[k] > most ? bc.words[k] : most;
   const unsigned bx = grid_capped((most + 15) / 16);
@@ -1492,6 +1500,8 @@ int build_all(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds
     if (rs != HBCSF_OK) return rs;
   }
   ModeBuild mbs[HBCSF_MAX_ORDER];
+  bool othersCounted = nModes == N;   // every mode's slices are its distinct indices (with blocking they are pieces)
+  for (int m = 0; m < N; ++m) othersCounted = othersCounted && mid_block_bits(N, dims, opts, m) == 0;
   for (int mode = 0; mode < nModes; ++mode) {
     ModeBuild& mb = mbs[mode];
     ModeFormat* out = t->modes[mode].get();
@@ -1531,7 +1541,8 @@ int build_all(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds
       const int rs = sort_mode<Key>(M, base, mb, mode == order[0] && sp.blockBits == 0, w, &so, st);
       if (rs != HBCSF_OK) return rs;
     }
-    const int rb = build_mode_device<Key>(N, dims, M, slice_bound(M, dims[mode], sp.blockBits != 0), so, mb, w, place, out, st);
+    const int rb = build_mode_device<Key>(N, dims, M, slice_bound(M, dims[mode], sp.blockBits != 0), so, mb, w, place, out,
+                                          othersCounted, st);
     if (rb != HBCSF_OK) return rb;
   }
   unsigned long long host[HBCSF_MAX_ORDER * kCounters];
@@ -1545,7 +1556,8 @@ int build_all(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds
     fill_count_stats(out, N, M, mb.S, mb.fibNat, mb.fibCsf, mb.nSeg, mb.gS, mb.gM, c[1]);
     out->stats.owned_rows = c[4];
     for (int g = 0; g < 3; ++g)
-      for (int l = 1; l < N; ++l) out->stats.distinct_rows[g][l] = c[8 + g * HBCSF_MAX_ORDER + l];
+      for (int l = 1; l < N; ++l)
+        out->stats.distinct_rows[g][l] = mb.whole[g] ? mbs[out->levelMode[l]].S : c[8 + g * HBCSF_MAX_ORDER + l];
     out->stats.build_seconds = seconds / nModes;
   }
   return HBCSF_OK;
