@@ -9,6 +9,7 @@
 // passes instead of a whole key's eight.  The keys keep the layout of the common order in every mode: the sort looks at
 // the root's bits where they lie, and "the index of some level or one above it changes" is a difference of two keys
 // under that level's mask (a pass that rewrote the keys as (root, ..., leaf) first took 0.23 ms of 50 M nonzeros).
+// Keys of 64 bits are sorted by hbcsf_sort.h, wider ones and tensors of 2^30 nonzeros and more by rocPRIM.
 //
 // Numbering.  No array is kept per nonzero.  A wavefront takes 1024 sorted nonzeros, 64 at a time; "a slice / a fiber
 // begins here" are ballots, so what it needs to number them is the count before its tile (one scan over the tiles).
@@ -17,7 +18,7 @@
 // the runs), so a segment's number is the fibers before it plus the cuts before it.  The sorted keys are read three times
 // and each output is written once.
 //
-// Radix sort and the scans over tiles, slices and runs are rocPRIM device primitives; everything specific to the format
+// The scans over tiles, slices and runs are rocPRIM device primitives; everything specific to the format
 // is in the kernels below.  With the per-fiber group choice a slice's nonzeros part between two groups, and the
 // numbering goes through per-nonzero scans instead (number_mode_per_fiber).
 
@@ -34,6 +35,7 @@
 #include <string>
 
 #include "hbcsf.h"
+#include "hbcsf_sort.h"
 #include "hbcsf_tensor.h"
 
 using namespace hbcsf;
@@ -200,19 +202,9 @@ __device__ __forceinline__ void wave_add(unsigned long long* dst, unsigned long 
   if ((threadIdx.x & 63) == 0 && v) atomicAdd(dst, v);
 }
 
-struct IndPtrs {
-  const uint32_t* p[HBCSF_MAX_ORDER];
-};
-
 struct Carried {  // what rides along while one 64-bit half of a wide key is being sorted
   uint64_t other;  // the half that is not the sort key of this pass
   uint32_t v, pad;
-};
-
-// Where each mode's index lies in the key of the common order.
-struct BaseKey {
-  int shift[HBCSF_MAX_ORDER];       // by mode
-  uint64_t mask[HBCSF_MAX_ORDER], dims[HBCSF_MAX_ORDER];
 };
 
 // Key = uint64_t: K / V receive the packed key and the value bits.  Key = u128: the key is sorted in two
@@ -222,20 +214,8 @@ __global__ void pack_kernel(IndPtrs inds, const float* vals, size_t M, int N, Ba
                             unsigned long long* bad) {
   const size_t z = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (z >= M) return;
-  Key key = 0;
   bool off = false;
-#pragma unroll
-  for (int m = 0; m < HBCSF_MAX_ORDER; ++m) {
-    if (m >= N) break;
-    uint32_t i = inds.p[m][z];
-    if ((uint64_t)i >= bk.dims[m]) {
-      // the call will be refused, but the numbering is enqueued before the host knows: it has room for as many
-      // slices as the mode has rows, so an index past them must not become one (nor spill into the next field)
-      off = true;
-      i = 0;
-    }
-    key |= (Key)i << bk.shift[m];
-  }
+  const Key key = pack_key<Key>(inds, N, bk, z, off);
   if (sizeof(Key) == 8) {
     K[z] = (uint64_t)key;
     V[z] = __float_as_uint(vals[z]);
@@ -966,6 +946,8 @@ struct Workspace {
   Totals* totals;
   double* normSq;
   uint8_t* seen;         // row maps of the 3 groups and the levels below the root (statistics)
+  bool ownSort;          // own_sort(): its scratch is sort.s
+  Sorter sort;
   void* temp;
   size_t tempBytes;
   uint64_t total;
@@ -987,11 +969,17 @@ uint64_t row_maps_bytes(int order, const uint64_t* dims) {
 // Entries the slice tables need: slices are at most nonzeros, and without blocking at most rows.
 uint64_t slice_bound(size_t M, uint64_t maxDim, bool blocked) { return blocked || (uint64_t)M < maxDim ? (uint64_t)M : maxDim; }
 
+// Does the pair sort of hbcsf_sort.h serve?  Keys of 64 bits, and places that fit its published words.  (A whole build by
+// rocPRIM's sort -> by that one, order 3, us: 20 000 nonzeros 668 -> 636, 0.2 M 745 -> 688, 0.8 M 1079 -> 825, 3.2 M 1271 -> 1071,
+// 40 M 7032 -> 4853; order 4: 803 -> 795, 979 -> 873, 1440 -> 1061, 1751 -> 1426, 10 142 -> 6974; a sixth of the last two's gain is
+// that the arrays are not copied any more.)
+bool own_sort(size_t M, int maxBits) { return maxBits <= 64 && M > 0 && M < (size_t)kSortCounts; }
+
 hipError_t temp_bytes(size_t M, size_t maxWords, uint64_t slices, uint32_t L, int totalBits, size_t* out) {
   const bool wide = totalBits > 64;
   // the largest scratch any rocPRIM call below asks for
   size_t need = 0, b = 0;
-  hipError_t e;
+  hipError_t e = hipSuccess;
   if (wide) {
     rocprim::double_buffer<uint64_t> kb((uint64_t*)nullptr, (uint64_t*)nullptr);
     rocprim::double_buffer<uint32_t> vb((uint32_t*)nullptr, (uint32_t*)nullptr);
@@ -1000,7 +988,7 @@ hipError_t temp_bytes(size_t M, size_t maxWords, uint64_t slices, uint32_t L, in
     need = b > need ? b : need;
     rocprim::double_buffer<Carried> cb((Carried*)nullptr, (Carried*)nullptr);
     e = rocprim::radix_sort_pairs(nullptr, b, kb, cb, M, 0u, 64u);
-  } else {
+  } else if (!own_sort(M, totalBits)) {
     // (the most any range of bits takes: with more than one pass the scratch holds a second copy of the pairs)
     e = rocprim::radix_sort_pairs(nullptr, b, (const uint64_t*)nullptr, (uint64_t*)nullptr, (const uint32_t*)nullptr,
                                   (uint32_t*)nullptr, M, 0u, 64u);
@@ -1047,6 +1035,7 @@ hipError_t temp_bytes(size_t M, size_t maxWords, uint64_t slices, uint32_t L, in
 void carve(Workspace& w, uint8_t* base, int order, size_t M, uint64_t mapBytes, uint64_t slices, uint32_t L, size_t tempBytes,
            bool wide, bool perFiber, bool blocked) {
   uint64_t off = 0;
+  w.ownSort = own_sort(M, wide ? 65 : 64);
   auto take = [&](uint64_t bytes) {
     uint8_t* p = base ? base + off : nullptr;
     off += up256(bytes);
@@ -1082,6 +1071,7 @@ void carve(Workspace& w, uint8_t* base, int order, size_t M, uint64_t mapBytes, 
   w.totals = (Totals*)take(sizeof(Totals));
   w.normSq = (double*)take(8);
   w.seen = (uint8_t*)take(3 * mapBytes);
+  if (w.ownSort) sort_scratch(M, take(sort_scratch(M, nullptr, &w.sort.s)), &w.sort.s);
   w.temp = take(tempBytes);
   w.tempBytes = tempBytes;
   w.total = off;
@@ -1152,6 +1142,7 @@ struct ModeBuild {
   uint64_t S = 0, gS[3] = {0, 0, 0}, gM[3] = {0, 0, 0};
   uint64_t nSeg[HBCSF_MAX_FIBER_LEVELS] = {0, 0, 0}, fibNat[HBCSF_MAX_FIBER_LEVELS] = {0, 0, 0};
   uint64_t fibCsf[HBCSF_MAX_FIBER_LEVELS] = {0, 0, 0};
+  int sortFrom = 0, sortMany = 0;  // own_sort(): the passes of this mode's order
   bool whole[3] = {false, false, false};  // the group holds all nonzeros: its distinct rows are the other modes' slices
   unsigned long long* cnt = nullptr;  // device counters: [1] shared slices, [2], [3], [5] CSF fibers (per-fiber choice),
                                       // [4] owned rows, [8 ..] distinct rows
@@ -1173,6 +1164,15 @@ int sort_base(int N, size_t M, const uint32_t* const* inds, const float* vals, c
   constexpr bool kWide = sizeof(Key) == 16;
   IndPtrs ip{};
   for (int m = 0; m < N; ++m) ip.p[m] = inds[m];
+  if constexpr (!kWide) {
+    if (w.ownSort) {
+      base->K = w.K[2];
+      base->V = w.V[2];
+      HIP_TRY(w.sort.count(ip, vals, M, N, bk, w.bad, st), "counting of the digits");
+      HIP_TRY(w.sort.run(0, (totalBits + 7) / 8, nullptr, nullptr, w.K[2], w.V[2], w.K[0], w.V[0], st), "radix sort");
+      return HBCSF_OK;
+    }
+  }
   hipLaunchKernelGGL(pack_kernel<Key>, dim3(grid_for(M)), dim3(256), 0, st, ip, vals, M, N, bk, w.K[0], w.V[0], w.C[0], w.bad);
   size_t tb = w.tempBytes;
   if constexpr (!kWide) {
@@ -1213,6 +1213,12 @@ int sort_mode(size_t M, const Sorted<Key>& base, const ModeBuild& mb, bool isBas
     out->V = base.V;
     if (isBase) return HBCSF_OK;
     const Spec& sp = mb.sp;
+    if (w.ownSort) {
+      HIP_TRY(w.sort.run(mb.sortFrom, mb.sortMany, base.K, base.V, w.K[0], w.V[0], w.sort.s.K, w.sort.s.V, st), "radix sort");
+      out->K = w.K[0];
+      out->V = w.V[0];
+      return HBCSF_OK;
+    }
     // by root, then (blocked modes) by block: the top bits of the level-1 index
     uint64_t* k = w.K[sp.blockBits ? 1 : 0];
     uint32_t* v = w.V[sp.blockBits ? 1 : 0];
@@ -1494,12 +1500,36 @@ int build_all(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds
   const int counters = HBCSF_MAX_ORDER * kCounters;
   hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(256), 0, st, (uint32_t*)w.cnt, (size_t)counters * 2, (uint32_t*)w.bad,
                      (size_t)2, (uint32_t*)nullptr, (size_t)0);
+  ModeBuild mbs[HBCSF_MAX_ORDER];
+  // a mode's order: by root, then (blocked modes) by block, the top bits of the level-1 index
+  for (int mode = 0; mode < nModes; ++mode) {
+    Spec& sp = mbs[mode].sp;
+    int lv[HBCSF_MAX_ORDER];
+    level_order(N, dims, mode, opts.mode_order_policy, lv);
+    sp.blockBits = mid_block_bits(N, dims, opts, mode);
+    sp.blockDrop = sp.blockBits ? bits_for(dims[lv[1]]) - sp.blockBits : 0;
+    mbs[mode].rootBits = bits_for(dims[mode]);
+  }
+  if (w.ownSort) {
+    SortPasses& ps = w.sort.passes;
+    bool room = ps.add(0, totalBits);
+    for (int mode = 0; mode < nModes; ++mode) {
+      ModeBuild& mb = mbs[mode];
+      mb.sortFrom = ps.n;
+      if (mode == order[0] && mb.sp.blockBits == 0) continue;
+      int lv[HBCSF_MAX_ORDER];
+      level_order(N, dims, mode, opts.mode_order_policy, lv);
+      room = room && ps.add(bk.shift[mode], mb.rootBits);
+      if (mb.sp.blockBits) room = room && ps.add(bk.shift[lv[1]] + mb.sp.blockDrop, mb.sp.blockBits);
+      mb.sortMany = ps.n - mb.sortFrom;
+    }
+    if (!room) return fail(HBCSF_ERANGE, "too many radix passes");
+  }
   Sorted<Key> base;
   if (M > 0) {
     const int rs = sort_base<Key>(N, M, inds, vals, bk, totalBits, w, &base, st);
     if (rs != HBCSF_OK) return rs;
   }
-  ModeBuild mbs[HBCSF_MAX_ORDER];
   bool othersCounted = nModes == N;   // every mode's slices are its distinct indices (with blocking they are pieces)
   for (int m = 0; m < N; ++m) othersCounted = othersCounted && mid_block_bits(N, dims, opts, m) == 0;
   for (int mode = 0; mode < nModes; ++mode) {
@@ -1510,14 +1540,12 @@ int build_all(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds
     sp.NF = N - 2;
     sp.L = opts.fiber_threshold;
     const uint32_t gmask = opts.group_mask == 0 ? 3u : (opts.group_mask & 3u);
-    sp.blockBits = mid_block_bits(N, dims, opts, mode);
     sp.cooOn = (gmask & 1u) && sp.blockBits == 0 ? 1u : 0u;   // with blocking no piece owns its row
     sp.cslOn = (gmask & 2u) ? 1u : 0u;
     sp.cooRowFlags = opts.coo_row_flags == 1 ? 1u : 0u;
     sp.perFiber = per_fiber(opts) ? 1u : 0u;
     int lv[HBCSF_MAX_ORDER];
     level_order(N, dims, mode, opts.mode_order_policy, lv);
-    sp.blockDrop = sp.blockBits ? bits_for(dims[lv[1]]) - sp.blockBits : 0;
     u128 upTo = 0;
     for (int l = 0; l < N; ++l) {
       sp.shift[l] = bk.shift[lv[l]];
@@ -1527,7 +1555,6 @@ int build_all(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds
       if (dims[lv[l]] <= kByteRows) sp.byteLevels |= 1u << l;
     }
     if (sp.blockBits) sp.upTo[0] |= ((u128)((1ull << sp.blockBits) - 1)) << (bk.shift[lv[1]] + sp.blockDrop);
-    mb.rootBits = bits_for(dims[mode]);
     mb.cnt = w.cnt + (size_t)mode * kCounters;
     out->order = N;
     out->mode = mode;
