@@ -11,11 +11,12 @@
 // under that level's mask (a pass that rewrote the keys as (root, ..., leaf) first took 0.23 ms of 50 M nonzeros).
 // Keys of 64 bits are sorted by hbcsf_sort.h, wider ones and tensors of 2^30 nonzeros and more by rocPRIM.
 //
-// Numbering.  No array is kept per nonzero.  A wavefront takes 1024 sorted nonzeros, 64 at a time; "a slice / a fiber
-// begins here" are ballots, so what it needs to number them is the count before its tile (one scan over the tiles).
+// Numbering.  No array is kept per nonzero but a bit a level.  A wavefront takes 1024 sorted nonzeros, 64 at a time; "a slice /
+// a fiber begins here" are ballots, kept as bits for the kernels that need no more of the keys, so what it needs to number
+// them is the count before its tile (one scan over the tiles).
 // Slices get their group, their place in it and the fibers before them by a scan over slices; fbr-split adds a segment
 // start only where a run begins inside a fiber, which is looked up once per run (a search over the slices, a scan over
-// the runs), so a segment's number is the fibers before it plus the cuts before it.  The sorted keys are read three times
+// the runs), so a segment's number is the fibers before it plus the cuts before it.  The sorted keys are read twice
 // and each output is written once.
 //
 // The scans over tiles, slices and runs are rocPRIM device primitives; everything specific to the format
@@ -497,19 +498,12 @@ struct Numbers {
   uint32_t* fib[2];      // [S] as fib0, levels 2, 3
   uint32_t* csfOff;      // by CSF slice: its first place in the stream,
   uint32_t* csfStart;    //               its first sorted nonzero
-  Count4* cut;           // [runs + 1] cuts inside a fiber, per run, then before each
+  unsigned long long* begun;  // [levels][tiles][16] bit p: a slice (level 0) or a fiber of the level begins at nonzero p
+  uint8_t* inside;       // [runs + 1] bit l: the run begins inside a fiber of level l
+  Count4* cutBlock;      // [blocks of runs + 1] cuts inside a fiber per kCutBlock runs, then before them
+  Count4* cut;           // [runs + 1] cuts inside a fiber before each run
   uint32_t* count;       // {S}
 };
-
-// bit l: a slice (l = 0) or a fiber of level l begins at sorted nonzero p
-template <typename Key>
-__device__ __forceinline__ uint32_t begins(const Key* __restrict__ K, size_t p, const Spec& sp) {
-  if (p == 0) return 15u;
-  const Key x = K[p] ^ K[p - 1];
-  uint32_t b = 0;
-  for (int l = 0; l <= sp.NF; ++l) b |= ((x & (Key)sp.upTo[l]) != 0 ? 1u : 0u) << l;
-  return b;
-}
 
 // x of the lane before; lane 0: `first`
 template <typename Key>
@@ -532,7 +526,6 @@ __device__ __forceinline__ Key last_lane(Key x) {
   return x;
 }
 
-// (The two kernels below, 50 M nonzeros: 106 -> 92 and 107 -> 88 us, 4.4 TB/s, with one load a nonzero and four in flight.)
 // Keys and begins of the kFill chunks of 64 sorted nonzeros from p0 on (a whole wavefront), zeros past M.  last: the key
 // before p0, then the last one here.
 constexpr int kFill = 4;
@@ -556,14 +549,15 @@ __device__ __forceinline__ void load_chunks(const Key* __restrict__ K, size_t p0
   }
 }
 
+// (50 M nonzeros: 106 -> 92 us, 4.4 TB/s, with one load a nonzero and four in flight.)
 template <typename Key>
-__global__ __launch_bounds__(256) void count_tiles_kernel(const Key* __restrict__ K, size_t M, Spec sp, uint32_t tiles,
-                                                          Count4* __restrict__ tile) {
+__global__ __launch_bounds__(256) void count_tiles_kernel(const Key* __restrict__ K, size_t M, Spec sp, uint32_t tiles, Numbers n) {
   const int lane = threadIdx.x & 63;
   const uint32_t t = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t > tiles) return;
   Count4 c{{0, 0, 0, 0}};
   if (t < tiles) {
+    unsigned long long mine[4] = {0, 0, 0, 0};  // lane k: the bits of the tile's chunk k
     const size_t p0 = (size_t)t * kTile;
     Key last = p0 ? K[p0 - 1] : Key(0);
     for (uint32_t j = 0; j < kTile; j += 64 * kFill) {
@@ -574,55 +568,53 @@ __global__ __launch_bounds__(256) void count_tiles_kernel(const Key* __restrict_
       for (int q = 0; q < kFill; ++q)
 #pragma unroll
         for (int l = 0; l < 4; ++l)
-          if (l <= sp.NF) c.v[l] += (uint32_t)__popcll(__ballot((b[q] >> l) & 1u));
+          if (l <= sp.NF) {
+            const unsigned long long w = __ballot((b[q] >> l) & 1u);
+            c.v[l] += (uint32_t)__popcll(w);
+            if (lane == (int)(j / 64) + q) mine[l] = w;
+          }
     }
+    for (int l = 0; l < 4; ++l)
+      if (l <= sp.NF && lane < (int)(kTile / 64)) n.begun[((size_t)l * tiles + t) * (kTile / 64) + lane] = mine[l];
   }
-  if (lane == 0) tile[t] = c;
+  if (lane == 0) n.tile[t] = c;
 }
 
-template <typename Key>
-__global__ __launch_bounds__(256) void slice_tables_kernel(const Key* __restrict__ K, size_t M, Spec sp, uint32_t tiles,
-                                                           Numbers n) {
+// From the bits alone: 50 M nonzeros 87 (from the keys) -> 37 us.
+__global__ __launch_bounds__(256) void slice_tables_kernel(size_t M, Spec sp, uint32_t tiles, Numbers n) {
+  constexpr int kChunks = kTile / 64;
   const int lane = threadIdx.x & 63;
   const uint32_t t = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= tiles) return;
   Count4 c = n.tile[t];
   const unsigned long long below = (1ull << lane) - 1ull;
-  const size_t p0 = (size_t)t * kTile;
-  Key last = p0 ? K[p0 - 1] : Key(0);
-  for (uint32_t j = 0; j < kTile; j += 64 * kFill) {
-    Key key[kFill];
-    uint32_t begun[kFill];
-    load_chunks(K, p0 + j, M, sp, lane, last, key, begun);
+  unsigned long long mine[4] = {0, 0, 0, 0};
 #pragma unroll
-    for (int q = 0; q < kFill; ++q) {
-      const size_t p = p0 + j + q * 64 + lane;
-      const uint32_t b = begun[q];
-      uint32_t before[4];
+  for (int l = 0; l < 4; ++l)
+    if (l <= sp.NF && lane < kChunks) mine[l] = n.begun[((size_t)l * tiles + t) * kChunks + lane];
+  for (int k = 0; k < kChunks; ++k) {
+    unsigned long long w[4];
 #pragma unroll
-      for (int l = 0; l < 4; ++l) {
-        before[l] = 0;
-        if (l <= sp.NF) {
-          const unsigned long long w = __ballot((b >> l) & 1u);
-          before[l] = c.v[l] + (uint32_t)__popcll(w & below);
-          c.v[l] += (uint32_t)__popcll(w);
-        }
-      }
-      if (b & 1u) {
-        n.sStart[before[0]] = (uint32_t)p;
+    for (int l = 0; l < 4; ++l)
+      w[l] = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((uint32_t)mine[l], k) |
+             (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(mine[l] >> 32), k) << 32;
+    if ((w[0] >> lane) & 1ull) {
+      const uint32_t s = c.v[0] + (uint32_t)__popcll(w[0] & below);
+      n.sStart[s] = t * kTile + k * 64 + lane;
 #pragma unroll
-        for (int l = 1; l < 4; ++l)
-          if (l <= sp.NF) n.fStart[l - 1][before[0]] = before[l];
-      }
-      if (p == M - 1) {  // one past the last slice
-        const uint32_t S = before[0] + (b & 1u);
-        n.sStart[S] = (uint32_t)M;
-#pragma unroll
-        for (int l = 1; l < 4; ++l)
-          if (l <= sp.NF) n.fStart[l - 1][S] = before[l] + ((b >> l) & 1u);
-        n.count[0] = S;
-      }
+      for (int l = 1; l < 4; ++l)
+        if (l <= sp.NF) n.fStart[l - 1][s] = c.v[l] + (uint32_t)__popcll(w[l] & below);
     }
+#pragma unroll
+    for (int l = 0; l < 4; ++l) c.v[l] += (uint32_t)__popcll(w[l]);
+  }
+  if (t == tiles - 1 && lane == 0) {  // one past the last slice
+    const uint32_t S = c.v[0];
+    n.sStart[S] = (uint32_t)M;
+#pragma unroll
+    for (int l = 1; l < 4; ++l)
+      if (l <= sp.NF) n.fStart[l - 1][S] = c.v[l];
+    n.count[0] = S;
   }
 }
 
@@ -715,39 +707,138 @@ __global__ __launch_bounds__(256) void number_slices_kernel(Numbers n, Spec sp) 
   }
 }
 
-// Per run of the CSF stream and level: does it begin inside a fiber?
-template <typename Key>
-__global__ __launch_bounds__(256) void find_cuts_kernel(const Key* __restrict__ K, Spec sp, Numbers n, uint32_t blocks,
-                                                        uint32_t maxRuns) {
-  const uint32_t r = blockIdx.x * 256 + threadIdx.x;
-  if (r > maxRuns) return;
-  const GroupCounts& all = n.block[blocks];
-  const uint64_t at = (uint64_t)r * sp.L;
-  Count4 c{{0, 0, 0, 0}};
-  if (at < all.m[kCsf]) {
-    uint32_t lo = 0, hi = all.s[kCsf];  // the last slice that begins at or before `at`
+// Per run of the CSF stream and level: does it begin inside a fiber?  A block of runs lies between two slices, which two of its
+// wavefronts look for with 64 places at a time; a run's own slice is searched between those.  The bits are an eighth of a
+// byte per nonzero, where the two keys they came from are a line of memory per run.  With the two kernels below 50 M nonzeros
+// 110 to 145 (a search over all slices, a library scan of 16 bytes a run) -> 30 to 34 us.
+constexpr uint32_t kCutBlock = 1024;
+__global__ __launch_bounds__(256) void find_cuts_kernel(Spec sp, Numbers n, uint32_t tiles, uint32_t blocks, uint32_t maxRuns) {
+  __shared__ uint32_t range[2], sum[4][4];
+  const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6, r0 = blockIdx.x * kCutBlock;
+  const uint64_t end = n.block[blocks].m[kCsf];
+  const uint32_t slices = n.block[blocks].s[kCsf];
+  if (w < 2 && (uint64_t)r0 * sp.L < end) {
+    const uint64_t far = ((uint64_t)r0 + kCutBlock - 1) * sp.L;
+    const uint64_t at = w == 0 ? (uint64_t)r0 * sp.L : far < end ? far : end - 1;
+    uint32_t lo = 0, hi = slices;  // the last slice that begins at or before `at`
     while (hi - lo > 1) {
-      const uint32_t mid = lo + (hi - lo) / 2;
-      if (n.csfOff[mid] <= at) lo = mid;
-      else hi = mid;
+      const uint64_t span = hi - lo;
+      const uint32_t upTo = (uint32_t)__popcll(__ballot(n.csfOff[lo + (uint32_t)(span * (lane + 1) / 65)] <= at));
+      const uint32_t from = lo;
+      lo = from + (uint32_t)(span * upTo / 65);
+      if (upTo < 64) hi = from + (uint32_t)(span * (upTo + 1) / 65);
     }
-    const uint32_t b = begins(K, (size_t)n.csfStart[lo] + (size_t)(at - n.csfOff[lo]), sp);
-    for (int l = 1; l <= sp.NF; ++l) c.v[l] = (b >> l) & 1u ? 0u : 1u;
+    if (lane == 0) range[w] = lo;
   }
-  n.cut[r] = c;
+  __syncthreads();
+  uint32_t c[4] = {0, 0, 0, 0};
+  for (uint32_t j = 0; j < kCutBlock; j += 256) {
+    const uint32_t r = r0 + j + threadIdx.x;
+    const uint64_t at = (uint64_t)r * sp.L;
+    uint32_t in = 0;
+    if (r <= maxRuns && at < end) {
+      uint32_t lo = range[0], hi = range[1] + 1;
+      while (hi - lo > 1) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        if (n.csfOff[mid] <= at) lo = mid;
+        else hi = mid;
+      }
+      const uint32_t p = n.csfStart[lo] + (uint32_t)(at - n.csfOff[lo]);
+      for (int l = 1; l <= sp.NF; ++l)
+        in |= (uint32_t)(~n.begun[(size_t)l * tiles * (kTile / 64) + p / 64] >> (p % 64) & 1ull) << l;
+    }
+    if (r <= maxRuns) n.inside[r] = (uint8_t)in;
+#pragma unroll
+    for (int l = 1; l < 4; ++l) c[l] += (uint32_t)__popcll(__ballot((in >> l) & 1u));
+  }
+  if (lane == 0)
+    for (int l = 1; l < 4; ++l) sum[w][l] = c[l];
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    Count4 all{{0, 0, 0, 0}};
+    for (int k = 0; k < 4; ++k)
+      for (int l = 1; l < 4; ++l) all.v[l] += sum[k][l];
+    n.cutBlock[blockIdx.x] = all;
+  }
 }
 
-__global__ void totals_kernel(Numbers n, Spec sp, uint32_t tiles, uint32_t blocks, uint32_t maxRuns,
-                              const unsigned long long* bad, Totals* out) {
+// Cuts before each block of runs, and what the host waits for.  One block.
+__global__ __launch_bounds__(1024) void totals_kernel(Numbers n, Spec sp, uint32_t tiles, uint32_t blocks, uint32_t cutBlocks,
+                                                      const unsigned long long* bad, Totals* out) {
+  __shared__ uint32_t wave[16][4];
+  const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t before[4] = {0, 0, 0, 0};
+  for (uint32_t b0 = 0; b0 < cutBlocks; b0 += 1024) {
+    const uint32_t b = b0 + threadIdx.x;
+    Count4 own{{0, 0, 0, 0}};
+    if (b < cutBlocks) own = n.cutBlock[b];
+    uint32_t upTo[4];
+    for (int l = 1; l < 4; ++l) {
+      upTo[l] = own.v[l];
+      for (uint32_t o = 1; o < 64; o <<= 1) {
+        const uint32_t up = __shfl_up(upTo[l], o);
+        if (lane >= o) upTo[l] += up;
+      }
+      if (lane == 63) wave[w][l] = upTo[l];
+    }
+    __syncthreads();
+    for (int l = 1; l < 4; ++l) {
+      uint32_t all = 0;
+      for (uint32_t k = 0; k < 16; ++k) {
+        if (k == w) upTo[l] += all;
+        all += wave[k][l];
+      }
+      own.v[l] = before[l] + upTo[l] - own.v[l];
+      before[l] += all;
+    }
+    if (b < cutBlocks) n.cutBlock[b] = own;
+    __syncthreads();
+  }
+  if (threadIdx.x != 0) return;
   Totals t{};
   t.bad = (uint32_t)*bad;
   t.S = n.count[0];
   for (int l = 0; l < sp.NF; ++l) {
     t.fibNat[l] = n.tile[tiles].v[1 + l];
-    t.extra[l] = n.cut[maxRuns].v[1 + l];
+    t.extra[l] = before[1 + l];
   }
   t.g = n.block[blocks];
   *out = t;
+}
+
+__global__ __launch_bounds__(256) void number_cuts_kernel(Numbers n, uint32_t maxRuns) {
+  constexpr int kEach = kCutBlock / 256;
+  __shared__ uint32_t count[kEach][4][4];
+  const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  const Count4 first = n.cutBlock[blockIdx.x];
+  uint32_t pre[kEach][4];
+#pragma unroll
+  for (int j = 0; j < kEach; ++j) {
+    const uint32_t r = blockIdx.x * kCutBlock + j * 256 + threadIdx.x;
+    const uint32_t in = r <= maxRuns ? n.inside[r] : 0u;
+#pragma unroll
+    for (int l = 1; l < 4; ++l) {
+      const unsigned long long set = __ballot((in >> l) & 1u);
+      pre[j][l] = (uint32_t)__popcll(set & below);
+      if (lane == 0) count[j][w][l] = (uint32_t)__popcll(set);
+    }
+  }
+  __syncthreads();
+  uint32_t before[4] = {0, first.v[1], first.v[2], first.v[3]};
+#pragma unroll
+  for (int j = 0; j < kEach; ++j) {
+    const uint32_t r = blockIdx.x * kCutBlock + j * 256 + threadIdx.x;
+    Count4 c{{0, 0, 0, 0}};
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k)
+#pragma unroll
+      for (int l = 1; l < 4; ++l) {
+        if (k == w) c.v[l] = before[l] + pre[j][l];
+        before[l] += count[j][k][l];
+      }
+    if (r <= maxRuns) n.cut[r] = c;
+  }
 }
 
 // Every nonzero writes itself into its group's stream; segment starts write the fiber-level entries.  A wavefront takes
@@ -975,7 +1066,7 @@ uint64_t slice_bound(size_t M, uint64_t maxDim, bool blocked) { return blocked |
 // that the arrays are not copied any more.)
 bool own_sort(size_t M, int maxBits) { return maxBits <= 64 && M > 0 && M < (size_t)kSortCounts; }
 
-hipError_t temp_bytes(size_t M, size_t maxWords, uint64_t slices, uint32_t L, int totalBits, size_t* out) {
+hipError_t temp_bytes(size_t M, size_t maxWords, uint64_t slices, int totalBits, size_t* out) {
   const bool wide = totalBits > 64;
   // the largest scratch any rocPRIM call below asks for
   size_t need = 0, b = 0;
@@ -995,8 +1086,8 @@ hipError_t temp_bytes(size_t M, size_t maxWords, uint64_t slices, uint32_t L, in
   }
   if (e != hipSuccess) return e;
   need = b > need ? b : need;
-  const size_t runs = M / L + 2, tiles = M / kTile + 2;
-  e = rocprim::exclusive_scan(nullptr, b, (Count4*)nullptr, (Count4*)nullptr, Count4{}, runs > tiles ? runs : tiles, Count4Plus());
+  const size_t tiles = M / kTile + 2;
+  e = rocprim::exclusive_scan(nullptr, b, (Count4*)nullptr, (Count4*)nullptr, Count4{}, tiles, Count4Plus());
   if (e != hipSuccess) return e;
   need = b > need ? b : need;
   e = rocprim::exclusive_scan(nullptr, b, (GroupCounts*)nullptr, (GroupCounts*)nullptr, GroupCounts{},
@@ -1056,6 +1147,7 @@ void carve(Workspace& w, uint8_t* base, int order, size_t M, uint64_t mapBytes, 
   w.n.csfOff = perFiber ? nullptr : (uint32_t*)take((tables + 1) * 4);
   w.n.csfStart = perFiber ? nullptr : (uint32_t*)take((tables + 1) * 4);
   w.n.cut = (Count4*)take((M / L + 2) * sizeof(Count4));
+  w.n.cutBlock = (Count4*)take((M / L / kCutBlock + 2) * sizeof(Count4));
   w.n.count = (uint32_t*)take(4);
   w.seg2 = perFiber && order >= 5 ? (uint32_t*)take((M + 2) * 4) : nullptr;
   w.sgScan = perFiber ? (uint32_t*)take((M + 2) * 4) : nullptr;
@@ -1072,6 +1164,10 @@ void carve(Workspace& w, uint8_t* base, int order, size_t M, uint64_t mapBytes, 
   w.normSq = (double*)take(8);
   w.seen = (uint8_t*)take(3 * mapBytes);
   if (w.ownSort) sort_scratch(M, take(sort_scratch(M, nullptr, &w.sort.s)), &w.sort.s);
+  // between the sorts of two modes the third buffer pair of hbcsf_sort.h is free (at least 32 KB and 12 bytes a nonzero)
+  const uint64_t begunBytes = (uint64_t)(order - 1) * ((M + kTile - 1) / kTile) * (kTile / 8);
+  w.n.begun = perFiber ? nullptr : w.ownSort ? (unsigned long long*)w.sort.s.K : (unsigned long long*)take(begunBytes);
+  w.n.inside = perFiber ? nullptr : w.ownSort ? (uint8_t*)w.sort.s.K + up256(begunBytes) : take(M / L + 2);
   w.temp = take(tempBytes);
   w.tempBytes = tempBytes;
   w.total = off;
@@ -1262,22 +1358,22 @@ int number_mode(size_t M, uint64_t slices, const Sorted<Key>& so, ModeBuild& mb,
   const uint32_t maxRuns = (uint32_t)((M + sp.L - 1) / sp.L);
   const dim3 tileGrid(tiles / 4 + 1);
   size_t tb = w.tempBytes;
-  hipLaunchKernelGGL(count_tiles_kernel<Key>, tileGrid, dim3(256), 0, st, so.K, M, sp, tiles, w.n.tile);
+  const uint32_t cutBlocks = maxRuns / kCutBlock + 1;
+  hipLaunchKernelGGL(count_tiles_kernel<Key>, tileGrid, dim3(256), 0, st, so.K, M, sp, tiles, w.n);
   HIP_TRY(rocprim::exclusive_scan(w.temp, tb, w.n.tile, w.n.tile, Count4{}, (size_t)tiles + 1, Count4Plus(), st), "scan");
-  hipLaunchKernelGGL(slice_tables_kernel<Key>, tileGrid, dim3(256), 0, st, so.K, M, sp, tiles, w.n);
+  hipLaunchKernelGGL(slice_tables_kernel, tileGrid, dim3(256), 0, st, M, sp, tiles, w.n);
   hipLaunchKernelGGL(count_slices_kernel, dim3(blocks + 1), dim3(256), 0, st, w.n, sp, blocks);
   tb = w.tempBytes;
   HIP_TRY(rocprim::exclusive_scan(w.temp, tb, w.n.block, w.n.block, GroupCounts{}, (size_t)blocks + 1, GroupCountsPlus(), st),
           "scan");
   hipLaunchKernelGGL(number_slices_kernel, dim3(blocks), dim3(256), 0, st, w.n, sp);
-  hipLaunchKernelGGL(find_cuts_kernel<Key>, dim3(maxRuns / 256 + 1), dim3(256), 0, st, so.K, sp, w.n, blocks, maxRuns);
-  tb = w.tempBytes;
-  HIP_TRY(rocprim::exclusive_scan(w.temp, tb, w.n.cut, w.n.cut, Count4{}, (size_t)maxRuns + 1, Count4Plus(), st), "scan");
-  hipLaunchKernelGGL(totals_kernel, dim3(1), dim3(1), 0, st, w.n, sp, tiles, blocks, maxRuns, w.bad, w.totals);
+  hipLaunchKernelGGL(find_cuts_kernel, dim3(cutBlocks), dim3(256), 0, st, sp, w.n, tiles, blocks, maxRuns);
+  hipLaunchKernelGGL(totals_kernel, dim3(1), dim3(1024), 0, st, w.n, sp, tiles, blocks, cutBlocks, w.bad, w.totals);
   Totals t{};
   HIP_TRY(hipMemcpyAsync(&t, w.totals, sizeof(Totals), hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
   HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
   if (t.bad) return fail(HBCSF_ERANGE, "an index is not below its dimension");
+  hipLaunchKernelGGL(number_cuts_kernel, dim3(cutBlocks), dim3(256), 0, st, w.n, maxRuns);  // (beside the caller's allocation)
   mb.S = t.S;
   for (int g = 0; g < 3; ++g) {
     mb.gS[g] = t.g.s[g];
@@ -1611,7 +1707,7 @@ int build_device(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* 
   for (int m = 0; m < order; ++m) maxDim = dims[m] > maxDim ? dims[m] : maxDim;
   size_t tbytes = 0;
   const uint64_t slices = slice_bound((size_t)nnz, maxDim, o.mid_blocking > 1);
-  HIP_TRY(temp_bytes((size_t)nnz, (size_t)((maxDim + 31) / 32), slices, o.fiber_threshold, maxBits, &tbytes),
+  HIP_TRY(temp_bytes((size_t)nnz, (size_t)((maxDim + 31) / 32), slices, maxBits, &tbytes),
           "rocPRIM scratch query");
   Workspace w{};
   carve(w, (uint8_t*)workspace, order, (size_t)nnz, row_maps_bytes(order, dims), slices, o.fiber_threshold, tbytes, maxBits > 64,
@@ -1675,7 +1771,7 @@ int hbcsf_device_build_bytes(int order, const uint64_t* dims, uint64_t nnz, cons
   for (int m = 0; m < order; ++m) maxDim = dims[m] > maxDim ? dims[m] : maxDim;
   size_t tbytes = 0;
   const uint64_t slices = slice_bound((size_t)nnz, maxDim, o.mid_blocking > 1);
-  HIP_TRY(temp_bytes((size_t)nnz, (size_t)((maxDim + 31) / 32), slices, o.fiber_threshold, maxBits, &tbytes),
+  HIP_TRY(temp_bytes((size_t)nnz, (size_t)((maxDim + 31) / 32), slices, maxBits, &tbytes),
           "rocPRIM scratch query");
   Workspace w{};
   carve(w, nullptr, order, (size_t)nnz, row_maps_bytes(order, dims), slices, o.fiber_threshold, tbytes, maxBits > 64, per_fiber(o),
