@@ -1033,7 +1033,7 @@ struct Workspace {
   uint8_t* grp;          // per-fiber choice only
   C6* c6;                // per-fiber choice only
   unsigned long long* bad;  // an index is not below its dimension
-  unsigned long long* cnt;  // kCounters per mode
+  unsigned long long* cnt;  // kCounters per mode; behind them normSq
   Totals* totals;
   double* normSq;
   uint8_t* seen;         // row maps of the 3 groups and the levels below the root (statistics)
@@ -1159,9 +1159,9 @@ void carve(Workspace& w, uint8_t* base, int order, size_t M, uint64_t mapBytes, 
   w.grp = perFiber ? (uint8_t*)take(M + 1) : nullptr;
   w.c6 = perFiber ? (C6*)take((M + 2) * sizeof(C6)) : nullptr;
   w.bad = (unsigned long long*)take(8);
-  w.cnt = (unsigned long long*)take(HBCSF_MAX_ORDER * kCounters * 8);
+  w.cnt = (unsigned long long*)take((HBCSF_MAX_ORDER * kCounters + 1) * 8);
+  w.normSq = (double*)(w.cnt + HBCSF_MAX_ORDER * kCounters);
   w.totals = (Totals*)take(sizeof(Totals));
-  w.normSq = (double*)take(8);
   w.seen = (uint8_t*)take(3 * mapBytes);
   if (w.ownSort) sort_scratch(M, take(sort_scratch(M, nullptr, &w.sort.s)), &w.sort.s);
   // between the sorts of two modes the third buffer pair of hbcsf_sort.h is free (at least 32 KB and 12 bytes a nonzero)
@@ -1593,7 +1593,7 @@ int build_all(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds
     bk.dims[m] = dims[m];
     at += b;
   }
-  const int counters = HBCSF_MAX_ORDER * kCounters;
+  const int counters = HBCSF_MAX_ORDER * kCounters + 1;
   hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(256), 0, st, (uint32_t*)w.cnt, (size_t)counters * 2, (uint32_t*)w.bad,
                      (size_t)2, (uint32_t*)nullptr, (size_t)0);
   ModeBuild mbs[HBCSF_MAX_ORDER];
@@ -1623,6 +1623,10 @@ int build_all(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds
   }
   Sorted<Key> base;
   if (M > 0) {
+    size_t tb = w.tempBytes;
+    auto cit = rocprim::counting_iterator<size_t>(0);
+    HIP_TRY(rocprim::reduce(w.temp, tb, rocprim::make_transform_iterator(cit, SquareIn{vals}), w.normSq, 0.0, M,
+                            rocprim::plus<double>(), st), "reduce");
     const int rs = sort_base<Key>(N, M, inds, vals, bk, totalBits, w, &base, st);
     if (rs != HBCSF_OK) return rs;
   }
@@ -1668,9 +1672,18 @@ int build_all(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds
                                           othersCounted, st);
     if (rb != HBCSF_OK) return rb;
   }
-  unsigned long long host[HBCSF_MAX_ORDER * kCounters];
+  // the last wait: for the counters, the sum of squares and the words of state
+  size_arena(t);
+  if (t->arenaBytes > t->formatBytes) {
+    uint8_t* states = nullptr;
+    const int rp = place(t->arenaBytes - t->formatBytes, &states);
+    if (rp != HBCSF_OK) return rp;
+    HIP_TRY(place_states(t, states, st), "launch of the zero-fill kernel");
+  }
+  unsigned long long host[HBCSF_MAX_ORDER * kCounters + 1];
   HIP_TRY(hipMemcpyAsync(host, w.cnt, sizeof(host), hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
   HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
+  std::memcpy(&t->normSq, host + HBCSF_MAX_ORDER * kCounters, sizeof(double));
   const double seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_begin).count();
   for (int mode = 0; mode < nModes; ++mode) {
     const ModeBuild& mb = mbs[mode];
@@ -1734,23 +1747,6 @@ int build_device(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* 
   const int rb = maxBits > 64 ? build_all<u128>(order, dims, (size_t)nnz, inds, vals, o, totalBits, w, place, t.get(), st)
                               : build_all<uint64_t>(order, dims, (size_t)nnz, inds, vals, o, totalBits, w, place, t.get(), st);
   if (rb != HBCSF_OK) return rb;
-  size_arena(t.get());
-  if (t->arenaBytes > t->formatBytes) {
-    uint8_t* states = nullptr;
-    const int rp = place(t->arenaBytes - t->formatBytes, &states);
-    if (rp != HBCSF_OK) return rp;
-    HIP_TRY(place_states(t.get(), states, st), "launch of the zero-fill kernel");
-  }
-  double sq = 0.0;
-  if (nnz > 0) {
-    size_t tb_ = w.tempBytes;
-    auto cit = rocprim::counting_iterator<size_t>(0);
-    HIP_TRY(rocprim::reduce(w.temp, tb_, rocprim::make_transform_iterator(cit, SquareIn{vals}), w.normSq, 0.0,
-                            (size_t)nnz, rocprim::plus<double>(), st), "reduce");
-    HIP_TRY(hipMemcpyAsync(&sq, w.normSq, 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-    HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
-  }
-  t->normSq = sq;
   t->uploaded = true;
   *out = t.release();
   return HBCSF_OK;
