@@ -493,191 +493,13 @@ void launch_scale_columns(float* a, uint64_t rows, int rank, const float* s, int
 // norms of the last update.  These kernels are one workgroup each (the work is R^3 at most 2 M multiply-adds in a serial
 // chain of R steps); what they replace is a copy to the host, a wait, and a copy back for every mode update.
 // ---------------------------------------------------------------------------------------------------
-constexpr int pinv_threads(int R) { return R == 32 ? 256 : small_threads(R); }       // the eigenvalue form uses them all
 constexpr int entry_threads(int R) { return R * R < 1024 ? R * R : 1024; }           // for kernels that walk R x R entries
-
-// Pseudo-inverse of the symmetric matrix V by cyclic Jacobi rotations, n / 2 disjoint pairs at a time (round-robin
-// pairing): only when V is not safely positive definite.  Eigenvalues below 1e-15 of the largest magnitude count as zero
-// (the cut-off numpy.linalg.pinv applies to singular values).
-// A round is a chain of its angles, the rotations and two barriers, some hundred rounds a matrix, so the matrix stays in
-// LDS: a 2 x 2 block of row pair k and column pair l takes both its rotations from one thread, which loads all its blocks
-// before it stores any.  So do the eigenvectors up to rank 64; at 128, where both do not fit, a wavefront keeps to its own
-// rows of them in `qGlobal` ([R][R] scratch).  At rank 32 four wavefronts work on it, which wait while one sweeps: 1.6 ->
-// 0.7 us a round.  One matrix with half the components equal takes 52 / 147 / 820 / 6200 us at ranks 16 / 32 / 64 / 128
-// (150 / 1170 / 6000 / 52700 with both matrices in global memory; the host routine 23 / 180 / 1640 / 22600 and two copies).
-// Two diagonal entries that would both count as zero are rotated only once the entry between them is no smaller than the
-// others: rounding noise would turn them by any angle and stir what the sweep has just cleared back into their columns
-// (half the components equal, rank 32: 7 sweeps instead of 12 to 17).
-template <int R>
-struct JacobiLds {
-  static constexpr bool kVectors = R <= 64;
-  double a[R * R];
-  double q[kVectors ? R * R : 1];
-  double c[R / 2], s[R / 2], inv[R];
-  double sums[3][pinv_threads(R) / 64];
-  int2 pair[R / 2];
-};
-
-template <int R>
-__device__ void jacobi_pinv(const SmallState& st, int n, JacobiLds<R>& lds, double* __restrict__ qGlobal, double* __restrict__ out) {
-  constexpr int T = pinv_threads(R), H = R / 2, S = T / H;   // S row pairs of a, or rows of q, at a time
-  constexpr bool kVectors = JacobiLds<R>::kVectors;
-  // blocks of a and rows of q a thread takes, and rows of q it holds at a time (with all eight at rank 128 it would spill)
-  constexpr int KA = (H + S - 1) / S, KQ = (R + S - 1) / S, KB = kVectors ? KQ : 4;
-  const int tid = threadIdx.x;
-  const int l = tid % H, first = tid / H;
-  double* a = lds.a;
-  double* q = kVectors ? lds.q : qGlobal;
-  for (int e = tid; e < R * R; e += T) {
-    a[e] = v_entry<R>(st, n, e / R, e % R);
-    q[e] = e / R == e % R ? 1.0 : 0.0;
-  }
-  __syncthreads();
-  for (int sweep = 0; sweep < 60; ++sweep) {
-    double off = 0.0, diagonal = 0.0, most = 0.0;
-    for (int e = tid; e < R * R; e += T) {
-      const double x = a[e] * a[e];
-      if (e / R == e % R) {
-        diagonal += x;
-        most = fmax(most, fabs(a[e]));
-      } else {
-        off += x;
-      }
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-      off += __shfl_xor(off, o);
-      diagonal += __shfl_xor(diagonal, o);
-      most = fmax(most, __shfl_xor(most, o));
-    }
-    if ((tid & 63) == 0) {
-      lds.sums[0][tid >> 6] = off;
-      lds.sums[1][tid >> 6] = diagonal;
-      lds.sums[2][tid >> 6] = most;
-    }
-    __syncthreads();
-    off = diagonal = most = 0.0;
-    for (int w = 0; w < T / 64; ++w) {
-      off += lds.sums[0][w];
-      diagonal += lds.sums[1][w];
-      most = fmax(most, lds.sums[2][w]);
-    }
-    if (off <= 1e-30 * diagonal || off == 0.0) break;   // the same for every thread
-    const double small = 1e-15 * most, least = off / (R * R);
-    for (int round = 0; round < R - 1; ++round) {
-      // pair k of this round: players 0 (fixed) and 1 .. R-1 (rotating)
-      auto player = [&](int slot) {
-        const int x = slot - 1 + round;
-        return slot == 0 ? 0 : 1 + (x >= R - 1 ? x - (R - 1) : x);
-      };
-      if (tid < H) {
-        const int x = player(tid), y = player(R - 1 - tid);
-        const int p = x < y ? x : y, r = x < y ? y : x;
-        const double app = a[p * R + p], arr = a[r * R + r], apr = a[p * R + r];
-        // t = tan of the angle, the smaller root: tan(2 angle) = 2 apr / (arr - app)
-        const double d = arr - app, h = 2.0 * apr, dh = fma(d, d, h * h);
-        double c = 1.0, sn = 0.0;
-        const bool skip = fabs(app) <= small && fabs(arr) <= small && apr * apr < least;
-        if (apr != 0.0 && !skip && !(dh <= 1e-280)) {
-          const double t = (d >= 0 ? h : -h) * reciprocal(fabs(d) + dh * reciprocal_root(dh));
-          c = reciprocal_root(fma(t, t, 1.0));
-          sn = t * c;
-        }
-        lds.c[tid] = c;
-        lds.s[tid] = sn;
-        lds.pair[tid] = make_int2(p, r);
-      }
-      __syncthreads();
-      const int2 cols = lds.pair[l];
-      const double cl = lds.c[l], sl = lds.s[l];
-      double x[KA][4], y[KB][2];
-      auto load_vectors = [&](int from) {
-#pragma unroll
-        for (int m = 0; m < KB; ++m) {
-          const int row = first + (from + m) * S;
-          if (row < R) {
-            y[m][0] = q[row * R + cols.x];
-            y[m][1] = q[row * R + cols.y];
-          }
-        }
-      };
-      auto turn_vectors = [&](int from) {
-#pragma unroll
-        for (int m = 0; m < KB; ++m) {
-          const int row = first + (from + m) * S;
-          if (row < R) {
-            q[row * R + cols.x] = cl * y[m][0] - sl * y[m][1];
-            q[row * R + cols.y] = sl * y[m][0] + cl * y[m][1];
-          }
-        }
-      };
-#pragma unroll
-      for (int m = 0; m < KA; ++m) {
-        const int k = first + m * S;
-        if (k < H) {
-          const int2 rows = lds.pair[k];
-          x[m][0] = a[rows.x * R + cols.x];
-          x[m][1] = a[rows.x * R + cols.y];
-          x[m][2] = a[rows.y * R + cols.x];
-          x[m][3] = a[rows.y * R + cols.y];
-        }
-      }
-      if (kVectors) load_vectors(0);
-#pragma unroll
-      for (int m = 0; m < KA; ++m) {
-        const int k = first + m * S;
-        if (k < H) {
-          const int2 rows = lds.pair[k];
-          const double ck = lds.c[k], sk = lds.s[k];
-          const double p0 = cl * x[m][0] - sl * x[m][1], p1 = sl * x[m][0] + cl * x[m][1];
-          const double r0 = cl * x[m][2] - sl * x[m][3], r1 = sl * x[m][2] + cl * x[m][3];
-          a[rows.x * R + cols.x] = ck * p0 - sk * r0;
-          a[rows.y * R + cols.x] = sk * p0 + ck * r0;
-          a[rows.x * R + cols.y] = ck * p1 - sk * r1;
-          a[rows.y * R + cols.y] = sk * p1 + ck * r1;
-        }
-      }
-      if (kVectors) {
-        turn_vectors(0);
-      } else {
-        for (int from = 0; from < KQ; from += KB) {
-          load_vectors(from);
-          turn_vectors(from);
-        }
-      }
-      __syncthreads();
-    }
-  }
-  double wmax = 0.0;
-  for (int k = 0; k < R; ++k) wmax = fmax(wmax, fabs(a[k * R + k]));
-  for (int k = tid; k < R; k += T) {
-    const double w = a[k * R + k];
-    lds.inv[k] = fabs(w) <= 1e-15 * wmax ? 0.0 : 1.0 / w;   // (a NaN is not small)
-  }
-  __syncthreads();
-  if constexpr (!kVectors) {
-    for (int e = tid; e < R * R; e += T) a[e] = q[e];
-    __syncthreads();
-    q = a;
-  }
-  // the terms of entry (i, j) from number i + j on: neighbouring threads then read different LDS banks, and (j, i) adds
-  // the same terms in the same order
-  for (int e = tid; e < R * R; e += T) {
-    const int i = e / R, j = e % R;
-    double t = 0.0;
-    for (int m = 0; m < R; ++m) {
-      const int k = (i + j + m) & (R - 1);
-      if (lds.inv[k] != 0.0) t += q[i * R + k] * lds.inv[k] * q[j * R + k];
-    }
-    out[e] = t;
-  }
-  __syncthreads();
-}
 
 // vp = V^+ for the update of mode n, and p = diag(d) V^+ (the right-hand matrix of a put-off update; an ordinary update
 // overwrites it).  A pivot of the sweep that is not safely positive sends the whole workgroup to the eigenvalue form.
 // resetScale: after the product the stored factor is the unnormalised one, so its column scale becomes 1.
 // hosted: null, or the outcome of the sweep that ran beside the MTTKRP: where that was good, all is done, and where it was
-// not only the eigenvalue form is left.  stamp: when it begins and ends (nothing where all is done).
+// not only the eigenvalue form is left (ranks that guest_finishes() leaves to this).  stamp: when it begins and ends (nothing where all is done).
 template <int R>
 __global__ __launch_bounds__(pinv_threads(R)) void small_pinv_kernel(SmallState st, int n, double* __restrict__ vp,
                                                                       float* __restrict__ p, double* __restrict__ jq,
@@ -1143,7 +965,7 @@ int enqueue_iteration(hbcsf_als* a, float* const* factors, float* lambda, int fl
     const float* facs[HBCSF_MAX_ORDER];
     for (int m = 0; m < order; ++m) facs[m] = factors[m];
     // a put-off update's inverse goes with the MTTKRP where it takes guests
-    // (what is left of it then begins at stamp 1, and its end, at stamp 2, is overwritten by the product that follows)
+    // (the eigenvalue form then begins at stamp 1, and its end, at stamp 2, is overwritten by the product that follows)
     const bool hosted = a->hosted[n] = lazy && mttkrp_takes_guest(t, n, R);
     auto invert = [&] {
       with_rank(R, [&](auto r) {
@@ -1158,6 +980,7 @@ int enqueue_iteration(hbcsf_als* a, float* const* factors, float* lambda, int fl
       guest.small = a->small;
       guest.n = n;
       guest.p = a->p;
+      guest.vp = a->vp;
       guest.good = a->good;
       guest.stamp = a->report->stamp[n];
       rc = mttkrp_with_guest(t, n, R, facs, a->m, guest, st);
@@ -1166,7 +989,7 @@ int enqueue_iteration(hbcsf_als* a, float* const* factors, float* lambda, int fl
       rc = hbcsf_mttkrp(t, n, R, facs, a->m, st);
     }
     if (rc != HBCSF_OK) return rc;
-    if (hosted) invert();   // what is left of it
+    if (hosted && !guest_finishes(R)) invert();   // what is left of it
     if (lazy) {
       // A_n = M V^+ written unnormalised, with its Gram matrix
       nDots = launch_apply(a->m, t->dims[n], R, a->p, factors[n], a->gramScratch, a->gramSlots, a->small.gram[n],

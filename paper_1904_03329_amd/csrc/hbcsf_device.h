@@ -45,8 +45,9 @@ struct GuestArgs {
   SmallState small;
   int n;                     // the mode being updated
   float* p;                  // right-hand matrix of the product that follows
-  int* good;                 // receives 1 where the inverse succeeded, else 0
-  unsigned long long* stamp; // [2]: receives the time at which the MTTKRP's first kernel begins, and 0
+  double* vp;                // [rank][rank], where the eigenvalue form is put
+  int* good;                 // receives 1 where the sweep succeeded, else 0
+  unsigned long long* stamp; // [2]: receives the time at which the MTTKRP's first kernel begins, and 0 (or the eigenvalue form)
 };
 
 // Device pointers of one slice group of one mode, by tree level (0 = root .. order-1 = leaf).
