@@ -11,7 +11,7 @@
 // under that level's mask (a pass that rewrote the keys as (root, ..., leaf) first took 0.23 ms of 50 M nonzeros).
 // Keys of 64 bits are sorted by hbcsf_sort.h, wider ones and tensors of 2^30 nonzeros and more by rocPRIM.
 //
-// Numbering.  No array is kept per nonzero but a bit a level.  A wavefront takes 1024 sorted nonzeros, 64 at a time; "a slice /
+// Numbering.  No array is kept per nonzero but a bit a level.  A wavefront takes 1024 (or 256) sorted nonzeros, 64 at a time; "a slice /
 // a fiber begins here" are ballots, kept as bits for the kernels that need no more of the keys, so what it needs to number
 // them is the count before its tile (one scan over the tiles).
 // Slices get their group, their place in it and the fibers before them by a scan over slices; fbr-split adds a segment
@@ -450,7 +450,11 @@ __global__ void fill_slices_kernel(const Key* K, size_t S, Spec sp, Tables t, Ou
 }
 
 // ---- numbering without per-nonzero arrays ----
-constexpr uint32_t kTile = 1024;       // sorted nonzeros a wavefront numbers
+// Sorted nonzeros a wavefront numbers, 256 at a time.  Below 2 M there are fewer tiles of 1024 than the chip holds wavefronts,
+// and the four steps of a tile, each a chain of dependent loads, are the kernels' time (50 000 nonzeros of order 4, tiles of
+// 1024 -> 256: filling 27 -> 11 us a mode, the slices' tables 10 -> 3.4, counting 8.7 -> 4.8; builds of 50 000 to 1.6 M nonzeros 3 to
+// 10 % shorter).
+inline uint32_t tile_of(size_t M) { return M < (2u << 20) ? 256u : 1024u; }
 constexpr uint32_t kSliceBlock = 1024; // slices a block numbers
 
 struct Count4 {  // v[0]: slices, v[1..3]: fibers of levels 1..3
@@ -490,6 +494,7 @@ struct Totals {
 
 // The tables one mode's numbering fills (device memory).
 struct Numbers {
+  uint32_t per;          // nonzeros of a tile: tile_of()
   Count4* tile;          // [tiles + 1] counts per tile, then before each
   uint32_t* sStart;      // [S + 1] first nonzero of every slice
   uint32_t* fStart[3];   // [S + 1] fibers of each level before the slice
@@ -498,7 +503,7 @@ struct Numbers {
   uint32_t* fib[2];      // [S] as fib0, levels 2, 3
   uint32_t* csfOff;      // by CSF slice: its first place in the stream,
   uint32_t* csfStart;    //               its first sorted nonzero
-  unsigned long long* begun;  // [levels][tiles][16] bit p: a slice (level 0) or a fiber of the level begins at nonzero p
+  unsigned long long* begun;  // [levels][tiles][per / 64] bit p: a slice (level 0) or a fiber of the level begins at nonzero p
   uint8_t* inside;       // [runs + 1] bit l: the run begins inside a fiber of level l
   Count4* cutBlock;      // [blocks of runs + 1] cuts inside a fiber per kCutBlock runs, then before them
   Count4* cut;           // [runs + 1] cuts inside a fiber before each run
@@ -558,9 +563,9 @@ __global__ __launch_bounds__(256) void count_tiles_kernel(const Key* __restrict_
   Count4 c{{0, 0, 0, 0}};
   if (t < tiles) {
     unsigned long long mine[4] = {0, 0, 0, 0};  // lane k: the bits of the tile's chunk k
-    const size_t p0 = (size_t)t * kTile;
+    const size_t p0 = (size_t)t * n.per;
     Key last = p0 ? K[p0 - 1] : Key(0);
-    for (uint32_t j = 0; j < kTile; j += 64 * kFill) {
+    for (uint32_t j = 0; j < n.per; j += 64 * kFill) {
       Key key[kFill];
       uint32_t b[kFill];
       load_chunks(K, p0 + j, M, sp, lane, last, key, b);
@@ -575,14 +580,14 @@ __global__ __launch_bounds__(256) void count_tiles_kernel(const Key* __restrict_
           }
     }
     for (int l = 0; l < 4; ++l)
-      if (l <= sp.NF && lane < (int)(kTile / 64)) n.begun[((size_t)l * tiles + t) * (kTile / 64) + lane] = mine[l];
+      if (l <= sp.NF && lane < (int)(n.per / 64)) n.begun[((size_t)l * tiles + t) * (n.per / 64) + lane] = mine[l];
   }
   if (lane == 0) n.tile[t] = c;
 }
 
 // From the bits alone: 50 M nonzeros 87 (from the keys) -> 37 us.
 __global__ __launch_bounds__(256) void slice_tables_kernel(size_t M, Spec sp, uint32_t tiles, Numbers n) {
-  constexpr int kChunks = kTile / 64;
+  const int chunks = (int)(n.per / 64);
   const int lane = threadIdx.x & 63;
   const uint32_t t = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= tiles) return;
@@ -591,8 +596,8 @@ __global__ __launch_bounds__(256) void slice_tables_kernel(size_t M, Spec sp, ui
   unsigned long long mine[4] = {0, 0, 0, 0};
 #pragma unroll
   for (int l = 0; l < 4; ++l)
-    if (l <= sp.NF && lane < kChunks) mine[l] = n.begun[((size_t)l * tiles + t) * kChunks + lane];
-  for (int k = 0; k < kChunks; ++k) {
+    if (l <= sp.NF && lane < chunks) mine[l] = n.begun[((size_t)l * tiles + t) * chunks + lane];
+  for (int k = 0; k < chunks; ++k) {
     unsigned long long w[4];
 #pragma unroll
     for (int l = 0; l < 4; ++l)
@@ -600,7 +605,7 @@ __global__ __launch_bounds__(256) void slice_tables_kernel(size_t M, Spec sp, ui
              (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(mine[l] >> 32), k) << 32;
     if ((w[0] >> lane) & 1ull) {
       const uint32_t s = c.v[0] + (uint32_t)__popcll(w[0] & below);
-      n.sStart[s] = t * kTile + k * 64 + lane;
+      n.sStart[s] = t * n.per + k * 64 + lane;
 #pragma unroll
       for (int l = 1; l < 4; ++l)
         if (l <= sp.NF) n.fStart[l - 1][s] = c.v[l] + (uint32_t)__popcll(w[l] & below);
@@ -745,7 +750,7 @@ __global__ __launch_bounds__(256) void find_cuts_kernel(Spec sp, Numbers n, uint
       }
       const uint32_t p = n.csfStart[lo] + (uint32_t)(at - n.csfOff[lo]);
       for (int l = 1; l <= sp.NF; ++l)
-        in |= (uint32_t)(~n.begun[(size_t)l * tiles * (kTile / 64) + p / 64] >> (p % 64) & 1ull) << l;
+        in |= (uint32_t)(~n.begun[(size_t)l * tiles * (n.per / 64) + p / 64] >> (p % 64) & 1ull) << l;
     }
     if (r <= maxRuns) n.inside[r] = (uint8_t)in;
 #pragma unroll
@@ -857,9 +862,9 @@ __global__ __launch_bounds__(256) void fill_tiles_kernel(const Key* __restrict__
   const unsigned long long below = (1ull << lane) - 1ull;
   constexpr int leaf = N - 1, NF = N - 2;
   const uint32_t ls = __builtin_ctz(sp.L);  // runs are of 8, 16, 32 or 64 nonzeros
-  const size_t p0 = (size_t)t * kTile;
+  const size_t p0 = (size_t)t * n.per;
   Key last = p0 ? K[p0 - 1] : Key(0);
-  for (uint32_t j0 = 0; j0 < kTile; j0 += 64 * kFill) {
+  for (uint32_t j0 = 0; j0 < n.per; j0 += 64 * kFill) {
     Key key[kFill];
     uint32_t b[kFill], v[kFill], begun[kFill][NF], fib[kFill][NF], pos[kFill], cuts[kFill][NF], leafIdx[kFill];
     SliceInfo in[kFill];
@@ -955,11 +960,33 @@ __global__ __launch_bounds__(256) void fill_tiles_kernel(const Key* __restrict__
   }
 }
 
-// Per-slice entries of the CSL and CSF groups; a slice inside one run owns its output row.
+struct Sentinels {
+  uint64_t cslN0, cslNnz, cslRuns, csfN[HBCSF_MAX_ORDER], csfNnz, csfRuns;
+};
+
+__device__ __forceinline__ void put_sentinels(const Spec& sp, const OutArrays& o, const Sentinels& z) {
+  o.cslInd[0][z.cslN0] = 0;
+  o.cslPtr[z.cslN0] = (uint32_t)z.cslNnz;
+  o.cslRun[z.cslRuns] = (uint32_t)z.cslN0;
+  for (int l = 0; l < sp.N - 1; ++l) {
+    o.csfInd[l][z.csfN[l]] = 0;
+    o.csfPtr[l][z.csfN[l]] = (uint32_t)z.csfNnz;
+    o.csfRun[l][z.csfRuns] = (uint32_t)z.csfN[l];
+  }
+}
+__global__ void sentinel_kernel(Spec sp, OutArrays o, Sentinels z) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) put_sentinels(sp, o, z);
+}
+
+// Per-slice entries of the CSL and CSF groups; a slice inside one run owns its output row.  The arrays' sentinels are written
+// beside.  The shared slices are counted per block, 512 blocks: one add a wavefront to the same word, 8192 of them, was the
+// kernel's time (0.9 M slices 108 -> 21 us).
 template <typename Key>
 __global__ __launch_bounds__(256) void fill_slice_entries_kernel(const Key* __restrict__ K, uint32_t S, Spec sp, Numbers n,
-                                                                 OutArrays o, unsigned long long* cnt) {
-  unsigned long long shared = 0;
+                                                                 OutArrays o, Sentinels z, unsigned long long* cnt) {
+  __shared__ uint32_t wave[4];
+  if (blockIdx.x == 0 && threadIdx.x == 0) put_sentinels(sp, o, z);
+  uint32_t shared = 0;
   for (uint64_t s = (uint64_t)blockIdx.x * 256 + threadIdx.x; s < S; s += (uint64_t)gridDim.x * 256) {
     const SliceInfo in = n.info[s];
     if (in.grp == kCoo) continue;
@@ -974,23 +1001,11 @@ __global__ __launch_bounds__(256) void fill_slice_entries_kernel(const Key* __re
     if (own) atomicOr(&o.owned[root >> 5], 1u << (root & 31));
     else ++shared;
   }
-  wave_add(cnt + 1, shared);
-}
-
-struct Sentinels {
-  uint64_t cslN0, cslNnz, cslRuns, csfN[HBCSF_MAX_ORDER], csfNnz, csfRuns;
-};
-
-__global__ void sentinel_kernel(Spec sp, OutArrays o, Sentinels z) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  o.cslInd[0][z.cslN0] = 0;
-  o.cslPtr[z.cslN0] = (uint32_t)z.cslNnz;
-  o.cslRun[z.cslRuns] = (uint32_t)z.cslN0;
-  for (int l = 0; l < sp.N - 1; ++l) {
-    o.csfInd[l][z.csfN[l]] = 0;
-    o.csfPtr[l][z.csfN[l]] = (uint32_t)z.csfNnz;
-    o.csfRun[l][z.csfRuns] = (uint32_t)z.csfN[l];
-  }
+  for (int d = 32; d > 0; d >>= 1) shared += __shfl_down(shared, d);
+  if ((threadIdx.x & 63) == 0) wave[threadIdx.x >> 6] = shared;
+  __syncthreads();
+  const uint32_t all = wave[0] + wave[1] + wave[2] + wave[3];
+  if (threadIdx.x == 0 && all) atomicAdd(cnt + 1, (unsigned long long)all);
 }
 
 __global__ void zero_words_kernel(uint32_t* a, size_t na, uint32_t* b, size_t nb, uint32_t* c, size_t nc) {
@@ -1086,7 +1101,7 @@ hipError_t temp_bytes(size_t M, size_t maxWords, uint64_t slices, int totalBits,
   }
   if (e != hipSuccess) return e;
   need = b > need ? b : need;
-  const size_t tiles = M / kTile + 2;
+  const size_t tiles = M / tile_of(M) + 2;
   e = rocprim::exclusive_scan(nullptr, b, (Count4*)nullptr, (Count4*)nullptr, Count4{}, tiles, Count4Plus());
   if (e != hipSuccess) return e;
   need = b > need ? b : need;
@@ -1138,7 +1153,8 @@ void carve(Workspace& w, uint8_t* base, int order, size_t M, uint64_t mapBytes, 
   for (int i = 0; i < 2; ++i) w.C[i] = wide ? (Carried*)take((M + 1) * sizeof(Carried)) : nullptr;
   for (int i = 0; i < 2; ++i) w.K128[i] = wide ? (u128*)take((M + 1) * 16) : nullptr;
   const uint64_t tables = perFiber ? (uint64_t)M : slices;
-  w.n.tile = (Count4*)take((M / kTile + 2) * sizeof(Count4));
+  w.n.tile = (Count4*)take((M / tile_of(M) + 2) * sizeof(Count4));
+  w.n.per = tile_of(M);
   w.n.sStart = (uint32_t*)take((tables + 2) * 4);
   for (int l = 0; l < 3; ++l) w.n.fStart[l] = l < order - 2 && !perFiber ? (uint32_t*)take((tables + 2) * 4) : nullptr;
   w.n.block = (GroupCounts*)take((tables / kSliceBlock + 2) * sizeof(GroupCounts));
@@ -1165,7 +1181,7 @@ void carve(Workspace& w, uint8_t* base, int order, size_t M, uint64_t mapBytes, 
   w.seen = (uint8_t*)take(3 * mapBytes);
   if (w.ownSort) sort_scratch(M, take(sort_scratch(M, nullptr, &w.sort.s)), &w.sort.s);
   // between the sorts of two modes the third buffer pair of hbcsf_sort.h is free (at least 32 KB and 12 bytes a nonzero)
-  const uint64_t begunBytes = (uint64_t)(order - 1) * ((M + kTile - 1) / kTile) * (kTile / 8);
+  const uint64_t begunBytes = (uint64_t)(order - 1) * ((M + tile_of(M) - 1) / tile_of(M)) * (tile_of(M) / 8);
   w.n.begun = perFiber ? nullptr : w.ownSort ? (unsigned long long*)w.sort.s.K : (unsigned long long*)take(begunBytes);
   w.n.inside = perFiber ? nullptr : w.ownSort ? (uint8_t*)w.sort.s.K + up256(begunBytes) : take(M / L + 2);
   w.temp = take(tempBytes);
@@ -1353,7 +1369,7 @@ int sort_mode(size_t M, const Sorted<Key>& base, const ModeBuild& mb, bool isBas
 template <typename Key>
 int number_mode(size_t M, uint64_t slices, const Sorted<Key>& so, ModeBuild& mb, Workspace& w, hipStream_t st) {
   const Spec& sp = mb.sp;
-  const uint32_t tiles = (uint32_t)((M + kTile - 1) / kTile);
+  const uint32_t tiles = (uint32_t)((M + w.n.per - 1) / w.n.per);
   const uint32_t blocks = (uint32_t)((slices + kSliceBlock - 1) / kSliceBlock);
   const uint32_t maxRuns = (uint32_t)((M + sp.L - 1) / sp.L);
   const dim3 tileGrid(tiles / 4 + 1);
@@ -1528,19 +1544,6 @@ int build_mode_device(int N, const uint64_t* dims, size_t M, uint64_t slices, co
     hipLaunchKernelGGL(zero_words_kernel, dim3(grid_capped(mapWords + 2 * ownedWords)), dim3(256), 0, st, (uint32_t*)w.seen,
                        mapWords, o.owned, ownedWords, o.cooBits, ownedWords);
   }
-  if (M > 0 && sp.perFiber) {
-    hipLaunchKernelGGL(fill_nonzeros_kernel<Key>, dim3(grid_for(M)), dim3(256), 0, st, so.K, so.V, M, sp, tb, seg[0], seg[1],
-                       seg[2], o);
-    hipLaunchKernelGGL(fill_slices_kernel<Key>, dim3(grid_capped(mb.S)), dim3(256), 0, st, so.K, mb.S, sp, tb, o, mb.cnt);
-  } else if (M > 0) {
-    const uint32_t tiles = (uint32_t)((M + kTile - 1) / kTile);
-    const dim3 grid(tiles / 4 + 1);
-    if (N == 3) hipLaunchKernelGGL((fill_tiles_kernel<Key, 3>), grid, dim3(256), 0, st, so.K, so.V, M, sp, tiles, w.n, o);
-    else if (N == 4) hipLaunchKernelGGL((fill_tiles_kernel<Key, 4>), grid, dim3(256), 0, st, so.K, so.V, M, sp, tiles, w.n, o);
-    else hipLaunchKernelGGL((fill_tiles_kernel<Key, 5>), grid, dim3(256), 0, st, so.K, so.V, M, sp, tiles, w.n, o);
-    hipLaunchKernelGGL(fill_slice_entries_kernel<Key>, dim3(grid_capped(mb.S)), dim3(256), 0, st, so.K, (uint32_t)mb.S, sp,
-                       w.n, o, mb.cnt);
-  }
   Sentinels z{};
   z.cslN0 = out->g[kCsl].n[0];
   z.cslNnz = out->g[kCsl].nnz;
@@ -1548,7 +1551,21 @@ int build_mode_device(int N, const uint64_t* dims, size_t M, uint64_t slices, co
   for (int l = 0; l < N - 1; ++l) z.csfN[l] = out->g[kCsf].n[l];
   z.csfNnz = out->g[kCsf].nnz;
   z.csfRuns = out->g[kCsf].runs;
-  hipLaunchKernelGGL(sentinel_kernel, dim3(1), dim3(64), 0, st, sp, o, z);
+  if (M == 0 || sp.perFiber) hipLaunchKernelGGL(sentinel_kernel, dim3(1), dim3(64), 0, st, sp, o, z);
+  if (M > 0 && sp.perFiber) {
+    hipLaunchKernelGGL(fill_nonzeros_kernel<Key>, dim3(grid_for(M)), dim3(256), 0, st, so.K, so.V, M, sp, tb, seg[0], seg[1],
+                       seg[2], o);
+    hipLaunchKernelGGL(fill_slices_kernel<Key>, dim3(grid_capped(mb.S)), dim3(256), 0, st, so.K, mb.S, sp, tb, o, mb.cnt);
+  } else if (M > 0) {
+    const uint32_t tiles = (uint32_t)((M + w.n.per - 1) / w.n.per);
+    const dim3 grid(tiles / 4 + 1);
+    if (N == 3) hipLaunchKernelGGL((fill_tiles_kernel<Key, 3>), grid, dim3(256), 0, st, so.K, so.V, M, sp, tiles, w.n, o);
+    else if (N == 4) hipLaunchKernelGGL((fill_tiles_kernel<Key, 4>), grid, dim3(256), 0, st, so.K, so.V, M, sp, tiles, w.n, o);
+    else hipLaunchKernelGGL((fill_tiles_kernel<Key, 5>), grid, dim3(256), 0, st, so.K, so.V, M, sp, tiles, w.n, o);
+    const unsigned sliceBlocks = grid_capped(mb.S);
+    hipLaunchKernelGGL(fill_slice_entries_kernel<Key>, dim3(sliceBlocks < 512 ? sliceBlocks : 512), dim3(256), 0, st, so.K, (uint32_t)mb.S, sp,
+                       w.n, o, z, mb.cnt);
+  }
   {
     size_t tb_ = w.tempBytes;
     auto cit = rocprim::counting_iterator<size_t>(0);
