@@ -30,7 +30,7 @@ EXPORTS = (
     "hbcsf_strerror", "hbcsf_last_error",
     "hbcsf_als_workspace_bytes", "hbcsf_als_create", "hbcsf_als_iteration", "hbcsf_als_normalise", "hbcsf_als_run", "hbcsf_als_phase_ms", "hbcsf_als_free", "hbcsf_sym_pinv",
     "hbcsf_gram_workspace_bytes", "hbcsf_gram", "hbcsf_gram_noalloc",
-    "hbcsf_device_build_bytes", "hbcsf_build_format_device", "hbcsf_download", "hbcsf_relocate",
+    "hbcsf_device_build_bytes", "hbcsf_build_format_device", "hbcsf_build_format_device_pieces", "hbcsf_download", "hbcsf_relocate",
 )
 
 
