@@ -258,7 +258,8 @@ int hbcsf_device_build_bytes(int order, const uint64_t *dims, uint64_t nnz, cons
 /* As hbcsf_build_format, but inds[m] and vals are device pointers (read only), and the result is
  * resident: the handle can be passed to hbcsf_mttkrp at once; hbcsf_upload must not be called on
  * it.  device_arena / workspace: device memory, 256-byte aligned; the arena is kept by the caller
- * for the handle's lifetime.  Blocking: the host waits for a few counts per mode.  Errors as
+ * for the handle's lifetime.  Blocking: the host waits for a few counts per mode, and the workspace is the
+ * caller's again on return (after an error the arena too: nothing enqueued still writes to them).  Errors as
  * hbcsf_build_format, plus ENOMEM when the arena or workspace is too small, and EHIP. */
 int hbcsf_build_format_device(int order, const uint64_t *dims, uint64_t nnz,
                               const uint32_t *const *inds, const float *vals, const hbcsf_opts *opts,
@@ -266,9 +267,10 @@ int hbcsf_build_format_device(int order, const uint64_t *dims, uint64_t nnz,
                               uint64_t workspace_bytes, void *hip_stream, hbcsf_tensor **out);
 
 /* The same, with memory that is asked for as the sizes become known, so that nothing has to be sized for every pattern nor
- * moved afterwards: `allocate` is called once per mode and once for the words of state (hbcsf_device_bytes in all), on the
- * calling thread, and returns device memory of that many bytes, 256-byte aligned, which the caller keeps for the handle's
- * lifetime (also what was given before an error), or NULL: ENOMEM. */
+ * moved afterwards: `allocate` is called once per mode, and once for the words of state if any mode has them
+ * (hbcsf_device_bytes in all), on the calling thread, and returns device memory of that many bytes, 256-byte aligned, or
+ * NULL: ENOMEM.  The caller keeps that memory for the handle's lifetime; after an error, where there is no handle, all of it
+ * is the caller's again. */
 typedef void *(*hbcsf_allocate)(void *context, uint64_t bytes);
 int hbcsf_build_format_device_pieces(int order, const uint64_t *dims, uint64_t nnz, const uint32_t *const *inds,
                                      const float *vals, const hbcsf_opts *opts, hbcsf_allocate allocate, void *context,

@@ -1769,9 +1769,11 @@ int build_device(int order, const uint64_t* dims, uint64_t nnz, const uint32_t* 
     t->modes[m].reset(new (std::nothrow) ModeFormat);
     if (!t->modes[m]) return fail(HBCSF_ENOMEM, "out of host memory");
   }
+  WaitOnError wait(st);
   const int rb = maxBits > 64 ? build_all<u128>(order, dims, (size_t)nnz, inds, vals, o, totalBits, w, place, t.get(), st)
                               : build_all<uint64_t>(order, dims, (size_t)nnz, inds, vals, o, totalBits, w, place, t.get(), st);
   if (rb != HBCSF_OK) return rb;
+  wait.done();
   t->uploaded = true;
   *out = t.release();
   return HBCSF_OK;

@@ -63,6 +63,23 @@ int fail_hip(hipError_t e, const char* what);
 // (std::bad_alloc -> HBCSF_ENOMEM, anything else -> HBCSF_EINVAL with its text) and never throws itself.
 int fail_exception() noexcept;
 
+// Waits for the stream when a call ends early, by an error or an exception: the memory that was to be written is then the
+// caller's again, and what was enqueued must not reach it later.
+class WaitOnError {
+ public:
+  explicit WaitOnError(hipStream_t s) : s_(s) {}
+  WaitOnError(const WaitOnError&) = delete;
+  WaitOnError& operator=(const WaitOnError&) = delete;
+  ~WaitOnError() {
+    if (!done_) (void)hipStreamSynchronize(s_);
+  }
+  void done() { done_ = true; }   // nothing is left on the stream
+
+ private:
+  hipStream_t s_;
+  bool done_ = false;
+};
+
 // Bytes of the words of state (DefineArgs) of a mode with that many rows.
 uint64_t define_state_bytes(uint64_t rows);
 // Sets the sizes of the words of state and of the whole, once the formats' are known.
