@@ -135,7 +135,8 @@ int hbcsf_device_bytes(const hbcsf_tensor *t, uint64_t *bytes);
 
 /* Copies all modes' arrays into the caller's device arena (device, 256-byte aligned, at least
  * hbcsf_device_bytes bytes) on hip_stream (a hipStream_t, NULL = the default stream) and
- * waits for the copy.  The arena must stay valid while the handle is used for hbcsf_mttkrp. */
+ * waits for the copy.  The arena must stay valid while the handle is used for hbcsf_mttkrp.  After an
+ * error the arena is the caller's again, and a handle that was uploaded before goes on using that arena. */
 int hbcsf_upload(hbcsf_tensor *t, void *device_arena, uint64_t bytes, void *hip_stream);
 
 /* Mode-`mode` (0-based) MTTKRP, asynchronous on hip_stream.
@@ -278,7 +279,8 @@ int hbcsf_build_format_device_pieces(int order, const uint64_t *dims, uint64_t n
 
 /* Moves a resident handle's arrays into another device arena of at least hbcsf_device_bytes
  * (256-byte aligned, not overlapping the old one) and makes the handle use it, e.g. to release the
- * upper-bound arena a device build was given.  Blocking.  The old arena is the caller's again. */
+ * upper-bound arena a device build was given.  Blocking.  The old arena is the caller's again; after an
+ * error the new one is, and the handle goes on using the old one. */
 int hbcsf_relocate(hbcsf_tensor *t, void *new_arena, uint64_t bytes, void *hip_stream);
 
 /* Copies the device-resident arrays of a handle built by hbcsf_build_format_device to host

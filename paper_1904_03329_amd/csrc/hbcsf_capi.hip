@@ -70,16 +70,28 @@ void size_arena(hbcsf_tensor* t) {
   t->arenaBytes = t->formatBytes + states;
 }
 
-hipError_t place_states(hbcsf_tensor* t, uint8_t* at, hipStream_t s) {
-  uint8_t* next = at;
-  for (int m = 0; m < t->order; ++m) {
-    if (!t->modes[m]) continue;
-    t->modes[m]->state = next;
-    next += t->modes[m]->stateBytes;
-  }
-  const uint64_t vecs = (uint64_t)(next - at) / 16;
+hipError_t clear_states(const hbcsf_tensor* t, uint8_t* at, hipStream_t s) {
+  const uint64_t vecs = (t->arenaBytes - t->formatBytes) / 16;
   if (vecs == 0) return hipSuccess;
   return launch_zero_rows((float*)at, vecs, (uint32_t)(vecs < 256 * 1024 ? (vecs + 255) / 256 : 1024), s);
+}
+
+void use_states(hbcsf_tensor* t, uint8_t* at) {
+  for (int m = 0; m < t->order; ++m) {
+    if (!t->modes[m]) continue;
+    t->modes[m]->state = at;
+    at += t->modes[m]->stateBytes;
+  }
+}
+
+void use_arena(hbcsf_tensor* t, uint8_t* arena) {
+  uint8_t* at = arena;
+  for (int m = 0; m < t->order; ++m) {
+    if (!t->modes[m]) continue;
+    t->modes[m]->dev = at;
+    at += t->modes[m]->blobBytes;
+  }
+  use_states(t, at);
 }
 
 }  // namespace hbcsf
@@ -243,20 +255,22 @@ int hbcsf_upload(hbcsf_tensor* t, void* device_arena, uint64_t bytes, void* hip_
   int cu = 0;
   e = hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return fail_hip(e, "hipDeviceGetAttribute");
-  t->numCU = cu > 0 ? cu : 256;
-  t->device = dev;
+  WaitOnError wait(s);
   uint8_t* at = (uint8_t*)device_arena;
   for (int m = 0; m < nModes; ++m) {
-    ModeFormat& f = *t->modes[m];
+    const ModeFormat& f = *t->modes[m];
     e = hipMemcpyAsync(at, f.blob, f.blobBytes, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return fail_hip(e, "hipMemcpyAsync");
-    f.dev = at;
     at += f.blobBytes;
   }
-  e = place_states(t, at, s);
+  e = clear_states(t, at, s);
   if (e != hipSuccess) return fail_hip(e, "launch of the zero-fill kernel");
   e = hipStreamSynchronize(s);
   if (e != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
+  wait.done();
+  t->numCU = cu > 0 ? cu : 256;
+  t->device = dev;
+  use_arena(t, (uint8_t*)device_arena);
   t->uploaded = true;
   return HBCSF_OK;
 } HBCSF_CATCH_ALL

@@ -1703,7 +1703,8 @@ int build_all(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds
     uint8_t* states = nullptr;
     const int rp = place(t->arenaBytes - t->formatBytes, &states);
     if (rp != HBCSF_OK) return rp;
-    HIP_TRY(place_states(t, states, st), "launch of the zero-fill kernel");
+    HIP_TRY(clear_states(t, states, st), "launch of the zero-fill kernel");
+    use_states(t, states);
   }
   unsigned long long host[HBCSF_MAX_ORDER * kCounters + 1];
   HIP_TRY(hipMemcpyAsync(host, w.cnt, sizeof(host), hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
@@ -1837,21 +1838,17 @@ int hbcsf_relocate(hbcsf_tensor* t, void* new_arena, uint64_t bytes, void* hip_s
   if (bytes < t->arenaBytes) return fail(HBCSF_ENOMEM, "the new arena is smaller than hbcsf_device_bytes");
   if (((uintptr_t)new_arena & (kAlign - 1)) != 0) return fail(HBCSF_EINVAL, "device arena must be 256-byte aligned");
   hipStream_t st = (hipStream_t)hip_stream;
+  WaitOnError wait(st);
   uint8_t* at = (uint8_t*)new_arena;
   for (int m = 0; m < t->order; ++m) {
     if (!t->modes[m]) continue;
     HIP_TRY(hipMemcpyAsync(at, t->modes[m]->dev, t->modes[m]->blobBytes, hipMemcpyDeviceToDevice, st), "hipMemcpyAsync");
     at += t->modes[m]->blobBytes;
   }
+  HIP_TRY(clear_states(t, at, st), "launch of the zero-fill kernel");
   HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
-  HIP_TRY(place_states(t, at, st), "launch of the zero-fill kernel");
-  HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
-  at = (uint8_t*)new_arena;
-  for (int m = 0; m < t->order; ++m) {
-    if (!t->modes[m]) continue;
-    t->modes[m]->dev = at;
-    at += t->modes[m]->blobBytes;
-  }
+  wait.done();
+  use_arena(t, (uint8_t*)new_arena);
   return HBCSF_OK;
 } HBCSF_CATCH_ALL
 

@@ -84,8 +84,12 @@ class WaitOnError {
 uint64_t define_state_bytes(uint64_t rows);
 // Sets the sizes of the words of state and of the whole, once the formats' are known.
 void size_arena(hbcsf_tensor* t);
-// Says where the words of state lie (one mode's behind the other's) and clears them.
-hipError_t place_states(hbcsf_tensor* t, uint8_t* at, hipStream_t s);
+// Clears words of state at `at` (one mode's behind the other's), which the tensor does not use yet.
+hipError_t clear_states(const hbcsf_tensor* t, uint8_t* at, hipStream_t s);
+// Makes the tensor use them, or an arena that holds the formats, one mode's behind the other's, and then them: only once all of
+// that memory is written, so that a call which fails before leaves the tensor where it was.
+void use_states(hbcsf_tensor* t, uint8_t* at);
+void use_arena(hbcsf_tensor* t, uint8_t* arena);
 
 // hbcsf_mttkrp with ALS work in the same launch, for calls that take it (fp32).
 struct GuestArgs;

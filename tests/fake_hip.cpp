@@ -3,11 +3,13 @@
 // place of the runtime's functions of these names.
 #include <hip/hip_runtime_api.h>
 
+#include <cstdint>
 #include <cstring>
 
 namespace {
-long copies, waits, pending;
+long copies, waits, pending, into;
 long failCopy, failWait;          // the how-manieth fails; 0: none
+uintptr_t range[2];
 void fillProperties(hipDeviceProp_t* p) {
   std::memset(p, 0, sizeof *p);
   std::strcpy(p->gcnArchName, "gfx950");
@@ -26,7 +28,15 @@ void fake_start(long failCopy_, long failWait_) {
   failWait = failWait_;
 }
 // Launches and copies enqueued since the last wait.
-long fake_pending() { return pending; }
+long fake_pending() { return pending; }// Counts pointers into [from, until) that the launches from now on are given: in the first 96 bytes of their arguments 0, 1 and 3,
+// structures of pointers all of them (the launch that defines an MTTKRP's output itself).
+void fake_range(const void* from, const void* until) {
+  range[0] = (uintptr_t)from;
+  range[1] = (uintptr_t)until;
+  into = 0;
+}
+long fake_into() { return into; }
+
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
 hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_t* p, int) { fillProperties(p); return hipSuccess; }
@@ -54,8 +64,15 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
   *s = nullptr;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void*, dim3, dim3, void** args, size_t, hipStream_t) {
   ++pending;
+  if (range[1] > range[0])
+    for (int k : {0, 1, 3})
+      for (int w = 0; w < 12; ++w) {
+        uintptr_t p;
+        std::memcpy(&p, (const char*)args[k] + 8 * w, 8);
+        into += p >= range[0] && p < range[1];
+      }
   return hipSuccess;
 }
 

@@ -13,7 +13,7 @@ sys.path.insert(0, sys.argv[2])
 fake = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)   # found before the runtime that the library names
 import numpy as np
 from paper_1904_03329_amd import binding as B
-fake.fake_pending.restype = ctypes.c_long
+fake.fake_pending.restype = fake.fake_into.restype = ctypes.c_long
 def start(copy=0, wait=0):
     fake.fake_start(ctypes.c_long(copy), ctypes.c_long(wait))
 def memory(n):
@@ -104,4 +104,49 @@ for opts in ({}, dict(hybrid_granularity=1)):
                 break
             assert c == -5
         assert nth > 3
+""")
+
+
+def test_a_failed_upload_or_move_leaves_the_handle_where_it_was(run):
+    """Every copy and wait of a second upload and of a move fails once.  The handle then still reads the arena it had: a further
+    move copies that arena's arrays, and an MTTKRP launch is given pointers into it, of the words of state too, and none into the
+    memory of the call that failed."""
+    run("""
+h = B.build_format(dims, inds, vals)
+n = B.device_bytes(h)
+start()
+first = memory(n)
+B.upload(h, first.ctypes.data, n)
+arrays = first.copy()
+facs = [rng.uniform(size=(d, 32)).astype(np.float32) for d in dims]
+out = memory(4 * 32 * max(dims))
+def pointers(arena):
+    fake.fake_range(ctypes.c_void_p(arena.ctypes.data), ctypes.c_void_p(arena.ctypes.data + n))
+    B.mttkrp(h, 0, 32, [f.ctypes.data for f in facs], out.ctypes.data)
+    into = fake.fake_into()
+    fake.fake_range(None, None)
+    return into
+uses = pointers(first)
+assert uses > 10
+held = first
+for call in (B.upload, B.relocate):
+    for what in ("copy", "wait"):
+        for nth in range(1, 9):
+            other = memory(n)
+            start(**{what: nth})
+            c = code(lambda: call(h, other.ctypes.data, n))
+            assert fake.fake_pending() == 0
+            start()
+            if c == 0:
+                assert pointers(other) == uses and pointers(held) == 0
+                held = other
+                break
+            assert c == -5
+            assert pointers(held) == uses and pointers(other) == 0, (call, what, nth)
+            other[:] = 0xff
+            moved = memory(n)
+            B.relocate(h, moved.ctypes.data, n)
+            assert np.array_equal(moved, arrays), (call, what, nth)
+            held = moved
+        assert nth > 1
 """)
