@@ -86,7 +86,7 @@ struct DefineArgs {
   const uint32_t* ind[5];        // the COO group, by tree level
   const float* val;
   uint32_t rows;
-  uint32_t blocks;               // the launch's first blocks (a multiple of 8); 0: the rows were defined before the launch
+  uint32_t blocks;               // the launch's first blocks, a multiple of 8
   uint32_t* state;
   uint32_t claimed;
 };

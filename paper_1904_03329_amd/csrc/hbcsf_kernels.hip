@@ -390,9 +390,8 @@ struct DefinedHere {
   const DefineArgs& d;
   float* out;
 
-  // State of the row's word; where the rows were defined before the launch, one past all.
+  // State of the row's word.
   __device__ __forceinline__ uint32_t ask(uint32_t row) const {
-    if (d.state == nullptr) return ~0u;
     return __hip_atomic_load(d.state + (row >> 5), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 
@@ -1570,26 +1569,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(N == 3 ? 5 
 // The same with ALS work in the launch's first block (of 8, so that the others keep their XCDs).  The inverse takes 110
 // registers: where units of 256 nonzeros fill the chip, the order-3 kernels are held to the 96 that leave five wavefronts
 // per SIMD.
+// HERE: with the output definition in its first blocks too.  A launch after a definition of its own does without the code that asks
+// for rows, which costs 1 to 6 % of it (five iterations at rank 32, asking -> not asking: 8 M nonzeros of order 4 2870 -> 2782 us, 6 M of
+// order 5 3842 -> 3564).
 constexpr uint32_t kGuestBlocks = 8;
-template <int G, int N, int SS>
+template <int G, int N, int SS, bool HERE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(N == 3 && ((64 / G) << SS) == 256 ? 5 : 4)))
 void guest_csl_csf_kernel(const GroupArgs csl, const GroupArgs csf, uint32_t cslBlocks, const DefineArgs define,
                           const GuestArgs guest) {
   extern __shared__ uint32_t lds[];
   if (blockIdx.x < kGuestBlocks) {
-    if (define.state) stamp_begin(guest.stamp);
+    if (HERE) stamp_begin(guest.stamp);
     if (blockIdx.x == 0) guest_block<4 * G>(guest, lds);
     return;
   }
-  if (blockIdx.x < kGuestBlocks + define.blocks) {
+  const uint32_t defining = HERE ? define.blocks : 0u;
+  if (HERE && blockIdx.x < kGuestBlocks + defining) {
     define_block<G, N>(csf, define, blockIdx.x - kGuestBlocks);
     return;
   }
-  const DefinedHere<G> defined{define, csf.out};
-  const uint32_t first = kGuestBlocks + define.blocks;
-  const uint32_t block = blockIdx.x - first, blocks = gridDim.x - first;
-  if (block < cslBlocks) csl_group_body<G, N, SS, 4, false>(csl, block, cslBlocks, defined);
-  else csf_group_body<G, N, SS, 4, false, false>(csf, block - cslBlocks, blocks - cslBlocks, defined);
+  const uint32_t block = blockIdx.x - kGuestBlocks - defining, blocks = gridDim.x - kGuestBlocks - defining;
+  auto walk = [&](const auto& defined) {
+    if (block < cslBlocks) csl_group_body<G, N, SS, 4, false>(csl, block, cslBlocks, defined);
+    else csf_group_body<G, N, SS, 4, false, false>(csf, block - cslBlocks, blocks - cslBlocks, defined);
+  };
+  if constexpr (HERE) walk(DefinedHere<G>{define, csf.out});
+  else walk(DefinedBefore());
 }
 #endif
 
@@ -1683,7 +1688,7 @@ hipError_t launch_one(int kind, const GroupArgs& a, const GroupArgs* csl, const 
       if (lds < guest_lds_bytes<R>()) lds = guest_lds_bytes<R>();
       const uint32_t cslBlocks = (uint32_t)span_blocks(*csl, wpb);
       const DefineArgs here = define ? *define : DefineArgs{};
-      hipLaunchKernelGGL((guest_csl_csf_kernel<G, N, SS>),
+      hipLaunchKernelGGL((define ? guest_csl_csf_kernel<G, N, SS, true> : guest_csl_csf_kernel<G, N, SS, false>),
                          dim3(kGuestBlocks + here.blocks + cslBlocks + (uint32_t)span_blocks(a, wpb)), block, lds, s, *csl, a,
                          cslBlocks, here, *guest);
       return hipGetLastError();

@@ -92,3 +92,33 @@ def test_singular_matrix_beside_and_before(rank):
         error = np.abs(written[0].astype(np.float64) @ rows.T - want).max() / np.abs(want).max()
         print(f"condition on the range {w[-1] / w[1]:.1f}, largest error {error:.1e}", flush=True)
         assert ms[2] > 0 and error <= tol
+
+
+@pytest.mark.parametrize("rank", [8, 16, 32, 64])
+@pytest.mark.parametrize("dims, nnz", [((4000, 40, 30), 30_000), ((90, 60, 40, 20), 300_000), ((60, 50, 20, 13, 11), 40_000)])
+@pytest.mark.parametrize("equal", [False, True])
+def test_same_result_on_another_stream(rank, dims, nnz, equal):
+    """There the output is defined in a launch of its own and the launch that carries the inverse is the form that does not ask for
+    rows.  Both are held to the update of mode 0 in fp64 (as above: through the model, which two equal components leave
+    determined)."""
+    import torch
+
+    inds, vals, facs = _problem(dims, nnz, rank)
+    if equal:
+        for f in facs:
+            f[:, 1] = f[:, 0]
+    f64 = [f.astype(np.float64) for f in facs]
+    rows = f64[1]
+    for f in f64[2:]:
+        rows = (rows[:, None, :] * f[None, :, :]).reshape(-1, rank)
+    v = _v(facs, 0)
+    w = np.linalg.eigvalsh(v)
+    tol = 1e-6 * max(10.0, w[-1] / w[1 if equal else 0])
+    rows = rows[np.random.default_rng(1).choice(len(rows), 2000)] if len(rows) > 2000 else rows
+    want = cpd_als.mttkrp(dims, inds, vals, f64, 0) @ np.linalg.pinv(v) @ rows.T
+    for stream in (torch.cuda.current_stream(), torch.cuda.Stream()):
+        with torch.cuda.stream(stream):
+            written, _, ms, _ = _iterate(dims, inds, vals, facs, {}, False)
+        error = np.abs(written[0].astype(np.float64) @ rows.T - want).max() / np.abs(want).max()
+        print(f"stream {stream.cuda_stream}: condition {tol * 1e6:.1f}, largest error {error:.1e}", flush=True)
+        assert (ms[2] > 0) == equal and error <= tol
