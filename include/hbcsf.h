@@ -384,8 +384,8 @@ int hbcsf_als_run(hbcsf_als *a, float *const *factors, float *lambda, int max_it
 
 /* Device time of the last iteration, summed over the modes, in milliseconds: ms[0] MTTKRP,
  * ms[1] Gram kernel (0 when the product formed the Gram matrix), ms[2] R x R pseudo-inverse, ms[3]
- * product kernel with the R x R algebra before it.  Where the pseudo-inverse runs beside the MTTKRP, ms[2] is the
- * time from where the eigenvalue form begins, 0 if no update needed that. */
+ * product kernel with the R x R algebra before it.  Where the pseudo-inverse runs beside the MTTKRP, ms[2] is what
+ * the eigenvalue form takes beyond the MTTKRP (taken to end with its last blocks), 0 if no update needed that form. */
 int hbcsf_als_phase_ms(const hbcsf_als *a, float ms[4]);
 
 /* Host only (no device call): the pseudo-inverse the mode update applies (on the device) to the Hadamard product of

@@ -16,6 +16,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <memory>
@@ -829,7 +830,8 @@ struct hbcsf_als {
   // thread of each kernel as it begins: an event record between two kernels costs 5.6 us on the stream, as much as
   // many of the kernels).  Per mode: inverse begins, inverse ends, Gram or product begins, R x R part after the Gram
   // begins; one more at the iteration's end.  Where the inverse goes with the MTTKRP the first two are: MTTKRP begins,
-  // eigenvalue form begins (0: it was not needed).
+  // eigenvalue form begins (0: it was not needed); the last is when the MTTKRP's last blocks end
+  // (if after that, otherwise some time before).
   struct Report {
     double value[2];
     unsigned long long stamp[HBCSF_MAX_ORDER][4], end;
@@ -1224,7 +1226,8 @@ int hbcsf_als_phase_ms(const hbcsf_als* a, float ms[4]) try {
     const unsigned long long* at = a->report->stamp[n];
     const unsigned long long end = n + 1 < order ? a->report->stamp[n + 1][0] : a->report->end;
     if (a->hosted[n]) {
-      const unsigned long long mttkrpEnd = at[1] ? at[1] : at[2];
+      // (the eigenvalue form may begin long before the MTTKRP ends, and end before it too)
+      const unsigned long long mttkrpEnd = at[1] ? std::min(std::max(at[1], at[3]), at[2]) : at[2];
       add(ms[0], at[0], mttkrpEnd);
       add(ms[2], mttkrpEnd, at[2]);
     } else {

@@ -47,7 +47,9 @@ struct GuestArgs {
   float* p;                  // right-hand matrix of the product that follows
   double* vp;                // [rank][rank], where the eigenvalue form is put
   int* good;                 // receives 1 where the sweep succeeded, else 0
-  unsigned long long* stamp; // [2]: receives the time at which the MTTKRP's first kernel begins, and 0 (or the eigenvalue form)
+  unsigned long long* stamp; // [4]: receives in [0] the time at which the MTTKRP's first kernel begins, in [1] 0 or when the
+                             // eigenvalue form does; where the sweep fails while the last blocks are at work, in [3] when
+                             // those end
 };
 
 // Device pointers of one slice group of one mode, by tree level (0 = root .. order-1 = leaf).

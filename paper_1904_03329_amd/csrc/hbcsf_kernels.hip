@@ -1595,6 +1595,12 @@ void guest_csl_csf_kernel(const GroupArgs csl, const GroupArgs csf, uint32_t csl
   };
   if constexpr (HERE) walk(DefinedHere<G>{define, csf.out});
   else walk(DefinedBefore());
+  // Where the sweep has failed, the last blocks (a launch's very last may have no span) leave the time; who ends last stays.  (All
+  // updates together took 0.7 us each to write it to the host.  One whose sweep ends after them is not seen to fail here,
+  // but then the eigenvalue form's begin says as much.)
+  if (gridDim.x - blockIdx.x <= 64 && threadIdx.x == 0 &&
+      __hip_atomic_load(guest.good, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
+    guest.stamp[3] = wall_clock64();
 }
 #endif
 

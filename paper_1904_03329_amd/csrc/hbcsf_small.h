@@ -376,7 +376,7 @@ __device__ __forceinline__ void guest_block(const GuestArgs& a, uint32_t* lds) {
   const int tid = threadIdx.x;
   double x[4][4];
   bool done = pinv_sweep<R, 256>(a.small, a.n, *reinterpret_cast<SweepLds<R>*>(lds), x);
-  if (tid == 0) *a.good = done;
+  if (tid == 0) __hip_atomic_store(a.good, (int)done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // read beside, too
   const int i0 = tile_row(R, tid), j0 = tile_column(R, tid);
   if constexpr (guest_finishes(R)) {
     if (!done) {

@@ -61,3 +61,19 @@ def test_eigenvalue_form_is_inverse_time():
     assert np.linalg.matrix_rank(v) < rank
     beside, alone = (_phases(dims, inds, vals, facs, p) for p in (False, True))
     assert beside[2] > 0.5 * alone[2] and beside[2] > beside[0]
+
+
+@pytest.mark.parametrize("rank", [8, 16, 32])
+def test_mttkrp_keeps_its_time_beside_the_eigenvalue_form(rank):
+    """Two equal columns and four million nonzeros: up to rank 32 the eigenvalue form runs in the launch of an MTTKRP that takes
+    tens of microseconds.  That launch's time up to its last blocks is MTTKRP time, the same as without equal columns (the form
+    begins some microseconds into it: counted from there, most of the MTTKRP would be missing)."""
+    dims = (400, 300, 250)
+    rng, inds, vals = _tensor(dims, 4_000_000, 4)
+    facs = [rng.uniform(-1, 1, (d, rank)).astype(np.float32) for d in dims]
+    regular = _phases(dims, inds, vals, facs, False)
+    for f in facs:
+        f[:, 1] = f[:, 0]
+    equal = _phases(dims, inds, vals, facs, False)
+    assert regular[2] == 0 and equal[2] > 0
+    assert 0.7 * regular[0] < equal[0] < 1.5 * regular[0]
