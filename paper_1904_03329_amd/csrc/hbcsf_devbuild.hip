@@ -1043,9 +1043,9 @@ inline uint64_t up256(uint64_t v) { return (v + 255) / 256 * 256; }
 
 // Workspace carve-up for M nonzeros; `temp` is the rocPRIM scratch, sized by temp_bytes().
 struct Workspace {
-  uint64_t* K[3];        // 64-bit sort keys.  Up to 64 bits: [2] the common order, [0] one mode's order, [1] where a
-  uint32_t* V[3];        // blocked order or the per-fiber choice needs it; wide keys: [0], [1] a double buffer.  V: the
-                         // values (or places) riding along
+  uint64_t* K[3];        // 64-bit sort keys.  Up to 64 bits: [2] the common order, [0] one mode's order, [1] where the
+  uint32_t* V[3];        // per-fiber choice or a blocked order by rocPRIM's sort needs it; wide keys: [0], [1] a double
+                         // buffer.  V: the values (or places) riding along
   Carried* C[2];         // wide keys only: the other half + value, double buffered
   u128* K128[2];         // wide keys only: the common order, one mode's order
   Numbers n;             // numbering tables
@@ -1155,9 +1155,9 @@ void carve(Workspace& w, uint8_t* base, int order, size_t M, uint64_t mapBytes, 
     off += up256(bytes);
     return p;
   };
-  for (int i = 0; i < 3; ++i)
-    w.K[i] = (wide ? i < 2 : i != 1 || perFiber || blocked) ? (uint64_t*)take((M + 1) * 8) : nullptr;
-  for (int i = 0; i < 3; ++i) w.V[i] = wide || i != 1 || perFiber || blocked ? (uint32_t*)take((M + 1) * 4) : nullptr;
+  const bool second = perFiber || (blocked && !w.ownSort);   // K[1], V[1] of keys up to 64 bits
+  for (int i = 0; i < 3; ++i) w.K[i] = (wide ? i < 2 : i != 1 || second) ? (uint64_t*)take((M + 1) * 8) : nullptr;
+  for (int i = 0; i < 3; ++i) w.V[i] = wide || i != 1 || second ? (uint32_t*)take((M + 1) * 4) : nullptr;
   for (int i = 0; i < 2; ++i) w.C[i] = wide ? (Carried*)take((M + 1) * sizeof(Carried)) : nullptr;
   for (int i = 0; i < 2; ++i) w.K128[i] = wide ? (u128*)take((M + 1) * 16) : nullptr;
   const uint64_t tables = perFiber ? (uint64_t)M : slices;

@@ -150,3 +150,17 @@ for call in (B.upload, B.relocate):
             held = moved
         assert nth > 1
 """)
+
+
+def test_workspace_of_blocked_builds(run):
+    """Blocked orders of 64-bit keys are sorted in the pair sort's own buffers: no workspace for a fourth pair of 12 bytes a nonzero,
+    which only the per-fiber choice uses."""
+    run("""
+long, nnz = (12_000_000, 9_000_000, 100), 10_000_000   # as many slices as nonzeros, blocked or not
+def workspace(**opts):
+    return B.device_build_bytes(long, nnz, **opts)[1]
+start()
+assert workspace(mid_blocking=4) == workspace()
+both = workspace(mid_blocking=4, hybrid_granularity=1)
+assert both == workspace(hybrid_granularity=1) and both > workspace() + 12 * nnz
+""")
