@@ -53,6 +53,7 @@ struct Spec {
   uint32_t L, cooOn, cslOn, cooRowFlags;
   uint32_t byteLevels;  // bit l: level l's row map holds bytes, otherwise bits
   uint32_t marked;      // bit g: group g has row maps
+  uint32_t askLeaf;     // a leaf's row is looked up before it is marked
   uint32_t perFiber;  // hybrid_granularity = 1: heavy slices are split into a CSL piece and a CSF piece
   int blockBits, blockDrop;  // level-1 blocking: (index of level 1 >> blockDrop) stands above the root
 };
@@ -899,10 +900,9 @@ __global__ __launch_bounds__(256) void fill_tiles_kernel(const Key* __restrict__
       leafIdx[q] = (uint32_t)((uint64_t)(key[q] >> sp.shift[leaf]) & sp.mask[leaf]);
       marked[q] = 0;
       if (p < M) {
-        // (is the leaf's row marked already?  nearly always, and looked up with the other loads that costs less than to mark
-        // it: modes of order 4, 50 M nonzeros, 617 and 669 -> 565 and 612 us; a stale answer only marks it once more)
+        // is the leaf's row marked already?  (a stale answer only marks it once more)
         const uint32_t grp = in[q].grp;
-        if (((sp.byteLevels >> leaf) & 1u) && ((sp.marked >> grp) & 1u)) {
+        if (sp.askLeaf && ((sp.marked >> grp) & 1u)) {
           const uint32_t* map = grp == kCsf ? o.seen[kCsf][leaf] : grp == kCsl ? o.seen[kCsl][leaf] : o.seen[kCoo][leaf];
           marked[q] = reinterpret_cast<const uint8_t*>(map)[leafIdx[q]];
         }
@@ -1071,6 +1071,14 @@ constexpr int kCounters = 32;
 
 // Is the group chosen per fiber?  (needs the CSL group)
 bool per_fiber(const hbcsf_opts& o) { return o.hybrid_granularity == 1 && (o.group_mask == 0 || (o.group_mask & 2u)); }
+
+// Is a leaf's row looked up before it is marked?  With a few nonzeros a row it is nearly always marked already, and the load, which
+// goes with the others, costs less than the store; with fewer it only adds to it.  Whole builds, marked at once -> looked up, us:
+// 50 M nonzeros of order 4 over 1 M leaf rows 7824 -> 7666, 20 M over 1 M 2976 -> 2948, 20 M over 4 M 4306 -> 4216, 10 M over 2 M 3396
+// -> 3402; but 8 M over 4 M 2003 -> 2114 (order 4 2545 -> 2660), 4 M over 4 M 1333 -> 1404 and 1619 -> 1766 (uniform leaf indices,
+// but for the 50 M).
+constexpr uint64_t kAskLeafPer = 4;   // nonzeros a row
+bool asks_leaf(size_t M, uint64_t rows) { return rows <= kByteRows && M >= kAskLeafPer * rows; }
 
 // Bytes of a mode's row map, and of one group's row maps of all modes.
 uint64_t row_map_bytes(uint64_t rows) { return up256(rows <= kByteRows ? rows : (rows + 7) / 8); }
@@ -1679,6 +1687,7 @@ int build_all(int N, const uint64_t* dims, size_t M, const uint32_t* const* inds
       sp.upTo[l] = upTo;
       if (dims[lv[l]] <= kByteRows) sp.byteLevels |= 1u << l;
     }
+    sp.askLeaf = asks_leaf(M, dims[lv[N - 1]]) ? 1u : 0u;
     if (sp.blockBits) sp.upTo[0] |= ((u128)((1ull << sp.blockBits) - 1)) << (bk.shift[lv[1]] + sp.blockDrop);
     mb.cnt = w.cnt + (size_t)mode * kCounters;
     out->order = N;

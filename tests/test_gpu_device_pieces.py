@@ -86,3 +86,26 @@ def test_memory_that_is_not_given():
     with pytest.raises(MemoryError):
         build(fails)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("nnz", [39_999, 40_000, 40_001])
+@pytest.mark.parametrize("dims", [(10_000, 9_000, 30), (10_000, 9_000, 40, 30)])
+def test_rows_that_are_looked_up_before_they_are_marked(dims, nnz):
+    """From four nonzeros per leaf row on; mode 1's leaf is the first mode.  Its three groups have row maps, and their distinct rows
+    are the host builder's."""
+    rng = np.random.default_rng(nnz)
+    inds = np.stack([rng.integers(0, d, 2 * nnz) for d in dims])
+    inds[1, ::2] %= 100   # half of it in a hundred slices, the rest thin
+    flat = np.unique(np.ravel_multi_index(inds, dims))
+    rng.shuffle(flat)
+    inds = [x.astype(np.uint32) for x in np.unravel_index(flat[:nnz], dims)]
+    vals = rng.uniform(-1, 1, nnz).astype(np.float32)
+    host = HbcsfTensor(dims, inds, vals)
+    assert host.stats(1)["level_mode"][len(dims) - 1] == 0 and all(host.stats(1)["group_nnz"])
+    dev = HbcsfTensor.from_device_coo(dims, *_on_device(inds, vals))
+    for mode in range(len(dims)):
+        a, b = dict(host.stats(mode)), dict(dev.stats(mode))
+        a.pop("build_seconds"), b.pop("build_seconds")
+        assert a == b
+    host.close()
+    dev.close()
