@@ -308,10 +308,23 @@ bool long_parts(const hbcsf_tensor* t, const ModeFormat& f, int G, uint32_t lshi
 // 423 (rank 8 273 -> 278), 50 M 2435 -> 2485; order 5 on 1.5 M 182 -> 172, 8 M 766 -> 775.  And no more words of 32 rows than
 // the first blocks have wavefronts, 16 MiB at most: the zeros go through the L2 8 bytes a lane, and who comes early waits for
 // them (modes of 300 000 and 100 000 rows, rank 32 on 0.3 M 73 -> 77, rank 128 on 30 000 102 -> 114).
+// Those wavefronts come before the ones that walk the nonzeros.  That is no loss
+//  - while they are few, up to 9 / 16 of what the chip holds of this kernel, 101 376 rows at order 3 and 82 944 at 4 and 5 (two modes of
+//    65 001 rows, rank 32, indices by Zipf's law of 1.2: 0.3 M 38.4 -> 32.7, 1 M 62.2 -> 56.2),
+//  - with many nonzeros a row to make up for it (131 001 rows: 2 M 94.3 -> 91.7, 3.5 M 132.8 -> 130.9),
+//  - at order 3 where half of the rows or more are stored by their slices and need no zeros (uniform indices, 131 001 rows: 0.6 M
+//    72.7 -> 63.8, 1 M 94.8 -> 88.7; by Zipf's law, where they are not, 0.3 M 40.5 -> 43.9, 1 M 63.6 -> 65.5; order 4, uniform,
+//    rank 8 on 0.3 M 58 -> 68),
+//  - where all find room at once and write 8 MiB at most (131 001 rows, rank 8: 0.3 M 34.4 -> 33.4, but 0.6 M 39.3 -> 41.9), or
+//    where few of the rows are added to (110 001 rows, rank 32: 0.1 M 31.1 -> 29.6, but 0.2 M 34.5 -> 37.8).
 constexpr uint64_t kDefineBlocksPerCU = 4;   // (with one the words are late: 5 M 180 -> 190 us)
-bool defines_here(const hbcsf_tensor* t, const ModeFormat& f, uint64_t nnz, uint64_t rowBytes) {
-  const uint64_t cus = (uint64_t)t->numCU;
-  return f.stateBytes > 0 && f.rows <= 32 * 4 * kDefineBlocksPerCU * cus && f.rows * rowBytes <= (16ull << 20) && nnz > 0 &&
+bool defines_here(const hbcsf_tensor* t, const ModeFormat& f, uint64_t nnz, uint64_t rowBytes, int NG, uint32_t lshift) {
+  const uint64_t cus = (uint64_t)t->numCU, all = t->nnz;
+  const uint64_t room = (t->order == 3 ? 22 : 18) * cus;   // wavefronts
+  const uint64_t words = (f.rows + 31) / 32, unit = (uint64_t)NG << part_shift(all, NG, lshift, t->numCU);
+  const bool inTime = 16 * words <= 9 * room || all >= 15 * f.rows || (t->order == 3 && 2 * f.stats.owned_rows >= f.rows) ||
+                      (words + (all + unit - 1) / unit <= room && (f.rows * rowBytes <= (8ull << 20) || all <= f.rows));
+  return inTime && f.stateBytes > 0 && f.rows <= 32 * 4 * kDefineBlocksPerCU * cus && f.rows * rowBytes <= (16ull << 20) && nnz > 0 &&
          (nnz <= 8192 * cus || (t->order == 3 && nnz * rowBytes <= (4ull << 20) * cus));
 }
 
@@ -390,7 +403,7 @@ int mttkrp_any(const hbcsf_tensor* t, int mode, int rank, int elem, const float*
   //    mode's words of state serve
   std::unique_lock<std::mutex> turn;
   DefineArgs here{};
-  const bool oneLaunch = defines_here(t, f, sparseNnz, rowBytes) && t->fuseCoo == 2 && t->opts.hybrid_granularity == 0 &&
+  const bool oneLaunch = defines_here(t, f, sparseNnz, rowBytes, NG, lshift) && t->fuseCoo == 2 && t->opts.hybrid_granularity == 0 &&
                          f.blockBits == 0 && t->kernelMask == 15u && !es && !dense && !longParts && !wide && !t->persistent &&
                          take_turn(t, mode, s, &turn, &here.claimed);
   if (oneLaunch) {

@@ -115,6 +115,35 @@ def test_where_the_output_is_defined_before(oracle):
         ht.close()
 
 
+@pytest.mark.parametrize("rows, used, nnz, rank, uses", [   # per compute unit; a wavefront for 32 rows, of 22 there is room for
+    (396, 150, 3800, 32, True), (397, 150, 3800, 32, False),          # words on 9 / 16 of them
+    (512, 200, 7680, 16, True), (512, 200, 7670, 16, False),          # 15 nonzeros a row
+    (512, 320, 3800, 32, True), (512, 290, 3800, 32, False),          # half of the rows stored by their slices
+    (512, 200, 760, 16, True), (512, 200, 776, 16, False),            # 16 wavefronts of words, units of 128 nonzeros for the others
+    (512, 200, 380, 32, True), (512, 200, 388, 32, False),            # units of 64
+    (430, 200, 430, 32, True), (430, 200, 434, 32, False)])           # an output of more than 8 MiB: a nonzero a row at most
+def test_long_modes(oracle, rows, used, nnz, rank, uses):
+    """`used` rows have nonzeros, in pairs, so that no slice has a single one."""
+    import torch
+
+    rng = np.random.default_rng(nnz)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rows, nnz = rows * cus, nnz * cus
+    dims = (rows, 60, 40)
+    fiber = rng.choice(used * cus * 30, nnz // 2, replace=False)
+    inds = [np.concatenate([x, x]).astype(np.uint32) for x in (fiber // 30, fiber % 30)]
+    inds.append(np.repeat(np.arange(2, dtype=np.uint32), nnz // 2))
+    vals = rng.uniform(-1, 1, nnz).astype(np.float32)
+    facs = [rng.uniform(0, 1, (d, rank)).astype(np.float32) for d in dims]
+    ht = HbcsfTensor(dims, inds, vals).to_device()
+    got = ht.mttkrp(0, [torch.from_numpy(f).cuda() for f in facs])
+    GU.assert_close(got.cpu().numpy(), oracle.mttkrp(dims, inds, vals, facs, 0))
+    print(rows, nnz, rank, "owned", ht.stats(0)["owned_rows"], flush=True)
+    assert sum(ht.stats(0)["group_nnz"][1:]) == nnz
+    assert (_state(ht, 0) > 0).all() if uses else not _state(ht, 0).any()
+    ht.close()
+
+
 def test_threads_share_the_stream(oracle):
     """Calls of one mode from several threads on the null stream, each into its own output."""
     import torch
