@@ -1569,38 +1569,54 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(N == 3 ? 5 
 // The same with ALS work in the launch's first block (of 8, so that the others keep their XCDs).  The inverse takes 110
 // registers: where units of 256 nonzeros fill the chip, the order-3 kernels are held to the 96 that leave five wavefronts
 // per SIMD.
-// HERE: with the output definition in its first blocks too.  A launch after a definition of its own does without the code that asks
-// for rows, which costs 1 to 6 % of it (five iterations at rank 32, asking -> not asking: 8 M nonzeros of order 4 2870 -> 2782 us, 6 M of
-// order 5 3842 -> 3564).
+// Two forms: with the output definition in the next blocks, and after one in a launch of its own, without the code that asks for
+// rows, which costs 1 to 6 % of a launch (five iterations at rank 32, asking -> not asking: 8 M nonzeros of order 4 2870 -> 2782 us,
+// 6 M of order 5 3842 -> 3564).
 constexpr uint32_t kGuestBlocks = 8;
-template <int G, int N, int SS, bool HERE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(N == 3 && ((64 / G) << SS) == 256 ? 5 : 4)))
-void guest_csl_csf_kernel(const GroupArgs csl, const GroupArgs csf, uint32_t cslBlocks, const DefineArgs define,
-                          const GuestArgs guest) {
+constexpr bool guest_held(int G, int N, int SS) { return N == 3 && ((64 / G) << SS) == 256; }
+
+// A block behind those of the guest and of the output definition, `first` of them.
+template <int G, int N, int SS, typename Defined>
+__device__ __forceinline__ void walk_beside_guest(const GroupArgs& csl, const GroupArgs& csf, uint32_t cslBlocks, uint32_t first,
+                                                  const Defined& defined, const GuestArgs& guest) {
+  const uint32_t block = blockIdx.x - first, blocks = gridDim.x - first;
+  if (block < cslBlocks) csl_group_body<G, N, SS, 4, false>(csl, block, cslBlocks, defined);
+  else csf_group_body<G, N, SS, 4, false, false>(csf, block - cslBlocks, blocks - cslBlocks, defined);
+  // Where the sweep has failed, the last blocks (a launch's very last may have no span) leave the time; who ends last stays.  (All
+  // updates together took 0.7 us each to write it to the host.  One whose sweep ends after them is not seen to fail here,
+  // but then the eigenvalue form's begin says as much.)  The lane is counted: see thread_number().
+  if (gridDim.x - blockIdx.x <= 64 && __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) == 0 &&
+      __hip_atomic_load(guest.good, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
+    guest.stamp[3] = wall_clock64();
+}
+
+template <int G, int N, int SS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(guest_held(G, N, SS) ? 5 : 4)))
+void guest_csl_csf_kernel(const GroupArgs csl, const GroupArgs csf, uint32_t cslBlocks, const GuestArgs guest) {
   extern __shared__ uint32_t lds[];
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (blockIdx.x < kGuestBlocks) {
-    if (HERE) stamp_begin(guest.stamp);
-    if (blockIdx.x == 0) guest_block<4 * G>(guest, lds);
+    if (blockIdx.x == 0) guest_block<4 * G, guest_held(G, N, SS)>(guest, lds, wave);
     return;
   }
-  const uint32_t defining = HERE ? define.blocks : 0u;
-  if (HERE && blockIdx.x < kGuestBlocks + defining) {
+  walk_beside_guest<G, N, SS>(csl, csf, cslBlocks, kGuestBlocks, DefinedBefore(), guest);
+}
+
+template <int G, int N, int SS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(guest_held(G, N, SS) ? 5 : 4)))
+void guest_define_csl_csf_kernel(const GroupArgs csl, const GroupArgs csf, uint32_t cslBlocks, const DefineArgs define,
+                                 const GuestArgs guest) {
+  extern __shared__ uint32_t lds[];
+  if (blockIdx.x < kGuestBlocks) {
+    stamp_begin(guest.stamp);
+    if (blockIdx.x == 0) guest_block<4 * G, false>(guest, lds, 0);
+    return;
+  }
+  if (blockIdx.x < kGuestBlocks + define.blocks) {
     define_block<G, N>(csf, define, blockIdx.x - kGuestBlocks);
     return;
   }
-  const uint32_t block = blockIdx.x - kGuestBlocks - defining, blocks = gridDim.x - kGuestBlocks - defining;
-  auto walk = [&](const auto& defined) {
-    if (block < cslBlocks) csl_group_body<G, N, SS, 4, false>(csl, block, cslBlocks, defined);
-    else csf_group_body<G, N, SS, 4, false, false>(csf, block - cslBlocks, blocks - cslBlocks, defined);
-  };
-  if constexpr (HERE) walk(DefinedHere<G>{define, csf.out});
-  else walk(DefinedBefore());
-  // Where the sweep has failed, the last blocks (a launch's very last may have no span) leave the time; who ends last stays.  (All
-  // updates together took 0.7 us each to write it to the host.  One whose sweep ends after them is not seen to fail here,
-  // but then the eigenvalue form's begin says as much.)
-  if (gridDim.x - blockIdx.x <= 64 && threadIdx.x == 0 &&
-      __hip_atomic_load(guest.good, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
-    guest.stamp[3] = wall_clock64();
+  walk_beside_guest<G, N, SS>(csl, csf, cslBlocks, kGuestBlocks + define.blocks, DefinedHere<G>{define, csf.out}, guest);
 }
 #endif
 
@@ -1693,10 +1709,11 @@ hipError_t launch_one(int kind, const GroupArgs& a, const GroupArgs* csl, const 
       if (!csl || block.x != 256) return hipErrorInvalidValue;
       if (lds < guest_lds_bytes<R>()) lds = guest_lds_bytes<R>();
       const uint32_t cslBlocks = (uint32_t)span_blocks(*csl, wpb);
-      const DefineArgs here = define ? *define : DefineArgs{};
-      hipLaunchKernelGGL((define ? guest_csl_csf_kernel<G, N, SS, true> : guest_csl_csf_kernel<G, N, SS, false>),
-                         dim3(kGuestBlocks + here.blocks + cslBlocks + (uint32_t)span_blocks(a, wpb)), block, lds, s, *csl, a,
-                         cslBlocks, here, *guest);
+      const uint32_t blocks = kGuestBlocks + cslBlocks + (uint32_t)span_blocks(a, wpb);
+      if (define)
+        hipLaunchKernelGGL((guest_define_csl_csf_kernel<G, N, SS>), dim3(blocks + define->blocks), block, lds, s, *csl, a, cslBlocks,
+                           *define, *guest);
+      else hipLaunchKernelGGL((guest_csl_csf_kernel<G, N, SS>), dim3(blocks), block, lds, s, *csl, a, cslBlocks, *guest);
       return hipGetLastError();
     }
 #endif

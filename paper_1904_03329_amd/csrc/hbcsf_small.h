@@ -52,6 +52,15 @@ constexpr bool tiles_inside(int R) {
 static_assert(tiles_inside(8) && tiles_inside(16) && tiles_inside(32) && tiles_inside(64) && tiles_inside(128),
               "every thread's tile lies in the matrix");
 
+// The thread's number in its block; COUNTED: made of its wavefront's, `wave` (uniform), and its lane's.  Held from a kernel's
+// beginning, as threadIdx is, it goes to memory and back in every wavefront of an MTTKRP that carries a guest and is held to 96
+// registers (rank 16 on 5 M nonzeros, five iterations 835 -> 903 us); in other kernels the inverse is 1 us faster with threadIdx.
+template <bool COUNTED>
+__device__ __forceinline__ int thread_number(uint32_t wave) {
+  if constexpr (COUNTED) return (int)(wave * 64u + __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)));
+  else return threadIdx.x;
+}
+
 // 1 / x for a normal positive x: the hardware's estimate and two Newton steps (relative error near 2^-53).
 __device__ __forceinline__ double reciprocal(double x) {
   double r = __builtin_amdgcn_rcp(x);
@@ -74,7 +83,7 @@ __device__ __forceinline__ double reciprocal_root(double x) {
 // every thread reads the 4 + 4 entries its tile needs.  The chain of R steps is latency: the next pivot is formed from
 // the published row by every thread, so that its reciprocal is under way while the tiles are updated (rank 32: 25 us in
 // the first form, one entry per thread and a division in the chain).
-// All U threads of the block call; x: the thread's tile of -V^-1.  False (for every thread) where a pivot is not safely
+// All U threads of the block call (COUNTED, wave: thread_number()); x: the thread's tile of -V^-1.  False (for every thread) where a pivot is not safely
 // positive: the eigenvalue form has to be taken.
 template <int R>
 struct SweepLds {
@@ -84,11 +93,11 @@ struct SweepLds {
   int good;
 };
 
-template <int R, int U>
-__device__ __forceinline__ bool pinv_sweep(const SmallState& st, int n, SweepLds<R>& l, double (&x)[4][4]) {
+template <int R, int U, bool COUNTED = false>
+__device__ __forceinline__ bool pinv_sweep(const SmallState& st, int n, SweepLds<R>& l, double (&x)[4][4], uint32_t wave = 0) {
   constexpr int T = small_threads(R), W = R / 4;
   static_assert(U >= T, "a thread per tile");
-  const int tid = threadIdx.x;
+  const int tid = thread_number<COUNTED>(wave);
   const bool owns = tid < W * W;
   const int i0 = tile_row(R, tid), j0 = tile_column(R, tid);
 #pragma unroll
@@ -194,13 +203,14 @@ struct JacobiLds {
   int2 pair[R / 2];
 };
 
-template <int R, int T = pinv_threads(R)>
-__device__ void jacobi_pinv(const SmallState& st, int n, JacobiLds<R, T>& lds, double* __restrict__ qGlobal, double* __restrict__ out) {
+template <int R, int T = pinv_threads(R), bool COUNTED = false>
+__device__ void jacobi_pinv(const SmallState& st, int n, JacobiLds<R, T>& lds, double* __restrict__ qGlobal, double* __restrict__ out,
+                            uint32_t wave = 0) {
   constexpr int H = R / 2, S = T / H;   // S row pairs of a, or rows of q, at a time
   constexpr bool kVectors = JacobiLds<R, T>::kVectors;
   // blocks of a and rows of q a thread takes, and rows of q it holds at a time (with all eight at rank 128 it would spill)
   constexpr int KA = (H + S - 1) / S, KQ = (R + S - 1) / S, KB = kVectors ? KQ : 4;
-  const int tid = threadIdx.x;
+  const int tid = thread_number<COUNTED>(wave);
   const int l = tid % H, first = tid / H;
   double* a = lds.a;
   double* q = kVectors ? lds.q : qGlobal;
@@ -366,23 +376,23 @@ constexpr bool guest_finishes(int rank) { return rank <= 32; }
 
 template <int R>
 constexpr uint32_t guest_lds_bytes() {
-  if constexpr (guest_finishes(R)) return sizeof(SweepLds<R>) > sizeof(JacobiLds<R, 256>) ? sizeof(SweepLds<R>) : sizeof(JacobiLds<R, 256>);
-  else return sizeof(SweepLds<R>);
+  constexpr uint32_t sweep = sizeof(SweepLds<R>), form = guest_finishes(R) ? sizeof(JacobiLds<R, 256>) : 0;
+  return sweep > form ? sweep : form;
 }
 
-template <int R>
-__device__ __forceinline__ void guest_block(const GuestArgs& a, uint32_t* lds) {
+template <int R, bool COUNTED>
+__device__ __forceinline__ void guest_block(const GuestArgs& a, uint32_t* lds, uint32_t wave) {
   static_assert(R <= 64, "one block of 256 threads inverts V");
-  const int tid = threadIdx.x;
+  const int tid = thread_number<COUNTED>(wave);
   double x[4][4];
-  bool done = pinv_sweep<R, 256>(a.small, a.n, *reinterpret_cast<SweepLds<R>*>(lds), x);
+  bool done = pinv_sweep<R, 256, COUNTED>(a.small, a.n, *reinterpret_cast<SweepLds<R>*>(lds), x, wave);
   if (tid == 0) __hip_atomic_store(a.good, (int)done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // read beside, too
   const int i0 = tile_row(R, tid), j0 = tile_column(R, tid);
   if constexpr (guest_finishes(R)) {
     if (!done) {
       if (tid == 0) a.stamp[1] = wall_clock64();
       __syncthreads();   // the sweep's part of the LDS is read no more
-      jacobi_pinv<R, 256>(a.small, a.n, *reinterpret_cast<JacobiLds<R, 256>*>(lds), nullptr, a.vp);
+      jacobi_pinv<R, 256, COUNTED>(a.small, a.n, *reinterpret_cast<JacobiLds<R, 256>*>(lds), nullptr, a.vp, wave);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
