@@ -500,7 +500,8 @@ constexpr int entry_threads(int R) { return R * R < 1024 ? R * R : 1024; }      
 // overwrites it).  A pivot of the sweep that is not safely positive sends the whole workgroup to the eigenvalue form.
 // resetScale: after the product the stored factor is the unnormalised one, so its column scale becomes 1.
 // hosted: null, or the outcome of the sweep that ran beside the MTTKRP: where that was good, all is done, and where it was
-// not only the eigenvalue form is left (ranks that guest_finishes() leaves to this).  stamp: when it begins and ends (nothing where all is done).
+// not only the eigenvalue form is left (ranks that guest_finishes() leaves to this).  stamp: when it begins and ends
+// (nothing where all is done).
 template <int R>
 __global__ __launch_bounds__(pinv_threads(R)) void small_pinv_kernel(SmallState st, int n, double* __restrict__ vp,
                                                                       float* __restrict__ p, double* __restrict__ jq,

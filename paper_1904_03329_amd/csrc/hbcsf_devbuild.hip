@@ -11,9 +11,9 @@
 // under that level's mask (a pass that rewrote the keys as (root, ..., leaf) first took 0.23 ms of 50 M nonzeros).
 // Keys of 64 bits are sorted by hbcsf_sort.h, wider ones and tensors of 2^30 nonzeros and more by rocPRIM.
 //
-// Numbering.  No array is kept per nonzero but a bit a level.  A wavefront takes 1024 (or 256) sorted nonzeros, 64 at a time; "a slice /
-// a fiber begins here" are ballots, kept as bits for the kernels that need no more of the keys, so what it needs to number
-// them is the count before its tile (one scan over the tiles).
+// Numbering.  No array is kept per nonzero but a bit a level.  A wavefront takes 1024 (or 256) sorted nonzeros, 64 at a
+// time; "a slice / a fiber begins here" are ballots, kept as bits for the kernels that need no more of the keys, so what
+// it needs to number them is the count before its tile (one scan over the tiles).
 // Slices get their group, their place in it and the fibers before them by a scan over slices; fbr-split adds a segment
 // start only where a run begins inside a fiber, which is looked up once per run (a search over the slices, a scan over
 // the runs), so a segment's number is the fibers before it plus the cuts before it.  The sorted keys are read twice
@@ -452,9 +452,9 @@ __global__ void fill_slices_kernel(const Key* K, size_t S, Spec sp, Tables t, Ou
 
 // ---- numbering without per-nonzero arrays ----
 // Sorted nonzeros a wavefront numbers, 256 at a time.  Below 2 M there are fewer tiles of 1024 than the chip holds wavefronts,
-// and the four steps of a tile, each a chain of dependent loads, are the kernels' time (50 000 nonzeros of order 4, tiles of
-// 1024 -> 256: filling 27 -> 11 us a mode, the slices' tables 10 -> 3.4, counting 8.7 -> 4.8; builds of 50 000 to 1.6 M nonzeros 3 to
-// 10 % shorter).
+// and the four steps of a tile, each a chain of dependent loads, are the kernels' time (50 000 nonzeros of order 4, tiles
+// of 1024 -> 256: filling 27 -> 11 us a mode, the slices' tables 10 -> 3.4, counting 8.7 -> 4.8; builds of 50 000 to 1.6 M
+// nonzeros 3 to 10 % shorter).
 inline uint32_t tile_of(size_t M) { return M < (2u << 20) ? 256u : 1024u; }
 constexpr uint32_t kSliceBlock = 1024; // slices a block numbers
 
@@ -1579,8 +1579,8 @@ int build_mode_device(int N, const uint64_t* dims, size_t M, uint64_t slices, co
     else if (N == 4) hipLaunchKernelGGL((fill_tiles_kernel<Key, 4>), grid, dim3(256), 0, st, so.K, so.V, M, sp, tiles, w.n, o);
     else hipLaunchKernelGGL((fill_tiles_kernel<Key, 5>), grid, dim3(256), 0, st, so.K, so.V, M, sp, tiles, w.n, o);
     const unsigned sliceBlocks = grid_capped(mb.S);
-    hipLaunchKernelGGL(fill_slice_entries_kernel<Key>, dim3(sliceBlocks < 512 ? sliceBlocks : 512), dim3(256), 0, st, so.K, (uint32_t)mb.S, sp,
-                       w.n, o, z, mb.cnt);
+    hipLaunchKernelGGL(fill_slice_entries_kernel<Key>, dim3(sliceBlocks < 512 ? sliceBlocks : 512), dim3(256), 0, st, so.K,
+                       (uint32_t)mb.S, sp, w.n, o, z, mb.cnt);
   }
   {
     size_t tb_ = w.tempBytes;
@@ -1600,7 +1600,8 @@ int build_mode_device(int N, const uint64_t* dims, size_t M, uint64_t slices, co
   count(o.owned, ownedWords, 4);
   for (int g = 0; g < 3; ++g)
     for (int l = 1; l < N; ++l)
-      if ((sp.marked >> g) & 1u) count(o.seen[g][l], (size_t)(row_map_bytes(dims[out->levelMode[l]]) / 4), 8 + g * HBCSF_MAX_ORDER + l);
+      if ((sp.marked >> g) & 1u)
+        count(o.seen[g][l], (size_t)(row_map_bytes(dims[out->levelMode[l]]) / 4), 8 + g * HBCSF_MAX_ORDER + l);
   size_t most = 0;
   for (int k = 0; k < which; ++k) most = bc.words[k] > most ? bc.words[k] : most;
   const unsigned bx = grid_capped((most + 15) / 16);

@@ -1553,8 +1553,8 @@ __global__ __launch_bounds__(256) void csl_csf_kernel(const GroupArgs csl, const
 
 // The same with the output definition in its first blocks.
 template <int G, int N, int SS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(N == 3 ? 5 : N == 4 ? 4 : 3))) void define_csl_csf_kernel(const GroupArgs csl, const GroupArgs csf, uint32_t cslBlocks,
-                                                             const DefineArgs define) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(N == 3 ? 5 : N == 4 ? 4 : 3)))
+void define_csl_csf_kernel(const GroupArgs csl, const GroupArgs csf, uint32_t cslBlocks, const DefineArgs define) {
   if (blockIdx.x < define.blocks) {
     define_block<G, N>(csf, define, blockIdx.x);
     return;

@@ -1,7 +1,9 @@
 // Stable radix sort of (64-bit key, 32-bit value) pairs on chosen bits of the key, for the device builder: the common order
 // straight from the COO arrays, and any number of further orders of it whose digits are counted in the same reading.
 //
-// What bounds a pass is memory: 12 bytes read and 12 written per pair, the writes in short runs.  So:
+// A pass follows the one-sweep scheme (A. Adinets and D. Merrill, "Onesweep: A Faster Least Significant Digit Radix Sort for GPUs",
+// 2022) with the decoupled look-back of D. Merrill and M. Garland ("Single-pass Parallel Prefix Scan with Decoupled Look-back",
+// 2016).  What bounds it is memory: 12 bytes read and 12 written per pair, the writes in short runs.  So:
 //  - a pass is one launch: a block ranks a tile of 8192 pairs, learns from the tiles before it where its digits' pairs
 //    go (each tile publishes its counts, then the sum up to it: a reader adds counts backwards until it meets a sum), and
 //    writes them from LDS in the order of the digits, in runs of 32 on average;
@@ -365,13 +367,15 @@ class Sorter {
   SortPasses passes;   // all of them; filled before count()
   SortScratch s{};
 
-  hipError_t count(const IndPtrs& inds, const float* vals, size_t n, int N, const BaseKey& bk, unsigned long long* bad, hipStream_t st) {
+  hipError_t count(const IndPtrs& inds, const float* vals, size_t n, int N, const BaseKey& bk, unsigned long long* bad,
+                   hipStream_t st) {
     coo_ = SortIn{nullptr, nullptr, inds, vals, bk, N};
     n_ = (uint32_t)n;
     const int copyBits = passes.n <= 16 ? 2 : 1;  // 64 KB of LDS at most
     const size_t lds = ((size_t)passes.n * kSortDigits * 4) << copyBits;
     const uint32_t blocks = count_blocks(n);
-    hipLaunchKernelGGL(sort_count_kernel, dim3(blocks), dim3(512), lds, st, inds, n_, N, bk, passes, s, sort_tiles(n), copyBits, bad);
+    hipLaunchKernelGGL(sort_count_kernel, dim3(blocks), dim3(512), lds, st, inds, n_, N, bk, passes, s, sort_tiles(n), copyBits,
+                       bad);
     hipLaunchKernelGGL(sort_start_kernel, dim3((unsigned)passes.n), dim3(1024), 0, st, s, blocks);
     return hipGetLastError();
   }
