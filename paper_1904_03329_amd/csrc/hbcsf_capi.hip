@@ -320,12 +320,14 @@ bool long_parts(const hbcsf_tensor* t, const ModeFormat& f, int G, uint32_t lshi
 constexpr uint64_t kDefineBlocksPerCU = 4;   // (with one the words are late: 5 M 180 -> 190 us)
 bool defines_here(const hbcsf_tensor* t, const ModeFormat& f, uint64_t nnz, uint64_t rowBytes, int NG, uint32_t lshift) {
   const uint64_t cus = (uint64_t)t->numCU, all = t->nnz;
+  if (f.stateBytes == 0 || nnz == 0 || f.rows > 32 * 4 * kDefineBlocksPerCU * cus || f.rows * rowBytes > (16ull << 20)) return false;
+  if (nnz > 8192 * cus && (t->order != 3 || nnz * rowBytes > (4ull << 20) * cus)) return false;
   const uint64_t room = (t->order == 3 ? 22 : 18) * cus;   // wavefronts
-  const uint64_t words = (f.rows + 31) / 32, unit = (uint64_t)NG << part_shift(all, NG, lshift, t->numCU);
-  const bool inTime = 16 * words <= 9 * room || all >= 15 * f.rows || (t->order == 3 && 2 * f.stats.owned_rows >= f.rows) ||
-                      (words + (all + unit - 1) / unit <= room && (f.rows * rowBytes <= (8ull << 20) || all <= f.rows));
-  return inTime && f.stateBytes > 0 && f.rows <= 32 * 4 * kDefineBlocksPerCU * cus && f.rows * rowBytes <= (16ull << 20) && nnz > 0 &&
-         (nnz <= 8192 * cus || (t->order == 3 && nnz * rowBytes <= (4ull << 20) * cus));
+  const uint64_t words = (f.rows + 31) / 32;
+  if (16 * words <= 9 * room || all >= 15 * f.rows) return true;
+  if (t->order == 3 && 2 * f.stats.owned_rows >= f.rows) return true;
+  const uint64_t unit = (uint64_t)NG << part_shift(all, NG, lshift, t->numCU);
+  return words + (all + unit - 1) / unit <= room && (f.rows * rowBytes <= (8ull << 20) || all <= f.rows);
 }
 
 // Takes the turn of the mode's words of state for a call on stream s, where that is the stream they serve
