@@ -1575,31 +1575,31 @@ void define_csl_csf_kernel(const GroupArgs csl, const GroupArgs csf, uint32_t cs
 constexpr uint32_t kGuestBlocks = 8;
 constexpr bool guest_held(int G, int N, int SS) { return N == 3 && ((64 / G) << SS) == 256; }
 
-// A block behind those of the guest and of the output definition, `first` of them.
-template <int G, int N, int SS, typename Defined>
-__device__ __forceinline__ void walk_beside_guest(const GroupArgs& csl, const GroupArgs& csf, uint32_t cslBlocks, uint32_t first,
-                                                  const Defined& defined, const GuestArgs& guest) {
-  const uint32_t block = blockIdx.x - first, blocks = gridDim.x - first;
-  if (block < cslBlocks) csl_group_body<G, N, SS, 4, false>(csl, block, cslBlocks, defined);
-  else csf_group_body<G, N, SS, 4, false, false>(csf, block - cslBlocks, blocks - cslBlocks, defined);
-  // Where the sweep has failed, the last blocks (a launch's very last may have no span) leave the time; who ends last stays.  (All
-  // updates together took 0.7 us each to write it to the host.  One whose sweep ends after them is not seen to fail here,
-  // but then the eigenvalue form's begin says as much.)  The lane is counted: see thread_number().
-  if (gridDim.x - blockIdx.x <= 64 && __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) == 0 &&
+// Where the sweep has failed, the last blocks (a launch's very last may have no span) leave the time; who ends last stays.  (All
+// updates together took 0.7 us each to write it to the host.  One whose sweep ends after them is not seen to fail here,
+// but then the eigenvalue form's begin says as much.  The lane is counted: see thread_number().)
+__device__ __forceinline__ void stamp_end(const GuestArgs& guest) {
+  if (gridDim.x - blockIdx.x <= 64 && thread_number<true>(0) == 0 &&
       __hip_atomic_load(guest.good, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
     guest.stamp[3] = wall_clock64();
 }
 
+// (The two kernels share no function around the groups': inlined in two steps, the groups' blockDim is a load that every wavefront
+// begins with by waiting for it, 1 % of the launch.)
 template <int G, int N, int SS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(guest_held(G, N, SS) ? 5 : 4)))
 void guest_csl_csf_kernel(const GroupArgs csl, const GroupArgs csf, uint32_t cslBlocks, const GuestArgs guest) {
   extern __shared__ uint32_t lds[];
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr bool kCounted = guest_held(G, N, SS);
+  const uint32_t wave = kCounted ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0u;
   if (blockIdx.x < kGuestBlocks) {
-    if (blockIdx.x == 0) guest_block<4 * G, guest_held(G, N, SS)>(guest, lds, wave);
+    if (blockIdx.x == 0) guest_block<4 * G, kCounted>(guest, lds, wave);
     return;
   }
-  walk_beside_guest<G, N, SS>(csl, csf, cslBlocks, kGuestBlocks, DefinedBefore(), guest);
+  const uint32_t block = blockIdx.x - kGuestBlocks, blocks = gridDim.x - kGuestBlocks;
+  if (block < cslBlocks) csl_group_body<G, N, SS, 4, false>(csl, block, cslBlocks);
+  else csf_group_body<G, N, SS, 4, false, false>(csf, block - cslBlocks, blocks - cslBlocks);
+  stamp_end(guest);
 }
 
 template <int G, int N, int SS>
@@ -1616,7 +1616,12 @@ void guest_define_csl_csf_kernel(const GroupArgs csl, const GroupArgs csf, uint3
     define_block<G, N>(csf, define, blockIdx.x - kGuestBlocks);
     return;
   }
-  walk_beside_guest<G, N, SS>(csl, csf, cslBlocks, kGuestBlocks + define.blocks, DefinedHere<G>{define, csf.out}, guest);
+  const DefinedHere<G> defined{define, csf.out};
+  const uint32_t first = kGuestBlocks + define.blocks;
+  const uint32_t block = blockIdx.x - first, blocks = gridDim.x - first;
+  if (block < cslBlocks) csl_group_body<G, N, SS, 4, false>(csl, block, cslBlocks, defined);
+  else csf_group_body<G, N, SS, 4, false, false>(csf, block - cslBlocks, blocks - cslBlocks, defined);
+  stamp_end(guest);
 }
 #endif
 
