@@ -307,7 +307,9 @@ bool long_parts(const hbcsf_tensor* t, const ModeFormat& f, int G, uint32_t lshi
 // 4 M 155 -> 147, 8 M 260 -> 255 (fp64 4 M 254 -> 249, 8 M 441 -> 445); order 4 on 0.3 M 57 -> 45, 1.5 M 130 -> 120, 8 M 422 ->
 // 423 (rank 8 273 -> 278), 50 M 2435 -> 2485; order 5 on 1.5 M 182 -> 172, 8 M 766 -> 775.  And no more words of 32 rows than
 // the first blocks have wavefronts, 16 MiB at most: the zeros go through the L2 8 bytes a lane, and who comes early waits for
-// them (modes of 300 000 and 100 000 rows, rank 32 on 0.3 M 73 -> 77, rank 128 on 30 000 102 -> 114).
+// them (modes of 300 000 and 100 000 rows, rank 32 on 0.3 M 73 -> 77, rank 128 on 30 000 102 -> 114).  (Figures without a law
+// are of skewed indices; uniform ones gain as much: order 3 on 0.3 M, ranks 8 / 32 / 128, 36.6 -> 27.5, 41.8 -> 31.0, 117 -> 92.5,
+// by Zipf's law of 1.2 31.6 -> 25.5, 35.9 -> 26.2, 80.3 -> 56.9.)
 // Those wavefronts come before the ones that walk the nonzeros.  That is no loss
 //  - while they are few, up to 9 / 16 of what the chip holds of this kernel, 101 376 rows at order 3 and 82 944 at 4 and 5 (two modes of
 //    65 001 rows, rank 32, indices by Zipf's law of 1.2: 0.3 M 38.4 -> 32.7, 1 M 62.2 -> 56.2),

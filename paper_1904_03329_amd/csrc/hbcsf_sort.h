@@ -36,9 +36,9 @@ struct BaseKey {
 };
 
 // A tile is 512 threads with 16 pairs each: 74 KB of LDS, two blocks on a compute unit, so that one ranks while the other waits
-// for memory.  Below 1 M nonzeros tiles of 4 pairs a thread, which fill the chip sooner: a whole build of order 3 / 4, short ->
-// long tiles, 50 000 nonzeros 621 -> 712 / 811 -> 950 us, 0.4 M 737 -> 783 / 939 -> 1027, 0.8 M 825 -> 832 / 1060 -> 1078, 1.6 M
-// 984 -> 926 / 1274 -> 1211.
+// for memory.  Below 1 M nonzeros tiles of 4 pairs a thread, which fill the chip sooner: a whole build of order 3 / 4 (indices by
+// Zipf's law of 1.2, of 1.3 to 0.8), short -> long tiles, 50 000 nonzeros 621 -> 712 / 811 -> 950 us, 0.4 M 737 -> 783 / 939 ->
+// 1027, 0.8 M 825 -> 832 / 1060 -> 1078, 1.6 M 984 -> 926 / 1274 -> 1211.
 constexpr int kSortThreads = 512, kSortWaves = kSortThreads / 64, kSortLong = 16, kSortShort = 4;
 constexpr size_t kSortLongMin = 1u << 20;
 constexpr int kSortDigits = 256;       // digits of at most 8 bits
